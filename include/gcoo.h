@@ -83,7 +83,8 @@ int32_t gcoo_default_p(int64_t m, int64_t k, int64_t nnz, int64_t N);
 /*
  * Device bytes a gcoo_from_csr() / gcoo_from_dense() call needs in dev_buf for an m x k matrix
  * with nnz stored entries and group height p: the five arrays of Section 3.1 (Table 1:
- * 3*nnz + 2*g elements, plus one sentinel), the kernel-private schedules derived from them (the run
+ * 3*nnz + 2*g elements, plus one sentinel), the entries in row order (2*nnz + m elements), the kernel-private
+ * schedules derived from them (the run
  * schedule of the register kernel, at most 3*nnz + 2048*g + 128 words; where gcoo_set_share_policy()
  * asks for it the share schedule of the workgroup-shared kernel) and the scratch space the
  * conversion kernels use; for p > 64 also a second copy of the matrix regrouped at 32 rows with its
@@ -209,7 +210,9 @@ int gcoo_spdm(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
 int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                       float* C_dev, int64_t ldc, void* stream, int variant);
 
-/* Variant gcoo_spdm() would pick for this matrix and these operand shapes (one of GCOO_VARIANT_* > 0). */
+/* Variant gcoo_spdm() would pick for this matrix and these operand shapes (one of GCOO_VARIANT_* > 0).  GCOO_VARIANT_AUTO
+ * has a kernel more than there are variants to ask for: one that works row by row, which takes short rows and small and
+ * narrow products; for such a call the answer is the variant that would serve it without that kernel. */
 int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                    const float* C_dev, int64_t ldc);
 

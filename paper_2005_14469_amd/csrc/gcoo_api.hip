@@ -80,6 +80,7 @@ int static_scratch(unsigned char** out)
 // Carve-up of the caller's device buffer.  Offsets depend on (m, nnz, g) only.
 struct Layout {
     size_t values, rows, cols, gIdxes, nnzPerGroup;        // the five arrays of the format
+    size_t row_start, row_cols, row_vals;                  // the entries in row order (p <= 64; taller groups: in the inner handle)
     size_t sched_hdr, sched;                               // run schedule of the register kernel
     size_t order;                                          // groups by falling size, then those sizes (matrices of few groups)
     size_t share_ucols, share_ucount, share_hdr, share_blocks, share_sbase, share_alloc;   // share schedule (may be empty)
@@ -227,6 +228,10 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.values = take(n4);
     L.rows = take(n4);
     L.cols = take(n4);
+    const bool rows = p <= gcoo::kSchedMaxP;
+    L.row_start = take(rows ? (size_t)(m + 1) * 4 : 0);
+    L.row_cols = take(rows ? n4 : 0);
+    L.row_vals = take(rows ? n4 : 0);
     L.sched_hdr = take((size_t)g * nw * gcoo::kMaxRun * sizeof(gcoo::SchedClass));
     L.sched = take((size_t)gcoo::sched_words(nnz, g, nw) * 4);
     L.order = take(g <= gcoo::kOrderMaxGroups && p <= gcoo::kSchedMaxP ? (size_t)g * 8 : 0);
@@ -309,6 +314,10 @@ struct gcoo_matrix {
     int32_t* nnzPerGroup() const { return reinterpret_cast<int32_t*>(base + L.nnzPerGroup); }
     gcoo::SchedClass* sched_hdr() const { return reinterpret_cast<gcoo::SchedClass*>(base + L.sched_hdr); }
     uint32_t* sched() const { return reinterpret_cast<uint32_t*>(base + L.sched); }
+    int32_t* row_start() const { return reinterpret_cast<int32_t*>(base + L.row_start); }
+    int32_t* row_cols() const { return reinterpret_cast<int32_t*>(base + L.row_cols); }
+    float* row_vals() const { return reinterpret_cast<float*>(base + L.row_vals); }
+    bool has_rows() const { return p <= gcoo::kSchedMaxP; }
     bool has_order() const { return has_sched && g > 0 && g <= gcoo::kOrderMaxGroups; }
     int32_t* order() const { return reinterpret_cast<int32_t*>(base + L.order); }
     unsigned long long* stats() const { return reinterpret_cast<unsigned long long*>(base + L.counter); }
@@ -526,9 +535,9 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
 
     // Algorithm 1, step 1: group index and counts straight from row_ptr (also writes the sentinel).
     {
-        const unsigned blocks = (unsigned)((g + 1 + 255) / 256) + 1u;     // the last one computes the statistics
+        const unsigned blocks = (unsigned)(((h->has_rows() ? m : g) + 1 + 255) / 256) + 1u;     // the last one computes the statistics
         gcoo::group_index_from_row_ptr<<<dim3(blocks), dim3(256), 0, s>>>(d_row_ptr, m, p, g, (int32_t)nnz, h->gIdxes(), h->nnzPerGroup(),
-                                                                         stats, h->bad_col());
+                                                                         stats, h->bad_col(), h->has_rows() ? h->row_start() : nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "group_index_from_row_ptr"); }
     }
@@ -552,14 +561,15 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             float* dv = to_final ? fin_v : tmp_v;
             const int shift = high_first ? 8 * (1 - pass) : 8 * pass;
             if (pass == 0)
-                gcoo::sort_groups_by_col_digit<true, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
-                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col());
+                gcoo::sort_groups_by_col_digit<gcoo::kSortFirst, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
+                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col(),
+                    h->has_rows() ? h->row_cols() : nullptr, h->row_vals());
             else if (high_first)
-                gcoo::sort_groups_by_col_digit<false, gcoo::kSortBucketWaves><<<dim3((unsigned)(g * buckets)), dim3(gcoo::kSortBucketWaves * gcoo::kWave), 0, s>>>(
-                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, (int32_t)buckets, (int32_t)k, h->bad_col());
+                gcoo::sort_groups_by_col_digit<gcoo::kSortNext, gcoo::kSortBucketWaves><<<dim3((unsigned)(g * buckets)), dim3(gcoo::kSortBucketWaves * gcoo::kWave), 0, s>>>(
+                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, (int32_t)buckets, (int32_t)k, h->bad_col(), nullptr, nullptr);
             else
-                gcoo::sort_groups_by_col_digit<false, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
-                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col());
+                gcoo::sort_groups_by_col_digit<gcoo::kSortNext, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
+                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col(), nullptr, nullptr);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) { delete h; return hip_fail(e, "sort_groups_by_col_digit"); }
             src_c = dc; src_r = dr; src_v = dv;
@@ -700,6 +710,13 @@ int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "fill_dense_blocks"); }
     }
+    if (g > 0 && h->has_rows()) {
+        gcoo::sort_groups_by_col_digit<gcoo::kSortByRow, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
+            h->gIdxes(), nullptr, m, p, h->cols(), h->rows(), h->values(), h->row_cols(), h->row_start(), h->row_vals(), 0, 0, (int32_t)k,
+            nullptr, nullptr, nullptr);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) { delete h; return hip_fail(e, "sort_groups_by_col_digit"); }
+    }
     rc = launch_build_schedule(h, h->base + h->L.persistent, s);
     if (rc != GCOO_OK) { delete h; return rc; }
     if (wants_inner(p)) {
@@ -770,6 +787,21 @@ bool share_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
     return sh.al4 && (uint64_t)A->k * (uint64_t)ldb * 4u <= 0xffffffffull - 4096u;
 }
 
+bool rows_possible(const gcoo_matrix* A, int64_t ldb, int64_t N)
+{
+    return A->has_rows() && N >= 4 && A->k >= 1 && (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
+}
+
+// Where the automatic choice is the row-by-row kernel.  It moves 4 x nnz x N bytes through the vector caches; the kernels
+// that work on groups move less the more entries share a column of a group, but need thousands of wave-sized items.  Measured
+// on uniform random matrices: level at about 40 entries per row (n = 4000: 1.2 %, n = 8000: 0.45 %; 30 where rows of B do not
+// start at 128-byte lines), and at well above a hundred where the groups' items fill less than half of the 2048 wave slots.
+bool rows_preferred(const gcoo_matrix* A, int64_t N)
+{
+    if (A->nnz <= 28 * A->m) return true;
+    return A->g * ((N + 255) / 256) <= 1024 && A->nnz <= 128 * A->m;
+}
+
 int check_spdm_args(const gcoo_matrix* A, const float* B, int64_t ldb, int64_t N, const float* C, int64_t ldc)
 {
     if (!A || N < 0 || ldb < N || ldc < N || N > INT32_MAX) return GCOO_EINVAL;
@@ -802,7 +834,8 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     int rc = check_spdm_args(A, B_dev, ldb, N, C_dev, ldc);
     if (rc != GCOO_OK) return rc;
     if (variant < GCOO_VARIANT_AUTO || variant > GCOO_VARIANT_SHARE) return GCOO_EINVAL;
-    if (variant == GCOO_VARIANT_AUTO) variant = gcoo_spdm_pick(A, B_dev, ldb, N, C_dev, ldc);
+    const bool automatic = variant == GCOO_VARIANT_AUTO;
+    if (automatic) variant = gcoo_spdm_pick(A, B_dev, ldb, N, C_dev, ldc);
     if (A->m == 0 || N == 0) return GCOO_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -817,6 +850,12 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         return GCOO_OK;
     }
     if (A->inner) A = A->inner;        // the schedules of the kernels below belong to the regrouped copy
+    if (automatic && rows_possible(A, ldb, N) && rows_preferred(A, N)) {
+        gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc};
+        hipError_t e = gcoo::launch_spdm_rows(a, s);
+        if (e != hipSuccess) return hip_fail(e, "spdm_rows launch");
+        return GCOO_OK;
+    }
     if (variant == GCOO_VARIANT_SHARE) {
         const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
         if (!A->has_share || !share_operands_ok(A, sh, ldb)) return GCOO_EINVAL;

@@ -49,13 +49,13 @@ __global__ __launch_bounds__(256) void group_stats_from_row_ptr(const int32_t* _
 // Algorithm 1, step 1 for a CSR input.  CSR is row-major, so the entries of group q are the
 // contiguous CSR range [row_ptr[q*p], row_ptr[min((q+1)*p, m)]): the count and the prefix sum
 // are two reads of row_ptr.  One thread per group; thread g also writes the sentinel.
-// 256 threads per workgroup, ceil((g+1)/256) workgroups; with `stats` given, one workgroup more,
-// which computes the statistics above in the same launch.
+// 256 threads per workgroup, ceil((g+1)/256) workgroups (ceil((m+1)/256) with `row_start` given, which receives the
+// clamped offsets of all rows); with `stats` given, one workgroup more, which computes the statistics above in the same launch.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void group_index_from_row_ptr(const int32_t* __restrict__ row_ptr, int64_t m, int32_t p, int64_t g,
                                                                  int32_t nnz, int32_t* __restrict__ gIdxes,
                                                                  int32_t* __restrict__ nnzPerGroup, unsigned long long* __restrict__ stats,
-                                                                 uint32_t* __restrict__ bad_col)
+                                                                 uint32_t* __restrict__ bad_col, int32_t* __restrict__ row_start)
 {
     if (stats && blockIdx.x == gridDim.x - 1) {                   // the whole workgroup
         if (threadIdx.x == 0) *bad_col = 0u;                      // set by the sort that follows if it meets a column out of range
@@ -63,10 +63,11 @@ __global__ __launch_bounds__(256) void group_index_from_row_ptr(const int32_t* _
         return;
     }
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q > g) return;
     // Offsets are clamped to [0, nnz]: with a device input whose row_ptr does not match the nnz
     // the buffer was laid out for, every later kernel still stays inside the arrays.
     auto at = [&](int64_t r) { const int32_t v = row_ptr[r]; return v < 0 ? 0 : (v > nnz ? nnz : v); };
+    if (row_start && q <= m) row_start[q] = at(q);
+    if (q > g) return;
     int64_t r0 = q * p;
     if (r0 > m) r0 = m;
     const int32_t b = at(r0);
@@ -115,6 +116,9 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool is_active)
 // into [0, kcols) and *bad_col is set if one was outside); otherwise the source is the (cols, rows,
 // values) triple written by the previous pass.
 //
+// BY_ROW: the finished arrays are the source, the digit is the row inside the group: the entries come out in (row,
+// column) order, which is what the row-by-row kernel reads when the input was no CSR matrix.
+//
 // nb > 0: the workgroup sorts one bucket of one group instead of a whole group.  The pass before
 // it has sorted the group by the digit above (col >> 8, nb values); bucket b of group q is the
 // stretch of the group with that digit equal to b, found by two binary searches, and it is sorted
@@ -126,24 +130,30 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool is_active)
 constexpr int kSortWaves = 16;          // waves of the workgroup that sorts a whole group
 constexpr int kSortBucketWaves = 4;     // and of the one that sorts one bucket of a group (about a thousand entries)
 
-template <bool FIRST, int WAVES>
+enum SortPass { kSortFirst, kSortNext, kSortByRow };
+
+template <SortPass PASS, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
     const int32_t* __restrict__ gIdxes, const int32_t* __restrict__ row_ptr, int64_t m, int32_t p,
     const int32_t* __restrict__ src_cols, const int32_t* __restrict__ src_rows, const float* __restrict__ src_vals,
     int32_t* __restrict__ dst_cols, int32_t* __restrict__ dst_rows, float* __restrict__ dst_vals, int shift, int32_t nb,
-    int32_t kcols, uint32_t* __restrict__ bad_col)
+    int32_t kcols, uint32_t* __restrict__ bad_col, int32_t* __restrict__ row_cols, float* __restrict__ row_vals)
 {
+    constexpr bool FIRST = PASS == kSortFirst, BY_ROW = PASS == kSortByRow;
     // FIRST: a column of the input outside [0, kcols) is stored clamped into that range and reported in
     // *bad_col, so that no later kernel forms an address outside B from it
+    const int64_t q = nb > 0 ? blockIdx.x / nb : blockIdx.x;
+    const int32_t row_first = (int32_t)(q * p);
     auto in_range = [&](int32_t c) { return FIRST ? (c < 0 ? 0 : (c >= kcols ? kcols - 1 : c)) : c; };
+    // the digit of an entry: 8 bits of its column, or (BY_ROW) its row inside the group
+    auto digit = [&](int32_t x) { return BY_ROW ? (uint32_t)(x - row_first) : ((uint32_t)in_range(x) >> shift) & 255u; };
     __shared__ int32_t slot_of[WAVES][256];      // counts, then running slots, per wave and digit
     __shared__ int32_t total[256];
     __shared__ int32_t rp_s[FIRST ? 257 : 1];         // FIRST: row_ptr of the group's rows (at most 256 + 1), searched per entry
     __shared__ int32_t range_s[2];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t q = nb > 0 ? blockIdx.x / nb : blockIdx.x;
     int32_t beg = gIdxes[q], end = gIdxes[q + 1];
-    if (beg >= end) return;
+    if (beg >= end && !BY_ROW) return;
     if (nb > 0) {
         // threads 0 and 1: first entry of the group whose high digit is >= b, and >= b + 1
         if (tid < 2) {
@@ -179,10 +189,10 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
     for (int32_t e = pb + lane; e < pe; e += 4 * kWave) {
         int32_t c[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = e + u * kWave < pe ? src_cols[e + u * kWave] : 0;
+        for (int u = 0; u < 4; ++u) c[u] = e + u * kWave < pe ? (BY_ROW ? src_rows : src_cols)[e + u * kWave] : 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (e + u * kWave < pe) atomicAdd(&slot_of[wv][((uint32_t)in_range(c[u]) >> shift) & 255u], 1);   // counts only: order-free
+            if (e + u * kWave < pe) atomicAdd(&slot_of[wv][digit(c[u])], 1);   // counts only: order-free
     }
     __syncthreads();
     if (tid < 256) {
@@ -213,6 +223,10 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
     }
     __syncthreads();
     for (int i = tid; i < WAVES * 256; i += WAVES * kWave) (&slot_of[0][0])[i] += total[i & 255];
+    if (BY_ROW) {                                    // where the rows of the group begin (dst_rows: row_start); the last group adds the end
+        if (tid < p && row_first + tid < m) dst_rows[row_first + tid] = beg + total[tid];
+        if (tid == 0 && row_first + p >= m) dst_rows[m] = end;
+    }
     __syncthreads();
 
     // From here on the waves do not meet again: a wave's LDS operations execute in order, and the
@@ -243,6 +257,10 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
             if (FIRST) {
                 const int32_t c = in_range(col);
                 if (c != col) { *bad_col = 1u; col = c; }
+                if (row_cols) {                                   // the entries in row order, as they came
+                    row_cols[e] = col;
+                    row_vals[e] = val;
+                }
                 // row r with row_ptr[r] <= e < row_ptr[r+1]; empty rows are skipped by the upper bound
                 int32_t lo = 0, hi = (int32_t)(r_hi - r_lo);      // answer in [lo, hi), relative to the group's first row
                 while (hi - lo > 1) {
@@ -252,7 +270,7 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
                 row = (int32_t)r_lo + lo;
             }
         }
-        const uint32_t d = ((uint32_t)col >> shift) & 255u;
+        const uint32_t d = BY_ROW ? (uint32_t)(row - row_first) : ((uint32_t)col >> shift) & 255u;
         const uint64_t same = match_digit(d, act);
         const int32_t before = __popcll(same & lt);
         int32_t slot = 0;
@@ -263,7 +281,7 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
         if (act) {
             const int32_t at = beg + slot + before;
             dst_cols[at] = col;
-            dst_rows[at] = row;
+            if (!BY_ROW) dst_rows[at] = row;
             dst_vals[at] = val;
         }
     }

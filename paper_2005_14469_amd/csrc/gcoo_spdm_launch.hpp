@@ -62,4 +62,22 @@ struct ShareArgs {
 };
 hipError_t launch_spdm_share(const ShareArgs& a, hipStream_t s);
 
+// The kernel that works row by row on the entries in row order: N >= 4, k >= 1, and B (its k rows at pitch ldb) within
+// 4 GB less 128 KB; any alignment of 4 bytes.
+struct RowsArgs {
+    const int32_t* row_ptr;    // [m + 1]
+    const int32_t* cols;       // [nnz]
+    const float* vals;         // [nnz]
+    int64_t m;
+    int64_t k;
+    int64_t nnz;
+    const float* B;
+    int64_t ldb;
+    int64_t N;
+    float* C;
+    int64_t ldc;
+};
+constexpr uint64_t kRowsMaxBytes = 0xfffe0000ull;
+hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s);
+
 }  // namespace gcoo

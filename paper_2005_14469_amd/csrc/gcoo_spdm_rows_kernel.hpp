@@ -1,0 +1,267 @@
+// SpDM kernel that works row by row: C(r, :) = sum over the stored entries of row r of value x B(column, :).
+//
+// Where a group has few entries per column (Section 4.1: the mean run is p(1-s)/(1-s^p)), the reuse of a fetched
+// value of B that Algorithm 2 is built around finds next to nothing to reuse, and a wave per (group, 256 columns) leaves
+// small and narrow products with a handful of waves.  This kernel reads the entries in row order (the copy of them that
+// the conversion keeps, gcoo_api.hip), so a partial sum never changes its register, and cuts the work much finer:
+//
+//   slot      LPR lanes x 4 adjacent columns (LPR = 16 or 32: 64 or 128 columns; 8 and 4 for a narrow B), one row of A at a time:
+//             a wave holds 64 / LPR slots, which load B rows of their own with one instruction
+//   entries   16 of a row at a time: every lane loads one (column, value) pair, and a DPP broadcast inside the
+//             instruction that uses them hands pair i to the whole slot, so an entry costs one address
+//             add, one load and four multiply-adds for 4 x 64 columns at LPR = 16
+//   ends      entries past the end of a row have an offset beyond the buffer descriptor's range: the load returns zero
+//             without touching memory, so a non-finite B row that no entry touches stays out of C
+//   long rows rows of more than `wave_row` entries are shared by the slots of the wave, of more than `group_row` by those of
+//             the workgroup: equal stretches, partial sums added in a fixed order, so the bits are the same on every run
+//
+// Bound: the vector cache (64 bytes per clock and compute unit), 4 x nnz x N bytes; a tile of 64 columns of B stays in an
+// XCD's L2 up to 16384 columns of A, so each row of B comes from memory about once per tile.  Measured (product alone,
+// before = the register kernel): 12000 x 12000, 0.5 %, N = 64: 83 -> 11.4 us; 1777 x 2301, 3 %, N = 1117: 80 -> 30; 2500 x 2500,
+// 1 %, N = 1024: 38 -> 13.7; 256 x 256, 10 %, N = 256: 35 -> 4.7; 4000 x 4000, 2 %, N = 4000: 25 TB/s through the vector cache.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gcoo_spdm_launch.hpp"
+
+namespace gcoo {
+
+constexpr int kRowsThreads = 256;
+constexpr int kRowsPerWave = 32;         // at most
+typedef float rows_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t rows_u32x4 __attribute__((ext_vector_type(4)));
+
+// Pair i of a batch of 16, in every lane of the slot.  LPR >= 16: lane i of every row of 16 lanes holds pair i; below,
+// every quad of lanes holds all pairs, pair i in register i / 4 of lane i % 4.
+template <int LPR, int I>
+__device__ __forceinline__ uint32_t rows_bcast(const uint32_t (&x)[LPR >= 16 ? 1 : 4])
+{
+    if constexpr (LPR >= 16)
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[0], 0x150 + I, 0xf, 0xf, true);                 // row_newbcast:I
+    else
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[I / 4], (I % 4) * 0x55, 0xf, 0xf, true);       // quad_perm:[i,i,i,i]
+}
+
+struct RowsAcc { float x[4]; };
+
+template <int LPR, int CNT, int I>
+__device__ __forceinline__ void rows_load(const uint32_t (&off)[LPR >= 16 ? 1 : 4], uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc,
+                                          rows_u32x4 (&b)[CNT])
+{
+    if constexpr (I < CNT) {
+        b[I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(rows_bcast<LPR, I>(off) + lane_off), 0, 0);
+        rows_load<LPR, CNT, I + 1>(off, lane_off, rsrc, b);
+    }
+}
+template <int LPR, int CNT, int I>
+__device__ __forceinline__ void rows_fma(const uint32_t (&val)[LPR >= 16 ? 1 : 4], const rows_u32x4 (&b)[CNT], RowsAcc& acc)
+{
+    if constexpr (I < CNT) {
+        const float v = __uint_as_float(rows_bcast<LPR, I>(val));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc.x[u] = __builtin_fmaf(v, __uint_as_float(b[I][u]), acc.x[u]);
+        rows_fma<LPR, CNT, I + 1>(val, b, acc);
+    }
+}
+template <int LPR, int CNT>
+__device__ __forceinline__ void rows_batch(const uint32_t (&off)[LPR >= 16 ? 1 : 4], const uint32_t (&val)[LPR >= 16 ? 1 : 4],
+                                           uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc, RowsAcc& acc)
+{
+    rows_u32x4 b[CNT];
+    rows_load<LPR, CNT, 0>(off, lane_off, rsrc, b);
+    rows_fma<LPR, CNT, 0>(val, b, acc);
+}
+
+// One (column, value) pair per lane (and register) of a batch of 16 entries: columns beyond the last row of B are brought inside (a
+// device CSR input is not checked), entries past `end` get an offset outside the descriptor.
+template <int LPR>
+struct RowsBatch {
+    static constexpr int REGS = LPR >= 16 ? 1 : 4;
+    uint32_t c[REGS], v[REGS];
+    __device__ __forceinline__ void request(const RowsArgs& a, int32_t base, int32_t end, int lane)
+    {
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) {
+            const int32_t e = base + (LPR >= 16 ? (lane & 15) : 4 * j + (lane & 3));
+            c[j] = 0xffffffffu;
+            v[j] = 0u;
+            if (e < end) {
+                c[j] = (uint32_t)a.cols[e];
+                v[j] = __float_as_uint(a.vals[e]);
+            }
+        }
+    }
+    __device__ __forceinline__ void offsets(uint32_t kmax, uint32_t ldb4)
+    {
+        constexpr uint32_t kNowhere = 0xffff0000u;         // beyond the range of every descriptor (the launcher checks it)
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) c[j] = c[j] == 0xffffffffu ? kNowhere : (c[j] < kmax ? c[j] : kmax) * ldb4;
+    }
+};
+
+// The batch in steps of two entries: as many as the fullest slot of the wave has (a load past a row's end returns at once but
+// holds the address path as long as any other).
+template <int LPR, int CNT>
+__device__ __forceinline__ void rows_pick(int32_t left, const RowsBatch<LPR>& now, uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc, RowsAcc& acc)
+{
+    if (__any(left > CNT - 2)) {
+        rows_batch<LPR, CNT>(now.c, now.v, lane_off, rsrc, acc);
+    } else {
+        if constexpr (CNT > 2) rows_pick<LPR, CNT - 2>(left, now, lane_off, rsrc, acc);
+    }
+}
+
+// Adds the entries [base, end) of the slot's row (every lane of the wave calls it; the slots may have different ranges).
+// `next` holds the first batch already; on return it holds the batch [more, more_end), requested in front of the loads of
+// the last batch.
+template <int LPR>
+__device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end,
+                                             uint32_t kmax, uint32_t ldb4, uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc, int lane, RowsAcc& acc)
+{
+    while (true) {
+        RowsBatch<LPR> now = next;
+        now.offsets(kmax, ldb4);
+        const int32_t left = end - base;
+        base += 16;
+        const bool last = !__any(base < end);
+        next.request(a, last ? more : base, last ? more_end : end, lane);
+        rows_pick<LPR, 16>(left, now, lane_off, rsrc, acc);
+        if (last) return;
+    }
+}
+
+// Workgroup (tile, wg): rows [wg * 4 * rpw, ...), `rpw` of them per wave, columns of the tile.
+template <int LPR>
+__global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, int32_t group_row)
+{
+    constexpr int SPW = 64 / LPR, WAVES = kRowsThreads / 64, SLOTS = SPW * WAVES, TILE = LPR * 4;
+    __shared__ __attribute__((aligned(16))) float part[SLOTS][TILE];
+    __shared__ int32_t listed, list[WAVES * kRowsPerWave];
+    // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
+    // eight XCDs work on eight tiles side by side, so that what they read and write of a row at about the same time is one
+    // stretch of 2 KB.  The tiles beyond the last whole eight are cut into eight slices of rows.
+    const int32_t xcd = (int32_t)(blockIdx.x & 7u), at = (int32_t)(blockIdx.x >> 3), eights = tiles / 8;
+    int32_t tile, wg;
+    if (at < eights * row_wgs) {
+        tile = at / row_wgs * 8 + xcd;
+        wg = at - at / row_wgs * row_wgs;
+    } else {
+        const int32_t rest = (tiles - eights * 8) * row_wgs, per = (rest + 7) / 8, i = xcd * per + (at - eights * row_wgs);
+        if (at - eights * row_wgs >= per || i >= rest) return;       // the whole workgroup
+        tile = eights * 8 + i / row_wgs;
+        wg = i - i / row_wgs * row_wgs;
+    }
+    const int lane = threadIdx.x & 63, slot = lane / LPR, sl = lane % LPR;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x == 0) listed = 0;
+    __syncthreads();
+    const int64_t j0 = (int64_t)tile * TILE;                          // first column of the tile, less up to 31 (place())
+    // The descriptor starts at or before the first column any lane of the tile loads.
+    const int64_t jb = j0 - 31 < 0 ? 0 : (j0 - 31 < a.N - 4 ? j0 - 31 : a.N - 4);
+    const char* bbase = reinterpret_cast<const char*>(a.B + jb);
+    const uint64_t bytes = ((uint64_t)(a.k - 1) * (uint64_t)a.ldb + (uint64_t)a.N - (uint64_t)jb) * 4u;
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(bbase), 0, (int)(uint32_t)bytes, 0x00027000);
+    const uint32_t ldb4 = (uint32_t)a.ldb * 4u, kmax = (uint32_t)(a.k - 1);
+    // A lane's columns in row r: the tile is moved down by what the row's start in C lies past a 128-byte line, so that the
+    // stores of a slot are whole lines whatever N and ldc are.  A lane that would reach outside [0, N) loads four columns
+    // inside instead and stores those that are its own.
+    struct Place { int32_t jc, first, last; };              // elements [first, last) of the vector at column jc
+    const int32_t N = (int32_t)a.N, lane_j = (int32_t)j0 + sl * 4;
+    const uint32_t c_word = (uint32_t)(reinterpret_cast<uintptr_t>(a.C) >> 2), ldc_word = (uint32_t)a.ldc;
+    auto place = [&](int32_t r) {
+        const int32_t want = lane_j - (int32_t)((c_word + (uint32_t)r * ldc_word) & 31u);
+        Place pl;
+        pl.jc = want < 0 ? 0 : (want > N - 4 ? N - 4 : want);
+        pl.first = want - pl.jc < 0 ? 0 : want - pl.jc;
+        pl.last = want - pl.jc + 4;
+        return pl;
+    };
+    auto store = [&](int32_t r, const Place& pl, const RowsAcc& acc) {
+        float* dst = a.C + (int64_t)r * a.ldc + pl.jc;
+        if (pl.first == 0 && pl.last >= 4) {
+            rows_f32x4 o = {acc.x[0], acc.x[1], acc.x[2], acc.x[3]};
+            __builtin_nontemporal_store(o, reinterpret_cast<rows_f32x4*>(dst));
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (u >= pl.first && u < pl.last) __builtin_nontemporal_store(acc.x[u], dst + u);
+        }
+    };
+
+    const int32_t m = (int32_t)a.m, w0 = (wg * WAVES + wv) * rpw;                    // the wave's first row
+    const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
+    // where the wave's rows begin (lane i: row w0 + i)
+    const int32_t start = lane <= wrows && wrows > 0 ? a.row_ptr[w0 + lane] : 0;
+    auto bounds = [&](int32_t i, int32_t* beg, int32_t* end) {                      // of the wave's row i (empty past the last)
+        const int32_t b = __shfl(start, i, 64), e = __shfl(start, i + 1, 64);
+        *beg = b;
+        *end = i < wrows ? e : b;
+    };
+    int32_t beg, end;
+    bounds(slot, &beg, &end);
+    RowsBatch<LPR> next;
+    bool whole = end - beg > wave_row;                                              // the row is left to all slots of the wave, or of the workgroup
+    next.request(a, beg, whole ? beg : end, lane);
+    for (int32_t i = 0; i < wrows; i += SPW) {
+        const int32_t r = w0 + i + slot;
+        int32_t beg2, end2;
+        bounds(i + SPW + slot, &beg2, &end2);
+        const bool whole2 = end2 - beg2 > wave_row;
+        const Place pl = place(r);
+        RowsAcc acc = {{0.0f, 0.0f, 0.0f, 0.0f}};
+        rows_entries<LPR>(a, next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, kmax, ldb4, (uint32_t)(pl.jc - (int32_t)jb) * 4u, rsrc, lane, acc);
+        if (i + slot < wrows && !whole) store(r, pl, acc);
+        uint64_t todo = __ballot(whole && sl == 0);
+        while (todo) {                                                              // wave-uniform
+            const int32_t s = (__ffsll((long long)todo) - 1) / LPR;
+            todo &= todo - 1;
+            const int32_t lb = __builtin_amdgcn_readlane(start, i + s), le = __builtin_amdgcn_readlane(start, i + s + 1);
+            const int32_t lr = w0 + i + s, n = le - lb;
+            if (n > group_row) {
+                if (lane == 0) list[atomicAdd(&listed, 1)] = lr;
+                continue;
+            }
+            // equal stretches for the slots, their sums added up in a fixed tree
+            const int32_t each = (n + SPW - 1) / SPW, b = lb + slot * each, e = b + each < le ? b + each : le;
+            const Place lpl = place(lr);
+            RowsBatch<LPR> mine;
+            mine.request(a, b, e, lane);
+            RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
+            rows_entries<LPR>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, rsrc, lane, sum);
+#pragma unroll
+            for (int d = LPR; d < 64; d <<= 1)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sum.x[u] += __shfl_xor(sum.x[u], d, 64);
+            if (slot == 0) store(lr, lpl, sum);
+        }
+        beg = beg2;
+        end = end2;
+        whole = whole2;
+    }
+    // the longest rows of this workgroup, one after another, all its slots on each
+    __syncthreads();
+    const int32_t n_list = listed;
+    for (int32_t x = 0; x < n_list; ++x) {
+        const int32_t lr = __builtin_amdgcn_readfirstlane(list[x]);
+        const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
+        const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + slot) * each, e = b + each < le ? b + each : le;
+        const Place lpl = place(lr);
+        RowsBatch<LPR> mine;
+        mine.request(a, b, e, lane);
+        RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
+        rows_entries<LPR>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, rsrc, lane, sum);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) part[wv * SPW + slot][sl * 4 + u] = sum.x[u];
+        __syncthreads();
+        if (wv == 0 && slot == 0) {
+            for (int s = 1; s < SLOTS; ++s)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sum.x[u] += part[s][sl * 4 + u];
+            store(lr, lpl, sum);
+        }
+        __syncthreads();
+    }
+}
+
+}  // namespace gcoo

@@ -1,0 +1,80 @@
+"""The row-by-row kernel (the automatic choice for short rows and for small and narrow products) at the sizes where it can go
+wrong: batches of 16 entries full and one over, rows shared by a wave and by a workgroup, every width of a slot, tiles that
+begin inside a 128-byte line, entries of a dense input brought back into row order.  Against the CPU oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gcoo_oracle as orc
+from paper_2005_14469_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _rows_of_lengths(lens, k, N, seed):
+    """CSR with the given row lengths (columns distinct while they fit, repeated beyond), B dense."""
+    rng = np.random.default_rng(seed)
+    cols = [np.sort(rng.choice(k, n, replace=n > k)).astype(np.int32) for n in lens]
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate(cols) if len(lens) else np.zeros(0, np.int32)
+    va = rng.standard_normal(len(ci)).astype(np.float32)
+    return workloads.Workload("lens", len(lens), k, N, rp, ci, va, rng.standard_normal((k, N)).astype(np.float32))
+
+
+def _check(w, p, shift=0, pad=0, dense=False):
+    Bbig = torch.zeros((w.k, w.N + shift + pad), device=DEV)
+    Bbig[:, shift:shift + w.N] = torch.from_numpy(w.B).to(DEV)
+    Cbig = torch.full((w.m, w.N + shift + pad + 8), 7.0, device=DEV)
+    Bv, Cv = Bbig[:, shift:shift + w.N], Cbig[:, shift:shift + w.N]
+    dev = [torch.from_numpy(x).to(DEV) for x in (w.row_ptr, w.col_idx, w.vals)]
+    if dense:
+        Ah = np.zeros((w.m, w.k), np.float32)
+        Ah[np.repeat(np.arange(w.m), np.diff(w.row_ptr)), w.col_idx] = w.vals
+        A = binding.gcoo_from_dense(torch.from_numpy(Ah).to(DEV), p)
+    else:
+        A = binding.gcoo_from_csr(w.m, w.k, *dev, p, known_nnz=True)
+    binding.gcoo_spdm(A, Bv, Cv)
+    torch.cuda.synchronize()
+    C64, D64 = orc.spdm_csr(w.k, w.N, w.row_ptr, w.col_idx, w.vals, w.B)
+    err, bad = orc.max_scaled_error(Cv.cpu().numpy(), C64, D64)
+    assert bad == 0 and err < 2e-6, (err, bad)
+    assert torch.all(Cbig[:, :shift] == 7.0) and torch.all(Cbig[:, shift + w.N:] == 7.0)
+    first = Cv.clone()
+    binding.gcoo_spdm(A, Bv, Cv)
+    assert torch.equal(first, Cv)                          # the same bits on every run
+
+
+@pytest.mark.parametrize("N,shift,pad", [(4, 0, 0), (5, 0, 0), (16, 0, 0), (17, 1, 2), (32, 0, 0), (33, 0, 0), (64, 0, 0), (65, 3, 0), (128, 0, 0),
+                                         (131, 2, 3), (260, 0, 0), (1031, 1, 0)])
+def test_widths_and_alignments(N, shift, pad):
+    print(f"rows: N={N} shift={shift} pad={pad}", flush=True)
+    _check(_rows_of_lengths([0, 1, 15, 16, 17, 31, 32, 33, 2, 0, 7, 48, 64, 65, 3, 5, 90] * 3, 211, N, seed=N), 32, shift, pad)
+
+
+@pytest.mark.parametrize("p,dense", [(8, False), (32, True), (64, False), (64, True), (128, True)])
+def test_long_rows_shared_by_a_wave_and_by_a_workgroup(p, dense):
+    """Rows just below and above the lengths from which a wave and a workgroup take them, several in one workgroup."""
+    rng = np.random.default_rng(p)
+    lens = np.minimum(rng.zipf(1.6, 400), 40)
+    lens[[3, 4, 5, 40, 41, 200]] = [65, 64, 512, 513, 1900, 2000]
+    lens[-1] = 700
+    print(f"rows: long rows p={p} dense={dense}", flush=True)
+    _check(_rows_of_lengths(lens, 2048, 68, seed=p), p, dense=dense)
+
+
+@pytest.mark.parametrize("m,k,N,n", [(1, 1, 4, 1), (1, 5000, 64, 120), (3, 300, 260, 100), (64, 300, 64, 100), (5000, 9, 40, 2), (40000, 3000, 20, 3)])
+def test_few_and_many_rows(m, k, N, n):
+    print(f"rows: m={m} k={k} N={N}, {n} entries each", flush=True)
+    _check(_rows_of_lengths([n] * m, k, N, seed=m), 32)
+
+
+def test_repeated_and_non_finite():
+    """Repeated coordinates add up; a row of B that no entry touches may hold anything."""
+    w = _rows_of_lengths([30, 0, 5, 17] * 20, 12, 36, seed=4)              # more entries than columns: coordinates repeat
+    _check(w, 16)
+    w = _rows_of_lengths([3, 9, 0, 20] * 10, 400, 36, seed=5)
+    w.B[np.setdiff1d(np.arange(w.k), w.col_idx)] = np.inf
+    _check(w, 16)
