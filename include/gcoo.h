@@ -84,9 +84,7 @@ int32_t gcoo_default_p(int64_t m, int64_t k, int64_t nnz, int64_t N);
  * Device bytes a gcoo_from_csr() / gcoo_from_dense() call needs in dev_buf for an m x k matrix
  * with nnz stored entries and group height p: the five arrays of Section 3.1 (Table 1:
  * 3*nnz + 2*g elements, plus one sentinel), the entries in row order (2*nnz + m elements), the kernel-private
- * schedules derived from them (the run
- * schedule of the register kernel, at most 3*nnz + 2048*g + 128 words; where gcoo_set_share_policy()
- * asks for it the share schedule of the workgroup-shared kernel) and the scratch space the
+ * schedules that gcoo_set_share_policy() asks for and the scratch space the
  * conversion kernels use; for p > 64 also a second copy of the matrix regrouped at 32 rows with its
  * schedules, which is what the fast kernels multiply with (they hold at most 64 rows of partial sums).
  * Returns 0 for invalid arguments.  Pure host arithmetic.
@@ -189,30 +187,26 @@ int gcoo_spdm(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
  */
 #define GCOO_VARIANT_AUTO 0
 #define GCOO_VARIANT_LDS  1  /* partial sums in LDS, reads the five arrays directly; any p, any alignment */
-/* partial sums in VGPRs, reads the run schedule built at conversion; needs N >= 4 (p <= 38 and p > 64:
- * four columns per lane) or N >= 2 (39 <= p <= 64: two), else GCOO_EINVAL.  A matrix of groups taller than
+/* partial sums in VGPRs: the kernel that reads the run schedule where the conversion built one (any policy but
+ * GCOO_SHARE_AUTO), else the one that works row by row; needs N >= 4 (p <= 38 and p > 64) or N >= 2 (39 <= p <= 64), else
+ * GCOO_EINVAL.  A matrix of groups taller than
  * 64 rows is multiplied through a second, kernel-private copy regrouped at 32 rows that the conversion keeps
  * behind the five arrays (gcoo_device_bytes() counts it); GCOO_VARIANT_SHARE works on that copy too.  Any N, ldb, ldc and base
- * addresses: where N is not a multiple of the columns per lane, the lane at the end of a row computes the
- * last columns of the row instead of reaching beyond N, and rows aligned to 4 bytes only are read and
- * written with unaligned 16-byte accesses (a few per cent slower than aligned ones).  No access leaves
- * the first N columns of a row.  Groups with very many entries are shared by the waves of a workgroup
- * except for 33 <= p <= 38 */
+ * addresses; no access leaves the first N columns of a row */
 #define GCOO_VARIANT_REG  2
-/* the eight groups of a workgroup (a super-group, up to 8 x 48 rows of A) fetch each row of B that
- * any of them needs once into LDS, and every multiply-add takes its B values from there; reads the
- * share schedule built at conversion (see gcoo_set_share_policy()); needs p <= 48, B, C, ldb, ldc, N
- * multiples of 4 elements (16-byte aligned rows) and k * ldb * 4 < 2^32, else GCOO_EINVAL.
- * gcoo_spdm() picks it where the matrix has that schedule by the automatic rule, the operands
- * qualify and C has at least 192 blocks of (8p rows) x 256 columns - below 9000 columns of A also
- * only if those blocks fill their rounds over the 256 compute units to 80 % */
+/* the waves of a workgroup share the rows of B: each row of B that any of them needs is fetched once into LDS, and every
+ * multiply-add takes its B values from there.  Reads the share schedule where the conversion built one (GCOO_SHARE_ALWAYS), else the
+ * band schedule; needs p <= 48, B, C, ldb, ldc, N
+ * multiples of 4 elements (16-byte aligned rows) and k * ldb * 4 < 2^32, else GCOO_EINVAL */
 #define GCOO_VARIANT_SHARE 3
 int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                       float* C_dev, int64_t ldc, void* stream, int variant);
 
-/* Variant gcoo_spdm() would pick for this matrix and these operand shapes (one of GCOO_VARIANT_* > 0).  GCOO_VARIANT_AUTO
- * has a kernel more than there are variants to ask for: one that works row by row, which takes short rows and small and
- * narrow products; for such a call the answer is the variant that would serve it without that kernel. */
+/* One of GCOO_VARIANT_* > 0: GCOO_VARIANT_SHARE where the matrix may be asked for it (see GCOO_SHARE_AUTO), the operands
+ * qualify and C has at least 192 blocks of (8p rows) x 256 columns - below 9000 columns of A also only if those blocks fill their
+ * rounds over the 256 compute units to 80 % -, else GCOO_VARIANT_REG where it serves the shape, else GCOO_VARIANT_LDS.
+ * GCOO_VARIANT_AUTO itself goes by the time that the row-by-row kernel (any shape) and the kernel of the band schedule are expected
+ * to take, so it may run either of them whatever this function answers. */
 int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                    const float* C_dev, int64_t ldc);
 
@@ -232,14 +226,13 @@ int gcoo_export(const gcoo_matrix* A, float* values, int32_t* rows, int32_t* col
                 int64_t* gIdxes, int32_t* nnzPerGroup, void* stream);
 
 /*
- * When conversions build the share schedule (process-wide setting, not thread-safe; takes effect
- * for matrices converted afterwards).
- * GCOO_SHARE_AUTO: only for matrices on which gcoo_spdm() then picks GCOO_VARIANT_SHARE when B is
- *   wide enough: p <= 48, density at most 6 %, and at least 1.5 % from 3500 columns on, 0.8 % from 5500, 0.35 % from
- *   7000 (at most 262144 columns);
- * GCOO_SHARE_ALWAYS: whenever that kernel could run (p <= 48, at most 262144 columns, nnz > 0);
- *   gcoo_spdm() keeps its usual choice and GCOO_VARIANT_SHARE must be asked for;
- * GCOO_SHARE_NEVER: never.
+ * Which kernel-private schedules conversions build (process-wide setting; takes effect for matrices converted afterwards).
+ * GCOO_SHARE_AUTO: the band schedule where a product with a B as wide as A gains by it, and for p <= 48, density at most 6 %, and
+ *   at least 1.5 % from 3500 columns on, 0.8 % from 5500, 0.35 % from 7000 (at most 262144 columns): there
+ *   GCOO_VARIANT_SHARE can be asked for;
+ * GCOO_SHARE_ALWAYS: also the run schedule that GCOO_VARIANT_REG then reads, and the share schedule that GCOO_VARIANT_SHARE then
+ *   reads, whenever that kernel could run (p <= 48, at most 262144 columns, nnz > 0); for tuning and tests;
+ * GCOO_SHARE_NEVER: the run schedule only; gcoo_spdm() has the register kernel and the row-by-row kernel to choose from.
  */
 #define GCOO_SHARE_AUTO   0
 #define GCOO_SHARE_ALWAYS 1
@@ -250,7 +243,8 @@ int gcoo_set_share_policy(int policy);
  * Introspection for tests: copies the share schedule (the kernel-private re-listing that the
  * workgroup-shared SpDM kernel reads) to HOST buffers, any of which may be NULL.
  * *hdr_words and *block_count receive the sizes of `hdr` (32-bit words) and `blocks` (blocks of 64 words);
- * call once with the arrays NULL to learn them.  sbase has 8 * ceil(g / 8) entries, ucount ceil(g / 8),
+ * call once with the arrays NULL to learn them.  Both are 0, and nothing is copied, for a matrix whose GCOO_VARIANT_SHARE reads the band
+ * schedule instead.  sbase has 8 * ceil(g / 8) entries, ucount ceil(g / 8),
  * ucols nnz (the distinct columns of super-group Q start at index gIdxes[8Q]).  Synchronises `stream`.
  * GCOO_EINVAL if A is NULL or has no share schedule.
  */

@@ -47,7 +47,7 @@ def _checked(src: str) -> bool:
     """Sources whose generated code is verified by isa_check (kernels that issue loads from asm, or that
     load straight to LDS next to the index mode)."""
     name = os.path.basename(src)
-    return name.startswith("spdm_sched_v") or name == "spdm_share.hip"
+    return name.startswith("spdm_sched_v") or name in ("spdm_share.hip", "spdm_band.hip")
 
 
 def _compile(src: str) -> str:
@@ -83,6 +83,9 @@ def verify_generated_code() -> None:
         if stem == "spdm_share":
             verify_share_code(stem, text)
             continue
+        if stem == "spdm_band":
+            verify_band_code(stem, text)
+            continue
         for kernel in sched_kernel_names(stem):
             regs, bad = isa_check.check(text, kernel)
             if not regs:
@@ -107,6 +110,24 @@ def verify_share_code(stem: str, text: str) -> None:
     spills = [int(x) for x in re.findall(r"\.vgpr_spill_count:\s+(\d+)", text)]
     if len(spills) != 1 or any(spills):
         raise RuntimeError(f"{stem}: register spills {spills}")
+
+
+def verify_band_code(stem: str, text: str) -> None:
+    """The sixteen-wave kernel, both instances: no register spills, 128 VGPRs at most (four waves per SIMD), every load that writes LDS sets M0
+    itself, nothing is in flight at a barrier, and its asm text writes the scalar registers that its clobber list names."""
+    from . import isa_check
+    for kernel in ("_ZN4gcoo9spdm_bandILb0E", "_ZN4gcoo9spdm_bandILb1E"):
+        loads, problems = isa_check.check_lds_loads(text, kernel)
+        if loads < 15 or problems:
+            raise RuntimeError(f"{stem} {kernel}: {loads} loads to LDS, {problems[:3]}")
+        written, read = isa_check.asm_scalar_writes(text, kernel)
+        if written != set(range(12, 32)) | set(range(36, 100)) or not read:
+            raise RuntimeError(f"{stem} {kernel}: scalar registers written {sorted(written)}, read {sorted(read)}")
+    meta = text[text.index("amdhsa.kernels"):]
+    for key, most in (("vgpr_spill_count", 0), ("sgpr_spill_count", 0), ("private_segment_fixed_size", 0), ("vgpr_count", 128)):
+        got = [int(x) for x in re.findall(rf"\.{key}:\s+(\d+)", meta)]
+        if len(got) != 2 or max(got) > most:
+            raise RuntimeError(f"{stem}: {key} {got}")
 
 
 def build(force: bool = True, jobs: int = 8) -> str:

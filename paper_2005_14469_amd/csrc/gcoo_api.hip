@@ -11,8 +11,11 @@
 #include <string>
 
 #include <atomic>
+#include <cmath>
 #include <mutex>
 
+#include "gcoo_band.hpp"
+#include "gcoo_band_build.hpp"
 #include "gcoo_build_kernels.hpp"
 #include "gcoo_sched.hpp"
 #include "gcoo_sched_build.hpp"
@@ -80,13 +83,15 @@ int static_scratch(unsigned char** out)
 // Carve-up of the caller's device buffer.  Offsets depend on (m, nnz, g) only.
 struct Layout {
     size_t values, rows, cols, gIdxes, nnzPerGroup;        // the five arrays of the format
-    size_t row_start, row_cols, row_vals;                  // the entries in row order (p <= 64; taller groups: in the inner handle)
+    size_t row_start, row_cols, row_vals, row_long;        // the entries in row order, the long rows (p <= 64; taller groups: in the inner handle)
     size_t sched_hdr, sched;                               // run schedule of the register kernel
     size_t order;                                          // groups by falling size, then those sizes (matrices of few groups)
     size_t share_ucols, share_ucount, share_hdr, share_blocks, share_sbase, share_alloc;   // share schedule (may be empty)
+    int32_t band_h;                                        // rows per wave of the band schedule, 0: none
+    size_t band_head, band_units, band_first, band_count;  // band schedule
     size_t tmp_cols, tmp_rows, tmp_vals;                   // conversion scratch (second sort buffer)
     size_t in_row_ptr, in_cols, in_vals;                   // staging of a host CSR input
-    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4)
+    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4)
     size_t persistent;                                     // bytes up to here stay in use after the conversion
     // offsets from here on are relative to the scratch area: the caller's buffer from `persistent` on, or the
     // library's static scratch
@@ -172,12 +177,18 @@ bool share_kernel_preferred(int64_t m, int64_t k, int64_t nnz, int32_t p)
     return share_schedule_possible(m, k, nnz, p) && share_shape_preferred(m, k, nnz);
 }
 
+int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p);
+
+// The share schedule itself is built on request, and for a matrix of the automatic rule that is too small for a band schedule.
 bool share_schedule_wanted(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     const int policy = share_policy_now();
     if (policy == GCOO_SHARE_NEVER || !share_schedule_possible(m, k, nnz, p)) return false;
-    return policy == GCOO_SHARE_ALWAYS || share_kernel_preferred(m, k, nnz, p);
+    return policy == GCOO_SHARE_ALWAYS || (share_kernel_preferred(m, k, nnz, p) && band_schedule_h(m, k, nnz, p) == 0);
 }
+
+// The run schedule is what GCOO_VARIANT_REG reads when the policy is not the automatic one.
+bool run_schedule_wanted(int32_t p) { return p <= gcoo::kSchedMaxP && share_policy_now() != GCOO_SHARE_AUTO; }
 
 // A workgroup of that kernel runs for a whole (super-group, column tile): how well `items` of them fill
 // the 256 compute units, as the fraction of the rounds they need that is work.
@@ -211,6 +222,54 @@ int32_t share_best_p(int64_t m, int64_t N)
     return best;
 }
 
+// Times of the two kernels that the automatic choice is between, in microseconds, from measurements on uniform random matrices
+// (n = 500 .. 14000, 0.05 .. 20 % dense, N = n and N = 500 .. 2001; within 15 % where the times are more than 20 us).
+// Row by row: 4 x nnz x N bytes through the vector caches, at 24 TB/s while a tile of 64 columns of B stays in an XCD's L2 and
+// rows of B begin at 128-byte lines; C.
+double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
+{
+    const bool small = k <= 8500;
+    const double rate = small ? (lines ? 24e6 : 17e6) : (lines ? 16.5e6 : 14e6);       // bytes per us
+    return 5.0 + 4.0 * (double)N * ((double)nnz / rate + (double)m / (small ? 4.2e6 : 2.8e6));
+}
+// Bands: a workgroup per compute unit and round; 0.85 us for a band by itself (80 rows of B, the barrier, the bubble behind it) and
+// 2.65 ns per entry of the block; C, and B where it does not fit the memory-side cache.
+double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, int32_t h)
+{
+    const int64_t blocks = gcoo::band_blocks(m, h), rounds = (blocks * ((N + 255) / 256) + 255) / 256;
+    const double entries = (double)nnz / (double)blocks;
+    const double columns = (double)k * -std::expm1(-entries / (double)k);                // distinct ones of a block
+    return 6.0 + (double)rounds * (0.85 * std::ceil(columns / gcoo::kBandRows) + 0.00265 * entries) +
+           4.0 * ((double)m + ((double)k * (double)N > 75e6 ? (double)k : 0.0)) * (double)N / 4.2e6;
+}
+
+// Rows per wave of the band schedule, 0 where none is built.  The width of B is not known here: the blocks are cut so that a
+// product with N = k is fastest, and the schedule is built where that product gains more by it than a conversion
+// pays for it (12 us), or where GCOO_VARIANT_SHARE has to be served.
+int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p)
+{
+    if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return 0;
+    const bool asked = share_kernel_preferred(m, k, nnz, p);
+    if (!asked && rows_time(m, k, nnz, k, true) < 30.0) return 0;
+    // (a conversion asks for every layout it makes: the last answer of this thread is kept)
+    static thread_local struct { int64_t m, k, nnz; bool asked; int32_t h; } last = {0, 0, 0, false, 0};
+    if (last.m == m && last.k == k && last.nnz == nnz && last.asked == asked) return last.h;
+    int32_t best = 0;
+    double best_time = 0.0;
+    for (int32_t h = gcoo::kBandMaxH; h >= 12; --h) {
+        // the columns of every wave's rows as a bitmap, in the second sort buffer
+        if (gcoo::band_blocks(m, h) * gcoo::kBandWaves * ((k + 31) / 32) > 3 * nnz) continue;
+        const double t = band_time(m, k, nnz, k, h);
+        if (best == 0 || t < best_time) { best_time = t; best = h; }
+    }
+    if (best && !asked && best_time + 12.0 > rows_time(m, k, nnz, k, true)) best = 0;
+    last = {m, k, nnz, asked, best};
+    return best;
+}
+
+// (device offsets that contradict each other may make more rows long than these: the rest are not listed)
+int32_t long_room(int64_t m, int64_t nnz) { return (int32_t)(nnz / gcoo::rows_long(m, nnz)) + 1; }
+
 Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool scratch_inside = true)
 {
     int32_t nw, wc;
@@ -232,9 +291,11 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.row_start = take(rows ? (size_t)(m + 1) * 4 : 0);
     L.row_cols = take(rows ? n4 : 0);
     L.row_vals = take(rows ? n4 : 0);
-    L.sched_hdr = take((size_t)g * nw * gcoo::kMaxRun * sizeof(gcoo::SchedClass));
-    L.sched = take((size_t)gcoo::sched_words(nnz, g, nw) * 4);
-    L.order = take(g <= gcoo::kOrderMaxGroups && p <= gcoo::kSchedMaxP ? (size_t)g * 8 : 0);
+    L.row_long = take(rows ? (size_t)long_room(m, nnz) * 4 : 0);
+    const bool sched = run_schedule_wanted(p);
+    L.sched_hdr = take(sched ? (size_t)g * nw * gcoo::kMaxRun * sizeof(gcoo::SchedClass) : 0);
+    L.sched = take(sched ? (size_t)gcoo::sched_words(nnz, g, nw) * 4 : 0);
+    L.order = take(sched && g <= gcoo::kOrderMaxGroups ? (size_t)g * 8 : 0);
     const bool share = share_schedule_wanted(m, k, nnz, p);
     const int64_t nQ = gcoo::share_super_groups(g);
     L.share_ucols = take(share ? n4 : 0);
@@ -242,6 +303,12 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.share_hdr = take(share ? (size_t)gcoo::share_hdr_words(nnz, g) * 4 : 0);
     L.share_blocks = take(share ? (size_t)gcoo::share_stream_blocks(nnz, g, k) * gcoo::kShareBlockWords * 4 : 0);
     L.share_sbase = take(share ? (size_t)nQ * gcoo::kShareW * 4 : 0);
+    L.band_h = band_schedule_h(m, k, nnz, p);
+    const int64_t lists = L.band_h ? gcoo::band_blocks(m, L.band_h) * gcoo::kBandWaves : 0;
+    L.band_head = take((size_t)(lists * gcoo::band_head_stride(k)) * gcoo::kBandHeadWords * 4);
+    L.band_units = take(L.band_h ? (size_t)gcoo::band_units(nnz, m, k, L.band_h) * gcoo::kBandUnitWords * 4 : 0);
+    L.band_first = take((size_t)lists * 4);
+    L.band_count = take((size_t)(lists / gcoo::kBandWaves) * 4);
     L.persistent = at;
     if (!scratch_inside) {
         // the fixed carve-up of the static scratch (no staging of a host input there)
@@ -254,7 +321,7 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
         return L;
     }
     at = 0;
-    L.share_alloc = take(share ? 4 : 0);
+    L.share_alloc = take(4);
     L.tmp_cols = take(n4);
     L.tmp_rows = take(n4);
     L.tmp_vals = take(n4);
@@ -297,9 +364,9 @@ struct gcoo_matrix {
     int64_t m, k, nnz, g;
     int32_t p;
     int32_t nw, window_cols;
-    bool has_sched;            // the run schedule of the register kernel was built (p <= 64)
+    bool has_sched;            // the run schedule of the register kernel was built
     bool has_share;            // the share schedule was built
-    bool share_preferred;      // and the kernel that reads it is the automatic choice
+    bool share_preferred;      // GCOO_VARIANT_SHARE can be asked for and is what gcoo_spdm_pick() answers where B is wide enough
     int device;
     char* base;
     Layout L;
@@ -317,6 +384,12 @@ struct gcoo_matrix {
     int32_t* row_start() const { return reinterpret_cast<int32_t*>(base + L.row_start); }
     int32_t* row_cols() const { return reinterpret_cast<int32_t*>(base + L.row_cols); }
     float* row_vals() const { return reinterpret_cast<float*>(base + L.row_vals); }
+    int32_t* long_rows() const { return reinterpret_cast<int32_t*>(base + L.row_long); }
+    int32_t* long_count() const { return reinterpret_cast<int32_t*>(base + L.counter + 20); }
+    uint32_t* band_head() const { return reinterpret_cast<uint32_t*>(base + L.band_head); }
+    uint32_t* band_units() const { return reinterpret_cast<uint32_t*>(base + L.band_units); }
+    int32_t* band_first() const { return reinterpret_cast<int32_t*>(base + L.band_first); }
+    int32_t* band_count() const { return reinterpret_cast<int32_t*>(base + L.band_count); }
     bool has_rows() const { return p <= gcoo::kSchedMaxP; }
     bool has_order() const { return has_sched && g > 0 && g <= gcoo::kOrderMaxGroups; }
     int32_t* order() const { return reinterpret_cast<int32_t*>(base + L.order); }
@@ -332,6 +405,12 @@ struct gcoo_matrix {
 
 namespace {
 
+gcoo::RowsOut rows_out(const gcoo_matrix* h)
+{
+    if (!h->has_rows()) return {};
+    return {h->row_cols(), h->row_vals(), h->row_start(), h->long_rows(), h->long_count(), gcoo::rows_long(h->m, h->nnz), long_room(h->m, h->nnz)};
+}
+
 int new_handle(int64_t m, int64_t k, int64_t nnz, int32_t p, void* dev_buf, gcoo_matrix** out, bool scratch_inside = true)
 {
     gcoo_matrix* h = new (std::nothrow) gcoo_matrix;
@@ -341,8 +420,8 @@ int new_handle(int64_t m, int64_t k, int64_t nnz, int32_t p, void* dev_buf, gcoo
     h->base = static_cast<char*>(dev_buf);
     h->L = make_layout(m, k, nnz, h->g, p, scratch_inside);
     h->has_share = share_schedule_wanted(m, k, nnz, p);
-    h->share_preferred = h->has_share && share_kernel_preferred(m, k, nnz, p);
-    h->has_sched = h->p <= gcoo::kSchedMaxP;
+    h->share_preferred = (h->has_share || h->L.band_h > 0) && share_kernel_preferred(m, k, nnz, p);
+    h->has_sched = run_schedule_wanted(p);
     pick_windows(k, h->g, &h->nw, &h->window_cols);
     if (hipGetDevice(&h->device) != hipSuccess) h->device = -1;
     *out = h;
@@ -364,6 +443,22 @@ hipError_t share_fill_lds_limit()
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gcoo::share_fill), hipFuncAttributeMaxDynamicSharedMemorySize, kShareFillMaxLds);
+    if (e == hipSuccess) done[dev].store(1u, std::memory_order_release);
+    return e;
+}
+
+constexpr size_t kBandFillMaxLds = 150 * 1024;
+hipError_t band_fill_lds_limit()
+{
+    static std::atomic<unsigned> done[64];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gcoo::band_fill<512>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gcoo::band_fill<1024>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
     if (e == hipSuccess) done[dev].store(1u, std::memory_order_release);
     return e;
 }
@@ -413,6 +508,25 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s)
         gcoo::share_fill<<<dim3((unsigned)(h->share_nq() * gcoo::kShareW)), dim3(gcoo::kShareBuildThreads), fill_lds, s>>>(
             h->gIdxes(), h->rows(), h->cols(), h->values(), h->p, h->g, h->k, h->share_ucols(), h->share_ucount(), h->share_hdr(),
             h->share_blocks(), h->share_sbase(), share_alloc, (int32_t)stage_cap);
+        HIP_TRY(hipGetLastError());
+    }
+    if (h->L.band_h > 0) {
+        const int32_t rows = h->L.band_h;
+        const unsigned lists = (unsigned)(gcoo::band_blocks(h->m, rows) * gcoo::kBandWaves);
+        const size_t words = (size_t)((h->k + 31) / 32);
+        uint32_t* parts = reinterpret_cast<uint32_t*>(scratch + h->L.tmp_cols);          // the second sort buffer, free by now
+        uint32_t* alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
+        gcoo::band_mark<<<dim3(lists), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows, parts, alloc);
+        HIP_TRY(hipGetLastError());
+        int64_t chunk = (h->k + gcoo::kBandRows - 1) / gcoo::kBandRows * gcoo::kBandRows;
+        const int64_t most = (int64_t)(kBandFillMaxLds - words * 8) / (4 * gcoo::kBandRows + 4 * gcoo::kBandRows / gcoo::kBandGroup) * gcoo::kBandRows;
+        if (chunk > gcoo::kBandChunk) chunk = gcoo::kBandChunk;
+        if (chunk > most) chunk = most;
+        HIP_TRY(band_fill_lds_limit());
+        const bool large = h->nnz / lists > 4096;
+        (large ? gcoo::band_fill<1024> : gcoo::band_fill<512>)<<<dim3(lists), dim3(large ? 1024 : 512), words * 8 + (size_t)(chunk + chunk / gcoo::kBandGroup) * 4, s>>>(
+            h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk, gcoo::band_units(h->nnz, h->m, h->k, rows),
+            gcoo::band_head_stride(h->k), h->band_head(), h->band_units(), h->band_first(), h->band_count(), alloc);
         HIP_TRY(hipGetLastError());
     }
     return GCOO_OK;
@@ -562,14 +676,13 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             const int shift = high_first ? 8 * (1 - pass) : 8 * pass;
             if (pass == 0)
                 gcoo::sort_groups_by_col_digit<gcoo::kSortFirst, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
-                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col(),
-                    h->has_rows() ? h->row_cols() : nullptr, h->row_vals());
+                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col(), rows_out(h));
             else if (high_first)
                 gcoo::sort_groups_by_col_digit<gcoo::kSortNext, gcoo::kSortBucketWaves><<<dim3((unsigned)(g * buckets)), dim3(gcoo::kSortBucketWaves * gcoo::kWave), 0, s>>>(
-                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, (int32_t)buckets, (int32_t)k, h->bad_col(), nullptr, nullptr);
+                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, (int32_t)buckets, (int32_t)k, h->bad_col(), {});
             else
                 gcoo::sort_groups_by_col_digit<gcoo::kSortNext, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
-                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col(), nullptr, nullptr);
+                    h->gIdxes(), d_row_ptr, m, p, src_c, src_r, src_v, dc, dr, dv, shift, 0, (int32_t)k, h->bad_col(), {});
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) { delete h; return hip_fail(e, "sort_groups_by_col_digit"); }
             src_c = dc; src_r = dr; src_v = dv;
@@ -693,7 +806,7 @@ int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32
         HIP_TRY(hipMemsetAsync(idx, 0, 4, s));          // only the sentinel exists
         HIP_TRY(hipMemsetAsync(tot, 0, 16, s));
     }
-    HIP_TRY(hipMemsetAsync(base + L0.counter + 16, 0, 4, s));   // no column can be out of range here
+    HIP_TRY(hipMemsetAsync(base + L0.counter + 16, 0, 8, s));   // no column can be out of range here; no long rows so far
     if (total > (unsigned long long)INT32_MAX) return GCOO_EINVAL;
     const int64_t nnz = (int64_t)total;
     const Layout L = make_layout(m, k, nnz, g, p);
@@ -712,8 +825,8 @@ int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32
     }
     if (g > 0 && h->has_rows()) {
         gcoo::sort_groups_by_col_digit<gcoo::kSortByRow, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
-            h->gIdxes(), nullptr, m, p, h->cols(), h->rows(), h->values(), h->row_cols(), h->row_start(), h->row_vals(), 0, 0, (int32_t)k,
-            nullptr, nullptr, nullptr);
+            h->gIdxes(), nullptr, m, p, h->cols(), h->rows(), h->values(), h->row_cols(), nullptr, h->row_vals(), 0, 0, (int32_t)k,
+            nullptr, rows_out(h));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "sort_groups_by_col_digit"); }
     }
@@ -735,6 +848,7 @@ namespace {
 struct Shape {
     bool al4;          // N, both leading dimensions and both base addresses fit 16-byte accesses: what the
                        // workgroup-shared kernel's loads straight to LDS need
+    bool b16;          // B begins at a multiple of 16 bytes
     bool wide_pitch;   // row pitch of B in bytes does not fit 32 bits: LDS variant only
     int64_t N;
 };
@@ -744,6 +858,7 @@ Shape shape_of(const float* B, int64_t ldb, int64_t N, const float* C, int64_t l
     const uintptr_t pb = reinterpret_cast<uintptr_t>(B), pc = reinterpret_cast<uintptr_t>(C);
     Shape s;
     s.al4 = (N % 4 == 0) && (ldb % 4 == 0) && (ldc % 4 == 0) && (pb % 16 == 0) && (pc % 16 == 0);
+    s.b16 = pb % 16 == 0;
     s.wide_pitch = ldb > 0x3fffffffLL;
     s.N = N;
     return s;
@@ -787,15 +902,14 @@ bool share_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
     return sh.al4 && (uint64_t)A->k * (uint64_t)ldb * 4u <= 0xffffffffull - 4096u;
 }
 
-bool rows_possible(const gcoo_matrix* A, int64_t ldb, int64_t N)
+bool band_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
 {
-    return A->has_rows() && N >= 4 && A->k >= 1 && (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
+    const bool aligned = sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16;
+    return (aligned || sh.N >= 256) && (uint64_t)A->k * (uint64_t)ldb * 4u <= 0xffffffffull;
 }
 
-// Where the automatic choice is the row-by-row kernel.  It moves 4 x nnz x N bytes through the vector caches; the kernels
-// that work on groups move less the more entries share a column of a group, but need thousands of wave-sized items.  Measured
-// on uniform random matrices: level at about 40 entries per row (n = 4000: 1.2 %, n = 8000: 0.45 %; 30 where rows of B do not
-// start at 128-byte lines), and at well above a hundred where the groups' items fill less than half of the 2048 wave slots.
+// Row by row before the register kernel, for a handle that carries the run schedule: up to about 30 entries per row (n = 4000: level at
+// 1.2 %, n = 8000: 0.45 %), and well above a hundred where the groups' items fill less than half of the 2048 wave slots.
 bool rows_preferred(const gcoo_matrix* A, int64_t N)
 {
     if (A->nnz <= 28 * A->m) return true;
@@ -825,7 +939,7 @@ int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_
     const int64_t items = A->share_nq() * ((N + 255) / 256);
     if (A->share_preferred && share_operands_ok(A, sh, ldb) && items >= 192 && (A->k >= 9000 || fill_of_rounds(items) >= 0.8))
         return GCOO_VARIANT_SHARE;
-    return (A->has_sched && sched_width(A->p, sh)) ? GCOO_VARIANT_REG : GCOO_VARIANT_LDS;
+    return (A->has_rows() && sched_width(A->p, sh)) ? GCOO_VARIANT_REG : GCOO_VARIANT_LDS;
 }
 
 int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N, float* C_dev, int64_t ldc,
@@ -839,7 +953,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     if (A->m == 0 || N == 0) return GCOO_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (variant == GCOO_VARIANT_LDS) {
+    if (variant == GCOO_VARIANT_LDS && !(automatic && A->k >= 1)) {
         const int64_t tiles = (N + 63) / 64;
         const int64_t total = A->g * tiles;
         if (total > 0x7fffffffLL) return GCOO_EINVAL;
@@ -850,23 +964,37 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         return GCOO_OK;
     }
     if (A->inner) A = A->inner;        // the schedules of the kernels below belong to the regrouped copy
-    if (automatic && rows_possible(A, ldb, N) && rows_preferred(A, N)) {
-        gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc};
+    const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
+    auto run_rows = [&]() -> int {
+        gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
+                         A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
         hipError_t e = gcoo::launch_spdm_rows(a, s);
-        if (e != hipSuccess) return hip_fail(e, "spdm_rows launch");
-        return GCOO_OK;
+        return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
+    };
+    auto run_band = [&]() -> int {
+        gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band_h), A->L.band_h,
+                         0, 0, gcoo::band_head_stride(A->k), A->m, A->k, B_dev, ldb, N, C_dev, ldc};
+        hipError_t e = gcoo::launch_spdm_band(a, s);
+        return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_band launch");
+    };
+    if (automatic && A->has_rows() && A->k >= 1) {
+        const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
+        if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) && band_time(A->m, A->k, A->nnz, N, A->L.band_h) < rows_time(A->m, A->k, A->nnz, N, lines))
+            return run_band();
+        if (!A->has_sched || rows_preferred(A, N)) return run_rows();
     }
     if (variant == GCOO_VARIANT_SHARE) {
-        const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
-        if (!A->has_share || !share_operands_ok(A, sh, ldb)) return GCOO_EINVAL;
+        if (!share_operands_ok(A, sh, ldb)) return GCOO_EINVAL;
+        if (!A->has_share) return A->share_preferred && band_operands_ok(A, sh, ldb) ? run_band() : GCOO_EINVAL;
         gcoo::ShareArgs a{A->share_hdr(), A->share_blocks(), A->share_sbase(), A->share_ucols(), A->share_ucount(), A->gIdxes(),
                           A->m, A->p, A->g, A->share_nq(), B_dev, ldb, N, C_dev, ldc};
         hipError_t e = gcoo::launch_spdm_share(a, s);
         if (e != hipSuccess) return hip_fail(e, "spdm_share launch");
         return GCOO_OK;
     }
-    const int V = sched_width(A->p, shape_of(B_dev, ldb, N, C_dev, ldc));
-    if (V == 0 || !A->has_sched) return GCOO_EINVAL;
+    const int V = sched_width(A->p, sh);
+    if (V == 0 || !A->has_rows()) return GCOO_EINVAL;
+    if (!A->has_sched) return run_rows();
     const int cols_per_lane = V == kTallInstance ? 4 : V;
     // Heavy groups are shared by a workgroup in the standard instances only, and only a launch of few
     // items can have any: then the kernels decide group by group, from the statistics on the device.
@@ -930,7 +1058,13 @@ int gcoo_export(const gcoo_matrix* A, float* values, int32_t* rows, int32_t* col
 int gcoo_export_share(const gcoo_matrix* A, uint32_t* hdr, uint32_t* blocks, int32_t* sbase, int32_t* ucount, int32_t* ucols,
                       int64_t* hdr_words, int64_t* block_count, void* stream)
 {
-    if (!A || !A->has_share) return GCOO_EINVAL;
+    if (!A) return GCOO_EINVAL;
+    if (!A->has_share) {
+        if (!A->share_preferred) return GCOO_EINVAL;
+        if (hdr_words) *hdr_words = 0;
+        if (block_count) *block_count = 0;
+        return GCOO_OK;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t hw = gcoo::share_hdr_words(A->nnz, A->g), nb = gcoo::share_stream_blocks(A->nnz, A->g, A->k);
     if (hdr_words) *hdr_words = hw;

@@ -58,7 +58,8 @@ __global__ __launch_bounds__(256) void group_index_from_row_ptr(const int32_t* _
                                                                  uint32_t* __restrict__ bad_col, int32_t* __restrict__ row_start)
 {
     if (stats && blockIdx.x == gridDim.x - 1) {                   // the whole workgroup
-        if (threadIdx.x == 0) *bad_col = 0u;                      // set by the sort that follows if it meets a column out of range
+        // bad_col[0] is set by the sort that follows if it meets a column out of range, bad_col[1] counts the rows it lists as long
+        if (threadIdx.x < 2) bad_col[threadIdx.x] = 0u;
         group_stats_block(row_ptr, m, p, g, stats);
         return;
     }
@@ -132,12 +133,28 @@ constexpr int kSortBucketWaves = 4;     // and of the one that sorts one bucket 
 
 enum SortPass { kSortFirst, kSortNext, kSortByRow };
 
+// What the row-by-row kernel reads, as far as the sorts write it (nothing where `cols` is null).
+struct RowsOut {
+    int32_t* cols;             // the entries in row order
+    float* vals;
+    int32_t* start;            // where the rows begin (read by kSortFirst, written by kSortByRow)
+    int32_t* long_rows;        // the rows of more than `long_row` entries, in any order; at most long_room of them
+    int32_t* long_count;
+    int32_t long_row, long_room;
+};
+__device__ __forceinline__ void list_long_row(const RowsOut& out, int32_t row, int32_t entries)
+{
+    if (entries <= out.long_row) return;
+    const int32_t at = atomicAdd(out.long_count, 1);
+    if (at < out.long_room) out.long_rows[at] = row;
+}
+
 template <SortPass PASS, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
     const int32_t* __restrict__ gIdxes, const int32_t* __restrict__ row_ptr, int64_t m, int32_t p,
     const int32_t* __restrict__ src_cols, const int32_t* __restrict__ src_rows, const float* __restrict__ src_vals,
     int32_t* __restrict__ dst_cols, int32_t* __restrict__ dst_rows, float* __restrict__ dst_vals, int shift, int32_t nb,
-    int32_t kcols, uint32_t* __restrict__ bad_col, int32_t* __restrict__ row_cols, float* __restrict__ row_vals)
+    int32_t kcols, uint32_t* __restrict__ bad_col, RowsOut out)
 {
     constexpr bool FIRST = PASS == kSortFirst, BY_ROW = PASS == kSortByRow;
     // FIRST: a column of the input outside [0, kcols) is stored clamped into that range and reported in
@@ -175,6 +192,7 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
         const int64_t r_hi = (r_lo + p < m) ? r_lo + p : m;
         static_assert(!FIRST || WAVES * kWave >= 257, "one thread per row of the group, and one more");
         if (tid <= r_hi - r_lo) rp_s[tid] = row_ptr[r_lo + tid];     // the barriers below publish it
+        if (out.cols && tid < r_hi - r_lo) list_long_row(out, (int32_t)r_lo + tid, out.start[r_lo + tid + 1] - out.start[r_lo + tid]);
     }
     // part of wave wv: whole 64-entry tiles
     const int32_t tiles = (end - beg + kWave - 1) / kWave;
@@ -223,9 +241,12 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
     }
     __syncthreads();
     for (int i = tid; i < WAVES * 256; i += WAVES * kWave) (&slot_of[0][0])[i] += total[i & 255];
-    if (BY_ROW) {                                    // where the rows of the group begin (dst_rows: row_start); the last group adds the end
-        if (tid < p && row_first + tid < m) dst_rows[row_first + tid] = beg + total[tid];
-        if (tid == 0 && row_first + p >= m) dst_rows[m] = end;
+    if (BY_ROW) {                                    // where the rows of the group begin; the last group adds the end
+        if (tid < p && row_first + tid < m) {
+            out.start[row_first + tid] = beg + total[tid];
+            list_long_row(out, row_first + tid, total[tid + 1] - total[tid]);
+        }
+        if (tid == 0 && row_first + p >= m) out.start[m] = end;
     }
     __syncthreads();
 
@@ -257,9 +278,9 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
             if (FIRST) {
                 const int32_t c = in_range(col);
                 if (c != col) { *bad_col = 1u; col = c; }
-                if (row_cols) {                                   // the entries in row order, as they came
-                    row_cols[e] = col;
-                    row_vals[e] = val;
+                if (out.cols) {                                   // the entries in row order, as they came
+                    out.cols[e] = col;
+                    out.vals[e] = val;
                 }
                 // row r with row_ptr[r] <= e < row_ptr[r+1]; empty rows are skipped by the upper bound
                 int32_t lo = 0, hi = (int32_t)(r_hi - r_lo);      // answer in [lo, hi), relative to the group's first row

@@ -62,8 +62,7 @@ struct ShareArgs {
 };
 hipError_t launch_spdm_share(const ShareArgs& a, hipStream_t s);
 
-// The kernel that works row by row on the entries in row order: N >= 4, k >= 1, and B (its k rows at pitch ldb) within
-// 4 GB less 128 KB; any alignment of 4 bytes.
+// The kernel that works row by row on the entries in row order: any N, ldb < 2^30, any alignment of 4 bytes, k >= 1.
 struct RowsArgs {
     const int32_t* row_ptr;    // [m + 1]
     const int32_t* cols;       // [nnz]
@@ -76,8 +75,39 @@ struct RowsArgs {
     int64_t N;
     float* C;
     int64_t ldc;
+    const int32_t* long_rows;  // the rows of more than `long_row` entries, in any order
+    const int32_t* long_count;
+    int32_t long_row, long_room;
 };
+// A row of more entries than this is shared by a whole workgroup.
+inline int32_t rows_long(int64_t m, int64_t nnz)
+{
+    const int64_t n = m > 0 ? 8 * (nnz / m) : 0;
+    return (int32_t)(n < 512 ? 512 : (n > INT32_MAX ? INT32_MAX : n));
+}
 constexpr uint64_t kRowsMaxBytes = 0xfffe0000ull;
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s);
+
+
+// The sixteen-wave kernel that reads the band schedule (gcoo_band.hpp): N >= 256, or N, ldb a multiple of 4 and B 16-byte aligned; every row offset
+// of B in bytes below 2^32.
+struct BandArgs {
+    const uint32_t* head;
+    const uint32_t* units;
+    const int32_t* first;      // [16 * blocks] first unit of every wave
+    const int32_t* count;      // [blocks] distinct columns
+    int32_t blocks;
+    int32_t h;                 // rows per wave
+    int32_t total, grid;       // workgroups with work, workgroups launched (set by the launcher)
+    int64_t head_stride;
+    int64_t m;
+    int64_t k;
+    const float* B;
+    int64_t ldb;
+    int64_t N;
+    float* C;
+    int64_t ldc;
+};
+hipError_t launch_spdm_band(const BandArgs& a, hipStream_t s);
 
 }  // namespace gcoo

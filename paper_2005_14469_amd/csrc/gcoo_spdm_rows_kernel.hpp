@@ -12,8 +12,11 @@
 //             add, one load and four multiply-adds for 4 x 64 columns at LPR = 16
 //   ends      entries past the end of a row have an offset beyond the buffer descriptor's range: the load returns zero
 //             without touching memory, so a non-finite B row that no entry touches stays out of C
-//   long rows rows of more than `wave_row` entries are shared by the slots of the wave, of more than `group_row` by those of
-//             the workgroup: equal stretches, partial sums added in a fixed order, so the bits are the same on every run
+//   long rows rows of more than `wave_row` entries, and of three times what the rows beside them have, are shared by the slots of the
+//             wave: equal stretches, partial sums added in a fixed order, so the bits are the same on every run.  Rows of more
+//             than rows_long() are shared by a workgroup and come first: the conversion lists them, and the workgroups of a column
+//             tile take one each before their own rows, so that none of them starts when the others have ended
+//             (power-law rows, 16384 x 16384, 50 entries on average, N = 512: 100 us; with those of its own rows last 112)
 //
 // Bound: the vector cache (64 bytes per clock and compute unit), 4 x nnz x N bytes; a tile of 64 columns of B stays in an
 // XCD's L2 up to 16384 columns of A, so each row of B comes from memory about once per tile.  Measured (product alone,
@@ -45,13 +48,23 @@ __device__ __forceinline__ uint32_t rows_bcast(const uint32_t (&x)[LPR >= 16 ? 1
 
 struct RowsAcc { float x[4]; };
 
-template <int LPR, int CNT, int I>
-__device__ __forceinline__ void rows_load(const uint32_t (&off)[LPR >= 16 ? 1 : 4], uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc,
-                                          rows_u32x4 (&b)[CNT])
+// WIDE (a B of more than 4 GB): `off` holds columns, 0xffffffff past the end, and the address is formed in 64 bits.
+struct RowsB {
+    __amdgpu_buffer_rsrc_t rsrc;
+    const char* base;          // WIDE: B, at the descriptor's place
+    uint64_t pitch;            // WIDE: bytes
+};
+template <int LPR, int CNT, int I, bool WIDE>
+__device__ __forceinline__ void rows_load(const uint32_t (&off)[LPR >= 16 ? 1 : 4], uint32_t lane_off, const RowsB& B, rows_u32x4 (&b)[CNT])
 {
     if constexpr (I < CNT) {
-        b[I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(rows_bcast<LPR, I>(off) + lane_off), 0, 0);
-        rows_load<LPR, CNT, I + 1>(off, lane_off, rsrc, b);
+        if constexpr (WIDE) {
+            const uint32_t col = rows_bcast<LPR, I>(off);
+            b[I] = 0u;
+            if (col != 0xffffffffu) __builtin_memcpy(&b[I], B.base + (uint64_t)col * B.pitch + lane_off, 16);
+        } else
+        b[I] = __builtin_amdgcn_raw_buffer_load_b128(B.rsrc, (int)(rows_bcast<LPR, I>(off) + lane_off), 0, 0);
+        rows_load<LPR, CNT, I + 1, WIDE>(off, lane_off, B, b);
     }
 }
 template <int LPR, int CNT, int I>
@@ -64,12 +77,12 @@ __device__ __forceinline__ void rows_fma(const uint32_t (&val)[LPR >= 16 ? 1 : 4
         rows_fma<LPR, CNT, I + 1>(val, b, acc);
     }
 }
-template <int LPR, int CNT>
+template <int LPR, int CNT, bool WIDE>
 __device__ __forceinline__ void rows_batch(const uint32_t (&off)[LPR >= 16 ? 1 : 4], const uint32_t (&val)[LPR >= 16 ? 1 : 4],
-                                           uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc, RowsAcc& acc)
+                                           uint32_t lane_off, const RowsB& B, RowsAcc& acc)
 {
     rows_u32x4 b[CNT];
-    rows_load<LPR, CNT, 0>(off, lane_off, rsrc, b);
+    rows_load<LPR, CNT, 0, WIDE>(off, lane_off, B, b);
     rows_fma<LPR, CNT, 0>(val, b, acc);
 }
 
@@ -92,52 +105,57 @@ struct RowsBatch {
             }
         }
     }
+    template <bool WIDE>
     __device__ __forceinline__ void offsets(uint32_t kmax, uint32_t ldb4)
     {
         constexpr uint32_t kNowhere = 0xffff0000u;         // beyond the range of every descriptor (the launcher checks it)
 #pragma unroll
-        for (int j = 0; j < REGS; ++j) c[j] = c[j] == 0xffffffffu ? kNowhere : (c[j] < kmax ? c[j] : kmax) * ldb4;
+        for (int j = 0; j < REGS; ++j) {
+            const bool none = c[j] == 0xffffffffu;
+            c[j] = c[j] < kmax ? c[j] : kmax;
+            if constexpr (WIDE) c[j] = none ? 0xffffffffu : c[j];
+            else c[j] = none ? kNowhere : c[j] * ldb4;
+        }
     }
 };
 
 // The batch in steps of two entries: as many as the fullest slot of the wave has (a load past a row's end returns at once but
 // holds the address path as long as any other).
-template <int LPR, int CNT>
-__device__ __forceinline__ void rows_pick(int32_t left, const RowsBatch<LPR>& now, uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc, RowsAcc& acc)
+template <int LPR, int CNT, bool WIDE>
+__device__ __forceinline__ void rows_pick(int32_t left, const RowsBatch<LPR>& now, uint32_t lane_off, const RowsB& B, RowsAcc& acc)
 {
     if (__any(left > CNT - 2)) {
-        rows_batch<LPR, CNT>(now.c, now.v, lane_off, rsrc, acc);
+        rows_batch<LPR, CNT, WIDE>(now.c, now.v, lane_off, B, acc);
     } else {
-        if constexpr (CNT > 2) rows_pick<LPR, CNT - 2>(left, now, lane_off, rsrc, acc);
+        if constexpr (CNT > 2) rows_pick<LPR, CNT - 2, WIDE>(left, now, lane_off, B, acc);
     }
 }
 
 // Adds the entries [base, end) of the slot's row (every lane of the wave calls it; the slots may have different ranges).
 // `next` holds the first batch already; on return it holds the batch [more, more_end), requested in front of the loads of
 // the last batch.
-template <int LPR>
+template <int LPR, bool WIDE>
 __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end,
-                                             uint32_t kmax, uint32_t ldb4, uint32_t lane_off, __amdgpu_buffer_rsrc_t rsrc, int lane, RowsAcc& acc)
+                                             uint32_t kmax, uint32_t ldb4, uint32_t lane_off, const RowsB& B, int lane, RowsAcc& acc)
 {
     while (true) {
         RowsBatch<LPR> now = next;
-        now.offsets(kmax, ldb4);
+        now.template offsets<WIDE>(kmax, ldb4);
         const int32_t left = end - base;
         base += 16;
         const bool last = !__any(base < end);
         next.request(a, last ? more : base, last ? more_end : end, lane);
-        rows_pick<LPR, 16>(left, now, lane_off, rsrc, acc);
+        rows_pick<LPR, 16, WIDE>(left, now, lane_off, B, acc);
         if (last) return;
     }
 }
 
 // Workgroup (tile, wg): rows [wg * 4 * rpw, ...), `rpw` of them per wave, columns of the tile.
-template <int LPR>
-__global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, int32_t group_row)
+template <int LPR, bool WIDE>
+__global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
 {
     constexpr int SPW = 64 / LPR, WAVES = kRowsThreads / 64, SLOTS = SPW * WAVES, TILE = LPR * 4;
     __shared__ __attribute__((aligned(16))) float part[SLOTS][TILE];
-    __shared__ int32_t listed, list[WAVES * kRowsPerWave];
     // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
     // eight XCDs work on eight tiles side by side, so that what they read and write of a row at about the same time is one
     // stretch of 2 KB.  The tiles beyond the last whole eight are cut into eight slices of rows.
@@ -154,14 +172,13 @@ __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t
     }
     const int lane = threadIdx.x & 63, slot = lane / LPR, sl = lane % LPR;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x == 0) listed = 0;
-    __syncthreads();
     const int64_t j0 = (int64_t)tile * TILE;                          // first column of the tile, less up to 31 (place())
     // The descriptor starts at or before the first column any lane of the tile loads.
     const int64_t jb = j0 - 31 < 0 ? 0 : (j0 - 31 < a.N - 4 ? j0 - 31 : a.N - 4);
     const char* bbase = reinterpret_cast<const char*>(a.B + jb);
     const uint64_t bytes = ((uint64_t)(a.k - 1) * (uint64_t)a.ldb + (uint64_t)a.N - (uint64_t)jb) * 4u;
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(bbase), 0, (int)(uint32_t)bytes, 0x00027000);
+    const RowsB B = {rsrc, bbase, (uint64_t)a.ldb * 4u};
     const uint32_t ldb4 = (uint32_t)a.ldb * 4u, kmax = (uint32_t)(a.k - 1);
     // A lane's columns in row r: the tile is moved down by what the row's start in C lies past a 128-byte line, so that the
     // stores of a slot are whole lines whatever N and ldc are.  A lane that would reach outside [0, N) loads four columns
@@ -193,64 +210,18 @@ __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
     // where the wave's rows begin (lane i: row w0 + i)
     const int32_t start = lane <= wrows && wrows > 0 ? a.row_ptr[w0 + lane] : 0;
-    auto bounds = [&](int32_t i, int32_t* beg, int32_t* end) {                      // of the wave's row i (empty past the last)
-        const int32_t b = __shfl(start, i, 64), e = __shfl(start, i + 1, 64);
-        *beg = b;
-        *end = i < wrows ? e : b;
-    };
-    int32_t beg, end;
-    bounds(slot, &beg, &end);
-    RowsBatch<LPR> next;
-    bool whole = end - beg > wave_row;                                              // the row is left to all slots of the wave, or of the workgroup
-    next.request(a, beg, whole ? beg : end, lane);
-    for (int32_t i = 0; i < wrows; i += SPW) {
-        const int32_t r = w0 + i + slot;
-        int32_t beg2, end2;
-        bounds(i + SPW + slot, &beg2, &end2);
-        const bool whole2 = end2 - beg2 > wave_row;
-        const Place pl = place(r);
-        RowsAcc acc = {{0.0f, 0.0f, 0.0f, 0.0f}};
-        rows_entries<LPR>(a, next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, kmax, ldb4, (uint32_t)(pl.jc - (int32_t)jb) * 4u, rsrc, lane, acc);
-        if (i + slot < wrows && !whole) store(r, pl, acc);
-        uint64_t todo = __ballot(whole && sl == 0);
-        while (todo) {                                                              // wave-uniform
-            const int32_t s = (__ffsll((long long)todo) - 1) / LPR;
-            todo &= todo - 1;
-            const int32_t lb = __builtin_amdgcn_readlane(start, i + s), le = __builtin_amdgcn_readlane(start, i + s + 1);
-            const int32_t lr = w0 + i + s, n = le - lb;
-            if (n > group_row) {
-                if (lane == 0) list[atomicAdd(&listed, 1)] = lr;
-                continue;
-            }
-            // equal stretches for the slots, their sums added up in a fixed tree
-            const int32_t each = (n + SPW - 1) / SPW, b = lb + slot * each, e = b + each < le ? b + each : le;
-            const Place lpl = place(lr);
-            RowsBatch<LPR> mine;
-            mine.request(a, b, e, lane);
-            RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
-            rows_entries<LPR>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, rsrc, lane, sum);
-#pragma unroll
-            for (int d = LPR; d < 64; d <<= 1)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) sum.x[u] += __shfl_xor(sum.x[u], d, 64);
-            if (slot == 0) store(lr, lpl, sum);
-        }
-        beg = beg2;
-        end = end2;
-        whole = whole2;
-    }
-    // the longest rows of this workgroup, one after another, all its slots on each
-    __syncthreads();
-    const int32_t n_list = listed;
-    for (int32_t x = 0; x < n_list; ++x) {
-        const int32_t lr = __builtin_amdgcn_readfirstlane(list[x]);
+    // the long rows, all slots of the workgroup on each
+    int32_t n_long = *a.long_count;
+    n_long = n_long < a.long_room ? n_long : a.long_room;
+    for (int32_t x = wg; x < n_long; x += row_wgs) {
+        const int32_t lr = __builtin_amdgcn_readfirstlane(a.long_rows[x]);
         const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
         const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + slot) * each, e = b + each < le ? b + each : le;
         const Place lpl = place(lr);
         RowsBatch<LPR> mine;
         mine.request(a, b, e, lane);
         RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
-        rows_entries<LPR>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, rsrc, lane, sum);
+        rows_entries<LPR, WIDE>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, B, lane, sum);
 #pragma unroll
         for (int u = 0; u < 4; ++u) part[wv * SPW + slot][sl * 4 + u] = sum.x[u];
         __syncthreads();
@@ -262,6 +233,89 @@ __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t
         }
         __syncthreads();
     }
+
+    auto bounds = [&](int32_t i, int32_t* beg, int32_t* end) {                      // of the wave's row i (empty past the last)
+        const int32_t b = __shfl(start, i, 64), e = __shfl(start, i + 1, 64);
+        *beg = b;
+        *end = i < wrows ? e : b;
+    };
+    int32_t beg, end;
+    bounds(slot, &beg, &end);
+    // the row is left to all slots of the wave (or, when it is a long one, to nobody here)
+    auto shared = [&](int32_t n) {
+        if (!__any(n > 16)) return n > wave_row;
+        int32_t all = n;
+#pragma unroll
+        for (int d = LPR; d < 64; d <<= 1) all += __shfl_xor(all, d, 64);
+        return n > wave_row || (n > 16 && n * (SPW - 1) > 3 * (all - n));
+    };
+    RowsBatch<LPR> next;
+    bool whole = shared(end - beg);
+    next.request(a, beg, whole ? beg : end, lane);
+    for (int32_t i = 0; i < wrows; i += SPW) {
+        const int32_t r = w0 + i + slot;
+        int32_t beg2, end2;
+        bounds(i + SPW + slot, &beg2, &end2);
+        const bool whole2 = shared(end2 - beg2);
+        const Place pl = place(r);
+        RowsAcc acc = {{0.0f, 0.0f, 0.0f, 0.0f}};
+        rows_entries<LPR, WIDE>(a, next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, kmax, ldb4, (uint32_t)(pl.jc - (int32_t)jb) * 4u, B, lane, acc);
+        if (i + slot < wrows && !whole) store(r, pl, acc);
+        uint64_t todo = __ballot(whole && sl == 0);
+        while (todo) {                                                              // wave-uniform
+            const int32_t s = (__ffsll((long long)todo) - 1) / LPR;
+            todo &= todo - 1;
+            const int32_t lb = __builtin_amdgcn_readlane(start, i + s), le = __builtin_amdgcn_readlane(start, i + s + 1);
+            const int32_t lr = w0 + i + s, n = le - lb;
+            if (n > a.long_row) continue;
+            // equal stretches for the slots, their sums added up in a fixed tree
+            const int32_t each = (n + SPW - 1) / SPW, b = lb + slot * each, e = b + each < le ? b + each : le;
+            const Place lpl = place(lr);
+            RowsBatch<LPR> mine;
+            mine.request(a, b, e, lane);
+            RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
+            rows_entries<LPR, WIDE>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, B, lane, sum);
+#pragma unroll
+            for (int d = LPR; d < 64; d <<= 1)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sum.x[u] += __shfl_xor(sum.x[u], d, 64);
+            if (slot == 0) store(lr, lpl, sum);
+        }
+        beg = beg2;
+        end = end2;
+        whole = whole2;
+    }
+}
+
+// B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a
+// fixed tree.
+template <int N>
+__global__ __launch_bounds__(kRowsThreads) void spdm_vectors(RowsArgs a)
+{
+    const int lane = threadIdx.x & 15;
+    const int64_t r = (int64_t)blockIdx.x * (kRowsThreads / 16) + (threadIdx.x >> 4);
+    const uint32_t kmax = (uint32_t)(a.k - 1);
+    float sum[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) sum[n] = 0.0f;
+    if (r < a.m) {
+        const int32_t end = a.row_ptr[r + 1];
+        for (int32_t e = a.row_ptr[r] + lane; e < end; e += 16) {
+            uint32_t c = (uint32_t)a.cols[e];
+            c = c < kmax ? c : kmax;
+            const float v = a.vals[e];
+            const float* b = a.B + (int64_t)c * a.ldb;
+#pragma unroll
+            for (int n = 0; n < N; ++n) sum[n] = __builtin_fmaf(v, b[n], sum[n]);
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) sum[n] += __shfl_xor(sum[n], d, 16);
+    if (r < a.m && lane == 0)
+#pragma unroll
+        for (int n = 0; n < N; ++n) a.C[r * a.ldc + n] = sum[n];
 }
 
 }  // namespace gcoo

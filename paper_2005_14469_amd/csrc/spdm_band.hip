@@ -1,0 +1,40 @@
+// The sixteen-wave SpDM kernel that reads the band schedule, and its launcher.
+#include "gcoo_spdm_band_kernel.hpp"
+
+#include <atomic>
+
+namespace gcoo {
+
+template <bool UNALIGNED>
+static hipError_t launch_band(const BandArgs& a, hipStream_t s)
+{
+    // more LDS than the default limit of a workgroup: asked for once per device
+    static std::atomic<unsigned> done[64];
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!done[dev].load(std::memory_order_acquire)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<UNALIGNED>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
+        if (e != hipSuccess) return e;
+        done[dev].store(1u, std::memory_order_release);
+    }
+    spdm_band<UNALIGNED><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_spdm_band(const BandArgs& a, hipStream_t s)
+{
+    const int64_t tiles = (a.N + 255) / 256, total = a.blocks * tiles;
+    if (total <= 0 || total > 0x7ffffff0LL) return hipErrorInvalidConfiguration;
+    if (a.h < 1 || a.h > kBandMaxH || a.blocks != band_blocks(a.m, a.h) || a.head_stride != band_head_stride(a.k)) return hipErrorInvalidValue;
+    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > 0xffffffffull) return hipErrorInvalidValue;
+    const bool aligned = a.N % 4 == 0 && a.ldb % 4 == 0 && reinterpret_cast<uintptr_t>(a.B) % 16 == 0;
+    if (!aligned && a.N < 256) return hipErrorInvalidValue;
+    BandArgs b = a;
+    b.total = (int32_t)total;
+    b.grid = (int32_t)((total + 7) / 8 * 8);                 // whole rounds over the 8 XCDs
+    return aligned ? launch_band<false>(b, s) : launch_band<true>(b, s);
+}
+
+}  // namespace gcoo

@@ -3,7 +3,7 @@
 
 namespace gcoo {
 
-template <int LPR>
+template <int LPR, bool WIDE = false>
 static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
 {
     constexpr int64_t waves = kRowsThreads / 64, tile = 4 * LPR, spw = 64 / LPR;
@@ -24,19 +24,26 @@ static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
     const int64_t row_wgs = groups(rpw);
     const int64_t rest = tiles % 8 * row_wgs, grid = tiles / 8 * 8 * row_wgs + (rest + 7) / 8 * 8;
     if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them,
-    // and of the workgroup from eight times the mean on (power-law rows of 53 entries on average: 111 us, 139 without).
+    // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them.
     const int64_t wave_row = rpw < spw ? 8 : (2 * mean > 64 ? 2 * mean : 64);
-    const int64_t group_row = 8 * mean > 512 ? 8 * mean : 512;
-    spdm_rows<LPR><<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw,
-                                                                     (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row),
-                                                                     (int32_t)(group_row > INT32_MAX ? INT32_MAX : group_row));
+    spdm_rows<LPR, WIDE><<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw,
+                                                                     (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row));
     return hipGetLastError();
 }
 
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
 {
-    if (a.m < 1 || a.N < 4 || a.k < 1 || (uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return hipErrorInvalidValue;
+    if (a.m < 1 || a.k < 1 || a.N < 1 || a.ldb > 0x3fffffffLL) return hipErrorInvalidValue;
+    if (a.N < 4) {
+        constexpr int64_t rows = kRowsThreads / 16;
+        const int64_t grid = (a.m + rows - 1) / rows;
+        if (a.N == 1) spdm_vectors<1><<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a);
+        else if (a.N == 2) spdm_vectors<2><<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a);
+        else spdm_vectors<3><<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a);
+        return hipGetLastError();
+    }
+    // a B of more than 4 GB is beyond the offsets of a buffer descriptor
+    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows<16, true>(a, s);
     // 64, 32 or 16 columns per tile: the fewest lanes without a column of their own
     if (a.N <= 16) return launch_rows<4>(a, s);
     if (a.N <= 32) return launch_rows<8>(a, s);

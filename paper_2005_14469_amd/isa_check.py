@@ -187,7 +187,7 @@ def check(asm_text: str, mangled_prefix: str):
 
 
 def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0):
-    """Loads that write LDS directly (`global_load_lds_*`) in a kernel that also uses the VGPR index mode.
+    """Loads that write LDS directly (`global_load_lds_*`, `buffer_load_* ... lds`) in a kernel that also uses the VGPR index mode.
 
     Such a load takes the LDS address of lane 0 from M0, and `s_set_gpr_idx_on/idx` overwrite M0.
     Returns (number of such loads, list of problems).  Proved on the text, block by block:
@@ -200,10 +200,13 @@ def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0):
     """
     body = [l.split(";")[0].strip() for l in kernel_body(asm_text, mangled_prefix)]
     body = [l for l in body if l]
+    def to_lds(t):
+        return t.startswith("global_load_lds") or (t.startswith("buffer_load") and t.endswith(" lds"))
+
     problems = []
     loads = 0
     for i, line in enumerate(body):
-        if line.startswith("global_load_lds"):
+        if to_lds(line):
             loads += 1
             j = i - 1
             while j >= 0:
@@ -223,12 +226,40 @@ def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0):
                 waited = re.search(r"vmcnt\((\d+)\)", t) if t.startswith("s_waitcnt") else None
                 if waited and int(waited.group(1)) <= in_flight:
                     break
-                if t.startswith("global_load_lds"):
+                if to_lds(t):
                     problems.append(f"line {i}: barrier with a load to LDS ('{t}') not awaited")
                     break
                 if _LABEL.match(t):            # the walk stays in the block: a barrier that opens a block is judged unsafe
-                    if any(b.startswith("global_load_lds") for b in body):
+                    if any(to_lds(b) for b in body):
                         problems.append(f"line {i}: barrier at the start of a block, no wait seen")
                     break
                 j -= 1
     return loads, problems
+
+
+def asm_scalar_writes(asm_text: str, mangled_prefix: str):
+    """(scalar registers written, scalar registers only read) by the asm statements of a kernel: the first set has to be what
+    their clobber lists name, or the compiler may keep something of its own there."""
+    def regs(text):
+        out = set()
+        for m in re.finditer(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", text):
+            out |= set(range(int(m.group(1)), int(m.group(2)) + 1)) if m.group(1) else {int(m.group(3))}
+        return out
+
+    written, read, in_asm = set(), set(), False
+    for l in kernel_body(asm_text, mangled_prefix):
+        if "#ASMSTART" in l or "#ASMEND" in l:
+            in_asm = "#ASMSTART" in l
+            continue
+        t = l.split(";")[0].strip()
+        if not in_asm or not t or t.startswith("."):
+            continue
+        op, _, rest = t.partition(" ")
+        ops = rest.split(",")
+        writes = op.startswith("s_") and not re.match(r"s_(cbranch|branch|barrier|waitcnt|nop|cmp|bitcmp|set_gpr_idx)", op) or op.startswith("v_read")
+        if writes:
+            written |= regs(ops[0])
+            ops = ops[1:]
+        for x in ops:
+            read |= regs(x)
+    return written, read - written

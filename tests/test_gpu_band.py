@@ -1,0 +1,89 @@
+"""The sixteen-wave kernel that reads the band schedule, at the sizes where it can go wrong: one, two and three bands full and with
+one column over, lists with one unit and with several, last steps of a unit, more rows than a block, widths around a tile,
+rows of B aligned to 4 bytes only, repeated coordinates.  Against the CPU oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gcoo_oracle as orc
+from paper_2005_14469_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _run(w, p, variant, shift=0, pad=0):
+    Bbig = torch.zeros((w.k, w.N + shift + pad), device=DEV)
+    Bbig[:, shift:shift + w.N] = torch.from_numpy(w.B).to(DEV)
+    dev = [torch.from_numpy(x).to(DEV) for x in (w.row_ptr, w.col_idx, w.vals)]
+    outs = []
+    for _ in range(2):                                     # two conversions: the same bits
+        A = binding.gcoo_from_csr(w.m, w.k, *dev, p, known_nnz=True)
+        Cbig = torch.full((w.m, w.N + shift + pad + 8), 7.0, device=DEV)
+        Cv = Cbig[:, shift:shift + w.N]
+        binding.gcoo_spdm(A, Bbig[:, shift:shift + w.N], Cv, variant=variant)
+        torch.cuda.synchronize()
+        assert torch.all(Cbig[:, :shift] == 7.0) and torch.all(Cbig[:, shift + w.N:] == 7.0)
+        outs.append(Cv.clone())
+    assert torch.equal(outs[0], outs[1])
+    C64, D64 = orc.spdm_csr(w.k, w.N, w.row_ptr, w.col_idx, w.vals, w.B)
+    err, bad = orc.max_scaled_error(outs[0].cpu().numpy(), C64, D64)
+    assert bad == 0 and err < 2e-6, (err, bad)
+
+
+def _columns_used(m, k, used, per_row, N, seed):
+    """m rows of `per_row` entries in `used` of k columns (all of them used)."""
+    rng = np.random.default_rng(seed)
+    cols = np.sort(rng.choice(k, used, replace=False))
+    pick = np.stack([np.sort(rng.choice(used, per_row, replace=False)) for _ in range(m)])
+    for u in range(used):                                  # every column at least once
+        if not (pick == u).any():
+            pick[u % m, 0] = u
+            pick[u % m].sort()
+    rp = (np.arange(m + 1) * per_row).astype(np.int32)
+    return workloads.Workload("used", m, k, N, rp, cols[pick].reshape(-1).astype(np.int32),
+                              rng.standard_normal(m * per_row).astype(np.float32), rng.standard_normal((k, N)).astype(np.float32))
+
+
+@pytest.mark.parametrize("m,used,per_row,N", [(1, 60, 60, 4), (40, 80, 70, 256), (384, 81, 60, 260), (300, 160, 64, 512), (400, 161, 64, 252), (777, 240, 62, 516),
+                                              (97, 241, 130, 64)])
+def test_bands_full_and_one_column_over(m, used, per_row, N):
+    """3500 columns, of which few are used, at 1.5 % density and more: the shapes for which GCOO_VARIANT_SHARE is served."""
+    print(f"band: m={m} used={used} per_row={per_row} N={N}", flush=True)
+    _run(_columns_used(m, 3500, used, per_row, N, seed=m + used), 32, binding.VARIANT_SHARE)
+
+
+@pytest.mark.parametrize("m,k,N,s", [(100, 3500, 300, 0.94), (385, 3600, 1024, 0.98), (1000, 7000, 768, 0.995), (50, 20000, 260, 0.97)])
+def test_uniform_through_the_share_variant(m, k, N, s):
+    print(f"band: m={m} k={k} N={N} s={s}", flush=True)
+    _run(workloads.uniform_random(m, k, N, s, seed=m + k), 48, binding.VARIANT_SHARE)
+
+
+@pytest.mark.parametrize("m,k,N,s,shift,pad", [(4000, 4000, 1001, 0.95, 0, 0), (4000, 4000, 1000, 0.95, 1, 2), (3000, 3000, 2999, 0.7, 0, 0), (5000, 2600, 1280, 0.9, 0, 0)])
+def test_automatic_choice_ragged_and_dense(m, k, N, s, shift, pad):
+    """Large enough that the automatic choice is this kernel: N and rows of B that are no multiple of four, runs of pairs."""
+    print(f"band, automatic: m={m} k={k} N={N} s={s} shift={shift}", flush=True)
+    _run(workloads.uniform_random(m, k, N, s, seed=m + N), 32, binding.VARIANT_AUTO, shift, pad)
+
+
+def test_repeated_coordinates_and_skewed_rows():
+    rng = np.random.default_rng(8)
+    rows = []
+    for i in range(200):
+        c = list(rng.choice(3500, 60, replace=False))
+        if i % 9 == 0:
+            c += [17] * 45 + [18] * 70
+        rng.shuffle(c)                                      # columns of a row in any order
+        rows.append(np.array(c, np.int32))
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.concatenate(rows)
+    w = workloads.Workload("repeated", 200, 3500, 132, rp, ci, rng.standard_normal(len(ci)).astype(np.float32),
+                           rng.standard_normal((3500, 132)).astype(np.float32))
+    print("band: repeated coordinates", flush=True)
+    _run(w, 32, binding.VARIANT_SHARE)
+    z = workloads.zipf_rows(500, 3600, 256, seed=2, exponent=1.3, row_max=3500)
+    assert 0.015 * z.m * z.k < z.nnz < 0.06 * z.m * z.k
+    print("band: skewed rows", flush=True)
+    _run(z, 40, binding.VARIANT_SHARE)

@@ -71,6 +71,19 @@ def test_few_and_many_rows(m, k, N, n):
     _check(_rows_of_lengths([n] * m, k, N, seed=m), 32)
 
 
+@pytest.mark.parametrize("N", [1, 2, 3])
+def test_one_two_and_three_columns(N):
+    print(f"rows: N={N}", flush=True)
+    _check(_rows_of_lengths([0, 1, 15, 16, 17, 100, 3] * 7, 300, N, seed=N), 32, shift=1, pad=1)
+
+
+def test_b_of_more_than_4_gb():
+    """Offsets of rows of B beyond 32 bits."""
+    w = _rows_of_lengths([0, 20, 40, 3, 70] * 9, 2100, 72, seed=6)
+    print("rows: B of 8.8 GB", flush=True)
+    _check(w, 32, pad=(1 << 20) - 72)
+
+
 def test_repeated_and_non_finite():
     """Repeated coordinates add up; a row of B that no entry touches may hold anything."""
     w = _rows_of_lengths([30, 0, 5, 17] * 20, 12, 36, seed=4)              # more entries than columns: coordinates repeat
