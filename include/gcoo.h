@@ -164,6 +164,18 @@ int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32
                     gcoo_matrix** out);
 
 /*
+ * The same in the two steps of Algorithm 1, for a caller that sizes dev_buf by the count and reads A_dev for it only once:
+ * gcoo_dense_count() counts into count_buf (gcoo_dense_count_bytes() bytes of device memory, 256-byte aligned) and waits for
+ * *nnz; gcoo_from_dense_counted() takes that nnz and count_buf, which it only reads, with the same matrix, p and stream, and does
+ * not wait for the device.
+ */
+size_t gcoo_dense_count_bytes(int64_t m, int64_t k, int32_t p);
+int gcoo_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* count_buf, size_t count_buf_bytes,
+                     void* stream, int64_t* nnz);
+int gcoo_from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, int64_t lda, int32_t p, const void* count_buf,
+                            void* dev_buf, size_t dev_buf_bytes, void* stream, gcoo_matrix** out);
+
+/*
  * Algorithm 2 (GCOOSpDM): C = A x B, alpha = 1, beta = 0; every element of C (m x N) is
  * overwritten, rows of empty groups with +0.
  *   B_dev  k x N row-major device matrix, leading dimension ldb >= N

@@ -25,6 +25,7 @@ SHARE_AUTO, SHARE_ALWAYS, SHARE_NEVER = 0, 1, 2
 
 # every symbol include/gcoo.h declares
 SYMBOLS = ["gcoo_default_p", "gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_csr_device", "gcoo_dense_nnz", "gcoo_from_dense", "gcoo_spdm",
+           "gcoo_dense_count_bytes", "gcoo_dense_count", "gcoo_from_dense_counted",
            "gcoo_spdm_variant", "gcoo_spdm_pick", "gcoo_free", "gcoo_info", "gcoo_export",
            "gcoo_strerror", "gcoo_last_hip_error", "gcoo_set_share_policy", "gcoo_export_share",
            "gcoo_static_handle_bytes", "gcoo_from_csr_device_static"]
@@ -63,6 +64,12 @@ def lib():
         L.gcoo_dense_nnz.argtypes = [i64, i64, vp, i64, vp, C.POINTER(i64)]
         L.gcoo_from_dense.restype = C.c_int
         L.gcoo_from_dense.argtypes = [i64, i64, vp, i64, i32, vp, sz, vp, C.POINTER(vp)]
+        L.gcoo_dense_count_bytes.restype = sz
+        L.gcoo_dense_count_bytes.argtypes = [i64, i64, i32]
+        L.gcoo_dense_count.restype = C.c_int
+        L.gcoo_dense_count.argtypes = [i64, i64, vp, i64, i32, vp, sz, vp, C.POINTER(i64)]
+        L.gcoo_from_dense_counted.restype = C.c_int
+        L.gcoo_from_dense_counted.argtypes = [i64, i64, i64, vp, i64, i32, vp, vp, sz, vp, C.POINTER(vp)]
         L.gcoo_spdm.restype = C.c_int
         L.gcoo_spdm.argtypes = [vp, vp, i64, i64, vp, i64, vp]
         L.gcoo_spdm_variant.restype = C.c_int
@@ -256,15 +263,20 @@ def gcoo_from_dense(A: torch.Tensor, p: int, stream=None) -> GcooMatrix:
     """Algorithm 1 as the paper runs it: count, allocate by the count, fill."""
     assert A.is_cuda and A.dtype == torch.float32 and A.dim() == 2 and A.stride(1) == 1
     m, k = A.shape
-    nnz = gcoo_dense_nnz(A, stream)
-    need = gcoo_device_bytes(m, k, nnz, p)
-    if need == 0:
-        raise GcooError(GCOO_EINVAL, "gcoo_device_bytes")
+    L, lda = lib(), A.stride(0)
+    nbytes = L.gcoo_dense_count_bytes(m, k, p)
+    if nbytes == 0:
+        raise GcooError(GCOO_EINVAL, "gcoo_dense_count_bytes")
     with torch.cuda.device(A.device):
-        buf = _alloc(need, A.device)
-        out = C.c_void_p()
-        _check(lib().gcoo_from_dense(m, k, A.data_ptr(), A.stride(0), p, buf.data_ptr(), buf.numel(),
-                                     _stream_ptr(stream), C.byref(out)), "gcoo_from_dense")
+        sp = _stream_ptr(stream)
+        counts = _alloc(nbytes, A.device)
+        if stream is not None:
+            counts.record_stream(stream)
+        n, out = C.c_int64(), C.c_void_p()
+        _check(L.gcoo_dense_count(m, k, A.data_ptr(), lda, p, counts.data_ptr(), counts.numel(), sp, C.byref(n)), "gcoo_from_dense")
+        buf = _alloc(L.gcoo_device_bytes(m, k, n.value, p), A.device)
+        _check(L.gcoo_from_dense_counted(m, k, n.value, A.data_ptr(), lda, p, counts.data_ptr(), buf.data_ptr(), buf.numel(), sp,
+                                         C.byref(out)), "gcoo_from_dense")
     return GcooMatrix(out.value, buf)
 
 

@@ -13,6 +13,7 @@
 #include <atomic>
 #include <cmath>
 #include <mutex>
+#include <thread>
 
 #include "gcoo_band.hpp"
 #include "gcoo_band_build.hpp"
@@ -43,13 +44,76 @@ int hip_fail(hipError_t e, const char* what)
 constexpr size_t kAlign = 256;
 size_t al(size_t bytes) { return (bytes + kAlign - 1) / kAlign * kAlign; }
 
-// Device memory for gcoo_dense_nnz(), which is handed no device buffer: kDenseSlots counters per
-// device, addressed through hipGetSymbolAddress.  Every call takes the next slot (round robin), so
-// calls that overlap on one device - other streams, other host threads - count into different
-// words as long as fewer than kDenseSlots of them are in flight at once.
-constexpr unsigned kDenseSlots = 256;
-__device__ unsigned long long g_dense_total[kDenseSlots];
-std::atomic<unsigned> g_dense_next{0};
+constexpr int kMaxDevices = 64;
+
+// A number that a kernel hands to the host in the middle of a call: the kernel writes it to pinned host memory, so that no copy
+// stands between the kernel and the host's wait for the stream.  kHostSlots such calls may be under way at once, over all devices and threads; a call takes a
+// slot for its own use and gives it back when it returns, and waits for one while all are taken.  Each slot has a word of device memory as
+// well (per device, zero between calls), in which the workgroups of a kernel count themselves.  The pinned page is allocated once per process.
+constexpr int kHostSlots = 64;
+constexpr size_t kHostSlotWords = 8;
+__device__ unsigned long long g_tickets[kHostSlots];
+std::atomic<uint64_t> g_slots_taken{0};
+
+class HostSlot {
+public:
+    ~HostSlot()
+    {
+        if (i_ >= 0) g_slots_taken.fetch_and(~(1ull << i_), std::memory_order_acq_rel);
+    }
+    int claim()
+    {
+        static std::mutex mutex;
+        static unsigned long long* pinned = nullptr;
+        static unsigned long long* tickets[kMaxDevices] = {};
+        int dev = -1;
+        HIP_TRY(hipGetDevice(&dev));
+        if (dev < 0 || dev >= kMaxDevices) return GCOO_EINVAL;
+        {
+            std::lock_guard<std::mutex> lock(mutex);
+            if (!pinned) {
+                void* ptr = nullptr;
+                HIP_TRY(hipHostMalloc(&ptr, kHostSlots * kHostSlotWords * 8, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
+                pinned = static_cast<unsigned long long*>(ptr);
+            }
+            if (!tickets[dev]) {
+                void* ptr = nullptr;
+                HIP_TRY(hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_tickets)));
+                tickets[dev] = static_cast<unsigned long long*>(ptr);
+            }
+            host_ = pinned;
+            ticket_ = tickets[dev];
+        }
+        uint64_t taken = g_slots_taken.load(std::memory_order_relaxed);
+        while (true) {
+            if (taken == ~0ull) {
+                std::this_thread::yield();
+                taken = g_slots_taken.load(std::memory_order_relaxed);
+                continue;
+            }
+            const int i = __builtin_ctzll(~taken);
+            if (g_slots_taken.compare_exchange_weak(taken, taken | 1ull << i, std::memory_order_acq_rel)) { i_ = i; break; }
+        }
+        host_ += (size_t)i_ * kHostSlotWords;
+        ticket_ += i_;
+        __atomic_store_n(host_, 0ull, __ATOMIC_RELEASE);
+        return GCOO_OK;
+    }
+    unsigned long long* host() const { return host_; }
+    unsigned long long* ticket() const { return ticket_; }
+    // After the launch.
+    int wait(hipStream_t s, unsigned long long* answer)
+    {
+        HIP_TRY(hipStreamSynchronize(s));
+        *answer = __atomic_load_n(host_, __ATOMIC_ACQUIRE);
+        return GCOO_OK;
+    }
+
+private:
+    int i_ = -1;
+    unsigned long long* host_ = nullptr;
+    unsigned long long* ticket_ = nullptr;
+};
 
 // Scratch of gcoo_from_csr_device_static(), the conversion for callers that may not allocate device
 // memory: the second buffer of the per-group radix sort (3 arrays of nnz words) and the counter from
@@ -60,7 +124,6 @@ constexpr int64_t kStaticMaxNnz = 2 * 1024 * 1024;
 constexpr size_t kStaticSortBytes = (size_t)kStaticMaxNnz * 4;        // each of the three arrays, a multiple of 256
 constexpr size_t kStaticScratchBytes = 3 * kStaticSortBytes + 256;
 static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes];
-constexpr int kMaxDevices = 64;
 std::mutex g_static_mutex;
 unsigned char* g_static_ptr[kMaxDevices] = {};
 
@@ -600,17 +663,20 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     if (dev_buf_bytes < L0.total) return GCOO_ENOMEM;
     unsigned long long* stats = reinterpret_cast<unsigned long long*>(static_cast<char*>(dev_buf) + L0.counter);
     if (src_on_device) {
-        // With nnz given nothing is read back here; otherwise nnz comes back in one small copy.
+        // With nnz given nothing is read back here; otherwise nnz comes back in one word.
         if (nnz_known >= 0) {
             nnz = nnz_known;
         } else {
-            gcoo::group_stats_from_row_ptr<<<dim3(1), dim3(256), 0, s>>>(row_ptr, m, p, g, stats);
+            HostSlot slot;
+            int rc = slot.claim();
+            if (rc != GCOO_OK) return rc;
+            gcoo::read_entry_count<<<dim3(1), dim3(1), 0, s>>>(row_ptr, m, slot.host());
             HIP_TRY(hipGetLastError());
-            unsigned long long got[2] = {0, 0};
-            HIP_TRY(hipMemcpyAsync(got, stats, sizeof(got), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            if (got[0] > (unsigned long long)INT32_MAX) return GCOO_EBOUNDS;
-            nnz = (int64_t)got[0];
+            unsigned long long got = 0;
+            rc = slot.wait(s, &got);
+            if (rc != GCOO_OK) return rc;
+            if (got > (unsigned long long)INT32_MAX) return GCOO_EBOUNDS;
+            nnz = (int64_t)got;
         }
     } else {
         if (row_ptr[0] != 0) return GCOO_EBOUNDS;
@@ -744,82 +810,80 @@ int gcoo_dense_nnz(int64_t m, int64_t k, const float* A_dev, int64_t lda, void* 
     *nnz = 0;
     if (m == 0 || k == 0) return GCOO_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    unsigned long long* dptr = nullptr;
-    HIP_TRY(hipGetSymbolAddress(reinterpret_cast<void**>(&dptr), HIP_SYMBOL(g_dense_total)));
-    dptr += g_dense_next.fetch_add(1u, std::memory_order_relaxed) % kDenseSlots;
-    unsigned long long got = 0;
-    HIP_TRY(hipMemsetAsync(dptr, 0, 8, s));
-    const unsigned blocks = (unsigned)(m < 2048 ? m : 2048);
-    if (dense_vec_width(A_dev, lda, k) == 4)
-        gcoo::count_dense_total<4><<<dim3(blocks), dim3(256), 0, s>>>(A_dev, lda, m, k, dptr);
-    else
-        gcoo::count_dense_total<1><<<dim3(blocks), dim3(256), 0, s>>>(A_dev, lda, m, k, dptr);
+    HostSlot slot;
+    int rc = slot.claim();
+    if (rc != GCOO_OK) return rc;
+    const int vw = dense_vec_width(A_dev, lda, k);
+    const int64_t nblk = dense_blocks(k, vw);
+    const int64_t items = (m + 15) / 16 * nblk;
+    const dim3 grid((unsigned)(items < gcoo::kDenseWorkgroups ? items : gcoo::kDenseWorkgroups)), block(gcoo::kDenseThreads);
+    if (vw == 4) gcoo::count_dense_total<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, nblk, slot.ticket(), slot.host());
+    else gcoo::count_dense_total<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, nblk, slot.ticket(), slot.host());
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(&got, dptr, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    unsigned long long got = 0;
+    rc = slot.wait(s, &got);
+    if (rc != GCOO_OK) return rc;
     *nnz = (int64_t)got;
     return GCOO_OK;
 }
 
-int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* dev_buf, size_t dev_buf_bytes,
-                    void* stream, gcoo_matrix** out)
+}  // extern "C"
+
+namespace {
+
+// The counts of a dense matrix, at the places where a matrix buffer has them (offsets that do not depend on nnz).
+gcoo::DenseCounts dense_counts(void* buf, const Layout& L)
 {
-    const PolicyOfCall policy_of_call;
-    if (!out) return GCOO_EINVAL;
-    *out = nullptr;
-    if (!dev_buf || !dims_ok(m, k, 0, p) || lda < k || (m > 0 && k > 0 && !A_dev)) return GCOO_EINVAL;
-    if (reinterpret_cast<uintptr_t>(dev_buf) % kAlign) return GCOO_EINVAL;
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    char* base = static_cast<char*>(buf);
+    return {reinterpret_cast<int32_t*>(base + L.blk), reinterpret_cast<int32_t*>(base + L.gIdxes),
+            reinterpret_cast<int32_t*>(base + L.nnzPerGroup), reinterpret_cast<unsigned long long*>(base + L.counter)};
+}
+
+// Step 1 of Algorithm 1, and the wait for its sum.
+int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, hipStream_t s, int64_t* nnz)
+{
     const int64_t g = (m + p - 1) / p;
-    // gIdxes / nnzPerGroup / counter sit at the front of the buffer at offsets that do not
-    // depend on nnz, so step 1 can run before the buffer size for this nnz is checked.
-    const Layout L0 = make_layout(m, k, 0, g, p);
-    if (dev_buf_bytes < L0.total) return GCOO_ENOMEM;
-    char* base = static_cast<char*>(dev_buf);
-    int32_t* cnt = reinterpret_cast<int32_t*>(base + L0.nnzPerGroup);
-    int32_t* idx = reinterpret_cast<int32_t*>(base + L0.gIdxes);
-    int32_t* blk = reinterpret_cast<int32_t*>(base + L0.blk);
-    unsigned long long* tot = reinterpret_cast<unsigned long long*>(base + L0.counter);
-    unsigned long long total = 0;
     const int vw = dense_vec_width(A_dev, lda, k);
     const int64_t nblk = dense_blocks(k, vw);
-    // one workgroup per (group, column block); a band holds fewer than 2^31 elements so that
+    // one workgroup per (group, column block) fills; a band holds fewer than 2^31 elements so that
     // 32-bit counts cannot wrap before the total is checked
     if (nblk > 0 && g > 0x7fffffffLL / nblk) return GCOO_EINVAL;
     if ((int64_t)p * k > INT32_MAX) return GCOO_EINVAL;
-    if (g > 0) {
-        if (nblk > 0) {
-            const dim3 grid((unsigned)(nblk * g)), block(gcoo::kDenseThreads);
-            if (vw == 4) gcoo::count_dense_blocks<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, blk);
-            else gcoo::count_dense_blocks<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, blk);
-            HIP_TRY(hipGetLastError());
-        }
-        gcoo::scan_dense_blocks<<<dim3((unsigned)g), dim3(256), 0, s>>>(blk, nblk, cnt);
-        HIP_TRY(hipGetLastError());
-        gcoo::scan_group_counts<<<dim3(1), dim3(256), 0, s>>>(cnt, g, idx, tot);
-        HIP_TRY(hipGetLastError());
-        unsigned long long got[2] = {0, 0};
-        HIP_TRY(hipMemcpyAsync(got, tot, sizeof(got), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        total = got[0];
-    } else {
-        HIP_TRY(hipMemsetAsync(idx, 0, 4, s));          // only the sentinel exists
-        HIP_TRY(hipMemsetAsync(tot, 0, 16, s));
-    }
-    HIP_TRY(hipMemsetAsync(base + L0.counter + 16, 0, 8, s));   // no column can be out of range here; no long rows so far
+    HostSlot slot;
+    int rc = slot.claim();
+    if (rc != GCOO_OK) return rc;
+    const gcoo::DenseCounts out = dense_counts(buf, make_layout(m, k, 0, g, p));
+    const int64_t items = g * nblk;
+    const dim3 grid((unsigned)(items < 1 ? 1 : (items < gcoo::kDenseWorkgroups ? items : gcoo::kDenseWorkgroups))), block(gcoo::kDenseThreads);
+    if (vw == 4) gcoo::count_dense_blocks<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, g, out, slot.ticket(), slot.host());
+    else gcoo::count_dense_blocks<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, g, out, slot.ticket(), slot.host());
+    HIP_TRY(hipGetLastError());
+    unsigned long long total = 0;
+    rc = slot.wait(s, &total);
+    if (rc != GCOO_OK) return rc;
     if (total > (unsigned long long)INT32_MAX) return GCOO_EINVAL;
-    const int64_t nnz = (int64_t)total;
-    const Layout L = make_layout(m, k, nnz, g, p);
+    *nnz = (int64_t)total;
+    return GCOO_OK;
+}
+
+int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, int64_t lda, int32_t p, const void* counts, void* dev_buf,
+                       size_t dev_buf_bytes, void* stream, gcoo_matrix** out)
+{
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int64_t g = (m + p - 1) / p;
     if (dev_buf_bytes < total_bytes(m, k, nnz, p, true)) return GCOO_ENOMEM;
     gcoo_matrix* h = nullptr;
     int rc = new_handle(m, k, nnz, p, dev_buf, &h);
     if (rc != GCOO_OK) return rc;
-    if (g > 0 && nnz > 0) {
-        const dim3 grid((unsigned)(nblk * g)), block(gcoo::kDenseThreads);
-        if (vw == 4)
-            gcoo::fill_dense_blocks<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, h->gIdxes(), blk, h->values(), h->rows(), h->cols());
-        else
-            gcoo::fill_dense_blocks<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, h->gIdxes(), blk, h->values(), h->rows(), h->cols());
+    const int vw = dense_vec_width(A_dev, lda, k);
+    const int64_t nblk = dense_blocks(k, vw);
+    const gcoo::DenseCounts from = dense_counts(const_cast<void*>(counts), h->L), to = dense_counts(dev_buf, h->L);
+    {
+        const dim3 grid((unsigned)(g * nblk > 0 ? g * nblk : 1)), block(gcoo::kDenseThreads);
+        const bool small = p <= 64;
+        (vw == 4 ? (small ? gcoo::fill_dense_blocks<4, true> : gcoo::fill_dense_blocks<4, false>)
+                 : (small ? gcoo::fill_dense_blocks<1, true> : gcoo::fill_dense_blocks<1, false>))<<<grid, block, 0, s>>>(
+            A_dev, lda, m, k, p, nblk, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols());
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "fill_dense_blocks"); }
     }
@@ -833,12 +897,64 @@ int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32
     rc = launch_build_schedule(h, h->base + h->L.persistent, s);
     if (rc != GCOO_OK) { delete h; return rc; }
     if (wants_inner(p)) {
-        const size_t own = al(L.total);
-        rc = gcoo_from_dense(m, k, A_dev, lda, kInnerP, base + own, dev_buf_bytes - own, stream, &h->inner);
+        const size_t own = al(h->L.total);
+        rc = gcoo_from_dense(m, k, A_dev, lda, kInnerP, h->base + own, dev_buf_bytes - own, stream, &h->inner);
         if (rc != GCOO_OK) { delete h; return rc; }
     }
     *out = h;
     return GCOO_OK;
+}
+
+bool dense_args_ok(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, const void* buf)
+{
+    return buf && dims_ok(m, k, 0, p) && lda >= k && (m == 0 || k == 0 || A_dev) && reinterpret_cast<uintptr_t>(buf) % kAlign == 0;
+}
+
+}  // namespace
+
+extern "C" {
+
+size_t gcoo_dense_count_bytes(int64_t m, int64_t k, int32_t p)
+{
+    if (!dims_ok(m, k, 0, p)) return 0;
+    return make_layout(m, k, 0, (m + p - 1) / p, p).values;
+}
+
+int gcoo_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* count_buf, size_t count_buf_bytes,
+                     void* stream, int64_t* nnz)
+{
+    if (!nnz) return GCOO_EINVAL;
+    *nnz = 0;
+    if (!dense_args_ok(m, k, A_dev, lda, p, count_buf)) return GCOO_EINVAL;
+    if (count_buf_bytes < gcoo_dense_count_bytes(m, k, p)) return GCOO_ENOMEM;
+    return count_dense(m, k, A_dev, lda, p, count_buf, static_cast<hipStream_t>(stream), nnz);
+}
+
+int gcoo_from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, int64_t lda, int32_t p, const void* count_buf,
+                            void* dev_buf, size_t dev_buf_bytes, void* stream, gcoo_matrix** out)
+{
+    const PolicyOfCall policy_of_call;
+    if (!out) return GCOO_EINVAL;
+    *out = nullptr;
+    if (!dense_args_ok(m, k, A_dev, lda, p, dev_buf) || !count_buf || reinterpret_cast<uintptr_t>(count_buf) % kAlign) return GCOO_EINVAL;
+    if (!dims_ok(m, k, nnz, p) || nnz > m * k) return GCOO_EINVAL;
+    return from_dense_counted(m, k, nnz, A_dev, lda, p, count_buf, dev_buf, dev_buf_bytes, stream, out);
+}
+
+int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* dev_buf, size_t dev_buf_bytes,
+                    void* stream, gcoo_matrix** out)
+{
+    const PolicyOfCall policy_of_call;
+    if (!out) return GCOO_EINVAL;
+    *out = nullptr;
+    if (!dense_args_ok(m, k, A_dev, lda, p, dev_buf)) return GCOO_EINVAL;
+    // The counts sit at the front of the buffer at offsets that do not depend on nnz, so step 1 can run before the buffer size for
+    // this nnz is checked.
+    if (dev_buf_bytes < make_layout(m, k, 0, (m + p - 1) / p, p).total) return GCOO_ENOMEM;
+    int64_t nnz = 0;
+    const int rc = count_dense(m, k, A_dev, lda, p, dev_buf, static_cast<hipStream_t>(stream), &nnz);
+    if (rc != GCOO_OK) return rc;
+    return from_dense_counted(m, k, nnz, A_dev, lda, p, dev_buf, dev_buf, dev_buf_bytes, stream, out);
 }
 
 }  // extern "C"

@@ -39,10 +39,17 @@ __device__ __forceinline__ void group_stats_block(const int32_t* __restrict__ ro
     }
 }
 
-__global__ __launch_bounds__(256) void group_stats_from_row_ptr(const int32_t* __restrict__ row_ptr, int64_t m, int32_t p, int64_t g,
-                                                                 unsigned long long* __restrict__ out)
+// A kernel's answer to the host, straight to pinned host memory.
+__device__ __forceinline__ void tell_host(unsigned long long* host, unsigned long long a)
 {
-    group_stats_block(row_ptr, m, p, g, out);
+    __hip_atomic_store(host, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// nnz = row_ptr[m] of a CSR input on the device.  One thread.
+__global__ void read_entry_count(const int32_t* __restrict__ row_ptr, int64_t m, unsigned long long* __restrict__ host)
+{
+    const int32_t last = row_ptr[m];
+    tell_host(host, last < 0 ? ~0ull : (unsigned long long)last);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -313,11 +320,13 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
 // kDenseThreads*VW columns; workgroup (block, q) gives every thread VW adjacent columns, and the
 // threads of a wave read 64*VW adjacent floats of a row at a time (coalesced), row after row.
 //
-// Step 1 (count_dense_blocks): entries != 0 per block.  scan_dense_blocks then turns the counts
-// of a group into offsets (exclusive prefix sum over its blocks) and their sum into
-// nnzPerGroup[q]; scan_group_counts makes gIdxes from that.
+// Step 1 (count_dense_blocks): entries != 0 per block; the last workgroup to end turns the counts into the first slot of
+// every block (exclusive prefix sum, groups and blocks in order), gIdxes and nnzPerGroup.
+// Bound: reading A once.  The counts of the workgroups meet in one word only at the end of each (an atomic per wave on
+// one address took 105 us for 4000 x 4000; one per workgroup of 1024, with the scan behind it: 26 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kDenseThreads = 256;
+constexpr int kDenseWorkgroups = 1024;       // of a counting launch, at most: each one's arrival is an atomic on one word
 
 // VW adjacent floats of a row: one 16-byte load when VW = 4 (the launcher checks alignment).
 template <int VW>
@@ -340,108 +349,127 @@ __device__ __forceinline__ int32_t block_sum_256(int32_t n, int32_t* part)
 {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_down(n, d, kWave);
+    __syncthreads();
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
     __syncthreads();
     return part[0] + part[1] + part[2] + part[3];
 }
 
-// Thread t of block b owns columns (b*kDenseThreads + t)*VW .. +VW-1 of the band (k % VW == 0 when VW > 1).
+// Where the counts of a dense matrix live: in the buffer of the matrix, or in one of their own until nnz is known.
+struct DenseCounts {
+    int32_t* blk;              // [g * nblk] first slot of a block
+    int32_t* gIdxes;           // [g + 1]
+    int32_t* nnzPerGroup;      // [g]
+    unsigned long long* stats; // nnz, entries of the largest group
+};
+
+// Entries != 0 in rows [r0, r1), columns c .. c + VW - 1 (c < k).  Eight loads in flight.
 template <int VW>
-__global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
-                                                                     int32_t p, int64_t nblk, int32_t* __restrict__ blk_cnt)
+__device__ __forceinline__ int32_t count_dense_tile(const float* __restrict__ A, int64_t lda, int64_t r0, int64_t r1, int64_t c)
+{
+    int32_t n = 0;
+    const float* a = A + r0 * lda + c;
+    int64_t r = r0;
+    for (; r + 8 <= r1; r += 8) {
+        DenseVec<VW> v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = load_dense<VW>(a + x * lda);
+        a += 8 * lda;
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+#pragma unroll
+            for (int u = 0; u < VW; ++u) n += (v[x].x[u] != 0.0f) ? 1 : 0;
+    }
+    for (; r < r1; ++r, a += lda) {
+        const DenseVec<VW> v = load_dense<VW>(a);
+#pragma unroll
+        for (int u = 0; u < VW; ++u) n += (v.x[u] != 0.0f) ? 1 : 0;
+    }
+    return n;
+}
+
+// Item i = q*nblk + b, items strided over the workgroups; thread t of block b owns columns (b*kDenseThreads + t)*VW .. +VW-1 of the
+// band (k % VW == 0 when VW > 1).  `ticket` is 0 before and after.
+template <int VW>
+__global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k, int32_t p,
+                                                                     int64_t nblk, int64_t g, DenseCounts out,
+                                                                     unsigned long long* __restrict__ ticket, unsigned long long* __restrict__ host)
 {
     __shared__ int32_t part[4];
-    const int64_t q = blockIdx.x / nblk, b = blockIdx.x - q * nblk;      // blockIdx.x = q*nblk + b
-    const int64_t c = (b * kDenseThreads + threadIdx.x) * VW;
-    const int64_t r0 = q * p, r1 = (r0 + p < m) ? r0 + p : m;
-    int32_t n = 0;
-    if (c < k) {
-        const float* a = A + r0 * lda + c;
-        for (int64_t r = r0; r < r1; ++r, a += lda) {
-            const DenseVec<VW> v = load_dense<VW>(a);
-#pragma unroll
-            for (int u = 0; u < VW; ++u) n += (v.x[u] != 0.0f) ? 1 : 0;
-        }
+    __shared__ int32_t last_s;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t items = g * nblk;
+    for (int64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        const int64_t q = i / nblk, b = i - q * nblk;
+        const int64_t c = (b * kDenseThreads + tid) * VW;
+        const int64_t r0 = q * p, r1 = (r0 + p < m) ? r0 + p : m;
+        const int32_t tot = block_sum_256(c < k ? count_dense_tile<VW>(A, lda, r0, r1, c) : 0, part);
+        // written where every XCD sees it, before this workgroup's arrival is counted
+        if (tid == 0) __hip_atomic_store(&out.blk[i], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    const int32_t tot = block_sum_256(n, part);
-    if (threadIdx.x == 0) blk_cnt[blockIdx.x] = tot;
-}
-
-// One workgroup per group: blk[q][0..nblk) counts -> exclusive offsets in place, sum -> nnzPerGroup[q].
-__global__ __launch_bounds__(256) void scan_dense_blocks(int32_t* __restrict__ blk, int64_t nblk, int32_t* __restrict__ nnzPerGroup)
-{
-    __shared__ int32_t wsum[4];
-    __shared__ int32_t carry_s;
-    if (threadIdx.x == 0) carry_s = 0;
+    if (tid == 0) {
+        const unsigned long long before = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        last_s = before + 1 == gridDim.x;
+    }
     __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t* b = blk + (int64_t)blockIdx.x * nblk;
-    for (int64_t t0 = 0; t0 < nblk; t0 += 256) {
-        const int64_t i = t0 + threadIdx.x;
-        const int32_t v = (i < nblk) ? b[i] : 0;
-        int32_t incl = v;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int32_t t = __shfl_up(incl, d, kWave);
-            if (lane >= d) incl += t;
-        }
-        if (lane == 63) wsum[w] = incl;
-        __syncthreads();
-        int32_t off = carry_s;
-        for (int j = 0; j < w; ++j) off += wsum[j];
-        if (i < nblk) b[i] = off + incl - v;
-        __syncthreads();
-        if (threadIdx.x == 255) carry_s = off + incl;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) nnzPerGroup[blockIdx.x] = carry_s;
-}
+    if (!last_s) return;                                                  // the whole workgroup
 
-// Exclusive prefix sum of nnzPerGroup[g] into gIdxes[g+1] (sentinel = total).  One workgroup;
-// g is small (m / p), so a serial carry over 256-wide tiles is enough.  total[0] = nnz,
-// total[1] = entries of the largest group.
-__global__ __launch_bounds__(256) void scan_group_counts(const int32_t* __restrict__ nnzPerGroup, int64_t g,
-                                                          int32_t* __restrict__ gIdxes, unsigned long long* __restrict__ total)
-{
+    // The last workgroup: 1024 counts at a time, four per thread.
+    int64_t carry = 0;
     __shared__ int64_t wsum[4];
-    __shared__ int64_t carry_s;
-    __shared__ int32_t wmax[4];
-    if (threadIdx.x == 0) carry_s = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t mx = 0;
-    for (int64_t t0 = 0; t0 < g; t0 += 256) {
-        const int64_t i = t0 + threadIdx.x;
-        const int64_t v = (i < g) ? nnzPerGroup[i] : 0;
-        mx = (int32_t)v > mx ? (int32_t)v : mx;
-        int64_t incl = v;
+    for (int64_t t0 = 0; t0 < items; t0 += 4 * kDenseThreads) {
+        int32_t x[4];
+        const int64_t i0 = t0 + 4 * tid;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = i0 + u < items ? __hip_atomic_load(&out.blk[i0 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        const int64_t mine = (int64_t)x[0] + x[1] + x[2] + x[3];
+        int64_t incl = mine;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
-            int64_t t = __shfl_up(incl, d, kWave);
+            const int64_t t = __shfl_up(incl, d, kWave);
             if (lane >= d) incl += t;
         }
+        __syncthreads();
         if (lane == 63) wsum[w] = incl;
         __syncthreads();
-        int64_t off = carry_s;
-        for (int j = 0; j < w; ++j) off += wsum[j];
-        if (i < g) gIdxes[i] = (int32_t)(off + incl - v);
-        __syncthreads();
-        if (threadIdx.x == 255) carry_s = off + incl;
-        __syncthreads();
+        int64_t at = carry + incl - mine;
+        for (int j = 0; j < w; ++j) at += wsum[j];
+        carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            // (a total above INT32_MAX is rejected by the host)
+            if (i0 + u < items) __hip_atomic_store(&out.blk[i0 + u], (int32_t)(at > 0x7fffffffLL ? 0x7fffffffLL : at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            at += x[u];
+        }
+    }
+    __syncthreads();
+    const int32_t total = (int32_t)(carry > 0x7fffffffLL ? 0x7fffffffLL : carry);
+    int32_t mx = 0;
+    for (int64_t q = tid; q <= g; q += kDenseThreads) {
+        auto first = [&](int64_t gq) {
+            return gq < g && nblk > 0 ? __hip_atomic_load(&out.blk[gq * nblk], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : total;
+        };
+        const int32_t at = first(q);
+        out.gIdxes[q] = at;
+        if (q < g) {
+            const int32_t n = first(q + 1) - at;
+            out.nnzPerGroup[q] = n;
+            mx = n > mx ? n : mx;
+        }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const int32_t o = __shfl_down(mx, d, kWave);
         mx = o > mx ? o : mx;
     }
-    if (lane == 0) wmax[w] = mx;
+    if (lane == 0) part[w] = mx;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // totals above INT32_MAX are reported through total[0] and rejected by the host
-        gIdxes[g] = (int32_t)(carry_s > 0x7fffffffLL ? 0x7fffffffLL : carry_s);
-        total[0] = (unsigned long long)carry_s;
-        for (int i = 1; i < 4; ++i) mx = wmax[i] > mx ? wmax[i] : mx;
-        total[1] = (unsigned long long)mx;
+    if (tid == 0) {
+        for (int j = 1; j < 4; ++j) mx = part[j] > mx ? part[j] : mx;
+        out.stats[0] = (unsigned long long)carry;
+        out.stats[1] = (unsigned long long)mx;
+        __hip_atomic_store(ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        tell_host(host, (unsigned long long)carry);
     }
 }
 
@@ -449,37 +477,78 @@ __global__ __launch_bounds__(256) void scan_group_counts(const int32_t* __restri
 // Algorithm 1, step 2 for a dense input (fill_dense_blocks), same blocks as step 1.  Inside a
 // group the entries are ordered by (column, row), so the entries of block b come right after
 // those of blocks 0..b-1, column by column, and inside a column by row.  Thread c counts the
-// entries of its column, a workgroup-wide exclusive prefix sum of those counts gives the first
-// slot of every column, and the thread walks its column a second time (now from cache) and
-// writes each entry to its final slot.  No sort, no atomics: the slot of an entry is a
+// entries of its columns, a workgroup-wide exclusive prefix sum of those counts gives the first
+// slot of every column, and the thread writes each entry to its final slot.  No sort, no atomics: the slot of an entry is a
 // function of the matrix alone.
+// SMALL (at most 64 rows per group): the count leaves a bit per element behind, and only the elements that are entries
+// are read a second time, the next one of each column together; taller groups walk the columns again.
+// (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)
+// The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..1].
 // ---------------------------------------------------------------------------------------------
-template <int VW>
+template <int VW, bool SMALL>
 __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
-                                                                    int32_t p, int64_t nblk, const int32_t* __restrict__ gIdxes,
-                                                                    const int32_t* __restrict__ blk_off, float* __restrict__ values,
+                                                                    int32_t p, int64_t nblk, int64_t g, DenseCounts from, DenseCounts to,
+                                                                    uint32_t* __restrict__ zeroed, float* __restrict__ values,
                                                                     int32_t* __restrict__ rows, int32_t* __restrict__ cols)
 {
     __shared__ int32_t wsum[4];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (blockIdx.x == 0 && tid < 2) zeroed[tid] = 0u;
+    if (from.gIdxes != to.gIdxes) {
+        if (blockIdx.x == 0 && tid < 2) to.stats[tid] = from.stats[tid];
+        for (int64_t q = (int64_t)blockIdx.x * kDenseThreads + tid; q <= g; q += (int64_t)gridDim.x * kDenseThreads) {
+            to.gIdxes[q] = from.gIdxes[q];
+            if (q < g) to.nnzPerGroup[q] = from.nnzPerGroup[q];
+        }
+    }
+    if (nblk == 0 || (int64_t)blockIdx.x >= g * nblk) return;            // the whole workgroup
     const int64_t q = blockIdx.x / nblk, b = blockIdx.x - q * nblk;      // blockIdx.x = q*nblk + b
-    const int64_t c = (b * kDenseThreads + threadIdx.x) * VW;
+    const int64_t c = (b * kDenseThreads + tid) * VW;
     const int64_t r0 = q * p, r1 = (r0 + p < m) ? r0 + p : m;
     const float* col0 = A + r0 * lda + c;
+    uint64_t bits[VW];
     int32_t n[VW];
 #pragma unroll
-    for (int u = 0; u < VW; ++u) n[u] = 0;
+    for (int u = 0; u < VW; ++u) {
+        n[u] = 0;
+        bits[u] = 0;
+    }
     if (c < k) {
         const float* a = col0;
-        for (int64_t r = r0; r < r1; ++r, a += lda) {
+        const int32_t nr = (int32_t)(r1 - r0);
+        int32_t r = 0;
+        for (; r + 8 <= nr; r += 8, a += 8 * lda) {
+            DenseVec<VW> v[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) v[x] = load_dense<VW>(a + x * lda);
+#pragma unroll
+            for (int u = 0; u < VW; ++u) {
+                if constexpr (SMALL) {
+                    uint32_t eight = 0;
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) eight |= (v[x].x[u] != 0.0f) ? 1u << x : 0u;
+                    bits[u] |= (uint64_t)eight << r;
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) n[u] += (v[x].x[u] != 0.0f) ? 1 : 0;
+                }
+            }
+        }
+        for (; r < nr; ++r, a += lda) {
             const DenseVec<VW> v = load_dense<VW>(a);
 #pragma unroll
-            for (int u = 0; u < VW; ++u) n[u] += (v.x[u] != 0.0f) ? 1 : 0;
+            for (int u = 0; u < VW; ++u) {
+                if constexpr (SMALL) bits[u] |= (uint64_t)(v.x[u] != 0.0f) << r;
+                else n[u] += (v.x[u] != 0.0f) ? 1 : 0;
+            }
         }
     }
     int32_t mine = 0;
 #pragma unroll
-    for (int u = 0; u < VW; ++u) mine += n[u];
+    for (int u = 0; u < VW; ++u) {
+        if constexpr (SMALL) n[u] = __popcll(bits[u]);
+        mine += n[u];
+    }
     int32_t incl = mine;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -488,12 +557,37 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
     }
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
-    int32_t first = gIdxes[q] + blk_off[blockIdx.x] + incl - mine;       // slot of the first entry of this thread's columns
+    int32_t first = from.blk[blockIdx.x] + incl - mine;                  // slot of the first entry of this thread's columns
     for (int j = 0; j < w; ++j) first += wsum[j];
-    if (c < k && mine > 0) {
-        int32_t at[VW];
+    if (mine == 0) return;
+    int32_t at[VW];
 #pragma unroll
-        for (int u = 0; u < VW; ++u) { at[u] = first; first += n[u]; }
+    for (int u = 0; u < VW; ++u) { at[u] = first; first += n[u]; }
+    if constexpr (SMALL) {
+        while (true) {
+            uint64_t any = 0;
+#pragma unroll
+            for (int u = 0; u < VW; ++u) any |= bits[u];
+            if (!any) break;
+            int32_t r[VW];
+            float v[VW];
+#pragma unroll
+            for (int u = 0; u < VW; ++u) {
+                r[u] = __ffsll((unsigned long long)bits[u]) - 1;
+                if (bits[u]) v[u] = col0[r[u] * lda + u];
+            }
+#pragma unroll
+            for (int u = 0; u < VW; ++u) {
+                if (bits[u]) {
+                    values[at[u]] = v[u];
+                    rows[at[u]] = (int32_t)r0 + r[u];
+                    cols[at[u]] = (int32_t)(c + u);
+                    ++at[u];
+                }
+                bits[u] &= bits[u] - 1;
+            }
+        }
+    } else {
         const float* a = col0;
         for (int64_t r = r0; r < r1; ++r, a += lda) {
             const DenseVec<VW> v = load_dense<VW>(a);
@@ -510,23 +604,35 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
     }
 }
 
-// Total count of entries != 0 of a dense matrix (Algorithm 1, step 1, without the grouping).
+// Total count of entries != 0 of a dense matrix (Algorithm 1, step 1, without the grouping): pieces of 16 rows x kDenseThreads*VW
+// columns, strided over the workgroups.  `ticket` (0 before and after) collects the count in its low 48 bits and the
+// workgroups that have ended above.
 template <int VW>
-__global__ __launch_bounds__(256) void count_dense_total(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
-                                                          unsigned long long* __restrict__ total)
+__global__ __launch_bounds__(kDenseThreads) void count_dense_total(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k, int64_t nblk,
+                                                                    unsigned long long* __restrict__ ticket, unsigned long long* __restrict__ host)
 {
+    constexpr int64_t ROWS = 16;
+    __shared__ unsigned long long wide[4];
     unsigned long long n = 0;
-    for (int64_t r = blockIdx.x; r < m; r += gridDim.x) {
-        const float* a = A + r * lda;
-        for (int64_t j = (int64_t)threadIdx.x * VW; j < k; j += 256 * VW) {
-            const DenseVec<VW> v = load_dense<VW>(a + j);
-#pragma unroll
-            for (int u = 0; u < VW; ++u) n += (v.x[u] != 0.0f) ? 1u : 0u;
-        }
+    const int64_t items = (m + ROWS - 1) / ROWS * nblk;
+    for (int64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        const int64_t q = i / nblk, b = i - q * nblk;
+        const int64_t c = (b * kDenseThreads + threadIdx.x) * VW;
+        const int64_t r0 = q * ROWS, r1 = (r0 + ROWS < m) ? r0 + ROWS : m;
+        if (c < k) n += (unsigned long long)count_dense_tile<VW>(A, lda, r0, r1, c);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) n += __shfl_down(n, d, kWave);
-    if ((threadIdx.x & 63) == 0 && n) atomicAdd(total, n);   // integer sum: order-free
+    if ((threadIdx.x & 63) == 0) wide[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        n = wide[0] + wide[1] + wide[2] + wide[3] + (1ull << 48);
+        const unsigned long long all = __hip_atomic_fetch_add(ticket, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + n;   // integer sum: order-free
+        if (all >> 48 == gridDim.x) {
+            __hip_atomic_store(ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            tell_host(host, all & 0xffffffffffffull);
+        }
+    }
 }
 
 }  // namespace gcoo

@@ -1,0 +1,48 @@
+"""Counting and filling a dense matrix where the split can go wrong: no rows or no columns, one block and many, more blocks than the
+last workgroup scans at a time, 64 and 65 rows per group (a bit per element, and walking twice), columns in fours and one by one.
+Both routes of the C interface, bit for bit against the CPU oracle."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gcoo_oracle as orc
+from paper_2005_14469_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("m,k,p,density", [(1, 1, 1, 1.0), (0, 8, 4, 0.0), (5, 0, 4, 0.0), (33, 1023, 32, 0.05), (130, 1024, 64, 0.3),
+                                           (130, 1028, 65, 0.3), (63, 4097, 64, 0.02), (70, 260, 7, 0.0), (64, 512, 64, 1.0), (2100, 1500, 1, 0.1),
+                                           (2100, 301, 1, 0.1)])
+def test_counts_and_fill(m, k, p, density):
+    print(f"dense count: {m}x{k} p={p}", flush=True)
+    rng = np.random.default_rng(m + k)
+    Ah = (rng.standard_normal((m, k)) * (rng.random((m, k)) < density)).astype(np.float32)
+    if m * k > 4:
+        Ah[-1, -1] = np.nan
+        Ah[0, 0] = -0.0
+    A = torch.from_numpy(Ah).to(DEV)
+    L, n = binding.lib(), C.c_int64()
+    stream = torch.cuda.current_stream().cuda_stream
+    assert L.gcoo_dense_nnz(m, k, A.data_ptr(), k, stream, C.byref(n)) == 0
+    if m and k:
+        want = orc.gcoo_from_dense(Ah, p)
+        assert n.value == want.nnz
+    handles = [binding.gcoo_from_dense(A, p)] if m and k else []
+    buf = torch.empty(max(256, L.gcoo_device_bytes(m, k, n.value, p)), dtype=torch.uint8, device=DEV)
+    out = C.c_void_p()
+    assert L.gcoo_from_dense(m, k, A.data_ptr(), k, p, buf.data_ptr(), buf.numel(), stream, C.byref(out)) == 0
+    handles.append(binding.GcooMatrix(out.value, buf))
+    for h in handles:
+        e = h.export()
+        if m and k:
+            assert np.array_equal(e["values"].view(np.uint32), want.values.view(np.uint32))
+            assert np.array_equal(e["rows"], want.rows) and np.array_equal(e["cols"], want.cols)
+            assert np.array_equal(e["gIdxes"], want.gIdxes) and np.array_equal(e["nnzPerGroup"], want.nnzPerGroup)
+        else:
+            assert len(e["values"]) == 0 and not e["gIdxes"].any()
