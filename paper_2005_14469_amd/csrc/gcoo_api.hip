@@ -12,12 +12,14 @@
 
 #include <atomic>
 #include <cmath>
+#include <memory>
 #include <mutex>
 #include <thread>
 
 #include "gcoo_band.hpp"
 #include "gcoo_band_build.hpp"
 #include "gcoo_build_kernels.hpp"
+#include "gcoo_order_kernels.hpp"
 #include "gcoo_sched.hpp"
 #include "gcoo_sched_build.hpp"
 #include "gcoo_share.hpp"
@@ -152,6 +154,10 @@ struct Layout {
     size_t share_ucols, share_ucount, share_hdr, share_blocks, share_sbase, share_alloc;   // share schedule (may be empty)
     int32_t band_h;                                        // rows per wave of the band schedule, 0: none
     size_t band_head, band_units, band_first, band_count;  // band schedule
+    bool by_masks;                                         // a CSR input is ordered by take_rows and order_groups, else sorted by digits
+    gcoo::OrderPlan plan;
+    int64_t lists;                                         // workgroups of take_rows
+    size_t take_flags, splits;
     size_t tmp_cols, tmp_rows, tmp_vals;                   // conversion scratch (second sort buffer)
     size_t in_row_ptr, in_cols, in_vals;                   // staging of a host CSR input
     size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4)
@@ -330,6 +336,30 @@ int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p)
     return best;
 }
 
+// How a CSR input of this shape is put into the order of the groups; false: sorted by digits of the column.  A part has up to 4096
+// columns of at most 32 rows (2048 of 64, 512 of 256: 16 KB of masks) and fewer where it would hold more than 1024 entries on
+// average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).  A part costs a workgroup its steps over all its columns, so the sort is the better one where the groups have far more columns
+// than entries (12001 x 12001, 0.05 %, 62 columns per entry: 12 us sorting, 20 this way; 16384 x 16384, power-law rows, 10: 55 and 40).
+bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, int32_t band_h, gcoo::OrderPlan* plan)
+{
+    *plan = {};
+    if (m <= 0 || k <= 0 || nnz <= 0) return false;
+    const int64_t g = (m + p - 1) / p, mean = nnz / g + 1;
+    if (k > 32 * mean) return false;
+    int32_t shift = 0;
+    while (((int64_t)1 << shift) < k && shift < (p <= 32 ? 12 : (p <= 64 ? 11 : 9))) ++shift;
+    while (shift > 7 && (mean << shift) / k > 1024) --shift;
+    const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
+    if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;
+    // lists of rows of take_rows: those of the band schedule, else enough workgroups for four per compute unit
+    int64_t rows = (m + 1023) / 1024;
+    rows = band_h > 0 ? band_h : (rows > 64 ? 64 : rows);
+    int64_t cap = mean / parts * 3 / 2 + 64;
+    cap = cap < 256 ? 256 : (cap > gcoo::kOrderMaxCap ? gcoo::kOrderMaxCap : cap);
+    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), parts == 1 && band_h == 0 && !run_schedule_wanted(p)};
+    return true;
+}
+
 // (device offsets that contradict each other may make more rows long than these: the rest are not listed)
 int32_t long_room(int64_t m, int64_t nnz) { return (int32_t)(nnz / gcoo::rows_long(m, nnz)) + 1; }
 
@@ -351,7 +381,7 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.rows = take(n4);
     L.cols = take(n4);
     const bool rows = p <= gcoo::kSchedMaxP;
-    L.row_start = take(rows ? (size_t)(m + 1) * 4 : 0);
+    L.row_start = take((size_t)(m + 1) * 4);
     L.row_cols = take(rows ? n4 : 0);
     L.row_vals = take(rows ? n4 : 0);
     L.row_long = take(rows ? (size_t)long_room(m, nnz) * 4 : 0);
@@ -372,6 +402,10 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.band_units = take(L.band_h ? (size_t)gcoo::band_units(nnz, m, k, L.band_h) * gcoo::kBandUnitWords * 4 : 0);
     L.band_first = take((size_t)lists * 4);
     L.band_count = take((size_t)(lists / gcoo::kBandWaves) * 4);
+    L.by_masks = order_plan(m, k, nnz, p, L.band_h, &L.plan);
+    L.lists = L.plan.fused ? g : lists ? lists : (L.by_masks ? (m + L.plan.list_rows - 1) / L.plan.list_rows : 0);     // (a band block has empty lists behind the last row)
+    L.take_flags = take(L.by_masks ? (size_t)L.lists * 4 : 0);
+    L.splits = take(L.by_masks ? (size_t)m * (size_t)(L.plan.parts - 1) * 4 : 0);
     L.persistent = at;
     if (!scratch_inside) {
         // the fixed carve-up of the static scratch (no staging of a host input there)
@@ -429,6 +463,7 @@ struct gcoo_matrix {
     int32_t nw, window_cols;
     bool has_sched;            // the run schedule of the register kernel was built
     bool has_share;            // the share schedule was built
+    bool from_csr = false;     // the input was CSR (as opposed to dense)
     bool share_preferred;      // GCOO_VARIANT_SHARE can be asked for and is what gcoo_spdm_pick() answers where B is wide enough
     int device;
     char* base;
@@ -457,6 +492,7 @@ struct gcoo_matrix {
     bool has_order() const { return has_sched && g > 0 && g <= gcoo::kOrderMaxGroups; }
     int32_t* order() const { return reinterpret_cast<int32_t*>(base + L.order); }
     unsigned long long* stats() const { return reinterpret_cast<unsigned long long*>(base + L.counter); }
+    uint32_t* take_flags() const { return reinterpret_cast<uint32_t*>(base + L.take_flags); }
     uint32_t* bad_col() const { return reinterpret_cast<uint32_t*>(base + L.counter + 16); }
     int32_t* share_ucols() const { return reinterpret_cast<int32_t*>(base + L.share_ucols); }
     int32_t* share_ucount() const { return reinterpret_cast<int32_t*>(base + L.share_ucount); }
@@ -526,8 +562,9 @@ hipError_t band_fill_lds_limit()
     return e;
 }
 
-// `scratch`: the conversion's scratch area (the counter of share_fill sits in it).
-int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s)
+// `scratch`: the conversion's scratch area (the counter of share_fill sits in it).  `marked`: the bitmaps of the band schedule are there, and
+// the counter is zero.
+int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false)
 {
     uint32_t* share_alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
     if (h->g > 0 && h->has_sched) {
@@ -579,7 +616,7 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s)
         const size_t words = (size_t)((h->k + 31) / 32);
         uint32_t* parts = reinterpret_cast<uint32_t*>(scratch + h->L.tmp_cols);          // the second sort buffer, free by now
         uint32_t* alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
-        gcoo::band_mark<<<dim3(lists), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows, parts, alloc);
+        if (!marked) gcoo::band_mark<<<dim3(lists), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows, parts, alloc);
         HIP_TRY(hipGetLastError());
         int64_t chunk = (h->k + gcoo::kBandRows - 1) / gcoo::kBandRows * gcoo::kBandRows;
         const int64_t most = (int64_t)(kBandFillMaxLds - words * 8) / (4 * gcoo::kBandRows + 4 * gcoo::kBandRows / gcoo::kBandGroup) * gcoo::kBandRows;
@@ -694,6 +731,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     gcoo_matrix* h = nullptr;
     int rc = new_handle(m, k, nnz, p, dev_buf, &h, inside);
     if (rc != GCOO_OK) return rc;
+    h->from_csr = true;
     char* base = h->base;
     char* scratch = inside ? base + L.persistent : reinterpret_cast<char*>(static_scratch_ptr);
 
@@ -713,6 +751,41 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         d_row_ptr = sp; d_cols = sc; d_vals = sv;
     }
 
+    bool marked = false;
+    const int words = p <= 32 ? 1 : (p <= 64 ? 2 : 8);
+    if (L.by_masks && L.plan.fused) {
+        gcoo::OrderArgs o{};
+        o.cols = d_cols; o.vals = d_vals; o.m = m; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.out = rows_out(h);
+        o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
+        o.row_ptr = d_row_ptr; o.nnz = (int32_t)nnz; o.g = g; o.gIdxes_out = h->gIdxes(); o.nnzPerGroup_out = h->nnzPerGroup();
+        o.row_start_out = h->row_start(); o.flags_out = h->take_flags();
+        (words == 1 ? gcoo::order_groups<1, true> : (words == 2 ? gcoo::order_groups<2, true> : gcoo::order_groups<8, true>))<<<
+            dim3((unsigned)g), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
+    } else if (L.by_masks) {
+        marked = L.band_h > 0 && !h->has_share;              // (the share schedule's builder uses the same scratch)
+        gcoo::TakeArgs t{};
+        t.row_ptr = d_row_ptr; t.cols = d_cols; t.vals = d_vals;
+        t.m = m; t.g = g; t.lists = L.lists; t.p = p; t.nnz = (int32_t)nnz; t.k = (int32_t)k; t.plan = L.plan;
+        t.gIdxes = h->gIdxes(); t.nnzPerGroup = h->nnzPerGroup(); t.row_start = h->row_start();
+        t.row_cols = h->has_rows() ? h->row_cols() : nullptr; t.row_vals = h->row_vals();
+        t.flags = h->take_flags(); t.splits = reinterpret_cast<int32_t*>(base + L.splits);
+        t.bits = marked ? reinterpret_cast<uint32_t*>(scratch + L.tmp_cols) : nullptr;
+        t.zero_bad = h->bad_col(); t.zero_alloc = reinterpret_cast<uint32_t*>(scratch + L.share_alloc);
+        t.stats = h->has_sched ? stats : nullptr;
+        gcoo::take_rows<<<dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(gcoo::kTakeThreads), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) { delete h; return hip_fail(e, "take_rows"); }
+        gcoo::OrderArgs o{};
+        o.row_start = h->row_start(); o.cols = h->has_rows() ? h->row_cols() : d_cols; o.vals = h->has_rows() ? h->row_vals() : d_vals;
+        o.m = m; o.lists = L.lists; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.gIdxes = h->gIdxes(); o.flags = t.flags; o.splits = t.splits;
+        o.out = rows_out(h); o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
+        (words == 1 ? gcoo::order_groups<1, false> : (words == 2 ? gcoo::order_groups<2, false> : gcoo::order_groups<8, false>))<<<
+            dim3((unsigned)(g * L.plan.parts)), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+        e = hipGetLastError();
+        if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
+    } else
     // Algorithm 1, step 1: group index and counts straight from row_ptr (also writes the sentinel).
     {
         const unsigned blocks = (unsigned)(((h->has_rows() ? m : g) + 1 + 255) / 256) + 1u;     // the last one computes the statistics
@@ -723,7 +796,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     }
     // Algorithm 1, step 2: stable per-group radix sort on the column, 8 bits per pass, ping-pong
     // between the scratch triple and the final arrays so that the last pass lands in the latter.
-    if (g > 0 && nnz > 0) {
+    if (!L.by_masks && g > 0 && nnz > 0) {
         const int passes = radix_passes(k);
         int32_t* fin_c = h->cols(); int32_t* fin_r = h->rows(); float* fin_v = h->values();
         int32_t* tmp_c = reinterpret_cast<int32_t*>(scratch + L.tmp_cols);
@@ -754,7 +827,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             src_c = dc; src_r = dr; src_v = dv;
         }
     }
-    rc = launch_build_schedule(h, scratch, s);
+    rc = launch_build_schedule(h, scratch, s, marked);
     if (rc != GCOO_OK) { delete h; return rc; }
     if (wants_inner(p)) {
         // the same entries once more, regrouped at kInnerP rows, from the CSR arrays on the device (a host input's
@@ -1084,6 +1157,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     auto run_rows = [&]() -> int {
         gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
                          A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
+        if (A->from_csr && A->L.by_masks && A->L.plan.fused) { a.long_count = nullptr; a.long_row = INT32_MAX; }     // (none are listed)
         hipError_t e = gcoo::launch_spdm_rows(a, s);
         return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
     };
@@ -1154,21 +1228,20 @@ int gcoo_export(const gcoo_matrix* A, float* values, int32_t* rows, int32_t* col
     if (rows && n4) HIP_TRY(hipMemcpyAsync(rows, A->rows(), n4, hipMemcpyDeviceToHost, s));
     if (cols && n4) HIP_TRY(hipMemcpyAsync(cols, A->cols(), n4, hipMemcpyDeviceToHost, s));
     if (nnzPerGroup && A->g) HIP_TRY(hipMemcpyAsync(nnzPerGroup, A->nnzPerGroup(), (size_t)A->g * 4, hipMemcpyDeviceToHost, s));
-    int32_t* narrow = nullptr;
-    if (gIdxes) {
-        narrow = new (std::nothrow) int32_t[(size_t)A->g + 1];
-        if (!narrow) return GCOO_ENOMEM;
-        hipError_t e = hipMemcpyAsync(narrow, A->gIdxes(), (size_t)(A->g + 1) * 4, hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) { delete[] narrow; return hip_fail(e, "hipMemcpyAsync(gIdxes)"); }
-    }
-    uint32_t bad = 0;
-    hipError_t e = hipMemcpyAsync(&bad, A->bad_col(), 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (gIdxes && e == hipSuccess)
+    // columns out of range: one word, or one per list of rows that the conversion took
+    const bool lists = A->from_csr && A->L.by_masks;
+    const size_t n_bad = lists ? (size_t)A->L.lists : 1;
+    std::unique_ptr<int32_t[]> narrow(gIdxes ? new (std::nothrow) int32_t[(size_t)A->g + 1] : nullptr);
+    std::unique_ptr<uint32_t[]> bad(new (std::nothrow) uint32_t[n_bad]);
+    if ((gIdxes && !narrow) || !bad) return GCOO_ENOMEM;
+    if (gIdxes) HIP_TRY(hipMemcpyAsync(narrow.get(), A->gIdxes(), (size_t)(A->g + 1) * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(bad.get(), lists ? A->take_flags() : A->bad_col(), n_bad * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (gIdxes)
         for (int64_t i = 0; i <= A->g; ++i) gIdxes[i] = narrow[i];
-    delete[] narrow;
-    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    return bad ? GCOO_EBOUNDS : GCOO_OK;
+    uint32_t any = 0;
+    for (size_t i = 0; i < n_bad; ++i) any |= bad[i] & (lists ? gcoo::kBadColumn : ~0u);
+    return any ? GCOO_EBOUNDS : GCOO_OK;
 }
 
 int gcoo_export_share(const gcoo_matrix* A, uint32_t* hdr, uint32_t* blocks, int32_t* sbase, int32_t* ucount, int32_t* ucols,

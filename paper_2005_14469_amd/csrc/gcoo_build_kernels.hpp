@@ -13,13 +13,14 @@ namespace gcoo {
 constexpr int kWave = 64;
 
 // What the host wants to know about a CSR input before it sizes anything: out[0] = nnz = row_ptr[m],
-// out[1] = entries of the largest group.  The work of one workgroup of 256 threads.
+// out[1] = entries of the largest group.  The work of one workgroup of THREADS threads.
+template <int THREADS>
 __device__ __forceinline__ void group_stats_block(const int32_t* __restrict__ row_ptr, int64_t m, int32_t p, int64_t g,
                                                   unsigned long long* __restrict__ out)
 {
-    __shared__ int32_t part[4];
+    __shared__ int32_t part[THREADS / 64];
     int32_t mx = 0;
-    for (int64_t q = threadIdx.x; q < g; q += 256) {
+    for (int64_t q = threadIdx.x; q < g; q += THREADS) {
         const int64_t r0 = q * p, r1 = (r0 + p < m) ? r0 + p : m;
         const int32_t n = row_ptr[r1] - row_ptr[r0];
         mx = n > mx ? n : mx;
@@ -32,7 +33,7 @@ __device__ __forceinline__ void group_stats_block(const int32_t* __restrict__ ro
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) mx = part[i] > mx ? part[i] : mx;
+        for (int i = 1; i < THREADS / 64; ++i) mx = part[i] > mx ? part[i] : mx;
         const int32_t last = row_ptr[m];
         out[0] = last < 0 ? ~0ull : (unsigned long long)last;
         out[1] = (unsigned long long)mx;
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(256) void group_index_from_row_ptr(const int32_t* _
     if (stats && blockIdx.x == gridDim.x - 1) {                   // the whole workgroup
         // bad_col[0] is set by the sort that follows if it meets a column out of range, bad_col[1] counts the rows it lists as long
         if (threadIdx.x < 2) bad_col[threadIdx.x] = 0u;
-        group_stats_block(row_ptr, m, p, g, stats);
+        group_stats_block<256>(row_ptr, m, p, g, stats);
         return;
     }
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -1,0 +1,464 @@
+// Conversion of a CSR input in two kernels, without a sort: take_rows reads the input once, order_groups writes the five arrays.
+//
+// Inside a group the entries are ordered by (column, row).  With the rows that hold an entry in a column as a bit mask per
+// column (at most p bits), the place of an entry is what the columns before it hold, a prefix sum of popcounts, plus the
+// popcount of the mask below its row: two passes over the entries with a few LDS accesses each, no ranking, any order inside the rows.
+// The radix sort (gcoo_build_kernels.hpp) moves every entry through memory once per digit and walks it in tiles of 64
+// with eight ballots each; it stays for matrices whose columns far outnumber the entries of a group (order_by_masks()).
+//
+// A workgroup orders one part of a group: `ncols` columns.  Where the columns of every row ascend, which take_rows checks, a part is
+// one stretch of each row, and take_rows has noted where it begins; otherwise the workgroup looks through the whole group.
+// A group that holds a coordinate twice has no place for it in a mask: such a part is ranked in input order by one wave.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gcoo_build_kernels.hpp"
+
+namespace gcoo {
+
+constexpr int kTakeThreads = 512;
+constexpr int kOrderThreads = 256;
+constexpr int kOrderMaxParts = 64;
+constexpr int kOrderMaxCap = 3072;       // entries of a part that are put in order in LDS; a larger part is written in place
+constexpr uint32_t kBadColumn = 1u, kUnsorted = 2u;
+
+// How the groups of a matrix are cut; the same on the host for the layout and for the launches.
+struct OrderPlan {
+    int32_t shift;             // log2 of the columns of a part
+    int32_t parts;
+    int32_t list_rows;         // rows per workgroup of take_rows
+    int32_t cap;
+    bool fused;
+};
+
+struct TakeArgs {
+    const int32_t* row_ptr;
+    const int32_t* cols;
+    const float* vals;
+    int64_t m, g, lists;
+    int32_t p, nnz, k;
+    OrderPlan plan;
+    int32_t* gIdxes;
+    int32_t* nnzPerGroup;
+    int32_t* row_start;        // [m + 1]
+    int32_t* row_cols;         // entries in row order, or null
+    float* row_vals;
+    uint32_t* flags;           // [lists]
+    int32_t* splits;           // [m * (parts - 1)] where the later parts of a row begin
+    uint32_t* bits;            // [lists * ceil(k/32)] columns of a list, or null
+    uint32_t* zero_bad;        // bad_col and the count of long rows
+    uint32_t* zero_alloc;
+    unsigned long long* stats; // or null; a workgroup more
+};
+
+// Row r with start[r] <= e < start[r + 1], among ascending starts of which those from the last row's end on are INT32_MAX; empty
+// rows are skipped.  Always log2(ROWS) steps, so that a thread's entries go through it side by side.
+template <int ROWS>
+__device__ __forceinline__ int32_t row_of_entry(const int32_t* start, int32_t e)
+{
+    int32_t r = 0;
+#pragma unroll
+    for (int d = ROWS / 2; d >= 1; d >>= 1) r += start[r + d] <= e ? d : 0;
+    return r;
+}
+
+// One workgroup per list of rows.  Bound: memory, an entry is read once and its copy in row order written once.  Dynamic LDS: the
+// list's columns as a bitmap, where the band schedule wants it.
+__global__ __launch_bounds__(kTakeThreads) void take_rows(TakeArgs a)
+{
+    extern __shared__ uint32_t take_bits[];
+    __shared__ int32_t rs[65], find[64];
+    __shared__ uint32_t flag_s;
+    const int tid = threadIdx.x;
+    const int64_t list = blockIdx.x;
+    if (list == a.lists) {                                       // the whole workgroup
+        group_stats_block<kTakeThreads>(a.row_ptr, a.m, a.p, a.g, a.stats);
+        return;
+    }
+    if (list == 0 && tid < 2) a.zero_bad[tid] = 0u;
+    if (list == 0 && tid == 2) *a.zero_alloc = 0u;
+    // Offsets are clamped to [0, nnz]: with a device input whose row_ptr does not match the nnz the buffer was laid out
+    // for, every later kernel still stays inside the arrays.
+    const int32_t nnz = a.nnz;
+    auto at = [&](int64_t r) { const int32_t v = a.row_ptr[r]; return v < 0 ? 0 : (v > nnz ? nnz : v); };
+    const int64_t r0 = list * a.plan.list_rows < a.m ? list * a.plan.list_rows : a.m;
+    const int32_t rows = (int32_t)(a.m - r0 < a.plan.list_rows ? a.m - r0 : a.plan.list_rows);
+    const int32_t nbw = (a.k + 31) / 32;
+    if (tid == 0) flag_s = 0u;
+    if (tid <= rows) {
+        const int32_t v = at(r0 + tid);
+        rs[tid] = v;
+        a.row_start[r0 + tid] = v;
+        if (tid < 64) find[tid] = tid < rows ? v : INT32_MAX;
+    } else if (tid < 64) {
+        find[tid] = INT32_MAX;
+    }
+    if (tid < rows && (r0 + tid) % a.p == 0) {
+        const int64_t q = (r0 + tid) / a.p, r1 = r0 + tid + a.p < a.m ? r0 + tid + a.p : a.m;
+        const int32_t b = at(r0 + tid), n = at(r1) - b;
+        a.gIdxes[q] = b;
+        a.nnzPerGroup[q] = n < 0 ? 0 : n;
+    }
+    if (tid == 0 && r0 + rows == a.m) a.gIdxes[a.g] = at(a.m);
+    if (a.bits)
+        for (int32_t i = tid; i < nbw; i += kTakeThreads) take_bits[i] = 0u;
+    __syncthreads();
+    const int32_t shift = a.plan.shift, later = a.plan.parts - 1;
+    uint32_t flag = 0u;
+    if (tid < rows) {
+        const int32_t b = rs[tid];
+        if (rs[tid + 1] < b) flag |= kUnsorted;                  // offsets that contradict each other
+        if (rs[tid + 1] <= b)
+            for (int32_t j = 0; j < later; ++j) a.splits[(r0 + tid) * later + j] = b;
+    }
+    const int32_t beg = rs[0], end = rs[rows];
+    auto in_range = [&](int32_t c) { return c < 0 ? 0 : (c >= a.k ? a.k - 1 : c); };
+    // (four loads in flight per lane)
+    for (int32_t e = beg + tid; e < end; e += 4 * kTakeThreads) {
+        int32_t c[4], before[4], row[4];
+        float v[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int32_t i = e + x * kTakeThreads < end ? e + x * kTakeThreads : e;
+            c[x] = a.cols[i];
+            before[x] = a.cols[i > beg ? i - 1 : i];
+            if (a.row_cols) v[x] = a.vals[i];
+            row[x] = row_of_entry<64>(find, i);
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int32_t i = e + x * kTakeThreads;
+            if (i >= end) break;
+            const int32_t col = in_range(c[x]), prev = in_range(before[x]), r = row[x];
+            if (col != c[x]) flag |= kBadColumn;
+            const bool first = rs[r] == i, last = rs[r + 1] == i + 1;
+            if (!first && prev >= col) flag |= kUnsorted;
+            if (a.row_cols) {
+                a.row_cols[i] = col;
+                a.row_vals[i] = v[x];
+            }
+            if (a.bits) atomicOr(&take_bits[col >> 5], 1u << (col & 31));
+            if (later > 0) {
+                int32_t* split = a.splits + (r0 + r) * later - 1;
+                const int32_t part = col >> shift;
+                for (int32_t j = first ? 1 : (prev >> shift) + 1; j <= part; ++j) split[j] = i;
+                if (last)
+                    for (int32_t j = part + 1; j <= later; ++j) split[j] = i + 1;
+            }
+        }
+    }
+    if (flag) atomicOr(&flag_s, flag);
+    __syncthreads();
+    if (tid == 0) a.flags[list] = flag_s;
+    if (a.bits)
+        for (int32_t i = tid; i < nbw; i += kTakeThreads) a.bits[list * nbw + i] = take_bits[i];
+}
+
+struct OrderArgs {
+    const int32_t* row_start;
+    const int32_t* cols;       // entries in row order; clamped here
+    const float* vals;
+    int64_t m, lists;
+    int32_t p, k;
+    OrderPlan plan;
+    const int32_t* gIdxes;
+    const uint32_t* flags;
+    const int32_t* splits;
+    RowsOut out;               // long rows
+    int32_t* dst_cols;
+    int32_t* dst_rows;
+    float* dst_vals;
+    // FUSED only: the input's offsets, and what take_rows would have written
+    const int32_t* row_ptr;
+    int32_t nnz;
+    int64_t g;
+    int32_t* gIdxes_out;
+    int32_t* nnzPerGroup_out;
+    int32_t* row_start_out;
+    uint32_t* flags_out;       // [g]
+};
+
+inline size_t order_lds_bytes(const OrderPlan& plan, int words)
+{
+    const size_t ncols = (size_t)1 << plan.shift, spare = ncols < 256 ? ncols : 256;
+    return (ncols * (words + 1) + 2 * spare) * 4 + (size_t)plan.cap * 9;
+}
+
+// Workgroup (q, part).  WORDS = 32-bit words of a column's mask.  Dynamic LDS: order_lds_bytes().
+// Bound: the latency of the chain of steps.  A thread takes eight entries through each step side by side and keeps them between the
+// two passes where they are all, the parts are small enough for several workgroups per compute unit, and a part's entries leave LDS in
+// their order, so that the stores are whole lines.
+// (Index, two radix passes and bitmaps before, take_rows and this now: 8000 x 8000, 10 %: 190 -> 78 us; 0.5 %: 28 -> 17; 4000 x 4000,
+// 5 %: 41 -> 19; power-law rows, 16384 x 16384: 65 -> 40.)
+//
+// FUSED (one part per group, no band schedule): there is nothing to know about a group but its rows, so this is the whole conversion, one
+// launch instead of two (256 x 256: 4.2 + 6.4 us before, 6.3 so).
+template <int WORDS, bool FUSED>
+__global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
+{
+    constexpr int ROWS = WORDS == 8 ? 256 : 32 * WORDS, WAVES = kOrderThreads / 64, EACH = 8;
+    extern __shared__ uint32_t order_lds[];
+    __shared__ int32_t seg[ROWS], off[ROWS];     // a row's place among the part's entries (or in the input), and what takes it to the input
+    __shared__ int32_t wsum[WAVES], wsum2[WAVES];
+    __shared__ int32_t below_s, count_s;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int32_t parts = a.plan.parts, shift = a.plan.shift, ncols = 1 << shift, later = parts - 1;
+    const int64_t q = blockIdx.x / parts;
+    const int32_t part = (int32_t)(blockIdx.x - q * parts);
+    const int64_t r0 = q * a.p;
+    const int32_t rows = (int32_t)(a.m - r0 < a.p ? a.m - r0 : a.p);
+    // A thread sums up `1 << ps` columns one after another: a word more for each such stretch keeps the threads on different banks.
+    const int32_t ps = shift > 8 ? shift - 8 : 0, spare = ((ncols - 1) >> ps) + 1;
+    uint32_t* mask = order_lds;                              // the masks, then the first places of the columns
+    int32_t* base = (int32_t*)(mask + ncols * WORDS + spare);
+    float* o_val = (float*)(base + ncols + spare);
+    auto mask_at = [&](int32_t col) { return mask + col * WORDS + (col >> ps); };
+    auto base_at = [&](int32_t col) { return base + col + (col >> ps); };
+    int32_t* o_col = (int32_t*)(o_val + a.plan.cap);
+    uint8_t* o_row = (uint8_t*)(o_col + a.plan.cap);
+
+    // everything that does not wait for anything else
+    int32_t g0, g1;
+    int32_t rs0 = 0, re = 0, s = 0, e = 0;
+    if constexpr (FUSED) {
+        auto at = [&](int64_t r) { const int32_t x = a.row_ptr[r]; return x < 0 ? 0 : (x > a.nnz ? a.nnz : x); };    // as in take_rows
+        g0 = at(r0);
+        g1 = at(r0 + rows);
+        if (tid < rows) {
+            rs0 = at(r0 + tid);
+            a.row_start_out[r0 + tid] = rs0;
+        }
+        if (tid == 0) {
+            a.gIdxes_out[q] = g0;
+            a.nnzPerGroup_out[q] = g1 < g0 ? 0 : g1 - g0;
+            if (q == a.g - 1) {
+                a.gIdxes_out[a.g] = g1;
+                a.row_start_out[a.m] = g1;
+            }
+        }
+    } else {
+        g0 = a.gIdxes[q];
+        g1 = a.gIdxes[q + 1];
+    }
+    if (!FUSED && tid < rows) {
+        rs0 = a.row_start[r0 + tid];
+        re = a.row_start[r0 + tid + 1];
+        s = part == 0 ? rs0 : a.splits[(r0 + tid) * later + part - 1];
+        e = part == later ? re : a.splits[(r0 + tid) * later + part];
+    }
+    uint32_t f = 0u;
+    if (!FUSED && parts > 1) {
+        const int64_t l0 = r0 / a.plan.list_rows, l1 = (r0 + rows - 1) / a.plan.list_rows;
+        for (int64_t l = l0 + tid; l <= l1; l += kOrderThreads) f |= a.flags[l];
+    }
+    if (tid == 0) { below_s = 0; count_s = 0; }
+    for (int32_t i = tid; i < ncols * WORDS + spare; i += kOrderThreads) mask[i] = 0u;
+    // With one part the group is taken in the order of the input and nothing depends on the order in its rows.
+    const bool in_order = !FUSED && parts > 1 && __syncthreads_or((int)(f & kUnsorted)) == 0;
+    const bool some = !FUSED && parts > 1 && !in_order;                // entries of other parts are among those looked at
+
+    int32_t n, out0;                                         // entries to look at, place of the part's first one in the arrays
+    if (in_order) {
+        const int32_t len = e - s;
+        int32_t incl = len, skip = s - rs0;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t t = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += t;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) skip += __shfl_xor(skip, d, 64);
+        if (lane == 63) { wsum[wv] = incl; wsum2[wv] = skip; }
+        __syncthreads();
+        int32_t at = incl - len;
+        for (int j = 0; j < wv; ++j) at += wsum[j];
+        n = 0;
+        out0 = g0;
+        for (int j = 0; j < WAVES; ++j) { n += wsum[j]; out0 += wsum2[j]; }
+        if (tid < ROWS) {
+            seg[tid] = tid < rows ? at : INT32_MAX;
+            off[tid] = s - at;
+        }
+    } else {
+        n = g1 - g0;
+        out0 = g0;
+        if (tid < ROWS) {
+            seg[tid] = tid < rows ? rs0 - g0 : INT32_MAX;
+            off[tid] = g0;
+        }
+    }
+    __syncthreads();
+    if (!FUSED && part == 0 && tid < rows && a.out.cols) list_long_row(a.out, (int32_t)r0 + tid, re - rs0);
+    if (n <= 0) {                                            // the whole workgroup
+        if (FUSED && tid == 0) a.flags_out[q] = 0u;
+        return;
+    }
+    const int32_t c0 = part << shift, kmax = a.k - 1;
+    bool bad = false;                                        // FUSED: a column was out of range
+    // entry i of those to look at: its row, its column in the part, its value
+    auto take = [&](int32_t i, int32_t* r, int32_t* c, float* v) {
+        *r = row_of_entry<ROWS>(seg, i);
+        const int32_t at = off[*r] + i, col = a.cols[at];
+        const int32_t inside = col < 0 ? 0 : (col > kmax ? kmax : col);
+        *c = inside - c0;
+        *v = a.vals[at];
+        if (FUSED) bad |= inside != col;
+    };
+    int32_t r[EACH], c[EACH];
+    float v[EACH];
+    auto take_some = [&](int32_t i0) {                       // eight entries per thread; past the end the last one again
+#pragma unroll
+        for (int x = 0; x < EACH; ++x) {
+            const int32_t i = i0 + x * kOrderThreads + tid;
+            take(i < n ? i : n - 1, &r[x], &c[x], &v[x]);
+        }
+    };
+
+    // the masks; what lies before the part and what is in it, where that is not known yet
+    bool twice = false;
+    int32_t below = 0, mine = 0;
+    for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
+        take_some(i0);
+#pragma unroll
+        for (int x = 0; x < EACH; ++x) {
+            if (i0 + x * kOrderThreads + tid >= n) break;
+            if (some) {
+                below += c[x] < 0;
+                if (c[x] < 0 || c[x] >= ncols) continue;
+                ++mine;
+            }
+            if (FUSED && a.out.cols) {                       // the entries in row order
+                a.out.cols[g0 + i0 + x * kOrderThreads + tid] = c[x];
+                a.out.vals[g0 + i0 + x * kOrderThreads + tid] = v[x];
+            }
+            const uint32_t bit = 1u << (r[x] & 31);
+            const uint32_t old = atomicOr(mask_at(c[x]) + (r[x] >> 5), bit);
+            twice |= (old & bit) != 0;
+        }
+    }
+    int32_t count = n;
+    if (some) {
+        if (below) atomicAdd(&below_s, below);
+        if (mine) atomicAdd(&count_s, mine);
+    }
+    if (FUSED) {
+        if (bad) atomicOr(&below_s, 1);
+        twice = __syncthreads_or(twice) != 0;
+        if (tid == 0) a.flags_out[q] = below_s ? kBadColumn : 0u;
+    } else {
+        twice = __syncthreads_or(twice) != 0;
+    }
+    if (some) {
+        out0 = g0 + below_s;
+        count = count_s;
+        if (count == 0) return;                              // the whole workgroup
+    }
+    if (twice) {
+        // counts instead of masks
+        for (int32_t i = tid; i < ncols + spare; i += kOrderThreads) base[i] = 0;
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += kOrderThreads) {
+            int32_t ri, ci;
+            float vi;
+            take(i, &ri, &ci, &vi);
+            if (ci >= 0 && ci < ncols) atomicAdd(base_at(ci), 1);
+        }
+        __syncthreads();
+    }
+    // the first place of every column
+    {
+        const int32_t i0 = tid << ps, i1 = i0 + (1 << ps) < ncols ? i0 + (1 << ps) : ncols;
+        auto entries = [&](int32_t col) {
+            if (twice) return *base_at(col);
+            int32_t x = 0;
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) x += __popc(mask_at(col)[w]);
+            return x;
+        };
+        int32_t sum = 0;
+#pragma unroll 4
+        for (int32_t i = i0; i < i1; ++i) sum += entries(i);
+        int32_t incl = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t t = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += t;
+        }
+        if (lane == 63) wsum[wv] = incl;                     // (read before the barrier above)
+        __syncthreads();
+        int32_t at = incl - sum;
+        for (int j = 0; j < wv; ++j) at += wsum[j];
+#pragma unroll 4
+        for (int32_t i = i0; i < i1; ++i) {
+            const int32_t x = entries(i);
+            *base_at(i) = at;
+            at += x;
+        }
+    }
+    __syncthreads();
+    if (twice) {
+        // 64 entries at a time, in input order
+        if (wv > 0) return;
+        for (int32_t t = 0; t < n; t += 64) {
+            int32_t ri = 0, ci = -1;
+            float vi = 0.0f;
+            if (t + lane < n) take(t + lane, &ri, &ci, &vi);
+            const bool act = ci >= 0 && ci < ncols;
+            uint64_t same = __ballot(act);
+            for (int b = 0; b < shift; ++b) {
+                const bool bit = (ci >> b) & 1;
+                const uint64_t bb = __ballot(act && bit);
+                same &= bit ? bb : ~bb;
+            }
+            const int32_t before = __popcll(same & lanemask_lt());
+            int32_t slot = 0;
+            volatile int32_t* next = base_at(act ? ci : 0);
+            if (act) slot = *next;
+            __builtin_amdgcn_wave_barrier();
+            if (act && before == 0) *next = slot + __popcll(same);
+            __builtin_amdgcn_wave_barrier();
+            if (act) {
+                const int32_t to = out0 + slot + before;
+                a.dst_cols[to] = c0 + ci;
+                a.dst_rows[to] = (int32_t)r0 + ri;
+                a.dst_vals[to] = vi;
+            }
+        }
+        return;
+    }
+    const bool staged = count <= a.plan.cap;
+    for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
+        if (n > EACH * kOrderThreads) take_some(i0);         // (else they are still there)
+#pragma unroll
+        for (int x = 0; x < EACH; ++x) {
+            if (i0 + x * kOrderThreads + tid >= n) break;
+            if (some && (c[x] < 0 || c[x] >= ncols)) continue;
+            int32_t at = *base_at(c[x]);
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) {
+                const uint32_t word = mask_at(c[x])[w];
+                const int32_t b = r[x] - 32 * w;
+                at += __popc(WORDS == 1 || b < 32 ? (b <= 0 ? 0u : word & ((1u << b) - 1u)) : word);
+            }
+            if (staged) {
+                o_val[at] = v[x];
+                o_col[at] = c0 + c[x];
+                o_row[at] = (uint8_t)r[x];
+            } else {
+                a.dst_cols[out0 + at] = c0 + c[x];
+                a.dst_rows[out0 + at] = (int32_t)r0 + r[x];
+                a.dst_vals[out0 + at] = v[x];
+            }
+        }
+    }
+    if (!staged) return;
+    __syncthreads();
+    for (int32_t i = tid; i < count; i += kOrderThreads) {
+        a.dst_cols[out0 + i] = o_col[i];
+        a.dst_rows[out0 + i] = (int32_t)r0 + (int32_t)o_row[i];
+        a.dst_vals[out0 + i] = o_val[i];
+    }
+}
+
+}  // namespace gcoo

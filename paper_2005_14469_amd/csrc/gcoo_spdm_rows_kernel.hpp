@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t
     // where the wave's rows begin (lane i: row w0 + i)
     const int32_t start = lane <= wrows && wrows > 0 ? a.row_ptr[w0 + lane] : 0;
     // the long rows, all slots of the workgroup on each
-    int32_t n_long = *a.long_count;
+    int32_t n_long = a.long_count ? *a.long_count : 0;
     n_long = n_long < a.long_room ? n_long : a.long_room;
     for (int32_t x = wg; x < n_long; x += row_wgs) {
         const int32_t lr = __builtin_amdgcn_readfirstlane(a.long_rows[x]);

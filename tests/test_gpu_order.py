@@ -1,0 +1,56 @@
+"""Ordering a CSR input by column masks where it can go wrong: one part and many, a part that is one column short or over, parts of more
+entries than are put in order in LDS, one, two and eight mask words per column, empty rows at either end, rows whose columns do not
+ascend, coordinates that occur twice.  Bit for bit against the CPU oracle, and the product that the rows and bands give."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gcoo_oracle as orc
+from paper_2005_14469_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _csr(m, k, density, kind, seed):
+    rng = np.random.default_rng(seed)
+    lens = rng.binomial(k, density, m)
+    lens[: m // 7] = 0
+    lens[-(m // 9 + 1):] = 0 if m > 3 else lens[-1]
+    if m > 20:
+        lens[m // 2] = k                                           # one full row
+    cols = []
+    for i, n in enumerate(lens):
+        c = np.sort(rng.choice(k, n, replace=False))
+        if kind != "sorted" and i % 5 == 0:
+            c = rng.permutation(c)
+        if kind == "twice" and i % 3 == 0 and n > 1:
+            c[rng.integers(1, n)] = c[0]
+        cols.append(c.astype(np.int32))
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate(cols).astype(np.int32)
+    return rp, ci, rng.standard_normal(len(ci)).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["sorted", "unsorted", "twice"])
+@pytest.mark.parametrize("m,k,density,p", [(1, 1, 1.0, 1), (3, 130, 0.5, 32), (500, 127, 0.2, 32), (500, 128, 0.2, 33), (300, 4096, 0.02, 32),
+                                           (300, 4097, 0.02, 31), (300, 8193, 0.01, 32), (130, 2049, 0.05, 64), (400, 300, 0.9, 64),
+                                           (400, 1000, 0.3, 65), (600, 513, 0.1, 256), (1500, 700, 0.03, 8), (2100, 900, 0.05, 1)])
+def test_ordered_by_masks(m, k, density, p, kind):
+    print(f"order: {m}x{k} d={density} p={p} {kind}", flush=True)
+    rp, ci, va = _csr(m, k, density, kind, seed=m + k + p)
+    want = orc.gcoo_from_csr(m, k, rp, ci, va, p)
+    dev = [torch.from_numpy(x).to(DEV) for x in (rp, ci, va)]
+    A = binding.gcoo_from_csr(m, k, *dev, p, known_nnz=True)
+    e = A.export()
+    for key in ("rows", "cols", "gIdxes", "nnzPerGroup"):
+        assert np.array_equal(e[key], getattr(want, key)), key
+    assert np.array_equal(e["values"].view(np.uint32), want.values.view(np.uint32))
+    B = np.random.default_rng(p).standard_normal((k, 20)).astype(np.float32)
+    C64, D64 = orc.spdm_csr(k, 20, rp, ci, va, B)
+    for variant in (binding.VARIANT_AUTO, binding.VARIANT_LDS):
+        got = binding.gcoo_spdm(A, torch.from_numpy(B).to(DEV), variant=variant)
+        err, bad = orc.max_scaled_error(got.cpu().numpy(), C64, D64)
+        assert bad == 0 and err < 2e-6, (variant, err, bad)
