@@ -31,7 +31,7 @@
 namespace gcoo {
 
 constexpr int kRowsThreads = 256;
-constexpr int kRowsPerWave = 32;         // at most
+constexpr int kShortRowsPerWave = 8;     // rows per wave where they are short, at most
 typedef float rows_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t rows_u32x4 __attribute__((ext_vector_type(4)));
 

@@ -12,12 +12,13 @@ static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
     const int64_t tiles = (a.N + (aligned ? 0 : 31) + tile - 1) / tile, mean = a.nnz / a.m;
     auto groups = [&](int64_t r) { return (a.m + waves * r - 1) / (waves * r); };
     // Rows per wave: one per slot, so that a launch has many short workgroups.  Short rows (one batch each) go several to a
-    // slot, the loads of one behind those of the one before, while enough workgroups are left (12001 rows of 6 entries: 460 us
-    // with 16 rows per wave, 474 with 8, 536 with 4; rows of 25 to 80 entries are fastest with 4).  A launch that cannot
+    // slot, the loads of one behind those of the one before, while enough workgroups are left (64 columns per tile, rows of 6 entries,
+    // 12000 x 12000: 445 us with 4 rows per wave, 408 with 8, 399 with 16; rows of 12: 553, 499, 501; 12001 x 12001: 512, 471, 472 and
+    // 683, 653, 708; rows of 25 to 80 entries are fastest with 4).  A launch that cannot
     // fill the chip has fewer rows per wave, each on all slots of it.
     int64_t rpw = spw;
     if (mean <= 12) {
-        while (2 * rpw <= kRowsPerWave / 2 && groups(2 * rpw) * tiles >= 4096) rpw *= 2;
+        while (2 * rpw <= kShortRowsPerWave && groups(2 * rpw) * tiles >= 4096) rpw *= 2;
     } else {
         while (rpw > 1 && groups(rpw) * tiles < 256) rpw /= 2;
     }
@@ -49,8 +50,11 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     if (a.N <= 32) return launch_rows<8>(a, s);
     // 128 columns per tile while the tile stays in an XCD's L2 (4 MB): rows of B that do not start at 128-byte lines cost a line
     // more per segment (3000 x 3000, 1 %: N = 2999 59.9 us with 64 columns, 50.9 with 128; 9001 columns: 452 and 460).
+    // Rows of a few entries take theirs from a tile of B hardly more than once before it has to be read anyway, so that the wider
+    // stretches of B and C count for more than the L2 (rows of 6 entries: 12000 columns 399 -> 377 us, 12001 472 -> 435; rows of 9,
+    // 9024 columns: 242 -> 235; rows of 12, 12000: 499 -> 521).
     const bool lines = a.ldb % 32 == 0 && reinterpret_cast<uintptr_t>(a.B) % 128 == 0;
-    if (a.N > 64 && a.k <= (lines ? 4096 : 6500)) return launch_rows<32>(a, s);
+    if (a.N > 64 && (a.k <= (lines ? 4096 : 6500) || a.nnz <= 9 * a.m)) return launch_rows<32>(a, s);
     return launch_rows<16>(a, s);
 }
 

@@ -91,3 +91,10 @@ def test_repeated_and_non_finite():
     w = _rows_of_lengths([3, 9, 0, 20] * 10, 400, 36, seed=5)
     w.B[np.setdiff1d(np.arange(w.k), w.col_idx)] = np.inf
     _check(w, 16)
+
+
+@pytest.mark.parametrize("k,N", [(7000, 131), (9001, 320)])
+def test_a_few_entries_per_row_of_many_columns(k, N):
+    """Rows short enough for the wide tiles whatever k is, and one row beyond: 16 entries and more beside them."""
+    print(f"rows: few entries, k={k} N={N}", flush=True)
+    _check(_rows_of_lengths([0, 3, 9, 1, 7, 12, 2, 16, 5, 17, 4, 6, 8, 0, 1, 40] * 9, k, N, seed=k), 32)
