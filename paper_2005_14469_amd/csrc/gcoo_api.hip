@@ -10,6 +10,7 @@
 #include <new>
 #include <string>
 
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <memory>
@@ -116,6 +117,104 @@ private:
     unsigned long long* host_ = nullptr;
     unsigned long long* ticket_ = nullptr;
 };
+
+// Pinned memory in which a host CSR input waits for the device: the call copies the caller's arrays there (5 us for half a
+// megabyte, where a copy from pageable memory takes 17 to 25 us for each array) and need not wait for the device, whose kernels read them where
+// they are or from one copy.  kStageSlots buffers of kStageBytes each, allocated when first needed and held until the process ends; a buffer is free
+// again when the event behind its last reader has come.  Larger inputs, and calls that find all buffers in the hands of other threads, are
+// copied from the caller's arrays.
+constexpr int kStageSlots = 4;
+constexpr size_t kStageBytes = 4u << 20;
+class HostStage {
+public:
+    ~HostStage()
+    {
+        if (!slot_) return;
+        (void)hipDeviceSynchronize();                         // (a call that failed: its launches may still read the buffer)
+        give_back(false);
+    }
+    // false: none to be had (or HIP failed, which the copies that follow will say)
+    bool claim()
+    {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess) return false;
+        std::unique_lock<std::mutex> lock(mutex());
+        Slot* found = nullptr;
+        Slot* oldest = nullptr;
+        for (Slot& s : slots()) {
+            if (s.held) continue;
+            if (!s.in_flight || hipEventQuery(s.event) == hipSuccess) { found = &s; break; }
+            if (!oldest || s.turn < oldest->turn) oldest = &s;
+        }
+        (void)hipGetLastError();                              // (an event that has not come is no error)
+        if (!found && !oldest) return false;
+        slot_ = found ? found : oldest;
+        slot_->held = true;
+        if (!found) {
+            lock.unlock();
+            const hipError_t e = hipEventSynchronize(slot_->event);
+            lock.lock();
+            if (e != hipSuccess) { slot_->held = false; slot_ = nullptr; return false; }
+        }
+        slot_->in_flight = false;
+        if (slot_->event && slot_->device != dev) { (void)hipEventDestroy(slot_->event); slot_->event = nullptr; }
+        if (!slot_->event) {
+            if (hipEventCreateWithFlags(&slot_->event, hipEventDisableTiming) != hipSuccess) slot_->event = nullptr;
+            slot_->device = dev;
+        }
+        if (!slot_->ptr && hipHostMalloc(&slot_->ptr, kStageBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) slot_->ptr = nullptr;
+        if (slot_->event && slot_->ptr) return true;
+        (void)hipGetLastError();
+        slot_->held = false;
+        slot_ = nullptr;
+        return false;
+    }
+    char* ptr() const { return static_cast<char*>(slot_->ptr); }
+    explicit operator bool() const { return slot_ != nullptr; }
+    // Behind the last launch that reads the buffer.
+    hipError_t release(hipStream_t s)
+    {
+        const hipError_t e = hipEventRecord(slot_->event, s);
+        give_back(e == hipSuccess);
+        return e;
+    }
+
+private:
+    struct Slot {
+        void* ptr = nullptr;
+        hipEvent_t event = nullptr;
+        int device = -1;
+        bool held = false, in_flight = false;
+        uint64_t turn = 0;
+    };
+    static std::mutex& mutex() { static std::mutex m; return m; }
+    static std::array<Slot, kStageSlots>& slots() { static std::array<Slot, kStageSlots> s; return s; }
+    void give_back(bool in_flight)
+    {
+        static uint64_t turns = 0;
+        std::lock_guard<std::mutex> lock(mutex());
+        slot_->held = false;
+        slot_->in_flight = in_flight;
+        slot_->turn = ++turns;
+        slot_ = nullptr;
+    }
+    Slot* slot_ = nullptr;
+};
+
+// Offsets of rows that do not descend and columns inside [0, k), without a branch per element.
+bool csr_in_bounds(const int32_t* row_ptr, int64_t m, const int32_t* col_idx, int64_t nnz, int64_t k)
+{
+    int bad = 0;
+    for (int64_t i = 0; i < m; ++i) bad |= row_ptr[i + 1] < row_ptr[i];
+    if (bad) return false;
+    const int32_t most = (int32_t)(k - 1);
+    for (int64_t e0 = 0; e0 < nnz; e0 += 4096) {
+        const int64_t e1 = e0 + 4096 < nnz ? e0 + 4096 : nnz;
+        for (int64_t e = e0; e < e1; ++e) bad |= (col_idx[e] < 0) | (col_idx[e] > most);
+        if (bad) return false;
+    }
+    return true;
+}
 
 // Scratch of gcoo_from_csr_device_static(), the conversion for callers that may not allocate device
 // memory: the second buffer of the per-group radix sort (3 arrays of nnz words) and the counter from
@@ -717,12 +816,10 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         }
     } else {
         if (row_ptr[0] != 0) return GCOO_EBOUNDS;
-        for (int64_t i = 0; i < m; ++i)
-            if (row_ptr[i + 1] < row_ptr[i]) return GCOO_EBOUNDS;
+        if (!csr_in_bounds(row_ptr, m, nullptr, 0, k)) return GCOO_EBOUNDS;
         nnz = row_ptr[m];
         if (nnz > 0 && (!col_idx || !vals)) return GCOO_EINVAL;
-        for (int64_t e = 0; e < nnz; ++e)
-            if (col_idx[e] < 0 || col_idx[e] >= k) return GCOO_EBOUNDS;
+        if (!csr_in_bounds(row_ptr, 0, col_idx, nnz, k)) return GCOO_EBOUNDS;
     }
     if (nnz > 0 && (!col_idx || !vals)) return GCOO_EINVAL;
     const Layout L = make_layout(m, k, nnz, g, p, inside);
@@ -738,7 +835,31 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     const int32_t* d_row_ptr = row_ptr;
     const int32_t* d_cols = col_idx;
     const float* d_vals = vals;
-    if (!src_on_device) {
+    HostStage stage;
+    const size_t in_bytes = L.in_vals + (size_t)nnz * 4 - L.in_row_ptr;          // row_ptr, columns and values as they lie in the scratch area
+    if (!src_on_device && in_bytes <= kStageBytes && stage.claim()) {
+        // the caller may release its host arrays as soon as this call returns
+        char* to = stage.ptr();
+        std::memcpy(to, row_ptr, (size_t)(m + 1) * 4);
+        if (nnz > 0) {
+            std::memcpy(to + (L.in_cols - L.in_row_ptr), col_idx, (size_t)nnz * 4);
+            std::memcpy(to + (L.in_vals - L.in_row_ptr), vals, (size_t)nnz * 4);
+        }
+        if (L.by_masks && h->has_rows()) {
+            // every word of the input is read once: the kernel takes it from where it is
+            void* seen = nullptr;
+            hipError_t e = hipHostGetDevicePointer(&seen, to, 0);
+            if (e != hipSuccess) { delete h; return hip_fail(e, "hipHostGetDevicePointer"); }
+            to = static_cast<char*>(seen);
+        } else {
+            hipError_t e = hipMemcpyAsync(scratch + L.in_row_ptr, to, in_bytes, hipMemcpyHostToDevice, s);
+            if (e != hipSuccess) { delete h; return hip_fail(e, "copy of the CSR input to the device"); }
+            to = scratch + L.in_row_ptr;
+        }
+        d_row_ptr = reinterpret_cast<const int32_t*>(to);
+        d_cols = reinterpret_cast<const int32_t*>(to + (L.in_cols - L.in_row_ptr));
+        d_vals = reinterpret_cast<const float*>(to + (L.in_vals - L.in_row_ptr));
+    } else if (!src_on_device) {
         int32_t* sp = reinterpret_cast<int32_t*>(scratch + L.in_row_ptr);
         int32_t* sc = reinterpret_cast<int32_t*>(scratch + L.in_cols);
         float* sv = reinterpret_cast<float*>(scratch + L.in_vals);
@@ -826,6 +947,11 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             if (e != hipSuccess) { delete h; return hip_fail(e, "sort_groups_by_col_digit"); }
             src_c = dc; src_r = dr; src_v = dv;
         }
+    }
+    if (stage) {
+        // (what follows reads the entries in row order; with more than 64 rows per group, the copy on the device)
+        hipError_t e = stage.release(s);
+        if (e != hipSuccess) { delete h; return hip_fail(e, "hipEventRecord"); }
     }
     rc = launch_build_schedule(h, scratch, s, marked);
     if (rc != GCOO_OK) { delete h; return rc; }

@@ -122,8 +122,11 @@ __global__ __launch_bounds__(kTakeThreads) void take_rows(TakeArgs a)
         for (int x = 0; x < 4; ++x) {
             const int32_t i = e + x * kTakeThreads < end ? e + x * kTakeThreads : e;
             c[x] = a.cols[i];
-            before[x] = a.cols[i > beg ? i - 1 : i];
             if (a.row_cols) v[x] = a.vals[i];
+            // the column before it, from the lane before; the first lane of a wave reads it (the input may be host memory)
+            before[x] = (tid & 63) == 0 && i > beg ? a.cols[i - 1] : 0;
+            const int32_t lane_before = __shfl_up(c[x], 1, 64);
+            if ((tid & 63) != 0) before[x] = lane_before;
             row[x] = row_of_entry<64>(find, i);
         }
 #pragma unroll
