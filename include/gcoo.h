@@ -239,7 +239,8 @@ int gcoo_export(const gcoo_matrix* A, float* values, int32_t* rows, int32_t* col
 
 /*
  * Which kernel-private schedules conversions build (process-wide setting; takes effect for matrices converted afterwards).
- * GCOO_SHARE_AUTO: the band schedule where a product with a B as wide as A gains by it, and for p <= 48, density at most 6 %, and
+ * GCOO_SHARE_AUTO: the band schedule (unless the rows turn out uneven, which the device finds and acts on) where a product with a B as
+ *   wide as A gains by it, and for p <= 48, density at most 6 %, and
  *   at least 1.5 % from 3500 columns on, 0.8 % from 5500, 0.35 % from 7000 (at most 262144 columns): there
  *   GCOO_VARIANT_SHARE can be asked for;
  * GCOO_SHARE_ALWAYS: also the run schedule that GCOO_VARIANT_REG then reads, and the share schedule that GCOO_VARIANT_SHARE then

@@ -117,8 +117,8 @@ def verify_band_code(stem: str, text: str) -> None:
     itself, nothing is in flight at a barrier, and its asm text writes the scalar registers that its clobber list names."""
     from . import isa_check
     for kernel in ("_ZN4gcoo9spdm_bandILb0E", "_ZN4gcoo9spdm_bandILb1E"):
-        loads, problems = isa_check.check_lds_loads(text, kernel)
-        if loads < 15 or problems:
+        loads, problems = isa_check.check_lds_loads(text, kernel, asm_only=True)
+        if loads < 15 or problems or isa_check.check_lds_loads(text, kernel)[0] != loads:
             raise RuntimeError(f"{stem} {kernel}: {loads} loads to LDS, {problems[:3]}")
         written, read = isa_check.asm_scalar_writes(text, kernel)
         if written != set(range(12, 32)) | set(range(36, 100)) or not read:

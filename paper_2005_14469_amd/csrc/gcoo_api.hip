@@ -259,7 +259,7 @@ struct Layout {
     size_t take_flags, splits;
     size_t tmp_cols, tmp_rows, tmp_vals;                   // conversion scratch (second sort buffer)
     size_t in_row_ptr, in_cols, in_vals;                   // staging of a host CSR input
-    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4)
+    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4), uneven rows (4)
     size_t persistent;                                     // bytes up to here stay in use after the conversion
     // offsets from here on are relative to the scratch area: the caller's buffer from `persistent` on, or the
     // library's static scratch
@@ -582,6 +582,7 @@ struct gcoo_matrix {
     int32_t* row_cols() const { return reinterpret_cast<int32_t*>(base + L.row_cols); }
     float* row_vals() const { return reinterpret_cast<float*>(base + L.row_vals); }
     int32_t* long_rows() const { return reinterpret_cast<int32_t*>(base + L.row_long); }
+    uint32_t* uneven() const { return reinterpret_cast<uint32_t*>(base + L.counter + 24); }
     int32_t* long_count() const { return reinterpret_cast<int32_t*>(base + L.counter + 20); }
     uint32_t* band_head() const { return reinterpret_cast<uint32_t*>(base + L.band_head); }
     uint32_t* band_units() const { return reinterpret_cast<uint32_t*>(base + L.band_units); }
@@ -715,7 +716,8 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
         const size_t words = (size_t)((h->k + 31) / 32);
         uint32_t* parts = reinterpret_cast<uint32_t*>(scratch + h->L.tmp_cols);          // the second sort buffer, free by now
         uint32_t* alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
-        if (!marked) gcoo::band_mark<<<dim3(lists), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows, parts, alloc);
+        if (!marked) gcoo::band_mark<<<dim3(lists), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows, parts, alloc,
+                                                                                                                gcoo::band_heavy(h->nnz, lists), h->uneven());
         HIP_TRY(hipGetLastError());
         int64_t chunk = (h->k + gcoo::kBandRows - 1) / gcoo::kBandRows * gcoo::kBandRows;
         const int64_t most = (int64_t)(kBandFillMaxLds - words * 8) / (4 * gcoo::kBandRows + 4 * gcoo::kBandRows / gcoo::kBandGroup) * gcoo::kBandRows;
@@ -725,7 +727,7 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
         const bool large = h->nnz / lists > 4096;
         (large ? gcoo::band_fill<1024> : gcoo::band_fill<512>)<<<dim3(lists), dim3(large ? 1024 : 512), words * 8 + (size_t)(chunk + chunk / gcoo::kBandGroup) * 4, s>>>(
             h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk, gcoo::band_units(h->nnz, h->m, h->k, rows),
-            gcoo::band_head_stride(h->k), h->band_head(), h->band_units(), h->band_first(), h->band_count(), alloc);
+            gcoo::band_head_stride(h->k), h->band_head(), h->band_units(), h->band_first(), h->band_count(), alloc, h->uneven());
         HIP_TRY(hipGetLastError());
     }
     return GCOO_OK;
@@ -893,15 +895,16 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         t.row_cols = h->has_rows() ? h->row_cols() : nullptr; t.row_vals = h->row_vals();
         t.flags = h->take_flags(); t.splits = reinterpret_cast<int32_t*>(base + L.splits);
         t.bits = marked ? reinterpret_cast<uint32_t*>(scratch + L.tmp_cols) : nullptr;
+        t.heavy = marked ? gcoo::band_heavy(nnz, L.lists) : INT32_MAX;
         t.zero_bad = h->bad_col(); t.zero_alloc = reinterpret_cast<uint32_t*>(scratch + L.share_alloc);
         t.stats = h->has_sched ? stats : nullptr;
-        gcoo::take_rows<<<dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(gcoo::kTakeThreads), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
+        (stage ? gcoo::take_rows<true> : gcoo::take_rows<false>)<<<dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(gcoo::kTakeThreads), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "take_rows"); }
         gcoo::OrderArgs o{};
         o.row_start = h->row_start(); o.cols = h->has_rows() ? h->row_cols() : d_cols; o.vals = h->has_rows() ? h->row_vals() : d_vals;
         o.m = m; o.lists = L.lists; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.gIdxes = h->gIdxes(); o.flags = t.flags; o.splits = t.splits;
-        o.out = rows_out(h); o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
+        o.out = rows_out(h); o.uneven = marked ? h->uneven() : nullptr; o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
         (words == 1 ? gcoo::order_groups<1, false> : (words == 2 ? gcoo::order_groups<2, false> : gcoo::order_groups<8, false>))<<<
             dim3((unsigned)(g * L.plan.parts)), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
         e = hipGetLastError();
@@ -1280,17 +1283,20 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     }
     if (A->inner) A = A->inner;        // the schedules of the kernels below belong to the regrouped copy
     const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
-    auto run_rows = [&]() -> int {
+    auto rows_args = [&]() {
         gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
                          A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
         if (A->from_csr && A->L.by_masks && A->L.plan.fused) { a.long_count = nullptr; a.long_row = INT32_MAX; }     // (none are listed)
-        hipError_t e = gcoo::launch_spdm_rows(a, s);
+        return a;
+    };
+    auto run_rows = [&]() -> int {
+        hipError_t e = gcoo::launch_spdm_rows(rows_args(), s);
         return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
     };
     auto run_band = [&]() -> int {
         gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band_h), A->L.band_h,
-                         0, 0, gcoo::band_head_stride(A->k), A->m, A->k, B_dev, ldb, N, C_dev, ldc};
-        hipError_t e = gcoo::launch_spdm_band(a, s);
+                         0, 0, A->uneven(), gcoo::band_head_stride(A->k), A->m, A->k, B_dev, ldb, N, C_dev, ldc};
+        hipError_t e = gcoo::launch_spdm_band(a, rows_args(), s);
         return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_band launch");
     };
     if (automatic && A->has_rows() && A->k >= 1) {

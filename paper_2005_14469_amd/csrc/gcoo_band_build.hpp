@@ -34,12 +34,13 @@ __device__ __forceinline__ BandList band_list(const int32_t* __restrict__ row_st
 // is irrelevant.  Dynamic LDS: ceil(k/32) words.
 __global__ __launch_bounds__(kBandMarkThreads) void band_mark(const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_cols,
                                                               int64_t m, int64_t k, int32_t h, uint32_t* __restrict__ parts,
-                                                              uint32_t* __restrict__ zeroed)
+                                                              uint32_t* __restrict__ zeroed, int32_t heavy, uint32_t* __restrict__ uneven)
 {
     extern __shared__ uint32_t band_lds[];
     if (blockIdx.x == 0 && threadIdx.x == 0) *zeroed = 0u;            // the counter from which band_fill places the lists
     const int32_t nbw = (int32_t)((k + 31) / 32);
     const BandList l = band_list(row_start, m, h, blockIdx.x);
+    if (threadIdx.x == 0 && l.end - l.beg > heavy) *uneven = 1u;      // (zero so far)
     for (int32_t i = threadIdx.x; i < nbw; i += kBandMarkThreads) band_lds[i] = 0u;
     __syncthreads();
     for (int32_t e = l.beg + (int32_t)threadIdx.x; e < l.end; e += 4 * kBandMarkThreads) {
@@ -105,8 +106,10 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                                                               const float* __restrict__ row_vals, int64_t m, int64_t k, int32_t h,
                                                               const uint32_t* __restrict__ parts, int32_t chunk, int64_t capacity,
                                                               int64_t head_stride, uint32_t* __restrict__ head, uint32_t* __restrict__ units,
-                                                              int32_t* __restrict__ first, int32_t* __restrict__ count, uint32_t* __restrict__ alloc)
+                                                              int32_t* __restrict__ first, int32_t* __restrict__ count, uint32_t* __restrict__ alloc,
+                                                              const uint32_t* __restrict__ uneven)
 {
+    if (*uneven != 0u) return;                                 // the product goes row by row
     constexpr int kBandBuildWaves = kBandBuildThreads / 64;
     static_assert(kBandChunkBands <= kBandBuildThreads, "");
     extern __shared__ uint32_t band_lds[];

@@ -66,8 +66,9 @@ __global__ __launch_bounds__(256) void group_index_from_row_ptr(const int32_t* _
                                                                  uint32_t* __restrict__ bad_col, int32_t* __restrict__ row_start)
 {
     if (stats && blockIdx.x == gridDim.x - 1) {                   // the whole workgroup
-        // bad_col[0] is set by the sort that follows if it meets a column out of range, bad_col[1] counts the rows it lists as long
-        if (threadIdx.x < 2) bad_col[threadIdx.x] = 0u;
+        // bad_col[0] is set by the sort that follows if it meets a column out of range, bad_col[1] counts the rows it lists as long,
+        // bad_col[2] is set for uneven rows
+        if (threadIdx.x < 3) bad_col[threadIdx.x] = 0u;
         group_stats_block<256>(row_ptr, m, p, g, stats);
         return;
     }
@@ -484,7 +485,7 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
 // SMALL (at most 64 rows per group): the count leaves a bit per element behind, and only the elements that are entries
 // are read a second time, the next one of each column together; taller groups walk the columns again.
 // (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)
-// The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..1].
+// The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..2].
 // ---------------------------------------------------------------------------------------------
 template <int VW, bool SMALL>
 __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
@@ -494,7 +495,7 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
 {
     __shared__ int32_t wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (blockIdx.x == 0 && tid < 2) zeroed[tid] = 0u;
+    if (blockIdx.x == 0 && tid < 3) zeroed[tid] = 0u;
     if (from.gIdxes != to.gIdxes) {
         if (blockIdx.x == 0 && tid < 2) to.stats[tid] = from.stats[tid];
         for (int64_t q = (int64_t)blockIdx.x * kDenseThreads + tid; q <= g; q += (int64_t)gridDim.x * kDenseThreads) {

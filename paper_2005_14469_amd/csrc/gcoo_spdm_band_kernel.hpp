@@ -25,6 +25,7 @@
 
 #include "gcoo_band.hpp"
 #include "gcoo_spdm_launch.hpp"
+#include "gcoo_spdm_rows_kernel.hpp"
 
 namespace gcoo {
 
@@ -230,10 +231,23 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
           "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", "s92",  \
           "s93", "s94", "s95", "s96", "s97", "s98", "s99")
 
+// How the launch works row by row instead: items of kBandWaves x rpw rows x 64 columns, strided over the workgroups.
+struct BandRowsGrid { int32_t tiles, row_wgs, rpw, wave_row, items; };
+
+// A matrix with a list of far more entries than the others (take_rows and band_mark say so on the device, where the
+// row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, as the row-by-row
+// kernel does, by the workgroups of this launch.
 template <bool UNALIGNED>
-__global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a)
+__global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
+    if (*a.uneven != 0u) {
+        for (uint32_t block = blockIdx.x; block < (uint32_t)rg.items; block += gridDim.x) {
+            rows_item<16, false, kBandWaves>(by_rows, block, rg.tiles, rg.row_wgs, rg.rpw, rg.wave_row, reinterpret_cast<float(*)[64]>(band_smem));
+            __syncthreads();
+        }
+        return;
+    }
     // XCD-aware order: XCD x walks the contiguous slice [x*per, (x+1)*per) of the tile-major list, so the blocks that run on
     // it together read the same column tile of B.
     const int32_t per = (int32_t)(a.grid >> 3);

@@ -99,6 +99,7 @@ struct BandArgs {
     int32_t blocks;
     int32_t h;                 // rows per wave
     int32_t total, grid;       // workgroups with work, workgroups launched (set by the launcher)
+    const uint32_t* uneven;    // not 0: no schedule was built, the rows are multiplied one by one
     int64_t head_stride;
     int64_t m;
     int64_t k;
@@ -108,6 +109,7 @@ struct BandArgs {
     float* C;
     int64_t ldc;
 };
-hipError_t launch_spdm_band(const BandArgs& a, hipStream_t s);
+// `rows` is for a matrix whose rows turn out to be uneven.
+hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t s);
 
 }  // namespace gcoo

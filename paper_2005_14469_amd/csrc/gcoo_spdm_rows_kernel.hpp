@@ -150,16 +150,16 @@ __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& 
     }
 }
 
-// Workgroup (tile, wg): rows [wg * 4 * rpw, ...), `rpw` of them per wave, columns of the tile.
-template <int LPR, bool WIDE>
-__global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
+// Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.
+// `part`: WAVES * 64 / LPR stretches of a tile's columns in LDS.
+template <int LPR, bool WIDE, int WAVES>
+__device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
 {
-    constexpr int SPW = 64 / LPR, WAVES = kRowsThreads / 64, SLOTS = SPW * WAVES, TILE = LPR * 4;
-    __shared__ __attribute__((aligned(16))) float part[SLOTS][TILE];
+    constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES, TILE = LPR * 4;
     // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
     // eight XCDs work on eight tiles side by side, so that what they read and write of a row at about the same time is one
     // stretch of 2 KB.  The tiles beyond the last whole eight are cut into eight slices of rows.
-    const int32_t xcd = (int32_t)(blockIdx.x & 7u), at = (int32_t)(blockIdx.x >> 3), eights = tiles / 8;
+    const int32_t xcd = (int32_t)(block & 7u), at = (int32_t)(block >> 3), eights = tiles / 8;
     int32_t tile, wg;
     if (at < eights * row_wgs) {
         tile = at / row_wgs * 8 + xcd;
@@ -285,6 +285,13 @@ __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t
         end = end2;
         whole = whole2;
     }
+}
+
+template <int LPR, bool WIDE>
+__global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
+{
+    __shared__ __attribute__((aligned(16))) float part[kRowsThreads / LPR][LPR * 4];
+    rows_item<LPR, WIDE, kRowsThreads / 64>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
 }
 
 // B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a

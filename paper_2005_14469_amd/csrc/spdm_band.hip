@@ -6,7 +6,7 @@
 namespace gcoo {
 
 template <bool UNALIGNED>
-static hipError_t launch_band(const BandArgs& a, hipStream_t s)
+static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const BandRowsGrid& rg, hipStream_t s)
 {
     // more LDS than the default limit of a workgroup: asked for once per device
     static std::atomic<unsigned> done[64];
@@ -19,11 +19,11 @@ static hipError_t launch_band(const BandArgs& a, hipStream_t s)
         if (e != hipSuccess) return e;
         done[dev].store(1u, std::memory_order_release);
     }
-    spdm_band<UNALIGNED><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a);
+    spdm_band<UNALIGNED><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
     return hipGetLastError();
 }
 
-hipError_t launch_spdm_band(const BandArgs& a, hipStream_t s)
+hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t s)
 {
     const int64_t tiles = (a.N + 255) / 256, total = a.blocks * tiles;
     if (total <= 0 || total > 0x7ffffff0LL) return hipErrorInvalidConfiguration;
@@ -34,7 +34,17 @@ hipError_t launch_spdm_band(const BandArgs& a, hipStream_t s)
     BandArgs b = a;
     b.total = (int32_t)total;
     b.grid = (int32_t)((total + 7) / 8 * 8);                 // whole rounds over the 8 XCDs
-    return aligned ? launch_band<false>(b, s) : launch_band<true>(b, s);
+    // as in the launch of the row-by-row kernel: a row per slot, a tile of 64 columns
+    BandRowsGrid rg;
+    const int64_t mean = rows.nnz / rows.m, wave_row = 2 * mean > 64 ? 2 * mean : 64;
+    rg.tiles = (int32_t)((rows.N + 31 + 63) / 64);
+    rg.rpw = 4;
+    rg.row_wgs = (int32_t)((rows.m + kBandWaves * rg.rpw - 1) / (kBandWaves * rg.rpw));
+    rg.wave_row = (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row);
+    const int64_t rest = (int64_t)(rg.tiles % 8) * rg.row_wgs, items = (int64_t)(rg.tiles / 8 * 8) * rg.row_wgs + (rest + 7) / 8 * 8;
+    if (items > 0x7fffffffLL || rows.N < 4) return hipErrorInvalidConfiguration;
+    rg.items = (int32_t)items;
+    return aligned ? launch_band<false>(b, rows, rg, s) : launch_band<true>(b, rows, rg, s);
 }
 
 }  // namespace gcoo

@@ -186,7 +186,7 @@ def check(asm_text: str, mangled_prefix: str):
     return sorted(load_regs), bad
 
 
-def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0):
+def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0, asm_only: bool = False):
     """Loads that write LDS directly (`global_load_lds_*`, `buffer_load_* ... lds`) in a kernel that also uses the VGPR index mode.
 
     Such a load takes the LDS address of lane 0 from M0, and `s_set_gpr_idx_on/idx` overwrite M0.
@@ -197,8 +197,16 @@ def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0):
       * walking back from every `s_barrier`, an `s_waitcnt` that names vmcnt(n), n <= in_flight, comes before
         any such load (what a wave has sent to LDS has arrived before the other waves are let past the
         barrier, except the youngest in_flight loads, which a kernel may keep on their way on purpose).
+    asm_only: look at the asm statements only, for a kernel all of whose loads to LDS are in one of them that ends with
+    nothing in flight.
     """
-    body = [l.split(";")[0].strip() for l in kernel_body(asm_text, mangled_prefix)]
+    lines, inside = [], False
+    for l in kernel_body(asm_text, mangled_prefix):
+        if "#ASMSTART" in l or "#ASMEND" in l:
+            inside = "#ASMSTART" in l
+        elif inside or not asm_only:
+            lines.append(l)
+    body = [l.split(";")[0].strip() for l in lines]
     body = [l for l in body if l]
     def to_lds(t):
         return t.startswith("global_load_lds") or (t.startswith("buffer_load") and t.endswith(" lds"))

@@ -87,3 +87,32 @@ def test_repeated_coordinates_and_skewed_rows():
     assert 0.015 * z.m * z.k < z.nnz < 0.06 * z.m * z.k
     print("band: skewed rows", flush=True)
     _run(z, 40, binding.VARIANT_SHARE)
+
+
+@pytest.mark.parametrize("dense,p,N,shift", [(False, 32, 1024, 0), (False, 64, 1021, 1), (True, 32, 1024, 0), (False, 32, 260, 0)])
+def test_uneven_rows_are_multiplied_one_by_one(dense, p, N, shift):
+    """A matrix that gets a band schedule by its size, with one list of rows of far more entries than the others: the launch of the
+    sixteen-wave kernel works row by row.  GCOO_VARIANT_SHARE asks for that kernel where it is served."""
+    print(f"band: uneven rows dense={dense} p={p} N={N}", flush=True)
+    rng = np.random.default_rng(N + p)
+    m, k = 4000, 3600
+    lens = rng.integers(40, 90, m)
+    lens[1000:1012] = 3000
+    cols = [np.sort(rng.choice(k, n, replace=False)).astype(np.int32) for n in lens]
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate(cols)
+    w = workloads.Workload("uneven", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, N)).astype(np.float32))
+    if dense:
+        Ah = np.zeros((m, k), np.float32)
+        Ah[np.repeat(np.arange(m), lens), ci] = w.vals
+        A = binding.gcoo_from_dense(torch.from_numpy(Ah).to(DEV), p)
+    else:
+        A = binding.gcoo_from_csr(m, k, *[torch.from_numpy(x).to(DEV) for x in (rp, ci, w.vals)], p, known_nnz=True)
+    Bbig = torch.zeros((k, N + shift), device=DEV)
+    Bbig[:, shift:] = torch.from_numpy(w.B).to(DEV)
+    C64, D64 = orc.spdm_csr(k, N, rp, ci, w.vals, w.B)
+    for variant in (binding.VARIANT_AUTO, binding.VARIANT_SHARE) if p <= 48 and not shift else (binding.VARIANT_AUTO,):
+        C = binding.gcoo_spdm(A, Bbig[:, shift:], variant=variant)
+        err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
+        assert bad == 0 and err < 2e-6, (variant, err, bad)
+        assert torch.equal(C, binding.gcoo_spdm(A, Bbig[:, shift:], variant=variant))
