@@ -146,7 +146,7 @@ class GcooMatrix:
     """Owner of one handle and of the torch buffer behind it."""
 
     def __init__(self, handle, buf: torch.Tensor):
-        self._h = C.c_void_p(handle)
+        self._h = handle if isinstance(handle, C.c_void_p) else C.c_void_p(handle)
         self.buf = buf
         self._mk = None
 
@@ -226,28 +226,32 @@ def gcoo_from_csr(m: int, k: int, row_ptr, col_idx, vals, p: int, device="cuda:0
     if on_dev:
         assert row_ptr.is_cuda and row_ptr.dtype == torch.int32 and row_ptr.is_contiguous()
         assert col_idx.dtype == torch.int32 and vals.dtype == torch.float32
-        nnz = int(col_idx.numel())
+        nnz = col_idx.numel()
         ptrs = (row_ptr.data_ptr(), col_idx.data_ptr(), vals.data_ptr())
-        device = row_ptr.device
+        device, index = row_ptr.device, row_ptr.get_device()
     else:
         row_ptr = np.ascontiguousarray(row_ptr, dtype=np.int32)
         col_idx = np.ascontiguousarray(col_idx, dtype=np.int32)
         vals = np.ascontiguousarray(vals, dtype=np.float32)
         nnz = int(col_idx.shape[0])
         ptrs = (row_ptr.ctypes.data, col_idx.ctypes.data, vals.ctypes.data)
-    need = gcoo_device_bytes(m, k, nnz, p)
+        device = torch.device(device)
+        index = torch.cuda.current_device() if device.index is None else device.index
+    L = lib()
+    need = L.gcoo_device_bytes(m, k, nnz, p)
     if need == 0:
         raise GcooError(GCOO_EINVAL, "gcoo_device_bytes")
-    with _on(row_ptr.get_device()) if on_dev else torch.cuda.device(device):
+    with _on(index):
         buf = _alloc(need, device)
         out = C.c_void_p()
+        sp = _raw_stream(index) if stream is None else stream.cuda_stream
         if on_dev and known_nnz:
-            _check(lib().gcoo_from_csr_device(m, k, nnz, ptrs[0], ptrs[1], ptrs[2], p, buf.data_ptr(), buf.numel(),
-                                              _stream_ptr(stream), C.byref(out)), "gcoo_from_csr_device")
+            status = L.gcoo_from_csr_device(m, k, nnz, *ptrs, p, buf.data_ptr(), need, sp, C.byref(out))
         else:
-            _check(lib().gcoo_from_csr(m, k, ptrs[0], ptrs[1], ptrs[2], 1 if on_dev else 0, p, buf.data_ptr(),
-                                       buf.numel(), _stream_ptr(stream), C.byref(out)), "gcoo_from_csr")
-    A = GcooMatrix(out.value, buf)
+            status = L.gcoo_from_csr(m, k, *ptrs, 1 if on_dev else 0, p, buf.data_ptr(), need, sp, C.byref(out))
+    if status:
+        raise GcooError(status, "gcoo_from_csr_device" if on_dev and known_nnz else "gcoo_from_csr")
+    A = GcooMatrix(out, buf)
     A._mk = (m, k)
     return A
 
