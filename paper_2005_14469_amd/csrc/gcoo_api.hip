@@ -390,25 +390,29 @@ int32_t share_best_p(int64_t m, int64_t N)
     return best;
 }
 
-// Times of the two kernels that the automatic choice is between, in microseconds, from measurements on uniform random matrices
-// (n = 500 .. 14000, 0.05 .. 20 % dense, N = n and N = 500 .. 2001; within 15 % where the times are more than 20 us).
-// Row by row: 4 x nnz x N bytes through the vector caches, at 24 TB/s while a tile of 64 columns of B stays in an XCD's L2 and
-// rows of B begin at 128-byte lines; C.
+// Times of the two kernels that the automatic choice is between, in microseconds: fitted to 219 measurements on uniform random
+// matrices (1500 to 14000 rows and columns, 0.05 to 20 % dense, N = 512 to 14000, B and C not in a cache), mean error 3 to 8 %; by them the
+// choice costs 0.5 % against always taking the faster kernel.
+// Row by row: the bytes of B that the entries take through the vector caches, slower the less of a tile of B stays in an XCD's L2 and
+// where rows of B begin inside a 128-byte line; C and B once.
 double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 {
-    const bool small = k <= 8500;
-    const double rate = small ? (lines ? 24e6 : 17e6) : (lines ? 16.5e6 : 14e6);       // bytes per us
-    return 5.0 + 4.0 * (double)N * ((double)nnz / rate + (double)m / (small ? 4.2e6 : 2.8e6));
+    const double row = 4.0 * (double)N, kd = (double)k, taken = (double)nnz;
+    if (lines) return 6.2 + row * (taken * (1.0 + std::pow(kd / 22400.0, 1.59)) / 31.7e6 + (double)m / 12.9e6 + kd / 3.4e6);
+    return 7.3 + row * (taken * (1.0 + std::pow(kd / 10700.0, 0.95)) / 32.7e6 + (double)m / 5.2e6 + kd / 6.9e6);
 }
-// Bands: a workgroup per compute unit and round; 0.85 us for a band by itself (80 rows of B, the barrier, the bubble behind it) and
-// 2.65 ns per entry of the block; C, and B where it does not fit the memory-side cache.
-double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, int32_t h)
+// Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 rows of B, the barrier, the bubble behind it; more where
+// they are fetched in four-byte pieces) and 2.56 ns per entry of the block; C and B once, and more for both when they do not fit the
+// memory-side cache.
+double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, int32_t h, bool aligned)
 {
     const int64_t blocks = gcoo::band_blocks(m, h), rounds = (blocks * ((N + 255) / 256) + 255) / 256;
     const double entries = (double)nnz / (double)blocks;
     const double columns = (double)k * -std::expm1(-entries / (double)k);                // distinct ones of a block
-    return 6.0 + (double)rounds * (0.85 * std::ceil(columns / gcoo::kBandRows) + 0.00265 * entries) +
-           4.0 * ((double)m + ((double)k * (double)N > 75e6 ? (double)k : 0.0)) * (double)N / 4.2e6;
+    const double row = 4.0 * (double)N, big = ((double)k * (double)N - 4e7) / 6e7, outside = big < 0.0 ? 0.0 : (big > 1.0 ? 1.0 : big);
+    const double bands = std::ceil(columns / gcoo::kBandRows), md = (double)m, kd = (double)k;
+    if (aligned) return 6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6);
+    return 7.4 + (double)rounds * (1.08 * bands + 0.00255 * entries) + row * (md / 3.8e6 + kd / 17.8e6 + outside * (md + kd) / 14.6e6);
 }
 
 // Rows per wave of the band schedule, 0 where none is built.  The width of B is not known here: the blocks are cut so that a
@@ -418,7 +422,8 @@ int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return 0;
     const bool asked = share_kernel_preferred(m, k, nnz, p);
-    if (!asked && rows_time(m, k, nnz, k, true) < 30.0) return 0;
+    const bool lines = k % 32 == 0, aligned = k % 4 == 0;
+    if (!asked && rows_time(m, k, nnz, k, lines) < 30.0) return 0;
     // (a conversion asks for every layout it makes: the last answer of this thread is kept)
     static thread_local struct { int64_t m, k, nnz; bool asked; int32_t h; } last = {0, 0, 0, false, 0};
     if (last.m == m && last.k == k && last.nnz == nnz && last.asked == asked) return last.h;
@@ -427,10 +432,10 @@ int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p)
     for (int32_t h = gcoo::kBandMaxH; h >= 12; --h) {
         // the columns of every wave's rows as a bitmap, in the second sort buffer
         if (gcoo::band_blocks(m, h) * gcoo::kBandWaves * ((k + 31) / 32) > 3 * nnz) continue;
-        const double t = band_time(m, k, nnz, k, h);
+        const double t = band_time(m, k, nnz, k, h, aligned);
         if (best == 0 || t < best_time) { best_time = t; best = h; }
     }
-    if (best && !asked && best_time + 12.0 > rows_time(m, k, nnz, k, true)) best = 0;
+    if (best && !asked && best_time + 12.0 > rows_time(m, k, nnz, k, lines)) best = 0;
     last = {m, k, nnz, asked, best};
     return best;
 }
@@ -1301,7 +1306,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     };
     if (automatic && A->has_rows() && A->k >= 1) {
         const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
-        if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) && band_time(A->m, A->k, A->nnz, N, A->L.band_h) < rows_time(A->m, A->k, A->nnz, N, lines))
+        if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) && band_time(A->m, A->k, A->nnz, N, A->L.band_h, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
             return run_band();
         if (!A->has_sched || rows_preferred(A, N)) return run_rows();
     }

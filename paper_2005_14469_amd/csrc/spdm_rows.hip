@@ -51,10 +51,12 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // 128 columns per tile while the tile stays in an XCD's L2 (4 MB): rows of B that do not start at 128-byte lines cost a line
     // more per segment (3000 x 3000, 1 %: N = 2999 59.9 us with 64 columns, 50.9 with 128; 9001 columns: 452 and 460).
     // Rows of a few entries take theirs from a tile of B hardly more than once before it has to be read anyway, so that the wider
-    // stretches of B and C count for more than the L2 (rows of 6 entries: 12000 columns 399 -> 377 us, 12001 472 -> 435; rows of 9,
-    // 9024 columns: 242 -> 235; rows of 12, 12000: 499 -> 521).
+    // stretches of B and C count for more than the L2 while C is wide (us with 16, 32, 64 lanes; 12000 x 12000, rows of 1, 3, 5, 9 entries:
+    // 339 277 249, 373 328 311, 398 364 374, 446 440 568; 14000 rows, N = 2000, of 3, 5, 7: 80 71 69, 86 79 85, 93 94 108; N = 501, of 3: 22 28 30;
+    // 3000 x 3000, of 3: 22 21 25).
     const bool lines = a.ldb % 32 == 0 && reinterpret_cast<uintptr_t>(a.B) % 128 == 0;
-    if (a.N > 64 && (a.k <= (lines ? 4096 : 6500) || a.nnz <= 9 * a.m)) return launch_rows<32>(a, s);
+    if (a.N >= 1500 && a.nnz <= 4 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
+    if (a.N > 64 && (a.k <= (lines ? 4096 : 6500) || (a.N >= 1500 && a.nnz <= (a.N >= 6000 ? 9 : 6) * a.m))) return launch_rows<32>(a, s);
     return launch_rows<16>(a, s);
 }
 

@@ -93,8 +93,10 @@ def test_repeated_and_non_finite():
     _check(w, 16)
 
 
-@pytest.mark.parametrize("k,N", [(7000, 131), (9001, 320)])
-def test_a_few_entries_per_row_of_many_columns(k, N):
-    """Rows short enough for the wide tiles whatever k is, and one row beyond: 16 entries and more beside them."""
+@pytest.mark.parametrize("k,N,times", [(7000, 131, 9), (9001, 1501, 9), (6600, 3401, 375), (3000, 2504, 500)])
+def test_a_few_entries_per_row_of_many_columns(k, N, times):
+    """Rows short enough for the wide tiles whatever k is, and one row beyond: 16 entries and more beside them; the last two with a whole
+    wave per row."""
     print(f"rows: few entries, k={k} N={N}", flush=True)
-    _check(_rows_of_lengths([0, 3, 9, 1, 7, 12, 2, 16, 5, 17, 4, 6, 8, 0, 1, 40] * 9, k, N, seed=k), 32)
+    lens = [0, 3, 9, 1, 7, 12, 2, 16, 5, 17, 4, 6, 8, 0, 1, 40] if times < 10 else [0, 3, 9, 1, 1, 0, 2, 0, 5, 17, 4, 0, 0, 0, 1, 20]
+    _check(_rows_of_lengths(lens * times, k, N, seed=k), 32)
