@@ -15,10 +15,19 @@
 // moves them.  A multiply-add with a scalar (or DPP) operand or in index mode takes 1.8 ns per SIMD, the other vector
 // instructions too: five of them per single entry, 9 ns, are what bounds dense bands; 10.1 measured in a loop of nothing else.
 //
-// B: three bands of 48 rows x 1 KB in LDS.  While band b is multiplied, band b + 1 is landing and the rows of band b + 2 are
-// requested, three per wave, straight to LDS (two at the band's start, one at its end); their columns come with the band's head,
-// and the address is formed by the scalar unit.  One barrier per band; the wait in front of it leaves the rows of band b + 2
-// in flight.  UNALIGNED: rows of B aligned to 4 bytes only are fetched with four 4-byte-per-lane loads instead of one of 16.
+// B: two bands of 80 rows x 1 KB in LDS.  While band b is multiplied, the rows of band b + 1 are requested, five per wave, straight
+// to LDS; their columns come with the band's head, and the address is formed by the scalar unit.  One barrier per band, nothing in
+// flight across it.  UNALIGNED: rows of B aligned to 4 bytes only are fetched with four 4-byte-per-lane loads instead of one of 16.
+//
+// When the rows are requested.  A request holds the one address path of the compute unit for 16 clocks, and a wave that finds it taken
+// stands still: with all five requests of all waves at the band's start nobody multiplied for the first 0.5 us.  Two ways:
+//   SPREAD false   waves 0 - 7 at the start, waves 8 - 15 behind their first unit (or at the end of a band that has only one): one half
+//                  multiplies while the other asks
+//   SPREAD true    every wave asks for two rows at the start and one behind each of its first three steps; a band of few entries per
+//                  wave would end before the late half's rows have landed
+// Product alone, all at the start -> now (us): 14000 x 14000, 2 % 3460 -> 3165; 8000 x 8000, 2 % 672 -> 633; 10 % 2323 -> 2284; 6001 x 6001,
+// 1 % 290 -> 254; SPREAD: 8000 x 8000, 0.5 % 366 -> 345; 10000 x 10000, 0.4 % 667 -> 590 (the other way 371 and 670).  A quarter of the
+// waves at a time, a unit apart, was slower (3517 for the first); so was asking a row at a time and step everywhere (3365).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -56,8 +65,9 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 //   v3        LDS address of the next read    v[4:27] six sets of B values
 //   s[36:67]  bank A: the unit that is multiplied, s[68:99]  bank B: the next one (or the other way round): value, place and row of record i
 //   s12 s13   byte offsets of the head after next and of the next unit    s14  where the wave's rows of the next band go in LDS
-//   s15 bands left   s[16:20]  head of this band: three columns, pair steps, single steps    s[24:28] of the next one    s23 scratch
+//   s15 bands left   s[16:22]  head of this band: five columns, pair steps, single steps    s[24:30] of the next one    s23 scratch
 //   s[32:35]  buffer descriptor of B, from the tile's first column on
+//   vcc       not 0: rows of the next band are still to be requested (SPREAD: 1 + how often it was done behind a step)
 #define BD_FMAC(val, b0, b1, b2, b3)                   \
     "v_fmac_f32 v28, " #val ", " #b0 "\n\t"             \
     "v_fmac_f32 v53, " #val ", " #b1 "\n\t"             \
@@ -85,12 +95,34 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     "s_set_gpr_idx_off\n\t"
 #define BD_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
 
-// Row t of the three that the wave fetches for the band after next: column in s<16 + t>.
+// Row t of the five that the wave fetches for the next band: column in s<16 + t>.
 #define BD_FILL(col, at)                        \
     "s_add_u32 m0, s14, " #at "\n\t"             \
     "s_mul_i32 s23, " #col ", %[ldb4]\n\t"       \
     BD_LOAD_ROW
 #define BD_FILL_BAND BD_FILL(s16, 0) BD_FILL(s17, 0x400) BD_FILL(s18, 0x800) BD_FILL(s19, 0xc00) BD_FILL(s20, 0x1000)
+// The places where rows are requested; T = p (pair steps) or s (single steps).  BD_ASK_START behind the first reads of a band, BD_ASK_STEP behind
+// step I of its first unit, BD_ASK_UNIT in front of a further unit, BD_ASK_END at its end; what is done there stands out of line (BD_ASK_REST).
+#define BD_ASK_HERE(L, X) "s_cbranch_vccnz .Lbd_" #L "_" #X "_%=\n.Lbd_" #L "back_" #X "_%=:\n\t"
+#define BD_ASK_THERE(L, X, STATE, FILLS) ".Lbd_" #L "_" #X "_%=:\n\ts_mov_b32 vcc_lo, " #STATE "\n\t" FILLS "s_branch .Lbd_" #L "back_" #X "_%=\n"
+#define BD_ASK_END(X) BD_ASK_HERE(fe, X)
+// SPREAD false
+#define BD_HALVES_START(T, X) "s_cmp_ge_u32 %[fillw], 0xa000\n\ts_cselect_b32 vcc_lo, 1, 0\n\ts_cbranch_scc1 .Lbd_late" #T "_" #X "_%=\n\t" BD_FILL_BAND ".Lbd_late" #T "_" #X "_%=:\n\t"
+#define BD_HALVES_STEP(T, I, X)
+#define BD_HALVES_UNIT(T, X) BD_ASK_HERE(f##T, X)
+#define BD_HALVES_REST(X) BD_ASK_THERE(fp, X, 0, BD_FILL_BAND) BD_ASK_THERE(fs, X, 0, BD_FILL_BAND) BD_ASK_THERE(fe, X, 0, BD_FILL_BAND)
+// SPREAD true
+#define BD_SPREAD_START(T, X) "s_mov_b32 vcc_lo, 1\n\t" BD_FILL(s16, 0) BD_FILL(s17, 0x400)
+#define BD_SPREAD_STEP(T, I, X) BD_ASK_HERE(f##T##I, X)
+#define BD_SPREAD_UNIT(T, X)
+#define BD_SPREAD_REST(X)                                                                              \
+    BD_ASK_THERE(fp0, X, 2, BD_FILL(s18, 0x800)) BD_ASK_THERE(fp1, X, 3, BD_FILL(s19, 0xc00)) BD_ASK_THERE(fp2, X, 0, BD_FILL(s20, 0x1000))    \
+    BD_ASK_THERE(fs0, X, 2, BD_FILL(s18, 0x800)) BD_ASK_THERE(fs1, X, 3, BD_FILL(s19, 0xc00)) BD_ASK_THERE(fs2, X, 0, BD_FILL(s20, 0x1000))    \
+    ".Lbd_fe_" #X "_%=:\n\t"                                                                           \
+    "s_cmp_gt_u32 vcc_lo, 1\n\ts_cbranch_scc1 .Lbd_fe1_" #X "_%=\n\t" BD_FILL(s18, 0x800) ".Lbd_fe1_" #X "_%=:\n\t"     \
+    "s_cmp_gt_u32 vcc_lo, 2\n\ts_cbranch_scc1 .Lbd_fe2_" #X "_%=\n\t" BD_FILL(s19, 0xc00) ".Lbd_fe2_" #X "_%=:\n\t"     \
+    BD_FILL(s20, 0x1000) "s_mov_b32 vcc_lo, 0\n\ts_branch .Lbd_feback_" #X "_%=\n"
+
 #define BD_LOAD_UNIT(lo, hi)                                      \
     "s_load_dwordx16 s[" lo "], %[units], s13\n\t"                 \
     "s_load_dwordx16 s[" hi "], %[units], s13 offset:0x40\n\t"     \
@@ -103,10 +135,12 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 // band begins), unitp_X / units_X (a band goes on in X, with pairs / with singles), p<i>_X, s<i>_X (step i of the unit).
 #define BD_HALF(X, Y, a0, m0, a1, m1, a2, m2, a3, m3, a4, m4, a5, m5, a6, m6, a7, m7, a8, m8, a9, m9, a10, m10, a11, m11, a12, m12, a13, m13, a14, m14, a15, m15) \
     ".Lbd_unitp_" #X "_%=:\n\t"                                                                 \
+    BD_ASK_UNIT(p, X)                                                                           \
     BD_WAIT(0) BD_LOAD_##Y                                                                      \
     BD_READ_T0(m0) BD_READ_T1(m2) BD_READ_T2(m4) BD_READ_T3(m6)                                 \
     "s_branch .Lbd_p0_" #X "_%=\n"                                                              \
     ".Lbd_units_" #X "_%=:\n\t"                                                                 \
+    BD_ASK_UNIT(s, X)                                                                           \
     BD_WAIT(0) BD_LOAD_##Y                                                                      \
     BD_READ_T0(m0) BD_READ_T1(m1) BD_READ_T2(m2) BD_READ_T3(m3)                                 \
     "s_branch .Lbd_s0_" #X "_%=\n"                                                              \
@@ -122,8 +156,9 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     "s_cmp_eq_u32 s22, 0\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                              \
     BD_READ_T0(m12) BD_READ_T1(m13) BD_READ_T2(m14) BD_READ_T3(m15)                             \
     "s_branch .Lbd_s3_" #X "_%=\n"                                                              \
-    /* the end of a band: its last row request, then the rows of the next band have landed and all waves are done with this one */ \
+    /* the end of a band: its last row requests, then the rows of the next band have landed and all waves are done with this one */ \
     ".Lbd_end_" #X "_%=:\n\t"                                                                   \
+    BD_ASK_END(X)                                                                               \
     "s_sub_u32 s14, %[flip], s14\n\t"                                                           \
     BD_WAIT_BAND                                                                                \
     "s_mov_b64 s[16:17], s[24:25]\n\t"                                                          \
@@ -139,17 +174,20 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     BD_LOAD_##Y                                                                                 \
     "s_cmp_eq_u32 s21, 0\n\ts_cbranch_scc1 .Lbd_bs_" #X "_%=\n\t"                               \
     BD_READ_T0(m0) BD_READ_T1(m2) BD_READ_T2(m4) BD_READ_T3(m6)                                 \
-    BD_FILL_BAND                                                                                \
+    BD_ASK_START(p, X)                                                                          \
     ".Lbd_p0_" #X "_%=:\n\t"                                                                    \
     "s_sub_u32 s21, s21, 1\n\t"                                                                 \
     BD_READ_T4(m8) BD_WAIT(4) BD_TWO(a0, m0, T0, a1, m1, T0)                                    \
     BD_READ_T5(m10) BD_WAIT(4) BD_TWO(a2, m2, T1, a3, m3, T1)                                   \
+    BD_ASK_STEP(p, 0, X)                                                                        \
     "s_sub_u32 s21, s21, 1\n\ts_cbranch_scc1 .Lbd_ps1_" #X "_%=\n\t"                            \
     BD_READ_T0(m12) BD_WAIT(4) BD_TWO(a4, m4, T2, a5, m5, T2)                                   \
     BD_READ_T1(m14) BD_WAIT(4) BD_TWO(a6, m6, T3, a7, m7, T3)                                   \
+    BD_ASK_STEP(p, 1, X)                                                                        \
     "s_sub_u32 s21, s21, 1\n\ts_cbranch_scc1 .Lbd_ps2_" #X "_%=\n\t"                            \
     BD_WAIT(3) BD_TWO(a8, m8, T4, a9, m9, T4)                                                   \
     BD_WAIT(2) BD_TWO(a10, m10, T5, a11, m11, T5)                                               \
+    BD_ASK_STEP(p, 2, X)                                                                        \
     "s_sub_u32 s21, s21, 1\n\ts_cbranch_scc1 .Lbd_ps3_" #X "_%=\n\t"                            \
     BD_WAIT(1) BD_TWO(a12, m12, T0, a13, m13, T0)                                               \
     BD_WAIT(0) BD_TWO(a14, m14, T1, a15, m15, T1)                                               \
@@ -159,22 +197,26 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     ".Lbd_empty_" #X "_%=:\n\t"                                                                 \
     BD_FILL_BAND                                                                                \
     "s_branch .Lbd_end_" #Y "_%=\n"                                                             \
+    BD_ASK_REST(X)                                                                              \
     ".Lbd_bs_" #X "_%=:\n\t"                                                                    \
     "s_cmp_eq_u32 s22, 0\n\ts_cbranch_scc1 .Lbd_empty_" #X "_%=\n\t"                            \
     BD_READ_T0(m0) BD_READ_T1(m1) BD_READ_T2(m2) BD_READ_T3(m3)                                 \
-    BD_FILL_BAND                                                                                \
+    BD_ASK_START(s, X)                                                                          \
     ".Lbd_s0_" #X "_%=:\n\t"                                                                    \
     "s_sub_u32 s22, s22, 1\n\t"                                                                 \
     BD_READ_T4(m4) BD_READ_T5(m5) BD_WAIT(4) BD_TWO(a0, m0, T0, a1, m1, T1)                     \
     BD_READ_T0(m6) BD_READ_T1(m7) BD_WAIT(4) BD_TWO(a2, m2, T2, a3, m3, T3)                     \
+    BD_ASK_STEP(s, 0, X)                                                                        \
     ".Lbd_s1_" #X "_%=:\n\t"                                                                    \
     "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
     BD_READ_T2(m8) BD_READ_T3(m9) BD_WAIT(4) BD_TWO(a4, m4, T4, a5, m5, T5)                     \
     BD_READ_T4(m10) BD_READ_T5(m11) BD_WAIT(4) BD_TWO(a6, m6, T0, a7, m7, T1)                   \
+    BD_ASK_STEP(s, 1, X)                                                                        \
     ".Lbd_s2_" #X "_%=:\n\t"                                                                    \
     "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
     BD_READ_T0(m12) BD_READ_T1(m13) BD_WAIT(4) BD_TWO(a8, m8, T2, a9, m9, T3)                   \
     BD_READ_T2(m14) BD_READ_T3(m15) BD_WAIT(4) BD_TWO(a10, m10, T4, a11, m11, T5)               \
+    BD_ASK_STEP(s, 2, X)                                                                        \
     ".Lbd_s3_" #X "_%=:\n\t"                                                                    \
     "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
     BD_WAIT(2) BD_TWO(a12, m12, T0, a13, m13, T1)                                               \
@@ -203,6 +245,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
         "v_mov_b32 v1, 0x3fc00\n\t"                                                                    \
         "s_mov_b32 s12, 0x60\n\t"                                                                       \
         "s_mov_b32 s13, 0\n\t"                                                                          \
+        "s_mov_b64 vcc, 0\n\t"                                                                          \
         "s_sub_u32 s15, %[nb], 1\n\t"                                                                   \
         "s_load_dwordx8 s[16:23], %[head], 0x0\n\t"                                                     \
         "s_load_dwordx8 s[24:31], %[head], 0x40\n\t"                                                    \
@@ -222,7 +265,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
         "s_waitcnt vmcnt(0) lgkmcnt(0)\n\t" \
         : "={v[28:31]}"(acc.t0), "={v[32:63]}"(acc.t1), "={v[64:95]}"(acc.t2), "={v[96:127]}"(acc.t3), "+{v0}"(l16), [fillw] "+s"(fillw) \
         : [head] "s"(head), [units] "s"(units), [nb] "s"(nb), [ldb4] "s"(ldb4), [flip] "s"(flip), "{s[32:35]}"(rsrc), "{v2}"(lane_b) \
-        : "m0", "scc", "memory",  \
+        : "m0", "scc", "vcc", "memory",  \
           "v1", "v3", "v4", "v5", "v6", "v7", "v8", "v9", "v10", "v11", "v12", "v13", "v14", "v15", "v16", "v17", "v18", "v19",  \
           "v20", "v21", "v22", "v23", "v24", "v25", "v26", "v27", "s12", "s13", "s14", "s15", "s16", "s17", "s18", "s19", "s20",  \
           "s21", "s22", "s23", "s24", "s25", "s26", "s27", "s28", "s29", "s30", "s31", "s36", "s37", "s38", "s39", "s40", "s41",  \
@@ -237,7 +280,7 @@ struct BandRowsGrid { int32_t tiles, row_wgs, rpw, wave_row, items; };
 // A matrix with a list of far more entries than the others (take_rows and band_mark say so on the device, where the
 // row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, as the row-by-row
 // kernel does, by the workgroups of this launch.
-template <bool UNALIGNED>
+template <bool UNALIGNED, bool SPREAD>            // (SPREAD without UNALIGNED only)
 __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
@@ -270,23 +313,49 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
         const band_u32x4 rsrc = {(uint32_t)bt, (uint32_t)(bt >> 32) & 0xffffu, (uint32_t)bytes, 0x00027000u};
         const uint32_t flip = 2u * fillw + kBandBufferBytes;
         const uint32_t ldb4 = (uint32_t)a.ldb * 4u;                // the launcher checks that every row offset fits 32 bits
+#define BD_WAIT_BAND "s_waitcnt vmcnt(0) lgkmcnt(0)\n\t"
         if constexpr (UNALIGNED) {
             const uint32_t lane_b = l16 >> 2;
 #define BD_LOAD_ROW                                                                                          \
     "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"               \
     "buffer_load_dword v2, s[32:35], s23 offen offset:512 lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:768 lds\n\t"
-#define BD_WAIT_BAND "s_waitcnt vmcnt(0) lgkmcnt(0)\n\t"
+#define BD_ASK_START BD_HALVES_START
+#define BD_ASK_STEP BD_HALVES_STEP
+#define BD_ASK_UNIT BD_HALVES_UNIT
+#define BD_ASK_REST BD_HALVES_REST
             BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
 #undef BD_LOAD_ROW
-#undef BD_WAIT_BAND
         } else {
             const uint32_t lane_b = jb + (int32_t)(l16 >> 2) < n ? l16 : 0u;     // lanes beyond N fetch the first columns of the tile
 #define BD_LOAD_ROW "buffer_load_dwordx4 v2, s[32:35], s23 offen lds\n\t"
-#define BD_WAIT_BAND "s_waitcnt vmcnt(0) lgkmcnt(0)\n\t"
-            BD_MAIN;
+            if constexpr (SPREAD) {
+#define BD_ASK_START BD_SPREAD_START
+#define BD_ASK_STEP BD_SPREAD_STEP
+#define BD_ASK_UNIT BD_SPREAD_UNIT
+#define BD_ASK_REST BD_SPREAD_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else {
+#define BD_ASK_START BD_HALVES_START
+#define BD_ASK_STEP BD_HALVES_STEP
+#define BD_ASK_UNIT BD_HALVES_UNIT
+#define BD_ASK_REST BD_HALVES_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            }
 #undef BD_LOAD_ROW
-#undef BD_WAIT_BAND
         }
+#undef BD_WAIT_BAND
     }
 
     // What the stores need is made again from the kernel's arguments: the loop leaves the compiler no vector register and eighteen

@@ -2,10 +2,11 @@
 #include "gcoo_spdm_band_kernel.hpp"
 
 #include <atomic>
+#include <cmath>
 
 namespace gcoo {
 
-template <bool UNALIGNED>
+template <bool UNALIGNED, bool SPREAD>
 static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const BandRowsGrid& rg, hipStream_t s)
 {
     // more LDS than the default limit of a workgroup: asked for once per device
@@ -15,11 +16,11 @@ static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const Ban
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!done[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<UNALIGNED>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<UNALIGNED, SPREAD>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
         if (e != hipSuccess) return e;
         done[dev].store(1u, std::memory_order_release);
     }
-    spdm_band<UNALIGNED><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
+    spdm_band<UNALIGNED, SPREAD><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
     return hipGetLastError();
 }
 
@@ -44,7 +45,12 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     const int64_t rest = (int64_t)(rg.tiles % 8) * rg.row_wgs, items = (int64_t)(rg.tiles / 8 * 8) * rg.row_wgs + (rest + 7) / 8 * 8;
     if (items > 0x7fffffffLL || rows.N < 4) return hipErrorInvalidConfiguration;
     rg.items = (int32_t)items;
-    return aligned ? launch_band<false>(b, rows, rg, s) : launch_band<true>(b, rows, rg, s);
+    if (!aligned) return launch_band<true, false>(b, rows, rg, s);
+    // How the rows of B are requested goes by the entries of a (wave, band), of which SPREAD serves the few (us, halves and SPREAD:
+    // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; with four loads per row 10: 697 698, 19: 254 279, so never there).
+    const double touched = (double)a.k * -std::expm1(-(double)rows.nnz / (double)a.blocks / (double)a.k);
+    const double entries = (double)rows.nnz / (double)(a.blocks * kBandWaves) * kBandRows / (touched > 1.0 ? touched : 1.0);
+    return entries < 28.0 ? launch_band<false, true>(b, rows, rg, s) : launch_band<false, false>(b, rows, rg, s);
 }
 
 }  // namespace gcoo

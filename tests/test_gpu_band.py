@@ -116,3 +116,10 @@ def test_uneven_rows_are_multiplied_one_by_one(dense, p, N, shift):
         err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
         assert bad == 0 and err < 2e-6, (variant, err, bad)
         assert torch.equal(C, binding.gcoo_spdm(A, Bbig[:, shift:], variant=variant))
+
+
+@pytest.mark.parametrize("m,k,N,s,pad", [(300, 7000, 1000, 0.9955, 0), (700, 7003, 516, 0.995, 4), (385, 7000, 260, 0.9955, 0), (2000, 7000, 300, 0.988, 0)])
+def test_few_entries_per_band(m, k, N, s, pad):
+    """Waves with no entry in a band, with one step, and with more than the three behind which rows of the next band are requested."""
+    print(f"band, few entries: m={m} k={k} N={N} s={s} pad={pad}", flush=True)
+    _run(workloads.uniform_random(m, k, N, s, seed=m + k), 32, binding.VARIANT_SHARE, 0, pad)
