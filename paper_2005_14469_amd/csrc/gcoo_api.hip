@@ -1276,7 +1276,9 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     if (A->m == 0 || N == 0) return GCOO_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    if (variant == GCOO_VARIANT_LDS && !(automatic && A->k >= 1)) {
+    const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
+    // The automatic choice leaves the LDS kernel a matrix without columns, and a row pitch of B that the others do not hold in 32 bits.
+    if (variant == GCOO_VARIANT_LDS && (!automatic || A->k < 1 || sh.wide_pitch)) {
         const int64_t tiles = (N + 63) / 64;
         const int64_t total = A->g * tiles;
         if (total > 0x7fffffffLL) return GCOO_EINVAL;
@@ -1287,7 +1289,6 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         return GCOO_OK;
     }
     if (A->inner) A = A->inner;        // the schedules of the kernels below belong to the regrouped copy
-    const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
     auto rows_args = [&]() {
         gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
                          A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};

@@ -1,0 +1,98 @@
+"""The host code of libgcoo.so run without a GPU, on the HIP calls of tests/host/hip_on_host.cpp: which kernels a call launches, where it
+waits, what it does when a HIP call fails.  Every case runs in a process of its own (`python -m tests.host_calls NAME`), which
+loads no torch: its HIP runtime would be found before the one of the test."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import numpy as np
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = os.path.join(ROOT, "tests", "host", "hip_on_host.cpp")
+STUB = os.path.join(ROOT, "paper_2005_14469_amd", "_build", "libhip_on_host.so")
+LIB = os.environ.get("GCOO_LIBRARY") or os.path.join(ROOT, "paper_2005_14469_amd", "libgcoo.so")
+OK, EINVAL, ENOMEM, EHIP = 0, -1, -3, -4
+AUTO, LDS, REG, SHARE = 0, 1, 2, 3
+
+
+def build():
+    os.makedirs(os.path.dirname(STUB), exist_ok=True)
+    tmp = f"{STUB}.{os.getpid()}"
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", SOURCE, "-o", tmp])
+    os.replace(tmp, STUB)
+
+
+class Host:
+    """The library on the host's HIP calls, and addresses for what it only passes on."""
+
+    def __init__(self):
+        self.hip = C.CDLL(STUB, mode=C.RTLD_GLOBAL)
+        self.hip.host_set.argtypes = [C.c_char_p, C.c_longlong]
+        self.hip.host_log.restype = C.c_char_p
+        self.L = C.CDLL(LIB)
+        i64, i32, vp, sz = C.c_int64, C.c_int32, C.c_void_p, C.c_size_t
+        for name, res, args in [
+                ("gcoo_device_bytes", sz, [i64, i64, i64, i32]), ("gcoo_default_p", i32, [i64] * 4),
+                ("gcoo_from_csr", C.c_int, [i64, i64, vp, vp, vp, C.c_int, i32, vp, sz, vp, C.POINTER(vp)]),
+                ("gcoo_from_csr_device", C.c_int, [i64, i64, i64, vp, vp, vp, i32, vp, sz, vp, C.POINTER(vp)]),
+                ("gcoo_dense_nnz", C.c_int, [i64, i64, vp, i64, vp, C.POINTER(i64)]),
+                ("gcoo_dense_count_bytes", sz, [i64, i64, i32]),
+                ("gcoo_dense_count", C.c_int, [i64, i64, vp, i64, i32, vp, sz, vp, C.POINTER(i64)]),
+                ("gcoo_from_dense", C.c_int, [i64, i64, vp, i64, i32, vp, sz, vp, C.POINTER(vp)]),
+                ("gcoo_from_dense_counted", C.c_int, [i64, i64, i64, vp, i64, i32, vp, vp, sz, vp, C.POINTER(vp)]),
+                ("gcoo_spdm_variant", C.c_int, [vp, vp, i64, i64, vp, i64, vp, C.c_int]),
+                ("gcoo_spdm_pick", C.c_int, [vp, vp, i64, i64, vp, i64]),
+                ("gcoo_free", C.c_int, [vp]), ("gcoo_set_share_policy", C.c_int, [C.c_int])]:
+            f = getattr(self.L, name)
+            f.restype, f.argtypes = res, args
+        self.log()
+
+    def set(self, key, value):
+        self.hip.host_set(key.encode(), value)
+
+    def log(self):
+        return self.hip.host_log().decode().split("\n")[:-1]
+
+    def launches(self):
+        return [line.split()[1] for line in self.log() if line.startswith("launch")]
+
+    def buffer(self, nbytes):
+        """`nbytes` of memory at a multiple of 4096; kept."""
+        raw = np.zeros(nbytes + 4096, np.uint8)
+        self.keep = getattr(self, "keep", []) + [raw]
+        return raw.ctypes.data + (-raw.ctypes.data) % 4096
+
+    def matrix(self, m, k, nnz, p):
+        """A handle of a CSR matrix on the device; no kernel looks at the arrays."""
+        h = C.c_void_p()
+        # (the conversion only launches: a place that nothing reads serves as the buffer, however large)
+        rc = self.L.gcoo_from_csr_device(m, k, nnz, 1 << 20, 1 << 20, 1 << 20, p, 1 << 20, 1 << 50, None, C.byref(h))
+        assert rc == OK, rc
+        return h
+
+    def spdm(self, h, N, ldb, variant=AUTO, ldc=None, B=1 << 30, Cp=1 << 40):
+        return self.L.gcoo_spdm_variant(h, B, ldb, N, Cp, N if ldc is None else ldc, None, variant)
+
+
+# ---- a row pitch of B of 2^30 elements or more ---------------------------------------------------
+
+def wide_pitch(host):
+    """The automatic choice serves any row pitch of B; the kernels that hold it in 32 bits refuse it when asked for."""
+    for m, k, nnz, p in [(100, 2, 150, 32), (100, 2, 150, 128), (4000, 4000, 800000, 32), (8000, 8000, 320000, 42)]:
+        h = host.matrix(m, k, nnz, p)
+        for N in (1, 3, 4, 64, 513):
+            for ldb in (1 << 30, (1 << 30) + 1, 1 << 33):
+                host.log()
+                assert host.spdm(h, N, ldb) == OK, (m, p, N, ldb)
+                names = host.launches()
+                assert len(names) == 1 and "spdm_lds" in names[0], (m, p, N, ldb, names)
+                assert host.spdm(h, N, ldb, REG) == EINVAL and host.spdm(h, N, ldb, SHARE) == EINVAL
+            host.log()
+            assert host.spdm(h, N, (1 << 30) - 1) == OK
+            assert "spdm_lds" not in host.launches()[0]
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]](Host())
+    print("ok")

@@ -100,3 +100,20 @@ def test_a_few_entries_per_row_of_many_columns(k, N, times):
     print(f"rows: few entries, k={k} N={N}", flush=True)
     lens = [0, 3, 9, 1, 7, 12, 2, 16, 5, 17, 4, 6, 8, 0, 1, 40] if times < 10 else [0, 3, 9, 1, 1, 0, 2, 0, 5, 17, 4, 0, 0, 0, 1, 20]
     _check(_rows_of_lengths(lens * times, k, N, seed=k), 32)
+
+
+@pytest.mark.parametrize("p", [32, 100])
+def test_row_pitch_of_b_beyond_32_bits(p):
+    """Rows of B 2^30 elements apart and one element more, which the automatic choice leaves to the LDS kernel, and one element less."""
+    w = _rows_of_lengths([0, 2, 1, 3] * 9, 3, 68, seed=8)
+    dev = [torch.from_numpy(x).to(DEV) for x in (w.row_ptr, w.col_idx, w.vals)]
+    A = binding.gcoo_from_csr(w.m, w.k, *dev, p, known_nnz=True)
+    C64, D64 = orc.spdm_csr(w.k, w.N, w.row_ptr, w.col_idx, w.vals, w.B)
+    room = torch.empty(2 * ((1 << 30) + 1) + w.N, device=DEV)
+    for ldb in ((1 << 30) - 1, 1 << 30, (1 << 30) + 1):
+        print(f"rows: ldb={ldb} p={p}", flush=True)
+        B = room.as_strided((w.k, w.N), (ldb, 1))
+        B.copy_(torch.from_numpy(w.B))
+        C = binding.gcoo_spdm(A, B)
+        err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
+        assert bad == 0 and err < 2e-6, (ldb, err, bad)

@@ -1,0 +1,18 @@
+"""The host code of the library without a GPU (see host_calls.py): one process per case."""
+import subprocess
+import sys
+
+import pytest
+
+from tests import host_calls
+
+
+@pytest.fixture(scope="module", autouse=True)
+def stub():
+    host_calls.build()
+
+
+@pytest.mark.parametrize("case", ["wide_pitch"])
+def test_host_code(case):
+    r = subprocess.run([sys.executable, "-m", "tests.host_calls", case], cwd=host_calls.ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
