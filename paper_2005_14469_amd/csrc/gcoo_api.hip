@@ -1309,7 +1309,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
         if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) && band_time(A->m, A->k, A->nnz, N, A->L.band_h, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
             return run_band();
-        if (!A->has_sched || rows_preferred(A, N)) return run_rows();
+        if (!A->has_sched || rows_preferred(A, N) || sched_width(A->p, sh) == 0) return run_rows();     // (0: fewer columns than the register kernel serves)
     }
     if (variant == GCOO_VARIANT_SHARE) {
         if (!share_operands_ok(A, sh, ldb)) return GCOO_EINVAL;

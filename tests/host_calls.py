@@ -93,6 +93,18 @@ def wide_pitch(host):
             assert "spdm_lds" not in host.launches()[0]
 
 
+# ---- one to three columns, with a run schedule ----------------------------------------------------
+
+def few_columns(host):
+    """The automatic choice serves one to three columns whatever schedules the matrix carries."""
+    for policy in (0, 1, 2):
+        assert host.L.gcoo_set_share_policy(policy) == OK
+        for m, k, nnz, p in [(40000, 5000, 3000000, 32), (70000, 5000, 9000000, 64), (70000, 300, 9000000, 100), (100, 200, 9000, 32)]:
+            h = host.matrix(m, k, nnz, p)
+            for N in (1, 2, 3, 4, 5):
+                assert host.spdm(h, N, N) == OK, (policy, m, p, N)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Host())
     print("ok")

@@ -117,3 +117,26 @@ def test_row_pitch_of_b_beyond_32_bits(p):
         C = binding.gcoo_spdm(A, B)
         err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
         assert bad == 0 and err < 2e-6, (ldb, err, bad)
+
+
+@pytest.mark.parametrize("policy", [binding.SHARE_ALWAYS, binding.SHARE_NEVER])
+def test_few_columns_of_a_matrix_with_a_run_schedule(policy):
+    """More rows and entries than the automatic choice takes row by row where the matrix has a run schedule, whose kernel has no
+    instance for so few columns."""
+    rng = np.random.default_rng(policy)
+    m, k, n = 33000, 900, 30
+    rp = (np.arange(m + 1) * n).astype(np.int32)
+    ci = np.sort(rng.integers(0, k, (m, n)), axis=1).astype(np.int32).reshape(-1)
+    va = rng.standard_normal(m * n).astype(np.float32)
+    binding.gcoo_set_share_policy(policy)
+    try:
+        A = binding.gcoo_from_csr(m, k, *[torch.from_numpy(x).to(DEV) for x in (rp, ci, va)], 32, known_nnz=True)
+    finally:
+        binding.gcoo_set_share_policy(binding.SHARE_AUTO)
+    for N in (1, 2, 3, 4):
+        print(f"rows: run schedule, policy={policy} N={N}", flush=True)
+        B = rng.standard_normal((k, N)).astype(np.float32)
+        C = binding.gcoo_spdm(A, torch.from_numpy(B).to(DEV))
+        C64, D64 = orc.spdm_csr(k, N, rp, ci, va, B)
+        err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
+        assert bad == 0 and err < 2e-6, (N, err, bad)
