@@ -209,7 +209,7 @@ int gcoo_spdm(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
 /* the waves of a workgroup share the rows of B: each row of B that any of them needs is fetched once into LDS, and every
  * multiply-add takes its B values from there.  Reads the share schedule where the conversion built one (GCOO_SHARE_ALWAYS), else the
  * band schedule; needs p <= 48, B, C, ldb, ldc, N
- * multiples of 4 elements (16-byte aligned rows) and k * ldb * 4 < 2^32, else GCOO_EINVAL */
+ * multiples of 4 elements (16-byte aligned rows) and k * ldb * 4 < 2^32 - 4096, else GCOO_EINVAL */
 #define GCOO_VARIANT_SHARE 3
 int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                       float* C_dev, int64_t ldc, void* stream, int variant);

@@ -1221,14 +1221,15 @@ namespace {
 
 bool share_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
 {
-    // (the kernel keeps byte offsets into B in 32 bits, each up to 3072 above the place it stands for)
-    return sh.al4 && (uint64_t)A->k * (uint64_t)ldb * 4u <= 0xffffffffull - 4096u;
+    // (the workgroup-shared kernel keeps byte offsets into B in 32 bits, each up to 3072 above the place it stands for; the limit of the
+    // sixteen-wave kernel is the same)
+    return sh.al4 && (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
 }
 
 bool band_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
 {
     const bool aligned = sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16;
-    return (aligned || sh.N >= 256) && (uint64_t)A->k * (uint64_t)ldb * 4u <= 0xffffffffull;
+    return (aligned || sh.N >= 256) && (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
 }
 
 // Row by row before the register kernel, for a handle that carries the run schedule: up to about 30 entries per row (n = 4000: level at

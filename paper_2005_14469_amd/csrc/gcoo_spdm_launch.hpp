@@ -85,12 +85,13 @@ inline int32_t rows_long(int64_t m, int64_t nnz)
     const int64_t n = m > 0 ? 8 * (nnz / m) : 0;
     return (int32_t)(n < 512 ? 512 : (n > INT32_MAX ? INT32_MAX : n));
 }
-constexpr uint64_t kRowsMaxBytes = 0xfffe0000ull;
+// Largest B (k x ldb) whose rows a buffer descriptor reaches with something left above for the entries past the end of a row.
+constexpr uint64_t kRowsMaxBytes = 0xffffefffull;
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s);
 
 
-// The sixteen-wave kernel that reads the band schedule (gcoo_band.hpp): N >= 256, or N, ldb a multiple of 4 and B 16-byte aligned; every row offset
-// of B in bytes below 2^32.
+// The sixteen-wave kernel that reads the band schedule (gcoo_band.hpp): N >= 256, or N, ldb a multiple of 4 and B 16-byte aligned; a B of at
+// most kRowsMaxBytes (the launch may work row by row).
 struct BandArgs {
     const uint32_t* head;
     const uint32_t* units;

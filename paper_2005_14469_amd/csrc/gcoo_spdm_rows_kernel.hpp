@@ -48,6 +48,11 @@ __device__ __forceinline__ uint32_t rows_bcast(const uint32_t (&x)[LPR >= 16 ? 1
 
 struct RowsAcc { float x[4]; };
 
+// The offset of an entry past the end of its row: no descriptor reaches that far, and a lane's place in the tile (below 2 KB) added to it
+// stays below 2^32.  Whoever launches rows_item without WIDE keeps B below kRowsMaxBytes.
+constexpr uint32_t kRowsNowhere = 0xfffff000u;
+static_assert(kRowsMaxBytes <= kRowsNowhere, "an entry past the end of a row would load an element of B");
+
 // WIDE (a B of more than 4 GB): `off` holds columns, 0xffffffff past the end, and the address is formed in 64 bits.
 struct RowsB {
     __amdgpu_buffer_rsrc_t rsrc;
@@ -108,13 +113,12 @@ struct RowsBatch {
     template <bool WIDE>
     __device__ __forceinline__ void offsets(uint32_t kmax, uint32_t ldb4)
     {
-        constexpr uint32_t kNowhere = 0xffff0000u;         // beyond the range of every descriptor (the launcher checks it)
 #pragma unroll
         for (int j = 0; j < REGS; ++j) {
             const bool none = c[j] == 0xffffffffu;
             c[j] = c[j] < kmax ? c[j] : kmax;
             if constexpr (WIDE) c[j] = none ? 0xffffffffu : c[j];
-            else c[j] = none ? kNowhere : c[j] * ldb4;
+            else c[j] = none ? kRowsNowhere : c[j] * ldb4;
         }
     }
 };

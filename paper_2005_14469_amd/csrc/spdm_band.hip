@@ -29,7 +29,7 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     const int64_t tiles = (a.N + 255) / 256, total = a.blocks * tiles;
     if (total <= 0 || total > 0x7ffffff0LL) return hipErrorInvalidConfiguration;
     if (a.h < 1 || a.h > kBandMaxH || a.blocks != band_blocks(a.m, a.h) || a.head_stride != band_head_stride(a.k)) return hipErrorInvalidValue;
-    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > 0xffffffffull) return hipErrorInvalidValue;
+    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return hipErrorInvalidValue;
     const bool aligned = a.N % 4 == 0 && a.ldb % 4 == 0 && reinterpret_cast<uintptr_t>(a.B) % 16 == 0;
     if (!aligned && a.N < 256) return hipErrorInvalidValue;
     BandArgs b = a;

@@ -123,3 +123,25 @@ def test_few_entries_per_band(m, k, N, s, pad):
     """Waves with no entry in a band, with one step, and with more than the three behind which rows of the next band are requested."""
     print(f"band, few entries: m={m} k={k} N={N} s={s} pad={pad}", flush=True)
     _run(workloads.uniform_random(m, k, N, s, seed=m + k), 32, binding.VARIANT_SHARE, 0, pad)
+
+
+def test_non_finite_values_beside_uneven_rows_of_a_b_of_almost_4_gb():
+    """Uneven rows multiplied one by one by the launch of the sixteen-wave kernel, with rows of B as far up as a descriptor reaches: an
+    entry past the end of a row must not load the last ones, which hold infinities and are touched by no entry."""
+    rng = np.random.default_rng(14)
+    m, k, N, ldb = 400, 131071, 64, 8192
+    lens = rng.integers(465, 495, m)
+    lens[100:112] = 20000
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(k - 3, n, replace=False)) for n in lens]).astype(np.int32)
+    va = rng.standard_normal(len(ci)).astype(np.float32)
+    B = rng.standard_normal((k, N)).astype(np.float32)
+    B[k - 3:] = np.inf
+    Bd = torch.zeros((k, ldb), device=DEV)[:, :N]
+    Bd.copy_(torch.from_numpy(B))
+    A = binding.gcoo_from_csr(m, k, *[torch.from_numpy(x).to(DEV) for x in (rp, ci, va)], 32, known_nnz=True)
+    C64, D64 = orc.spdm_csr(k, N, rp, ci, va, B)
+    for variant in (binding.VARIANT_SHARE, binding.VARIANT_AUTO):
+        print(f"band: uneven rows, B of 4.29 GB, variant={variant}", flush=True)
+        err, bad = orc.max_scaled_error(binding.gcoo_spdm(A, Bd, variant=variant).cpu().numpy(), C64, D64)
+        assert bad == 0 and err < 2e-6, (variant, err, bad)
