@@ -102,8 +102,11 @@ size_t gcoo_device_bytes(int64_t m, int64_t k, int64_t nnz, int32_t p);
  *   p             rows per group, 1..GCOO_MAX_P
  *   dev_buf       caller-owned device memory, 256-byte aligned, >= gcoo_device_bytes(m,k,nnz,p)
  * The conversion kernels (group index from row_ptr, then a stable per-group radix sort on the
- * column) run on `stream`.  With host input the call returns after the input has been copied
- * (the copies synchronise); the kernels may still be running.  *out receives the handle.
+ * column) run on `stream`.  With host input the call returns after the input has been copied, so the
+ * caller may change or release its arrays; the kernels may still be running.  An input of up to 4 MB is copied
+ * to one of four pinned buffers of the library and the call waits for the device only while all four are in
+ * use; a larger one is copied to the device, which synchronises `stream`.  A stream that is being captured is
+ * refused for host input (GCOO_EHIP), and nothing is recorded.  *out receives the handle.
  * Degenerate shapes (m = 0, nnz = 0) succeed.
  */
 int gcoo_from_csr(int64_t m, int64_t k,

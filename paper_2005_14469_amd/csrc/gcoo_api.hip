@@ -44,6 +44,15 @@ int hip_fail(hipError_t e, const char* what)
         if (e_ != hipSuccess) return hip_fail(e_, #expr); \
     } while (0)
 
+// A call that cannot be recorded into a graph says so before it launches anything: the replay of a kernel that reads or writes pinned
+// memory of the library would meet what later calls have put there.
+int refuse_capture(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &status));
+    return status == hipStreamCaptureStatusNone ? GCOO_OK : hip_fail(hipErrorStreamCaptureUnsupported, "call on a stream that is being captured");
+}
+
 constexpr size_t kAlign = 256;
 size_t al(size_t bytes) { return (bytes + kAlign - 1) / kAlign * kAlign; }
 
@@ -831,9 +840,11 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     if (nnz > 0 && (!col_idx || !vals)) return GCOO_EINVAL;
     const Layout L = make_layout(m, k, nnz, g, p, inside);
     if (dev_buf_bytes < total_bytes(m, k, nnz, p, inside)) return GCOO_ENOMEM;
+    int rc = src_on_device ? GCOO_OK : refuse_capture(s);
+    if (rc != GCOO_OK) return rc;
 
     gcoo_matrix* h = nullptr;
-    int rc = new_handle(m, k, nnz, p, dev_buf, &h, inside);
+    rc = new_handle(m, k, nnz, p, dev_buf, &h, inside);
     if (rc != GCOO_OK) return rc;
     h->from_csr = true;
     char* base = h->base;

@@ -105,6 +105,38 @@ def few_columns(host):
                 assert host.spdm(h, N, N) == OK, (policy, m, p, N)
 
 
+# ---- calls that cannot be recorded ----------------------------------------------------------------
+
+def _host_csr(host, m, k, per_row, p=32):
+    """gcoo_from_csr() with arrays in host memory; the status."""
+    rp = (np.arange(m + 1) * per_row).astype(np.int32)
+    ci = np.tile(np.arange(per_row, dtype=np.int32), m)
+    va = np.ones(m * per_row, np.float32)
+    need = host.L.gcoo_device_bytes(m, k, m * per_row, p)
+    h = C.c_void_p()
+    rc = host.L.gcoo_from_csr(m, k, rp.ctypes.data, ci.ctypes.data, va.ctypes.data, 0, p, host.buffer(need), need, None, C.byref(h))
+    assert bool(h.value) == (rc == OK)
+    if rc == OK:
+        host.L.gcoo_free(h)
+    return rc
+
+
+def host_csr_under_capture(host):
+    """A host CSR input on a stream that records: refused, and nothing of it recorded - a replay would read the library's pinned
+    buffer with whatever a later conversion has put there."""
+    for m, k, per_row, p in [(500, 700, 7, 32), (500, 700, 7, 128), (40, 60000, 3, 32), (3000, 2000, 200, 32)]:
+        assert _host_csr(host, m, k, per_row, p) == OK                        # (the pinned buffer is there)
+        host.log()
+        host.set("capturing", 1)
+        assert _host_csr(host, m, k, per_row, p) == EHIP
+        assert host.log() == []
+        host.set("capturing", 0)
+        assert _host_csr(host, m, k, per_row, p) == OK
+        host.set("hipStreamIsCapturing", 1)                                  # (the default stream while another one records)
+        assert _host_csr(host, m, k, per_row, p) == EHIP
+        host.set("hipStreamIsCapturing", 0)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Host())
     print("ok")

@@ -76,3 +76,32 @@ def test_conversion_and_product_in_a_graph(case):
         L.gcoo_free(h_g)
     finally:
         binding.gcoo_set_share_policy(binding.SHARE_AUTO)
+
+
+@pytest.mark.parametrize("m,per_row", [(500, 7), (3000, 200)])
+def test_host_csr_is_refused_while_recording(m, per_row):
+    """A host CSR input on a stream that records (one that fits the library's pinned buffers and one that does not): refused, the recording
+    goes on, and its replays are not disturbed by conversions of host inputs between them."""
+    L, k, p = binding.lib(), 2000, 32
+    w = workloads.uniform_random(m, k, 64, 1.0 - per_row / k, seed=m)
+    arrays = (w.row_ptr.ctypes.data, w.col_idx.ctypes.data, w.vals.ctypes.data)
+    B = torch.from_numpy(w.B).to(DEV)
+    need = int(L.gcoo_device_bytes(w.m, w.k, w.nnz, p))
+    buf = torch.empty(need, dtype=torch.uint8, device=DEV)
+    A = binding.gcoo_from_csr(w.m, w.k, w.row_ptr, w.col_idx, w.vals, p, device=DEV)
+    want = binding.gcoo_spdm(A, B)
+    Cg = torch.empty_like(want)
+    torch.cuda.synchronize()
+    print(f"graph: host CSR refused, m={m} nnz={w.nnz}", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp = torch.cuda.current_stream().cuda_stream
+        h = C.c_void_p()
+        assert L.gcoo_from_csr(w.m, w.k, *arrays, 0, p, buf.data_ptr(), need, sp, C.byref(h)) == binding.GCOO_EHIP and not h.value
+        binding.gcoo_spdm(A, B, Cg)
+    for replay in range(3):
+        Cg.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Cg, want), replay
+        binding.gcoo_from_csr(w.m, w.k, w.row_ptr, w.col_idx, w.vals * np.float32(2.0), p, device=DEV)
