@@ -22,7 +22,7 @@
  *
  * Streams.  `stream` arguments are hipStream_t values passed as void* (NULL = the default
  * stream).  Kernels are launched on that stream and the call returns without waiting, except
- * where a function says that it synchronises.
+ * where a function says that it synchronises; such a call cannot be recorded into a stream capture (GCOO_EHIP).
  *
  * Errors.  Every function returning int returns GCOO_OK (0) or a negative gcoo_status.  On error
  * no handle is produced and C is not written by the failing call.  No C++ exception crosses

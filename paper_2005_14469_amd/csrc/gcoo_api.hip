@@ -73,8 +73,11 @@ public:
     {
         if (i_ >= 0) g_slots_taken.fetch_and(~(1ull << i_), std::memory_order_acq_rel);
     }
-    int claim()
+    // For a kernel on stream `s`.
+    int claim(hipStream_t s)
     {
+        const int rc = refuse_capture(s);
+        if (rc != GCOO_OK) return rc;
         static std::mutex mutex;
         static unsigned long long* pinned = nullptr;
         static unsigned long long* tickets[kMaxDevices] = {};
@@ -820,7 +823,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             nnz = nnz_known;
         } else {
             HostSlot slot;
-            int rc = slot.claim();
+            int rc = slot.claim(s);
             if (rc != GCOO_OK) return rc;
             gcoo::read_entry_count<<<dim3(1), dim3(1), 0, s>>>(row_ptr, m, slot.host());
             HIP_TRY(hipGetLastError());
@@ -1029,7 +1032,7 @@ int gcoo_dense_nnz(int64_t m, int64_t k, const float* A_dev, int64_t lda, void* 
     if (m == 0 || k == 0) return GCOO_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     HostSlot slot;
-    int rc = slot.claim();
+    int rc = slot.claim(s);
     if (rc != GCOO_OK) return rc;
     const int vw = dense_vec_width(A_dev, lda, k);
     const int64_t nblk = dense_blocks(k, vw);
@@ -1068,7 +1071,7 @@ int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p
     if (nblk > 0 && g > 0x7fffffffLL / nblk) return GCOO_EINVAL;
     if ((int64_t)p * k > INT32_MAX) return GCOO_EINVAL;
     HostSlot slot;
-    int rc = slot.claim();
+    int rc = slot.claim(s);
     if (rc != GCOO_OK) return rc;
     const gcoo::DenseCounts out = dense_counts(buf, make_layout(m, k, 0, g, p));
     const int64_t items = g * nblk;

@@ -137,6 +137,29 @@ def host_csr_under_capture(host):
         host.set("hipStreamIsCapturing", 0)
 
 
+def counts_under_capture(host):
+    """A call that waits for a number from the device, on a stream that records: refused, and nothing of it recorded - a replay would
+    write its number where another call waits for its own."""
+    m, k, p = 300, 500, 32
+    n, h = C.c_int64(), C.c_void_p()
+    buf = host.buffer(1 << 20)
+    calls = [lambda: host.L.gcoo_from_csr(m, k, buf, buf, buf, 1, p, 1 << 20, 1 << 50, None, C.byref(h)),
+             lambda: host.L.gcoo_dense_nnz(m, k, 1 << 20, k, None, C.byref(n)),
+             lambda: host.L.gcoo_dense_count(m, k, 1 << 20, k, p, 1 << 20, 1 << 50, None, C.byref(n)),
+             lambda: host.L.gcoo_from_dense(m, k, 1 << 20, k, p, 1 << 20, 1 << 50, None, C.byref(h))]
+    host.set("answer", 1234)
+    for call in calls:
+        assert call() == OK
+        host.log()
+        host.set("capturing", 1)
+        host.set("hipStreamSynchronize", 900)
+        assert call() == EHIP
+        assert host.log() == []
+        host.set("capturing", 0)
+        host.set("hipStreamSynchronize", 0)
+        assert call() == OK
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Host())
     print("ok")

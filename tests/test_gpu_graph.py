@@ -105,3 +105,35 @@ def test_host_csr_is_refused_while_recording(m, per_row):
         torch.cuda.synchronize()
         assert torch.equal(Cg, want), replay
         binding.gcoo_from_csr(w.m, w.k, w.row_ptr, w.col_idx, w.vals * np.float32(2.0), p, device=DEV)
+
+
+def test_counts_are_refused_while_recording():
+    """Calls that wait for a number from the device, on a stream that records: refused, and the recording goes on without them."""
+    L, p = binding.lib(), 32
+    w = workloads.uniform_random(700, 900, 64, 0.97, seed=11)
+    dev = [torch.from_numpy(x).to(DEV) for x in (w.row_ptr, w.col_idx, w.vals)]
+    Ad = torch.zeros((w.m, w.k), device=DEV)
+    Ad[torch.repeat_interleave(torch.arange(w.m, device=DEV), torch.diff(dev[0]).long()), dev[1].long()] = dev[2]
+    B = torch.from_numpy(w.B).to(DEV)
+    need = int(L.gcoo_device_bytes(w.m, w.k, w.nnz, p))
+    buf = torch.empty(need, dtype=torch.uint8, device=DEV)
+    A = binding.gcoo_from_dense(Ad, p)
+    want = binding.gcoo_spdm(A, B)
+    Cg = torch.empty_like(want)
+    torch.cuda.synchronize()
+    print("graph: counts refused", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp = torch.cuda.current_stream().cuda_stream
+        h, n = C.c_void_p(), C.c_int64()
+        got = [L.gcoo_from_csr(w.m, w.k, *[x.data_ptr() for x in dev], 1, p, buf.data_ptr(), need, sp, C.byref(h)),
+               L.gcoo_dense_nnz(w.m, w.k, Ad.data_ptr(), w.k, sp, C.byref(n)),
+               L.gcoo_from_dense(w.m, w.k, Ad.data_ptr(), w.k, p, buf.data_ptr(), need, sp, C.byref(h))]
+        binding.gcoo_spdm(A, B, Cg)
+    assert got == [binding.GCOO_EHIP] * 3 and not h.value
+    for replay in range(3):
+        Cg.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Cg, want), replay
+        assert binding.gcoo_dense_nnz(Ad) == w.nnz
