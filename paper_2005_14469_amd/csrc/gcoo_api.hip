@@ -142,8 +142,9 @@ public:
     ~HostStage()
     {
         if (!slot_) return;
-        (void)hipDeviceSynchronize();                         // (a call that failed: its launches may still read the buffer)
-        give_back(false);
+        // A call that failed: its launches may still read the buffer.  Where even the wait for them fails nobody gets the buffer again.
+        if (hipDeviceSynchronize() == hipSuccess) give_back(false);
+        (void)hipGetLastError();
     }
     // false: none to be had (or HIP failed, which the copies that follow will say)
     bool claim()
@@ -183,11 +184,11 @@ public:
     }
     char* ptr() const { return static_cast<char*>(slot_->ptr); }
     explicit operator bool() const { return slot_ != nullptr; }
-    // Behind the last launch that reads the buffer.
+    // Behind the last launch that reads the buffer.  Without the event the buffer is kept, for the destructor to wait.
     hipError_t release(hipStream_t s)
     {
         const hipError_t e = hipEventRecord(slot_->event, s);
-        give_back(e == hipSuccess);
+        if (e == hipSuccess) give_back(true);
         return e;
     }
 

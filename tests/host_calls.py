@@ -160,6 +160,29 @@ def counts_under_capture(host):
         assert call() == OK
 
 
+# ---- the pinned buffers of host inputs ---------------------------------------------------------------
+
+def stage_release_fails(host):
+    """The event behind the readers of a pinned buffer cannot be recorded: the call waits for the device before it gives the buffer
+    back, and does not give it back at all where that fails too - its readers may still be queued."""
+    shape = (500, 700, 7)
+    assert _host_csr(host, *shape) == OK
+    host.log()
+    host.set("hipEventRecord", 1)
+    assert _host_csr(host, *shape) == EHIP
+    log = [line for line in host.log() if not line.startswith("launch")]
+    assert log == ["record", "wait device"], log
+    host.set("hipDeviceSynchronize", 1)
+    for _ in range(4):                                                       # all four are lost
+        assert _host_csr(host, *shape) == EHIP
+    host.set("hipEventRecord", 0)
+    host.set("hipDeviceSynchronize", 0)
+    host.log()
+    assert _host_csr(host, *shape) == OK
+    log = host.log()
+    assert "record" not in log and log.count("copy") == 3 and "wait stream" in log, log
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Host())
     print("ok")
