@@ -272,13 +272,15 @@ struct Layout {
     size_t take_flags, splits;
     size_t tmp_cols, tmp_rows, tmp_vals;                   // conversion scratch (second sort buffer)
     size_t in_row_ptr, in_cols, in_vals;                   // staging of a host CSR input
-    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4), uneven rows (4)
+    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4), uneven rows (4), -, ticket of a dense count (8)
     size_t persistent;                                     // bytes up to here stay in use after the conversion
     // offsets from here on are relative to the scratch area: the caller's buffer from `persistent` on, or the
     // library's static scratch
     size_t blk;                                            // dense input: entries per (group, column block)
     size_t total;
 };
+
+constexpr size_t kTicketAt = 32;                           // among the words of `counter`
 
 // Column windows of the run schedule: bands of kWindowCols columns (a band of B of that many
 // rows by one column tile stays in the L2 of the XCD working on the tile), at most kMaxWindows,
@@ -492,7 +494,7 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     // counted into them before nnz is known
     L.gIdxes = take((size_t)(g + 1) * 4);
     L.nnzPerGroup = take((size_t)g * 4);
-    L.counter = take(32);
+    L.counter = take(kTicketAt + 8);
     L.blk = take((size_t)g * (size_t)dense_blocks(k) * 4);
     L.values = take(n4);
     L.rows = take(n4);
@@ -1061,8 +1063,9 @@ gcoo::DenseCounts dense_counts(void* buf, const Layout& L)
             reinterpret_cast<int32_t*>(base + L.nnzPerGroup), reinterpret_cast<unsigned long long*>(base + L.counter)};
 }
 
-// Step 1 of Algorithm 1, and the wait for its sum.
-int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, hipStream_t s, int64_t* nnz)
+// Step 1 of Algorithm 1.  `ticket` is zero before and after; `host` receives the sum, or is null.
+int launch_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, unsigned long long* ticket,
+                       unsigned long long* host, hipStream_t s)
 {
     const int64_t g = (m + p - 1) / p;
     const int vw = dense_vec_width(A_dev, lda, k);
@@ -1071,15 +1074,23 @@ int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p
     // 32-bit counts cannot wrap before the total is checked
     if (nblk > 0 && g > 0x7fffffffLL / nblk) return GCOO_EINVAL;
     if ((int64_t)p * k > INT32_MAX) return GCOO_EINVAL;
-    HostSlot slot;
-    int rc = slot.claim(s);
-    if (rc != GCOO_OK) return rc;
     const gcoo::DenseCounts out = dense_counts(buf, make_layout(m, k, 0, g, p));
     const int64_t items = g * nblk;
     const dim3 grid((unsigned)(items < 1 ? 1 : (items < gcoo::kDenseWorkgroups ? items : gcoo::kDenseWorkgroups))), block(gcoo::kDenseThreads);
-    if (vw == 4) gcoo::count_dense_blocks<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, g, out, slot.ticket(), slot.host());
-    else gcoo::count_dense_blocks<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, g, out, slot.ticket(), slot.host());
+    if (vw == 4) gcoo::count_dense_blocks<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, g, out, ticket, host);
+    else gcoo::count_dense_blocks<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, p, nblk, g, out, ticket, host);
     HIP_TRY(hipGetLastError());
+    return GCOO_OK;
+}
+
+// The same, and the wait for its sum.
+int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, hipStream_t s, int64_t* nnz)
+{
+    HostSlot slot;
+    int rc = slot.claim(s);
+    if (rc != GCOO_OK) return rc;
+    rc = launch_dense_count(m, k, A_dev, lda, p, buf, slot.ticket(), slot.host(), s);
+    if (rc != GCOO_OK) return rc;
     unsigned long long total = 0;
     rc = slot.wait(s, &total);
     if (rc != GCOO_OK) return rc;
@@ -1100,12 +1111,20 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
     const int vw = dense_vec_width(A_dev, lda, k);
     const int64_t nblk = dense_blocks(k, vw);
     const gcoo::DenseCounts from = dense_counts(const_cast<void*>(counts), h->L), to = dense_counts(dev_buf, h->L);
+    // Groups of more than 64 rows: the regrouped copy is counted on the device alone, behind the fill, which clears its ticket.
+    const size_t own = al(h->L.total);
+    char* inner_buf = nullptr;
+    unsigned long long* inner_ticket = nullptr;
+    if (wants_inner(p)) {
+        inner_buf = h->base + own;
+        inner_ticket = reinterpret_cast<unsigned long long*>(inner_buf + make_layout(m, k, 0, (m + kInnerP - 1) / kInnerP, kInnerP).counter + kTicketAt);
+    }
     {
         const dim3 grid((unsigned)(g * nblk > 0 ? g * nblk : 1)), block(gcoo::kDenseThreads);
         const bool small = p <= 64;
         (vw == 4 ? (small ? gcoo::fill_dense_blocks<4, true> : gcoo::fill_dense_blocks<4, false>)
                  : (small ? gcoo::fill_dense_blocks<1, true> : gcoo::fill_dense_blocks<1, false>))<<<grid, block, 0, s>>>(
-            A_dev, lda, m, k, p, nblk, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols());
+            A_dev, lda, m, k, p, nblk, g, from, to, h->bad_col(), inner_ticket, h->values(), h->rows(), h->cols());
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "fill_dense_blocks"); }
     }
@@ -1118,9 +1137,10 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
     }
     rc = launch_build_schedule(h, h->base + h->L.persistent, s);
     if (rc != GCOO_OK) { delete h; return rc; }
-    if (wants_inner(p)) {
-        const size_t own = al(h->L.total);
-        rc = gcoo_from_dense(m, k, A_dev, lda, kInnerP, h->base + own, dev_buf_bytes - own, stream, &h->inner);
+    if (inner_buf) {
+        rc = launch_dense_count(m, k, A_dev, lda, kInnerP, inner_buf, inner_ticket, nullptr, s);
+        if (rc == GCOO_OK)
+            rc = from_dense_counted(m, k, nnz, A_dev, lda, kInnerP, inner_buf, inner_buf, dev_buf_bytes - own, stream, &h->inner);
         if (rc != GCOO_OK) { delete h; return rc; }
     }
     *out = h;

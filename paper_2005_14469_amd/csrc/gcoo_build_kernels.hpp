@@ -391,7 +391,7 @@ __device__ __forceinline__ int32_t count_dense_tile(const float* __restrict__ A,
 }
 
 // Item i = q*nblk + b, items strided over the workgroups; thread t of block b owns columns (b*kDenseThreads + t)*VW .. +VW-1 of the
-// band (k % VW == 0 when VW > 1).  `ticket` is 0 before and after.
+// band (k % VW == 0 when VW > 1).  `ticket` is 0 before and after; `host` may be null.
 template <int VW>
 __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k, int32_t p,
                                                                      int64_t nblk, int64_t g, DenseCounts out,
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
         out.stats[0] = (unsigned long long)carry;
         out.stats[1] = (unsigned long long)mx;
         __hip_atomic_store(ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        tell_host(host, (unsigned long long)carry);
+        if (host) tell_host(host, (unsigned long long)carry);
     }
 }
 
@@ -485,17 +485,20 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
 // SMALL (at most 64 rows per group): the count leaves a bit per element behind, and only the elements that are entries
 // are read a second time, the next one of each column together; taller groups walk the columns again.
 // (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)
-// The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..2].
+// The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..2] and, where given, the
+// ticket of the count that follows.
 // ---------------------------------------------------------------------------------------------
 template <int VW, bool SMALL>
 __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
                                                                     int32_t p, int64_t nblk, int64_t g, DenseCounts from, DenseCounts to,
-                                                                    uint32_t* __restrict__ zeroed, float* __restrict__ values,
+                                                                    uint32_t* __restrict__ zeroed, unsigned long long* __restrict__ ticket,
+                                                                    float* __restrict__ values,
                                                                     int32_t* __restrict__ rows, int32_t* __restrict__ cols)
 {
     __shared__ int32_t wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (blockIdx.x == 0 && tid < 3) zeroed[tid] = 0u;
+    if (blockIdx.x == 0 && tid == 3 && ticket) *ticket = 0ull;
     if (from.gIdxes != to.gIdxes) {
         if (blockIdx.x == 0 && tid < 2) to.stats[tid] = from.stats[tid];
         for (int64_t q = (int64_t)blockIdx.x * kDenseThreads + tid; q <= g; q += (int64_t)gridDim.x * kDenseThreads) {

@@ -183,6 +183,25 @@ def stage_release_fails(host):
     assert "record" not in log and log.count("copy") == 3 and "wait stream" in log, log
 
 
+# ---- where a dense conversion waits ------------------------------------------------------------------
+
+def dense_waits(host):
+    """gcoo_from_dense_counted() waits for nothing, gcoo_from_dense() once, whatever the group height."""
+    m, k, nnz = 3000, 700, 1234
+    host.set("answer", nnz)
+    for p in (1, 32, 64, 65, 128, 256):
+        n, h = C.c_int64(), C.c_void_p()
+        assert host.L.gcoo_dense_count(m, k, 1 << 20, k, p, 1 << 20, 1 << 50, None, C.byref(n)) == OK and n.value == nnz
+        host.log()
+        assert host.L.gcoo_from_dense_counted(m, k, nnz, 1 << 20, k, p, 1 << 20, 1 << 30, 1 << 50, None, C.byref(h)) == OK
+        log = host.log()
+        assert all(line.startswith("launch") for line in log), (p, log)
+        assert host.L.gcoo_from_dense(m, k, 1 << 20, k, p, 1 << 30, 1 << 50, None, C.byref(h)) == OK
+        assert [line for line in host.log() if not line.startswith("launch")] == ["wait stream"], p
+    host.set("capturing", 1)                                                 # so the former can be recorded
+    assert host.L.gcoo_from_dense_counted(m, k, nnz, 1 << 20, k, 128, 1 << 20, 1 << 30, 1 << 50, None, C.byref(h)) == OK
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Host())
     print("ok")

@@ -46,3 +46,41 @@ def test_counts_and_fill(m, k, p, density):
             assert np.array_equal(e["gIdxes"], want.gIdxes) and np.array_equal(e["nnzPerGroup"], want.nnzPerGroup)
         else:
             assert len(e["values"]) == 0 and not e["gIdxes"].any()
+
+
+@pytest.mark.parametrize("m,k,p", [(700, 900, 65), (130, 1031, 128), (3000, 260, 256)])
+def test_fill_of_tall_groups_in_a_graph(m, k, p):
+    """gcoo_from_dense_counted() waits for nothing and can be recorded, for groups of more than 64 rows too, whose regrouped copy is counted
+    on the device alone.  Replayed on new values in the same cells, against the oracle."""
+    print(f"dense count: {m}x{k} p={p} in a graph", flush=True)
+    rng = np.random.default_rng(p)
+    Ah = (rng.standard_normal((m, k)) * (rng.random((m, k)) < 0.07)).astype(np.float32)
+    A, B = torch.from_numpy(Ah).to(DEV), torch.from_numpy(rng.standard_normal((k, 68)).astype(np.float32)).to(DEV)
+    L, n, h = binding.lib(), C.c_int64(), C.c_void_p()
+    counts = torch.empty(L.gcoo_dense_count_bytes(m, k, p), dtype=torch.uint8, device=DEV)
+    sp = torch.cuda.current_stream().cuda_stream
+    assert L.gcoo_dense_count(m, k, A.data_ptr(), k, p, counts.data_ptr(), counts.numel(), sp, C.byref(n)) == 0
+    need = L.gcoo_device_bytes(m, k, n.value, p)
+    buf = torch.full((need,), 0x5a, dtype=torch.uint8, device=DEV)
+    Cg = torch.empty((m, 68), device=DEV)
+    binding.gcoo_spdm(binding.gcoo_from_dense(A, p), B, Cg)                # (kernel limits are raised on a first call)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp = torch.cuda.current_stream().cuda_stream
+        assert L.gcoo_from_dense_counted(m, k, n.value, A.data_ptr(), k, p, counts.data_ptr(), buf.data_ptr(), need, sp, C.byref(h)) == 0
+        H = binding.GcooMatrix(h.value, buf)
+        binding.gcoo_spdm(H, B, Cg)
+    for replay in range(4):
+        A.mul_(1.25)
+        Cg.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        want = orc.gcoo_from_dense(A.cpu().numpy(), p)
+        e = H.export()
+        assert np.array_equal(e["values"].view(np.uint32), want.values.view(np.uint32)) and np.array_equal(e["rows"], want.rows)
+        assert np.array_equal(e["cols"], want.cols) and np.array_equal(e["gIdxes"], want.gIdxes)
+        Ce = binding.gcoo_spdm(binding.gcoo_from_dense(A, p), B)
+        assert torch.equal(Cg, Ce), replay
+        ref = A.double() @ B.double()
+        assert ((Cg.double() - ref).abs().max() / ref.abs().max()).item() < 2e-6
