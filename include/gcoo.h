@@ -262,7 +262,7 @@ int gcoo_set_share_policy(int policy);
  * call once with the arrays NULL to learn them.  Both are 0, and nothing is copied, for a matrix whose GCOO_VARIANT_SHARE reads the band
  * schedule instead.  sbase has 8 * ceil(g / 8) entries, ucount ceil(g / 8),
  * ucols nnz (the distinct columns of super-group Q start at index gIdxes[8Q]).  Synchronises `stream`.
- * GCOO_EINVAL if A is NULL or has no share schedule.
+ * GCOO_EINVAL if A is NULL or has neither schedule.
  */
 int gcoo_export_share(const gcoo_matrix* A, uint32_t* hdr, uint32_t* blocks, int32_t* sbase, int32_t* ucount, int32_t* ucols,
                       int64_t* hdr_words, int64_t* block_count, void* stream);

@@ -182,10 +182,14 @@ class GcooMatrix:
         return dict(values=v, rows=r, cols=c, gIdxes=gi, nnzPerGroup=npg)
 
     def export_share(self, stream=None):
-        """The share schedule as numpy arrays on the host, or None if this matrix has none."""
+        """The share schedule as numpy arrays on the host; arrays of no elements where VARIANT_SHARE reads the band schedule instead;
+        None for a matrix that VARIANT_SHARE does not serve."""
         hw, nb = C.c_int64(), C.c_int64()
         if lib().gcoo_export_share(self.handle, None, None, None, None, None, C.byref(hw), C.byref(nb), _stream_ptr(stream)) != GCOO_OK:
             return None
+        if hw.value == 0:
+            return dict(hdr=np.empty(0, np.uint32), blocks=np.empty(0, np.uint32), sbase=np.empty(0, np.int32), ucount=np.empty(0, np.int32),
+                        ucols=np.empty(0, np.int32))
         i = self.info()
         nq = (i["g"] + 7) // 8
         hdr = np.empty(hw.value, np.uint32)

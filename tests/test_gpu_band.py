@@ -145,3 +145,12 @@ def test_non_finite_values_beside_uneven_rows_of_a_b_of_almost_4_gb():
         print(f"band: uneven rows, B of 4.29 GB, variant={variant}", flush=True)
         err, bad = orc.max_scaled_error(binding.gcoo_spdm(A, Bd, variant=variant).cpu().numpy(), C64, D64)
         assert bad == 0 and err < 2e-6, (variant, err, bad)
+
+
+def test_export_share_of_a_matrix_with_a_band_schedule():
+    """There is no share schedule to copy: nothing but empty arrays, no uninitialised ones."""
+    print("band: export_share", flush=True)
+    w = workloads.uniform_random(385, 3600, 64, 0.98, seed=5)
+    A = binding.gcoo_from_csr(w.m, w.k, w.row_ptr, w.col_idx, w.vals, 32, device=DEV)
+    assert {key: x.size for key, x in A.export_share().items()} == dict(hdr=0, blocks=0, sbase=0, ucount=0, ucols=0)
+    assert binding.gcoo_from_csr(w.m, w.k, w.row_ptr, w.col_idx, w.vals, 49, device=DEV).export_share() is None
