@@ -1313,8 +1313,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
-    // The automatic choice leaves the LDS kernel a matrix without columns, and a row pitch of B that the others do not hold in 32 bits.
-    if (variant == GCOO_VARIANT_LDS && (!automatic || A->k < 1 || sh.wide_pitch)) {
+    auto run_lds = [&]() -> int {
         const int64_t tiles = (N + 63) / 64;
         const int64_t total = A->g * tiles;
         if (total > 0x7fffffffLL) return GCOO_EINVAL;
@@ -1323,7 +1322,10 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
                                                                      A->p, B_dev, ldb, N, C_dev, ldc, A->g);
         HIP_TRY(hipGetLastError());
         return GCOO_OK;
-    }
+    };
+    // The automatic choice leaves the LDS kernel a row pitch of B that the others do not hold in 32 bits, and a matrix without columns, which
+    // the row-by-row kernel does not take.
+    if (automatic ? A->k < 1 || (variant == GCOO_VARIANT_LDS && sh.wide_pitch) : variant == GCOO_VARIANT_LDS) return run_lds();
     if (A->inner) A = A->inner;        // the schedules of the kernels below belong to the regrouped copy
     auto rows_args = [&]() {
         gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
@@ -1341,7 +1343,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         hipError_t e = gcoo::launch_spdm_band(a, rows_args(), s);
         return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_band launch");
     };
-    if (automatic && A->has_rows() && A->k >= 1) {
+    if (automatic && A->has_rows()) {
         const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
         if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) && band_time(A->m, A->k, A->nnz, N, A->L.band_h, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
             return run_band();
@@ -1358,6 +1360,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     }
     const int V = sched_width(A->p, sh);
     if (V == 0 || !A->has_rows()) return GCOO_EINVAL;
+    if (A->k < 1) return run_lds();
     if (!A->has_sched) return run_rows();
     const int cols_per_lane = V == kTallInstance ? 4 : V;
     // Heavy groups are shared by a workgroup in the standard instances only, and only a launch of few

@@ -202,6 +202,24 @@ def dense_waits(host):
     assert host.L.gcoo_from_dense_counted(m, k, nnz, 1 << 20, k, 128, 1 << 20, 1 << 30, 1 << 50, None, C.byref(h)) == OK
 
 
+# ---- a matrix without columns --------------------------------------------------------------------------
+
+def no_columns(host):
+    """A of k = 0 columns: the product is all zeros, and some kernel writes them, also where the register variant is asked for."""
+    for policy in (0, 1, 2):
+        assert host.L.gcoo_set_share_policy(policy) == OK
+        for p in (1, 32, 64, 65, 256):
+            h = host.matrix(500, 0, 0, p)
+            for N in (1, 2, 3, 4, 260):
+                host.log()
+                assert host.spdm(h, N, N, AUTO, None, None) == OK, (policy, p, N)
+                assert len(host.launches()) == 1
+                wide = N >= (2 if 38 < p <= 64 else 4)
+                status = host.spdm(h, N, N, REG, None, None)
+                assert status == OK if wide else status in (OK, EINVAL), (policy, p, N, status)
+                assert len(host.launches()) == (status == OK)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[1]](Host())
     print("ok")

@@ -140,3 +140,19 @@ def test_few_columns_of_a_matrix_with_a_run_schedule(policy):
         C64, D64 = orc.spdm_csr(k, N, rp, ci, va, B)
         err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
         assert bad == 0 and err < 2e-6, (N, err, bad)
+
+
+@pytest.mark.parametrize("p,policy", [(1, binding.SHARE_AUTO), (32, binding.SHARE_AUTO), (32, binding.SHARE_NEVER), (128, binding.SHARE_AUTO)])
+def test_no_columns(p, policy):
+    """A of k = 0 columns: zeros, in all N columns of C and nowhere else."""
+    binding.gcoo_set_share_policy(policy)
+    try:
+        A = binding.gcoo_from_csr(70, 0, np.zeros(71, np.int32), np.zeros(0, np.int32), np.zeros(0, np.float32), p, device=DEV)
+    finally:
+        binding.gcoo_set_share_policy(binding.SHARE_AUTO)
+    for N in (1, 3, 4, 130):
+        for variant in (binding.VARIANT_AUTO, binding.VARIANT_REG) if N >= 4 else (binding.VARIANT_AUTO,):
+            print(f"rows: no columns, p={p} N={N} variant={variant}", flush=True)
+            C = torch.full((70, N + 5), 7.0, device=DEV)
+            binding.gcoo_spdm(A, torch.empty((0, N), device=DEV), C[:, :N], variant=variant)
+            assert not C[:, :N].any() and torch.all(C[:, N:] == 7.0)
