@@ -220,10 +220,22 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
 /* One of GCOO_VARIANT_* > 0: GCOO_VARIANT_SHARE where the matrix may be asked for it (see GCOO_SHARE_AUTO), the operands
  * qualify and C has at least 192 blocks of (8p rows) x 256 columns - below 9000 columns of A also only if those blocks fill their
  * rounds over the 256 compute units to 80 % -, else GCOO_VARIANT_REG where it serves the shape, else GCOO_VARIANT_LDS.
- * GCOO_VARIANT_AUTO itself goes by the time that the row-by-row kernel (any shape) and the kernel of the band schedule are expected
- * to take, so it may run either of them whatever this function answers. */
+ * A variant that may be asked for, by a rule on the shape; GCOO_VARIANT_AUTO itself goes by the time that the row-by-row kernel (any
+ * shape) and the kernel of the band schedule are expected to take.  gcoo_spdm_kernel() says which kernel runs. */
 int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                    const float* C_dev, int64_t ldc);
+
+/* The kernel that gcoo_spdm_variant() launches for these arguments, GCOO_VARIANT_AUTO included: one of GCOO_KERNEL_*, or the status it
+ * returns instead (a negative number).  Launches nothing.  Where the device has found the rows of a matrix too uneven for the band
+ * schedule (GCOO_SHARE_AUTO), which the host does not know, the launch of GCOO_KERNEL_BAND multiplies them one by one. */
+#define GCOO_KERNEL_NONE  0  /* nothing to multiply */
+#define GCOO_KERNEL_LDS   1  /* spdm_lds */
+#define GCOO_KERNEL_SCHED 2  /* spdm_sched, spdm_sched_coop: the run schedule */
+#define GCOO_KERNEL_SHARE 3  /* spdm_share: the share schedule */
+#define GCOO_KERNEL_ROWS  4  /* spdm_rows, spdm_vectors: the entries in row order */
+#define GCOO_KERNEL_BAND  5  /* spdm_band: the band schedule */
+int gcoo_spdm_kernel(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
+                     const float* C_dev, int64_t ldc, int variant);
 
 /* Release the host handle.  The device buffer stays the caller's.  NULL is accepted. */
 int gcoo_free(gcoo_matrix* A);

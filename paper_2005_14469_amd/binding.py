@@ -22,12 +22,13 @@ GCOO_OK, GCOO_EINVAL, GCOO_EBOUNDS, GCOO_ENOMEM, GCOO_EHIP, GCOO_ELIMIT = 0, -1,
 GCOO_STATIC_MAX_NNZ = 2097152
 GCOO_MAX_P = 256
 VARIANT_AUTO, VARIANT_LDS, VARIANT_REG, VARIANT_SHARE = 0, 1, 2, 3
+KERNEL_NONE, KERNEL_LDS, KERNEL_SCHED, KERNEL_SHARE, KERNEL_ROWS, KERNEL_BAND = 0, 1, 2, 3, 4, 5
 SHARE_AUTO, SHARE_ALWAYS, SHARE_NEVER = 0, 1, 2
 
 # every symbol include/gcoo.h declares
 SYMBOLS = ["gcoo_default_p", "gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_csr_device", "gcoo_dense_nnz", "gcoo_from_dense", "gcoo_spdm",
            "gcoo_dense_count_bytes", "gcoo_dense_count", "gcoo_from_dense_counted",
-           "gcoo_spdm_variant", "gcoo_spdm_pick", "gcoo_free", "gcoo_info", "gcoo_export",
+           "gcoo_spdm_variant", "gcoo_spdm_pick", "gcoo_spdm_kernel", "gcoo_free", "gcoo_info", "gcoo_export",
            "gcoo_strerror", "gcoo_last_hip_error", "gcoo_set_share_policy", "gcoo_export_share",
            "gcoo_static_handle_bytes", "gcoo_from_csr_device_static"]
 # and include/gcoo_baseline.h (libgcoo_baseline.so)
@@ -77,6 +78,8 @@ def lib():
         L.gcoo_spdm_variant.argtypes = [vp, vp, i64, i64, vp, i64, vp, C.c_int]
         L.gcoo_spdm_pick.restype = C.c_int
         L.gcoo_spdm_pick.argtypes = [vp, vp, i64, i64, vp, i64]
+        L.gcoo_spdm_kernel.restype = C.c_int
+        L.gcoo_spdm_kernel.argtypes = [vp, vp, i64, i64, vp, i64, C.c_int]
         L.gcoo_free.restype = C.c_int
         L.gcoo_free.argtypes = [vp]
         L.gcoo_info.restype = C.c_int
@@ -339,6 +342,11 @@ def gcoo_spdm(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor | None = None,
 
 def gcoo_spdm_pick(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor) -> int:
     return int(lib().gcoo_spdm_pick(A.handle, B.data_ptr(), B.stride(0), B.shape[1], C_out.data_ptr(), C_out.stride(0)))
+
+
+def gcoo_spdm_kernel(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor, variant: int = VARIANT_AUTO) -> int:
+    """The kernel (KERNEL_*) that gcoo_spdm() launches for these arguments, or the negative status it fails with."""
+    return int(lib().gcoo_spdm_kernel(A.handle, B.data_ptr(), B.stride(0), B.shape[1], C_out.data_ptr(), C_out.stride(0), variant))
 
 
 def gcoo_csr_spmm_baseline(m: int, k: int, row_ptr: torch.Tensor, col_idx: torch.Tensor, vals: torch.Tensor,

@@ -1301,19 +1301,63 @@ int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_
     return (A->has_rows() && sched_width(A->p, sh)) ? GCOO_VARIANT_REG : GCOO_VARIANT_LDS;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The kernel that a product runs (GCOO_KERNEL_*), or GCOO_EINVAL.  The arguments have passed check_spdm_args().  *M becomes the copy
+// regrouped at kInnerP rows where the product is made with that.
+int kernel_of_product(const gcoo_matrix** M, const Shape& sh, const float* B_dev, int64_t ldb, const float* C_dev, int64_t ldc, int variant)
+{
+    const gcoo_matrix* A = *M;
+    const int64_t N = sh.N;
+    if (variant < GCOO_VARIANT_AUTO || variant > GCOO_VARIANT_SHARE) return GCOO_EINVAL;
+    if (A->m == 0 || N == 0) return GCOO_KERNEL_NONE;
+    const bool automatic = variant == GCOO_VARIANT_AUTO;
+    if (automatic) variant = gcoo_spdm_pick(A, B_dev, ldb, N, C_dev, ldc);
+    // The automatic choice leaves the LDS kernel a row pitch of B that the others do not hold in 32 bits, and a matrix without columns, which
+    // the row-by-row kernel does not take.
+    if (automatic ? A->k < 1 || (variant == GCOO_VARIANT_LDS && sh.wide_pitch) : variant == GCOO_VARIANT_LDS) return GCOO_KERNEL_LDS;
+    if (A->inner) *M = A = A->inner;   // the schedules of the other kernels belong to the regrouped copy
+    if (automatic && A->has_rows()) {
+        const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
+        if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) &&
+            band_time(A->m, A->k, A->nnz, N, A->L.band_h, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
+            return GCOO_KERNEL_BAND;
+        if (!A->has_sched || rows_preferred(A, N) || sched_width(A->p, sh) == 0) return GCOO_KERNEL_ROWS;     // (0: fewer columns than the register kernel serves)
+    }
+    if (variant == GCOO_VARIANT_SHARE) {
+        if (!share_operands_ok(A, sh, ldb)) return GCOO_EINVAL;
+        if (A->has_share) return GCOO_KERNEL_SHARE;
+        return A->share_preferred && band_operands_ok(A, sh, ldb) ? GCOO_KERNEL_BAND : GCOO_EINVAL;
+    }
+    if (sched_width(A->p, sh) == 0 || !A->has_rows()) return GCOO_EINVAL;
+    if (A->k < 1) return GCOO_KERNEL_LDS;
+    return A->has_sched ? GCOO_KERNEL_SCHED : GCOO_KERNEL_ROWS;
+}
+
+}  // namespace
+
+extern "C" {
+
+int gcoo_spdm_kernel(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N, const float* C_dev, int64_t ldc, int variant)
+{
+    const int rc = check_spdm_args(A, B_dev, ldb, N, C_dev, ldc);
+    if (rc != GCOO_OK) return rc;
+    return kernel_of_product(&A, shape_of(B_dev, ldb, N, C_dev, ldc), B_dev, ldb, C_dev, ldc, variant);
+}
+
 int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N, float* C_dev, int64_t ldc,
                       void* stream, int variant)
 {
-    int rc = check_spdm_args(A, B_dev, ldb, N, C_dev, ldc);
+    const int rc = check_spdm_args(A, B_dev, ldb, N, C_dev, ldc);
     if (rc != GCOO_OK) return rc;
-    if (variant < GCOO_VARIANT_AUTO || variant > GCOO_VARIANT_SHARE) return GCOO_EINVAL;
-    const bool automatic = variant == GCOO_VARIANT_AUTO;
-    if (automatic) variant = gcoo_spdm_pick(A, B_dev, ldb, N, C_dev, ldc);
-    if (A->m == 0 || N == 0) return GCOO_OK;
+    const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
+    const int kernel = kernel_of_product(&A, sh, B_dev, ldb, C_dev, ldc, variant);
+    if (kernel <= GCOO_KERNEL_NONE) return kernel;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
-    const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
-    auto run_lds = [&]() -> int {
+    if (kernel == GCOO_KERNEL_LDS) {
         const int64_t tiles = (N + 63) / 64;
         const int64_t total = A->g * tiles;
         if (total > 0x7fffffffLL) return GCOO_EINVAL;
@@ -1322,46 +1366,27 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
                                                                      A->p, B_dev, ldb, N, C_dev, ldc, A->g);
         HIP_TRY(hipGetLastError());
         return GCOO_OK;
-    };
-    // The automatic choice leaves the LDS kernel a row pitch of B that the others do not hold in 32 bits, and a matrix without columns, which
-    // the row-by-row kernel does not take.
-    if (automatic ? A->k < 1 || (variant == GCOO_VARIANT_LDS && sh.wide_pitch) : variant == GCOO_VARIANT_LDS) return run_lds();
-    if (A->inner) A = A->inner;        // the schedules of the kernels below belong to the regrouped copy
-    auto rows_args = [&]() {
-        gcoo::RowsArgs a{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
-                         A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
-        if (A->from_csr && A->L.by_masks && A->L.plan.fused) { a.long_count = nullptr; a.long_row = INT32_MAX; }     // (none are listed)
-        return a;
-    };
-    auto run_rows = [&]() -> int {
-        hipError_t e = gcoo::launch_spdm_rows(rows_args(), s);
-        return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
-    };
-    auto run_band = [&]() -> int {
+    }
+    if (kernel == GCOO_KERNEL_ROWS || kernel == GCOO_KERNEL_BAND) {
+        gcoo::RowsArgs rows{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
+                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
+        if (A->from_csr && A->L.by_masks && A->L.plan.fused) { rows.long_count = nullptr; rows.long_row = INT32_MAX; }     // (none are listed)
+        if (kernel == GCOO_KERNEL_ROWS) {
+            hipError_t e = gcoo::launch_spdm_rows(rows, s);
+            return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
+        }
         gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band_h), A->L.band_h,
                          0, 0, A->uneven(), gcoo::band_head_stride(A->k), A->m, A->k, B_dev, ldb, N, C_dev, ldc};
-        hipError_t e = gcoo::launch_spdm_band(a, rows_args(), s);
+        hipError_t e = gcoo::launch_spdm_band(a, rows, s);
         return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_band launch");
-    };
-    if (automatic && A->has_rows()) {
-        const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
-        if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) && band_time(A->m, A->k, A->nnz, N, A->L.band_h, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
-            return run_band();
-        if (!A->has_sched || rows_preferred(A, N) || sched_width(A->p, sh) == 0) return run_rows();     // (0: fewer columns than the register kernel serves)
     }
-    if (variant == GCOO_VARIANT_SHARE) {
-        if (!share_operands_ok(A, sh, ldb)) return GCOO_EINVAL;
-        if (!A->has_share) return A->share_preferred && band_operands_ok(A, sh, ldb) ? run_band() : GCOO_EINVAL;
+    if (kernel == GCOO_KERNEL_SHARE) {
         gcoo::ShareArgs a{A->share_hdr(), A->share_blocks(), A->share_sbase(), A->share_ucols(), A->share_ucount(), A->gIdxes(),
                           A->m, A->p, A->g, A->share_nq(), B_dev, ldb, N, C_dev, ldc};
         hipError_t e = gcoo::launch_spdm_share(a, s);
-        if (e != hipSuccess) return hip_fail(e, "spdm_share launch");
-        return GCOO_OK;
+        return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_share launch");
     }
     const int V = sched_width(A->p, sh);
-    if (V == 0 || !A->has_rows()) return GCOO_EINVAL;
-    if (A->k < 1) return run_lds();
-    if (!A->has_sched) return run_rows();
     const int cols_per_lane = V == kTallInstance ? 4 : V;
     // Heavy groups are shared by a workgroup in the standard instances only, and only a launch of few
     // items can have any: then the kernels decide group by group, from the statistics on the device.

@@ -43,6 +43,7 @@ class Host:
                 ("gcoo_from_dense_counted", C.c_int, [i64, i64, i64, vp, i64, i32, vp, vp, sz, vp, C.POINTER(vp)]),
                 ("gcoo_spdm_variant", C.c_int, [vp, vp, i64, i64, vp, i64, vp, C.c_int]),
                 ("gcoo_spdm_pick", C.c_int, [vp, vp, i64, i64, vp, i64]),
+                ("gcoo_spdm_kernel", C.c_int, [vp, vp, i64, i64, vp, i64, C.c_int]),
                 ("gcoo_free", C.c_int, [vp]), ("gcoo_set_share_policy", C.c_int, [C.c_int])]:
             f = getattr(self.L, name)
             f.restype, f.argtypes = res, args
@@ -218,6 +219,40 @@ def no_columns(host):
                 status = host.spdm(h, N, N, REG, None, None)
                 assert status == OK if wide else status in (OK, EINVAL), (policy, p, N, status)
                 assert len(host.launches()) == (status == OK)
+
+
+# ---- which kernel runs --------------------------------------------------------------------------------
+
+def kernel_of_product(host):
+    """gcoo_spdm_kernel() names the kernel that gcoo_spdm_variant() launches, or the status it fails with."""
+    kernels = {1: ("spdm_lds",), 2: ("spdm_sched",), 3: ("spdm_share",), 4: ("spdm_rows", "spdm_vectors"), 5: ("spdm_band",)}
+    seen = set()
+    shapes = [(256, 256, 0.1), (4000, 4000, 0.05), (1777, 2301, 0.03), (8000, 8000, 0.005), (8000, 8000, 0.1), (12001, 12001, 0.0005),
+              (16384, 16384, 0.0032), (20, 8000, 0.01), (385, 3600, 0.02), (5, 0, 0.0), (40, 7, 0.0), (0, 5, 0.0), (40000, 40, 0.5)]
+    for policy in (0, 1, 2):
+        assert host.L.gcoo_set_share_policy(policy) == OK
+        for m, k, density in shapes:
+            for p in (1, 32, 38, 42, 48, 64, 65, 256):
+                h = host.matrix(m, k, int(m * k * density), p)
+                for N, pad, off in [(0, 0, 0), (1, 0, 0), (3, 1, 4), (4, 0, 0), (64, 0, 0), (255, 0, 0), (256, 4, 4), (1024, 0, 0), (1117, 0, 0),
+                                    (8000, 0, 0), (8000, 8, 16), (64, 1 << 30, 0), (256, 600000, 0)]:
+                    for variant in (-1, 0, 1, 2, 3, 4):
+                        B, Cp, ldb = (1 << 30) + off, (1 << 40) + off, N + pad
+                        host.log()
+                        kernel = host.L.gcoo_spdm_kernel(h, B, ldb, N, Cp, N, variant)
+                        assert host.log() == []
+                        status = host.spdm(h, N, ldb, variant, None, B, Cp)
+                        names = host.launches()
+                        what = (policy, m, k, density, p, N, pad, off, variant, kernel, status, names)
+                        if kernel <= 0:
+                            assert status == kernel and names == [], what
+                            assert kernel == EINVAL or m == 0 or N == 0, what
+                        else:
+                            assert status == OK and names and all(any(x in n for x in kernels[kernel]) for n in names), what
+                        seen.add((variant, kernel))
+                host.L.gcoo_free(h)
+    assert {(0, x) for x in (1, 2, 4, 5)} | {(2, 2), (2, 4), (3, 3), (3, 5)} <= seen, seen
+    assert host.L.gcoo_spdm_kernel(None, 1 << 20, 4, 4, 1 << 20, 4, 0) == EINVAL
 
 
 if __name__ == "__main__":
