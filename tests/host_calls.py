@@ -47,6 +47,7 @@ class Host:
                 ("gcoo_free", C.c_int, [vp]), ("gcoo_set_share_policy", C.c_int, [C.c_int])]:
             f = getattr(self.L, name)
             f.restype, f.argtypes = res, args
+        self.keep = []
         self.log()
 
     def set(self, key, value):
@@ -61,7 +62,7 @@ class Host:
     def buffer(self, nbytes):
         """`nbytes` of memory at a multiple of 4096; kept."""
         raw = np.zeros(nbytes + 4096, np.uint8)
-        self.keep = getattr(self, "keep", []) + [raw]
+        self.keep.append(raw)
         return raw.ctypes.data + (-raw.ctypes.data) % 4096
 
     def matrix(self, m, k, nnz, p):
@@ -253,6 +254,44 @@ def kernel_of_product(host):
                 host.L.gcoo_free(h)
     assert {(0, x) for x in (1, 2, 4, 5)} | {(2, 2), (2, 4), (3, 3), (3, 5)} <= seen, seen
     assert host.L.gcoo_spdm_kernel(None, 1 << 20, 4, 4, 1 << 20, 4, 0) == EINVAL
+
+
+# ---- threads ---------------------------------------------------------------------------------------------
+
+def one_handle_many_threads(host):
+    """Eight threads multiply with one handle and convert matrices of their own beside it: every call launches what it launches
+    alone, and nothing writes to the handle."""
+    import threading
+    libc = C.CDLL(None)
+    libc.malloc_usable_size.restype, libc.malloc_usable_size.argtypes = C.c_size_t, [C.c_void_p]
+    shape = (4000, 4000, 800000, 32)
+    h = host.matrix(*shape)
+    inside = C.string_at(h, libc.malloc_usable_size(h))
+    host.log()
+    calls = [(8000, AUTO), (64, AUTO), (1, AUTO), (260, REG), (512, SHARE), (100, LDS)]
+
+    def work(wrong):
+        for _ in range(50):
+            for N, variant in calls:
+                if host.spdm(h, N, N, variant) != OK:
+                    wrong.append((N, variant))
+            host.L.gcoo_free(host.matrix(*shape))
+            if _host_csr(host, 500, 700, 7) != OK:
+                wrong.append("host")
+
+    def launched(threads):
+        wrong = []
+        ts = [threading.Thread(target=work, args=(wrong,)) for _ in range(threads)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        assert wrong == []
+        return sorted(line for line in host.log() if line.startswith("launch"))
+
+    alone = launched(1)
+    assert launched(8) == sorted(alone * 8)
+    assert C.string_at(h, libc.malloc_usable_size(h)) == inside
 
 
 if __name__ == "__main__":
