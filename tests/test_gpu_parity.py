@@ -196,7 +196,7 @@ def test_ragged_shapes_all_variants(m, k, N, p):
 
 
 def test_register_kernel_refuses_what_it_does_not_serve():
-    _say("REG variant: a single column is refused, AUTO falls back to the LDS kernel")
+    _say("REG variant: a single column is refused, where gcoo_spdm_pick names the LDS variant")
     w = workloads.uniform_random(256, 256, 64, 0.9, seed=5)
     Bt = torch.from_numpy(w.B).to(DEV)
     for p, N in [(128, 1), (32, 1), (48, 1)]:
@@ -251,8 +251,8 @@ def test_register_kernel_one_column_per_lane():
     (256, 2500, 1024, 32, 0.9),
 ])
 def test_heavy_groups_shared_by_a_workgroup(m, k, N, p, sparsity):
-    """Few (group, tile) items with thousands of entries each: the register kernel hands such groups
-    to eight waves that split the entries and add their partial sums in a fixed order."""
+    """Few (group, tile) items with thousands of entries each, row by row: rows shared by a wave or a workgroup, whose partial sums are
+    added in a fixed order.  (The register kernel on the same shapes: test_gpu_run_schedule.py.)"""
     w = workloads.uniform_random(m, k, N, sparsity, seed=m + k + N)
     _say(f"heavy groups m={m} k={k} N={N} p={p} nnz={w.nnz}")
     err, A, c1 = _check_product(w, p, binding.VARIANT_REG)
@@ -500,8 +500,8 @@ def test_share_variant_repeated_coordinates_and_strides(share_always):
 
 
 def test_share_policy_and_automatic_choice():
-    """By default a matrix gets a share schedule only where the workgroup-shared kernel is the automatic choice;
-    the register kernel's schedule is always there, so either kernel can run on the same handle."""
+    """By default GCOO_VARIANT_SHARE can be asked for only where the shape qualifies (gcoo_spdm_pick then names it for a B that is wide enough);
+    GCOO_VARIANT_REG can always be.  The automatic product is right whichever kernel it takes."""
     _say("share policy")
     w = workloads.uniform_random(4096, 12000, 3072, 0.97, seed=8)      # 12000 columns, 3 % dense
     Bt = torch.from_numpy(w.B).to(DEV)
@@ -570,15 +570,15 @@ def test_full_size_configs_every_element(index):
     _say(f"  every element within {worst:.2e}")
     _, C2 = _every_element(w, A, Bt, binding.VARIANT_AUTO)
     assert torch.equal(C1, C2)
-    if index == 3:                       # the register kernel at its best height, as before the workgroup-shared one took over here
+    if index == 3:                       # row by row as well, which GCOO_VARIANT_REG is without a run schedule
         A32 = binding.gcoo_from_csr(w.m, w.k, *dev, 32, device=DEV, known_nnz=True)
         worst, _ = _every_element(w, A32, Bt, binding.VARIANT_REG)
-        _say(f"  register kernel, p = 32: every element within {worst:.2e}")
+        _say(f"  row by row, p = 32: every element within {worst:.2e}")
 
 
 def test_full_size_sweep_point_every_element():
     """8000^2 at s=0.98, N = 8000, as the benchmark's sweeps run it: group height from gcoo_default_p, automatic
-    variant (the workgroup-shared kernel); arrays and every element of C against the oracle."""
+    variant (the sixteen-wave kernel); arrays and every element of C against the oracle."""
     n, s = 8000, 0.98
     w = workloads.uniform_random(n, n, n, s, workloads.BASE_SEED + n, name="uniform_8000_0.98")
     p = binding.gcoo_default_p(w.m, w.k, w.nnz, w.N)
@@ -604,9 +604,8 @@ def test_skewed_config_through_the_share_variant(share_always, p):
 
 
 def test_zipf_config_every_element_default_path():
-    """The 16384^2 power-law workload as the benchmark runs it (library default height, automatic variant): a launch of
-    few items, so the register kernel takes the groups in order of falling size, splits the heavy ones over the
-    waves of a workgroup and bundles the others.  Every element against the oracle; the same bits twice."""
+    """The 16384^2 power-law workload as the benchmark runs it (library default height, automatic variant): row by row, the long
+    rows first, each shared by a workgroup.  Every element against the oracle; the same bits twice."""
     w = workloads.config(4)
     p = binding.gcoo_default_p(w.m, w.k, w.nnz, w.N)
     _say(f"config4 default path p={p} nnz={w.nnz}")
@@ -622,8 +621,8 @@ def test_zipf_config_every_element_default_path():
 @pytest.mark.parametrize("p", [4, 16, 32, 64])
 @pytest.mark.parametrize("N", [64, 260, 1031])
 def test_skewed_rows_few_items(p, N):
-    """Power-law rows in launches of few items, from all groups heavy (one tile, tall groups) to a mix of heavy
-    groups and bundles of light ones, with N that is no multiple of the columns per lane."""
+    """Power-law rows in launches of few workgroups, row by row, with N that is no multiple of four.  (Through the register kernel, with heavy
+    groups and bundles of light ones: test_gpu_run_schedule.py.)"""
     w = workloads.zipf_rows(900, 5000, N, seed=23 + p, row_max=3000)
     _say(f"skewed rows, few items: p={p} N={N} nnz={w.nnz}")
     err, A, c1 = _check_product(w, p, binding.VARIANT_REG)
@@ -636,9 +635,8 @@ def test_skewed_rows_few_items(p, N):
 
 @pytest.mark.parametrize("p", [8, 32, 38, 48])
 def test_register_kernel_with_any_n_and_alignment(p):
-    """N that is no multiple of the columns per lane, and views that start 4, 8 or 12 bytes into a row with odd leading
-    dimensions: the register kernel serves them all (unaligned 16-byte accesses, the last lane of a row shifted
-    inside), and nothing outside the N columns of C is written."""
+    """N that is no multiple of four, and views that start 4, 8 or 12 bytes into a row with odd leading dimensions, where gcoo_spdm_pick names
+    GCOO_VARIANT_REG: nothing outside the N columns of C is written.  (Through the register kernel: test_gpu_run_schedule.py.)"""
     w = workloads.uniform_random(300, 400, 1031, 0.9, seed=31)
     _say(f"register kernel, ragged N and alignment, p={p}")
     A = binding.gcoo_from_csr(w.m, w.k, w.row_ptr, w.col_idx, w.vals, p, device=DEV)
@@ -659,7 +657,7 @@ def test_register_kernel_with_any_n_and_alignment(p):
 
 
 def test_skewed_matrix_through_the_tall_layout():
-    """Power-law row lengths at p = 38 (the tall accumulator layout, which never splits a heavy group)."""
+    """Power-law row lengths at p = 38, row by row.  (Through the tall accumulator layout: test_gpu_run_schedule.py.)"""
     w = workloads.zipf_rows(700, 3000, 260, seed=17, row_max=2500)
     _say(f"skewed rows, p = 38, nnz={w.nnz}")
     err, A, c1 = _check_product(w, 38, binding.VARIANT_REG)
