@@ -63,13 +63,16 @@ typedef struct gcoo_matrix gcoo_matrix;
 
 /*
  * Group height to use when the caller has no better idea (the paper leaves p to a tuner, Section 5).
+ * The automatic product works on the entries in row order or on the band schedule, neither of which is cut by groups: for it the height
+ * decides the order of the five arrays and, slightly, the time of the conversion.  The heights are the best ones of the kernels that
+ * gcoo_set_share_policy() brings back:
  * 32 is the tallest group the widest instance of the register kernel holds (32 rows x 4 columns
  * per lane); on MI355X it was the fastest of {4, 8, 16, 32, 64} for that kernel for uniform random
  * matrices of density 0.001 .. 0.5, for a power-law row-length matrix and for a diagonal one.
- * Where gcoo_spdm() will run the workgroup-shared kernel (GCOO_VARIANT_SHARE: N a multiple of 4,
+ * Where GCOO_VARIANT_SHARE can be asked for (N a multiple of 4,
  * density at most 6 %, and at least 1.5 % from 3500 columns on, 0.8 % from 5500, 0.35 % from 7000; never while
  * the policy is GCOO_SHARE_NEVER), a height between
- * 24 and 48 is returned that makes the workgroups of that kernel (one per 8p rows x 256 columns of C)
+ * 24 and 48 is returned that makes the workgroups of the workgroup-shared kernel (one per 8p rows x 256 columns of C)
  * fill whole rounds over the 256 compute units: the p that minimises
  * ceil(workgroups / 256) x (p + 24).
  * 38, the tallest group the register kernel holds with four columns per lane (its second
@@ -86,7 +89,7 @@ int32_t gcoo_default_p(int64_t m, int64_t k, int64_t nnz, int64_t N);
  * 3*nnz + 2*g elements, plus one sentinel), the entries in row order (2*nnz + m elements), the kernel-private
  * schedules that gcoo_set_share_policy() asks for and the scratch space the
  * conversion kernels use; for p > 64 also a second copy of the matrix regrouped at 32 rows with its
- * schedules, which is what the fast kernels multiply with (they hold at most 64 rows of partial sums).
+ * schedules, which is what all kernels but the LDS one multiply with.
  * Returns 0 for invalid arguments.  Pure host arithmetic.
  */
 size_t gcoo_device_bytes(int64_t m, int64_t k, int64_t nnz, int32_t p);
@@ -101,8 +104,8 @@ size_t gcoo_device_bytes(int64_t m, int64_t k, int64_t nnz, int32_t p);
  *                    `stream`)
  *   p             rows per group, 1..GCOO_MAX_P
  *   dev_buf       caller-owned device memory, 256-byte aligned, >= gcoo_device_bytes(m,k,nnz,p)
- * The conversion kernels (group index from row_ptr, then a stable per-group radix sort on the
- * column) run on `stream`.  With host input the call returns after the input has been copied, so the
+ * The conversion kernels (the entries put into the order of the groups by column masks or by a stable radix sort, a copy
+ * of them in row order, the schedules) run on `stream`.  With host input the call returns after the input has been copied, so the
  * caller may change or release its arrays; the kernels may still be running.  An input of up to 4 MB is copied
  * to one of four pinned buffers of the library and the call waits for the device only while all four are in
  * use; a larger one is copied to the device, which synchronises `stream`.  A stream that is being captured is
@@ -132,7 +135,7 @@ int gcoo_from_csr_device(int64_t m, int64_t k, int64_t nnz,
  * gcoo_from_csr_device() for callers that may not allocate device memory beyond what they hand over as
  * output - code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  out_buf
  * (256-byte aligned, >= gcoo_static_handle_bytes(m, k, nnz, p)) receives only what the handle keeps:
- * the five arrays, the statistics and the schedules.  What the conversion needs beyond that (the second
+ * the five arrays, the entries in row order, the statistics and the schedules.  What the conversion needs beyond that (the second
  * buffer of the radix sort, 12 bytes per stored entry, and a counter) is a fixed array inside the
  * library, 24 MiB + 256 bytes per device, held until the process ends; hence the limit
  *   nnz <= GCOO_STATIC_MAX_NNZ, else GCOO_ELIMIT (gcoo_static_handle_bytes() then returns 0).
@@ -203,15 +206,15 @@ int gcoo_spdm(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
 #define GCOO_VARIANT_AUTO 0
 #define GCOO_VARIANT_LDS  1  /* partial sums in LDS, reads the five arrays directly; any p, any alignment */
 /* partial sums in VGPRs: the kernel that reads the run schedule where the conversion built one (any policy but
- * GCOO_SHARE_AUTO), else the one that works row by row; needs N >= 4 (p <= 38 and p > 64) or N >= 2 (39 <= p <= 64), else
+ * GCOO_SHARE_AUTO), else the one that works row by row; needs N >= 2 and ldb < 2^30, else
  * GCOO_EINVAL.  A matrix of groups taller than
  * 64 rows is multiplied through a second, kernel-private copy regrouped at 32 rows that the conversion keeps
- * behind the five arrays (gcoo_device_bytes() counts it); GCOO_VARIANT_SHARE works on that copy too.  Any N, ldb, ldc and base
+ * behind the five arrays (gcoo_device_bytes() counts it); GCOO_VARIANT_SHARE works on that copy too.  Any ldc and base
  * addresses; no access leaves the first N columns of a row */
 #define GCOO_VARIANT_REG  2
 /* the waves of a workgroup share the rows of B: each row of B that any of them needs is fetched once into LDS, and every
  * multiply-add takes its B values from there.  Reads the share schedule where the conversion built one (GCOO_SHARE_ALWAYS), else the
- * band schedule; needs p <= 48, B, C, ldb, ldc, N
+ * band schedule; needs p <= 48 or p > 64, B, C, ldb, ldc, N
  * multiples of 4 elements (16-byte aligned rows) and k * ldb * 4 < 2^32 - 4096, else GCOO_EINVAL */
 #define GCOO_VARIANT_SHARE 3
 int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
@@ -257,7 +260,7 @@ int gcoo_export(const gcoo_matrix* A, float* values, int32_t* rows, int32_t* col
  * GCOO_SHARE_AUTO: the band schedule (unless the rows turn out uneven, which the device finds and acts on) where a product with a B as
  *   wide as A gains by it, and for p <= 48, density at most 6 %, and
  *   at least 1.5 % from 3500 columns on, 0.8 % from 5500, 0.35 % from 7000 (at most 262144 columns): there
- *   GCOO_VARIANT_SHARE can be asked for;
+ *   GCOO_VARIANT_SHARE can be asked for (it reads the share schedule, built for it, where the matrix has too few rows for a band schedule);
  * GCOO_SHARE_ALWAYS: also the run schedule that GCOO_VARIANT_REG then reads, and the share schedule that GCOO_VARIANT_SHARE then
  *   reads, whenever that kernel could run (p <= 48, at most 262144 columns, nnz > 0); for tuning and tests;
  * GCOO_SHARE_NEVER: the run schedule only; gcoo_spdm() has the register kernel and the row-by-row kernel to choose from.

@@ -230,8 +230,8 @@ bool csr_in_bounds(const int32_t* row_ptr, int64_t m, const int32_t* col_idx, in
 }
 
 // Scratch of gcoo_from_csr_device_static(), the conversion for callers that may not allocate device
-// memory: the second buffer of the per-group radix sort (3 arrays of nnz words) and the counter from
-// which the share schedule's streams take their place.  One copy per device, held until the process
+// memory: the second buffer of the per-group radix sort (3 arrays of nnz words), which also holds the column bitmaps of the band
+// schedule, and the counter from which the lists of a schedule take their place.  One copy per device, held until the process
 // ends.  Host code never uses the array's name as an address: static_scratch() asks the runtime for
 // the address on the current device, once per device, and everything goes through that pointer.
 constexpr int64_t kStaticMaxNnz = 2 * 1024 * 1024;
@@ -311,17 +311,10 @@ int dense_vec_width(const float* A, int64_t lda, int64_t k)
     return (k % 4 == 0 && lda % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0) ? 4 : 1;
 }
 
-// The share schedule costs conversion time (0.04 ms at 320 000 entries) and memory, so it is built only where
-// the workgroup-shared kernel is the one gcoo_spdm() will pick.  Measured on MI355X with uniform random square
-// matrices (n = 4000 .. 14000, density 0.1 % .. 10 %, N = n), against the register kernel at its best group height:
-// the workgroup-shared kernel wins from 3500 columns on at 0.8 % density or more (n = 8000: by 10 .. 30 % between
-// 1 % and 5 %; n = 4000, 2 %: 12 %) and from 9000 columns on already at 0.4 % (n = 10000, 0.5 %: 1.0 against 1.23 ms; n = 14000: 1.7 .. 2.3x between 0.5 %
-// and 2 %); at n = 8000 and 0.5 % the two kernels are level and the schedule's cost decides for the register
-// kernel.  The B tile of a column tile then no longer stays in L2 between the groups that need it, and what
-// the register kernel pays per run (a 1 KB segment through the vector cache) costs more than the per-band steps
-// of the workgroup-shared kernel.  Above 6 % the register kernel, which reuses a fetched segment along runs of
-// up to eight entries, is ahead (10 %: 2.9 against 3.2 ms at n = 8000); at 0.1 % and at n <= 3000 too.
-// gcoo_set_share_policy() overrides the choice.
+// Which schedules a conversion builds.  The automatic product runs the sixteen-wave kernel on the band schedule or works row by row,
+// whichever band_time() and rows_time() below expect to be the faster; under GCOO_SHARE_AUTO a conversion builds the band schedule at most
+// (and see share_schedule_wanted()).  The run schedule and the share schedule, and with them the register kernel and the workgroup-shared one, are reached
+// through gcoo_set_share_policy() only.
 std::atomic<int> g_share_policy{GCOO_SHARE_AUTO};
 // A conversion lays its buffer out more than once (size check, handle, inner handle): it reads the policy once, when
 // it starts, and every layout of that call uses that value, whatever another thread sets meanwhile.
@@ -338,18 +331,17 @@ bool share_schedule_possible(int64_t m, int64_t k, int64_t nnz, int32_t p)
     return p <= gcoo::kShareMaxP && k <= gcoo::kShareMaxK && nnz > 0 && m > 0 && k > 0;
 }
 
-// (density and shape only: also the rule by which gcoo_default_p() picks a height for that kernel)
+// The shapes for which GCOO_VARIANT_SHARE can be asked for under the automatic policy, and for which gcoo_default_p() returns a height for the
+// workgroup-shared kernel; density and shape only.  The lines lie where the workgroup-shared kernel overtook the register kernel; they are kept as a promise to
+// callers, the automatic product does not go by them.
 bool share_shape_preferred(int64_t m, int64_t k, int64_t nnz)
 {
     if (m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kShareMaxK) return false;
     const double density = (double)nnz / ((double)m * (double)k);
     if (density > 0.06) return false;
-    // Whole steps (conversion + product) measured on uniform random square matrices, n = 2000 .. 14000: the wider A, the
+    // Whole steps (conversion + product) of those two kernels on uniform random square matrices, n = 2000 .. 14000: the wider A, the
     // less of a column tile of B stays in an XCD's L2 between the groups that read it, and the sooner fetching each
-    // row once per 8 groups pays for the second schedule that the conversion then builds.
-    // (From 9000 columns on it is ahead down to 0.05 % - 8 to 16 % of the step at n = 10000 .. 14000 - but a conversion
-    // sees neither the width of B nor how even the rows are, and a second schedule built for nothing costs a matrix
-    // with few long rows a third of its step: the limit stays where the gain is large.)
+    // row once per 8 groups pays for a second schedule (n = 8000, 0.5 %: 0.43 against 0.49 ms; n = 10000, 0.5 %: 1.0 against 1.23).
     if (k >= 7000) return density >= 0.0035;
     if (k >= 5500) return density >= 0.008;
     return k >= 3500 && density >= 0.015;
@@ -362,7 +354,9 @@ bool share_kernel_preferred(int64_t m, int64_t k, int64_t nnz, int32_t p)
 
 int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p);
 
-// The share schedule itself is built on request, and for a matrix of the automatic rule that is too small for a band schedule.
+// The share schedule itself is built on request, and for a matrix of the rule above whose bitmaps do not fit the scratch that band_schedule_h()
+// has for them: one of fewer than about 1 / (6 density) rows, 48 at 0.35 %.  No automatic product reads it there; GCOO_VARIANT_SHARE,
+// which the rule promises, does.
 bool share_schedule_wanted(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     const int policy = share_policy_now();
@@ -388,7 +382,7 @@ int64_t share_items(int64_t m, int32_t p, int64_t N)
     return gcoo::share_super_groups(g) * ((N + 255) / 256);
 }
 
-// Group height for the workgroup-shared kernel: taller groups mean fewer rows of B fetched per
+// Group height for the workgroup-shared kernel (the sixteen-wave kernel cuts the rows by itself, band_schedule_h()): taller groups mean fewer rows of B fetched per
 // multiply-add, but the workgroups must fill their rounds over the compute units.  The time of a launch goes
 // like rounds x (time of a workgroup), and the time of a workgroup like p plus a part that does not depend
 // on p (the per-band steps); measured best heights: 42 at 8000 x 8000 (768 workgroups = 3 rounds), 48 at
@@ -647,9 +641,6 @@ int new_handle(int64_t m, int64_t k, int64_t nnz, int32_t p, void* dev_buf, gcoo
     return GCOO_OK;
 }
 
-// The kernel-private schedules that a conversion ends with: the run schedule of the register kernel
-// (every matrix of at most 64 rows per group) and, where wanted, the share schedule.  Both are built
-// here, on the conversion's stream, so that the handle is never written again.
 // share_fill may ask for more dynamic LDS than a kernel gets by default: raised once per device (a compute unit
 // has 160 KB; the kernel's static variables take a little of it).
 constexpr int kShareFillMaxLds = 156 * 1024;
@@ -682,7 +673,9 @@ hipError_t band_fill_lds_limit()
     return e;
 }
 
-// `scratch`: the conversion's scratch area (the counter of share_fill sits in it).  `marked`: the bitmaps of the band schedule are there, and
+// The kernel-private schedules that a conversion ends with (see share_schedule_wanted(), run_schedule_wanted() and band_schedule_h()), on the
+// conversion's stream, so that the handle is never written again.
+// `scratch`: the conversion's scratch area (the counter of share_fill and band_fill sits in it).  `marked`: the bitmaps of the band schedule are there, and
 // the counter is zero.
 int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false)
 {
@@ -772,10 +765,10 @@ int32_t gcoo_default_p(int64_t m, int64_t k, int64_t nnz, int64_t N)
         const int64_t items = share_items(m, p, N);
         if (items >= 192 && (k >= 9000 || fill_of_rounds(items) >= 0.8)) return p;
     }
-    // Between 6 % and 12 % density most groups touch most columns, and what the register kernel
-    // fetches falls with the number of groups: 38 rows (the tall accumulator file) beat 32 by
-    // 8 .. 28 % from 6000 columns on (whole steps, n = 6000 .. 14000, s = 0.9 and 0.93); at 20 % and
-    // more, and at n = 4000, the two are within a few per cent either way.
+    // The tall accumulator file of the register kernel (it needs a run schedule; the automatic product does not depend on the height).  Between 6 % and
+    // 12 % density most groups touch most columns, and what that kernel fetches falls with the number of groups: 38 rows beat 32 by
+    // 8 .. 28 % from 6000 columns on (n = 6000 .. 14000, s = 0.9 and 0.93); at 20 % and more, and at n = 4000, the two are within a few
+    // per cent either way.
     if (m > 0 && k >= 5000 && N % 4 == 0) {
         const double density = (double)nnz / ((double)m * (double)k);
         if (density > 0.06 && density <= 0.12) return 38;
@@ -1236,7 +1229,7 @@ int sched_width(int32_t p, const Shape& sh)
     if (p <= 64 && sh.N >= 2) return 2;
     // There is no one-column-per-lane instance (65 <= p <= 128, or N = 1): a run of one on an 8000 x 8000
     // matrix with p = 128 ended in a GPU memory fault whose cause was never found, and it was taken out of
-    // the build.  Such calls get the LDS kernel (automatic choice) or GCOO_EINVAL (explicit GCOO_VARIANT_REG).
+    // the build.  Such calls are multiplied row by row (automatic choice) or get GCOO_EINVAL (explicit GCOO_VARIANT_REG).
     return 0;
 }
 
@@ -1294,7 +1287,7 @@ int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_
     if (A->inner) A = A->inner;        // groups taller than 64 rows: the fast kernels run on the regrouped copy
     const Shape sh = shape_of(B_dev, ldb, N, C_dev, ldc);
     // the workgroup-shared kernel wants enough workgroups to occupy the chip (one per 8p rows and 256 columns),
-    // and below 9000 columns its margin does not survive a last round that is mostly idle
+    // and below 9000 columns its margin over the register kernel does not survive a last round that is mostly idle
     const int64_t items = A->share_nq() * ((N + 255) / 256);
     if (A->share_preferred && share_operands_ok(A, sh, ldb) && items >= 192 && (A->k >= 9000 || fill_of_rounds(items) >= 0.8))
         return GCOO_VARIANT_SHARE;

@@ -4,7 +4,7 @@
 // column (at most p bits), the place of an entry is what the columns before it hold, a prefix sum of popcounts, plus the
 // popcount of the mask below its row: two passes over the entries with a few LDS accesses each, no ranking, any order inside the rows.
 // The radix sort (gcoo_build_kernels.hpp) moves every entry through memory once per digit and walks it in tiles of 64
-// with eight ballots each; it stays for matrices whose columns far outnumber the entries of a group (order_by_masks()).
+// with eight ballots each; it stays for matrices whose columns far outnumber the entries of a group (order_plan() in gcoo_api.hip).
 //
 // A workgroup orders one part of a group: `ncols` columns.  Where the columns of every row ascend, which take_rows checks, a part is
 // one stretch of each row, and take_rows has noted where it begins; otherwise the workgroup looks through the whole group.

@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 
     BandAcc acc;
     uint32_t l16 = (threadIdx.x & 63u) * 16u;
-    uint32_t fillw = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (kBandRows / kBandWaves * 1024u);       // the wave's three rows inside a band buffer
+    uint32_t fillw = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (kBandRows / kBandWaves * 1024u);       // the wave's five rows inside a band buffer
     const int32_t nb = (__builtin_amdgcn_readfirstlane(a.count[Q]) + kBandRows - 1) / kBandRows;
     {
         const int64_t list = (int64_t)Q * kBandWaves + fillw / (kBandRows / kBandWaves * 1024u);

@@ -1,4 +1,4 @@
-// Host-side launch interface of the register SpDM kernel.  Each V (columns per lane) is compiled
+// Host-side launch interface of the SpDM kernels.  Each V (columns per lane) of the register kernel is compiled
 // in a translation unit of its own (spdm_sched_v*.hip) so that the instances build in parallel.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -33,7 +33,7 @@ struct SpdmArgs {
 };
 
 // V = 4 needs p <= 32, V = 38 (four columns per lane, tall accumulator file) p <= 38, V = 2 needs
-// p <= 64; N, ldb, ldc and both base addresses must be multiples of the columns per lane.
+// p <= 64; N at least the columns per lane, ldb < 2^30, any alignment of 4 bytes.
 // Anything else returns hipErrorInvalidValue.
 hipError_t launch_spdm_sched(int V, const SpdmArgs& a, hipStream_t s);
 

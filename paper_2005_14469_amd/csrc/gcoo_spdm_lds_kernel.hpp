@@ -11,7 +11,7 @@ namespace gcoo {
 // ---------------------------------------------------------------------------------------------
 // Variant LDS: the p x 64 partial sums of a wave live in LDS (one column per lane, so no bank
 // conflicts and no cross-lane hazards).  Works for every p <= 256, every N and leading
-// dimension.  The fallback for shapes the register kernels do not take.
+// dimension.  The automatic choice where a row pitch of B does not fit 32 bits and for a matrix without columns; else on request.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void spdm_lds(const float* __restrict__ values, const int32_t* __restrict__ rows,
                                                const int32_t* __restrict__ cols, const int32_t* __restrict__ gIdxes,

@@ -54,6 +54,7 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // stretches of B and C count for more than the L2 while C is wide (us with 16, 32, 64 lanes; 12000 x 12000, rows of 1, 3, 5, 9 entries:
     // 339 277 249, 373 328 311, 398 364 374, 446 440 568; 14000 rows, N = 2000, of 3, 5, 7: 80 71 69, 86 79 85, 93 94 108; N = 501, of 3: 22 28 30;
     // 3000 x 3000, of 3: 22 21 25).
+    // Where between two points of these sweeps a line lies is a choice, not derived from anything.
     const bool lines = a.ldb % 32 == 0 && reinterpret_cast<uintptr_t>(a.B) % 128 == 0;
     if (a.N >= 1500 && a.nnz <= 4 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
     if (a.N > 64 && (a.k <= (lines ? 4096 : 6500) || (a.N >= 1500 && a.nnz <= (a.N >= 6000 ? 9 : 6) * a.m))) return launch_rows<32>(a, s);
