@@ -26,8 +26,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-KERNEL_NAMES = {1: "gcoo::spdm_lds", 2: "gcoo::spdm_sched", 3: "gcoo::spdm_share"}
-KERNEL_FILES = {1: "spdm_lds", 2: "spdm_sched", 3: "spdm_share"}
+KERNEL_NAMES = {1: "spdm_lds", 2: "spdm_sched", 3: "spdm_share", 4: "spdm_rows", 5: "spdm_band"}      # by GCOO_KERNEL_*
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TF = 157.3    # published (packed fp32); plain v_fma_f32 reaches half of it
 
@@ -41,10 +40,12 @@ def parse():
                     help="config0..config4 (the five named workloads; config3 = 8000^2, sparsity 0.995), or "
                          "uniform_<n>_<sparsity> for a square uniform random A with N = n")
     ap.add_argument("--p", type=int, default=0, help="group height; 0 = library default for the workload")
-    ap.add_argument("--variant", type=int, default=0, help="0 auto, 1 partial sums in LDS, 2 partial sums in registers, 3 the same with the rows of B shared through LDS by the eight groups of a workgroup")
+    ap.add_argument("--variant", type=int, default=0, help="0 automatic, 1 partial sums in LDS, 2 partial sums in registers (the register kernel where there is a run schedule, else row "
+                         "by row), 3 the rows of B shared through LDS (the workgroup-shared kernel where there is a share schedule, else the "
+                         "sixteen-wave kernel)")
     ap.add_argument("--share", choices=["auto", "always", "never"], default="auto",
-                    help="when the conversion also builds the schedule of variant 3: where the library expects that kernel to be "
-                         "picked (auto), wherever it can run (always: needed to force --variant 3 elsewhere), or never")
+                    help="the schedules a conversion builds: the band schedule where it pays (auto), also the run schedule and the share schedule "
+                         "(always: variants 2 and 3 then run the register kernel and the workgroup-shared kernel), or the run schedule only (never)")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle timing")
     ap.add_argument("--no-dense", action="store_true", help="skip the dense SGEMM timing")
     ap.add_argument("--secondary", default="config2", help="second workload reported in the same line ('' = none)")
@@ -59,9 +60,9 @@ def parse():
                     help="instead of the headline run: dense A on the device -> GCOO (Algorithm 1) -> SpDM at n = 4000 and "
                          "14000, sparsity 0.95..0.99: the split of Section 4.3 into extra overhead (conversion) and kernel")
     ap.add_argument("--kernels", action="store_true",
-                    help="instead of the headline run: the register kernel (p = 32, 38) against the workgroup-shared kernel "
-                         "(p = 32, 42, 48) on uniform random square matrices, kernel and conversion times: the grid behind "
-                         "the library's choice between the two")
+                    help="instead of the headline run: the row-by-row kernel and the sixteen-wave kernel, which the automatic choice is between, against "
+                         "the register kernel (p = 32, 38) and the workgroup-shared kernel (p = 32, 42, 48) on uniform random square matrices, "
+                         "kernel and conversion times")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a plain 256 MiB device copy a few times: the reference launch against which the "
                          "FETCH_SIZE / WRITE_SIZE counters of rocprofv3 --pmc are scaled")
@@ -122,11 +123,11 @@ def time_path(torch, binding, w, dev, p, variant, steps, warmup):
     conv = [e[0].elapsed_time(e[1]) for e in ev.values()]
     mult = [e[1].elapsed_time(e[2]) for e in ev.values()]
     h = convert()
-    picked = L.gcoo_spdm_pick(h, B.data_ptr(), B.stride(0), w.N, C.data_ptr(), C.stride(0)) if variant == 0 else variant
+    kernel = L.gcoo_spdm_kernel(h, B.data_ptr(), B.stride(0), w.N, C.data_ptr(), C.stride(0), variant)
     L.gcoo_free(h)
     torch.cuda.synchronize()
     return dict(ms_per_step=(t1 - t0) * 1e3 / steps, convert_ms=sum(conv) / len(conv), spdm_ms=sum(mult) / len(mult),
-                spdm_ms_min=min(mult), variant=int(picked), B=B, C=C)
+                spdm_ms_min=min(mult), kernel=KERNEL_NAMES[kernel], B=B, C=C)
 
 
 def dense_ms(torch, w, dev, reps=5):
@@ -202,7 +203,7 @@ def run_one(torch, binding, workloads, name, args, dev, steps, warmup):
     flops = 2.0 * w.nnz * w.N
     alg_bytes = 12.0 * w.nnz + 4.0 * w.k * w.N + 4.0 * w.m * w.N
     out = dict(
-        workload=name, m=w.m, k=w.k, N=w.N, nnz=w.nnz, p=p, variant=r["variant"],
+        workload=name, m=w.m, k=w.k, N=w.N, nnz=w.nnz, p=p, kernel=r["kernel"],
         ms_per_step=r["ms_per_step"], gflops=flops / r["ms_per_step"] / 1e6,
         convert_ms=r["convert_ms"], spdm_ms=r["spdm_ms"], spdm_ms_min=r["spdm_ms_min"],
         spdm_gflops=flops / r["spdm_ms"] / 1e6,
@@ -224,7 +225,7 @@ def crossover(torch, binding, workloads, args, dev, n=8000):
         r = time_path(torch, binding, w, dev, p, args.variant, 5, 2)
         if dense is None:
             dense = dense_ms(torch, w, dev)
-        rows.append(dict(sparsity=s, nnz=w.nnz, p=p, variant=r["variant"], spdm_ms=r["spdm_ms"], convert_ms=r["convert_ms"],
+        rows.append(dict(sparsity=s, nnz=w.nnz, p=p, kernel=r["kernel"], spdm_ms=r["spdm_ms"], convert_ms=r["convert_ms"],
                          step_ms=r["ms_per_step"],
                          spdm_gflops=2.0 * w.nnz * n / r["spdm_ms"] / 1e6))
         del w, r
@@ -336,12 +337,18 @@ def sweep(torch, binding, workloads, args, dev):
 
 
 def kernels_compared(torch, binding, workloads, args, dev):
-    """Register kernel against workgroup-shared kernel on the same matrices (uniform random, N = n)."""
+    """The four kernels on the same matrices (uniform random, N = n), each with the conversion that it needs."""
     rows = []
     plan = [(4000, 0.98), (4000, 0.995), (8000, 0.9), (8000, 0.95), (8000, 0.98), (8000, 0.99), (8000, 0.995), (8000, 0.999),
             (14000, 0.98), (14000, 0.995)]
+    # name, policy of the conversion, variant, p, kernel it has to be
+    runs = [("rows", binding.SHARE_AUTO, binding.VARIANT_REG, 32, "spdm_rows"), ("band", binding.SHARE_AUTO, binding.VARIANT_SHARE, 32, "spdm_band"),
+            ("auto", binding.SHARE_AUTO, binding.VARIANT_AUTO, 32, None),
+            ("reg32", binding.SHARE_NEVER, binding.VARIANT_REG, 32, "spdm_sched"), ("reg38", binding.SHARE_NEVER, binding.VARIANT_REG, 38, "spdm_sched"),
+            ("share32", binding.SHARE_ALWAYS, binding.VARIANT_SHARE, 32, "spdm_share"),
+            ("share42", binding.SHARE_ALWAYS, binding.VARIANT_SHARE, 42, "spdm_share"),
+            ("share48", binding.SHARE_ALWAYS, binding.VARIANT_SHARE, 48, "spdm_share")]
     cur_n, Bd, Cd = None, None, None
-    binding.gcoo_set_share_policy(binding.SHARE_ALWAYS)
     try:
         for n, sp in plan:
             if n != cur_n:
@@ -354,25 +361,28 @@ def kernels_compared(torch, binding, workloads, args, dev):
             w = workloads.uniform_random(n, n, 1, sp, workloads.BASE_SEED + n + int(round(sp * 10000)), name="kernels")
             rp, ci, va = [torch.from_numpy(x).to(dev) for x in (w.row_ptr, w.col_idx, w.vals)]
             row = dict(n=n, sparsity=sp, nnz=w.nnz)
-            for name, variant, p in (("reg32", binding.VARIANT_REG, 32), ("reg38", binding.VARIANT_REG, 38),
-                                     ("share32", binding.VARIANT_SHARE, 32), ("share42", binding.VARIANT_SHARE, 42),
-                                     ("share48", binding.VARIANT_SHARE, 48)):
+            for name, policy, variant, p, kernel in runs:
                 holder = {}
+                binding.gcoo_set_share_policy(policy)
 
                 def convert():
-                    holder["A"] = binding.gcoo_from_csr(n, n, rp, ci, va, p)
+                    holder["A"] = binding.gcoo_from_csr(n, n, rp, ci, va, p, known_nnz=True)
 
                 t_conv = _event_ms(torch, convert, 3)
                 A = holder["A"]
-                row[name + "_ms"] = _event_ms(torch, lambda: binding.gcoo_spdm(A, Bd, Cd, variant=variant), 5)
-                row[name + "_convert_ms"] = t_conv      # with both schedules built (the policy above)
+                got = binding.gcoo_spdm_kernel(A, Bd, Cd, variant)
+                if got > 0 and kernel in (None, KERNEL_NAMES[got]):
+                    row[name + "_ms"] = _event_ms(torch, lambda: binding.gcoo_spdm(A, Bd, Cd, variant=variant), 5)
+                    row[name + "_convert_ms"] = t_conv
+                    if kernel is None:
+                        row["auto_kernel"] = KERNEL_NAMES[got]
                 A.free()
             print("kernels " + " ".join(f"{k}={v:.3f}" if isinstance(v, float) else f"{k}={v}" for k, v in row.items()),
                   file=sys.stderr, flush=True)
             rows.append(row)
     finally:
         binding.gcoo_set_share_policy(binding.SHARE_AUTO)
-    return {"metric": "register kernel against workgroup-shared kernel, uniform random square A, N = n, fp32, ms", "rows": rows}
+    return {"metric": "the kernels of the product on the same matrices, uniform random square A, N = n, fp32, ms", "rows": rows}
 
 
 def eo_kc(torch, binding, workloads, args, dev):
@@ -393,21 +403,19 @@ def eo_kc(torch, binding, workloads, args, dev):
             p = args.p or binding.gcoo_default_p(n, n, w.nnz, n)
 
             def convert():
-                holder["A"] = binding.gcoo_from_dense(Ad, p)      # count, size the buffer, count per block, fill, schedule
+                holder["A"] = binding.gcoo_from_dense(Ad, p)      # count per block, size the buffer, fill, row order, schedule
 
-            t_count = _event_ms(torch, lambda: binding.gcoo_dense_nnz(Ad), 5)
             t_eo = _event_ms(torch, convert, 5)
             A = holder["A"]
             t_kc = _event_ms(torch, lambda: binding.gcoo_spdm(A, B, C, variant=args.variant), 5)
             dense_bytes = 4.0 * n * n
-            rows.append(dict(n=n, sparsity=s, nnz=w.nnz, p=p, count_ms=t_count, eo_ms=t_eo, kc_ms=t_kc,
-                             eo_share=t_eo / (t_eo + t_kc),
-                             eo_gbs=(3 * dense_bytes + 12.0 * w.nnz) / t_eo / 1e6))
+            rows.append(dict(n=n, sparsity=s, nnz=w.nnz, p=p, eo_ms=t_eo, kc_ms=t_kc, eo_share=t_eo / (t_eo + t_kc),
+                             eo_gbs=(2 * dense_bytes + 12.0 * w.nnz) / t_eo / 1e6))
             A.free()
             del Ad, w
         del B, C
     return {"metric": "dense -> GCOO conversion (EO) against SpDM kernel (KC), fp32, A on the device",
-            "note": "eo_ms includes the count that sizes the buffer (three reads of A in all); eo_gbs = (3*4*n*n + 12*nnz)/eo_ms",
+            "note": "eo_ms includes the count that sizes the buffer and the wait for it (two reads of A in all); eo_gbs = (2*4*n*n + 12*nnz)/eo_ms",
             "rows": rows}
 
 
@@ -449,21 +457,19 @@ def main():
         print(json.dumps(sweep(torch, binding, workloads, args, dev)))
         return
     w, head = run_one(torch, binding, workloads, args.workload, args, dev, args.steps, args.warmup)
+    traffic = read_traffic(head["kernel"], args.workload)
     line = {
         "metric": "fp32 SpDM effective GFLOP/s (2*nnz*N/t, whole path: CSR->GCOO conversion + SpDM kernel)",
         "value": head["gflops"], "unit": "GFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": head["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"{args.workload}: A {w.m}x{w.k} uniform random, nnz={w.nnz}, B {w.k}x{w.N}, fp32",
-                   "p": head["p"], "variant": head["variant"]},
+                   "p": head["p"], "variant": args.variant},
         "spdm": {"ms": head["spdm_ms"], "ms_min": head["spdm_ms_min"], "gflops": head["spdm_gflops"],
                  "convert_ms": head["convert_ms"], "frac_of_fp32_vector_peak": head["valu_frac_of_published"]},
         "roofline": {"bound": "hbm", "achieved": head["hbm_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": head["hbm_frac"], "traffic": read_traffic(KERNEL_FILES.get(head["variant"], "spdm_sched"), args.workload),
-                     "traffic_source": (traffic_file(KERNEL_FILES.get(head["variant"], "spdm_sched"), args.workload)
-                                        if read_traffic(KERNEL_FILES.get(head["variant"], "spdm_sched"), args.workload) is not None
-                                        else None),
-                     "kernel": KERNEL_NAMES.get(head["variant"], "?"), "algorithmic_bytes_per_launch": head["alg_bytes"]},
+                     "frac": head["hbm_frac"], "traffic": traffic, "traffic_source": traffic_file(head["kernel"], args.workload) if traffic else None,
+                     "kernel": "gcoo::" + head["kernel"], "algorithmic_bytes_per_launch": head["alg_bytes"]},
     }
     if not args.no_dense:
         bw = copy_bandwidth_gbs(torch, dev)
@@ -473,7 +479,7 @@ def main():
         line["dense"] = {"sgemm_ms": d, "spdm_speedup_over_dense": d / head["spdm_ms"]}
     if args.secondary and args.secondary != args.workload:
         w2, sec = run_one(torch, binding, workloads, args.secondary, args, dev, max(5, args.steps // 5), 2)
-        line["secondary"] = {k: sec[k] for k in ("workload", "nnz", "p", "variant", "ms_per_step", "gflops", "convert_ms",
+        line["secondary"] = {k: sec[k] for k in ("workload", "nnz", "p", "kernel", "ms_per_step", "gflops", "convert_ms",
                                                  "spdm_ms", "spdm_gflops", "hbm_frac", "valu_frac_of_published")}
         line["secondary"]["roofline"] = {"bound": "alu", "achieved": sec["spdm_gflops"] / 1e3, "peak": FP32_VECTOR_PEAK_TF,
                                          "unit": "TFLOP/s", "frac": sec["valu_frac_of_published"]}
