@@ -18,9 +18,13 @@
 //             tile take one each before their own rows, so that none of them starts when the others have ended
 //             (power-law rows, 16384 x 16384, 50 entries on average, N = 512: 100 us; with those of its own rows last 112)
 //
-// Bound: the vector cache (64 bytes per clock and compute unit), 4 x nnz x N bytes; a tile of 64 columns of B stays in an
-// XCD's L2 up to 16384 columns of A, so each row of B comes from memory about once per tile.  Measured (product alone,
-// before = the register kernel): 12000 x 12000, 0.5 %, N = 64: 83 -> 11.4 us; 1777 x 2301, 3 %, N = 1117: 80 -> 30; 2500 x 2500,
+// Bound, by the counters: 4 x nnz x N bytes have to come from L2 through the vector caches, which take 64 bytes per clock and compute unit (39 TB/s) at
+// the most.  Where the tile of B that an XCD works on stays in its L2 the kernel gets 17 to 23 TB/s of that: 22.7 at 1777 x 2301, 3 %, N = 1117
+// (94 % of the requests hit), 17.4 at 12000 x 12000, 0.5 %, N = 64.  Where it does not, what the L2 has to fetch counts as well: power-law rows,
+// 16384 x 16384, N = 512, whose tile of 64 columns is all of an XCD's 4 MB, take 0.32 GB from behind the L2 for a B of 34 MB (17.6 TB/s from L2);
+// 12001 x 12001 with 6 entries per row 2.5 GB for a B of 0.58 GB, which with C is 7.0 TB/s between the L2s and memory where a large copy reaches 5.2:
+// there the bound lies behind the L2.
+// Measured (product alone, before = the register kernel): 12000 x 12000, 0.5 %, N = 64: 83 -> 11.4 us; 1777 x 2301, 3 %, N = 1117: 80 -> 30; 2500 x 2500,
 // 1 %, N = 1024: 38 -> 13.7; 256 x 256, 10 %, N = 256: 35 -> 4.7; 4000 x 4000, 2 %, N = 4000: 25 TB/s through the vector cache.
 #pragma once
 #include <hip/hip_runtime.h>
