@@ -88,47 +88,17 @@ __device__ __forceinline__ float share_acc_get(const ShareAcc& a, int reg)
 #define SH_DPP(i) " row_newbcast:" #i " row_mask:0xf bank_mask:0xf\n\t"
 #define SH_ADDR(dst, src, i) "v_add_u32_dpp " #dst ", " #src ", v48" SH_DPP(i)
 #define SH_ROWS(reg, i) "v_readlane_b32 " #reg ", v41, " #i "\n\t"
-// Timing ablations (GCOO_SHARE_ABLATE, a set of bits): the kernel with one of its parts taken out, to see what that
-// part costs.  Such a build computes WRONG products; every address it forms is one the whole kernel forms too.
-// Only the micro-benchmark builds them, into libraries of their own; libgcoo.so is always built with 0.
-//   1 no row of B is requested (the bands in LDS hold whatever was there)      2 no multiply-adds, no index mode
-//   4 no barrier between bands      8 the singles read no B values from LDS    16 the wait in front of the barrier
-//   leaves the rows of two bands in flight instead of one
-#ifndef GCOO_SHARE_ABLATE
-#define GCOO_SHARE_ABLATE 0
-#endif
-#if GCOO_SHARE_ABLATE & 1
-#define SH_FILL_LOAD(off) ""
-#else
 #define SH_FILL_LOAD(off) "global_load_lds_dwordx4 v50, %[bt] offset:" #off "\n\t"
-#endif
-#if GCOO_SHARE_ABLATE & 4
-#define SH_BAND_BARRIER ""
-#else
 #define SH_BAND_BARRIER "s_barrier\n\t"
-#endif
-#if GCOO_SHARE_ABLATE & 8
-#define SH_GROUP_READS(x) ""
-#else
-#define SH_GROUP_READS(x) x
-#endif
-#if GCOO_SHARE_ABLATE & 16
-#define SH_WAIT_FILLS "s_waitcnt vmcnt(12)\n\t"
-#else
 #define SH_WAIT_FILLS "s_waitcnt vmcnt(6)\n\t"
-#endif
 // one entry: record i of this block, its row in the low byte of `rows`, its B values in b0..b3
 // (SH_FMACL: the last entry of its group of four, after which the packed rows are not needed any more)
-#if GCOO_SHARE_ABLATE & 2
-#define SH_FMACL(i, rows, b0, b1, b2, b3) ""
-#else
 #define SH_FMACL(i, rows, b0, b1, b2, b3)                   \
     "s_set_gpr_idx_on " #rows ", gpr_idx(SRC2,DST)\n\t"      \
     "v_fmac_f32_dpp v60, v40, " #b0 SH_DPP(i)                \
     "v_fmac_f32_dpp v109, v40, " #b1 SH_DPP(i)               \
     "v_fmac_f32_dpp v158, v40, " #b2 SH_DPP(i)               \
     "v_fmac_f32_dpp v207, v40, " #b3 SH_DPP(i)
-#endif
 #define SH_FMAC(i, rows, b0, b1, b2, b3) SH_FMACL(i, rows, b0, b1, b2, b3) "s_lshr_b32 " #rows ", " #rows ", 8\n\t"
 #define SH_FMAC_SET0(i, rows) SH_FMAC(i, rows, v20, v21, v22, v23)
 #define SH_FMAC_SET1(i, rows) SH_FMAC(i, rows, v24, v25, v26, v27)
@@ -407,7 +377,7 @@ __global__ __launch_bounds__(64 * kShareW) void spdm_share(ShareArgs a, int64_t 
 #define SH_GROUP(src, n0, n1, n2, n3, R0, R1, R2, R3, nextrows, F0, F1, F2, F3)           \
             "s_sub_u32 s73, s73, 1\n\t"                                               \
             "s_cbranch_scc1 .Lsh_send_%=\n\t"                                         \
-            SH_GROUP_READS(SH_ADDR(v36, src, n0) SH_ADDR(v37, src, n1) SH_ADDR(v38, src, n2) SH_ADDR(v39, src, n3) R0 R1 R2 R3) \
+            SH_ADDR(v36, src, n0) SH_ADDR(v37, src, n1) SH_ADDR(v38, src, n2) SH_ADDR(v39, src, n3) R0 R1 R2 R3 \
             nextrows                                                                  \
             "s_waitcnt lgkmcnt(4)\n\t"                                                \
             F0 F1 F2 F3                                                               \
