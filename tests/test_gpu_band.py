@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _run(w, p, variant, shift=0, pad=0):
+def _run(w, p, variant, shift=0, pad=0, kernel=None):
     Bbig = torch.zeros((w.k, w.N + shift + pad), device=DEV)
     Bbig[:, shift:shift + w.N] = torch.from_numpy(w.B).to(DEV)
     dev = [torch.from_numpy(x).to(DEV) for x in (w.row_ptr, w.col_idx, w.vals)]
@@ -23,6 +23,7 @@ def _run(w, p, variant, shift=0, pad=0):
         A = binding.gcoo_from_csr(w.m, w.k, *dev, p, known_nnz=True)
         Cbig = torch.full((w.m, w.N + shift + pad + 8), 7.0, device=DEV)
         Cv = Cbig[:, shift:shift + w.N]
+        assert kernel is None or binding.gcoo_spdm_kernel(A, Bbig[:, shift:shift + w.N], Cv, variant) == kernel
         binding.gcoo_spdm(A, Bbig[:, shift:shift + w.N], Cv, variant=variant)
         torch.cuda.synchronize()
         assert torch.all(Cbig[:, :shift] == 7.0) and torch.all(Cbig[:, shift + w.N:] == 7.0)
@@ -63,7 +64,8 @@ def test_uniform_through_the_share_variant(m, k, N, s):
 
 @pytest.mark.parametrize("m,k,N,s,shift,pad", [(4000, 4000, 1001, 0.95, 0, 0), (4000, 4000, 1000, 0.95, 1, 2), (3000, 3000, 2999, 0.7, 0, 0), (5000, 2600, 1280, 0.9, 0, 0)])
 def test_automatic_choice_ragged_and_dense(m, k, N, s, shift, pad):
-    """Large enough that the automatic choice is this kernel: N and rows of B that are no multiple of four, runs of pairs."""
+    """The automatic choice of a matrix that has a band schedule (for the first two the row-by-row kernel, for the last two this one): N and rows of
+    B that are no multiple of four, runs of pairs."""
     print(f"band, automatic: m={m} k={k} N={N} s={s} shift={shift}", flush=True)
     _run(workloads.uniform_random(m, k, N, s, seed=m + N), 32, binding.VARIANT_AUTO, shift, pad)
 
@@ -92,7 +94,8 @@ def test_repeated_coordinates_and_skewed_rows():
 @pytest.mark.parametrize("dense,p,N,shift", [(False, 32, 1024, 0), (False, 64, 1021, 1), (True, 32, 1024, 0), (False, 32, 260, 0)])
 def test_uneven_rows_are_multiplied_one_by_one(dense, p, N, shift):
     """A matrix that gets a band schedule by its size, with one list of rows of far more entries than the others: the launch of the
-    sixteen-wave kernel works row by row.  GCOO_VARIANT_SHARE asks for that kernel where it is served."""
+    sixteen-wave kernel works row by row.  GCOO_VARIANT_SHARE asks for that kernel where it is served; the automatic choice is the row-by-row kernel
+    for a B this narrow, and this one for those of test_automatic_choice_of_this_kernel_for_uneven_rows."""
     print(f"band: uneven rows dense={dense} p={p} N={N}", flush=True)
     rng = np.random.default_rng(N + p)
     m, k = 4000, 3600
@@ -145,6 +148,28 @@ def test_non_finite_values_beside_uneven_rows_of_a_b_of_almost_4_gb():
         print(f"band: uneven rows, B of 4.29 GB, variant={variant}", flush=True)
         err, bad = orc.max_scaled_error(binding.gcoo_spdm(A, Bd, variant=variant).cpu().numpy(), C64, D64)
         assert bad == 0 and err < 2e-6, (variant, err, bad)
+
+
+@pytest.mark.parametrize("m,k,N,s,shift,pad", [(4000, 3000, 1001, 0.9, 0, 0), (4000, 3000, 1021, 0.9, 1, 1), (4000, 4000, 2052, 0.95, 1, 2),
+                                               (4000, 4000, 2044, 0.95, 4, 4), (30000, 3600, 513, 0.95, 2, 1), (30000, 3600, 257, 0.95, 3, 2)])
+def test_automatic_choice_of_this_kernel(m, k, N, s, shift, pad):
+    """Wide enough that the automatic choice is this kernel: last tiles that begin inside the tile before, rows of B and C aligned to 4 bytes only."""
+    print(f"band, automatic: m={m} k={k} N={N} s={s} shift={shift}", flush=True)
+    w = workloads.uniform_random(m, k, N, s, seed=m + N)
+    _run(w, 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
+
+
+@pytest.mark.parametrize("p,N,shift", [(32, 2048, 0), (64, 2045, 1), (32, 2560, 4)])
+def test_automatic_choice_of_this_kernel_for_uneven_rows(p, N, shift):
+    print(f"band, automatic: uneven rows p={p} N={N} shift={shift}", flush=True)
+    rng = np.random.default_rng(N + p)
+    m, k = 4000, 3600
+    lens = rng.integers(40, 90, m)
+    lens[1000:1012] = 3000
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(k, n, replace=False)) for n in lens]).astype(np.int32)
+    w = workloads.Workload("uneven", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, N)).astype(np.float32))
+    _run(w, p, binding.VARIANT_AUTO, shift, 3, kernel=binding.KERNEL_BAND)
 
 
 def test_export_share_of_a_matrix_with_a_band_schedule():
