@@ -60,12 +60,13 @@ constexpr int kMaxDevices = 64;
 
 // A number that a kernel hands to the host in the middle of a call: the kernel writes it to pinned host memory, so that no copy
 // stands between the kernel and the host's wait for the stream.  kHostSlots such calls may be under way at once, over all devices and threads; a call takes a
-// slot for its own use and gives it back when it returns, and waits for one while all are taken.  Each slot has a word of device memory as
+// slot for its own use and gives it back when it returns, and waits for one while all are taken (fails where all are lost).  Each slot has a word of device memory as
 // well (per device, zero between calls), in which the workgroups of a kernel count themselves.  The pinned page is allocated once per process.
 constexpr int kHostSlots = 64;
 constexpr size_t kHostSlotWords = 8;
 __device__ unsigned long long g_tickets[kHostSlots];
 std::atomic<uint64_t> g_slots_taken{0};
+std::atomic<int> g_slots_lost{0};
 
 class HostSlot {
 public:
@@ -102,6 +103,7 @@ public:
         uint64_t taken = g_slots_taken.load(std::memory_order_relaxed);
         while (true) {
             if (taken == ~0ull) {
+                if (g_slots_lost.load(std::memory_order_relaxed) == kHostSlots) return hip_fail(hipErrorUnknown, "all places for a number from the device are lost");
                 std::this_thread::yield();
                 taken = g_slots_taken.load(std::memory_order_relaxed);
                 continue;
@@ -116,10 +118,15 @@ public:
     }
     unsigned long long* host() const { return host_; }
     unsigned long long* ticket() const { return ticket_; }
-    // After the launch.
+    // After the launch.  Where the wait fails nobody gets the slot again: the kernel may still write there.
     int wait(hipStream_t s, unsigned long long* answer)
     {
-        HIP_TRY(hipStreamSynchronize(s));
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) {
+            i_ = -1;
+            g_slots_lost.fetch_add(1, std::memory_order_relaxed);
+            return hip_fail(e, "wait for a number from the device");
+        }
         *answer = __atomic_load_n(host_, __ATOMIC_ACQUIRE);
         return GCOO_OK;
     }

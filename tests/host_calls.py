@@ -30,6 +30,7 @@ class Host:
         self.hip = C.CDLL(STUB, mode=C.RTLD_GLOBAL)
         self.hip.host_set.argtypes = [C.c_char_p, C.c_longlong]
         self.hip.host_log.restype = C.c_char_p
+        self.hip.host_told.restype = C.c_void_p
         self.L = C.CDLL(LIB)
         i64, i32, vp, sz = C.c_int64, C.c_int32, C.c_void_p, C.c_size_t
         for name, res, args in [
@@ -183,6 +184,28 @@ def stage_release_fails(host):
     assert _host_csr(host, *shape) == OK
     log = host.log()
     assert "record" not in log and log.count("copy") == 3 and "wait stream" in log, log
+
+
+def slot_wait_fails(host):
+    """The wait for a kernel that tells the host a number fails: nobody gets its slot again, the kernel may still write there.  With all slots lost such
+    calls fail instead of waiting for one."""
+    n = C.c_int64()
+    host.set("answer", 77)
+    host.set("hipStreamSynchronize", 1)
+    places = set()
+    for i in range(64):
+        assert host.L.gcoo_dense_nnz(30, 50, 1 << 20, 50, None, C.byref(n)) == EHIP
+        places.add(host.hip.host_told())
+        if i == 3:                                                           # the other calls go on
+            host.set("hipStreamSynchronize", 0)
+            assert host.L.gcoo_dense_nnz(30, 50, 1 << 20, 50, None, C.byref(n)) == OK and n.value == 77
+            assert host.hip.host_told() not in places
+            host.set("hipStreamSynchronize", 1)
+    assert len(places) == 64
+    host.set("hipStreamSynchronize", 0)
+    host.log()
+    assert host.L.gcoo_dense_nnz(30, 50, 1 << 20, 50, None, C.byref(n)) == EHIP
+    assert host.log() == []
 
 
 # ---- where a dense conversion waits ------------------------------------------------------------------
