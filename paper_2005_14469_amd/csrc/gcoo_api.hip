@@ -264,6 +264,9 @@ int static_scratch(unsigned char** out)
     return GCOO_OK;
 }
 
+// How the band schedule cuts a matrix: rows per wave and columns per lane (BandCut); h = 0: none is built.
+struct BandPlan { int32_t h, v; };
+
 // Carve-up of the caller's device buffer.  Offsets depend on (m, nnz, g) only.
 struct Layout {
     size_t values, rows, cols, gIdxes, nnzPerGroup;        // the five arrays of the format
@@ -271,7 +274,7 @@ struct Layout {
     size_t sched_hdr, sched;                               // run schedule of the register kernel
     size_t order;                                          // groups by falling size, then those sizes (matrices of few groups)
     size_t share_ucols, share_ucount, share_hdr, share_blocks, share_sbase, share_alloc;   // share schedule (may be empty)
-    int32_t band_h;                                        // rows per wave of the band schedule, 0: none
+    BandPlan band;                                         // the band schedule
     size_t band_head, band_units, band_first, band_count;  // band schedule
     bool by_masks;                                         // a CSR input is ordered by take_rows and order_groups, else sorted by digits
     gcoo::OrderPlan plan;
@@ -359,16 +362,16 @@ bool share_kernel_preferred(int64_t m, int64_t k, int64_t nnz, int32_t p)
     return share_schedule_possible(m, k, nnz, p) && share_shape_preferred(m, k, nnz);
 }
 
-int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p);
+BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p);
 
-// The share schedule itself is built on request, and for a matrix of the rule above whose bitmaps do not fit the scratch that band_schedule_h()
+// The share schedule itself is built on request, and for a matrix of the rule above whose bitmaps do not fit the scratch that band_plan()
 // has for them: one of fewer than about 1 / (6 density) rows, 48 at 0.35 %.  No automatic product reads it there; GCOO_VARIANT_SHARE,
 // which the rule promises, does.
 bool share_schedule_wanted(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     const int policy = share_policy_now();
     if (policy == GCOO_SHARE_NEVER || !share_schedule_possible(m, k, nnz, p)) return false;
-    return policy == GCOO_SHARE_ALWAYS || (share_kernel_preferred(m, k, nnz, p) && band_schedule_h(m, k, nnz, p) == 0);
+    return policy == GCOO_SHARE_ALWAYS || (share_kernel_preferred(m, k, nnz, p) && band_plan(m, k, nnz, p).h == 0);
 }
 
 // The run schedule is what GCOO_VARIANT_REG reads when the policy is not the automatic one.
@@ -389,7 +392,7 @@ int64_t share_items(int64_t m, int32_t p, int64_t N)
     return gcoo::share_super_groups(g) * ((N + 255) / 256);
 }
 
-// Group height for the workgroup-shared kernel (the sixteen-wave kernel cuts the rows by itself, band_schedule_h()): taller groups mean fewer rows of B fetched per
+// Group height for the workgroup-shared kernel (the sixteen-wave kernel cuts the rows by itself, band_plan()): taller groups mean fewer rows of B fetched per
 // multiply-add, but the workgroups must fill their rounds over the compute units.  The time of a launch goes
 // like rounds x (time of a workgroup), and the time of a workgroup like p plus a part that does not depend
 // on p (the per-band steps); measured best heights: 42 at 8000 x 8000 (768 workgroups = 3 rounds), 48 at
@@ -417,41 +420,58 @@ double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
     if (lines) return 6.2 + row * (taken * (1.0 + std::pow(kd / 22400.0, 1.59)) / 31.7e6 + (double)m / 12.9e6 + kd / 3.4e6);
     return 7.3 + row * (taken * (1.0 + std::pow(kd / 10700.0, 0.95)) / 32.7e6 + (double)m / 5.2e6 + kd / 6.9e6);
 }
-// Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 rows of B, the barrier, the bubble behind it; more where
-// they are fetched in four-byte pieces) and 2.56 ns per entry of the block; C and B once, and more for both when they do not fit the
-// memory-side cache.
-double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, int32_t h, bool aligned)
+// Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 KB of B, the barrier, the bubble behind it; more where
+// they are fetched in four-byte pieces) and 2.56 ns per entry of the block, 1.77 in the tall cut, whose tiles are half as wide; C and B once, and
+// more for both when they do not fit the memory-side cache.  The tall cut (fitted to 140 measurements like those of the two others, 2000 to 14000 rows
+// and columns, 0.05 to 2 % dense, N = 300 to 14000; mean error 4 to 7 %) is bound by what it fetches, which the compute units share, rather than by its last round: that
+// counts in full for one round and less the more there are.
+double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bool aligned)
 {
-    const int64_t blocks = gcoo::band_blocks(m, h), rounds = (blocks * ((N + 255) / 256) + 255) / 256;
-    const double entries = (double)nnz / (double)blocks;
-    const double columns = (double)k * -std::expm1(-entries / (double)k);                // distinct ones of a block
+    const int64_t blocks = gcoo::band_blocks(m, plan.h), tile = 64 * plan.v, tiles = (N + tile - 1) / tile, rounds = (blocks * tiles + 255) / 256;
     const double row = 4.0 * (double)N, big = ((double)k * (double)N - 4e7) / 6e7, outside = big < 0.0 ? 0.0 : (big > 1.0 ? 1.0 : big);
-    const double bands = std::ceil(columns / gcoo::kBandRows), md = (double)m, kd = (double)k;
-    if (aligned) return 6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6);
-    return 7.4 + (double)rounds * (1.08 * bands + 0.00255 * entries) + row * (md / 3.8e6 + kd / 17.8e6 + outside * (md + kd) / 14.6e6);
+    const double md = (double)m, kd = (double)k, block_rows = (double)(gcoo::kBandWaves * plan.h);
+    const double entries = plan.v == 4 || md < block_rows ? (double)nnz / (double)blocks : (double)nnz / md * block_rows;       // of a full block
+    const double bands = std::ceil(kd * -std::expm1(-entries / kd) / gcoo::band_rows_of(plan.v));                  // distinct columns of a block
+    if (plan.v == 4) {
+        if (aligned) return 6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6);
+        return 7.4 + (double)rounds * (1.08 * bands + 0.00255 * entries) + row * (md / 3.8e6 + kd / 17.8e6 + outside * (md + kd) / 14.6e6);
+    }
+    const double full = md / block_rows * (double)tiles / 256.0, turns = full + ((double)rounds - full) * (rounds > 1 ? 1.2 / (double)rounds : 1.0);
+    if (aligned) return 6.2 + turns * (0.722 * bands + 0.00177 * entries) + row * (md / 3.76e6 + outside * (md + kd) / 9.8e6);
+    return 10.2 + turns * (0.771 * bands + 0.00234 * entries) + row * (md / 3.1e6 + outside * (md + kd) / 9.6e6);
 }
 
-// Rows per wave of the band schedule, 0 where none is built.  The width of B is not known here: the blocks are cut so that a
+// The band schedule of a matrix, if it gets one.  The width of B is not known here: the blocks are cut so that a
 // product with N = k is fastest, and the schedule is built where that product gains more by it than a conversion
 // pays for it (12 us), or where GCOO_VARIANT_SHARE has to be served.
-int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p)
+// The tall cut fetches half as much and has half as many barriers, but reads LDS eight bytes at a time, which takes as long as sixteen.  It is
+// taken where its expected time is clearly the shorter one and a (wave, band) has no more than 64 entries (product alone, us, wide and tall; 8000 x
+// 8000, 0.35 %: 298 286, 0.5 %: 336 300, 1 %: 437 453, 2 %: 638 739; 12000 x 12000, 0.2 %: 813 670, 0.5 %: 1152 876, 1 %: 1474 1362; 4000 x 4000,
+// 0.5 %: 59 51, 2 %: 103 109; 14001 x 14001, 0.5 %: 2162 1795; 14000 x 14000, 0.3 %, N = 500: 92 64; over 100 such shapes 10 % less than with the
+// wide cut alone, 4 % more at the worst).
+BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
-    if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return 0;
+    if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return {0, 0};
     const bool asked = share_kernel_preferred(m, k, nnz, p);
     const bool lines = k % 32 == 0, aligned = k % 4 == 0;
-    if (!asked && rows_time(m, k, nnz, k, lines) < 30.0) return 0;
+    if (!asked && rows_time(m, k, nnz, k, lines) < 30.0) return {0, 0};
     // (a conversion asks for every layout it makes: the last answer of this thread is kept)
-    static thread_local struct { int64_t m, k, nnz; bool asked; int32_t h; } last = {0, 0, 0, false, 0};
-    if (last.m == m && last.k == k && last.nnz == nnz && last.asked == asked) return last.h;
-    int32_t best = 0;
+    static thread_local struct { int64_t m, k, nnz; bool asked; BandPlan plan; } last = {0, 0, 0, false, {0, 0}};
+    if (last.m == m && last.k == k && last.nnz == nnz && last.asked == asked) return last.plan;
+    BandPlan best = {0, 0};
     double best_time = 0.0;
-    for (int32_t h = gcoo::kBandMaxH; h >= 12; --h) {
-        // the columns of every wave's rows as a bitmap, in the second sort buffer
-        if (gcoo::band_blocks(m, h) * gcoo::kBandWaves * ((k + 31) / 32) > 3 * nnz) continue;
-        const double t = band_time(m, k, nnz, k, h, aligned);
-        if (best == 0 || t < best_time) { best_time = t; best = h; }
+    for (int v : {4, 2}) {
+        if (v == 2 && (best.h == 0 || k > gcoo::kBandTallMaxK)) break;
+        for (int32_t h = 96 / v; h >= 12; --h) {
+            // the columns of every list's rows as a bitmap, in the second sort buffer
+            if (h % gcoo::band_lists_of(v) || gcoo::band_lists(m, h, v) * ((k + 31) / 32) > 3 * nnz) continue;
+            const BandPlan plan = {h, v};
+            if (v == 2 && gcoo::band_entries(m, k, nnz, h, v) > 64.0) continue;
+            const double t = band_time(m, k, nnz, k, plan, aligned), least = best.v == v ? best_time : 0.97 * best_time;
+            if (best.h == 0 || t < least) { best_time = t; best = plan; }
+        }
     }
-    if (best && !asked && best_time + 12.0 > rows_time(m, k, nnz, k, lines)) best = 0;
+    if (best.h && !asked && best_time + 12.0 > rows_time(m, k, nnz, k, lines)) best = {0, 0};
     last = {m, k, nnz, asked, best};
     return best;
 }
@@ -460,7 +480,7 @@ int32_t band_schedule_h(int64_t m, int64_t k, int64_t nnz, int32_t p)
 // columns of at most 32 rows (2048 of 64, 512 of 256: 16 KB of masks) and fewer where it would hold more than 1024 entries on
 // average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).  A part costs a workgroup its steps over all its columns, so the sort is the better one where the groups have far more columns
 // than entries (12001 x 12001, 0.05 %, 62 columns per entry: 12 us sorting, 20 this way; 16384 x 16384, power-law rows, 10: 55 and 40).
-bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, int32_t band_h, gcoo::OrderPlan* plan)
+bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, gcoo::OrderPlan* plan)
 {
     *plan = {};
     if (m <= 0 || k <= 0 || nnz <= 0) return false;
@@ -473,10 +493,10 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, int32_t band_h, gc
     if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;
     // lists of rows of take_rows: those of the band schedule, else enough workgroups for four per compute unit
     int64_t rows = (m + 1023) / 1024;
-    rows = band_h > 0 ? band_h : (rows > 64 ? 64 : rows);
+    rows = band.h > 0 ? band.h / gcoo::band_lists_of(band.v) : (rows > 64 ? 64 : rows);
     int64_t cap = mean / parts * 3 / 2 + 64;
     cap = cap < 256 ? 256 : (cap > gcoo::kOrderMaxCap ? gcoo::kOrderMaxCap : cap);
-    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), parts == 1 && band_h == 0 && !run_schedule_wanted(p)};
+    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), parts == 1 && band.h == 0 && !run_schedule_wanted(p)};
     return true;
 }
 
@@ -516,14 +536,14 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.share_hdr = take(share ? (size_t)gcoo::share_hdr_words(nnz, g) * 4 : 0);
     L.share_blocks = take(share ? (size_t)gcoo::share_stream_blocks(nnz, g, k) * gcoo::kShareBlockWords * 4 : 0);
     L.share_sbase = take(share ? (size_t)nQ * gcoo::kShareW * 4 : 0);
-    L.band_h = band_schedule_h(m, k, nnz, p);
-    const int64_t lists = L.band_h ? gcoo::band_blocks(m, L.band_h) * gcoo::kBandWaves : 0;
-    L.band_head = take((size_t)(lists * gcoo::band_head_stride(k)) * gcoo::kBandHeadWords * 4);
-    L.band_units = take(L.band_h ? (size_t)gcoo::band_units(nnz, m, k, L.band_h) * gcoo::kBandUnitWords * 4 : 0);
+    L.band = band_plan(m, k, nnz, p);
+    const int64_t lists = L.band.h ? gcoo::band_blocks(m, L.band.h) * gcoo::kBandWaves : 0;
+    L.band_head = take(L.band.h ? (size_t)(lists * gcoo::band_head_stride(k, L.band.v)) * gcoo::kBandHeadWords * 4 : 0);
+    L.band_units = take(L.band.h ? (size_t)gcoo::band_units(nnz, m, k, L.band.h, L.band.v) * gcoo::kBandUnitWords * 4 : 0);
     L.band_first = take((size_t)lists * 4);
     L.band_count = take((size_t)(lists / gcoo::kBandWaves) * 4);
-    L.by_masks = order_plan(m, k, nnz, p, L.band_h, &L.plan);
-    L.lists = L.plan.fused ? g : lists ? lists : (L.by_masks ? (m + L.plan.list_rows - 1) / L.plan.list_rows : 0);     // (a band block has empty lists behind the last row)
+    L.by_masks = order_plan(m, k, nnz, p, L.band, &L.plan);
+    L.lists = L.plan.fused ? g : lists ? gcoo::band_lists(m, L.band.h, L.band.v) : (L.by_masks ? (m + L.plan.list_rows - 1) / L.plan.list_rows : 0);     // (a band block has empty lists behind the last row)
     L.take_flags = take(L.by_masks ? (size_t)L.lists * 4 : 0);
     L.splits = take(L.by_masks ? (size_t)m * (size_t)(L.plan.parts - 1) * 4 : 0);
     L.persistent = at;
@@ -640,7 +660,7 @@ int new_handle(int64_t m, int64_t k, int64_t nnz, int32_t p, void* dev_buf, gcoo
     h->base = static_cast<char*>(dev_buf);
     h->L = make_layout(m, k, nnz, h->g, p, scratch_inside);
     h->has_share = share_schedule_wanted(m, k, nnz, p);
-    h->share_preferred = (h->has_share || h->L.band_h > 0) && share_kernel_preferred(m, k, nnz, p);
+    h->share_preferred = (h->has_share || h->L.band.h > 0) && share_kernel_preferred(m, k, nnz, p);
     h->has_sched = run_schedule_wanted(p);
     pick_windows(k, h->g, &h->nw, &h->window_cols);
     if (hipGetDevice(&h->device) != hipSuccess) h->device = -1;
@@ -673,14 +693,16 @@ hipError_t band_fill_lds_limit()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gcoo::band_fill<512>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gcoo::band_fill<1024>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
-    if (e == hipSuccess) done[dev].store(1u, std::memory_order_release);
+    for (const void* f : {reinterpret_cast<const void*>(&gcoo::band_fill<4, 512>), reinterpret_cast<const void*>(&gcoo::band_fill<4, 1024>),
+                          reinterpret_cast<const void*>(&gcoo::band_fill<2, 1024>)}) {
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
+        if (e != hipSuccess) return e;
+    }
+    done[dev].store(1u, std::memory_order_release);
     return e;
 }
 
-// The kernel-private schedules that a conversion ends with (see share_schedule_wanted(), run_schedule_wanted() and band_schedule_h()), on the
+// The kernel-private schedules that a conversion ends with (see share_schedule_wanted(), run_schedule_wanted() and band_plan()), on the
 // conversion's stream, so that the handle is never written again.
 // `scratch`: the conversion's scratch area (the counter of share_fill and band_fill sits in it).  `marked`: the bitmaps of the band schedule are there, and
 // the counter is zero.
@@ -730,24 +752,26 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
             h->share_blocks(), h->share_sbase(), share_alloc, (int32_t)stage_cap);
         HIP_TRY(hipGetLastError());
     }
-    if (h->L.band_h > 0) {
-        const int32_t rows = h->L.band_h;
-        const unsigned lists = (unsigned)(gcoo::band_blocks(h->m, rows) * gcoo::kBandWaves);
+    if (h->L.band.h > 0) {
+        const int32_t rows = h->L.band.h;
+        const int v = h->L.band.v, band_rows = gcoo::band_rows_of(v);
+        const unsigned lists = (unsigned)(gcoo::band_blocks(h->m, rows) * gcoo::kBandWaves), marks = (unsigned)gcoo::band_lists(h->m, rows, v);
         const size_t words = (size_t)((h->k + 31) / 32);
         uint32_t* parts = reinterpret_cast<uint32_t*>(scratch + h->L.tmp_cols);          // the second sort buffer, free by now
         uint32_t* alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
-        if (!marked) gcoo::band_mark<<<dim3(lists), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows, parts, alloc,
-                                                                                                                gcoo::band_heavy(h->nnz, lists), h->uneven());
+        if (!marked) gcoo::band_mark<<<dim3(marks), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows / gcoo::band_lists_of(v), parts, alloc,
+                                                                                                                gcoo::band_heavy(h->nnz, marks), h->uneven());
         HIP_TRY(hipGetLastError());
-        int64_t chunk = (h->k + gcoo::kBandRows - 1) / gcoo::kBandRows * gcoo::kBandRows;
-        const int64_t most = (int64_t)(kBandFillMaxLds - words * 8) / (4 * gcoo::kBandRows + 4 * gcoo::kBandRows / gcoo::kBandGroup) * gcoo::kBandRows;
+        // distinct columns at a time: all, or as many as the LDS holds
+        int64_t chunk = gcoo::band_max_bands(h->k, v) * band_rows;
         if (chunk > gcoo::kBandChunk) chunk = gcoo::kBandChunk;
-        if (chunk > most) chunk = most;
+        while (gcoo::band_fill_lds(h->k, chunk, v) > kBandFillMaxLds) chunk -= band_rows;
         HIP_TRY(band_fill_lds_limit());
-        const bool large = h->nnz / lists > 4096;
-        (large ? gcoo::band_fill<1024> : gcoo::band_fill<512>)<<<dim3(lists), dim3(large ? 1024 : 512), words * 8 + (size_t)(chunk + chunk / gcoo::kBandGroup) * 4, s>>>(
-            h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk, gcoo::band_units(h->nnz, h->m, h->k, rows),
-            gcoo::band_head_stride(h->k), h->band_head(), h->band_units(), h->band_first(), h->band_count(), alloc, h->uneven());
+        const bool large = v == 2 || h->nnz / lists > 4096;
+        (v == 2 ? gcoo::band_fill<2, 1024> : (large ? gcoo::band_fill<4, 1024> : gcoo::band_fill<4, 512>))
+            <<<dim3(lists), dim3(large ? 1024 : 512), gcoo::band_fill_lds(h->k, chunk, v), s>>>(
+            h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk, gcoo::band_units(h->nnz, h->m, h->k, rows, v),
+            gcoo::band_head_stride(h->k, v), h->band_head(), h->band_units(), h->band_first(), h->band_count(), alloc, h->uneven());
         HIP_TRY(hipGetLastError());
     }
     return GCOO_OK;
@@ -909,7 +933,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
     } else if (L.by_masks) {
-        marked = L.band_h > 0 && !h->has_share;              // (the share schedule's builder uses the same scratch)
+        marked = L.band.h > 0 && !h->has_share;              // (the share schedule's builder uses the same scratch)
         gcoo::TakeArgs t{};
         t.row_ptr = d_row_ptr; t.cols = d_cols; t.vals = d_vals;
         t.m = m; t.g = g; t.lists = L.lists; t.p = p; t.nnz = (int32_t)nnz; t.k = (int32_t)k; t.plan = L.plan;
@@ -1264,7 +1288,7 @@ bool share_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
 bool band_operands_ok(const gcoo_matrix* A, const Shape& sh, int64_t ldb)
 {
     const bool aligned = sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16;
-    return (aligned || sh.N >= 256) && (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
+    return (aligned || sh.N >= 64 * A->L.band.v) && (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
 }
 
 // Row by row before the register kernel, for a handle that carries the run schedule: up to about 30 entries per row (n = 4000: level at
@@ -1321,8 +1345,8 @@ int kernel_of_product(const gcoo_matrix** M, const Shape& sh, const float* B_dev
     if (A->inner) *M = A = A->inner;   // the schedules of the other kernels belong to the regrouped copy
     if (automatic && A->has_rows()) {
         const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
-        if (A->L.band_h > 0 && band_operands_ok(A, sh, ldb) &&
-            band_time(A->m, A->k, A->nnz, N, A->L.band_h, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
+        if (A->L.band.h > 0 && band_operands_ok(A, sh, ldb) &&
+            band_time(A->m, A->k, A->nnz, N, A->L.band, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
             return GCOO_KERNEL_BAND;
         if (!A->has_sched || rows_preferred(A, N) || sched_width(A->p, sh) == 0) return GCOO_KERNEL_ROWS;     // (0: fewer columns than the register kernel serves)
     }
@@ -1375,8 +1399,8 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
             hipError_t e = gcoo::launch_spdm_rows(rows, s);
             return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
         }
-        gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band_h), A->L.band_h,
-                         0, 0, A->uneven(), gcoo::band_head_stride(A->k), A->m, A->k, B_dev, ldb, N, C_dev, ldc};
+        gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band.h), A->L.band.h, A->L.band.v,
+                         0, 0, A->uneven(), gcoo::band_head_stride(A->k, A->L.band.v), A->m, A->k, B_dev, ldb, N, C_dev, ldc};
         hipError_t e = gcoo::launch_spdm_band(a, rows, s);
         return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_band launch");
     }

@@ -9,12 +9,10 @@
 namespace gcoo {
 
 constexpr int kBandMarkThreads = 512;
-constexpr int kBandChunk = 150 * kBandRows;              // distinct columns that band_fill holds at a time, at most
-constexpr int kBandChunkBands = kBandChunk / kBandRows;
-constexpr int kBandGroup = kBandRows / 16;               // columns of a band that one lane of sixteen counts
-static_assert(kBandRows % 16 == 0, "");
+constexpr int kBandChunk = 14400;                        // distinct columns that band_fill holds at a time, at most (whole bands of both cuts)
+constexpr int kBandGroup = 5;                            // columns of a band that one lane counts
 
-// Entries of list w of block Q: the rows [(16 Q + w) h, + h) of A.
+// Entries of a list: the rows [list * h, + h) of A.
 struct BandList {
     int64_t r0;
     int32_t rows, beg, end;
@@ -36,7 +34,7 @@ __global__ __launch_bounds__(kBandMarkThreads) void band_mark(const int32_t* __r
                                                               int64_t m, int64_t k, int32_t h, uint32_t* __restrict__ parts,
                                                               uint32_t* __restrict__ zeroed, int32_t heavy, uint32_t* __restrict__ uneven)
 {
-    extern __shared__ uint32_t band_lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t band_lds[];
     if (blockIdx.x == 0 && threadIdx.x == 0) *zeroed = 0u;            // the counter from which band_fill places the lists
     const int32_t nbw = (int32_t)((k + 31) / 32);
     const BandList l = band_list(row_start, m, h, blockIdx.x);
@@ -79,7 +77,8 @@ __device__ __forceinline__ int32_t band_block_scan(int32_t mine, int32_t* wsum, 
     return off;
 }
 
-// Exclusive prefix sum of x over every row of 16 lanes; the row's total in *total.
+// Exclusive prefix sum of x over every stretch of LANES (16 or 32) lanes; the stretch's total in *total.
+template <int LANES>
 __device__ __forceinline__ int32_t band_row_scan(int32_t x, int32_t* total)
 {
     int32_t incl = x;
@@ -87,21 +86,38 @@ __device__ __forceinline__ int32_t band_row_scan(int32_t x, int32_t* total)
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
-    *total = __builtin_amdgcn_update_dpp(0, incl, 0x15f, 0xf, 0xf, true);      // row_newbcast:15
+    if constexpr (LANES == 32) {
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15, into rows 1 and 3
+        *total = __shfl(incl, (int)(threadIdx.x & 63u) | 31, 64);
+    } else {
+        *total = __builtin_amdgcn_update_dpp(0, incl, 0x15f, 0xf, 0xf, true);  // row_newbcast:15
+    }
     return incl - x;
 }
 
-// One workgroup per list.  The columns of the block are the OR of its sixteen bitmaps; their popcounts, summed up, give a
-// column its place among the distinct ones.  A word per distinct column collects the rows that hold an entry in it
-// (bit sets again, so nothing depends on timing), and from those words follow, without a sort, the pairs and singles of every
+// The rows of a list as a bit mask.
+template <int V> struct BandRowMask { typedef uint32_t type; };
+template <> struct BandRowMask<2> { typedef unsigned long long type; };
+__device__ __forceinline__ uint32_t band_popc(uint32_t x) { return (uint32_t)__popc(x); }
+__device__ __forceinline__ uint32_t band_popc(unsigned long long x) { return (uint32_t)__popcll(x); }
+
+// Dynamic LDS of band_fill: the column words of a block, a mask per column of the chunk, a place per five of them.
+inline size_t band_fill_lds(int64_t k, int64_t chunk, int v)
+{
+    return (size_t)((k + 31) / 32) * 8 + (size_t)chunk * (v == 4 ? 4 : 8) + (size_t)(chunk / kBandGroup) * 4;
+}
+
+// One workgroup per wave's list.  The columns of the block are the OR of its bitmaps; their popcounts, summed up, give a
+// column its place among the distinct ones.  A mask per distinct column collects the rows that hold an entry in it
+// (bit sets again, so nothing depends on timing), and from those masks follow, without a sort, the pairs and singles of every
 // band and the place of every entry in them.  A coordinate that occurs twice sets its bit twice: such a list is written the
 // slow way, a wave per band that picks the band's entries from the whole list in order.
 // Bound: latency.  A list is a few hundred to a few thousand entries, so a thread has few of them, and every step is a chain of LDS reads: four
 // entries per thread go through it side by side, sixteen lanes count a band, four bands per wave, and the LDS per column is kept
 // small enough for four workgroups per compute unit (8000 x 8000, 0.5 %: 31 us with a band per wave and two workgroups, 17 us so).
-// kBandBuildThreads = 1024 for lists of many entries, of which there are too few to fill the chip with workgroups of 512.
-// Dynamic LDS: 2 * ceil(k/32) + chunk + chunk / 5 words.
-template <int kBandBuildThreads>
+// V as in BandCut.  kBandBuildThreads = 1024 for lists of many entries, of which there are too few to fill the chip with workgroups of 512.
+// Dynamic LDS: band_fill_lds().
+template <int V, int kBandBuildThreads>
 __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_cols,
                                                               const float* __restrict__ row_vals, int64_t m, int64_t k, int32_t h,
                                                               const uint32_t* __restrict__ parts, int32_t chunk, int64_t capacity,
@@ -110,17 +126,21 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                                                               const uint32_t* __restrict__ uneven)
 {
     if (*uneven != 0u) return;                                 // the product goes row by row
-    constexpr int kBandBuildWaves = kBandBuildThreads / 64;
-    static_assert(kBandChunkBands <= kBandBuildThreads, "");
-    extern __shared__ uint32_t band_lds[];
-    __shared__ int32_t wsum[kBandBuildWaves], total_s, repeated_s, base_s, rs[32];
+    typedef BandCut<V> Cut;
+    typedef typename BandRowMask<V>::type Mask;
+    constexpr int kBandBuildWaves = kBandBuildThreads / 64, kBandRows = Cut::kRows, kBandChunkBands = kBandChunk / kBandRows;
+    constexpr int kParts = kBandWaves * 4 / V;             // bitmaps of a block, band_lists_of(V) per wave
+    constexpr int kFind = V == 4 ? 32 : 64, kLanes = kBandRows / kBandGroup;       // lanes that count a band
+    static_assert(kBandChunk % kBandRows == 0 && kBandChunkBands <= kBandBuildThreads && Cut::kMaxH < kFind && (kLanes == 16 || kLanes == 32), "");
+    extern __shared__ __attribute__((aligned(16))) uint32_t band_lds[];
+    __shared__ int32_t wsum[kBandBuildWaves], total_s, repeated_s, base_s, rs[kFind];
     __shared__ int32_t pairs_s[kBandChunkBands], singles_s[kBandChunkBands], at_s[kBandChunkBands];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int32_t nbw = (int32_t)((k + 31) / 32);
     uint32_t* bits = band_lds;                              // the block's columns
     int32_t* before = (int32_t*)(bits + nbw);               // distinct columns in front of a word of them
-    uint32_t* rows_of = (uint32_t*)(before + nbw);          // rows of the list with an entry in a column of the chunk
-    uint32_t* place_of = rows_of + chunk;                   // pairs | singles << 16 of the band in front of five columns
+    Mask* rows_of = (Mask*)(before + nbw);                  // rows of the list with an entry in a column of the chunk
+    uint32_t* place_of = (uint32_t*)(rows_of + chunk);      // pairs | singles << 16 of the band in front of five columns
     const int64_t list = blockIdx.x, Q = list / kBandWaves;
     const int32_t w = (int32_t)(list - Q * kBandWaves);
     const BandList l = band_list(row_start, m, h, list);
@@ -128,11 +148,11 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
     for (int32_t i = tid; i < nbw; i += kBandBuildThreads) {
         uint32_t b = 0u;
 #pragma unroll
-        for (int x = 0; x < kBandWaves; ++x) b |= parts[(Q * kBandWaves + x) * nbw + i];
+        for (int x = 0; x < kParts; ++x) b |= parts[(Q * kParts + x) * nbw + i];
         bits[i] = b;
     }
-    // where the rows begin; places past the last row hold a number no entry reaches, so that the search below always takes five steps
-    if (tid < 32) rs[tid] = tid <= l.rows ? row_start[l.r0 + tid] : INT32_MAX;
+    // where the rows begin; places past the last row hold a number no entry reaches, so that the search below always takes as many steps
+    if (tid < kFind) rs[tid] = tid <= l.rows ? row_start[l.r0 + tid] : INT32_MAX;
     if (tid == 0) repeated_s = 0;
     __syncthreads();
     if (tid == 0) rs[l.rows] = INT32_MAX;
@@ -152,9 +172,7 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
     if (tid == 0 && w == 0) count[Q] = nU;
     uint32_t* hd = head + list * head_stride * kBandHeadWords;
     // the columns whose rows the wave fetches, one band beyond the last
-    for (int32_t i = tid; i < (NB + 1) * kBandGroup && nU > 0; i += kBandBuildThreads) {
-        const int32_t b = i / kBandGroup, t = i - b * kBandGroup;
-        int32_t u = b * kBandRows + kBandGroup * w + t;
+    auto column = [&](int32_t u) -> uint32_t {
         u = u < nU ? u : nU - 1;
         int32_t lo = 0, hi = nbw;                           // last word with before[] <= u
         while (hi - lo > 1) {
@@ -163,7 +181,14 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
         }
         uint32_t x = bits[lo];
         for (int32_t n = u - before[lo]; n > 0; --n) x &= x - 1u;
-        hd[b * kBandHeadWords + t] = (uint32_t)(lo * 32 + __ffs(x) - 1);
+        return (uint32_t)(lo * 32 + __ffs(x) - 1);
+    };
+    for (int32_t i = tid; i < (NB + 1) * kBandFetches && nU > 0; i += kBandBuildThreads) {
+        const int32_t b = i / kBandFetches, t = i - b * kBandFetches;
+        const int32_t u = b * kBandRows + (kBandFetches * w + t) * (4 / V);
+        uint32_t c = column(u);
+        if constexpr (V == 2) c |= (column(u + 1) - c) << 16;
+        hd[b * kBandHeadWords + t] = c;
     }
 
     auto in_range = [&](uint32_t c) -> uint32_t { return c < (uint32_t)k ? c : (uint32_t)k - 1u; };
@@ -171,7 +196,7 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
     auto row_of = [&](int32_t e) -> int32_t {
         int32_t r = 0;
 #pragma unroll
-        for (int d = 16; d >= 1; d >>= 1) r += rs[r + d] <= e ? d : 0;
+        for (int d = kFind / 2; d >= 1; d >>= 1) r += rs[r + d] <= e ? d : 0;
         return r;
     };
 
@@ -184,7 +209,7 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
         for (int32_t ch = 0; ch < chunks; ++ch) {
             const int32_t u0 = ch * chunk, nu = u0 + chunk < nU ? chunk : nU - u0, b0 = u0 / kBandRows, bands = (nu + kBandRows - 1) / kBandRows;
             if (round == 0 || chunks > 1) {
-                for (int32_t i = tid; i < bands * kBandRows; i += kBandBuildThreads) rows_of[i] = 0u;
+                for (int32_t i = tid; i < bands * kBandRows; i += kBandBuildThreads) rows_of[i] = 0;
                 __syncthreads();
                 for (int32_t e = l.beg + tid; e < l.end; e += 4 * kBandBuildThreads) {
                     uint32_t c[4];
@@ -194,16 +219,16 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                         c[x] = (uint32_t)row_cols[at < l.end ? at : e];
                     }
                     int32_t u[4];
-                    uint32_t bit[4];
+                    Mask bit[4];
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
                         u[x] = distinct(in_range(c[x])) - u0;
-                        bit[x] = 1u << row_of(e + x * kBandBuildThreads);
+                        bit[x] = (Mask)1 << row_of(e + x * kBandBuildThreads);
                     }
-                    uint32_t old[4];
+                    Mask old[4];
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
-                        old[x] = 0u;
+                        old[x] = 0;
                         if (e + x * kBandBuildThreads < l.end && u[x] >= 0 && u[x] < nu) old[x] = atomicOr(&rows_of[u[x]], bit[x]) & bit[x];
                     }
                     if (old[0] | old[1] | old[2] | old[3]) repeated_s = 1;
@@ -223,22 +248,23 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                         }
                     }
                 } else {
-                    // sixteen lanes per band, five columns per lane
-                    for (int32_t b = wv * 4; b < bands; b += kBandBuildWaves * 4) {
-                        const int32_t mine = b + (lane >> 4), at = mine * kBandRows + (lane & 15) * kBandGroup;
+                    // five columns per lane
+                    constexpr int kPerWave = 64 / kLanes;
+                    for (int32_t b = wv * kPerWave; b < bands; b += kBandBuildWaves * kPerWave) {
+                        const int32_t mine = b + lane / kLanes, at = mine * kBandRows + lane % kLanes * kBandGroup;
                         uint32_t both = 0u;
                         if (mine < bands) {
 #pragma unroll
                             for (int x = 0; x < kBandGroup; ++x) {
-                                const uint32_t n = (uint32_t)__popc(rows_of[at + x]);
+                                const uint32_t n = band_popc(rows_of[at + x]);
                                 both += (n >> 1) | (n & 1u) << 16;
                             }
                         }
                         int32_t total;
-                        const int32_t in_front = band_row_scan((int32_t)both, &total);
+                        const int32_t in_front = band_row_scan<kLanes>((int32_t)both, &total);
                         if (mine < bands) {
                             place_of[at / kBandGroup] = (uint32_t)in_front;
-                            if ((lane & 15) == 0) {
+                            if (lane % kLanes == 0) {
                                 pairs_s[mine] = total & 0xffff;
                                 singles_s[mine] = total >> 16;
                             }
@@ -282,15 +308,15 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                         uint32_t front = place_of[g];
 #pragma unroll
                         for (int y = 0; y < kBandGroup - 1; ++y) {
-                            const uint32_t n = (uint32_t)__popc(rows_of[g * kBandGroup + y]);
+                            const uint32_t n = band_popc(rows_of[g * kBandGroup + y]);
                             front += g * kBandGroup + y < u ? (n >> 1) | (n & 1u) << 16 : 0u;
                         }
-                        const uint32_t rows = rows_of[u];
-                        const int32_t n = __popc(rows), mine = __popc(rows & ((1u << row) - 1u));
+                        const Mask rows = rows_of[u];
+                        const int32_t n = (int32_t)band_popc(rows), mine = (int32_t)band_popc(rows & (((Mask)1 << row) - 1));
                         const int32_t idx = (mine == n - 1 && (n & 1)) ? 4 * ((pairs_s[b] + 1) / 2) + (int32_t)(front >> 16)
                                                                       : 2 * (int32_t)(front & 0xffffu) + mine;
                         rec[(int64_t)at_s[b] * 16 + idx] = make_uint2(__float_as_uint(v[x]),
-                                                                      (uint32_t)row | (uint32_t)(((b0 + b) & 1) * kBandRows + u - b * kBandRows) << 10);
+                                                                      (uint32_t)row | (uint32_t)(((b0 + b) & 1) * kBandRows + u - b * kBandRows) << Cut::kPlaceShift);
                     }
                 }
             } else {
@@ -304,7 +330,7 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                         const uint64_t mk = __ballot(mine);
                         if (mine)
                             to[done + __popcll(mk & ((1ull << lane) - 1ull))] = make_uint2(__float_as_uint(row_vals[e]),
-                                (uint32_t)row_of(e) | (uint32_t)(((b0 + b) & 1) * kBandRows + u - (b0 + b) * kBandRows) << 10);
+                                (uint32_t)row_of(e) | (uint32_t)(((b0 + b) & 1) * kBandRows + u - (b0 + b) * kBandRows) << Cut::kPlaceShift);
                         done += __popcll(mk);
                     }
                 }
@@ -314,7 +340,7 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
                 const int32_t np = pairs_s[b], ns = singles_s[b], ps = (np + 1) / 2, ss = (ns + 3) / 4;
                 const int32_t room = 16 * (ps + ss > 0 ? (ps + ss + 3) / 4 : 1), i = tid & 15;
                 uint2* to = rec + (int64_t)at_s[b] * 16;
-                const uint2 none = make_uint2(0u, (uint32_t)kBandSink);
+                const uint2 none = make_uint2(0u, (uint32_t)Cut::kSink);
                 if (2 * np + i < 4 * ps) to[2 * np + i] = none;
                 if (4 * ps + ns + i < room) to[4 * ps + ns + i] = none;
             }

@@ -2,7 +2,7 @@
 // for CDNA4; the schedule it reads is described in gcoo_band.hpp).
 //
 // Work unit = (block of 16 h rows of A, column tile of 256 columns).  A lane keeps (24 + 1) x 4 partial sums (its four
-// columns of the wave's rows, and the sink row) in v[28:127], so four waves share a SIMD: what one wave waits for - LDS, scalar
+// columns of the wave's rows, and the sink row; the tall cut: (48 + 1) x 2, tiles of 128 columns) in v[28:127], so four waves share a SIMD: what one wave waits for - LDS, scalar
 // loads, the barrier - the other three fill.  With 48 rows per wave and two waves per SIMD nothing hid behind
 // anything: every instruction of a wave took six to eight clocks.
 //
@@ -17,6 +17,13 @@
 // By the counters a SIMD issues a vector instruction every 2.5 ns at 8000 x 8000, 10 %, and every 2.9 at 14000 x 14000, 2 % (15 of 16 waves resident,
 // waiting half their time).  At 8000 x 8000, 0.5 %, it is every 5.0 ns: there the rows of B are the bound, 5.1 GB of them into LDS at 15.3 TB/s
 // where a loop of nothing but such requests and barriers reaches 16.9.  No bank conflicts anywhere.
+//
+// The tall cut (V = 2): the same registers and the same LDS hold twice the rows of A and of B, half as wide.  A row of B is fetched for twice as
+// many rows of A, and a launch has half as many bands, each with four times the entries of a wave; an entry costs a multiply-add
+// less than half but the same address, read and index (7.5 ns in a loop of nothing else, where the wide cut takes 10.2 for twice the columns): the unit that reads LDS takes
+// as long for 8 bytes per lane as for 16, and is the bound of dense matrices.  For sparse ones what is fetched and the bands are: 8000 x 8000, 0.5 %: 336 -> 300 us,
+// where the same launch without its multiply-adds takes 290, without its requests 240, and with neither requests nor
+// entries 68: a band is a chain of waits (rows of B from L2, LDS, barrier) that fifteen other waves in the same phase do not fill.
 //
 // B: two bands of 80 rows x 1 KB in LDS.  While band b is multiplied, the rows of band b + 1 are requested, five per wave, straight
 // to LDS; their columns come with the band's head, and the address is formed by the scalar unit.  One barrier per band, nothing in
@@ -41,20 +48,20 @@
 
 namespace gcoo {
 
-constexpr int kBandBufferBytes = kBandRows * 1024;
+constexpr int kBandFillBytes = kBandFetches * 1024;                // what a wave fetches of a band
+constexpr int kBandBufferBytes = kBandWaves * kBandFillBytes;
 constexpr int kBandLdsBytes = 2 * kBandBufferBytes;
-static_assert(kBandRows == 5 * kBandWaves, "the asm text below uses these numbers");
+static_assert(kBandFetches == 5 && BandCut<4>::kRows * 1024 == kBandBufferBytes && BandCut<2>::kRows * 512 == kBandBufferBytes, "the asm text below uses these numbers");
 
 typedef float band_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t band_u32x4 __attribute__((ext_vector_type(4)));
 typedef float band_f32x32 __attribute__((ext_vector_type(32)));
 
-// sum(c, r) = v[28 + 25 * c + r], c = 0..3, r = 0..24
+// sum(c, r) = v[28 + 25 * c + r], c = 0..3, r = 0..24 (wide); v[28 + 49 * c + r], c = 0..1, r = 0..48 (tall)
 struct BandAcc {
     band_f32x4 t0;                    // v[28:31]
     band_f32x32 t1, t2, t3;           // v[32:127]
 };
-constexpr int kBandAccStride = kBandMaxH + 1;
 __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 {
     if (s < 4) return a.t0[s];
@@ -71,24 +78,18 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 //   s15 bands left   s[16:22]  head of this band: five columns, pair steps, single steps    s[24:30] of the next one    s23 scratch
 //   s[32:35]  buffer descriptor of B, from the tile's first column on
 //   vcc       not 0: rows of the next band are still to be requested (SPREAD: 1 + how often it was done behind a step)
-#define BD_FMAC(val, b0, b1, b2, b3)                   \
+//   tall only: v126 scratch, v127 all ones in the upper half of the wave, s100 scratch
+// What differs between the cuts: BD_FMAC_T<i> (the entry's partial sums += value x set i), BD_READ_T<i>, BD_MASK, BD_BEGIN, BD_FILL.
+#define BD_FMAC_WIDE(val, b0, b1, b2, b3)              \
     "v_fmac_f32 v28, " #val ", " #b0 "\n\t"             \
     "v_fmac_f32 v53, " #val ", " #b1 "\n\t"             \
     "v_fmac_f32 v78, " #val ", " #b2 "\n\t"             \
     "v_fmac_f32 v103, " #val ", " #b3 "\n\t"
-#define BD_FMAC_T0(val) BD_FMAC(val, v4, v5, v6, v7)
-#define BD_FMAC_T1(val) BD_FMAC(val, v8, v9, v10, v11)
-#define BD_FMAC_T2(val) BD_FMAC(val, v12, v13, v14, v15)
-#define BD_FMAC_T3(val) BD_FMAC(val, v16, v17, v18, v19)
-#define BD_FMAC_T4(val) BD_FMAC(val, v20, v21, v22, v23)
-#define BD_FMAC_T5(val) BD_FMAC(val, v24, v25, v26, v27)
-#define BD_READ(meta, set) "v_and_or_b32 v3, " #meta ", v1, v0\n\tds_read_b128 " set ", v3\n\t"
-#define BD_READ_T0(meta) BD_READ(meta, "v[4:7]")
-#define BD_READ_T1(meta) BD_READ(meta, "v[8:11]")
-#define BD_READ_T2(meta) BD_READ(meta, "v[12:15]")
-#define BD_READ_T3(meta) BD_READ(meta, "v[16:19]")
-#define BD_READ_T4(meta) BD_READ(meta, "v[20:23]")
-#define BD_READ_T5(meta) BD_READ(meta, "v[24:27]")
+#define BD_FMAC_TALL(val, b0, b1)                      \
+    "v_fmac_f32 v28, " #val ", " #b0 "\n\t"             \
+    "v_fmac_f32 v77, " #val ", " #b1 "\n\t"
+#define BD_READ_WIDE(meta, set) "v_and_or_b32 v3, " #meta ", v1, v0\n\tds_read_b128 " set ", v3\n\t"
+#define BD_READ_TALL(meta, set) "v_and_or_b32 v3, " #meta ", v1, v0\n\tds_read_b64 " set ", v3\n\t"
 // two entries, of sets A and B; index mode is off before and after
 #define BD_TWO(val0, meta0, A, val1, meta1, B)                    \
     "s_set_gpr_idx_on " #meta0 ", gpr_idx(SRC2,DST)\n\t"           \
@@ -98,11 +99,21 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     "s_set_gpr_idx_off\n\t"
 #define BD_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
 
-// Row t of the five that the wave fetches for the next band: column in s<16 + t>.
-#define BD_FILL(col, at)                        \
+// Request t of the five of a wave for the next band: one row of B (wide) or two, one per half of the wave (tall); the column, or both, in s<16 + t>.
+#define BD_FILL_WIDE(col, at)                   \
     "s_add_u32 m0, s14, " #at "\n\t"             \
     "s_mul_i32 s23, " #col ", %[ldb4]\n\t"       \
     BD_LOAD_ROW
+#define BD_FILL_TALL(cols, at)                                                                                          \
+    "s_add_u32 m0, s14, " #at "\n\ts_and_b32 s23, " #cols ", 0xffff\n\ts_lshr_b32 s100, " #cols ", 16\n\t"            \
+    "s_mul_i32 s23, s23, %[ldb4]\n\ts_mul_i32 s100, s100, %[ldb4]\n\t"                                                 \
+    "v_and_b32 v126, s100, v127\n\tv_add_u32 v126, v126, v2\n\tbuffer_load_dwordx4 v126, s[32:35], s23 offen lds\n\t"
+#define BD_FILL_TALL_UNALIGNED(cols, at)                                                                                \
+    "s_add_u32 m0, s14, " #at "\n\ts_and_b32 s23, " #cols ", 0xffff\n\ts_lshr_b32 s100, " #cols ", 16\n\t"            \
+    "s_mul_i32 s23, s23, %[ldb4]\n\ts_mul_i32 s100, s100, %[ldb4]\n\t"                                                 \
+    "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"   \
+    "s_add_u32 m0, s14, " #at " + 0x200\n\ts_add_u32 s23, s23, s100\n\t"                                              \
+    "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"
 #define BD_FILL_BAND BD_FILL(s16, 0) BD_FILL(s17, 0x400) BD_FILL(s18, 0x800) BD_FILL(s19, 0xc00) BD_FILL(s20, 0x1000)
 // The places where rows are requested; T = p (pair steps) or s (single steps).  BD_ASK_START behind the first reads of a band, BD_ASK_STEP behind
 // step I of its first unit, BD_ASK_UNIT in front of a further unit, BD_ASK_END at its end; what is done there stands out of line (BD_ASK_REST).
@@ -245,7 +256,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     asm volatile(                                                                                       \
         BD_CLEAR                                                                                        \
         "s_cmp_eq_u32 %[nb], 0\n\ts_cbranch_scc1 .Lbd_done_%=\n\t"                                   \
-        "v_mov_b32 v1, 0x3fc00\n\t"                                                                    \
+        BD_BEGIN                                                                                        \
         "s_mov_b32 s12, 0x60\n\t"                                                                       \
         "s_mov_b32 s13, 0\n\t"                                                                          \
         "s_mov_b64 vcc, 0\n\t"                                                                          \
@@ -260,13 +271,15 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
         "s_load_dwordx8 s[16:23], %[head], 0x20\n\t"                                                    \
         BD_WAIT_BAND                                                                                    \
         "s_barrier\n\t"                                                                                 \
-        "s_branch .Lbd_band_A_%=\n"                                                                     \
+        "s_branch .Lbd_band_A_%=\n\t"                                                                   \
+        /* (where the loop lies in the cache lines of the instructions makes up to 1 %: the same place in every build) */ \
+        ".p2align 8\n"                                                                                   \
         BD_HALF_A                                                                                       \
         BD_HALF_B                                                                                       \
         /* the rows requested for the bands beyond the last one arrive before the wave gives up its LDS */ \
         ".Lbd_done_%=:\n\t"                                                                             \
         "s_waitcnt vmcnt(0) lgkmcnt(0)\n\t" \
-        : "={v[28:31]}"(acc.t0), "={v[32:63]}"(acc.t1), "={v[64:95]}"(acc.t2), "={v[96:127]}"(acc.t3), "+{v0}"(l16), [fillw] "+s"(fillw) \
+        : "={v[28:31]}"(acc.t0), "={v[32:63]}"(acc.t1), "={v[64:95]}"(acc.t2), "={v[96:127]}"(acc.t3), "+{v0}"(lane_at), [fillw] "+s"(fillw) \
         : [head] "s"(head), [units] "s"(units), [nb] "s"(nb), [ldb4] "s"(ldb4), [flip] "s"(flip), "{s[32:35]}"(rsrc), "{v2}"(lane_b) \
         : "m0", "scc", "vcc", "memory",  \
           "v1", "v3", "v4", "v5", "v6", "v7", "v8", "v9", "v10", "v11", "v12", "v13", "v14", "v15", "v16", "v17", "v18", "v19",  \
@@ -275,7 +288,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
           "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58",  \
           "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75",  \
           "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", "s92",  \
-          "s93", "s94", "s95", "s96", "s97", "s98", "s99")
+          "s93", "s94", "s95", "s96", "s97", "s98", "s99" BD_MORE_SCALARS)
 
 // How the launch works row by row instead: items of kBandWaves x rpw rows x 64 columns, strided over the workgroups.
 struct BandRowsGrid { int32_t tiles, row_wgs, rpw, wave_row, items; };
@@ -283,7 +296,7 @@ struct BandRowsGrid { int32_t tiles, row_wgs, rpw, wave_row, items; };
 // A matrix with a list of far more entries than the others (take_rows and band_mark say so on the device, where the
 // row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, as the row-by-row
 // kernel does, by the workgroups of this launch.
-template <bool UNALIGNED, bool SPREAD>            // (SPREAD without UNALIGNED only)
+template <int V, bool UNALIGNED, bool SPREAD>            // V = 4: the wide cut, 2: the tall one
 __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
@@ -300,15 +313,16 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
     const int32_t item = (int32_t)(blockIdx.x & 7u) * per + (int32_t)(blockIdx.x >> 3);
     if (item >= a.total) return;                                     // the whole workgroup
     const int32_t tile = item / a.blocks, Q = item - tile * a.blocks;
-    // the last tile of a B that is no multiple of 256 wide begins where it can hold 256 columns
-    const int32_t n = (int32_t)a.N, j0 = tile * 256, jb = j0 > n - 256 && n >= 256 ? n - 256 : j0;
+    // the last tile of a B that is no multiple of a tile wide begins where it can hold a whole one
+    constexpr int32_t kTile = BandCut<V>::kTile;
+    const int32_t n = (int32_t)a.N, j0 = tile * kTile, jb = j0 > n - kTile && n >= kTile ? n - kTile : j0;
 
     BandAcc acc;
-    uint32_t l16 = (threadIdx.x & 63u) * 16u;
-    uint32_t fillw = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (kBandRows / kBandWaves * 1024u);       // the wave's five rows inside a band buffer
-    const int32_t nb = (__builtin_amdgcn_readfirstlane(a.count[Q]) + kBandRows - 1) / kBandRows;
+    uint32_t lane_at = (threadIdx.x & 63u) * (4u * V);           // the lane's columns in a row of B in LDS
+    uint32_t fillw = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (uint32_t)kBandFillBytes;       // the wave's rows inside a band buffer
+    const int32_t nb = (__builtin_amdgcn_readfirstlane(a.count[Q]) + BandCut<V>::kRows - 1) / BandCut<V>::kRows;
     {
-        const int64_t list = (int64_t)Q * kBandWaves + fillw / (kBandRows / kBandWaves * 1024u);
+        const int64_t list = (int64_t)Q * kBandWaves + fillw / (uint32_t)kBandFillBytes;
         const uint32_t* head = a.head + list * a.head_stride * kBandHeadWords;
         const uint32_t* units = a.units + (int64_t)__builtin_amdgcn_readfirstlane(a.first[list]) * kBandUnitWords;
         // B from the tile's first column on; a load outside it would return zero
@@ -317,8 +331,26 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
         const uint32_t flip = 2u * fillw + kBandBufferBytes;
         const uint32_t ldb4 = (uint32_t)a.ldb * 4u;                // the launcher checks that every row offset fits 32 bits
 #define BD_WAIT_BAND "s_waitcnt vmcnt(0) lgkmcnt(0)\n\t"
-        if constexpr (UNALIGNED) {
-            const uint32_t lane_b = l16 >> 2;
+        // the lane's byte offset in what a request fetches; lanes beyond N fetch the first columns of the tile
+        const uint32_t lane = threadIdx.x & 63u;
+        if constexpr (V == 4) {
+#define BD_FMAC_T0(val) BD_FMAC_WIDE(val, v4, v5, v6, v7)
+#define BD_FMAC_T1(val) BD_FMAC_WIDE(val, v8, v9, v10, v11)
+#define BD_FMAC_T2(val) BD_FMAC_WIDE(val, v12, v13, v14, v15)
+#define BD_FMAC_T3(val) BD_FMAC_WIDE(val, v16, v17, v18, v19)
+#define BD_FMAC_T4(val) BD_FMAC_WIDE(val, v20, v21, v22, v23)
+#define BD_FMAC_T5(val) BD_FMAC_WIDE(val, v24, v25, v26, v27)
+#define BD_READ_T0(meta) BD_READ_WIDE(meta, "v[4:7]")
+#define BD_READ_T1(meta) BD_READ_WIDE(meta, "v[8:11]")
+#define BD_READ_T2(meta) BD_READ_WIDE(meta, "v[12:15]")
+#define BD_READ_T3(meta) BD_READ_WIDE(meta, "v[16:19]")
+#define BD_READ_T4(meta) BD_READ_WIDE(meta, "v[20:23]")
+#define BD_READ_T5(meta) BD_READ_WIDE(meta, "v[24:27]")
+#define BD_BEGIN "v_mov_b32 v1, 0x3fc00\n\t"
+#define BD_MORE_SCALARS
+#define BD_FILL BD_FILL_WIDE
+            if constexpr (UNALIGNED) {
+                const uint32_t lane_b = lane * 4u;
 #define BD_LOAD_ROW                                                                                          \
     "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"               \
     "buffer_load_dword v2, s[32:35], s23 offen offset:512 lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:768 lds\n\t"
@@ -326,26 +358,71 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #define BD_ASK_STEP BD_HALVES_STEP
 #define BD_ASK_UNIT BD_HALVES_UNIT
 #define BD_ASK_REST BD_HALVES_REST
-            BD_MAIN;
-#undef BD_ASK_START
-#undef BD_ASK_STEP
-#undef BD_ASK_UNIT
-#undef BD_ASK_REST
-#undef BD_LOAD_ROW
-        } else {
-            const uint32_t lane_b = jb + (int32_t)(l16 >> 2) < n ? l16 : 0u;     // lanes beyond N fetch the first columns of the tile
-#define BD_LOAD_ROW "buffer_load_dwordx4 v2, s[32:35], s23 offen lds\n\t"
-            if constexpr (SPREAD) {
-#define BD_ASK_START BD_SPREAD_START
-#define BD_ASK_STEP BD_SPREAD_STEP
-#define BD_ASK_UNIT BD_SPREAD_UNIT
-#define BD_ASK_REST BD_SPREAD_REST
                 BD_MAIN;
 #undef BD_ASK_START
 #undef BD_ASK_STEP
 #undef BD_ASK_UNIT
 #undef BD_ASK_REST
+#undef BD_LOAD_ROW
             } else {
+                const uint32_t lane_b = jb + (int32_t)(lane * 4u) < n ? lane * 16u : 0u;
+#define BD_LOAD_ROW "buffer_load_dwordx4 v2, s[32:35], s23 offen lds\n\t"
+                if constexpr (SPREAD) {
+#define BD_ASK_START BD_SPREAD_START
+#define BD_ASK_STEP BD_SPREAD_STEP
+#define BD_ASK_UNIT BD_SPREAD_UNIT
+#define BD_ASK_REST BD_SPREAD_REST
+                    BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+                } else {
+#define BD_ASK_START BD_HALVES_START
+#define BD_ASK_STEP BD_HALVES_STEP
+#define BD_ASK_UNIT BD_HALVES_UNIT
+#define BD_ASK_REST BD_HALVES_REST
+                    BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+                }
+#undef BD_LOAD_ROW
+            }
+#undef BD_FILL
+#undef BD_MORE_SCALARS
+#undef BD_BEGIN
+#undef BD_FMAC_T0
+#undef BD_READ_T0
+#undef BD_FMAC_T1
+#undef BD_READ_T1
+#undef BD_FMAC_T2
+#undef BD_READ_T2
+#undef BD_FMAC_T3
+#undef BD_READ_T3
+#undef BD_FMAC_T4
+#undef BD_READ_T4
+#undef BD_FMAC_T5
+#undef BD_READ_T5
+        } else {
+#define BD_FMAC_T0(val) BD_FMAC_TALL(val, v4, v5)
+#define BD_FMAC_T1(val) BD_FMAC_TALL(val, v6, v7)
+#define BD_FMAC_T2(val) BD_FMAC_TALL(val, v8, v9)
+#define BD_FMAC_T3(val) BD_FMAC_TALL(val, v10, v11)
+#define BD_FMAC_T4(val) BD_FMAC_TALL(val, v12, v13)
+#define BD_FMAC_T5(val) BD_FMAC_TALL(val, v14, v15)
+#define BD_READ_T0(meta) BD_READ_TALL(meta, "v[4:5]")
+#define BD_READ_T1(meta) BD_READ_TALL(meta, "v[6:7]")
+#define BD_READ_T2(meta) BD_READ_TALL(meta, "v[8:9]")
+#define BD_READ_T3(meta) BD_READ_TALL(meta, "v[10:11]")
+#define BD_READ_T4(meta) BD_READ_TALL(meta, "v[12:13]")
+#define BD_READ_T5(meta) BD_READ_TALL(meta, "v[14:15]")
+#define BD_BEGIN "v_mov_b32 v1, 0x3fe00\n\tv_bfe_i32 v127, v0, 8, 1\n\t"
+#define BD_MORE_SCALARS , "s100"
+            if constexpr (UNALIGNED) {
+                const uint32_t lane_b = lane * 4u;
+#define BD_FILL BD_FILL_TALL_UNALIGNED
 #define BD_ASK_START BD_HALVES_START
 #define BD_ASK_STEP BD_HALVES_STEP
 #define BD_ASK_UNIT BD_HALVES_UNIT
@@ -355,8 +432,47 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #undef BD_ASK_STEP
 #undef BD_ASK_UNIT
 #undef BD_ASK_REST
+#undef BD_FILL
+            } else {
+                const uint32_t lane_b = jb + (int32_t)((lane & 31u) * 4u) < n ? (lane & 31u) * 16u : 0u;
+#define BD_FILL BD_FILL_TALL
+                if constexpr (SPREAD) {
+#define BD_ASK_START BD_SPREAD_START
+#define BD_ASK_STEP BD_SPREAD_STEP
+#define BD_ASK_UNIT BD_SPREAD_UNIT
+#define BD_ASK_REST BD_SPREAD_REST
+                    BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+                } else {
+#define BD_ASK_START BD_HALVES_START
+#define BD_ASK_STEP BD_HALVES_STEP
+#define BD_ASK_UNIT BD_HALVES_UNIT
+#define BD_ASK_REST BD_HALVES_REST
+                    BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+                }
+#undef BD_FILL
             }
-#undef BD_LOAD_ROW
+#undef BD_MORE_SCALARS
+#undef BD_BEGIN
+#undef BD_FMAC_T0
+#undef BD_READ_T0
+#undef BD_FMAC_T1
+#undef BD_READ_T1
+#undef BD_FMAC_T2
+#undef BD_READ_T2
+#undef BD_FMAC_T3
+#undef BD_READ_T3
+#undef BD_FMAC_T4
+#undef BD_READ_T4
+#undef BD_FMAC_T5
+#undef BD_READ_T5
         }
 #undef BD_WAIT_BAND
     }
@@ -370,24 +486,27 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
     const __attribute__((address_space(4))) BandArgs* z = (const __attribute__((address_space(4))) BandArgs*)args;
     const int32_t item2 = (int32_t)(bid & 7u) * (int32_t)(z->grid >> 3) + (int32_t)(bid >> 3);
     const int32_t tile2 = item2 / z->blocks, Q2 = item2 - tile2 * z->blocks;
-    const int32_t N = (int32_t)z->N, first = tile2 * 256, base = first > N - 256 && N >= 256 ? N - 256 : first;
-    const int32_t jc = base + (int32_t)(l16 >> 2);                 // the lane's first column; it stores those from `first` on
-    if (jc + 4 > first && jc < N) {
+    const int32_t N = (int32_t)z->N, first = tile2 * kTile, base = first > N - kTile && N >= kTile ? N - kTile : first;
+    const int32_t jc = base + (int32_t)(lane_at >> 2);             // the lane's first column; it stores those from `first` on
+    if (jc + V > first && jc < N) {
         const int own = first > jc ? first - jc : 0;
         const int32_t h = z->h;
-        const int64_t row0 = ((int64_t)Q2 * kBandWaves + fillw / (kBandRows / kBandWaves * 1024u)) * h, ldc = z->ldc;
+        const int64_t row0 = ((int64_t)Q2 * kBandWaves + fillw / (uint32_t)kBandFillBytes) * h, ldc = z->ldc;
         const int64_t rows = z->m - row0 < h ? z->m - row0 : h;
         float* __restrict__ dst = z->C + jc + row0 * ldc;
+        constexpr int kStride = BandCut<V>::kMaxH + 1;
+        typedef float vec __attribute__((ext_vector_type(V)));
 #pragma unroll
-        for (int r = 0; r < kBandMaxH; ++r) {
+        for (int r = 0; r < BandCut<V>::kMaxH; ++r) {
             if (r < rows) {
-                band_f32x4 o = {band_acc_get(acc, r), band_acc_get(acc, kBandAccStride + r), band_acc_get(acc, 2 * kBandAccStride + r),
-                                band_acc_get(acc, 3 * kBandAccStride + r)};
+                vec o;
+#pragma unroll
+                for (int v = 0; v < V; ++v) o[v] = band_acc_get(acc, v * kStride + r);
                 if (own == 0) {
-                    __builtin_nontemporal_store(o, reinterpret_cast<band_f32x4*>(dst));
+                    __builtin_nontemporal_store(o, reinterpret_cast<vec*>(dst));
                 } else {
 #pragma unroll
-                    for (int v = 1; v < 4; ++v)
+                    for (int v = 1; v < V; ++v)
                         if (v >= own) __builtin_nontemporal_store(o[v], dst + v);
                 }
             }

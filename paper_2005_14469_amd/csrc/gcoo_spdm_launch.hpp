@@ -90,7 +90,7 @@ constexpr uint64_t kRowsMaxBytes = 0xffffefffull;
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s);
 
 
-// The sixteen-wave kernel that reads the band schedule (gcoo_band.hpp): N >= 256, or N, ldb a multiple of 4 and B 16-byte aligned; a B of at
+// The sixteen-wave kernel that reads the band schedule (gcoo_band.hpp): N of at least a tile, or N, ldb a multiple of 4 and B 16-byte aligned; a B of at
 // most kRowsMaxBytes (the launch may work row by row).
 struct BandArgs {
     const uint32_t* head;
@@ -99,6 +99,7 @@ struct BandArgs {
     const int32_t* count;      // [blocks] distinct columns
     int32_t blocks;
     int32_t h;                 // rows per wave
+    int32_t v;                 // columns per lane: 4 (the wide cut) or 2 (the tall one)
     int32_t total, grid;       // workgroups with work, workgroups launched (set by the launcher)
     const uint32_t* uneven;    // not 0: no schedule was built, the rows are multiplied one by one
     int64_t head_stride;

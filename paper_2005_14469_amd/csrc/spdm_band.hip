@@ -2,11 +2,10 @@
 #include "gcoo_spdm_band_kernel.hpp"
 
 #include <atomic>
-#include <cmath>
 
 namespace gcoo {
 
-template <bool UNALIGNED, bool SPREAD>
+template <int V, bool UNALIGNED, bool SPREAD>
 static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const BandRowsGrid& rg, hipStream_t s)
 {
     // more LDS than the default limit of a workgroup: asked for once per device
@@ -16,22 +15,24 @@ static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const Ban
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!done[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<UNALIGNED, SPREAD>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<V, UNALIGNED, SPREAD>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
         if (e != hipSuccess) return e;
         done[dev].store(1u, std::memory_order_release);
     }
-    spdm_band<UNALIGNED, SPREAD><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
+    spdm_band<V, UNALIGNED, SPREAD><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
     return hipGetLastError();
 }
 
 hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t s)
 {
-    const int64_t tiles = (a.N + 255) / 256, total = a.blocks * tiles;
+    if (a.v != 2 && a.v != 4) return hipErrorInvalidValue;
+    const int64_t tile = 64 * a.v, tiles = (a.N + tile - 1) / tile, total = a.blocks * tiles;
     if (total <= 0 || total > 0x7ffffff0LL) return hipErrorInvalidConfiguration;
-    if (a.h < 1 || a.h > kBandMaxH || a.blocks != band_blocks(a.m, a.h) || a.head_stride != band_head_stride(a.k)) return hipErrorInvalidValue;
+    if (a.h < 1 || a.h > 96 / a.v || a.blocks != band_blocks(a.m, a.h) || a.head_stride != band_head_stride(a.k, a.v)) return hipErrorInvalidValue;
     if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return hipErrorInvalidValue;
     const bool aligned = a.N % 4 == 0 && a.ldb % 4 == 0 && reinterpret_cast<uintptr_t>(a.B) % 16 == 0;
-    if (!aligned && a.N < 256) return hipErrorInvalidValue;
+    if (a.v == 2 && a.k > kBandTallMaxK) return hipErrorInvalidValue;
+    if (!aligned && a.N < tile) return hipErrorInvalidValue;
     BandArgs b = a;
     b.total = (int32_t)total;
     b.grid = (int32_t)((total + 7) / 8 * 8);                 // whole rounds over the 8 XCDs
@@ -45,12 +46,16 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     const int64_t rest = (int64_t)(rg.tiles % 8) * rg.row_wgs, items = (int64_t)(rg.tiles / 8 * 8) * rg.row_wgs + (rest + 7) / 8 * 8;
     if (items > 0x7fffffffLL || rows.N < 4) return hipErrorInvalidConfiguration;
     rg.items = (int32_t)items;
-    if (!aligned) return launch_band<true, false>(b, rows, rg, s);
     // How the rows of B are requested goes by the entries of a (wave, band), of which SPREAD serves the few (us, halves and SPREAD:
-    // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; with four loads per row 10: 697 698, 19: 254 279, so never there).
-    const double touched = (double)a.k * -std::expm1(-(double)rows.nnz / (double)a.blocks / (double)a.k);
-    const double entries = (double)rows.nnz / (double)(a.blocks * kBandWaves) * kBandRows / (touched > 1.0 ? touched : 1.0);
-    return entries < 28.0 ? launch_band<false, true>(b, rows, rg, s) : launch_band<false, false>(b, rows, rg, s);
+    // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; with four loads per row 10: 697 698, 19: 254 279, so never there; tall, 19:
+    // 694 670, 27: 821 854; with four-byte loads 20: 1222 1307).
+    const double entries = band_entries(a.m, a.k, rows.nnz, a.h, a.v);
+    if (a.v == 2) {
+        if (!aligned) return launch_band<2, true, false>(b, rows, rg, s);
+        return entries < 22.0 ? launch_band<2, false, true>(b, rows, rg, s) : launch_band<2, false, false>(b, rows, rg, s);
+    }
+    if (!aligned) return launch_band<4, true, false>(b, rows, rg, s);
+    return entries < 28.0 ? launch_band<4, false, true>(b, rows, rg, s) : launch_band<4, false, false>(b, rows, rg, s);
 }
 
 }  // namespace gcoo

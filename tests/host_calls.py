@@ -279,6 +279,30 @@ def kernel_of_product(host):
     assert host.L.gcoo_spdm_kernel(None, 1 << 20, 4, 4, 1 << 20, 4, 0) == EINVAL
 
 
+# ---- the cuts of the band schedule -------------------------------------------------------------------
+
+# (m, k, N, entries, variant): what tests/test_gpu_band.py multiplies by the wide cut and by the tall one, and by which instance
+CUTS = [("ILi4ELb0ELb0E", 384, 3500, 260, 384 * 150, SHARE), ("ILi4ELb0ELb0E", 777, 3500, 252, 777 * 150, SHARE), ("ILi4ELb0ELb1E", 4000, 4000, 2044, 320000, AUTO),
+        ("ILi4ELb1ELb0E", 4000, 3000, 1001, 1200000, AUTO), ("ILi2ELb0ELb0E", 384, 3500, 260, 384 * 60, SHARE), ("ILi2ELb0ELb0E", 777, 3500, 252, 777 * 62, SHARE),
+        ("ILi2ELb0ELb0E", 97, 3500, 64, 97 * 130, SHARE), ("ILi2ELb0ELb1E", 300, 7000, 1000, 9450, SHARE), ("ILi2ELb0ELb1E", 40, 3500, 256, 2800, SHARE),
+        ("ILi2ELb1ELb0E", 5000, 5001, 2501, 125025, AUTO)]
+
+
+def cuts(host):
+    for instance, m, k, N, nnz, variant in CUTS:
+        h = host.matrix(m, k, nnz, 32)
+        host.log()
+        assert host.spdm(h, N, N, variant) == OK
+        names = host.launches()
+        assert len(names) == 1 and "spdm_band" + instance in names[0], (m, k, N, nnz, names)
+    # the tall cut's heads hold a column and the distance to the next one in a word
+    for k in (65536, 65537):
+        h = host.matrix(60000, k, 60000 * 300, 32)
+        host.log()
+        assert host.spdm(h, 4096, 4096) == OK
+        assert "spdm_bandILi%dE" % (2 if k == 65536 else 4) in host.launches()[0], k
+
+
 # ---- threads ---------------------------------------------------------------------------------------------
 
 def one_handle_many_threads(host):

@@ -56,6 +56,36 @@ def test_bands_full_and_one_column_over(m, used, per_row, N):
     _run(_columns_used(m, 3500, used, per_row, N, seed=m + used), 32, binding.VARIANT_SHARE)
 
 
+@pytest.mark.parametrize("m,used,per_row,N", [(384, 150, 150, 260), (384, 160, 150, 256), (385, 161, 150, 4), (400, 240, 150, 512), (777, 241, 150, 252), (384, 319, 60, 260),
+                                              (768, 320, 60, 128), (769, 321, 60, 4), (777, 480, 62, 252), (97, 481, 130, 64), (385, 160, 60, 132)])
+def test_bands_of_both_cuts(m, used, per_row, N):
+    """150 entries per row: the wide cut (bands of 80 rows of B, 24 rows of A per wave at most); 60 and 130: the tall one (160 and 48)."""
+    print(f"band, both cuts: m={m} used={used} per_row={per_row} N={N}", flush=True)
+    _run(_columns_used(m, 3500, used, per_row, N, seed=m + used), 32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
+
+
+@pytest.mark.parametrize("m,k,N,s,shift,pad", [(4000, 4000, 2044, 0.98, 0, 0), (5000, 5001, 2501, 0.995, 0, 0), (5000, 5001, 2500, 0.995, 1, 0)])
+def test_automatic_choice_of_both_cuts(m, k, N, s, shift, pad):
+    """The wide cut with few entries per band; the tall one with rows of B aligned to 4 bytes only, its last tile inside the one before."""
+    print(f"band, both cuts, automatic: m={m} k={k} N={N} s={s} shift={shift}", flush=True)
+    _run(workloads.uniform_random(m, k, N, s, seed=m + N), 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
+
+
+def test_tall_cut_with_repeated_coordinates_and_infinities():
+    """Lists that are written the slow way, of more than 32 rows; rows of B that no entry touches hold infinities."""
+    rng = np.random.default_rng(21)
+    m, k, N = 900, 3500, 132
+    rows = [np.concatenate([rng.choice(3400, 58, replace=False), [17] * (i % 5), [3000] * (i % 3)]).astype(np.int32) for i in range(m)]
+    for x in rows:
+        rng.shuffle(x)
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in rows])]).astype(np.int32)
+    ci = np.concatenate(rows)
+    B = rng.standard_normal((k, N)).astype(np.float32)
+    B[3400:] = np.inf
+    print("band, tall: repeated coordinates", flush=True)
+    _run(workloads.Workload("repeated", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), B), 32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
+
+
 @pytest.mark.parametrize("m,k,N,s", [(100, 3500, 300, 0.94), (385, 3600, 1024, 0.98), (1000, 7000, 768, 0.995), (50, 20000, 260, 0.97)])
 def test_uniform_through_the_share_variant(m, k, N, s):
     print(f"band: m={m} k={k} N={N} s={s}", flush=True)
