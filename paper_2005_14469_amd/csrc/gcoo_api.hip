@@ -478,17 +478,23 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 
 // How a CSR input of this shape is put into the order of the groups; false: sorted by digits of the column.  A part has up to 4096
 // columns of at most 32 rows (2048 of 64, 512 of 256: 16 KB of masks) and fewer where it would hold more than 1024 entries on
-// average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).  A part costs a workgroup its steps over all its columns, so the sort is the better one where the groups have far more columns
-// than entries (12001 x 12001, 0.05 %, 62 columns per entry: 12 us sorting, 20 this way; 16384 x 16384, power-law rows, 10: 55 and 40).
+// average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).
+// With more than four columns per entry of a group the distinct columns have the masks, not all of them, unless the whole conversion is one launch:
+// parts of up to 16384 columns, and fewer where a part would hold more than 640 entries, because one of a matrix with power-law rows holds many times the mean
+// (whole conversion, us, by masks or, beyond 32 columns per entry, by digits, and so; columns per entry in brackets: 12001 x 12001, 0.05 % (62): 21 12;
+// 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (5): 33.3 33.3; power-law rows,
+// 16384 x 16384 (10): 42 35, 20000 x 15000 (9): 51 42, 6000 x 6000 (4): 27 23.5).
 bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, gcoo::OrderPlan* plan)
 {
     *plan = {};
     if (m <= 0 || k <= 0 || nnz <= 0) return false;
     const int64_t g = (m + p - 1) / p, mean = nnz / g + 1;
-    if (k > 32 * mean) return false;
-    int32_t shift = 0;
-    while (((int64_t)1 << shift) < k && shift < (p <= 32 ? 12 : (p <= 64 ? 11 : 9))) ++shift;
-    while (shift > 7 && (mean << shift) / k > 1024) --shift;
+    if (k > 128 * mean) return false;
+    const int32_t most = p <= 32 ? 12 : (p <= 64 ? 11 : 9);
+    const bool ranked = k > 4 * mean && (k > ((int64_t)1 << most) || band.h > 0 || run_schedule_wanted(p));
+    int32_t shift = ranked ? 5 : 0;
+    while (((int64_t)1 << shift) < k && shift < (ranked ? 14 : most)) ++shift;
+    while (shift > 7 && (mean << shift) / k > (ranked ? 640 : 1024)) --shift;
     const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
     if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;
     // lists of rows of take_rows: those of the band schedule, else enough workgroups for four per compute unit
@@ -496,7 +502,8 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, gco
     rows = band.h > 0 ? band.h / gcoo::band_lists_of(band.v) : (rows > 64 ? 64 : rows);
     int64_t cap = mean / parts * 3 / 2 + 64;
     cap = cap < 256 ? 256 : (cap > gcoo::kOrderMaxCap ? gcoo::kOrderMaxCap : cap);
-    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), parts == 1 && band.h == 0 && !run_schedule_wanted(p)};
+    const int32_t keys = ranked ? (int32_t)1 << (shift < most ? shift : most) : 0;
+    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), !ranked && parts == 1 && band.h == 0 && !run_schedule_wanted(p), keys};
     return true;
 }
 
@@ -928,7 +935,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
         o.row_ptr = d_row_ptr; o.nnz = (int32_t)nnz; o.g = g; o.gIdxes_out = h->gIdxes(); o.nnzPerGroup_out = h->nnzPerGroup();
         o.row_start_out = h->row_start(); o.flags_out = h->take_flags();
-        (words == 1 ? gcoo::order_groups<1, true> : (words == 2 ? gcoo::order_groups<2, true> : gcoo::order_groups<8, true>))<<<
+        (words == 1 ? gcoo::order_groups<1, gcoo::kOrderFused> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderFused> : gcoo::order_groups<8, gcoo::kOrderFused>))<<<
             dim3((unsigned)g), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
@@ -951,8 +958,9 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.row_start = h->row_start(); o.cols = h->has_rows() ? h->row_cols() : d_cols; o.vals = h->has_rows() ? h->row_vals() : d_vals;
         o.m = m; o.lists = L.lists; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.gIdxes = h->gIdxes(); o.flags = t.flags; o.splits = t.splits;
         o.out = rows_out(h); o.uneven = marked ? h->uneven() : nullptr; o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
-        (words == 1 ? gcoo::order_groups<1, false> : (words == 2 ? gcoo::order_groups<2, false> : gcoo::order_groups<8, false>))<<<
-            dim3((unsigned)(g * L.plan.parts)), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+        auto order = L.plan.keys ? (words == 1 ? gcoo::order_groups<1, gcoo::kOrderRanked> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderRanked> : gcoo::order_groups<8, gcoo::kOrderRanked>))
+                                   : (words == 1 ? gcoo::order_groups<1, gcoo::kOrderMasks> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderMasks> : gcoo::order_groups<8, gcoo::kOrderMasks>));
+        order<<<dim3((unsigned)(g * L.plan.parts)), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
         e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
     } else

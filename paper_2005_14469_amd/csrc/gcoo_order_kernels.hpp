@@ -4,7 +4,7 @@
 // column (at most p bits), the place of an entry is what the columns before it hold, a prefix sum of popcounts, plus the
 // popcount of the mask below its row: two passes over the entries with a few LDS accesses each, no ranking, any order inside the rows.
 // The radix sort (gcoo_build_kernels.hpp) moves every entry through memory once per digit and walks it in tiles of 64
-// with eight ballots each; it stays for matrices whose columns far outnumber the entries of a group (order_plan() in gcoo_api.hip).
+// with eight ballots each; it stays for matrices whose columns far outnumber the entries of a group (more than 128 to one; order_plan() in gcoo_api.hip).
 //
 // A workgroup orders one part of a group: `ncols` columns.  Where the columns of every row ascend, which take_rows checks, a part is
 // one stretch of each row, and take_rows has noted where it begins; otherwise the workgroup looks through the whole group.
@@ -30,6 +30,7 @@ struct OrderPlan {
     int32_t list_rows;         // rows per workgroup of take_rows
     int32_t cap;
     bool fused;
+    int32_t keys;              // 0, or ranked: distinct columns of a window
 };
 
 struct TakeArgs {
@@ -191,6 +192,7 @@ struct OrderArgs {
 
 inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 {
+    if (plan.keys) return ((size_t)2 << plan.shift) / 8 + (size_t)plan.keys * (4 * words + 4) + (size_t)plan.cap * 9;
     const size_t ncols = (size_t)1 << plan.shift, spare = ncols < 256 ? ncols : 256;
     return (ncols * (words + 1) + 2 * spare) * 4 + (size_t)plan.cap * 9;
 }
@@ -204,10 +206,15 @@ inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 //
 // FUSED (one part per group, no band schedule): there is nothing to know about a group but its rows, so this is the whole conversion, one
 // launch instead of two (256 x 256: 4.2 + 6.4 us before, 6.3 so).
-template <int WORDS, bool FUSED>
+//
+// RANKED (many columns per entry): a part has many more columns, of which a bitmap says which hold an entry; the places of those among themselves take the
+// place of the columns, so that nothing is done per column but for a bit.  More distinct columns than plan.keys go window by window.
+enum OrderKind { kOrderMasks, kOrderFused, kOrderRanked };
+template <int WORDS, OrderKind KIND>
 __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
 {
     constexpr int ROWS = WORDS == 8 ? 256 : 32 * WORDS, WAVES = kOrderThreads / 64, EACH = 8;
+    constexpr bool FUSED = KIND == kOrderFused, RANKED = KIND == kOrderRanked;
     extern __shared__ uint32_t order_lds[];
     __shared__ int32_t seg[ROWS], off[ROWS];     // a row's place among the part's entries (or in the input), and what takes it to the input
     __shared__ int32_t wsum[WAVES], wsum2[WAVES];
@@ -219,12 +226,16 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
     const int64_t r0 = q * a.p;
     const int32_t rows = (int32_t)(a.m - r0 < a.p ? a.m - r0 : a.p);
     // A thread sums up `1 << ps` columns one after another: a word more for each such stretch keeps the threads on different banks.
-    const int32_t ps = shift > 8 ? shift - 8 : 0, spare = ((ncols - 1) >> ps) + 1;
-    uint32_t* mask = order_lds;                              // the masks, then the first places of the columns
-    int32_t* base = (int32_t*)(mask + ncols * WORDS + spare);
-    float* o_val = (float*)(base + ncols + spare);
-    auto mask_at = [&](int32_t col) { return mask + col * WORDS + (col >> ps); };
-    auto base_at = [&](int32_t col) { return base + col + (col >> ps); };
+    const int32_t ps = RANKED ? 31 : (shift > 8 ? shift - 8 : 0), spare = RANKED ? 0 : ((ncols - 1) >> ps) + 1;
+    const int32_t nbw = ncols >> 5;                          // RANKED: words of the part's columns; how many lie in front of each word
+    uint32_t* bits = order_lds;
+    int32_t* before = (int32_t*)(bits + nbw);
+    const int32_t keys = RANKED ? a.plan.keys : ncols;        // columns, or distinct columns of a window
+    uint32_t* mask = RANKED ? (uint32_t*)(before + nbw) : order_lds;       // the masks, then the first places of the columns
+    int32_t* base = (int32_t*)(mask + keys * WORDS + spare);
+    float* o_val = (float*)(base + keys + spare);
+    auto mask_at = [&](int32_t key) { return mask + key * WORDS + (RANKED ? 0 : key >> ps); };
+    auto base_at = [&](int32_t key) { return base + key + (RANKED ? 0 : key >> ps); };
     int32_t* o_col = (int32_t*)(o_val + a.plan.cap);
     uint8_t* o_row = (uint8_t*)(o_col + a.plan.cap);
 
@@ -264,7 +275,11 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         if (part == 0 && a.uneven && (f & kHeavy)) *a.uneven = 1u;
     }
     if (tid == 0) { below_s = 0; count_s = 0; }
-    for (int32_t i = tid; i < ncols * WORDS + spare; i += kOrderThreads) mask[i] = 0u;
+    if constexpr (RANKED) {
+        for (int32_t i = tid; i < nbw; i += kOrderThreads) bits[i] = 0u;
+    } else {
+        for (int32_t i = tid; i < ncols * WORDS + spare; i += kOrderThreads) mask[i] = 0u;
+    }
     // With one part the group is taken in the order of the input and nothing depends on the order in its rows.
     const bool in_order = !FUSED && parts > 1 && __syncthreads_or((int)(f & kUnsorted)) == 0;
     const bool some = !FUSED && parts > 1 && !in_order;                // entries of other parts are among those looked at
@@ -326,7 +341,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         }
     };
 
-    // the masks; what lies before the part and what is in it, where that is not known yet
+    // the masks (RANKED: the bitmap); what lies before the part and what is in it, where that is not known yet
     bool twice = false;
     int32_t below = 0, mine = 0;
     for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
@@ -343,9 +358,13 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
                 a.out.cols[g0 + i0 + x * kOrderThreads + tid] = c[x];
                 a.out.vals[g0 + i0 + x * kOrderThreads + tid] = v[x];
             }
-            const uint32_t bit = 1u << (r[x] & 31);
-            const uint32_t old = atomicOr(mask_at(c[x]) + (r[x] >> 5), bit);
-            twice |= (old & bit) != 0;
+            if constexpr (RANKED) {
+                atomicOr(&bits[c[x] >> 5], 1u << (c[x] & 31));
+            } else {
+                const uint32_t bit = 1u << (r[x] & 31);
+                const uint32_t old = atomicOr(mask_at(c[x]) + (r[x] >> 5), bit);
+                twice |= (old & bit) != 0;
+            }
         }
     }
     int32_t count = n;
@@ -353,122 +372,173 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         if (below) atomicAdd(&below_s, below);
         if (mine) atomicAdd(&count_s, mine);
     }
-    if (FUSED) {
-        if (bad) atomicOr(&below_s, 1);
-        twice = __syncthreads_or(twice) != 0;
-        if (tid == 0) a.flags_out[q] = below_s ? kBadColumn : 0u;
-    } else {
-        twice = __syncthreads_or(twice) != 0;
-    }
+    if (FUSED && bad) atomicOr(&below_s, 1);
+    if (!RANKED) twice = __syncthreads_or(twice) != 0;
+    else __syncthreads();
+    if (FUSED && tid == 0) a.flags_out[q] = below_s ? kBadColumn : 0u;
     if (some) {
         out0 = g0 + below_s;
         count = count_s;
         if (count == 0) return;                              // the whole workgroup
     }
-    if (twice) {
-        // counts instead of masks
-        for (int32_t i = tid; i < ncols + spare; i += kOrderThreads) base[i] = 0;
-        __syncthreads();
-        for (int32_t i = tid; i < n; i += kOrderThreads) {
-            int32_t ri, ci;
-            float vi;
-            take(i, &ri, &ci, &vi);
-            if (ci >= 0 && ci < ncols) atomicAdd(base_at(ci), 1);
-        }
-        __syncthreads();
-    }
-    // the first place of every column
-    {
-        const int32_t i0 = tid << ps, i1 = i0 + (1 << ps) < ncols ? i0 + (1 << ps) : ncols;
-        auto entries = [&](int32_t col) {
-            if (twice) return *base_at(col);
-            int32_t x = 0;
-#pragma unroll
-            for (int w = 0; w < WORDS; ++w) x += __popc(mask_at(col)[w]);
-            return x;
-        };
-        int32_t sum = 0;
-#pragma unroll 4
-        for (int32_t i = i0; i < i1; ++i) sum += entries(i);
-        int32_t incl = sum;
+    // Exclusive prefix sum over the workgroup; *all: the total.  (wsum was read before the barrier above, or the one at the end here.)
+    auto prefix = [&](int32_t x, int32_t* all) {
+        int32_t incl = x;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int32_t t = __shfl_up(incl, d, 64);
             if (lane >= d) incl += t;
         }
-        if (lane == 63) wsum[wv] = incl;                     // (read before the barrier above)
+        if (lane == 63) wsum[wv] = incl;
         __syncthreads();
-        int32_t at = incl - sum;
+        int32_t at = incl - x;
         for (int j = 0; j < wv; ++j) at += wsum[j];
-#pragma unroll 4
+        *all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        static_assert(WAVES == 4, "");
+        return at;
+    };
+    int32_t distinct = ncols;
+    if constexpr (RANKED) {
+        const int32_t per = (nbw + kOrderThreads - 1) / kOrderThreads, i0 = tid * per < nbw ? tid * per : nbw, i1 = i0 + per < nbw ? i0 + per : nbw;
+        int32_t sum = 0;
+        for (int32_t i = i0; i < i1; ++i) sum += __popc(bits[i]);
+        int32_t at = prefix(sum, &distinct);
         for (int32_t i = i0; i < i1; ++i) {
-            const int32_t x = entries(i);
-            *base_at(i) = at;
-            at += x;
+            before[i] = at;
+            at += __popc(bits[i]);
         }
     }
-    __syncthreads();
-    if (twice) {
-        // 64 entries at a time, in input order
-        if (wv > 0) return;
-        for (int32_t t = 0; t < n; t += 64) {
-            int32_t ri = 0, ci = -1;
-            float vi = 0.0f;
-            if (t + lane < n) take(t + lane, &ri, &ci, &vi);
-            const bool act = ci >= 0 && ci < ncols;
-            uint64_t same = __ballot(act);
-            for (int b = 0; b < shift; ++b) {
-                const bool bit = (ci >> b) & 1;
-                const uint64_t bb = __ballot(act && bit);
-                same &= bit ? bb : ~bb;
+    const bool staged = count <= a.plan.cap && (!RANKED || distinct <= keys);
+    for (int32_t w0 = 0; w0 < distinct; w0 += keys) {        // (one turn where a window holds all, always so without RANKED)
+        const int32_t nk = distinct - w0 < keys ? distinct - w0 : keys;
+        // what stands for a column: itself, or its place among the distinct ones of the window
+        auto key_of = [&](int32_t col) -> int32_t {
+            if (!RANKED) return col;
+            return before[col >> 5] + __popc(bits[col >> 5] & ((1u << (col & 31)) - 1u)) - w0;
+        };
+        auto ours = [&](int32_t col) { return !some || (col >= 0 && col < ncols); };
+        int32_t key[EACH];
+        if constexpr (RANKED) {
+            for (int32_t i = tid; i < nk * WORDS; i += kOrderThreads) mask[i] = 0u;
+            __syncthreads();
+            twice = false;
+            for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
+                if (n > EACH * kOrderThreads) take_some(i0);
+#pragma unroll
+                for (int x = 0; x < EACH; ++x) key[x] = i0 + x * kOrderThreads + tid < n && ours(c[x]) ? key_of(c[x]) : -1;
+#pragma unroll
+                for (int x = 0; x < EACH; ++x) {
+                    if (key[x] < 0 || key[x] >= nk) continue;
+                    const uint32_t bit = 1u << (r[x] & 31);
+                    const uint32_t old = atomicOr(mask_at(key[x]) + (r[x] >> 5), bit);
+                    twice |= (old & bit) != 0;
+                }
             }
-            const int32_t before = __popcll(same & lanemask_lt());
-            int32_t slot = 0;
-            volatile int32_t* next = base_at(act ? ci : 0);
-            if (act) slot = *next;
-            __builtin_amdgcn_wave_barrier();
-            if (act && before == 0) *next = slot + __popcll(same);
-            __builtin_amdgcn_wave_barrier();
-            if (act) {
-                const int32_t to = out0 + slot + before;
-                a.dst_cols[to] = c0 + ci;
-                a.dst_rows[to] = (int32_t)r0 + ri;
-                a.dst_vals[to] = vi;
+            twice = __syncthreads_or(twice) != 0;
+        }
+        if (twice) {
+            // counts instead of masks
+            for (int32_t i = tid; i < keys + spare; i += kOrderThreads) base[i] = 0;
+            __syncthreads();
+            for (int32_t i = tid; i < n; i += kOrderThreads) {
+                int32_t ri, ci;
+                float vi;
+                take(i, &ri, &ci, &vi);
+                const int32_t ki = ours(ci) ? key_of(ci) : -1;
+                if (ki >= 0 && ki < nk) atomicAdd(base_at(ki), 1);
+            }
+            __syncthreads();
+        }
+        // the first place of every column
+        int32_t entries_of_window;
+        {
+            const int32_t per = RANKED ? (nk + kOrderThreads - 1) / kOrderThreads : 1 << ps;
+            const int32_t i0 = RANKED ? (tid * per < nk ? tid * per : nk) : tid << ps, i1 = i0 + per < nk ? i0 + per : nk;
+            auto entries = [&](int32_t k) {
+                if (twice) return *base_at(k);
+                int32_t x = 0;
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) x += __popc(mask_at(k)[w]);
+                return x;
+            };
+            int32_t sum = 0;
+#pragma unroll 4
+            for (int32_t i = i0; i < i1; ++i) sum += entries(i);
+            int32_t at = prefix(sum, &entries_of_window);
+#pragma unroll 4
+            for (int32_t i = i0; i < i1; ++i) {
+                const int32_t x = entries(i);
+                *base_at(i) = at;
+                at += x;
             }
         }
-        return;
-    }
-    const bool staged = count <= a.plan.cap;
-    for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
-        if (n > EACH * kOrderThreads) take_some(i0);         // (else they are still there)
+        __syncthreads();
+        if (twice) {
+            // 64 entries at a time, in input order
+            for (int32_t t = 0; t < n && wv == 0; t += 64) {
+                int32_t ri = 0, ci = -1;
+                float vi = 0.0f;
+                if (t + lane < n) take(t + lane, &ri, &ci, &vi);
+                const int32_t ki = t + lane < n && ci >= 0 && ci < ncols ? key_of(ci) : -1;
+                const bool act = ki >= 0 && ki < nk;
+                uint64_t same = __ballot(act);
+                for (int b = 0; (keys - 1) >> b; ++b) {
+                    const bool bit = (ki >> b) & 1;
+                    const uint64_t bb = __ballot(act && bit);
+                    same &= bit ? bb : ~bb;
+                }
+                const int32_t ahead = __popcll(same & lanemask_lt());
+                int32_t slot = 0;
+                volatile int32_t* next = base_at(act ? ki : 0);
+                if (act) slot = *next;
+                __builtin_amdgcn_wave_barrier();
+                if (act && ahead == 0) *next = slot + __popcll(same);
+                __builtin_amdgcn_wave_barrier();
+                if (act) {
+                    const int32_t to = out0 + slot + ahead;
+                    a.dst_cols[to] = c0 + ci;
+                    a.dst_rows[to] = (int32_t)r0 + ri;
+                    a.dst_vals[to] = vi;
+                }
+            }
+        } else {
+            for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
+                if (n > EACH * kOrderThreads) take_some(i0);         // (else they are still there)
 #pragma unroll
-        for (int x = 0; x < EACH; ++x) {
-            if (i0 + x * kOrderThreads + tid >= n) break;
-            if (some && (c[x] < 0 || c[x] >= ncols)) continue;
-            int32_t at = *base_at(c[x]);
+                for (int x = 0; x < EACH; ++x) {
+                    if (i0 + x * kOrderThreads + tid >= n) break;
+                    if (!ours(c[x])) continue;
+                    const int32_t ki = RANKED && n <= EACH * kOrderThreads ? key[x] : key_of(c[x]);
+                    if (RANKED && (ki < 0 || ki >= nk)) continue;
+                    int32_t at = *base_at(ki);
 #pragma unroll
-            for (int w = 0; w < WORDS; ++w) {
-                const uint32_t word = mask_at(c[x])[w];
-                const int32_t b = r[x] - 32 * w;
-                at += __popc(WORDS == 1 || b < 32 ? (b <= 0 ? 0u : word & ((1u << b) - 1u)) : word);
+                    for (int w = 0; w < WORDS; ++w) {
+                        const uint32_t word = mask_at(ki)[w];
+                        const int32_t b = r[x] - 32 * w;
+                        at += __popc(WORDS == 1 || b < 32 ? (b <= 0 ? 0u : word & ((1u << b) - 1u)) : word);
+                    }
+                    if (staged) {
+                        o_val[at] = v[x];
+                        o_col[at] = c0 + c[x];
+                        o_row[at] = (uint8_t)r[x];
+                    } else {
+                        a.dst_cols[out0 + at] = c0 + c[x];
+                        a.dst_rows[out0 + at] = (int32_t)r0 + r[x];
+                        a.dst_vals[out0 + at] = v[x];
+                    }
+                }
             }
             if (staged) {
-                o_val[at] = v[x];
-                o_col[at] = c0 + c[x];
-                o_row[at] = (uint8_t)r[x];
-            } else {
-                a.dst_cols[out0 + at] = c0 + c[x];
-                a.dst_rows[out0 + at] = (int32_t)r0 + r[x];
-                a.dst_vals[out0 + at] = v[x];
+                __syncthreads();
+                for (int32_t i = tid; i < count; i += kOrderThreads) {
+                    a.dst_cols[out0 + i] = o_col[i];
+                    a.dst_rows[out0 + i] = (int32_t)r0 + (int32_t)o_row[i];
+                    a.dst_vals[out0 + i] = o_val[i];
+                }
             }
         }
-    }
-    if (!staged) return;
-    __syncthreads();
-    for (int32_t i = tid; i < count; i += kOrderThreads) {
-        a.dst_cols[out0 + i] = o_col[i];
-        a.dst_rows[out0 + i] = (int32_t)r0 + (int32_t)o_row[i];
-        a.dst_vals[out0 + i] = o_val[i];
+        out0 += entries_of_window;
+        if (RANKED) __syncthreads();                         // the masks and the sums are read before the next window's
     }
 }
 

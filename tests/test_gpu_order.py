@@ -1,5 +1,5 @@
 """Ordering a CSR input by column masks where it can go wrong: one part and many, a part that is one column short or over, parts of more
-entries than are put in order in LDS, one, two and eight mask words per column, empty rows at either end, rows whose columns do not
+entries than are put in order in LDS (of more distinct columns than a window holds), one, two and eight mask words per column, empty rows at either end, rows whose columns do not
 ascend, coordinates that occur twice.  Bit for bit against the CPU oracle, and the product that the rows and bands give."""
 import numpy as np
 import pytest
@@ -37,7 +37,10 @@ def _csr(m, k, density, kind, seed):
 @pytest.mark.parametrize("kind", ["sorted", "unsorted", "twice"])
 @pytest.mark.parametrize("m,k,density,p", [(1, 1, 1.0, 1), (3, 130, 0.5, 32), (500, 127, 0.2, 32), (500, 128, 0.2, 33), (300, 4096, 0.02, 32),
                                            (300, 4097, 0.02, 31), (300, 8193, 0.01, 32), (130, 2049, 0.05, 64), (400, 300, 0.9, 64),
-                                           (400, 1000, 0.3, 65), (600, 513, 0.1, 256), (1500, 700, 0.03, 8), (2100, 900, 0.05, 1)])
+                                           (400, 1000, 0.3, 65), (600, 513, 0.1, 256), (1500, 700, 0.03, 8), (2100, 900, 0.05, 1),
+                                           # more than four columns per entry of a group: by the places of the distinct columns
+                                           (300, 4097, 0.003, 31), (300, 70001, 0.0004, 32), (700, 5000, 0.0005, 64), (520, 9000, 0.0006, 256), (900, 66000, 0.00004, 8),
+                                           (2000, 40, 0.004, 1), (70, 1025, 0.002, 33), (3000, 3000, 0.001, 65)])
 def test_ordered_by_masks(m, k, density, p, kind):
     print(f"order: {m}x{k} d={density} p={p} {kind}", flush=True)
     rp, ci, va = _csr(m, k, density, kind, seed=m + k + p)
