@@ -60,11 +60,11 @@ constexpr int kMaxDevices = 64;
 
 // A number that a kernel hands to the host in the middle of a call: the kernel writes it to pinned host memory, so that no copy
 // stands between the kernel and the host's wait for the stream.  kHostSlots such calls may be under way at once, over all devices and threads; a call takes a
-// slot for its own use and gives it back when it returns, and waits for one while all are taken (fails where all are lost).  Each slot has a word of device memory as
+// slot for its own use and gives it back when it returns, and waits for one while all are taken (fails where all are lost).  Each slot has words of device memory as
 // well (per device, zero between calls), in which the workgroups of a kernel count themselves.  The pinned page is allocated once per process.
 constexpr int kHostSlots = 64;
 constexpr size_t kHostSlotWords = 8;
-__device__ unsigned long long g_tickets[kHostSlots];
+__device__ __align__(128) unsigned long long g_tickets[kHostSlots][(gcoo::kTicketWords + 1) * gcoo::kTicketStride];
 std::atomic<uint64_t> g_slots_taken{0};
 std::atomic<int> g_slots_lost{0};
 
@@ -112,12 +112,12 @@ public:
             if (g_slots_taken.compare_exchange_weak(taken, taken | 1ull << i, std::memory_order_acq_rel)) { i_ = i; break; }
         }
         host_ += (size_t)i_ * kHostSlotWords;
-        ticket_ += i_;
+        ticket_ += (size_t)i_ * (gcoo::kTicketWords + 1) * gcoo::kTicketStride;
         __atomic_store_n(host_, 0ull, __ATOMIC_RELEASE);
         return GCOO_OK;
     }
     unsigned long long* host() const { return host_; }
-    unsigned long long* ticket() const { return ticket_; }
+    gcoo::DenseTicket ticket() const { return {ticket_, gcoo::kTicketWords}; }
     // After the launch.  Where the wait fails nobody gets the slot again: the kernel may still write there.
     int wait(hipStream_t s, unsigned long long* answer)
     {
@@ -1095,8 +1095,8 @@ gcoo::DenseCounts dense_counts(void* buf, const Layout& L)
             reinterpret_cast<int32_t*>(base + L.nnzPerGroup), reinterpret_cast<unsigned long long*>(base + L.counter)};
 }
 
-// Step 1 of Algorithm 1.  `ticket` is zero before and after; `host` receives the sum, or is null.
-int launch_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, unsigned long long* ticket,
+// Step 1 of Algorithm 1.  `host` receives the sum, or is null.
+int launch_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, gcoo::DenseTicket ticket,
                        unsigned long long* host, hipStream_t s)
 {
     const int64_t g = (m + p - 1) / p;
@@ -1170,7 +1170,7 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
     rc = launch_build_schedule(h, h->base + h->L.persistent, s);
     if (rc != GCOO_OK) { delete h; return rc; }
     if (inner_buf) {
-        rc = launch_dense_count(m, k, A_dev, lda, kInnerP, inner_buf, inner_ticket, nullptr, s);
+        rc = launch_dense_count(m, k, A_dev, lda, kInnerP, inner_buf, {inner_ticket, 1}, nullptr, s);
         if (rc == GCOO_OK)
             rc = from_dense_counted(m, k, nnz, A_dev, lda, kInnerP, inner_buf, inner_buf, dev_buf_bytes - own, stream, &h->inner);
         if (rc != GCOO_OK) { delete h; return rc; }

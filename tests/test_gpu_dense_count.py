@@ -48,6 +48,22 @@ def test_counts_and_fill(m, k, p, density):
             assert len(e["values"]) == 0 and not e["gIdxes"].any()
 
 
+@pytest.mark.parametrize("workgroups", [1, 2, 31, 32, 33, 63, 65, 1023, 1024, 1025, 2500])
+def test_arrivals_of_few_and_many_workgroups(workgroups):
+    """The workgroups of a counting launch arrive at up to 32 words, which are zero again behind it: counts and offsets of launches with fewer
+    workgroups than words, one more, and more pieces than workgroups, several times over."""
+    print(f"dense count: {workgroups} pieces", flush=True)
+    rng = np.random.default_rng(workgroups)
+    Ah = (rng.random((16 * workgroups, 8)) < 0.3).astype(np.float32)
+    A, few = torch.from_numpy(Ah).to(DEV), torch.from_numpy(Ah[:workgroups]).to(DEV)
+    want = orc.gcoo_from_dense(Ah[:workgroups], 1)
+    for _ in range(3):
+        assert binding.gcoo_dense_nnz(A) == np.count_nonzero(Ah)
+        e = binding.gcoo_from_dense(few, 1).export()
+        assert np.array_equal(e["gIdxes"], want.gIdxes) and np.array_equal(e["nnzPerGroup"], want.nnzPerGroup)
+        assert np.array_equal(e["rows"], want.rows) and np.array_equal(e["cols"], want.cols)
+
+
 @pytest.mark.parametrize("m,k,p", [(700, 900, 65), (130, 1031, 128), (3000, 260, 256)])
 def test_fill_of_tall_groups_in_a_graph(m, k, p):
     """gcoo_from_dense_counted() waits for nothing and can be recorded, for groups of more than 64 rows too, whose regrouped copy is counted
