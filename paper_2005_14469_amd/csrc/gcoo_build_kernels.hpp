@@ -325,7 +325,7 @@ __global__ __launch_bounds__(WAVES * kWave) void sort_groups_by_col_digit(
 // Step 1 (count_dense_blocks): entries != 0 per block; the last workgroup to end turns the counts into the first slot of
 // every block (exclusive prefix sum, groups and blocks in order), gIdxes and nnzPerGroup.
 // Bound: reading A once.  The workgroups meet only at the end of each (an atomic per wave on one address took 105 us for 4000 x 4000; see arrive()
-// for one per workgroup).  With the scan behind it: 14.6 us.
+// for one per workgroup).  With the scan behind it: 14.6 us, 15.1 with the masks.
 // ---------------------------------------------------------------------------------------------
 constexpr int kDenseThreads = 256;
 constexpr int kDenseWorkgroups = 1024;       // of a counting launch, at most
@@ -405,7 +405,34 @@ struct DenseCounts {
     int32_t* gIdxes;           // [g + 1]
     int32_t* nnzPerGroup;      // [g]
     unsigned long long* stats; // nnz, entries of the largest group
+    uint64_t* masks;           // [g * k] the rows of a group that have an entry in a column, bit i for its i-th row; or null
 };
+
+// The rows among [0, nr), at most 64, in which the VW columns at `a` have an entry.  Eight loads in flight.
+template <int VW>
+__device__ __forceinline__ void dense_masks(const float* __restrict__ a, int64_t lda, int32_t nr, uint64_t* bits)
+{
+#pragma unroll
+    for (int u = 0; u < VW; ++u) bits[u] = 0;
+    int32_t r = 0;
+    for (; r + 8 <= nr; r += 8, a += 8 * lda) {
+        DenseVec<VW> v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = load_dense<VW>(a + x * lda);
+#pragma unroll
+        for (int u = 0; u < VW; ++u) {
+            uint32_t eight = 0;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) eight |= (v[x].x[u] != 0.0f) ? 1u << x : 0u;
+            bits[u] |= (uint64_t)eight << r;
+        }
+    }
+    for (; r < nr; ++r, a += lda) {
+        const DenseVec<VW> v = load_dense<VW>(a);
+#pragma unroll
+        for (int u = 0; u < VW; ++u) bits[u] |= (uint64_t)(v.x[u] != 0.0f) << r;
+    }
+}
 
 // Entries != 0 in rows [r0, r1), columns c .. c + VW - 1 (c < k).  Eight loads in flight.
 template <int VW>
@@ -433,8 +460,8 @@ __device__ __forceinline__ int32_t count_dense_tile(const float* __restrict__ A,
 }
 
 // Item i = q*nblk + b, items strided over the workgroups; thread t of block b owns columns (b*kDenseThreads + t)*VW .. +VW-1 of the
-// band (k % VW == 0 when VW > 1).  `host` may be null.
-template <int VW>
+// band (k % VW == 0 when VW > 1).  `host` may be null.  MASKS: out.masks is written as well (p <= 64).
+template <int VW, bool MASKS>
 __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k, int32_t p,
                                                                      int64_t nblk, int64_t g, DenseCounts out,
                                                                      DenseTicket ticket, unsigned long long* __restrict__ host)
@@ -447,7 +474,21 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
         const int64_t q = i / nblk, b = i - q * nblk;
         const int64_t c = (b * kDenseThreads + tid) * VW;
         const int64_t r0 = q * p, r1 = (r0 + p < m) ? r0 + p : m;
-        const int32_t tot = block_sum_256(c < k ? count_dense_tile<VW>(A, lda, r0, r1, c) : 0, part);
+        int32_t n = 0;
+        if (c < k) {
+            if constexpr (MASKS) {
+                uint64_t bits[VW];
+                dense_masks<VW>(A + r0 * lda + c, lda, (int32_t)(r1 - r0), bits);
+#pragma unroll
+                for (int u = 0; u < VW; ++u) n += __popcll(bits[u]);
+                uint64_t* to = out.masks + q * k + c;
+#pragma unroll
+                for (int u = 0; u < VW; ++u) to[u] = bits[u];
+            } else {
+                n = count_dense_tile<VW>(A, lda, r0, r1, c);
+            }
+        }
+        const int32_t tot = block_sum_256(n, part);
         // written where every XCD sees it, before this workgroup's arrival is counted
         if (tid == 0) __hip_atomic_store(&out.blk[i], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -523,21 +564,15 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
 // entries of its columns, a workgroup-wide exclusive prefix sum of those counts gives the first
 // slot of every column, and the thread writes each entry to its final slot.  No sort, no atomics: the slot of an entry is a
 // function of the matrix alone.
-// SMALL (at most 64 rows per group): the count leaves a bit per element behind, and only the elements that are entries
+// SMALL (at most 64 rows per group): a first walk leaves a bit per element behind, and only the elements that are entries
 // are read a second time, the next one of each column together; taller groups walk the columns again.
-// (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)
+// (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)  Where the count has left the bits in memory fill_dense_masked() does this step.
 // The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..2] and, where given, the
 // ticket of the count that follows.
 // ---------------------------------------------------------------------------------------------
-template <int VW, bool SMALL>
-__global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
-                                                                    int32_t p, int64_t nblk, int64_t g, DenseCounts from, DenseCounts to,
-                                                                    uint32_t* __restrict__ zeroed, unsigned long long* __restrict__ ticket,
-                                                                    float* __restrict__ values,
-                                                                    int32_t* __restrict__ rows, int32_t* __restrict__ cols)
+__device__ __forceinline__ void place_dense_counts(const DenseCounts& from, const DenseCounts& to, int64_t g, uint32_t* zeroed, unsigned long long* ticket)
 {
-    __shared__ int32_t wsum[4];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x;
     if (blockIdx.x == 0 && tid < 3) zeroed[tid] = 0u;
     if (blockIdx.x == 0 && tid == 3 && ticket) *ticket = 0ull;
     if (from.gIdxes != to.gIdxes) {
@@ -547,6 +582,18 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
             if (q < g) to.nnzPerGroup[q] = from.nnzPerGroup[q];
         }
     }
+}
+
+template <int VW, bool SMALL>
+__global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k,
+                                                                    int32_t p, int64_t nblk, int64_t g, DenseCounts from, DenseCounts to,
+                                                                    uint32_t* __restrict__ zeroed, unsigned long long* __restrict__ ticket,
+                                                                    float* __restrict__ values,
+                                                                    int32_t* __restrict__ rows, int32_t* __restrict__ cols)
+{
+    __shared__ int32_t wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    place_dense_counts(from, to, g, zeroed, ticket);
     if (nblk == 0 || (int64_t)blockIdx.x >= g * nblk) return;            // the whole workgroup
     const int64_t q = blockIdx.x / nblk, b = blockIdx.x - q * nblk;      // blockIdx.x = q*nblk + b
     const int64_t c = (b * kDenseThreads + tid) * VW;
@@ -554,38 +601,32 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
     const float* col0 = A + r0 * lda + c;
     uint64_t bits[VW];
     int32_t n[VW];
+    if constexpr (SMALL) {
+        if (c < k) {
+            dense_masks<VW>(col0, lda, (int32_t)(r1 - r0), bits);
+        } else {
 #pragma unroll
-    for (int u = 0; u < VW; ++u) {
-        n[u] = 0;
-        bits[u] = 0;
-    }
-    if (c < k) {
-        const float* a = col0;
-        const int32_t nr = (int32_t)(r1 - r0);
-        int32_t r = 0;
-        for (; r + 8 <= nr; r += 8, a += 8 * lda) {
-            DenseVec<VW> v[8];
+            for (int u = 0; u < VW; ++u) bits[u] = 0;
+        }
+    } else {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) v[x] = load_dense<VW>(a + x * lda);
+        for (int u = 0; u < VW; ++u) n[u] = 0;
+        if (c < k) {
+            const float* a = col0;
+            int64_t r = r0;
+            for (; r + 8 <= r1; r += 8, a += 8 * lda) {
+                DenseVec<VW> v[8];
 #pragma unroll
-            for (int u = 0; u < VW; ++u) {
-                if constexpr (SMALL) {
-                    uint32_t eight = 0;
+                for (int x = 0; x < 8; ++x) v[x] = load_dense<VW>(a + x * lda);
 #pragma unroll
-                    for (int x = 0; x < 8; ++x) eight |= (v[x].x[u] != 0.0f) ? 1u << x : 0u;
-                    bits[u] |= (uint64_t)eight << r;
-                } else {
+                for (int u = 0; u < VW; ++u)
 #pragma unroll
                     for (int x = 0; x < 8; ++x) n[u] += (v[x].x[u] != 0.0f) ? 1 : 0;
-                }
             }
-        }
-        for (; r < nr; ++r, a += lda) {
-            const DenseVec<VW> v = load_dense<VW>(a);
+            for (; r < r1; ++r, a += lda) {
+                const DenseVec<VW> v = load_dense<VW>(a);
 #pragma unroll
-            for (int u = 0; u < VW; ++u) {
-                if constexpr (SMALL) bits[u] |= (uint64_t)(v.x[u] != 0.0f) << r;
-                else n[u] += (v.x[u] != 0.0f) ? 1 : 0;
+                for (int u = 0; u < VW; ++u) n[u] += (v.x[u] != 0.0f) ? 1 : 0;
             }
         }
     }
@@ -647,6 +688,67 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
                 }
             }
         }
+    }
+}
+
+// The same where the count left its masks behind: A is read only where it has entries.  The entries of a workgroup are listed in LDS first,
+// kMaskedList at a time, so that the reads of A are in flight together and the arrays are written whole lines at a time.  Bound: the latency of the masks, the
+// list and the entries in turn.  (4000 x 4000, 2 %, p = 32: 8.3 us, where fill_dense_blocks takes 19; the masks add 0.5 us to the count.)
+constexpr int kMaskedList = 4096;
+template <int VW>
+__global__ __launch_bounds__(kDenseThreads) void fill_dense_masked(const float* __restrict__ A, int64_t lda, int64_t k, int32_t p, int64_t nblk, int64_t g,
+                                                                    DenseCounts from, DenseCounts to, uint32_t* __restrict__ zeroed,
+                                                                    float* __restrict__ values, int32_t* __restrict__ rows, int32_t* __restrict__ cols)
+{
+    static_assert(kDenseThreads * VW <= 1024, "a place in the block is listed as row * 1024 + column, in 16 bits");
+    __shared__ uint16_t list[kMaskedList];
+    __shared__ int32_t wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    place_dense_counts(from, to, g, zeroed, nullptr);
+    if (nblk == 0 || (int64_t)blockIdx.x >= g * nblk) return;            // the whole workgroup
+    const int64_t q = blockIdx.x / nblk, b = blockIdx.x - q * nblk;
+    const int64_t c0 = b * kDenseThreads * VW, c = c0 + tid * VW, r0 = q * p;
+    uint64_t bits[VW];
+    int32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < VW; ++u) {
+        bits[u] = c < k ? from.masks[q * k + c + u] : 0;
+        mine += __popcll(bits[u]);
+    }
+    const int32_t first = from.blk[blockIdx.x];
+    int32_t at = mine;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t t = __shfl_up(at, d, kWave);
+        if (lane >= d) at += t;
+    }
+    if (lane == 63) wsum[w] = at;
+    __syncthreads();
+    at -= mine;
+    for (int j = 0; j < w; ++j) at += wsum[j];
+    const int32_t total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    const float* block = A + r0 * lda + c0;
+    for (int32_t done = 0; done < total; done += kMaskedList) {
+        const int32_t end = done + kMaskedList;
+#pragma unroll
+        for (int u = 0; u < VW; ++u) {
+            while (bits[u] && at < end) {
+                list[at - done] = (uint16_t)(((__ffsll((unsigned long long)bits[u]) - 1) << 10) | (tid * VW + u));
+                bits[u] &= bits[u] - 1;
+                ++at;
+            }
+        }
+        __syncthreads();
+        const int32_t n = total - done < kMaskedList ? total - done : kMaskedList;
+#pragma unroll 4
+        for (int32_t e = tid; e < n; e += kDenseThreads) {
+            const int32_t r = list[e] >> 10, cc = list[e] & 1023;
+            const int64_t to_slot = (int64_t)first + done + e;
+            values[to_slot] = block[r * lda + cc];
+            rows[to_slot] = (int32_t)r0 + r;
+            cols[to_slot] = (int32_t)c0 + cc;
+        }
+        __syncthreads();
     }
 }
 

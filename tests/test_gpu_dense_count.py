@@ -48,6 +48,35 @@ def test_counts_and_fill(m, k, p, density):
             assert len(e["values"]) == 0 and not e["gIdxes"].any()
 
 
+@pytest.mark.parametrize("p", [7, 8, 9, 31, 32, 63, 64, 65])
+@pytest.mark.parametrize("k,density", [(511, 1.0), (512, 1.0), (513, 0.6), (1024, 0.5), (1025, 0.02)])
+def test_fill_from_the_masks_of_the_count(p, k, density):
+    """8 to 64 rows per group are filled from a bit per element that the count left in its buffer, other heights and a count in the matrix's
+    own buffer by reading the matrix again: both against the oracle, rows that are longer than k, columns in fours and one by one, blocks of less than a list, of a
+    whole one (8 x 512 entries) and of many, with and without an entry in the last row of a group."""
+    print(f"dense fill: k={k} p={p} density={density}", flush=True)
+    rng = np.random.default_rng(k + p)
+    m = 2 * p + 3
+    Ah = (rng.standard_normal((m, k)) * (rng.random((m, k)) < density)).astype(np.float32)
+    Ah[p - 1] = 0.0
+    L, stream = binding.lib(), torch.cuda.current_stream().cuda_stream
+    for pitch, off in ((k + (-k % 4) + 4, 0), (k + 3, 1)):
+        whole = torch.full((m * pitch + off,), 7.0, device=DEV)
+        A = whole[off:].view(m, pitch)[:, :k]
+        A.copy_(torch.from_numpy(Ah))
+        want = orc.gcoo_from_dense(Ah, p)
+        handles = [binding.gcoo_from_dense(A, p)]
+        buf = torch.empty(L.gcoo_device_bytes(m, k, want.nnz, p), dtype=torch.uint8, device=DEV)
+        out = C.c_void_p()
+        assert L.gcoo_from_dense(m, k, A.data_ptr(), pitch, p, buf.data_ptr(), buf.numel(), stream, C.byref(out)) == 0
+        handles.append(binding.GcooMatrix(out.value, buf))
+        for h in handles:
+            e = h.export()
+            assert np.array_equal(e["values"].view(np.uint32), want.values.view(np.uint32))
+            assert np.array_equal(e["rows"], want.rows) and np.array_equal(e["cols"], want.cols)
+            assert np.array_equal(e["gIdxes"], want.gIdxes) and np.array_equal(e["nnzPerGroup"], want.nnzPerGroup)
+
+
 @pytest.mark.parametrize("workgroups", [1, 2, 31, 32, 33, 63, 65, 1023, 1024, 1025, 2500])
 def test_arrivals_of_few_and_many_workgroups(workgroups):
     """The workgroups of a counting launch arrive at up to 32 words, which are zero again behind it: counts and offsets of launches with fewer
