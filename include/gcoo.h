@@ -100,8 +100,8 @@ size_t gcoo_device_bytes(int64_t m, int64_t k, int64_t nnz, int32_t p);
  *   col_idx[nnz]  each in [0, k); columns of a row may be unsorted and may repeat
  *   vals[nnz]     fp32; every stored entry is kept, explicit zeros included (nnz is preserved)
  *   src_on_device 0: the three arrays are host pointers (validated, then copied to the device);
- *                 1: device pointers (not validated; row_ptr[m] is read back, which synchronises
- *                    `stream`)
+ *                 1: device pointers (not validated; row_ptr[m] is read back, for which the call waits
+ *                    until the work before it on `stream` has ended)
  *   p             rows per group, 1..GCOO_MAX_P
  *   dev_buf       caller-owned device memory, 256-byte aligned, >= gcoo_device_bytes(m,k,nnz,p)
  * The conversion kernels (the entries put into the order of the groups by column masks or by a stable radix sort, a copy

@@ -50,7 +50,7 @@ __device__ __forceinline__ void tell_host(unsigned long long* host, unsigned lon
 __global__ void read_entry_count(const int32_t* __restrict__ row_ptr, int64_t m, unsigned long long* __restrict__ host)
 {
     const int32_t last = row_ptr[m];
-    tell_host(host, last < 0 ? ~0ull : (unsigned long long)last);
+    tell_host(host, last < 0 ? 1ull << 62 : (unsigned long long)last);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -553,7 +553,10 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
         for (int j = 1; j < 4; ++j) mx = part[j] > mx ? part[j] : mx;
         out.stats[0] = (unsigned long long)carry;
         out.stats[1] = (unsigned long long)mx;
-        if (host) tell_host(host, (unsigned long long)carry);
+        if (host) {
+            wait_for_memory();
+            tell_host(host, (unsigned long long)carry);
+        }
     }
 }
 
@@ -774,7 +777,10 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_total(const float* 
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long all;
-        if (arrive(ticket, wide[0] + wide[1] + wide[2] + wide[3], &all)) tell_host(host, all);   // integer sum: order-free
+        if (arrive(ticket, wide[0] + wide[1] + wide[2] + wide[3], &all)) {   // integer sum: order-free
+            wait_for_memory();
+            tell_host(host, all);
+        }
     }
 }
 

@@ -208,6 +208,25 @@ def slot_wait_fails(host):
     assert host.log() == []
 
 
+def looks_before_waiting(host):
+    """A conversion that goes on behind its counting kernel takes the number as soon as it is there and waits for the stream only where it does not
+    come; a wait that fails is reported, and a stream that ended without a number is not taken for one."""
+    m, k, nnz, dev = 300, 700, 1234, 1 << 20
+    calls = [lambda n, h: host.L.gcoo_from_csr(m, k, dev, dev, dev, 1, 8, 1 << 30, 1 << 50, None, C.byref(h)),
+             lambda n, h: host.L.gcoo_dense_count(m, k, dev, k, 8, dev, 1 << 50, None, C.byref(n))]
+    for call in calls:
+        n, h = C.c_int64(), C.c_void_p()
+        host.set("answer", nnz)
+        host.log()
+        assert call(n, h) == OK and "wait stream" not in host.log()
+        assert h.value if call is calls[0] else n.value == nnz
+        host.set("answer", -1)
+        assert call(n, h) not in (OK, EHIP) and host.log().count("wait stream") == 1
+        host.set("hipStreamSynchronize", 1)
+        assert call(n, h) == EHIP
+        host.set("hipStreamSynchronize", 0)
+
+
 # ---- where a dense conversion waits ------------------------------------------------------------------
 
 def dense_waits(host):

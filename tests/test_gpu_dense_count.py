@@ -93,6 +93,38 @@ def test_arrivals_of_few_and_many_workgroups(workgroups):
         assert np.array_equal(e["rows"], want.rows) and np.array_equal(e["cols"], want.cols)
 
 
+@pytest.mark.parametrize("copies", [0, 4, 200])
+def test_counts_come_from_streams_at_rest_and_at_work(copies):
+    """The conversions that need a count look for it a while and then wait for their stream: with nothing before them, with a little and with more than
+    they look for (64 MB copies), on two streams in turn, the matrix written anew on the stream before each."""
+    print(f"counts behind {copies} copies", flush=True)
+    rng = np.random.default_rng(copies)
+    n = 900
+    Ah = (rng.standard_normal((n, n)) * (rng.random((n, n)) < 0.05)).astype(np.float32)
+    want = orc.gcoo_from_dense(Ah, 32)
+    r, c = np.nonzero(Ah)
+    src = [torch.from_numpy(x).to(DEV) for x in (Ah, np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int32),
+                                                 c.astype(np.int32), Ah[r, c])]
+    big, x = torch.randn((4096, 4096), device=DEV), torch.empty((4096, 4096), device=DEV)
+    streams = [torch.cuda.Stream(device=DEV) for _ in range(2)]
+    torch.cuda.synchronize()
+    exports = []
+    for i in range(8):
+        st = streams[i % 2]
+        with torch.cuda.stream(st):
+            A, row_ptr, cols, vals = [torch.zeros_like(t) for t in src]
+            for _ in range(copies):
+                x.copy_(big)
+            for to, t in zip((A, row_ptr, cols, vals), src):
+                to.copy_(t)
+            H = binding.gcoo_from_dense(A, 32) if i % 4 < 2 else binding.gcoo_from_csr(n, n, row_ptr, cols, vals, 32, device=DEV)
+            exports.append(H.export())
+        torch.cuda.synchronize()
+    for e in exports:
+        assert np.array_equal(e["values"].view(np.uint32), want.values.view(np.uint32))
+        assert np.array_equal(e["rows"], want.rows) and np.array_equal(e["cols"], want.cols) and np.array_equal(e["gIdxes"], want.gIdxes)
+
+
 @pytest.mark.parametrize("m,k,p", [(700, 900, 65), (130, 1031, 128), (3000, 260, 256)])
 def test_fill_of_tall_groups_in_a_graph(m, k, p):
     """gcoo_from_dense_counted() waits for nothing and can be recorded, for groups of more than 64 rows too, whose regrouped copy is counted
