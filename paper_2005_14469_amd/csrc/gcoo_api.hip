@@ -499,31 +499,44 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 // How a CSR input of this shape is put into the order of the groups; false: sorted by digits of the column.  A part has up to 4096
 // columns of at most 32 rows (2048 of 64, 512 of 256: 16 KB of masks) and fewer where it would hold more than 1024 entries on
 // average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).
-// With more than four columns per entry of a group the distinct columns have the masks, not all of them, unless the whole conversion is one launch:
-// parts of up to 16384 columns, and fewer where a part would hold more than 640 entries, because one of a matrix with power-law rows holds many times the mean
+// With more than 5.5 columns per entry of a group the distinct columns have the masks, not all of them, unless the whole conversion is one launch:
+// parts of up to 16384 columns, and fewer where a part would hold more than 640 entries, 400 up to twelve columns per entry: there one of a matrix with power-law
+// rows holds many times the mean (640 and 400: 20000 x 16000, 0.1 % (31): 44 51; power-law rows, 11370 x 14582 (9): 39 35, 12000 x 10000 (6): 44 32)
 // (whole conversion, us, by masks or, beyond 32 columns per entry, by digits, and so; columns per entry in brackets: 12001 x 12001, 0.05 % (62): 21 12;
-// 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (5): 33.3 33.3; power-law rows,
-// 16384 x 16384 (10): 42 35, 20000 x 15000 (9): 51 42, 6000 x 6000 (4): 27 23.5).
+// 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (6): 33.3 33.3; power-law rows,
+// 16384 x 16384 (10): 42 35, 20000 x 15000 (9): 51 42, 9000 x 9000 (5.6): 31.3 26.9, 9000 x 8500 (5.3): 32.1 37.6, 7577 x 7577 (4.7): 33.7 39.0).
+//
+// Where a group's masks and entries fit the LDS of a workgroup and nothing else is to be made of the rows, one launch is the whole conversion, of 1024
+// threads per group for up to 256 groups, which are one to a compute unit, and for large ones (conversion and product, us, by take_rows and order_groups
+// and so; 600 x 600, 5 %, N = 600: 17.7 12.4; 1000 x 1000, 5 %: 25.7 20.8; 2500 x 2500, 1 %, N = 1024: 26.9 21.7, from host memory 48.0 35.7; 1777 x 2301, 3 %,
+// N = 1117: 40.9 36.4; 16000 x 300, 15 %, N = 64: 31.8 20.0; power-law rows, 2000 x 1300, N = 1000: 46.6 36.2.  256 and 1024 threads: 2500 x 2500 22.4 and
+// 21.5, 1777 x 2301 40.8 and 36.3, but 9000 x 1000, 2 %, N = 64 12.9 and 15.8, 20000 x 200, 30 % 27.6 and 30.8).
+constexpr int64_t kOrderLds = 61 * 1024;                  // dynamic LDS of order_groups, at most
 bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, gcoo::OrderPlan* plan)
 {
     *plan = {};
     if (m <= 0 || k <= 0 || nnz <= 0) return false;
     const int64_t g = (m + p - 1) / p, mean = nnz / g + 1;
     if (k > 128 * mean) return false;
-    const int32_t most = p <= 32 ? 12 : (p <= 64 ? 11 : 9);
-    const bool ranked = k > 4 * mean && (k > ((int64_t)1 << most) || band.h > 0 || run_schedule_wanted(p));
+    const int32_t words = p <= 32 ? 1 : (p <= 64 ? 2 : 8), most = words == 1 ? 12 : (words == 2 ? 11 : 9);
+    const bool ranked = 2 * k > 11 * mean && (k > ((int64_t)1 << most) || band.h > 0 || run_schedule_wanted(p));
     int32_t shift = ranked ? 5 : 0;
     while (((int64_t)1 << shift) < k && shift < (ranked ? 14 : most)) ++shift;
-    while (shift > 7 && (mean << shift) / k > (ranked ? 640 : 1024)) --shift;
+    // entries that the LDS holds beside the masks of all columns
+    const int64_t room = (kOrderLds - 4 * (((int64_t)1 << shift) * (words + 1) + 2 * 1024)) / 9;
+    const bool fused = !ranked && k <= ((int64_t)1 << most) && mean + mean / 16 <= room && band.h == 0 && !run_schedule_wanted(p);
+    const int32_t threads = fused && (g <= 256 || mean > 2048) ? 1024 : gcoo::kOrderThreads;
+    while (!fused && shift > 7 && (mean << shift) / k > (!ranked ? 1024 : (k > 12 * mean ? 640 : 400))) --shift;
     const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
     if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;
     // lists of rows of take_rows: those of the band schedule, else enough workgroups for four per compute unit
     int64_t rows = (m + 1023) / 1024;
     rows = band.h > 0 ? band.h / gcoo::band_lists_of(band.v) : (rows > 64 ? 64 : rows);
     int64_t cap = mean / parts * 3 / 2 + 64;
-    cap = cap < 256 ? 256 : (cap > gcoo::kOrderMaxCap ? gcoo::kOrderMaxCap : cap);
+    const int64_t most_cap = fused ? room : gcoo::kOrderMaxCap;
+    cap = cap < 256 ? 256 : (cap > most_cap ? most_cap : cap);
     const int32_t keys = ranked ? (int32_t)1 << (shift < most ? shift : most) : 0;
-    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), !ranked && parts == 1 && band.h == 0 && !run_schedule_wanted(p), keys};
+    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), fused, keys, threads};
     return true;
 }
 
@@ -955,8 +968,9 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
         o.row_ptr = d_row_ptr; o.nnz = (int32_t)nnz; o.g = g; o.gIdxes_out = h->gIdxes(); o.nnzPerGroup_out = h->nnzPerGroup();
         o.row_start_out = h->row_start(); o.flags_out = h->take_flags();
-        (words == 1 ? gcoo::order_groups<1, gcoo::kOrderFused> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderFused> : gcoo::order_groups<8, gcoo::kOrderFused>))<<<
-            dim3((unsigned)g), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+        auto order = L.plan.threads == 1024 ? (words == 1 ? gcoo::order_groups<1, gcoo::kOrderFused, 1024> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderFused, 1024> : gcoo::order_groups<8, gcoo::kOrderFused, 1024>))
+                                            : (words == 1 ? gcoo::order_groups<1, gcoo::kOrderFused> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderFused> : gcoo::order_groups<8, gcoo::kOrderFused>));
+        order<<<dim3((unsigned)g), dim3((unsigned)L.plan.threads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
     } else if (L.by_masks) {
@@ -1436,7 +1450,13 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     if (kernel == GCOO_KERNEL_ROWS || kernel == GCOO_KERNEL_BAND) {
         gcoo::RowsArgs rows{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
                             A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
-        if (A->from_csr && A->L.by_masks && A->L.plan.fused) { rows.long_count = nullptr; rows.long_row = INT32_MAX; }     // (none are listed)
+        if (A->from_csr && A->L.by_masks && A->L.plan.fused) {
+            // no places are looked at where only a row that repeats columns could be long
+            const bool some = A->k > rows.long_row;
+            rows.long_count = nullptr;
+            rows.long_room = some ? (int32_t)(A->nnz / rows.long_row) : 0;
+            if (!some) rows.long_row = INT32_MAX;
+        }
         if (kernel == GCOO_KERNEL_ROWS) {
             hipError_t e = gcoo::launch_spdm_rows(rows, s);
             return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");

@@ -31,6 +31,7 @@ struct OrderPlan {
     int32_t cap;
     bool fused;
     int32_t keys;              // 0, or ranked: distinct columns of a window
+    int32_t threads;           // of a workgroup of order_groups
 };
 
 struct TakeArgs {
@@ -193,7 +194,7 @@ struct OrderArgs {
 inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 {
     if (plan.keys) return ((size_t)2 << plan.shift) / 8 + (size_t)plan.keys * (4 * words + 4) + (size_t)plan.cap * 9;
-    const size_t ncols = (size_t)1 << plan.shift, spare = ncols < 256 ? ncols : 256;
+    const size_t ncols = (size_t)1 << plan.shift, spare = ncols < (size_t)plan.threads ? ncols : (size_t)plan.threads;
     return (ncols * (words + 1) + 2 * spare) * 4 + (size_t)plan.cap * 9;
 }
 
@@ -205,20 +206,20 @@ inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 // 5 %: 41 -> 19; power-law rows, 16384 x 16384: 65 -> 40.)
 //
 // FUSED (one part per group, no band schedule): there is nothing to know about a group but its rows, so this is the whole conversion, one
-// launch instead of two (256 x 256: 4.2 + 6.4 us before, 6.3 so).
+// launch instead of two (256 x 256: 4.2 + 6.4 us before, 6.3 so; order_plan() has more).
 //
 // RANKED (many columns per entry): a part has many more columns, of which a bitmap says which hold an entry; the places of those among themselves take the
 // place of the columns, so that nothing is done per column but for a bit.  More distinct columns than plan.keys go window by window.
 enum OrderKind { kOrderMasks, kOrderFused, kOrderRanked };
-template <int WORDS, OrderKind KIND>
-__global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
+template <int WORDS, OrderKind KIND, int THREADS = kOrderThreads>
+__global__ __launch_bounds__(THREADS) void order_groups(OrderArgs a)
 {
-    constexpr int ROWS = WORDS == 8 ? 256 : 32 * WORDS, WAVES = kOrderThreads / 64, EACH = 8;
+    constexpr int ROWS = WORDS == 8 ? 256 : 32 * WORDS, WAVES = THREADS / 64, EACH = 8;
     constexpr bool FUSED = KIND == kOrderFused, RANKED = KIND == kOrderRanked;
     extern __shared__ uint32_t order_lds[];
     __shared__ int32_t seg[ROWS], off[ROWS];     // a row's place among the part's entries (or in the input), and what takes it to the input
     __shared__ int32_t wsum[WAVES], wsum2[WAVES];
-    __shared__ int32_t below_s, count_s;
+    __shared__ int32_t below_s, count_s, long_s;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int32_t parts = a.plan.parts, shift = a.plan.shift, ncols = 1 << shift, later = parts - 1;
     const int64_t q = blockIdx.x / parts;
@@ -226,7 +227,9 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
     const int64_t r0 = q * a.p;
     const int32_t rows = (int32_t)(a.m - r0 < a.p ? a.m - r0 : a.p);
     // A thread sums up `1 << ps` columns one after another: a word more for each such stretch keeps the threads on different banks.
-    const int32_t ps = RANKED ? 31 : (shift > 8 ? shift - 8 : 0), spare = RANKED ? 0 : ((ncols - 1) >> ps) + 1;
+    constexpr int LOG = THREADS == 256 ? 8 : 10;
+    static_assert(THREADS == 1 << LOG, "");
+    const int32_t ps = RANKED ? 31 : (shift > LOG ? shift - LOG : 0), spare = RANKED ? 0 : ((ncols - 1) >> ps) + 1;
     const int32_t nbw = ncols >> 5;                          // RANKED: words of the part's columns; how many lie in front of each word
     uint32_t* bits = order_lds;
     int32_t* before = (int32_t*)(bits + nbw);
@@ -271,14 +274,14 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
     uint32_t f = 0u;
     if (!FUSED && (parts > 1 || a.uneven)) {
         const int64_t l0 = r0 / a.plan.list_rows, l1 = (r0 + rows - 1) / a.plan.list_rows;
-        for (int64_t l = l0 + tid; l <= l1; l += kOrderThreads) f |= a.flags[l];
+        for (int64_t l = l0 + tid; l <= l1; l += THREADS) f |= a.flags[l];
         if (part == 0 && a.uneven && (f & kHeavy)) *a.uneven = 1u;
     }
-    if (tid == 0) { below_s = 0; count_s = 0; }
+    if (tid == 0) { below_s = 0; count_s = 0; long_s = 0; }
     if constexpr (RANKED) {
-        for (int32_t i = tid; i < nbw; i += kOrderThreads) bits[i] = 0u;
+        for (int32_t i = tid; i < nbw; i += THREADS) bits[i] = 0u;
     } else {
-        for (int32_t i = tid; i < ncols * WORDS + spare; i += kOrderThreads) mask[i] = 0u;
+        for (int32_t i = tid; i < ncols * WORDS + spare; i += THREADS) mask[i] = 0u;
     }
     // With one part the group is taken in the order of the input and nothing depends on the order in its rows.
     const bool in_order = !FUSED && parts > 1 && __syncthreads_or((int)(f & kUnsorted)) == 0;
@@ -320,6 +323,17 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         if (FUSED && tid == 0) a.flags_out[q] = 0u;
         return;
     }
+    // FUSED: no earlier launch has cleared a count of long rows, so a group has places of its own among them, those that the multiples of long_row
+    // in its stretch of the entries give it: never fewer than it has rows of more entries than that.
+    int32_t long0 = 0, long1 = 0;
+    if (FUSED && a.out.cols) {
+        long0 = g0 / a.out.long_row;
+        long1 = g1 / a.out.long_row;
+        if (tid < rows && (tid + 1 < rows ? seg[tid + 1] : n) - seg[tid] > a.out.long_row) {
+            const int32_t at = long0 + atomicAdd(&long_s, 1);
+            if (at < long1) a.out.long_rows[at] = (int32_t)r0 + tid;
+        }
+    }
     const int32_t c0 = part << shift, kmax = a.k - 1;
     bool bad = false;                                        // FUSED: a column was out of range
     // entry i of those to look at: its row, its column in the part, its value
@@ -336,7 +350,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
     auto take_some = [&](int32_t i0) {                       // eight entries per thread; past the end the last one again
 #pragma unroll
         for (int x = 0; x < EACH; ++x) {
-            const int32_t i = i0 + x * kOrderThreads + tid;
+            const int32_t i = i0 + x * THREADS + tid;
             take(i < n ? i : n - 1, &r[x], &c[x], &v[x]);
         }
     };
@@ -344,19 +358,19 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
     // the masks (RANKED: the bitmap); what lies before the part and what is in it, where that is not known yet
     bool twice = false;
     int32_t below = 0, mine = 0;
-    for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
+    for (int32_t i0 = 0; i0 < n; i0 += EACH * THREADS) {
         take_some(i0);
 #pragma unroll
         for (int x = 0; x < EACH; ++x) {
-            if (i0 + x * kOrderThreads + tid >= n) break;
+            if (i0 + x * THREADS + tid >= n) break;
             if (some) {
                 below += c[x] < 0;
                 if (c[x] < 0 || c[x] >= ncols) continue;
                 ++mine;
             }
             if (FUSED && a.out.cols) {                       // the entries in row order
-                a.out.cols[g0 + i0 + x * kOrderThreads + tid] = c[x];
-                a.out.vals[g0 + i0 + x * kOrderThreads + tid] = v[x];
+                a.out.cols[g0 + i0 + x * THREADS + tid] = c[x];
+                a.out.vals[g0 + i0 + x * THREADS + tid] = v[x];
             }
             if constexpr (RANKED) {
                 atomicOr(&bits[c[x] >> 5], 1u << (c[x] & 31));
@@ -376,6 +390,8 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
     if (!RANKED) twice = __syncthreads_or(twice) != 0;
     else __syncthreads();
     if (FUSED && tid == 0) a.flags_out[q] = below_s ? kBadColumn : 0u;
+    if (FUSED)
+        for (int32_t i = long0 + long_s + tid; i < long1; i += THREADS) a.out.long_rows[i] = -1;
     if (some) {
         out0 = g0 + below_s;
         count = count_s;
@@ -393,13 +409,14 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         __syncthreads();
         int32_t at = incl - x;
         for (int j = 0; j < wv; ++j) at += wsum[j];
-        *all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        static_assert(WAVES == 4, "");
+        int32_t sum = 0;
+        for (int j = 0; j < WAVES; ++j) sum += wsum[j];
+        *all = sum;
         return at;
     };
     int32_t distinct = ncols;
     if constexpr (RANKED) {
-        const int32_t per = (nbw + kOrderThreads - 1) / kOrderThreads, i0 = tid * per < nbw ? tid * per : nbw, i1 = i0 + per < nbw ? i0 + per : nbw;
+        const int32_t per = (nbw + THREADS - 1) / THREADS, i0 = tid * per < nbw ? tid * per : nbw, i1 = i0 + per < nbw ? i0 + per : nbw;
         int32_t sum = 0;
         for (int32_t i = i0; i < i1; ++i) sum += __popc(bits[i]);
         int32_t at = prefix(sum, &distinct);
@@ -419,13 +436,13 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         auto ours = [&](int32_t col) { return !some || (col >= 0 && col < ncols); };
         int32_t key[EACH];
         if constexpr (RANKED) {
-            for (int32_t i = tid; i < nk * WORDS; i += kOrderThreads) mask[i] = 0u;
+            for (int32_t i = tid; i < nk * WORDS; i += THREADS) mask[i] = 0u;
             __syncthreads();
             twice = false;
-            for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
-                if (n > EACH * kOrderThreads) take_some(i0);
+            for (int32_t i0 = 0; i0 < n; i0 += EACH * THREADS) {
+                if (n > EACH * THREADS) take_some(i0);
 #pragma unroll
-                for (int x = 0; x < EACH; ++x) key[x] = i0 + x * kOrderThreads + tid < n && ours(c[x]) ? key_of(c[x]) : -1;
+                for (int x = 0; x < EACH; ++x) key[x] = i0 + x * THREADS + tid < n && ours(c[x]) ? key_of(c[x]) : -1;
 #pragma unroll
                 for (int x = 0; x < EACH; ++x) {
                     if (key[x] < 0 || key[x] >= nk) continue;
@@ -438,9 +455,9 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         }
         if (twice) {
             // counts instead of masks
-            for (int32_t i = tid; i < keys + spare; i += kOrderThreads) base[i] = 0;
+            for (int32_t i = tid; i < keys + spare; i += THREADS) base[i] = 0;
             __syncthreads();
-            for (int32_t i = tid; i < n; i += kOrderThreads) {
+            for (int32_t i = tid; i < n; i += THREADS) {
                 int32_t ri, ci;
                 float vi;
                 take(i, &ri, &ci, &vi);
@@ -452,7 +469,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
         // the first place of every column
         int32_t entries_of_window;
         {
-            const int32_t per = RANKED ? (nk + kOrderThreads - 1) / kOrderThreads : 1 << ps;
+            const int32_t per = RANKED ? (nk + THREADS - 1) / THREADS : 1 << ps;
             const int32_t i0 = RANKED ? (tid * per < nk ? tid * per : nk) : tid << ps, i1 = i0 + per < nk ? i0 + per : nk;
             auto entries = [&](int32_t k) {
                 if (twice) return *base_at(k);
@@ -502,13 +519,13 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
                 }
             }
         } else {
-            for (int32_t i0 = 0; i0 < n; i0 += EACH * kOrderThreads) {
-                if (n > EACH * kOrderThreads) take_some(i0);         // (else they are still there)
+            for (int32_t i0 = 0; i0 < n; i0 += EACH * THREADS) {
+                if (n > EACH * THREADS) take_some(i0);         // (else they are still there)
 #pragma unroll
                 for (int x = 0; x < EACH; ++x) {
-                    if (i0 + x * kOrderThreads + tid >= n) break;
+                    if (i0 + x * THREADS + tid >= n) break;
                     if (!ours(c[x])) continue;
-                    const int32_t ki = RANKED && n <= EACH * kOrderThreads ? key[x] : key_of(c[x]);
+                    const int32_t ki = RANKED && n <= EACH * THREADS ? key[x] : key_of(c[x]);
                     if (RANKED && (ki < 0 || ki >= nk)) continue;
                     int32_t at = *base_at(ki);
 #pragma unroll
@@ -530,7 +547,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_groups(OrderArgs a)
             }
             if (staged) {
                 __syncthreads();
-                for (int32_t i = tid; i < count; i += kOrderThreads) {
+                for (int32_t i = tid; i < count; i += THREADS) {
                     a.dst_cols[out0 + i] = o_col[i];
                     a.dst_rows[out0 + i] = (int32_t)r0 + (int32_t)o_row[i];
                     a.dst_vals[out0 + i] = o_val[i];

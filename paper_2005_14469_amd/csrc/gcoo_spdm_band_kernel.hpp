@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
     if (*a.uneven != 0u) {
         for (uint32_t block = blockIdx.x; block < (uint32_t)rg.items; block += gridDim.x) {
-            rows_item<16, false, kBandWaves>(by_rows, block, rg.tiles, rg.row_wgs, rg.rpw, rg.wave_row, reinterpret_cast<float(*)[64]>(band_smem));
+            rows_item<16, false, kBandWaves, false>(by_rows, block, rg.tiles, rg.row_wgs, rg.rpw, rg.wave_row, reinterpret_cast<float(*)[64]>(band_smem));
             __syncthreads();
         }
         return;

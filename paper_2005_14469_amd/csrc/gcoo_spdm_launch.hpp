@@ -76,7 +76,7 @@ struct RowsArgs {
     float* C;
     int64_t ldc;
     const int32_t* long_rows;  // the rows of more than `long_row` entries, in any order
-    const int32_t* long_count; // or null: none are listed
+    const int32_t* long_count; // or null: long_room places, -1 in those without a row
     int32_t long_row, long_room;
 };
 // A row of more entries than this is shared by a whole workgroup.

@@ -159,8 +159,9 @@ __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& 
 }
 
 // Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.
-// `part`: WAVES * 64 / LPR stretches of a tile's columns in LDS.
-template <int LPR, bool WIDE, int WAVES>
+// `part`: WAVES * 64 / LPR stretches of a tile's columns in LDS.  PLACES: the long rows are in places, not counted (RowsArgs); a template, since the
+// places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
+template <int LPR, bool WIDE, int WAVES, bool PLACES>
 __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
 {
     constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES, TILE = LPR * 4;
@@ -218,12 +219,15 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
     // where the wave's rows begin (lane i: row w0 + i)
     const int32_t start = lane <= wrows && wrows > 0 ? a.row_ptr[w0 + lane] : 0;
+    const int32_t long_first = PLACES && wg < a.long_room ? a.long_rows[wg] : -1;    // (asked for beside the starts)
     // the long rows, all slots of the workgroup on each
-    int32_t n_long = a.long_count ? *a.long_count : 0;
+    int32_t n_long = PLACES ? a.long_room : (a.long_count ? *a.long_count : 0);
     n_long = n_long < a.long_room ? n_long : a.long_room;
     for (int32_t x = wg; x < n_long; x += row_wgs) {
-        const int32_t lr = __builtin_amdgcn_readfirstlane(a.long_rows[x]);
+        const int32_t lr = __builtin_amdgcn_readfirstlane(PLACES && x == wg ? long_first : a.long_rows[x]);
+        if (PLACES && (lr < 0 || lr >= m)) continue;                                 // a place without a row
         const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
+        if (PLACES && le - lb <= a.long_row) continue;
         const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + slot) * each, e = b + each < le ? b + each : le;
         const Place lpl = place(lr);
         RowsBatch<LPR> mine;
@@ -295,11 +299,11 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     }
 }
 
-template <int LPR, bool WIDE>
+template <int LPR, bool WIDE, bool PLACES>
 __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
 {
     __shared__ __attribute__((aligned(16))) float part[kRowsThreads / LPR][LPR * 4];
-    rows_item<LPR, WIDE, kRowsThreads / 64>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
+    rows_item<LPR, WIDE, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
 }
 
 // B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a

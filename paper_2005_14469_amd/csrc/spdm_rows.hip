@@ -27,8 +27,9 @@ static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
     if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them.
     const int64_t wave_row = rpw < spw ? 8 : (2 * mean > 64 ? 2 * mean : 64);
-    spdm_rows<LPR, WIDE><<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw,
-                                                                     (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row));
+    const bool places = !a.long_count && a.long_room > 0;
+    (places ? spdm_rows<LPR, WIDE, true> : spdm_rows<LPR, WIDE, false>)<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(
+        a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw, (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row));
     return hipGetLastError();
 }
 

@@ -44,6 +44,31 @@ def _csr(m, k, density, kind, seed):
 def test_ordered_by_masks(m, k, density, p, kind):
     print(f"order: {m}x{k} d={density} p={p} {kind}", flush=True)
     rp, ci, va = _csr(m, k, density, kind, seed=m + k + p)
+    _check(m, k, rp, ci, va, p)
+
+
+# 1024 threads a group up to 256 groups and for groups of more than 2048 entries, 256 otherwise; groups that just fit the LDS and just not, of more
+# entries than a thread keeps; rows of more than 512 entries, which have places by group: the first and the last row of a group, all of them, none
+@pytest.mark.parametrize("kind", ["sorted", "twice"])
+@pytest.mark.parametrize("m,k,entries,p,long", [(8192, 300, 30, 32, []), (8193, 300, 30, 32, []), (8193, 300, 75, 32, []), (64, 4096, 70, 32, []), (64, 4096, 72, 32, []),
+                                                (96, 2048, 123, 32, []), (96, 2048, 125, 32, []), (320, 700, 5, 32, [*range(32), 96, 159, 319]),
+                                                (9000, 700, 3, 32, [*range(32), 96, 159, 8999]), (9000, 600, 8, 33, [0, 32, 33, 65, 66]),
+                                                (300, 2000, 20, 64, [63, 64, 127, 299]), (300, 512, 7, 65, [3, 299]), (200, 513, 2, 1, [0, 77, 199])])
+def test_in_one_launch(m, k, entries, p, long, kind):
+    print(f"order: {m}x{k} {entries} a row p={p} {len(long)} long rows {kind}", flush=True)
+    rng = np.random.default_rng(m + k + entries)
+    lens = np.full(m, entries)
+    lens[long] = k
+    cols = [np.sort(rng.permutation(k)[:n]) for n in lens]
+    if kind == "twice":
+        for i in (*long[:3], m // 2):
+            cols[i][-1] = cols[i][0]
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate(cols).astype(np.int32)
+    _check(m, k, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), p)
+
+
+def _check(m, k, rp, ci, va, p):
     want = orc.gcoo_from_csr(m, k, rp, ci, va, p)
     dev = [torch.from_numpy(x).to(DEV) for x in (rp, ci, va)]
     A = binding.gcoo_from_csr(m, k, *dev, p, known_nnz=True)
