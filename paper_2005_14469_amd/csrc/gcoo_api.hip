@@ -733,8 +733,8 @@ hipError_t band_fill_lds_limit()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
-    for (const void* f : {reinterpret_cast<const void*>(&gcoo::band_fill<4, 512>), reinterpret_cast<const void*>(&gcoo::band_fill<4, 1024>),
-                          reinterpret_cast<const void*>(&gcoo::band_fill<2, 1024>)}) {
+    for (const void* f : {reinterpret_cast<const void*>(&gcoo::band_fill<4, 512, 8>), reinterpret_cast<const void*>(&gcoo::band_fill<4, 1024, 4>),
+                          reinterpret_cast<const void*>(&gcoo::band_fill<2, 1024, 4>)}) {
         e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
         if (e != hipSuccess) return e;
     }
@@ -744,8 +744,7 @@ hipError_t band_fill_lds_limit()
 
 // The kernel-private schedules that a conversion ends with (see share_schedule_wanted(), run_schedule_wanted() and band_plan()), on the
 // conversion's stream, so that the handle is never written again.
-// `scratch`: the conversion's scratch area (the counter of share_fill and band_fill sits in it).  `marked`: the bitmaps of the band schedule are there, and
-// the counter is zero.
+// `scratch`: the conversion's scratch area (the counter of share_fill sits in it).  `marked`: the bitmaps of the band schedule are there.
 int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false)
 {
     uint32_t* share_alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
@@ -798,20 +797,19 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
         const unsigned lists = (unsigned)(gcoo::band_blocks(h->m, rows) * gcoo::kBandWaves), marks = (unsigned)gcoo::band_lists(h->m, rows, v);
         const size_t words = (size_t)((h->k + 31) / 32);
         uint32_t* parts = reinterpret_cast<uint32_t*>(scratch + h->L.tmp_cols);          // the second sort buffer, free by now
-        uint32_t* alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
-        if (!marked) gcoo::band_mark<<<dim3(marks), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows / gcoo::band_lists_of(v), parts, alloc,
+        if (!marked) gcoo::band_mark<<<dim3(marks), dim3(gcoo::kBandMarkThreads), words * 4, s>>>(h->row_start(), h->row_cols(), h->m, h->k, rows / gcoo::band_lists_of(v), parts,
                                                                                                                 gcoo::band_heavy(h->nnz, marks), h->uneven());
         HIP_TRY(hipGetLastError());
+        const bool large = v == 2 || h->nnz / lists > 4096;
         // distinct columns at a time: all, or as many as the LDS holds
         int64_t chunk = gcoo::band_max_bands(h->k, v) * band_rows;
         if (chunk > gcoo::kBandChunk) chunk = gcoo::kBandChunk;
         while (gcoo::band_fill_lds(h->k, chunk, v) > kBandFillMaxLds) chunk -= band_rows;
         HIP_TRY(band_fill_lds_limit());
-        const bool large = v == 2 || h->nnz / lists > 4096;
-        (v == 2 ? gcoo::band_fill<2, 1024> : (large ? gcoo::band_fill<4, 1024> : gcoo::band_fill<4, 512>))
+        (v == 2 ? gcoo::band_fill<2, 1024, 4> : (large ? gcoo::band_fill<4, 1024, 4> : gcoo::band_fill<4, 512, 8>))
             <<<dim3(lists), dim3(large ? 1024 : 512), gcoo::band_fill_lds(h->k, chunk, v), s>>>(
-            h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk, gcoo::band_units(h->nnz, h->m, h->k, rows, v),
-            gcoo::band_head_stride(h->k, v), h->band_head(), h->band_units(), h->band_first(), h->band_count(), alloc, h->uneven());
+            h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk,
+            gcoo::band_head_stride(h->k, v), h->band_head(), h->band_units(), h->band_first(), h->band_count(), h->uneven());
         HIP_TRY(hipGetLastError());
     }
     return GCOO_OK;
@@ -983,7 +981,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         t.flags = h->take_flags(); t.splits = reinterpret_cast<int32_t*>(base + L.splits);
         t.bits = marked ? reinterpret_cast<uint32_t*>(scratch + L.tmp_cols) : nullptr;
         t.heavy = marked ? gcoo::band_heavy(nnz, L.lists) : INT32_MAX;
-        t.zero_bad = h->bad_col(); t.zero_alloc = reinterpret_cast<uint32_t*>(scratch + L.share_alloc);
+        t.zero_bad = h->bad_col();
         t.stats = h->has_sched ? stats : nullptr;
         (stage ? gcoo::take_rows<true> : gcoo::take_rows<false>)<<<dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(gcoo::kTakeThreads), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
         hipError_t e = hipGetLastError();

@@ -15,12 +15,13 @@
 // band) has at least one unit, so that the units of a wave follow each other without gaps.
 //
 // Order.  Columns ascend inside the pairs and inside the singles, rows ascend inside a column; the last row of a column
-// with an odd count is the single.  A wave whose rows repeat a coordinate has singles only, in row order.
+// with an odd count is the single.  A wave whose rows repeat a coordinate has singles only, in row order (from the first stretch of kBandChunk distinct columns
+// on that holds a repeated one).
 //
 // Heads.  head[(block * 16 + w) * stride + i], i = 0 .. bands + 1, stride = band_head_stride(k, kRows): eight words
 //     { the columns whose B rows wave w fetches for band i, in five words; pair steps, single steps of band i - 1; unused }
 // wide: a column per word; tall: two, c | (the next one - c) << 16 (bands beyond the last repeat the last column).
-// count[block] = distinct columns; first[block * 16 + w] = first unit of a wave.
+// count[block] = distinct columns; first[block * 16 + w] = first unit of a wave: what the waves before it can need at the most.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -86,6 +86,24 @@ def test_tall_cut_with_repeated_coordinates_and_infinities():
     _run(workloads.Workload("repeated", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), B), 32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
 
 
+@pytest.mark.parametrize("m,k,lens,twice", [(777, 3500, [0, 1, 200, 3, 0, 0, 130, 64, 65, 63], ()), (800, 3500, [150] * 40 + [320] * 16, ()), (900, 3500, [170], ()),
+                                            (400, 3500, [0] * 15 + [900], ()), (60, 20000, [700], (19999,)), (60, 20000, [700], (3,)), (130, 30000, [900, 0, 500], (29999,))])
+def test_rows_of_all_lengths(m, k, lens, twice):
+    """Lists whose 64 neighbouring entries lie in one row and in many, with empty rows between; of more entries than the threads of a workgroup keep beside
+    shorter ones; more distinct columns than are counted at a time, a coordinate repeated among the first of them or the last."""
+    print(f"band: m={m} k={k} lens={lens[:4]} twice={twice}", flush=True)
+    rng = np.random.default_rng(m + k)
+    n = np.resize(lens, m)
+    rows = [np.sort(rng.permutation(k)[:x]) for x in n]
+    for c in twice:
+        for i in range(0, m, 7):
+            rows[i] = np.sort(np.concatenate([rows[i][:-2], [c, c]])) if n[i] > 2 else rows[i]
+    rp = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    _run(workloads.Workload("lengths", m, k, 132, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, 132)).astype(np.float32)),
+         32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
+
+
 @pytest.mark.parametrize("m,k,N,s", [(100, 3500, 300, 0.94), (385, 3600, 1024, 0.98), (1000, 7000, 768, 0.995), (50, 20000, 260, 0.97)])
 def test_uniform_through_the_share_variant(m, k, N, s):
     print(f"band: m={m} k={k} N={N} s={s}", flush=True)
