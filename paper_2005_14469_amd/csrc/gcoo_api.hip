@@ -983,7 +983,9 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         t.heavy = marked ? gcoo::band_heavy(nnz, L.lists) : INT32_MAX;
         t.zero_bad = h->bad_col();
         t.stats = h->has_sched ? stats : nullptr;
-        (stage ? gcoo::take_rows<true> : gcoo::take_rows<false>)<<<dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(gcoo::kTakeThreads), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
+        const bool few = !stage && nnz / L.lists > 2048;
+        (stage ? gcoo::take_rows<true, 512> : (few ? gcoo::take_rows<false, 1024> : gcoo::take_rows<false, 512>))<<<
+            dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(few ? 1024 : 512), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "take_rows"); }
         gcoo::OrderArgs o{};

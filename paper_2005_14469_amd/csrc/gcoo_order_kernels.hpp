@@ -17,7 +17,6 @@
 
 namespace gcoo {
 
-constexpr int kTakeThreads = 512;
 constexpr int kOrderThreads = 256;
 constexpr int kOrderMaxParts = 64;
 constexpr int kOrderMaxCap = 3072;       // entries of a part that are put in order in LDS; a larger part is written in place
@@ -68,44 +67,44 @@ __device__ __forceinline__ int32_t row_of_entry(const int32_t* start, int32_t e)
 // One workgroup per list of rows.  Bound: memory, an entry is read once and its copy in row order written once.  Dynamic LDS: the
 // list's columns as a bitmap, where the band schedule wants it.  FROM_HOST: the input is host memory, and a column is not read twice
 // (from device memory the second read, which the vector cache serves, is the cheaper way: 36.6 and 42.7 us for 6.4 million entries).
-template <bool FROM_HOST>
-__global__ __launch_bounds__(kTakeThreads) void take_rows(TakeArgs a)
+// THREADS = 1024 for lists of more than 2048 entries, of which there are few (4000 x 4000, 5 %: 10.0 us with 512, 8.4 so; 8000 x 8000, 10 %: 24.2 and 23.0; but
+// 0.5 %: 6.6 and 7.3; before the rows were found by lanes 10.0 and 27.6 for the first two).
+template <bool FROM_HOST, int THREADS>
+__global__ __launch_bounds__(THREADS) void take_rows(TakeArgs a)
 {
+    constexpr int EACH = 4;
     extern __shared__ uint32_t take_bits[];
-    __shared__ int32_t rs[65], find[64];
+    __shared__ int32_t rs[66];
     __shared__ uint32_t flag_s;
-    const int tid = threadIdx.x;
-    const int64_t list = blockIdx.x;
-    if (list == a.lists) {                                       // the whole workgroup
-        group_stats_block<kTakeThreads>(a.row_ptr, a.m, a.p, a.g, a.stats);
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (blockIdx.x == a.lists) {                                 // the whole workgroup
+        group_stats_block<THREADS>(a.row_ptr, a.m, a.p, a.g, a.stats);
         return;
     }
+    const int32_t list = (int32_t)blockIdx.x;
     if (list == 0 && tid < 3) a.zero_bad[tid] = 0u;
     // Offsets are clamped to [0, nnz]: with a device input whose row_ptr does not match the nnz the buffer was laid out
     // for, every later kernel still stays inside the arrays.
-    const int32_t nnz = a.nnz;
-    auto at = [&](int64_t r) { const int32_t v = a.row_ptr[r]; return v < 0 ? 0 : (v > nnz ? nnz : v); };
-    const int64_t r0 = list * a.plan.list_rows < a.m ? list * a.plan.list_rows : a.m;
-    const int32_t rows = (int32_t)(a.m - r0 < a.plan.list_rows ? a.m - r0 : a.plan.list_rows);
+    const int32_t nnz = a.nnz, m = (int32_t)a.m;
+    auto at = [&](int32_t r) { const int32_t v = a.row_ptr[r]; return v < 0 ? 0 : (v > nnz ? nnz : v); };
+    const int32_t r0 = (int64_t)list * a.plan.list_rows < m ? list * a.plan.list_rows : m;
+    const int32_t rows = m - r0 < a.plan.list_rows ? m - r0 : a.plan.list_rows;
     const int32_t nbw = (a.k + 31) / 32;
     if (tid == 0) flag_s = 0u;
     if (tid <= rows) {
-        const int32_t v = at(r0 + tid);
+        const bool group = tid < rows && (uint32_t)(r0 + tid) % (uint32_t)a.p == 0;
+        const int32_t v = at(r0 + tid), next = group ? at(a.p < m - (r0 + tid) ? r0 + tid + a.p : m) : 0;
         rs[tid] = v;
         a.row_start[r0 + tid] = v;
-        if (tid < 64) find[tid] = tid < rows ? v : INT32_MAX;
-    } else if (tid < 64) {
-        find[tid] = INT32_MAX;
+        if (group) {
+            const int32_t q = (int32_t)((uint32_t)(r0 + tid) / (uint32_t)a.p);
+            a.gIdxes[q] = v;
+            a.nnzPerGroup[q] = next < v ? 0 : next - v;
+        }
+        if (r0 + tid == m) a.gIdxes[a.g] = v;
     }
-    if (tid < rows && (r0 + tid) % a.p == 0) {
-        const int64_t q = (r0 + tid) / a.p, r1 = r0 + tid + a.p < a.m ? r0 + tid + a.p : a.m;
-        const int32_t b = at(r0 + tid), n = at(r1) - b;
-        a.gIdxes[q] = b;
-        a.nnzPerGroup[q] = n < 0 ? 0 : n;
-    }
-    if (tid == 0 && r0 + rows == a.m) a.gIdxes[a.g] = at(a.m);
     if (a.bits)
-        for (int32_t i = tid; i < nbw; i += kTakeThreads) take_bits[i] = 0u;
+        for (int32_t i = tid; i < nbw; i += THREADS) take_bits[i] = 0u;
     __syncthreads();
     const int32_t shift = a.plan.shift, later = a.plan.parts - 1;
     uint32_t flag = 0u;
@@ -113,17 +112,16 @@ __global__ __launch_bounds__(kTakeThreads) void take_rows(TakeArgs a)
         const int32_t b = rs[tid];
         if (rs[tid + 1] < b) flag |= kUnsorted;                  // offsets that contradict each other
         if (rs[tid + 1] <= b)
-            for (int32_t j = 0; j < later; ++j) a.splits[(r0 + tid) * later + j] = b;
+            for (int32_t j = 0; j < later; ++j) a.splits[(int64_t)(r0 + tid) * later + j] = b;
     }
-    const int32_t beg = rs[0], end = rs[rows];
+    const int32_t beg = rs[0], end = rs[rows], start = lane < rows ? rs[lane] : INT32_MAX;
     auto in_range = [&](int32_t c) { return c < 0 ? 0 : (c >= a.k ? a.k - 1 : c); };
-    // (four loads in flight per lane)
-    for (int32_t e = beg + tid; e < end; e += 4 * kTakeThreads) {
-        int32_t c[4], before[4], row[4];
-        float v[4];
+    for (int32_t e = beg + tid; e - tid < end; e += EACH * THREADS) {       // (the whole wave)
+        int32_t c[EACH], before[EACH];
+        float v[EACH];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int32_t i = e + x * kTakeThreads < end ? e + x * kTakeThreads : e;
+        for (int x = 0; x < EACH; ++x) {
+            const int32_t i = e + x * THREADS < end ? e + x * THREADS : end - 1;
             c[x] = a.cols[i];
             if (a.row_cols) v[x] = a.vals[i];
             // the column before it
@@ -133,27 +131,37 @@ __global__ __launch_bounds__(kTakeThreads) void take_rows(TakeArgs a)
             } else {
                 before[x] = a.cols[i > beg ? i - 1 : i];
             }
-            row[x] = row_of_entry<64>(find, i);
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int32_t i = e + x * kTakeThreads;
-            if (i >= end) break;
-            const int32_t col = in_range(c[x]), prev = in_range(before[x]), r = row[x];
-            if (col != c[x]) flag |= kBadColumn;
-            const bool first = rs[r] == i, last = rs[r + 1] == i + 1;
-            if (!first && prev >= col) flag |= kUnsorted;
-            if (a.row_cols) {
-                a.row_cols[i] = col;
-                a.row_vals[i] = v[x];
+        for (int x = 0; x < EACH; ++x) {
+            // The entry's row, and whether it is its first and its last: the rows that begin up to the entry of the wave's first lane, and those
+            // that begin at the 64 behind it, from the lanes, which hold where the rows begin (a search in LDS reads six words one after another).
+            const int32_t i = e + x * THREADS < end ? e + x * THREADS : end - 1, i0 = __builtin_amdgcn_readfirstlane(i);
+            const uint64_t here = __ballot(start == i0);                         // (of all lanes)
+            int32_t r = __popcll(__ballot(start <= i0)) - 1;
+            bool first = i == i0 && here != 0, last = i + 1 == end;
+            for (uint64_t in = __ballot(start > i0 && start - i0 <= 64); in; in &= in - 1) {
+                const int32_t begins = __builtin_amdgcn_readlane(start, __ffsll((unsigned long long)in) - 1);
+                r += begins <= i;
+                first |= begins == i;
+                last |= begins == i + 1;
             }
-            if (a.bits) atomicOr(&take_bits[col >> 5], 1u << (col & 31));
-            if (later > 0) {
-                int32_t* split = a.splits + (r0 + r) * later - 1;
-                const int32_t part = col >> shift;
-                for (int32_t j = first ? 1 : (prev >> shift) + 1; j <= part; ++j) split[j] = i;
-                if (last)
-                    for (int32_t j = part + 1; j <= later; ++j) split[j] = i + 1;
+            if (e + x * THREADS < end) {
+                const int32_t col = in_range(c[x]), prev = in_range(before[x]);
+                if (col != c[x]) flag |= kBadColumn;
+                if (!first && prev >= col) flag |= kUnsorted;
+                if (a.row_cols) {
+                    a.row_cols[i] = col;
+                    a.row_vals[i] = v[x];
+                }
+                if (a.bits) atomicOr(&take_bits[col >> 5], 1u << (col & 31));
+                if (later > 0) {
+                    int32_t* split = a.splits + (int64_t)(r0 + r) * later - 1;
+                    const int32_t part = col >> shift;
+                    for (int32_t j = first ? 1 : (prev >> shift) + 1; j <= part; ++j) split[j] = i;
+                    if (last)
+                        for (int32_t j = part + 1; j <= later; ++j) split[j] = i + 1;
+                }
             }
         }
     }
@@ -161,7 +169,7 @@ __global__ __launch_bounds__(kTakeThreads) void take_rows(TakeArgs a)
     __syncthreads();
     if (tid == 0) a.flags[list] = flag_s | (end - beg > a.heavy ? kHeavy : 0u);
     if (a.bits)
-        for (int32_t i = tid; i < nbw; i += kTakeThreads) a.bits[list * nbw + i] = take_bits[i];
+        for (int32_t i = tid; i < nbw; i += THREADS) a.bits[(int64_t)list * nbw + i] = take_bits[i];
 }
 
 struct OrderArgs {
