@@ -17,6 +17,7 @@
 #include <memory>
 #include <mutex>
 #include <thread>
+#include <type_traits>
 
 #include "gcoo_band.hpp"
 #include "gcoo_band_build.hpp"
@@ -496,9 +497,32 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
     return best;
 }
 
+// Distinct columns that band_fill holds at a time: all, or as many as fit `lds` bytes.
+constexpr size_t kBandFillMaxLds = 150 * 1024;
+int64_t band_fill_chunk(int64_t k, int v, size_t lds)
+{
+    const int64_t band_rows = gcoo::band_rows_of(v);
+    int64_t chunk = gcoo::band_max_bands(k, v) * band_rows;
+    if (chunk > gcoo::kBandChunk) chunk = gcoo::kBandChunk;
+    while (chunk > 0 && gcoo::band_fill_lds(k, chunk, v) > lds) chunk -= band_rows;
+    return chunk;
+}
+
+// Whether order_groups and band_fill are one launch, in 52 KB of LDS, with which a compute unit has room for three workgroups.  More columns than those hold at a time cost
+// another turn through the entries: that is worth it up to about two such turns, and only while the threads keep the entries of a list (2048 of them).
+// Conversion, us, as two launches and as one: 3000 x 3000, 3 %: 23.9 15.9; 4000 x 4000, 5 %: 32.8 23.8; 8000 x 8000, 0.5 %: 30.0 26.6; 2 %: 43.8 38.7; 5 %: 81 76;
+// power-law rows, 16384 x 16384: 41.6 36.6; but 14000 x 14000, 0.4 %: 61.2 62.5; 2 %: 104 116.
+constexpr size_t kBothMaxLds = 52 * 1024;
+bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, BandPlan band)
+{
+    const int64_t chunk = band_fill_chunk(k, band.v, kBothMaxLds);
+    return chunk >= k || (9 * chunk >= 4 * k && nnz / (gcoo::band_blocks(m, band.h) * gcoo::kBandWaves) <= 4096);
+}
+
 // How a CSR input of this shape is put into the order of the groups; false: sorted by digits of the column.  A part has up to 4096
 // columns of at most 32 rows (2048 of 64, 512 of 256: 16 KB of masks) and fewer where it would hold more than 1024 entries on
-// average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).
+// average (4000 x 4000, 5 %, us for 2048, 1024, 512, 256: 11.4, 11.4, 14.2, 21.2; 1777 x 2301, 3 %: 13.8, 9.0, 8.2, 7.9).  The launch that fills the bands as well
+// has 512 threads for a part, which holds twice as many (500 and 1000 parts there: 12.4 and 14.4 us with 512 threads, 11.7 with 256).
 // With more than 5.5 columns per entry of a group the distinct columns have the masks, not all of them, unless the whole conversion is one launch:
 // parts of up to 16384 columns, and fewer where a part would hold more than 640 entries, 400 up to twelve columns per entry: there one of a matrix with power-law
 // rows holds many times the mean (640 and 400: 20000 x 16000, 0.1 % (31): 44 51; power-law rows, 11370 x 14582 (9): 39 35, 12000 x 10000 (6): 44 32)
@@ -512,7 +536,7 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 // N = 1117: 40.9 36.4; 16000 x 300, 15 %, N = 64: 31.8 20.0; power-law rows, 2000 x 1300, N = 1000: 46.6 36.2.  256 and 1024 threads: 2500 x 2500 22.4 and
 // 21.5, 1777 x 2301 40.8 and 36.3, but 9000 x 1000, 2 %, N = 64 12.9 and 15.8, 20000 x 200, 30 % 27.6 and 30.8).
 constexpr int64_t kOrderLds = 61 * 1024;                  // dynamic LDS of order_groups, at most
-bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, gcoo::OrderPlan* plan)
+bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, bool marked, gcoo::OrderPlan* plan)
 {
     *plan = {};
     if (m <= 0 || k <= 0 || nnz <= 0) return false;
@@ -522,21 +546,23 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, gco
     const bool ranked = 2 * k > 11 * mean && (k > ((int64_t)1 << most) || band.h > 0 || run_schedule_wanted(p));
     int32_t shift = ranked ? 5 : 0;
     while (((int64_t)1 << shift) < k && shift < (ranked ? 14 : most)) ++shift;
-    // entries that the LDS holds beside the masks of all columns
-    const int64_t room = (kOrderLds - 4 * (((int64_t)1 << shift) * (words + 1) + 2 * 1024)) / 9;
+    // entries that the LDS holds beside the masks of a part's columns
+    const auto room_at = [&](int32_t shift) { return (kOrderLds - 4 * (((int64_t)1 << shift) * (words + 1) + 2 * 1024)) / 9; };
+    const int64_t room = room_at(shift);
     const bool fused = !ranked && k <= ((int64_t)1 << most) && mean + mean / 16 <= room && band.h == 0 && !run_schedule_wanted(p);
     const int32_t threads = fused && (g <= 256 || mean > 2048) ? 1024 : gcoo::kOrderThreads;
-    while (!fused && shift > 7 && (mean << shift) / k > (!ranked ? 1024 : (k > 12 * mean ? 640 : 400))) --shift;
+    const bool both = marked && words <= 2 && order_and_fill_wanted(m, k, nnz, band);
+    while (!fused && shift > 7 && (mean << shift) / k > (!ranked ? 1024 : (k > 12 * mean ? 640 : 400)) * (both ? 2 : 1)) --shift;
     const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
     if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;
     // lists of rows of take_rows: those of the band schedule, else enough workgroups for four per compute unit
     int64_t rows = (m + 1023) / 1024;
     rows = band.h > 0 ? band.h / gcoo::band_lists_of(band.v) : (rows > 64 ? 64 : rows);
     int64_t cap = mean / parts * 3 / 2 + 64;
-    const int64_t most_cap = fused ? room : gcoo::kOrderMaxCap;
+    const int64_t most_cap = fused ? room : (both ? room_at(shift < most ? shift : most) : gcoo::kOrderMaxCap);
     cap = cap < 256 ? 256 : (cap > most_cap ? most_cap : cap);
     const int32_t keys = ranked ? (int32_t)1 << (shift < most ? shift : most) : 0;
-    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), fused, keys, threads};
+    *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), fused, keys, both ? gcoo::kBothThreads : threads, both};
     return true;
 }
 
@@ -582,7 +608,7 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     L.band_units = take(L.band.h ? (size_t)gcoo::band_units(nnz, m, k, L.band.h, L.band.v) * gcoo::kBandUnitWords * 4 : 0);
     L.band_first = take((size_t)lists * 4);
     L.band_count = take((size_t)(lists / gcoo::kBandWaves) * 4);
-    L.by_masks = order_plan(m, k, nnz, p, L.band, &L.plan);
+    L.by_masks = order_plan(m, k, nnz, p, L.band, L.band.h > 0 && !share, &L.plan);
     L.lists = L.plan.fused ? g : lists ? gcoo::band_lists(m, L.band.h, L.band.v) : (L.by_masks ? (m + L.plan.list_rows - 1) / L.plan.list_rows : 0);     // (a band block has empty lists behind the last row)
     L.take_flags = take(L.by_masks ? (size_t)L.lists * 4 : 0);
     L.splits = take(L.by_masks ? (size_t)m * (size_t)(L.plan.parts - 1) * 4 : 0);
@@ -724,7 +750,6 @@ hipError_t share_fill_lds_limit()
     return e;
 }
 
-constexpr size_t kBandFillMaxLds = 150 * 1024;
 hipError_t band_fill_lds_limit()
 {
     static std::atomic<unsigned> done[64];
@@ -742,10 +767,22 @@ hipError_t band_fill_lds_limit()
     return e;
 }
 
+gcoo::FillArgs fill_args(const gcoo_matrix* h, const char* scratch, bool both)
+{
+    const int v = h->L.band.v;
+    gcoo::FillArgs f{};
+    f.row_start = h->row_start(); f.row_cols = h->row_cols(); f.row_vals = h->row_vals(); f.m = h->m; f.k = h->k; f.h = h->L.band.h;
+    f.chunk = (int32_t)band_fill_chunk(h->k, v, both ? kBothMaxLds : kBandFillMaxLds); f.parts = reinterpret_cast<const uint32_t*>(scratch + h->L.tmp_cols);
+    f.head_stride = gcoo::band_head_stride(h->k, v); f.head = h->band_head(); f.units = h->band_units(); f.first = h->band_first(); f.count = h->band_count();
+    if (both) { f.flags = h->take_flags(); f.flag_count = (int32_t)h->L.lists; f.heavy = gcoo::kHeavy; }
+    else f.uneven = h->uneven();
+    return f;
+}
+
 // The kernel-private schedules that a conversion ends with (see share_schedule_wanted(), run_schedule_wanted() and band_plan()), on the
 // conversion's stream, so that the handle is never written again.
 // `scratch`: the conversion's scratch area (the counter of share_fill sits in it).  `marked`: the bitmaps of the band schedule are there.
-int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false)
+int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false, bool filled = false)
 {
     uint32_t* share_alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
     if (h->g > 0 && h->has_sched) {
@@ -791,9 +828,9 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
             h->share_blocks(), h->share_sbase(), share_alloc, (int32_t)stage_cap);
         HIP_TRY(hipGetLastError());
     }
-    if (h->L.band.h > 0) {
+    if (h->L.band.h > 0 && !filled) {
         const int32_t rows = h->L.band.h;
-        const int v = h->L.band.v, band_rows = gcoo::band_rows_of(v);
+        const int v = h->L.band.v;
         const unsigned lists = (unsigned)(gcoo::band_blocks(h->m, rows) * gcoo::kBandWaves), marks = (unsigned)gcoo::band_lists(h->m, rows, v);
         const size_t words = (size_t)((h->k + 31) / 32);
         uint32_t* parts = reinterpret_cast<uint32_t*>(scratch + h->L.tmp_cols);          // the second sort buffer, free by now
@@ -801,15 +838,10 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
                                                                                                                 gcoo::band_heavy(h->nnz, marks), h->uneven());
         HIP_TRY(hipGetLastError());
         const bool large = v == 2 || h->nnz / lists > 4096;
-        // distinct columns at a time: all, or as many as the LDS holds
-        int64_t chunk = gcoo::band_max_bands(h->k, v) * band_rows;
-        if (chunk > gcoo::kBandChunk) chunk = gcoo::kBandChunk;
-        while (gcoo::band_fill_lds(h->k, chunk, v) > kBandFillMaxLds) chunk -= band_rows;
+        const gcoo::FillArgs f = fill_args(h, scratch, false);
         HIP_TRY(band_fill_lds_limit());
         (v == 2 ? gcoo::band_fill<2, 1024, 4> : (large ? gcoo::band_fill<4, 1024, 4> : gcoo::band_fill<4, 512, 8>))
-            <<<dim3(lists), dim3(large ? 1024 : 512), gcoo::band_fill_lds(h->k, chunk, v), s>>>(
-            h->row_start(), h->row_cols(), h->row_vals(), h->m, h->k, rows, parts, (int32_t)chunk,
-            gcoo::band_head_stride(h->k, v), h->band_head(), h->band_units(), h->band_first(), h->band_count(), h->uneven());
+            <<<dim3(lists), dim3(large ? 1024 : 512), gcoo::band_fill_lds(h->k, f.chunk, v), s>>>(f);
         HIP_TRY(hipGetLastError());
     }
     return GCOO_OK;
@@ -992,9 +1024,24 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.row_start = h->row_start(); o.cols = h->has_rows() ? h->row_cols() : d_cols; o.vals = h->has_rows() ? h->row_vals() : d_vals;
         o.m = m; o.lists = L.lists; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.gIdxes = h->gIdxes(); o.flags = t.flags; o.splits = t.splits;
         o.out = rows_out(h); o.uneven = marked ? h->uneven() : nullptr; o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
-        auto order = L.plan.keys ? (words == 1 ? gcoo::order_groups<1, gcoo::kOrderRanked> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderRanked> : gcoo::order_groups<8, gcoo::kOrderRanked>))
+        if (L.plan.both) {
+            const gcoo::FillArgs f = fill_args(h, scratch, true);
+            const int32_t lists = (int32_t)(gcoo::band_blocks(m, L.band.h) * gcoo::kBandWaves);
+            const size_t fill_lds = gcoo::band_fill_lds(k, f.chunk, L.band.v), order_lds = gcoo::order_lds_bytes(L.plan, words);
+            e = band_fill_lds_limit();
+            if (e != hipSuccess) { delete h; return hip_fail(e, "order_and_fill"); }
+            auto pick = [&](auto v) {
+                constexpr int V = decltype(v)::value;
+                return L.plan.keys ? (words == 1 ? gcoo::order_and_fill<1, gcoo::kOrderRanked, V> : gcoo::order_and_fill<2, gcoo::kOrderRanked, V>)
+                                   : (words == 1 ? gcoo::order_and_fill<1, gcoo::kOrderMasks, V> : gcoo::order_and_fill<2, gcoo::kOrderMasks, V>);
+            };
+            (L.band.v == 4 ? pick(std::integral_constant<int, 4>{}) : pick(std::integral_constant<int, 2>{}))<<<
+                dim3((unsigned)(lists + g * L.plan.parts)), dim3(gcoo::kBothThreads), fill_lds > order_lds ? fill_lds : order_lds, s>>>(o, f, lists);
+        } else {
+            auto order = L.plan.keys ? (words == 1 ? gcoo::order_groups<1, gcoo::kOrderRanked> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderRanked> : gcoo::order_groups<8, gcoo::kOrderRanked>))
                                    : (words == 1 ? gcoo::order_groups<1, gcoo::kOrderMasks> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderMasks> : gcoo::order_groups<8, gcoo::kOrderMasks>));
-        order<<<dim3((unsigned)(g * L.plan.parts)), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+            order<<<dim3((unsigned)(g * L.plan.parts)), dim3(gcoo::kOrderThreads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+        }
         e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
     } else
@@ -1044,7 +1091,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         hipError_t e = stage.release(s);
         if (e != hipSuccess) { delete h; return hip_fail(e, "hipEventRecord"); }
     }
-    rc = launch_build_schedule(h, scratch, s, marked);
+    rc = launch_build_schedule(h, scratch, s, marked, L.by_masks && L.plan.both);
     if (rc != GCOO_OK) { delete h; return rc; }
     if (wants_inner(p)) {
         // the same entries once more, regrouped at kInnerP rows, from the CSR arrays on the device (a host input's

@@ -137,13 +137,25 @@ inline size_t band_fill_lds(int64_t k, int64_t chunk, int v)
 // and writing it in whole lines took as long (84 to 121 us for 48 to 8 KB), and so did going through the entries once for each half of the columns (88).
 // V as in BandCut.  kBandBuildThreads = 1024 for lists of many entries, of which there are too few to fill the chip with workgroups of 512.
 // Dynamic LDS: band_fill_lds().
+struct FillArgs {
+    const int32_t* row_start;
+    const int32_t* row_cols;
+    const float* row_vals;
+    int64_t m, k;
+    int32_t h, chunk;
+    const uint32_t* parts;
+    int64_t head_stride;
+    uint32_t* head;
+    uint32_t* units;
+    int32_t* first;
+    int32_t* count;
+    const uint32_t* uneven;    // not 0: the product goes row by row; or null and
+    const uint32_t* flags;     // the word of every list, in some of which a bit of `heavy` says so
+    int32_t flag_count;
+    uint32_t heavy;
+};
 template <int V, int kBandBuildThreads, int EACH>
-__global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __restrict__ row_start, const int32_t* __restrict__ row_cols,
-                                                              const float* __restrict__ row_vals, int64_t m, int64_t k, int32_t h,
-                                                              const uint32_t* __restrict__ parts, int32_t chunk,
-                                                              int64_t head_stride, uint32_t* __restrict__ head, uint32_t* __restrict__ units,
-                                                              int32_t* __restrict__ first, int32_t* __restrict__ count,
-                                                              const uint32_t* __restrict__ uneven)
+__device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
 {
     typedef BandCut<V> Cut;
     typedef typename BandRowMask<V>::type Mask;
@@ -158,21 +170,28 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
     __shared__ int2 band_s[kBandChunkBands];                // first unit and pairs of a band
     __shared__ int32_t singles_s[kBandChunkBands];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t m = a.m, k = a.k, Q = list / kBandWaves;
+    const int32_t h = a.h, chunk = a.chunk, w = (int32_t)(list - Q * kBandWaves);
+    const int32_t* __restrict__ row_start = a.row_start;
+    const int32_t* __restrict__ row_cols = a.row_cols;
+    const float* __restrict__ row_vals = a.row_vals;
+    const uint32_t* __restrict__ parts = a.parts;
     const int32_t nbw = (int32_t)((k + 31) / 32);
     uint2* words = (uint2*)band_lds;                        // the block's columns, and the distinct ones in front of a word of them
     Mask* rows_of = (Mask*)(words + nbw);                   // rows of the list with an entry in a column of the chunk
     uint32_t* place_of = (uint32_t*)(rows_of + chunk);      // pairs | singles << 16 of the band in front of five columns
-    const int64_t list = blockIdx.x, Q = list / kBandWaves;
-    const int32_t w = (int32_t)(list - Q * kBandWaves);
     // What waits for nothing but the rows' bounds is asked for first: the bitmaps, then the entries.
-    const uint32_t by_rows = *uneven;                       // the product goes row by row
+    uint32_t by_rows = 0u;
+    if (a.uneven) by_rows = *a.uneven;
+    else
+        for (int32_t i = tid; i < a.flag_count; i += kBandBuildThreads) by_rows |= a.flags[i] & a.heavy;
     const BandList l = band_list(row_start, m, h, list);
     uint32_t mine_bits = 0u;
     if (tid < nbw) {
 #pragma unroll
         for (int x = 0; x < kParts; ++x) mine_bits |= parts[(Q * kParts + x) * nbw + tid];
     }
-    if (by_rows != 0u) return;
+    if (a.uneven && by_rows != 0u) return;
     const int32_t n = l.end - l.beg, begins = lane < l.rows ? row_start[l.r0 + lane] : INT32_MAX;
     const int32_t* list_cols = row_cols + l.beg;
     const float* list_vals = row_vals + l.beg;
@@ -196,7 +215,7 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
         words[i].x = b;
     }
     if (tid == 0) repeated_s = 0;
-    __syncthreads();
+    if (__syncthreads_or((int)by_rows)) return;             // the whole workgroup
     {
         const int32_t per = (nbw + kBandBuildThreads - 1) / kBandBuildThreads;
         const int32_t i0 = tid * per, i1 = i0 + per < nbw ? i0 + per : nbw;
@@ -213,11 +232,11 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
     // A list has as many units as its entries and bands can make (band_units()) for itself, so that no list waits for another to be counted.
     const int64_t most = band_max_bands(k, V) * list, base = l.beg / 16 + most + (most < l.beg ? most : l.beg);
     if (tid == 0) {
-        first[list] = (int32_t)base;
-        if (w == 0) count[Q] = nU;
+        a.first[list] = (int32_t)base;
+        if (w == 0) a.count[Q] = nU;
     }
-    uint32_t* hd = head + list * head_stride * kBandHeadWords;
-    uint2* rec = reinterpret_cast<uint2*>(units) + base * 16;
+    uint32_t* hd = a.head + list * a.head_stride * kBandHeadWords;
+    uint2* rec = reinterpret_cast<uint2*>(a.units) + base * 16;
 
     auto in_range = [&](uint32_t c) -> uint32_t { return c < (uint32_t)k ? c : (uint32_t)k - 1u; };
     auto distinct = [&](uint32_t c) -> int32_t {
@@ -385,6 +404,12 @@ __global__ __launch_bounds__(kBandBuildThreads) void band_fill(const int32_t* __
         }
         if (u0 + chunk < nU) __syncthreads();
     }
+}
+
+template <int V, int kBandBuildThreads, int EACH>
+__global__ __launch_bounds__(kBandBuildThreads) void band_fill(FillArgs a)
+{
+    band_fill_list<V, kBandBuildThreads, EACH>(a, blockIdx.x);
 }
 
 }  // namespace gcoo

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gcoo_band_build.hpp"
 #include "gcoo_build_kernels.hpp"
 
 namespace gcoo {
@@ -31,6 +32,7 @@ struct OrderPlan {
     bool fused;
     int32_t keys;              // 0, or ranked: distinct columns of a window
     int32_t threads;           // of a workgroup of order_groups
+    bool both;                 // order_groups and band_fill are one launch
 };
 
 struct TakeArgs {
@@ -217,8 +219,8 @@ inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 // RANKED (many columns per entry): a part has many more columns, of which a bitmap says which hold an entry; the places of those among themselves take the
 // place of the columns, so that nothing is done per column but for a bit.  More distinct columns than plan.keys go window by window.
 enum OrderKind { kOrderMasks, kOrderFused, kOrderRanked };
-template <int WORDS, OrderKind KIND, int THREADS = kOrderThreads>
-__global__ __launch_bounds__(THREADS) void order_groups(OrderArgs a)
+template <int WORDS, OrderKind KIND, int THREADS>
+__device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
 {
     constexpr int ROWS = WORDS == 8 ? 256 : 32 * WORDS, WAVES = THREADS / 64, EACH = 8;
     constexpr bool FUSED = KIND == kOrderFused, RANKED = KIND == kOrderRanked;
@@ -228,12 +230,12 @@ __global__ __launch_bounds__(THREADS) void order_groups(OrderArgs a)
     __shared__ int32_t below_s, count_s, long_s;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int32_t parts = a.plan.parts, shift = a.plan.shift, ncols = 1 << shift, later = parts - 1;
-    const int64_t q = blockIdx.x / parts;
-    const int32_t part = (int32_t)(blockIdx.x - q * parts);
+    const int64_t q = item / parts;
+    const int32_t part = (int32_t)(item - q * parts);
     const int64_t r0 = q * a.p;
     const int32_t rows = (int32_t)(a.m - r0 < a.p ? a.m - r0 : a.p);
     // A thread sums up `1 << ps` columns one after another: a word more for each such stretch keeps the threads on different banks.
-    constexpr int LOG = THREADS == 256 ? 8 : 10;
+    constexpr int LOG = THREADS == 256 ? 8 : (THREADS == 512 ? 9 : 10);
     static_assert(THREADS == 1 << LOG, "");
     const int32_t ps = RANKED ? 31 : (shift > LOG ? shift - LOG : 0), spare = RANKED ? 0 : ((ncols - 1) >> ps) + 1;
     const int32_t nbw = ncols >> 5;                          // RANKED: words of the part's columns; how many lie in front of each word
@@ -563,6 +565,23 @@ __global__ __launch_bounds__(THREADS) void order_groups(OrderArgs a)
         out0 += entries_of_window;
         if (RANKED) __syncthreads();                         // the masks and the sums are read before the next window's
     }
+}
+
+template <int WORDS, OrderKind KIND, int THREADS = kOrderThreads>
+__global__ __launch_bounds__(THREADS) void order_groups(OrderArgs a)
+{
+    order_part<WORDS, KIND, THREADS>(a, (int32_t)blockIdx.x);
+}
+
+// order_groups and band_fill in one launch, the lists first: neither needs anything of the other, both wait for LDS and memory most of their time, and neither fills the
+// chip by itself.  Six waves per SIMD and four entries per thread and step: with eight entries the registers spill (4000 x 4000, 5 %, whole conversion: 24.0 us,
+// 29.7 without the limit, 23.8 so).  Dynamic LDS: the larger of the two.
+constexpr int kBothThreads = 512;
+template <int WORDS, OrderKind KIND, int V>
+__global__ __launch_bounds__(kBothThreads, 6) void order_and_fill(OrderArgs a, FillArgs f, int32_t lists)
+{
+    if ((int32_t)blockIdx.x < lists) band_fill_list<V, kBothThreads, 4>(f, blockIdx.x);
+    else order_part<WORDS, KIND, kBothThreads>(a, (int32_t)blockIdx.x - lists);
 }
 
 }  // namespace gcoo
