@@ -509,14 +509,17 @@ int64_t band_fill_chunk(int64_t k, int v, size_t lds)
 }
 
 // Whether order_groups and band_fill are one launch, in 52 KB of LDS, with which a compute unit has room for three workgroups.  More columns than those hold at a time cost
-// another turn through the entries: that is worth it up to about two such turns, and only while the threads keep the entries of a list (2048 of them).
-// Conversion, us, as two launches and as one: 3000 x 3000, 3 %: 23.9 15.9; 4000 x 4000, 5 %: 32.8 23.8; 8000 x 8000, 0.5 %: 30.0 26.6; 2 %: 43.8 38.7; 5 %: 81 76;
-// power-law rows, 16384 x 16384: 41.6 36.6; but 14000 x 14000, 0.4 %: 61.2 62.5; 2 %: 104 116.
+// another turn through the entries: that is worth it up to about two such turns, three where a group has few entries, and only while the threads keep the entries
+// of a list (2048 of them).  Not where the distinct columns have the masks and a group has up to twelve columns per entry and more than one part: the heaviest groups of power-law rows take
+// longer with their parts of twice the entries than both launches.
+// Conversion, us, as two launches and as one: 3000 x 3000, 3 %: 23.9 15.9; 5000 x 5000, 0.3 %: 24.0 14.9; 4000 x 4000, 5 %: 32.8 23.8; 8000 x 8000, 2 %: 43.8 38.7; 5 %: 81 76;
+// 14000 x 14000, 0.2 %: 49 31; but 0.4 %: 61 63; 2 %: 104 116; power-law rows, 9000 x 9000: 26 31, 12000 x 10000: 31 37, 20000 x 15000: 50 62.
 constexpr size_t kBothMaxLds = 52 * 1024;
-bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, BandPlan band)
+bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, int64_t mean, BandPlan band)
 {
     const int64_t chunk = band_fill_chunk(k, band.v, kBothMaxLds);
-    return chunk >= k || (9 * chunk >= 4 * k && nnz / (gcoo::band_blocks(m, band.h) * gcoo::kBandWaves) <= 4096);
+    if (chunk >= k) return true;
+    return nnz / (gcoo::band_blocks(m, band.h) * gcoo::kBandWaves) <= 4096 && (9 * chunk >= 4 * k || (3 * chunk >= k && k > 12 * mean));
 }
 
 // How a CSR input of this shape is put into the order of the groups; false: sorted by digits of the column.  A part has up to 4096
@@ -551,7 +554,7 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, boo
     const int64_t room = room_at(shift);
     const bool fused = !ranked && k <= ((int64_t)1 << most) && mean + mean / 16 <= room && band.h == 0 && !run_schedule_wanted(p);
     const int32_t threads = fused && (g <= 256 || mean > 2048) ? 1024 : gcoo::kOrderThreads;
-    const bool both = marked && words <= 2 && order_and_fill_wanted(m, k, nnz, band);
+    const bool both = marked && words <= 2 && !(ranked && k <= 12 * mean && mean > 800) && order_and_fill_wanted(m, k, nnz, mean, band);
     while (!fused && shift > 7 && (mean << shift) / k > (!ranked ? 1024 : (k > 12 * mean ? 640 : 400)) * (both ? 2 : 1)) --shift;
     const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
     if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;

@@ -104,6 +104,30 @@ def test_rows_of_all_lengths(m, k, lens, twice):
          32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
 
 
+@pytest.mark.parametrize("kind", ["sorted", "unsorted", "twice", "uneven"])
+@pytest.mark.parametrize("m,k,per_row,p", [(800, 3500, 150, 32), (800, 3500, 60, 32), (700, 3500, 60, 48), (9000, 9000, 9, 32), (9000, 12000, 12, 40), (3500, 3500, 17, 32),
+                                           (400, 13000, 200, 32), (60, 3500, 60, 7)])
+def test_groups_and_bands_in_one_launch(m, k, per_row, p, kind):
+    """The launch that orders the groups and fills the bands, one and two mask words, columns and places of distinct ones, both cuts, one turn over the columns and more:
+    the five arrays bit for bit, and the product by the bands, or row by row where a list is far too long for them, which both parts have to find."""
+    print(f"band, with the groups: {m}x{k} {per_row} a row p={p} {kind}", flush=True)
+    rng = np.random.default_rng(m + k + p)
+    rows = [np.sort(rng.integers(0, k, per_row)) if kind == "twice" and i % 5 == 0 else np.sort(rng.permutation(k)[:per_row]) for i in range(m)]
+    if kind == "unsorted":
+        rows = [rng.permutation(x) if i % 3 == 0 else x for i, x in enumerate(rows)]
+    if kind == "uneven":
+        rows[m // 2:m // 2 + 3] = [np.arange(k)] * 3
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    w = workloads.Workload("both", m, k, 68, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, 68)).astype(np.float32))
+    e = binding.gcoo_from_csr(m, k, *[torch.from_numpy(x).to(DEV) for x in (rp, ci, w.vals)], p, known_nnz=True).export()
+    want = orc.gcoo_from_csr(m, k, rp, ci, w.vals, p)
+    for key in ("rows", "cols", "gIdxes", "nnzPerGroup"):
+        assert np.array_equal(e[key], getattr(want, key)), key
+    assert np.array_equal(e["values"].view(np.uint32), want.values.view(np.uint32))
+    _run(w, p, binding.VARIANT_SHARE if per_row >= 60 and k == 3500 and m > 60 else binding.VARIANT_AUTO)
+
+
 @pytest.mark.parametrize("m,k,N,s", [(100, 3500, 300, 0.94), (385, 3600, 1024, 0.98), (1000, 7000, 768, 0.995), (50, 20000, 260, 0.97)])
 def test_uniform_through_the_share_variant(m, k, N, s):
     print(f"band: m={m} k={k} N={N} s={s}", flush=True)
