@@ -533,11 +533,11 @@ bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, int64_t mean, Band
 // 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (6): 33.3 33.3; power-law rows,
 // 16384 x 16384 (10): 42 35, 20000 x 15000 (9): 51 42, 9000 x 9000 (5.6): 31.3 26.9, 9000 x 8500 (5.3): 32.1 37.6, 7577 x 7577 (4.7): 33.7 39.0).
 //
-// Where a group's masks and entries fit the LDS of a workgroup and nothing else is to be made of the rows, one launch is the whole conversion, of 1024
-// threads per group for up to 256 groups, which are one to a compute unit, and for large ones (conversion and product, us, by take_rows and order_groups
-// and so; 600 x 600, 5 %, N = 600: 17.7 12.4; 1000 x 1000, 5 %: 25.7 20.8; 2500 x 2500, 1 %, N = 1024: 26.9 21.7, from host memory 48.0 35.7; 1777 x 2301, 3 %,
-// N = 1117: 40.9 36.4; 16000 x 300, 15 %, N = 64: 31.8 20.0; power-law rows, 2000 x 1300, N = 1000: 46.6 36.2.  256 and 1024 threads: 2500 x 2500 22.4 and
-// 21.5, 1777 x 2301 40.8 and 36.3, but 9000 x 1000, 2 %, N = 64 12.9 and 15.8, 20000 x 200, 30 % 27.6 and 30.8).
+// Where a group's masks and entries fit the LDS of a workgroup and nothing else is to be made of the rows, one launch is the whole conversion (conversion and
+// product, us, by take_rows and order_groups and so; 600 x 600, 5 %, N = 600: 17.7 12.4; 1000 x 1000, 5 %: 25.7 20.8; 2500 x 2500, 1 %, N = 1024: 26.9 21.7, from host
+// memory 48.0 35.7; 1777 x 2301, 3 %, N = 1117: 40.9 36.4; 16000 x 300, 15 %, N = 64: 31.8 20.0; power-law rows, 2000 x 1300, N = 1000: 46.6 36.2).  It has 1024 threads for a
+// large group, and for one of many columns while the groups are one to a compute unit (this launch, 256 and 1024 threads: 927 x 655, 16 %: 11.9 8.6; 2500 x 2500, 1 %: 8.6 7.9;
+// 256 x 4000, 1 %: 9.1 8.0; but 1000 x 1000, 2 %: 6.4 7.2; 256 x 256, 10 %: 6.2 6.9; 9000 x 1000, 2 %, and product, N = 64: 12.9 15.8).
 constexpr int64_t kOrderLds = 61 * 1024;                  // dynamic LDS of order_groups, at most
 bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, bool marked, gcoo::OrderPlan* plan)
 {
@@ -553,7 +553,7 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, boo
     const auto room_at = [&](int32_t shift) { return (kOrderLds - 4 * (((int64_t)1 << shift) * (words + 1) + 2 * 1024)) / 9; };
     const int64_t room = room_at(shift);
     const bool fused = !ranked && k <= ((int64_t)1 << most) && mean + mean / 16 <= room && band.h == 0 && !run_schedule_wanted(p);
-    const int32_t threads = fused && (g <= 256 || mean > 2048) ? 1024 : gcoo::kOrderThreads;
+    const int32_t threads = fused && (mean > 2048 || (g <= 256 && ((int64_t)words << shift) >= 4096)) ? 1024 : gcoo::kOrderThreads;
     const bool both = marked && words <= 2 && !(ranked && k <= 12 * mean && mean > 800) && order_and_fill_wanted(m, k, nnz, mean, band);
     while (!fused && shift > 7 && (mean << shift) / k > (!ranked ? 1024 : (k > 12 * mean ? 640 : 400)) * (both ? 2 : 1)) --shift;
     const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
