@@ -272,8 +272,9 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
         BD_WAIT_BAND                                                                                    \
         "s_barrier\n\t"                                                                                 \
         "s_branch .Lbd_band_A_%=\n\t"                                                                   \
-        /* (where the loop lies in the cache lines of the instructions makes up to 1 %: the same place in every build) */ \
-        ".p2align 8\n"                                                                                   \
+        /* (where the loop lies in the cache lines of the instructions makes up to 1 %: the same place in every build, the best of those tried: 36 bytes \
+           behind a multiple of 256; 14000 x 14000, 2 %: 3190 us, 3188 for 4 bytes, 3200 for none and for multiples of 32, 3214 for 20 and 52) */ \
+        ".p2align 8\n.fill 9, 4, 0xbf800000\n"                                                           \
         BD_HALF_A                                                                                       \
         BD_HALF_B                                                                                       \
         /* the rows requested for the bands beyond the last one arrive before the wave gives up its LDS */ \
