@@ -1,4 +1,4 @@
-// Conversion of a CSR input in two kernels, without a sort: take_rows reads the input once, order_groups writes the five arrays.
+// Conversion of a CSR input without a sort, in two kernels or one: take_rows reads the input once, order_groups writes the five arrays, or does both.
 //
 // Inside a group the entries are ordered by (column, row).  With the rows that hold an entry in a column as a bit mask per
 // column (at most p bits), the place of an entry is what the columns before it hold, a prefix sum of popcounts, plus the
