@@ -508,13 +508,14 @@ int64_t band_fill_chunk(int64_t k, int v, size_t lds)
     return chunk;
 }
 
-// Whether order_groups and band_fill are one launch, in 52 KB of LDS, with which a compute unit has room for three workgroups.  More columns than those hold at a time cost
+// Whether order_groups and band_fill are one launch, in 49 KB of LDS, which with 3 KB of their own variables leave a compute unit room for three workgroups (52 KB, room for two:
+// 8000 x 8000, 0.5 %, p = 42: 28.7 us, 24.9 so; 7000 x 7000, 0.35 %: 24.0 20.2).  More columns than those hold at a time cost
 // another turn through the entries: that is worth it up to about two such turns, three where a group has few entries, and only while the threads keep the entries
 // of a list (2048 of them).  Not where the distinct columns have the masks and a group has up to twelve columns per entry and more than one part: the heaviest groups of power-law rows take
 // longer with their parts of twice the entries than both launches.
 // Conversion, us, as two launches and as one: 3000 x 3000, 3 %: 23.9 15.9; 5000 x 5000, 0.3 %: 24.0 14.9; 4000 x 4000, 5 %: 32.8 23.8; 8000 x 8000, 2 %: 43.8 38.7; 5 %: 81 76;
 // 14000 x 14000, 0.2 %: 49 31; but 0.4 %: 61 63; 2 %: 104 116; power-law rows, 9000 x 9000: 26 31, 12000 x 10000: 31 37, 20000 x 15000: 50 62.
-constexpr size_t kBothMaxLds = 52 * 1024;
+constexpr size_t kBothMaxLds = 49 * 1024;
 bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, int64_t mean, BandPlan band)
 {
     const int64_t chunk = band_fill_chunk(k, band.v, kBothMaxLds);
