@@ -38,7 +38,7 @@ def _csr(m, k, density, kind, seed):
 @pytest.mark.parametrize("m,k,density,p", [(1, 1, 1.0, 1), (3, 130, 0.5, 32), (500, 127, 0.2, 32), (500, 128, 0.2, 33), (300, 4096, 0.02, 32),
                                            (300, 4097, 0.02, 31), (300, 8193, 0.01, 32), (130, 2049, 0.05, 64), (400, 300, 0.9, 64),
                                            (400, 1000, 0.3, 65), (600, 513, 0.1, 256), (1500, 700, 0.03, 8), (2100, 900, 0.05, 1),
-                                           # more than four columns per entry of a group: by the places of the distinct columns
+                                           # many columns per entry of a group: by the places of the distinct columns
                                            (300, 4097, 0.003, 31), (300, 70001, 0.0004, 32), (700, 5000, 0.0005, 64), (520, 9000, 0.0006, 256), (900, 66000, 0.00004, 8),
                                            (2000, 40, 0.004, 1), (70, 1025, 0.002, 33), (3000, 3000, 0.001, 65)])
 def test_ordered_by_masks(m, k, density, p, kind):
@@ -47,7 +47,7 @@ def test_ordered_by_masks(m, k, density, p, kind):
     _check(m, k, rp, ci, va, p)
 
 
-# 1024 threads a group up to 256 groups and for groups of more than 2048 entries, 256 otherwise; groups that just fit the LDS and just not, of more
+# 1024 threads for groups of more than 2048 entries and, up to 256 groups, of many columns, 256 otherwise; groups that just fit the LDS and just not, of more
 # entries than a thread keeps; rows of more than 512 entries, which have places by group: the first and the last row of a group, all of them, none
 @pytest.mark.parametrize("kind", ["sorted", "twice"])
 @pytest.mark.parametrize("m,k,entries,p,long", [(8192, 300, 30, 32, []), (8193, 300, 30, 32, []), (8193, 300, 75, 32, []), (64, 4096, 70, 32, []), (64, 4096, 72, 32, []),
