@@ -10,6 +10,7 @@
 #include <new>
 #include <string>
 
+#include <algorithm>
 #include <array>
 #include <atomic>
 #include <chrono>
@@ -565,7 +566,9 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, boo
     int64_t cap = mean / parts * 3 / 2 + 64;
     const int64_t most_cap = fused ? room : (both ? room_at(shift < most ? shift : most) : gcoo::kOrderMaxCap);
     cap = cap < 256 ? 256 : (cap > most_cap ? most_cap : cap);
-    const int32_t keys = ranked ? (int32_t)1 << (shift < most ? shift : most) : 0;
+    // Distinct columns of a window: uniform parts have a few hundred, and the fewer, the more workgroups fit a compute unit; heavy groups go through their entries once more for
+    // every further window (us for 4096, 2048, 1024: 12000 x 12000, 0.3 %: 38.9 34.6 34.6; power-law rows, 16384 x 16384, six draws: 42.2 41.1 48.3).
+    const int32_t keys = ranked ? (int32_t)1 << std::min({shift, most, 11}) : 0;
     *plan = {shift, (int32_t)parts, (int32_t)rows, (int32_t)((cap + 3) / 4 * 4), fused, keys, both ? gcoo::kBothThreads : threads, both};
     return true;
 }
