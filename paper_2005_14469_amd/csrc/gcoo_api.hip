@@ -145,15 +145,24 @@ public:
     {
         const hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
-            i_ = -1;
-            g_slots_lost.fetch_add(1, std::memory_order_relaxed);
+            lose();
             return hip_fail(e, "wait for a number from the device");
         }
         *answer = __atomic_load_n(host_, __ATOMIC_ACQUIRE);
         return GCOO_OK;
     }
+    // An error behind the launch may be one of an earlier call of this thread, and the kernel on its way: the slot is given back when it has ended.
+    void abandon(hipStream_t s)
+    {
+        if (hipStreamSynchronize(s) != hipSuccess) lose();
+    }
 
 private:
+    void lose()
+    {
+        i_ = -1;
+        g_slots_lost.fetch_add(1, std::memory_order_relaxed);
+    }
     int i_ = -1;
     unsigned long long* host_ = nullptr;
     unsigned long long* ticket_ = nullptr;
@@ -930,7 +939,8 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             int rc = slot.claim(s);
             if (rc != GCOO_OK) return rc;
             gcoo::read_entry_count<<<dim3(1), dim3(1), 0, s>>>(row_ptr, m, slot.host());
-            HIP_TRY(hipGetLastError());
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) { slot.abandon(s); return hip_fail(e, "read_entry_count"); }
             unsigned long long got = 0;
             rc = slot.look(s, &got);
             if (rc != GCOO_OK) return rc;
@@ -1163,7 +1173,8 @@ int gcoo_dense_nnz(int64_t m, int64_t k, const float* A_dev, int64_t lda, void* 
     const dim3 grid((unsigned)(items < gcoo::kDenseWorkgroups ? items : gcoo::kDenseWorkgroups)), block(gcoo::kDenseThreads);
     if (vw == 4) gcoo::count_dense_total<4><<<grid, block, 0, s>>>(A_dev, lda, m, k, nblk, slot.ticket(), slot.host());
     else gcoo::count_dense_total<1><<<grid, block, 0, s>>>(A_dev, lda, m, k, nblk, slot.ticket(), slot.host());
-    HIP_TRY(hipGetLastError());
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { slot.abandon(s); return hip_fail(e, "count_dense_total"); }
     unsigned long long got = 0;
     rc = slot.wait(s, &got);
     if (rc != GCOO_OK) return rc;
@@ -1219,6 +1230,7 @@ int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p
     int rc = slot.claim(s);
     if (rc != GCOO_OK) return rc;
     rc = launch_dense_count(m, k, A_dev, lda, p, buf, own_buf && dense_masks_wanted(p), slot.ticket(), slot.host(), s);
+    if (rc == GCOO_EHIP) slot.abandon(s);
     if (rc != GCOO_OK) return rc;
     unsigned long long total = 0;
     rc = own_buf ? slot.look(s, &total) : slot.wait(s, &total);

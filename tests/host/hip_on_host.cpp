@@ -86,7 +86,7 @@ int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t, v
 }
 
 int hipGetDevice(int* d) { *d = 0; return 0; }
-int hipGetLastError() { return 0; }
+int hipGetLastError() { return (int)setting("hipGetLastError"); }
 const char* hipGetErrorString(int) { return "set by the test"; }
 int hipFuncSetAttribute(const void*, int, int) { return 0; }
 int hipGetSymbolAddress(void** p, const void* var)

@@ -208,6 +208,32 @@ def slot_wait_fails(host):
     assert host.log() == []
 
 
+def slot_launch_fails(host):
+    """An error that an earlier call of the thread has left is reported behind a launch that went well: the kernel still tells its number, so its slot is
+    given back behind it, and not at all where the wait for it fails."""
+    m, k, dev = 300, 700, 1 << 20
+    n, h = C.c_int64(), C.c_void_p()
+    calls = [lambda: host.L.gcoo_from_csr(m, k, dev, dev, dev, 1, 8, 1 << 30, 1 << 50, None, C.byref(h)),
+             lambda: host.L.gcoo_dense_nnz(m, k, dev, k, None, C.byref(n)),
+             lambda: host.L.gcoo_dense_count(m, k, dev, k, 8, dev, 1 << 50, None, C.byref(n)),
+             lambda: host.L.gcoo_from_dense(m, k, dev, k, 8, dev, 1 << 50, None, C.byref(h))]
+    host.set("answer", 5)
+    for call in calls:
+        assert call() == OK
+        free = host.hip.host_told()
+        host.set("hipGetLastError", 1)
+        host.log()
+        assert call() == EHIP
+        log = host.log()
+        assert len(log) == 2 and log[0].startswith("launch") and log[1] == "wait stream", log
+        assert host.hip.host_told() == free                                  # given back
+        host.set("hipStreamSynchronize", 1)
+        assert call() == EHIP and host.hip.host_told() == free
+        host.set("hipGetLastError", 0)
+        host.set("hipStreamSynchronize", 0)
+        assert call() == OK and host.hip.host_told() != free                 # lost
+
+
 def looks_before_waiting(host):
     """A conversion that goes on behind its counting kernel takes the number as soon as it is there and waits for the stream only where it does not
     come; a wait that fails is reported, and a stream that ended without a number is not taken for one."""
