@@ -213,7 +213,8 @@ public:
             if (hipEventCreateWithFlags(&slot_->event, hipEventDisableTiming) != hipSuccess) slot_->event = nullptr;
             slot_->device = dev;
         }
-        if (!slot_->ptr && hipHostMalloc(&slot_->ptr, kStageBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) slot_->ptr = nullptr;
+        // (coherent whatever the process has as its default: kernels read what the host has written there since the last one did)
+        if (!slot_->ptr && hipHostMalloc(&slot_->ptr, kStageBytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) slot_->ptr = nullptr;
         if (slot_->event && slot_->ptr) return true;
         (void)hipGetLastError();
         slot_->held = false;

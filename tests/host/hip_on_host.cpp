@@ -95,7 +95,7 @@ int hipGetSymbolAddress(void** p, const void* var)
     *p = g_vars[var];
     return *p ? 0 : 1;
 }
-int hipHostMalloc(void** p, size_t bytes, unsigned) { *p = aligned_alloc(4096, (bytes + 4095) / 4096 * 4096); say("pinned"); return 0; }
+int hipHostMalloc(void** p, size_t bytes, unsigned flags) { *p = aligned_alloc(4096, (bytes + 4095) / 4096 * 4096); say("pinned " + std::to_string(flags)); return 0; }
 int hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return 0; }
 int hipMemcpyAsync(void* to, const void* from, size_t bytes, int, void*) { memcpy(to, from, bytes); say("copy"); return 0; }
 int hipStreamSynchronize(void*) { say("wait stream"); return (int)setting("hipStreamSynchronize"); }

@@ -186,6 +186,17 @@ def stage_release_fails(host):
     assert "record" not in log and log.count("copy") == 3 and "wait stream" in log, log
 
 
+def pinned_memory_is_coherent(host):
+    """Memory that kernels read anew after the host has written to it, or write to under the host's eyes, is coherent by request, not by the process's default."""
+    COHERENT = 0x40000000                                                    # hipHostMallocCoherent
+    assert _host_csr(host, 500, 700, 7) == OK
+    host.set("answer", 7)
+    n = C.c_int64()
+    assert host.L.gcoo_dense_nnz(30, 50, 1 << 20, 50, None, C.byref(n)) == OK
+    flags = [int(line.split()[1]) for line in host.log() if line.startswith("pinned")]
+    assert len(flags) == 2 and all(f & COHERENT for f in flags), flags
+
+
 def slot_wait_fails(host):
     """The wait for a kernel that tells the host a number fails: nobody gets its slot again, the kernel may still write there.  With all slots lost such
     calls fail instead of waiting for one."""
