@@ -44,10 +44,10 @@ def stale() -> bool:
 
 
 def _checked(src: str) -> bool:
-    """Sources whose generated code is verified by isa_check (kernels that issue loads from asm, or that
-    load straight to LDS next to the index mode)."""
+    """Sources whose generated code is verified by isa_check (kernels that issue loads from asm, that load straight to LDS next
+    to the index mode, or whose workgroups hand words to each other without release and acquire)."""
     name = os.path.basename(src)
-    return name.startswith("spdm_sched_v") or name in ("spdm_share.hip", "spdm_band.hip")
+    return name.startswith("spdm_sched_v") or name in ("spdm_share.hip", "spdm_band.hip", "gcoo_api.hip")
 
 
 def _compile(src: str) -> str:
@@ -85,6 +85,9 @@ def verify_generated_code() -> None:
             continue
         if stem == "spdm_band":
             verify_band_code(stem, text)
+            continue
+        if stem == "gcoo_api":
+            verify_count_code(stem, text)
             continue
         for kernel in sched_kernel_names(stem):
             regs, bad = isa_check.check(text, kernel)
@@ -130,6 +133,18 @@ def verify_band_code(stem: str, text: str) -> None:
         got = [int(x) for x in re.findall(rf"\.{key}:\s+(\d+)", meta)]
         if len(got) != len(instances) or max(got) > most:
             raise RuntimeError(f"{stem}: {key} {got}")
+
+
+def verify_count_code(stem: str, text: str) -> None:
+    """The dense counts: their workgroups hand what they counted to the last of them by agent scope and waits (Handed and arrive() in
+    gcoo_build_kernels.hpp); the masks, in pieces of 8 and 16 bytes, are for later launches."""
+    from . import isa_check
+    masks = ("global_store_dwordx2", "global_store_dwordx4")
+    for kernel, plain in [(f"_ZN4gcoo17count_dense_totalILi{v}E", ()) for v in (1, 4)] + \
+                         [(f"_ZN4gcoo18count_dense_blocksILi{v}ELb{m}E", masks if m else ()) for v in (1, 4) for m in (0, 1)]:
+        arrivals, problems = isa_check.check_arrivals(text, kernel, plain)
+        if arrivals != 2 or problems:
+            raise RuntimeError(f"{stem} {kernel}: {arrivals} arrivals, {problems[:3]}")
 
 
 def build(force: bool = True, jobs: int = 8) -> str:

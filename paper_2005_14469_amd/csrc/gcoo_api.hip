@@ -1198,7 +1198,7 @@ bool dense_masks_wanted(int32_t p) { return p >= 8 && p <= 64; }
 gcoo::DenseCounts dense_counts(void* buf, const Layout& L, bool masks)
 {
     char* base = static_cast<char*>(buf);
-    return {reinterpret_cast<int32_t*>(base + L.blk), reinterpret_cast<int32_t*>(base + L.gIdxes),
+    return {reinterpret_cast<gcoo::Handed<int32_t>*>(base + L.blk), reinterpret_cast<int32_t*>(base + L.gIdxes),
             reinterpret_cast<int32_t*>(base + L.nnzPerGroup), reinterpret_cast<unsigned long long*>(base + L.counter),
             masks ? reinterpret_cast<uint64_t*>(base + L.values) : nullptr};
 }

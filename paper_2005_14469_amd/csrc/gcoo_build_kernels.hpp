@@ -340,6 +340,19 @@ struct DenseTicket {
     int32_t words;                           // 1 .. kTicketWords; 1: the word itself, and none behind it
 };
 
+// A word that the workgroups of one launch hand to each other across an arrival.  It has no plain access: it is stored and loaded with agent scope, that is
+// past the L2 of an XCD, which is what arrive() stands on.  settled() is the ordinary load of it, for later launches.
+template <typename T>
+class Handed {
+public:
+    __device__ __forceinline__ void store(T x) { __hip_atomic_store(&word_, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ T load() const { return __hip_atomic_load(&word_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ T settled() const { return word_; }
+
+private:
+    T word_;
+};
+
 // All earlier memory operations of this wave have been done: loads are back, and what was stored with agent scope is where every XCD reads it.
 __device__ __forceinline__ void wait_for_memory()
 {
@@ -348,10 +361,13 @@ __device__ __forceinline__ void wait_for_memory()
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-// One thread of each workgroup: true in the one that arrives last, which gets the sum of `n` over all (below 2^48).  What that thread stored
-// with agent scope before it arrived is seen by agent-scope loads behind the last arrival.  That takes the wait alone, since such
-// stores and loads go past the L2 of an XCD; an arrival with release and acquire would write back and invalidate that L2 as well, 26 ns for each workgroup
-// one after the other.  (4000 x 4000, 500 workgroups: the launch takes 25.8 us with release and acquire on one word or on 32, 17.1 with the wait on
+// One thread of each workgroup: true in the one that arrives last, which gets the sum of `n` over all (below 2^48).  The Handed words that this thread stored
+// before it arrived are what load() reads behind the last arrival; anything else that a workgroup stores is for later launches only.
+// The language's memory model knows no such order without release and acquire, which write back and invalidate the L2 of an XCD, 26 ns for each
+// workgroup one after the other.  The machine's order is enough: a store with agent scope is done, for the wait in front of the arrival, when it has passed
+// that L2, and a load with agent scope behind the arrival goes past it too.  The build reads the generated code for both: each arrival between
+// two waits for all memory operations, nothing but masks stored in front of one without agent scope, and the last workgroup's loads with it.
+// (4000 x 4000, 500 workgroups: the launch takes 25.8 us with release and acquire on one word or on 32, 17.1 with the wait on
 // one word, 13.2 with the wait on 32 and 12.8 without any arrival.)
 __device__ __forceinline__ bool arrive(const DenseTicket& t, unsigned long long n, unsigned long long* sum)
 {
@@ -401,7 +417,7 @@ __device__ __forceinline__ int32_t block_sum_256(int32_t n, int32_t* part)
 
 // Where the counts of a dense matrix live: in the buffer of the matrix, or in one of their own until nnz is known.
 struct DenseCounts {
-    int32_t* blk;              // [g * nblk] first slot of a block
+    Handed<int32_t>* blk;      // [g * nblk] first slot of a block
     int32_t* gIdxes;           // [g + 1]
     int32_t* nnzPerGroup;      // [g]
     unsigned long long* stats; // nnz, entries of the largest group
@@ -490,7 +506,7 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
         }
         const int32_t tot = block_sum_256(n, part);
         // written where every XCD sees it, before this workgroup's arrival is counted
-        if (tid == 0) __hip_atomic_store(&out.blk[i], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) out.blk[i].store(tot);
     }
     if (tid == 0) {
         unsigned long long none;
@@ -506,7 +522,7 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
         int32_t x[4];
         const int64_t i0 = t0 + 4 * tid;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = i0 + u < items ? __hip_atomic_load(&out.blk[i0 + u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        for (int u = 0; u < 4; ++u) x[u] = i0 + u < items ? out.blk[i0 + u].load() : 0;
         const int64_t mine = (int64_t)x[0] + x[1] + x[2] + x[3];
         int64_t incl = mine;
 #pragma unroll
@@ -523,7 +539,7 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             // (a total above INT32_MAX is rejected by the host)
-            if (i0 + u < items) __hip_atomic_store(&out.blk[i0 + u], (int32_t)(at > 0x7fffffffLL ? 0x7fffffffLL : at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (i0 + u < items) out.blk[i0 + u].store((int32_t)(at > 0x7fffffffLL ? 0x7fffffffLL : at));
             at += x[u];
         }
     }
@@ -532,7 +548,7 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
     int32_t mx = 0;
     for (int64_t q = tid; q <= g; q += kDenseThreads) {
         auto first = [&](int64_t gq) {
-            return gq < g && nblk > 0 ? __hip_atomic_load(&out.blk[gq * nblk], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : total;
+            return gq < g && nblk > 0 ? out.blk[gq * nblk].load() : total;
         };
         const int32_t at = first(q);
         out.gIdxes[q] = at;
@@ -647,7 +663,7 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_blocks(const float* 
     }
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
-    int32_t first = from.blk[blockIdx.x] + incl - mine;                  // slot of the first entry of this thread's columns
+    int32_t first = from.blk[blockIdx.x].settled() + incl - mine;                  // slot of the first entry of this thread's columns
     for (int j = 0; j < w; ++j) first += wsum[j];
     if (mine == 0) return;
     int32_t at[VW];
@@ -718,7 +734,7 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_masked(const float* 
         bits[u] = c < k ? from.masks[q * k + c + u] : 0;
         mine += __popcll(bits[u]);
     }
-    const int32_t first = from.blk[blockIdx.x];
+    const int32_t first = from.blk[blockIdx.x].settled();
     int32_t at = mine;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {

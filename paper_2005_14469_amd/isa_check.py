@@ -45,9 +45,8 @@ def kernel_body(asm_text: str, mangled_prefix: str) -> list[str]:
     return body
 
 
-def check(asm_text: str, mangled_prefix: str):
-    """Returns (load destination registers, [(line number, instruction)] of offending instructions)."""
-    body = kernel_body(asm_text, mangled_prefix)
+def _graph(body: list[str]):
+    """The basic blocks of a kernel: dict(labels, insts=[(index, text, in an asm statement)], succ=[indices])."""
     # instruction stream with asm flag; blocks start at labels and after branches
     insts = []          # (text, in_asm)
     in_asm = False
@@ -65,10 +64,6 @@ def check(asm_text: str, mangled_prefix: str):
                 continue
             t = l.strip().split(";")[0].strip()
         insts.append((t, in_asm))
-    load_regs: set[int] = set()
-    for t, a in insts:
-        if a and t.startswith("global_load"):
-            load_regs |= _regs(t.split()[1].rstrip(","))
     # basic blocks
     blocks = []         # dict(label, insts=[(idx, text, in_asm)], succ=[...])
     cur = dict(labels=[], insts=[])
@@ -126,9 +121,22 @@ def check(asm_text: str, mangled_prefix: str):
             succ.append(bi + 1)
         b["succ"] = succ
 
+    return blocks
+
+
+_VMEM = ("global_load", "global_store", "global_atomic", "buffer_load", "buffer_store", "flat_load", "flat_store",
+         "scratch_load", "scratch_store")
+
+
+def check(asm_text: str, mangled_prefix: str):
+    """Returns (load destination registers, [(line number, instruction)] of offending instructions)."""
+    blocks = _graph(kernel_body(asm_text, mangled_prefix))
+    insts = [(t, a) for b in blocks for _, t, a in b["insts"]]
+    load_regs: set[int] = set()
+    for t, a in insts:
+        if a and t.startswith("global_load"):
+            load_regs |= _regs(t.split()[1].rstrip(","))
     CAP = 64
-    VMEM = ("global_load", "global_store", "global_atomic", "buffer_load", "buffer_store", "flat_load", "flat_store",
-            "scratch_load", "scratch_store")
 
     def transfer(b, queue, report=None):
         queue = list(queue)
@@ -143,7 +151,7 @@ def check(asm_text: str, mangled_prefix: str):
                         queue = []
                 continue
             used = _regs(t)
-            if op.startswith(VMEM):
+            if op.startswith(_VMEM):
                 is_load = "_load" in op
                 dst = _regs(t.split()[1].rstrip(",")) if is_load else set()
                 if report is not None:
@@ -184,6 +192,74 @@ def check(asm_text: str, mangled_prefix: str):
         if entry[bi] is not None:
             transfer(b, entry[bi], bad)
     return sorted(load_regs), bad
+
+
+def check_arrivals(asm_text: str, mangled_prefix: str, plain_stores: tuple = ()):
+    """The arrivals (`global_atomic_add_x2`) of a kernel whose workgroups hand words to the last of them without release and acquire.
+
+    What one stores with agent scope (sc1) is past the caches of its XCD once the store is done, and a load with agent scope goes past
+    those of the reader's.  Returns (number of arrivals, list of problems).  Proved on the control-flow graph, over all paths:
+      * every arrival has nothing outstanding in front of it: a wait for vmcnt(0) behind the last vector-memory operation;
+      * no vector-memory operation and no barrier follows an arrival without such a wait in between;
+      * a store from which an arrival can be reached is one with agent scope, or of an opcode in `plain_stores` (what only later launches read);
+      * a load that can be reached from an arrival is one with agent scope.
+    """
+    blocks = _graph(kernel_body(asm_text, mangled_prefix))
+    arrival = "global_atomic_add_x2"
+    reaches = [any(t.startswith(arrival) for _, t, _ in b["insts"]) for b in blocks]         # an arrival lies in the block or behind it
+    changed = True
+    while changed:
+        changed = False
+        for i, b in enumerate(blocks):
+            if not reaches[i] and any(reaches[j] for j in b["succ"]):
+                reaches[i] = changed = True
+    problems, arrivals = [], set()
+
+    def walk(bi, state, report):
+        out, pending, behind = state                   # outstanding operations, an arrival not waited for, an arrival before
+        insts = blocks[bi]["insts"]
+        last = max((n for n, (_, t, _) in enumerate(insts) if t.startswith(arrival)), default=-1)
+        later = any(reaches[j] for j in blocks[bi]["succ"])
+        for n, (i, t, _) in enumerate(insts):
+            op = t.split()[0]
+            if op == "s_waitcnt":
+                if re.search(r"vmcnt\(0\)", t):
+                    out = pending = False
+                continue
+            if op == "s_barrier" and pending and report:
+                problems.append(f"{i}: a barrier behind an arrival that was not waited for")
+            if not op.startswith(_VMEM):
+                continue
+            if report:
+                if pending:
+                    problems.append(f"{i}: '{t}' behind an arrival that was not waited for")
+                if op == arrival and out:
+                    problems.append(f"{i}: an arrival with operations outstanding")
+                if "_store" in op and (later or n < last) and " sc1" not in t and op not in plain_stores:
+                    problems.append(f"{i}: '{t}' in front of an arrival without agent scope")
+                if "_load" in op and behind and " sc1" not in t:
+                    problems.append(f"{i}: '{t}' behind an arrival without agent scope")
+            if op == arrival:
+                arrivals.add(i)
+                pending = behind = True
+            out = True
+        return out, pending, behind
+
+    entry = [None] * len(blocks)
+    entry[0] = (False, False, False)
+    work = [0]
+    while work:
+        bi = work.pop()
+        after = walk(bi, entry[bi], False)
+        for j in blocks[bi]["succ"]:
+            new = after if entry[j] is None else tuple(a or b for a, b in zip(entry[j], after))
+            if new != entry[j]:
+                entry[j] = new
+                work.append(j)
+    for bi in range(len(blocks)):
+        if entry[bi] is not None:
+            walk(bi, entry[bi], True)
+    return len(arrivals), problems
 
 
 def check_lds_loads(asm_text: str, mangled_prefix: str, in_flight: int = 0, asm_only: bool = False):

@@ -129,3 +129,40 @@ def test_lds_load_checker_sees_planted_mistakes(share_asm):
     assert weakened != body
     _, problems = isa_check.check_lds_loads(head + weakened, SHARE, in_flight=6)
     assert problems and "barrier" in problems[0]
+
+
+# ------------------------------------------------------------------ counts that the last workgroup reads
+
+@pytest.fixture(scope="module")
+def count_asm():
+    src = os.path.join(CSRC, "gcoo_api.hip")
+    out = os.path.join(tempfile.mkdtemp(prefix="gcoo_isa_"), "api.s")
+    subprocess.check_call(["hipcc", *build.FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S",
+                           "--cuda-device-only", "-o", out, src], stderr=subprocess.DEVNULL)
+    return open(out).read()
+
+
+@pytest.mark.parametrize("vw", [1, 4])
+def test_arrivals_are_between_waits_and_what_they_hand_over_has_agent_scope(count_asm, vw):
+    """And the checker itself: a wait taken out, a count stored or loaded without agent scope, a load brought in front of the wait behind
+    an arrival, in the text alone."""
+    build.verify_count_code("gcoo_api", count_asm)
+    K = f"_ZN4gcoo18count_dense_blocksILi{vw}ELb0E"
+    start = re.search(rf"^{re.escape(K)}\w*:", count_asm, re.M).start()
+    end = count_asm.index(".Lfunc_end", start)
+    head, body, tail = count_asm[:start], count_asm[start:end], count_asm[end:]
+    full = "s_waitcnt vmcnt(0) expcnt(0) lgkmcnt(0)"
+    arrival = body.index("global_atomic_add_x2")
+    stored = body.rindex("global_store_dword ", 0, arrival)
+    loaded = body.index("global_load_dword ", body.index("s_barrier", arrival))
+
+    def plain(at):
+        eol = body.index("\n", at)
+        return body[:at] + body[at:eol].replace(" sc1", "") + body[eol:]
+    last_wait = body.rindex(full, 0, arrival)
+    eol = body.index("\n", arrival)
+    for planted, what in [(body[:last_wait] + "s_nop 0" + body[last_wait + len(full):], "outstanding"), (plain(stored), "in front of"), (plain(loaded), "behind"),
+                          (body[:eol] + "\n\tglobal_load_dword v1, v0, s[2:3] sc1" + body[eol:], "not waited for")]:
+        assert planted != body
+        arrivals, problems = isa_check.check_arrivals(head + planted + tail, K)
+        assert problems and any(what in x for x in problems), (what, problems)
