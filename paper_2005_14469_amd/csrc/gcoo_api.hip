@@ -456,7 +456,9 @@ double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 // they are fetched in four-byte pieces) and 2.56 ns per entry of the block, 1.77 in the tall cut, whose tiles are half as wide; C and B once, and
 // more for both when they do not fit the memory-side cache.  The tall cut (fitted to 140 measurements like those of the two others, 2000 to 14000 rows
 // and columns, 0.05 to 2 % dense, N = 300 to 14000; mean error 4 to 7 %) is bound by what it fetches, which the compute units share, rather than by its last round: that
-// counts in full for one round and less the more there are.
+// counts in full for one round and less the more there are.  With more than 40 entries per (wave, band) the multiply-adds, which a compute unit has to itself, come
+// near that bound, and the last round counts for half of what was left out (10000 x 10000, 0.75 %, heights of 48, 44 and 40, that is 4.3, 4.6 and 4.9 rounds: 804 750 753 us;
+// 9600 x 9600, 0.9 %, 44 and 48, 4.1 and 3.8 rounds: 798 683).
 double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bool aligned)
 {
     const int64_t blocks = gcoo::band_blocks(m, plan.h), tile = 64 * plan.v, tiles = (N + tile - 1) / tile, rounds = (blocks * tiles + 255) / 256;
@@ -468,7 +470,8 @@ double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bo
         if (aligned) return 6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6);
         return 7.4 + (double)rounds * (1.08 * bands + 0.00255 * entries) + row * (md / 3.8e6 + kd / 17.8e6 + outside * (md + kd) / 14.6e6);
     }
-    const double full = md / block_rows * (double)tiles / 256.0, turns = full + ((double)rounds - full) * (rounds > 1 ? 1.2 / (double)rounds : 1.0);
+    const double full = md / block_rows * (double)tiles / 256.0, part = rounds > 1 ? 1.2 / (double)rounds : 1.0;
+    const double turns = full + ((double)rounds - full) * (gcoo::band_entries(m, k, nnz, plan.h, 2) > 40.0 ? 0.5 + 0.5 * part : part);
     if (aligned) return 6.2 + turns * (0.722 * bands + 0.00177 * entries) + row * (md / 3.76e6 + outside * (md + kd) / 9.8e6);
     return 10.2 + turns * (0.771 * bands + 0.00234 * entries) + row * (md / 3.1e6 + outside * (md + kd) / 9.6e6);
 }
@@ -477,10 +480,11 @@ double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bo
 // product with N = k is fastest, and the schedule is built where that product gains more by it than a conversion
 // pays for it (12 us), or where GCOO_VARIANT_SHARE has to be served.
 // The tall cut fetches half as much and has half as many barriers, but reads LDS eight bytes at a time, which takes as long as sixteen.  It is
-// taken where its expected time is clearly the shorter one and a (wave, band) has no more than 64 entries (product alone, us, wide and tall; 8000 x
-// 8000, 0.35 %: 298 286, 0.5 %: 336 300, 1 %: 437 453, 2 %: 638 739; 12000 x 12000, 0.2 %: 813 670, 0.5 %: 1152 876, 1 %: 1474 1362; 4000 x 4000,
-// 0.5 %: 59 51, 2 %: 103 109; 14001 x 14001, 0.5 %: 2162 1795; 14000 x 14000, 0.3 %, N = 500: 92 64; over 100 such shapes 10 % less than with the
-// wide cut alone, 4 % more at the worst).
+// taken where its expected time is clearly the shorter one, by 3 %, by 1 % above 40 entries per (wave, band), where band_time() is the closer, and never above
+// 66 (product alone, us, wide and tall; 8000 x 8000, 0.35 %: 295 275, 0.5 %: 333 294, 0.9 %: 420 405, 1.2 %: 480 487; 12000 x 12000, 0.2 %: 809 669, 0.5 %: 1153 874, 0.9 %:
+// 1417 1309; 4000 x 4000, 0.5 %: 59 51, 2 %: 103 109; 14000 x 14000, 0.75 %: 2088 1845; 0.3 %, N = 500: 92 64).  Over 103 square matrices of 5000 to 14000 rows, 0.2 to
+// 1.2 % dense, that is 8 % less than with the wide cut alone.  Three of them lose by it, all of 10000 rows, whose wide launch is five rounds without a remainder:
+// 0.2 % 434 450, 0.9 % 829 838, 1 % 874 898.
 BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return {0, 0};
@@ -498,8 +502,9 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
             // the columns of every list's rows as a bitmap, in the second sort buffer
             if (h % gcoo::band_lists_of(v) || gcoo::band_lists(m, h, v) * ((k + 31) / 32) > 3 * nnz) continue;
             const BandPlan plan = {h, v};
-            if (v == 2 && gcoo::band_entries(m, k, nnz, h, v) > 64.0) continue;
-            const double t = band_time(m, k, nnz, k, plan, aligned), least = best.v == v ? best_time : 0.97 * best_time;
+            const double entries = gcoo::band_entries(m, k, nnz, h, v);
+            if (v == 2 && entries > 66.0) continue;
+            const double t = band_time(m, k, nnz, k, plan, aligned), least = best.v == v ? best_time : (entries > 40.0 ? 0.99 : 0.97) * best_time;
             if (best.h == 0 || t < least) { best_time = t; best = plan; }
         }
     }
