@@ -546,6 +546,8 @@ bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, int64_t mean, Band
 // With more than 5.5 columns per entry of a group the distinct columns have the masks, not all of them, unless the whole conversion is one launch:
 // parts of up to 16384 columns, and fewer where a part would hold more than 640 entries, 400 up to twelve columns per entry: there one of a matrix with power-law
 // rows holds many times the mean (640 and 400: 20000 x 16000, 0.1 % (31): 44 51; power-law rows, 11370 x 14582 (9): 39 35, 12000 x 10000 (6): 44 32)
+// (in a launch of its own up to fourteen columns per entry: power-law rows of up to 20000 columns are there, and three parts are not enough for the heavy groups; 640 and 400:
+// power-law rows, 20000 x 20000 (13.2): 61 42, 17000 x 20000 (12.9): 58 39; but 20000 x 20000, 0.24 % (13): 67 72, 16000 x 16000, 0.24 % (13): 48 54)
 // (whole conversion, us, by masks or, beyond 32 columns per entry, by digits, and so; columns per entry in brackets: 12001 x 12001, 0.05 % (62): 21 12;
 // 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (6): 33.3 33.3; power-law rows,
 // 16384 x 16384 (10): 42 35, 20000 x 15000 (9): 51 42, 9000 x 9000 (5.6): 31.3 26.9, 9000 x 8500 (5.3): 32.1 37.6, 7577 x 7577 (4.7): 33.7 39.0).
@@ -572,7 +574,8 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, boo
     const bool fused = !ranked && k <= ((int64_t)1 << most) && mean + mean / 16 <= room && band.h == 0 && !run_schedule_wanted(p);
     const int32_t threads = fused && (mean > 2048 || (g <= 256 && ((int64_t)words << shift) >= 4096)) ? 1024 : gcoo::kOrderThreads;
     const bool both = marked && words <= 2 && !(ranked && k <= 12 * mean && mean > 800) && order_and_fill_wanted(m, k, nnz, mean, band);
-    while (!fused && shift > 7 && (mean << shift) / k > (!ranked ? 1024 : (k > 12 * mean ? 640 : 400)) * (both ? 2 : 1)) --shift;
+    const int64_t each = !ranked ? 1024 : (k > (both ? 12 : 14) * mean ? 640 : 400);              // entries of a part
+    while (!fused && shift > 7 && (mean << shift) / k > each * (both ? 2 : 1)) --shift;
     const int64_t parts = (k + ((int64_t)1 << shift) - 1) >> shift;
     if (parts > gcoo::kOrderMaxParts || parts * g > 0x7fffffffLL) return false;
     // lists of rows of take_rows: those of the band schedule, else enough workgroups for four per compute unit

@@ -372,6 +372,18 @@ def tall_rounds(host):
         assert workgroups >= 0.95 * 256 * -(-workgroups // 256), (n, density, line)
 
 
+def parts_of_power_law_rows(host):
+    """The groups of a matrix with thirteen columns per entry of a group, as 20000 power-law rows have (exponent 1.5, at most 4096 entries), are cut into five parts: with three,
+    one workgroup had a third of a heavy group to itself (the conversion, us: 61 with three, 42 with five).  Where the bands are filled in the same launch parts are larger."""
+    for m, k, nnz, parts in [(20000, 20000, 944083, 5), (17000, 20000, 822886, 5), (18000, 20000, 847083, 5), (20000, 20000, 980676, 5), (20000, 20000, 800000, 3)]:
+        host.log()
+        host.matrix(m, k, nnz, 32)
+        (line,) = [x for x in host.log() if "order_groups" in x]
+        assert int(line.split()[2]) == parts * ((m + 31) // 32), (m, k, nnz, line)
+    host.matrix(14000, 14000, 470400, 32)
+    assert any("order_and_fill" in x for x in host.log())
+
+
 # ---- threads ---------------------------------------------------------------------------------------------
 
 def one_handle_many_threads(host):
