@@ -172,8 +172,10 @@ int gcoo_from_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32
 /*
  * The same in the two steps of Algorithm 1, for a caller that sizes dev_buf by the count and reads A_dev for it only once:
  * gcoo_dense_count() counts into count_buf (gcoo_dense_count_bytes() bytes of device memory, 256-byte aligned) and waits for
- * *nnz; gcoo_from_dense_counted() takes that nnz and count_buf, which it only reads, with the same matrix, p and stream, and does
- * not wait for the device.
+ * *nnz, not for the stream: count_buf is complete for what follows on `stream`.  gcoo_from_dense_counted() takes that nnz and count_buf, which it only reads, with the
+ * same matrix, p and stream, and does not wait for the device.
+ * count_buf holds the counts (4 bytes for each group and 256 of its columns, and a few for each group) and, for 8 <= p <= 64, a bit per element of A, so that
+ * A is not read again where it has no entry: 8 bytes for each group and column, that is a quarter of A at p = 8, a sixteenth at p = 32, a 32nd at p = 64.
  */
 size_t gcoo_dense_count_bytes(int64_t m, int64_t k, int32_t p);
 int gcoo_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* count_buf, size_t count_buf_bytes,

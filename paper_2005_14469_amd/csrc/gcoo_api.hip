@@ -526,11 +526,14 @@ int64_t band_fill_chunk(int64_t k, int v, size_t lds)
 
 // Whether order_groups and band_fill are one launch, in 49 KB of LDS, which with 3 KB of their own variables leave a compute unit room for three workgroups (52 KB, room for two:
 // 8000 x 8000, 0.5 %, p = 42: 28.7 us, 24.9 so; 7000 x 7000, 0.35 %: 24.0 20.2).  More columns than those hold at a time cost
-// another turn through the entries: that is worth it up to about two such turns, three where a group has few entries, and only while the threads keep the entries
-// of a list (2048 of them).  Not where the distinct columns have the masks and a group has up to twelve columns per entry and more than one part: the heaviest groups of power-law rows take
-// longer with their parts of twice the entries than both launches.
+// another turn through the entries: that is worth it up to about two such turns, three where a group has few entries, and only for lists of up to 4096
+// entries, twice what the threads keep.  order_plan() makes one more exception, where the distinct columns have the masks and a group has more than 800 entries and up to
+// twelve columns for each: there a part of twice the entries holds too much of the heaviest groups of power-law rows (exponent 1.5, at most 4096).  The host does not know
+// whether rows are uneven, so uniform matrices of that shape stay outside as well, and power-law rows of another shape are inside.
 // Conversion, us, as two launches and as one: 3000 x 3000, 3 %: 23.9 15.9; 5000 x 5000, 0.3 %: 24.0 14.9; 4000 x 4000, 5 %: 32.8 23.8; 8000 x 8000, 2 %: 43.8 38.7; 5 %: 81 76;
-// 14000 x 14000, 0.2 %: 49 31; but 0.4 %: 61 63; 2 %: 104 116; power-law rows, 9000 x 9000: 26 31, 12000 x 10000: 31 37, 20000 x 15000: 50 62.
+// 14000 x 14000, 0.2 %: 49 31; 2 %: 104 116.  With the distinct columns' masks and up to twelve columns per entry: power-law rows, 9000 x 9000: 26 29, 12000 x 10000: 30 32,
+// 14000 x 14000: 37 40, but 16384 x 16384: 35 to 46 and 38 to 50; uniform, 8000 x 8000, 0.44 %: 30 23, 14000 x 14000, 0.3 %: 53 43, 20000 x 16000, 0.32 %: 78 68.
+// Power-law rows of exponent 1.3, masks for all columns: 12000 x 10000 40 49, 9000 x 9000 36 41, 4000 x 4000 25 25.
 constexpr size_t kBothMaxLds = 49 * 1024;
 bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, int64_t mean, BandPlan band)
 {
@@ -549,8 +552,10 @@ bool order_and_fill_wanted(int64_t m, int64_t k, int64_t nnz, int64_t mean, Band
 // (in a launch of its own up to fourteen columns per entry: power-law rows of up to 20000 columns are there, and three parts are not enough for the heavy groups; 640 and 400:
 // power-law rows, 20000 x 20000 (13.2): 61 42, 17000 x 20000 (12.9): 58 39; but 20000 x 20000, 0.24 % (13): 67 72, 16000 x 16000, 0.24 % (13): 48 54)
 // (whole conversion, us, by masks or, beyond 32 columns per entry, by digits, and so; columns per entry in brackets: 12001 x 12001, 0.05 % (62): 21 12;
-// 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (6): 33.3 33.3; power-law rows,
-// 16384 x 16384 (10): 42 35, 20000 x 15000 (9): 51 42, 9000 x 9000 (5.6): 31.3 26.9, 9000 x 8500 (5.3): 32.1 37.6, 7577 x 7577 (4.7): 33.7 39.0).
+// 20000 x 20000, 0.05 % (62): 65 49; 8000 x 8000, 0.1 % (31): 14.3 12.2; 0.2 % (16): 29.6 27.6; 0.5 % (6): 33.3 33.3; power-law rows of exponent 1.5, 9000 x 8500 (5.3): 32.1 37.6,
+// 7577 x 7577 (4.7): 33.7 39.0.  With the other steps since, two or three matrices each: 16384 x 16384 (10): 43 42, from 0.86x to 1.04x for one matrix; 20000 x 15000 (9): 50 49;
+// 12000 x 10000 (8): 35 30; 9000 x 9000 (5.6): 33 26; 20000 x 20000 (13): 49 42.  Rows of exponent 1.6 and 1.8, whose heaviest groups are a large share of all entries, are
+// slower so: 16384 x 16384 39 91 and 37 49, 9000 x 9000 31 39 and 24 42: one workgroup goes through such a group).
 //
 // Where a group's masks and entries fit the LDS of a workgroup and nothing else is to be made of the rows, one launch is the whole conversion (conversion and
 // product, us, by take_rows and order_groups and so; 600 x 600, 5 %, N = 600: 17.7 12.4; 1000 x 1000, 5 %: 25.7 20.8; 2500 x 2500, 1 %, N = 1024: 26.9 21.7, from host
@@ -1232,7 +1237,9 @@ int launch_dense_count(int64_t m, int64_t k, const float* A_dev, int64_t lda, in
     return GCOO_OK;
 }
 
-// The same, and the wait for its sum.  `own_buf`: counts only, the matrix gets a buffer of its own.
+// The same, and the wait for its sum.  `own_buf`: counts only, the matrix gets a buffer of its own.  In the buffer of the matrix (gcoo_from_dense()) the call waits for
+// the stream without a look: that it synchronises is its description, and a caller may read in its status whether the work before it went well, which a number
+// that has come does not say.
 int count_dense(int64_t m, int64_t k, const float* A_dev, int64_t lda, int32_t p, void* buf, bool own_buf, hipStream_t s, int64_t* nnz)
 {
     HostSlot slot;

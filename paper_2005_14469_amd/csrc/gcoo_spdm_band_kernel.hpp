@@ -15,13 +15,13 @@
 // moves them.  A multiply-add with a scalar (or DPP) operand or in index mode takes 1.8 ns per SIMD, the other vector
 // instructions too: five of them per single entry, 9 ns, are what bounds dense bands; 10.1 measured in a loop of nothing else.
 // By the counters a SIMD issues a vector instruction every 2.5 ns at 8000 x 8000, 10 %, and every 2.9 at 14000 x 14000, 2 % (15 of 16 waves resident,
-// waiting half their time).  At 8000 x 8000, 0.5 %, it is every 5.0 ns: there the rows of B are the bound, 5.1 GB of them into LDS at 15.3 TB/s
-// where a loop of nothing but such requests and barriers reaches 16.9.  No bank conflicts anywhere.
+// waiting half their time).  Sparser matrices have few entries per (wave, band), 3.7 ns at 4000 x 4000, 2 %: there the bands by themselves weigh.  No bank conflicts anywhere.
 //
 // The tall cut (V = 2): the same registers and the same LDS hold twice the rows of A and of B, half as wide.  A row of B is fetched for twice as
 // many rows of A, and a launch has half as many bands, each with four times the entries of a wave; an entry costs a multiply-add
 // less than half but the same address, read and index (7.5 ns in a loop of nothing else, where the wide cut takes 10.2 for twice the columns): the unit that reads LDS takes
-// as long for 8 bytes per lane as for 16, and is the bound of dense matrices.  For sparse ones what is fetched and the bands are: 8000 x 8000, 0.5 %: 336 -> 300 us,
+// as long for 8 bytes per lane as for 16, and is the bound of dense matrices.  For sparse ones what is fetched and the bands are: 8000 x 8000, 0.5 %: 333 -> 294 us (a vector
+// instruction every 4.3 ns, rows of B and entries from L2 at 9.2 TB/s),
 // where the same launch without its multiply-adds takes 290, without its requests 240, and with neither requests nor
 // entries 68: a band is a chain of waits (rows of B from L2, LDS, barrier) that fifteen other waves in the same phase do not fill.
 //
@@ -272,8 +272,8 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
         BD_WAIT_BAND                                                                                    \
         "s_barrier\n\t"                                                                                 \
         "s_branch .Lbd_band_A_%=\n\t"                                                                   \
-        /* (where the loop lies in the cache lines of the instructions makes up to 1 %: the same place in every build, the best of those tried: 36 bytes \
-           behind a multiple of 256; 14000 x 14000, 2 %: 3190 us, 3188 for 4 bytes, 3200 for none and for multiples of 32, 3214 for 20 and 52) */ \
+        /* (where the loop lies in the cache lines of the instructions makes up to 1 %: the same place in every build, 36 bytes behind a multiple of 256, so that no change in \
+           front of it moves it; 14000 x 14000, 2 %: 3167 - 3177 us so, 3194 - 3201 without any alignment, as at multiples of 32; 8000 x 8000, 10 %: 2285 - 2295 and 2303 - 2310) */ \
         ".p2align 8\n.fill 9, 4, 0xbf800000\n"                                                           \
         BD_HALF_A                                                                                       \
         BD_HALF_B                                                                                       \
