@@ -144,8 +144,7 @@ def _on(device_index: int):
 def _used_on(t: torch.Tensor, stream) -> None:
     """`t`, of the current stream's memory, is used by kernels on `stream`: once it is dropped its memory is given out again only behind them.  (That `stream`
     is ordered behind what the current one has done so far is the caller's part, as everywhere in torch.)"""
-    if stream is not None:
-        t.record_stream(stream if isinstance(stream, torch.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, device=t.device))
+    t.record_stream(stream if isinstance(stream, torch.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, device=t.device))
 
 
 def gcoo_device_bytes(m: int, k: int, nnz: int, p: int) -> int:
@@ -257,7 +256,8 @@ def gcoo_from_csr(m: int, k: int, row_ptr, col_idx, vals, p: int, device="cuda:0
         raise GcooError(GCOO_EINVAL, "gcoo_device_bytes")
     with _on(index):
         buf = _alloc(need, device)
-        _used_on(buf, stream)
+        if stream is not None:
+            _used_on(buf, stream)
         out = C.c_void_p()
         sp = _raw_stream(index) if stream is None else stream.cuda_stream
         if on_dev and known_nnz:
@@ -284,7 +284,8 @@ def gcoo_from_csr_device_static(m: int, k: int, row_ptr: torch.Tensor, col_idx: 
             if need == 0:
                 raise GcooError(GCOO_ELIMIT if nnz > GCOO_STATIC_MAX_NNZ else GCOO_EINVAL, "gcoo_static_handle_bytes")
             out_buf = _alloc(need, row_ptr.device)
-        _used_on(out_buf, stream)
+        if stream is not None:
+            _used_on(out_buf, stream)
         out = C.c_void_p()
         _check(lib().gcoo_from_csr_device_static(m, k, nnz, row_ptr.data_ptr(), col_idx.data_ptr(), vals.data_ptr(), p,
                                                  out_buf.data_ptr(), out_buf.numel(), _stream_ptr(stream), C.byref(out)),
@@ -314,11 +315,13 @@ def gcoo_from_dense(A: torch.Tensor, p: int, stream=None) -> GcooMatrix:
     with _on(A.get_device()):
         sp = _stream_ptr(stream)
         counts = _alloc(nbytes, A.device)
-        _used_on(counts, stream)
+        if stream is not None:
+            _used_on(counts, stream)
         n, out = C.c_int64(), C.c_void_p()
         _check(L.gcoo_dense_count(m, k, A.data_ptr(), lda, p, counts.data_ptr(), counts.numel(), sp, C.byref(n)), "gcoo_from_dense")
         buf = _alloc(L.gcoo_device_bytes(m, k, n.value, p), A.device)
-        _used_on(buf, stream)
+        if stream is not None:
+            _used_on(buf, stream)
         _check(L.gcoo_from_dense_counted(m, k, n.value, A.data_ptr(), lda, p, counts.data_ptr(), buf.data_ptr(), buf.numel(), sp,
                                          C.byref(out)), "gcoo_from_dense")
     return GcooMatrix(out.value, buf)
@@ -334,7 +337,8 @@ def gcoo_spdm(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor | None = None,
     assert kb == k and (cs == 1 or N <= 1)
     if C_out is None:
         C_out = torch.empty((m, N), dtype=torch.float32, device=B.device)
-        _used_on(C_out, stream)
+        if stream is not None:
+            _used_on(C_out, stream)
     assert C_out.is_cuda and C_out.dtype is torch.float32 and C_out.shape == (m, N)
     if k <= 1:
         ldb = max(N, 1)
