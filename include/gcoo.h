@@ -237,7 +237,7 @@ int gcoo_spdm_pick(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_
 #define GCOO_KERNEL_LDS   1  /* spdm_lds */
 #define GCOO_KERNEL_SCHED 2  /* spdm_sched, spdm_sched_coop: the run schedule */
 #define GCOO_KERNEL_SHARE 3  /* spdm_share: the share schedule */
-#define GCOO_KERNEL_ROWS  4  /* spdm_rows, spdm_vectors: the entries in row order */
+#define GCOO_KERNEL_ROWS  4  /* spdm_rows, spdm_rows_tile, spdm_vectors: the entries in row order */
 #define GCOO_KERNEL_BAND  5  /* spdm_band: the band schedule */
 int gcoo_spdm_kernel(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int64_t N,
                      const float* C_dev, int64_t ldc, int variant);

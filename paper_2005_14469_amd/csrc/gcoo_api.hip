@@ -452,6 +452,58 @@ double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
     if (lines) return 6.2 + row * (taken * (1.0 + std::pow(kd / 22400.0, 1.59)) / 31.7e6 + (double)m / 12.9e6 + kd / 3.4e6);
     return 7.3 + row * (taken * (1.0 + std::pow(kd / 10700.0, 0.95)) / 32.7e6 + (double)m / 5.2e6 + kd / 6.9e6);
 }
+// The same for matrices of so few columns that the tile kernel is the other choice (k <= 2500 or so, cache-resident, 1336 products of 100 to 20000 rows, N = 16 to 8000, mean error 8 %):
+// what its slots take of B is whole tiles, and launches of few workgroups leave compute units idle.
+double few_columns_rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
+{
+    const int64_t tile = N <= 16 ? 16 : (N <= 32 ? 32 : (N > 64 && k <= (lines ? 4096 : 6500) ? 128 : 64)), tiles = (N + (lines ? 0 : 31) + tile - 1) / tile;
+    const double mean = (double)nnz / (double)m;
+    return 4.2 + 4.0 * ((double)nnz * (double)(tiles * tile) / (lines ? 32.2e6 : 28.2e6) + (double)m * (double)N / 5.0e6) + 0.0044 * std::min(mean, 400.0);
+}
+// How the tile kernel cuts a product, and the time that this takes; row_wgs = 0: it does not serve the shape.  A round of the launch over the compute units, two workgroups to one
+// where their LDS allows it, costs 1.5 us and what the tiles take to come in, and the entries of its rows: 3.8 ns per sixteen of them while enough waves read LDS, 26 ns per entry of a row for
+// a wave by itself.  Where rows are long and workgroups have fewer of them than slots, a row has a whole wave to itself (`whole`; 1000 x 2480, 20 %, N = 64: 19.7 us with a row per slot, 9.1 so).
+// Fitted to the products above in 2 to 14 cuts each: mean error 8 %; the cut so chosen takes 1.3 % longer than the best one.
+struct TilePlan { int64_t row_wgs; bool whole; double time; };
+TilePlan tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
+{
+    static thread_local struct { int64_t m, k, nnz, N; TilePlan plan; } last = {0, 0, 0, 0, {0, false, 0.0}};
+    if (last.m == m && last.k == k && last.nnz == nnz && last.N == N) return last.plan;
+    TilePlan best = {0, false, 0.0};
+    if (m >= 1 && k >= 1 && N >= gcoo::kTileCols && nnz <= gcoo::kTileMaxNnz) {
+        const int64_t tiles = (N + gcoo::kTileCols - 1) / gcoo::kTileCols, room = (gcoo::kTileLdsBytes - 4 - (k + 1) * (4 * gcoo::kTileCols)) / 6;
+        const int64_t most_rows = std::min<int64_t>(room, gcoo::kTileMaxRows), least = most_rows >= 1 ? (m + most_rows - 1) / most_rows : 0;
+        const double mean = (double)nnz / (double)m;
+        const int64_t wanted[] = {least, 256 / tiles, 512 / tiles, 768 / tiles, 1024 / tiles, m / 512, m / 256};
+        for (int64_t wgs : wanted) {
+            if (least < 1 || wgs < least) continue;
+            const int64_t rows = (m + wgs - 1) / wgs, total = tiles * ((m + rows - 1) / rows);
+            if (total > 0x7ffffff0LL) continue;
+            const int64_t per = gcoo::tile_lds(k, rows) <= gcoo::kTileLdsBytes / 2 - 16 && total > 256 ? 2 : 1, rounds = (total + 256 * per - 1) / (256 * per);
+            for (int whole = 0; whole <= (mean >= 24.0 ? 1 : 0); ++whole) {
+                const double items = whole ? (double)rows : (double)((rows + gcoo::kTileCols - 1) / gcoo::kTileCols), steps = whole ? std::ceil(mean / 16.0) : mean;
+                const double full = (double)per * items * (steps + (whole ? 12.0 : 0.0)) * 0.0038, alone = std::ceil(items / 16.0) * (steps * 0.026 + (whole ? 0.52 : 0.38));
+                const double t = 2.4 + (double)rounds * (1.54 + 0.00098 * (double)(k * per) + std::max(full, alone)) + 1e-6 * (double)m * (double)N;
+                if (best.row_wgs == 0 || t < best.time) best = {wgs, whole != 0, t};
+            }
+        }
+    }
+    last = {m, k, nnz, N, best};
+    return best;
+}
+// The tile kernel is taken where it is expected to need 0.85 of the time of the row-by-row kernel from the caches: of the 1336 products that leaves one that loses more than
+// 3 % by it (60 with 1, 10 with 0.9), and they take 9.6 % less on (geometric) average (9.8 with 1).
+bool tile_preferred(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
+{
+    const TilePlan plan = tile_plan(m, k, nnz, N);
+    return plan.row_wgs > 0 && plan.time < 0.85 * few_columns_rows_time(m, k, nnz, N, lines);
+}
+// The faster of the two without a schedule, on the scale of rows_time() and band_time(), which were fitted to products with 2 us more around them.
+double no_schedule_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
+{
+    const double rows = rows_time(m, k, nnz, N, lines);
+    return tile_preferred(m, k, nnz, N, lines) ? std::min(rows, tile_plan(m, k, nnz, N).time + 2.0) : rows;
+}
 // Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 KB of B, the barrier, the bubble behind it; more where
 // they are fetched in four-byte pieces) and 2.56 ns per entry of the block, 1.77 in the tall cut, whose tiles are half as wide; C and B once, and
 // more for both when they do not fit the memory-side cache.  The tall cut (fitted to 140 measurements like those of the two others, 2000 to 14000 rows
@@ -490,7 +542,7 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
     if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return {0, 0};
     const bool asked = share_kernel_preferred(m, k, nnz, p);
     const bool lines = k % 32 == 0, aligned = k % 4 == 0;
-    if (!asked && rows_time(m, k, nnz, k, lines) < 30.0) return {0, 0};
+    if (!asked && no_schedule_time(m, k, nnz, k, lines) < 30.0) return {0, 0};
     // (a conversion asks for every layout it makes: the last answer of this thread is kept)
     static thread_local struct { int64_t m, k, nnz; bool asked; BandPlan plan; } last = {0, 0, 0, false, {0, 0}};
     if (last.m == m && last.k == k && last.nnz == nnz && last.asked == asked) return last.plan;
@@ -508,7 +560,7 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
             if (best.h == 0 || t < least) { best_time = t; best = plan; }
         }
     }
-    if (best.h && !asked && best_time + 12.0 > rows_time(m, k, nnz, k, lines)) best = {0, 0};
+    if (best.h && !asked && best_time + 12.0 > no_schedule_time(m, k, nnz, k, lines)) best = {0, 0};
     last = {m, k, nnz, asked, best};
     return best;
 }
@@ -1484,7 +1536,7 @@ int kernel_of_product(const gcoo_matrix** M, const Shape& sh, const float* B_dev
     if (automatic && A->has_rows()) {
         const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
         if (A->L.band.h > 0 && band_operands_ok(A, sh, ldb) &&
-            band_time(A->m, A->k, A->nnz, N, A->L.band, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < rows_time(A->m, A->k, A->nnz, N, lines))
+            band_time(A->m, A->k, A->nnz, N, A->L.band, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < no_schedule_time(A->m, A->k, A->nnz, N, lines))
             return GCOO_KERNEL_BAND;
         if (!A->has_sched || rows_preferred(A, N) || sched_width(A->p, sh) == 0) return GCOO_KERNEL_ROWS;     // (0: fewer columns than the register kernel serves)
     }
@@ -1540,7 +1592,9 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
             if (!some) rows.long_row = INT32_MAX;
         }
         if (kernel == GCOO_KERNEL_ROWS) {
-            hipError_t e = gcoo::launch_spdm_rows(rows, s);
+            const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0, reach = (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
+            const TilePlan plan = tile_plan(A->m, A->k, A->nnz, N);
+            hipError_t e = reach && tile_preferred(A->m, A->k, A->nnz, N, lines) ? gcoo::launch_spdm_rows_tile(rows, plan.row_wgs, plan.whole, s) : gcoo::launch_spdm_rows(rows, s);
             return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
         }
         gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band.h), A->L.band.h, A->L.band.v,

@@ -89,6 +89,19 @@ inline int32_t rows_long(int64_t m, int64_t nnz)
 constexpr uint64_t kRowsMaxBytes = 0xffffefffull;
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s);
 
+// The kernel that works row by row on a tile of B in LDS (gcoo_spdm_tile_kernel.hpp), `row_wgs` workgroups per tile of kTileCols columns: N of at least a tile, any alignment of
+// 4 bytes, at most kTileMaxRows rows for a workgroup, tile_lds() at most kTileLdsBytes, k x ldb at most kRowsMaxBytes, at most kTileMaxNnz entries.
+constexpr int kTileCols = 16;
+constexpr int kTileMaxRows = 1023;
+constexpr int64_t kTileLdsBytes = 160 * 1024 - 16;        // the kernel has two words of its own
+constexpr int64_t kTileMaxNnz = 1 << 29;                  // byte offsets of entries
+inline int64_t tile_lds(int64_t k, int64_t rows)
+{
+    const int64_t bytes = (k + 1) * (4 * kTileCols) + 4 * (rows + 1) + 2 * rows;
+    return bytes < 1024 ? 1024 : bytes;                    // (the bins of the row lengths)
+}
+hipError_t launch_spdm_rows_tile(const RowsArgs& a, int64_t row_wgs, bool whole, hipStream_t s);
+
 
 // The sixteen-wave kernel that reads the band schedule (gcoo_band.hpp): N of at least a tile, or N, ldb a multiple of 4 and B 16-byte aligned; a B of at
 // most kRowsMaxBytes (the launch may work row by row).

@@ -335,6 +335,28 @@ def kernel_of_product(host):
     assert host.L.gcoo_spdm_kernel(None, 1 << 20, 4, 4, 1 << 20, 4, 0) == EINVAL
 
 
+# ---- the tile of B in LDS --------------------------------------------------------------------------
+
+# (m, k, N, entries, whether the row-by-row product goes by a tile of B in LDS): what tests/test_gpu_tile.py multiplies, and the shapes beside the lines of the rule
+TILES = [(2047, 63, 500, 90000, True), (1023, 400, 1031, 102300, True), (1024, 400, 1031, 102400, True), (500, 1000, 17, 200000, True), (4000, 1500, 31, 600000, True),
+         (700, 1280, 48, 300000, True), (700, 1279, 1031, 300000, True), (100, 2496, 517, 90000, True), (7, 2558, 4000, 14000, True), (92, 2550, 1024, 90000, True),
+         (93, 2550, 1024, 90000, True), (1777, 2301, 1117, 122666, True), (7, 2559, 4000, 14000, False), (500, 1000, 15, 200000, False), (256, 256, 256, 6553, False), (2500, 2500, 64, 62500, False)]
+
+
+def tiles(host):
+    for m, k, N, nnz, tile in TILES:
+        for variant in (AUTO, REG):
+            for ldb, off in ((N, 0), (N + 3, 4)):
+                host.log()
+                h = host.matrix(m, k, nnz, 32)
+                host.log()
+                assert host.spdm(h, N, ldb, variant, N + 5, (1 << 30) + off, (1 << 40) + off) == OK
+                names = host.launches()
+                assert len(names) == 1 and ("spdm_rows_tile" in names[0]) == tile, (m, k, N, nnz, variant, names)
+        # a B that the buffer descriptor does not reach
+        assert host.spdm(h, N, (1 << 32) // (4 * k) + N, AUTO) == OK and "spdm_rows_tile" not in host.launches()[0], (m, k, N)
+
+
 # ---- the cuts of the band schedule -------------------------------------------------------------------
 
 # (m, k, N, entries, variant): what tests/test_gpu_band.py multiplies by the wide cut and by the tall one, and by which instance
