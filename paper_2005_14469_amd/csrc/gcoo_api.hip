@@ -504,28 +504,25 @@ double no_schedule_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines
     const double rows = rows_time(m, k, nnz, N, lines);
     return tile_preferred(m, k, nnz, N, lines) ? std::min(rows, tile_plan(m, k, nnz, N).time + 2.0) : rows;
 }
-// Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 KB of B, the barrier, the bubble behind it; more where
-// they are fetched in four-byte pieces) and 2.56 ns per entry of the block, 1.77 in the tall cut, whose tiles are half as wide; C and B once, and
+// Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 KB of B, the barrier, the bubble behind it) and 2.56 ns per
+// entry of the block, 1.77 in the tall cut, whose tiles are half as wide; C and B once, and
 // more for both when they do not fit the memory-side cache.  The tall cut (fitted to 140 measurements like those of the two others, 2000 to 14000 rows
 // and columns, 0.05 to 2 % dense, N = 300 to 14000; mean error 4 to 7 %) is bound by what it fetches, which the compute units share, rather than by its last round: that
 // counts in full for one round and less the more there are.  With more than 40 entries per (wave, band) the multiply-adds, which a compute unit has to itself, come
 // near that bound, and the last round counts for half of what was left out (10000 x 10000, 0.75 %, heights of 48, 44 and 40, that is 4.3, 4.6 and 4.9 rounds: 804 750 753 us;
-// 9600 x 9600, 0.9 %, 44 and 48, 4.1 and 3.8 rounds: 798 683).
-double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bool aligned)
+// 9600 x 9600, 0.9 %, 44 and 48, 4.1 and 3.8 rounds: 798 683).  Rows of B that begin inside a 128-byte line cost a line more per stretch of 1 KB or of 512 bytes (91 products in the
+// wide cut and 60 in the tall one, N odd and multiples of 4 beside multiples of 32: 4 and 8 %, less for dense and more for sparse matrices; mean error with that 6 and 9 %).
+double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bool lines)
 {
     const int64_t blocks = gcoo::band_blocks(m, plan.h), tile = 64 * plan.v, tiles = (N + tile - 1) / tile, rounds = (blocks * tiles + 255) / 256;
     const double row = 4.0 * (double)N, big = ((double)k * (double)N - 4e7) / 6e7, outside = big < 0.0 ? 0.0 : (big > 1.0 ? 1.0 : big);
     const double md = (double)m, kd = (double)k, block_rows = (double)(gcoo::kBandWaves * plan.h);
     const double entries = plan.v == 4 || md < block_rows ? (double)nnz / (double)blocks : (double)nnz / md * block_rows;       // of a full block
     const double bands = std::ceil(kd * -std::expm1(-entries / kd) / gcoo::band_rows_of(plan.v));                  // distinct columns of a block
-    if (plan.v == 4) {
-        if (aligned) return 6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6);
-        return 7.4 + (double)rounds * (1.08 * bands + 0.00255 * entries) + row * (md / 3.8e6 + kd / 17.8e6 + outside * (md + kd) / 14.6e6);
-    }
+    if (plan.v == 4) return (lines ? 1.0 : 1.04) * (6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6));
     const double full = md / block_rows * (double)tiles / 256.0, part = rounds > 1 ? 1.2 / (double)rounds : 1.0;
     const double turns = full + ((double)rounds - full) * (gcoo::band_entries(m, k, nnz, plan.h, 2) > 40.0 ? 0.5 + 0.5 * part : part);
-    if (aligned) return 6.2 + turns * (0.722 * bands + 0.00177 * entries) + row * (md / 3.76e6 + outside * (md + kd) / 9.8e6);
-    return 10.2 + turns * (0.771 * bands + 0.00234 * entries) + row * (md / 3.1e6 + outside * (md + kd) / 9.6e6);
+    return (lines ? 1.0 : 1.08) * (6.2 + turns * (0.722 * bands + 0.00177 * entries) + row * (md / 3.76e6 + outside * (md + kd) / 9.8e6));
 }
 
 // The band schedule of a matrix, if it gets one.  The width of B is not known here: the blocks are cut so that a
@@ -541,7 +538,7 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return {0, 0};
     const bool asked = share_kernel_preferred(m, k, nnz, p);
-    const bool lines = k % 32 == 0, aligned = k % 4 == 0;
+    const bool lines = k % 32 == 0;
     if (!asked && no_schedule_time(m, k, nnz, k, lines) < 30.0) return {0, 0};
     // (a conversion asks for every layout it makes: the last answer of this thread is kept)
     static thread_local struct { int64_t m, k, nnz; bool asked; BandPlan plan; } last = {0, 0, 0, false, {0, 0}};
@@ -556,7 +553,7 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
             const BandPlan plan = {h, v};
             const double entries = gcoo::band_entries(m, k, nnz, h, v);
             if (v == 2 && entries > 66.0) continue;
-            const double t = band_time(m, k, nnz, k, plan, aligned), least = best.v == v ? best_time : (entries > 40.0 ? 0.99 : 0.97) * best_time;
+            const double t = band_time(m, k, nnz, k, plan, lines), least = best.v == v ? best_time : (entries > 40.0 ? 0.99 : 0.97) * best_time;
             if (best.h == 0 || t < least) { best_time = t; best = plan; }
         }
     }
@@ -1536,7 +1533,7 @@ int kernel_of_product(const gcoo_matrix** M, const Shape& sh, const float* B_dev
     if (automatic && A->has_rows()) {
         const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0;
         if (A->L.band.h > 0 && band_operands_ok(A, sh, ldb) &&
-            band_time(A->m, A->k, A->nnz, N, A->L.band, sh.N % 4 == 0 && ldb % 4 == 0 && sh.b16) < no_schedule_time(A->m, A->k, A->nnz, N, lines))
+            band_time(A->m, A->k, A->nnz, N, A->L.band, lines) < no_schedule_time(A->m, A->k, A->nnz, N, lines))
             return GCOO_KERNEL_BAND;
         if (!A->has_sched || rows_preferred(A, N) || sched_width(A->p, sh) == 0) return GCOO_KERNEL_ROWS;     // (0: fewer columns than the register kernel serves)
     }

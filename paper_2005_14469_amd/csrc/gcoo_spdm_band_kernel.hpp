@@ -27,7 +27,8 @@
 //
 // B: two bands of 80 rows x 1 KB in LDS.  While band b is multiplied, the rows of band b + 1 are requested, five per wave, straight
 // to LDS; their columns come with the band's head, and the address is formed by the scalar unit.  One barrier per band, nothing in
-// flight across it.  UNALIGNED: rows of B aligned to 4 bytes only are fetched with four 4-byte-per-lane loads instead of one of 16.
+// flight across it.  Rows of B that are aligned to 4 bytes only are fetched by the same requests of 16 bytes per lane, a line more for each: 8000 x 8000, N = 7999 (us, four requests of
+// 4 bytes per lane instead, so, and N = 8000): 0.5 % 358 317 288; 2 % 677 646 630; 10 % 2335 2295 2287.
 //
 // When the rows are requested.  A request holds the one address path of the compute unit for 16 clocks, and a wave that finds it taken
 // stands still: with all five requests of all waves at the band's start nobody multiplied for the first 0.5 us.  Two ways:
@@ -71,7 +72,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 
 // ---- asm text -----------------------------------------------------------------------------------
 // Registers of the main loop:
-//   v0 lane * 16    v1 0x3fc00, the place field of a record    v2 the lane's byte offset in a row of B (lane * 16, or * 4 UNALIGNED)
+//   v0 lane * 16    v1 0x3fc00, the place field of a record    v2 the lane's byte offset in a row of B (lane * 16)
 //   v3        LDS address of the next read    v[4:27] six sets of B values
 //   s[36:67]  bank A: the unit that is multiplied, s[68:99]  bank B: the next one (or the other way round): value, place and row of record i
 //   s12 s13   byte offsets of the head after next and of the next unit    s14  where the wave's rows of the next band go in LDS
@@ -108,12 +109,6 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     "s_add_u32 m0, s14, " #at "\n\ts_and_b32 s23, " #cols ", 0xffff\n\ts_lshr_b32 s100, " #cols ", 16\n\t"            \
     "s_mul_i32 s23, s23, %[ldb4]\n\ts_mul_i32 s100, s100, %[ldb4]\n\t"                                                 \
     "v_and_b32 v126, s100, v127\n\tv_add_u32 v126, v126, v2\n\tbuffer_load_dwordx4 v126, s[32:35], s23 offen lds\n\t"
-#define BD_FILL_TALL_UNALIGNED(cols, at)                                                                                \
-    "s_add_u32 m0, s14, " #at "\n\ts_and_b32 s23, " #cols ", 0xffff\n\ts_lshr_b32 s100, " #cols ", 16\n\t"            \
-    "s_mul_i32 s23, s23, %[ldb4]\n\ts_mul_i32 s100, s100, %[ldb4]\n\t"                                                 \
-    "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"   \
-    "s_add_u32 m0, s14, " #at " + 0x200\n\ts_add_u32 s23, s23, s100\n\t"                                              \
-    "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"
 #define BD_FILL_BAND BD_FILL(s16, 0) BD_FILL(s17, 0x400) BD_FILL(s18, 0x800) BD_FILL(s19, 0xc00) BD_FILL(s20, 0x1000)
 // The places where rows are requested; T = p (pair steps) or s (single steps).  BD_ASK_START behind the first reads of a band, BD_ASK_STEP behind
 // step I of its first unit, BD_ASK_UNIT in front of a further unit, BD_ASK_END at its end; what is done there stands out of line (BD_ASK_REST).
@@ -297,7 +292,7 @@ struct BandRowsGrid { int32_t tiles, row_wgs, rpw, wave_row, items; };
 // A matrix with a list of far more entries than the others (take_rows and band_mark say so on the device, where the
 // row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, as the row-by-row
 // kernel does, by the workgroups of this launch.
-template <int V, bool UNALIGNED, bool SPREAD>            // V = 4: the wide cut, 2: the tall one
+template <int V, bool SPREAD>            // V = 4: the wide cut, 2: the tall one
 __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
@@ -350,11 +345,19 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #define BD_BEGIN "v_mov_b32 v1, 0x3fc00\n\t"
 #define BD_MORE_SCALARS
 #define BD_FILL BD_FILL_WIDE
-            if constexpr (UNALIGNED) {
-                const uint32_t lane_b = lane * 4u;
-#define BD_LOAD_ROW                                                                                          \
-    "buffer_load_dword v2, s[32:35], s23 offen lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:256 lds\n\t"               \
-    "buffer_load_dword v2, s[32:35], s23 offen offset:512 lds\n\tbuffer_load_dword v2, s[32:35], s23 offen offset:768 lds\n\t"
+            const uint32_t lane_b = jb + (int32_t)(lane * 4u) < n ? lane * 16u : 0u;
+#define BD_LOAD_ROW "buffer_load_dwordx4 v2, s[32:35], s23 offen lds\n\t"
+            if constexpr (SPREAD) {
+#define BD_ASK_START BD_SPREAD_START
+#define BD_ASK_STEP BD_SPREAD_STEP
+#define BD_ASK_UNIT BD_SPREAD_UNIT
+#define BD_ASK_REST BD_SPREAD_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else {
 #define BD_ASK_START BD_HALVES_START
 #define BD_ASK_STEP BD_HALVES_STEP
 #define BD_ASK_UNIT BD_HALVES_UNIT
@@ -364,33 +367,8 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #undef BD_ASK_STEP
 #undef BD_ASK_UNIT
 #undef BD_ASK_REST
-#undef BD_LOAD_ROW
-            } else {
-                const uint32_t lane_b = jb + (int32_t)(lane * 4u) < n ? lane * 16u : 0u;
-#define BD_LOAD_ROW "buffer_load_dwordx4 v2, s[32:35], s23 offen lds\n\t"
-                if constexpr (SPREAD) {
-#define BD_ASK_START BD_SPREAD_START
-#define BD_ASK_STEP BD_SPREAD_STEP
-#define BD_ASK_UNIT BD_SPREAD_UNIT
-#define BD_ASK_REST BD_SPREAD_REST
-                    BD_MAIN;
-#undef BD_ASK_START
-#undef BD_ASK_STEP
-#undef BD_ASK_UNIT
-#undef BD_ASK_REST
-                } else {
-#define BD_ASK_START BD_HALVES_START
-#define BD_ASK_STEP BD_HALVES_STEP
-#define BD_ASK_UNIT BD_HALVES_UNIT
-#define BD_ASK_REST BD_HALVES_REST
-                    BD_MAIN;
-#undef BD_ASK_START
-#undef BD_ASK_STEP
-#undef BD_ASK_UNIT
-#undef BD_ASK_REST
-                }
-#undef BD_LOAD_ROW
             }
+#undef BD_LOAD_ROW
 #undef BD_FILL
 #undef BD_MORE_SCALARS
 #undef BD_BEGIN
@@ -421,9 +399,19 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #define BD_READ_T5(meta) BD_READ_TALL(meta, "v[14:15]")
 #define BD_BEGIN "v_mov_b32 v1, 0x3fe00\n\tv_bfe_i32 v127, v0, 8, 1\n\t"
 #define BD_MORE_SCALARS , "s100"
-            if constexpr (UNALIGNED) {
-                const uint32_t lane_b = lane * 4u;
-#define BD_FILL BD_FILL_TALL_UNALIGNED
+            const uint32_t lane_b = jb + (int32_t)((lane & 31u) * 4u) < n ? (lane & 31u) * 16u : 0u;
+#define BD_FILL BD_FILL_TALL
+            if constexpr (SPREAD) {
+#define BD_ASK_START BD_SPREAD_START
+#define BD_ASK_STEP BD_SPREAD_STEP
+#define BD_ASK_UNIT BD_SPREAD_UNIT
+#define BD_ASK_REST BD_SPREAD_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else {
 #define BD_ASK_START BD_HALVES_START
 #define BD_ASK_STEP BD_HALVES_STEP
 #define BD_ASK_UNIT BD_HALVES_UNIT
@@ -433,33 +421,8 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #undef BD_ASK_STEP
 #undef BD_ASK_UNIT
 #undef BD_ASK_REST
-#undef BD_FILL
-            } else {
-                const uint32_t lane_b = jb + (int32_t)((lane & 31u) * 4u) < n ? (lane & 31u) * 16u : 0u;
-#define BD_FILL BD_FILL_TALL
-                if constexpr (SPREAD) {
-#define BD_ASK_START BD_SPREAD_START
-#define BD_ASK_STEP BD_SPREAD_STEP
-#define BD_ASK_UNIT BD_SPREAD_UNIT
-#define BD_ASK_REST BD_SPREAD_REST
-                    BD_MAIN;
-#undef BD_ASK_START
-#undef BD_ASK_STEP
-#undef BD_ASK_UNIT
-#undef BD_ASK_REST
-                } else {
-#define BD_ASK_START BD_HALVES_START
-#define BD_ASK_STEP BD_HALVES_STEP
-#define BD_ASK_UNIT BD_HALVES_UNIT
-#define BD_ASK_REST BD_HALVES_REST
-                    BD_MAIN;
-#undef BD_ASK_START
-#undef BD_ASK_STEP
-#undef BD_ASK_UNIT
-#undef BD_ASK_REST
-                }
-#undef BD_FILL
             }
+#undef BD_FILL
 #undef BD_MORE_SCALARS
 #undef BD_BEGIN
 #undef BD_FMAC_T0

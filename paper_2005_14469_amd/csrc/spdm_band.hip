@@ -5,7 +5,7 @@
 
 namespace gcoo {
 
-template <int V, bool UNALIGNED, bool SPREAD>
+template <int V, bool SPREAD>
 static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const BandRowsGrid& rg, hipStream_t s)
 {
     // more LDS than the default limit of a workgroup: asked for once per device
@@ -15,11 +15,11 @@ static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const Ban
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!done[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<V, UNALIGNED, SPREAD>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<V, SPREAD>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
         if (e != hipSuccess) return e;
         done[dev].store(1u, std::memory_order_release);
     }
-    spdm_band<V, UNALIGNED, SPREAD><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
+    spdm_band<V, SPREAD><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
     return hipGetLastError();
 }
 
@@ -47,15 +47,12 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     if (items > 0x7fffffffLL || rows.N < 4) return hipErrorInvalidConfiguration;
     rg.items = (int32_t)items;
     // How the rows of B are requested goes by the entries of a (wave, band), of which SPREAD serves the few (us, halves and SPREAD:
-    // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; with four loads per row 10: 697 698, 19: 254 279, so never there; tall, 19:
-    // 694 670, 27: 821 854; with four-byte loads 20: 1222 1307).
+    // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; tall, 19: 694 670, 27: 821 854).
     const double entries = band_entries(a.m, a.k, rows.nnz, a.h, a.v);
     if (a.v == 2) {
-        if (!aligned) return launch_band<2, true, false>(b, rows, rg, s);
-        return entries < 22.0 ? launch_band<2, false, true>(b, rows, rg, s) : launch_band<2, false, false>(b, rows, rg, s);
+        return entries < 22.0 ? launch_band<2, true>(b, rows, rg, s) : launch_band<2, false>(b, rows, rg, s);
     }
-    if (!aligned) return launch_band<4, true, false>(b, rows, rg, s);
-    return entries < 28.0 ? launch_band<4, false, true>(b, rows, rg, s) : launch_band<4, false, false>(b, rows, rg, s);
+    return entries < 28.0 ? launch_band<4, true>(b, rows, rg, s) : launch_band<4, false>(b, rows, rg, s);
 }
 
 }  // namespace gcoo

@@ -71,6 +71,14 @@ def test_automatic_choice_of_both_cuts(m, k, N, s, shift, pad):
     _run(workloads.uniform_random(m, k, N, s, seed=m + N), 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
 
 
+@pytest.mark.parametrize("m,k,N,nnz", [(4000, 4000, 2045, 320000), (5600, 5601, 2601, 90000)])
+@pytest.mark.parametrize("shift,pad", [(1, 0), (2, 1), (3, 2)])
+def test_requests_spread_over_a_band_from_rows_aligned_to_4_bytes(m, k, N, nnz, shift, pad):
+    """Sixteen bytes per lane from any multiple of four bytes straight to LDS, in the wide cut and in the tall one with few entries per band."""
+    print(f"band, spread requests: m={m} k={k} N={N} shift={shift} pad={pad}", flush=True)
+    _run(workloads.uniform_random(m, k, N, 1 - nnz / (m * k), seed=m + N), 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
+
+
 def test_tall_cut_with_repeated_coordinates_and_infinities():
     """Lists that are written the slow way, of more than 32 rows; rows of B that no entry touches hold infinities."""
     rng = np.random.default_rng(21)
