@@ -52,6 +52,7 @@ namespace gcoo {
 constexpr int kBandFillBytes = kBandFetches * 1024;                // what a wave fetches of a band
 constexpr int kBandBufferBytes = kBandWaves * kBandFillBytes;
 constexpr int kBandLdsBytes = 2 * kBandBufferBytes;
+static_assert(sizeof(RowsAllLds) <= kBandLdsBytes && kRowsAllLong <= 64 * kBandWaves, "uneven rows");
 static_assert(kBandFetches == 5 && BandCut<4>::kRows * 1024 == kBandBufferBytes && BandCut<2>::kRows * 512 == kBandBufferBytes, "the asm text below uses these numbers");
 
 typedef float band_f32x4 __attribute__((ext_vector_type(4)));
@@ -286,28 +287,25 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
           "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", "s92",  \
           "s93", "s94", "s95", "s96", "s97", "s98", "s99" BD_MORE_SCALARS)
 
-// How the launch works row by row instead: items of kBandWaves x rpw rows x 64 columns, strided over the workgroups.
-struct BandRowsGrid { int32_t tiles, row_wgs, rpw, wave_row, items; };
+// How the launch works row by row instead (rows_all()), by tiles of 64 columns.
+struct BandRowsGrid { int32_t tiles, rpw, wave_row; };
 
 // A matrix with a list of far more entries than the others (take_rows and band_mark say so on the device, where the
-// row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, as the row-by-row
-// kernel does, by the workgroups of this launch.
+// row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, by the
+// workgroups of this launch.
 template <int V, bool SPREAD>            // V = 4: the wide cut, 2: the tall one
 __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
     if (*a.uneven != 0u) {
-        for (uint32_t block = blockIdx.x; block < (uint32_t)rg.items; block += gridDim.x) {
-            rows_item<16, false, kBandWaves, false>(by_rows, block, rg.tiles, rg.row_wgs, rg.rpw, rg.wave_row, reinterpret_cast<float(*)[64]>(band_smem));
-            __syncthreads();
-        }
+        rows_all<16>(by_rows, rg.tiles, rg.rpw, rg.wave_row, *reinterpret_cast<RowsAllLds*>(band_smem));
         return;
     }
     // XCD-aware order: XCD x walks the contiguous slice [x*per, (x+1)*per) of the tile-major list, so the blocks that run on
     // it together read the same column tile of B.
     const int32_t per = (int32_t)(a.grid >> 3);
     const int32_t item = (int32_t)(blockIdx.x & 7u) * per + (int32_t)(blockIdx.x >> 3);
-    if (item >= a.total) return;                                     // the whole workgroup
+    if (item >= a.total || (int32_t)(blockIdx.x >> 3) >= per) return;    // the whole workgroup
     const int32_t tile = item / a.blocks, Q = item - tile * a.blocks;
     // the last tile of a B that is no multiple of a tile wide begins where it can hold a whole one
     constexpr int32_t kTile = BandCut<V>::kTile;

@@ -158,52 +158,50 @@ __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& 
     }
 }
 
-// Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.
-// `part`: WAVES * 64 / LPR stretches of a tile's columns in LDS.  PLACES: the long rows are in places, not counted (RowsArgs); a template, since the
-// places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
-template <int LPR, bool WIDE, int WAVES, bool PLACES>
-__device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
-{
-    constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES, TILE = LPR * 4;
-    // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
-    // eight XCDs work on eight tiles side by side, so that what they read and write of a row at about the same time is one
-    // stretch of 2 KB.  The tiles beyond the last whole eight are cut into eight slices of rows.
-    const int32_t xcd = (int32_t)(block & 7u), at = (int32_t)(block >> 3), eights = tiles / 8;
-    int32_t tile, wg;
-    if (at < eights * row_wgs) {
-        tile = at / row_wgs * 8 + xcd;
-        wg = at - at / row_wgs * row_wgs;
-    } else {
-        const int32_t rest = (tiles - eights * 8) * row_wgs, per = (rest + 7) / 8, i = xcd * per + (at - eights * row_wgs);
-        if (at - eights * row_wgs >= per || i >= rest) return;       // the whole workgroup
-        tile = eights * 8 + i / row_wgs;
-        wg = i - i / row_wgs * row_wgs;
+// What a lane needs of a tile of 4 x LPR columns.
+template <int LPR, bool WIDE>
+struct RowsTile {
+    const RowsArgs& a;
+    int lane, slot, sl;
+    int32_t N, jb, lane_j;
+    uint32_t kmax, ldb4, c_word, ldc_word;
+    RowsB B;
+    __device__ __forceinline__ RowsTile(const RowsArgs& args, int32_t tile) : a(args)
+    {
+        lane = threadIdx.x & 63;
+        slot = lane / LPR;
+        sl = lane % LPR;
+        const int64_t j0 = (int64_t)tile * (LPR * 4);                 // first column of the tile, less up to 31 (place())
+        // The descriptor starts at or before the first column any lane of the tile loads.
+        const int64_t first = j0 - 31 < 0 ? 0 : (j0 - 31 < a.N - 4 ? j0 - 31 : a.N - 4);
+        const char* bbase = reinterpret_cast<const char*>(a.B + first);
+        const uint64_t bytes = ((uint64_t)(a.k - 1) * (uint64_t)a.ldb + (uint64_t)a.N - (uint64_t)first) * 4u;
+        B.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(bbase), 0, (int)(uint32_t)bytes, 0x00027000);
+        B.base = bbase;
+        B.pitch = (uint64_t)a.ldb * 4u;
+        jb = (int32_t)first;
+        N = (int32_t)a.N;
+        lane_j = (int32_t)j0 + sl * 4;
+        ldb4 = (uint32_t)a.ldb * 4u;
+        kmax = (uint32_t)(a.k - 1);
+        c_word = (uint32_t)(reinterpret_cast<uintptr_t>(a.C) >> 2);
+        ldc_word = (uint32_t)a.ldc;
     }
-    const int lane = threadIdx.x & 63, slot = lane / LPR, sl = lane % LPR;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t j0 = (int64_t)tile * TILE;                          // first column of the tile, less up to 31 (place())
-    // The descriptor starts at or before the first column any lane of the tile loads.
-    const int64_t jb = j0 - 31 < 0 ? 0 : (j0 - 31 < a.N - 4 ? j0 - 31 : a.N - 4);
-    const char* bbase = reinterpret_cast<const char*>(a.B + jb);
-    const uint64_t bytes = ((uint64_t)(a.k - 1) * (uint64_t)a.ldb + (uint64_t)a.N - (uint64_t)jb) * 4u;
-    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(bbase), 0, (int)(uint32_t)bytes, 0x00027000);
-    const RowsB B = {rsrc, bbase, (uint64_t)a.ldb * 4u};
-    const uint32_t ldb4 = (uint32_t)a.ldb * 4u, kmax = (uint32_t)(a.k - 1);
     // A lane's columns in row r: the tile is moved down by what the row's start in C lies past a 128-byte line, so that the
     // stores of a slot are whole lines whatever N and ldc are.  A lane that would reach outside [0, N) loads four columns
     // inside instead and stores those that are its own.
     struct Place { int32_t jc, first, last; };              // elements [first, last) of the vector at column jc
-    const int32_t N = (int32_t)a.N, lane_j = (int32_t)j0 + sl * 4;
-    const uint32_t c_word = (uint32_t)(reinterpret_cast<uintptr_t>(a.C) >> 2), ldc_word = (uint32_t)a.ldc;
-    auto place = [&](int32_t r) {
+    __device__ __forceinline__ Place place(int32_t r) const
+    {
         const int32_t want = lane_j - (int32_t)((c_word + (uint32_t)r * ldc_word) & 31u);
         Place pl;
         pl.jc = want < 0 ? 0 : (want > N - 4 ? N - 4 : want);
         pl.first = want - pl.jc < 0 ? 0 : want - pl.jc;
         pl.last = want - pl.jc + 4;
         return pl;
-    };
-    auto store = [&](int32_t r, const Place& pl, const RowsAcc& acc) {
+    }
+    __device__ __forceinline__ void store(int32_t r, const Place& pl, const RowsAcc& acc) const
+    {
         float* dst = a.C + (int64_t)r * a.ldc + pl.jc;
         if (pl.first == 0 && pl.last >= 4) {
             rows_f32x4 o = {acc.x[0], acc.x[1], acc.x[2], acc.x[3]};
@@ -213,46 +211,69 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
             for (int u = 0; u < 4; ++u)
                 if (u >= pl.first && u < pl.last) __builtin_nontemporal_store(acc.x[u], dst + u);
         }
-    };
-
-    const int32_t m = (int32_t)a.m, w0 = (wg * WAVES + wv) * rpw;                    // the wave's first row
-    const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
-    // where the wave's rows begin (lane i: row w0 + i)
-    const int32_t start = lane <= wrows && wrows > 0 ? a.row_ptr[w0 + lane] : 0;
-    const int32_t long_first = PLACES && wg < a.long_room ? a.long_rows[wg] : -1;    // (asked for beside the starts)
-    // the long rows, all slots of the workgroup on each
-    int32_t n_long = PLACES ? a.long_room : (a.long_count ? *a.long_count : 0);
-    n_long = n_long < a.long_room ? n_long : a.long_room;
-    for (int32_t x = wg; x < n_long; x += row_wgs) {
-        const int32_t lr = __builtin_amdgcn_readfirstlane(PLACES && x == wg ? long_first : a.long_rows[x]);
-        if (PLACES && (lr < 0 || lr >= m)) continue;                                 // a place without a row
-        const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
-        if (PLACES && le - lb <= a.long_row) continue;
-        const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + slot) * each, e = b + each < le ? b + each : le;
-        const Place lpl = place(lr);
+    }
+    __device__ __forceinline__ void entries(RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end, const Place& pl, RowsAcc& acc) const
+    {
+        rows_entries<LPR, WIDE>(a, next, base, end, more, more_end, kmax, ldb4, (uint32_t)(pl.jc - jb) * 4u, B, lane, acc);
+    }
+    // The entries [b, e) of row r, equal stretches of them for the slots of the wave; the sums of the slots added up in a fixed tree.
+    __device__ __forceinline__ RowsAcc shared_row(const Place& pl, int32_t b, int32_t e) const
+    {
         RowsBatch<LPR> mine;
         mine.request(a, b, e, lane);
         RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
-        rows_entries<LPR, WIDE>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, B, lane, sum);
+        entries(mine, b, e, 0, 0, pl, sum);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) part[wv * SPW + slot][sl * 4 + u] = sum.x[u];
+        for (int d = LPR; d < 64; d <<= 1)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sum.x[u] += __shfl_xor(sum.x[u], d, 64);
+        return sum;
+    }
+};
+
+// The long rows `turn`, `turn` + step, ..., all slots of a workgroup of WAVES waves on each.  `part`: WAVES stretches of a tile's columns in LDS.  PLACES: the long rows are
+// in places, not counted (RowsArgs), and place `turn` holds `at_turn`.
+template <int LPR, bool WIDE, int WAVES, bool PLACES>
+__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE>& T, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
+{
+    constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES;
+    const RowsArgs& a = T.a;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int32_t x = turn; x < n_long; x += step) {
+        const int32_t lr = __builtin_amdgcn_readfirstlane(PLACES && x == turn ? at_turn : a.long_rows[x]);
+        if (PLACES && (lr < 0 || lr >= (int32_t)a.m)) continue;                      // a place without a row
+        const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
+        if (PLACES && le - lb <= a.long_row) continue;
+        const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + T.slot) * each, e = b + each < le ? b + each : le;
+        const typename RowsTile<LPR, WIDE>::Place lpl = T.place(lr);
+        RowsAcc sum = T.shared_row(lpl, b, e);
+        if (T.slot == 0)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) part[wv][T.sl * 4 + u] = sum.x[u];
         __syncthreads();
-        if (wv == 0 && slot == 0) {
-            for (int s = 1; s < SLOTS; ++s)
+        if (wv == 0 && T.slot == 0) {
+            for (int s = 1; s < WAVES; ++s)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) sum.x[u] += part[s][sl * 4 + u];
-            store(lr, lpl, sum);
+                for (int u = 0; u < 4; ++u) sum.x[u] += part[s][T.sl * 4 + u];
+            T.store(lr, lpl, sum);
         }
         __syncthreads();
     }
+}
 
+// The wave's rows [w0, w0 + wrows), a slot on each; lane i holds in `start` where row w0 + i begins, i = 0 .. wrows.  Rows of more than `long_row` entries are left out.
+template <int LPR, bool WIDE>
+__device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE>& T, int32_t w0, int32_t wrows, int32_t start, int32_t wave_row, int32_t long_row)
+{
+    constexpr int SPW = 64 / LPR;
+    const RowsArgs& a = T.a;
     auto bounds = [&](int32_t i, int32_t* beg, int32_t* end) {                      // of the wave's row i (empty past the last)
         const int32_t b = __shfl(start, i, 64), e = __shfl(start, i + 1, 64);
         *beg = b;
         *end = i < wrows ? e : b;
     };
     int32_t beg, end;
-    bounds(slot, &beg, &end);
+    bounds(T.slot, &beg, &end);
     // the row is left to all slots of the wave (or, when it is a long one, to nobody here)
     auto shared = [&](int32_t n) {
         if (!__any(n > 16)) return n > wave_row;
@@ -263,35 +284,27 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     };
     RowsBatch<LPR> next;
     bool whole = shared(end - beg);
-    next.request(a, beg, whole ? beg : end, lane);
+    next.request(a, beg, whole ? beg : end, T.lane);
     for (int32_t i = 0; i < wrows; i += SPW) {
-        const int32_t r = w0 + i + slot;
+        const int32_t r = w0 + i + T.slot;
         int32_t beg2, end2;
-        bounds(i + SPW + slot, &beg2, &end2);
+        bounds(i + SPW + T.slot, &beg2, &end2);
         const bool whole2 = shared(end2 - beg2);
-        const Place pl = place(r);
+        const typename RowsTile<LPR, WIDE>::Place pl = T.place(r);
         RowsAcc acc = {{0.0f, 0.0f, 0.0f, 0.0f}};
-        rows_entries<LPR, WIDE>(a, next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, kmax, ldb4, (uint32_t)(pl.jc - (int32_t)jb) * 4u, B, lane, acc);
-        if (i + slot < wrows && !whole) store(r, pl, acc);
-        uint64_t todo = __ballot(whole && sl == 0);
+        T.entries(next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, pl, acc);
+        if (i + T.slot < wrows && !whole) T.store(r, pl, acc);
+        uint64_t todo = __ballot(whole && T.sl == 0);
         while (todo) {                                                              // wave-uniform
             const int32_t s = (__ffsll((long long)todo) - 1) / LPR;
             todo &= todo - 1;
             const int32_t lb = __builtin_amdgcn_readlane(start, i + s), le = __builtin_amdgcn_readlane(start, i + s + 1);
             const int32_t lr = w0 + i + s, n = le - lb;
-            if (n > a.long_row) continue;
-            // equal stretches for the slots, their sums added up in a fixed tree
-            const int32_t each = (n + SPW - 1) / SPW, b = lb + slot * each, e = b + each < le ? b + each : le;
-            const Place lpl = place(lr);
-            RowsBatch<LPR> mine;
-            mine.request(a, b, e, lane);
-            RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
-            rows_entries<LPR, WIDE>(a, mine, b, e, 0, 0, kmax, ldb4, (uint32_t)(lpl.jc - (int32_t)jb) * 4u, B, lane, sum);
-#pragma unroll
-            for (int d = LPR; d < 64; d <<= 1)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) sum.x[u] += __shfl_xor(sum.x[u], d, 64);
-            if (slot == 0) store(lr, lpl, sum);
+            if (n > long_row) continue;
+            const int32_t each = (n + SPW - 1) / SPW, b = lb + T.slot * each, e = b + each < le ? b + each : le;
+            const typename RowsTile<LPR, WIDE>::Place lpl = T.place(lr);
+            const RowsAcc sum = T.shared_row(lpl, b, e);
+            if (T.slot == 0) T.store(lr, lpl, sum);
         }
         beg = beg2;
         end = end2;
@@ -299,10 +312,154 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     }
 }
 
+// Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
+// places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
+template <int LPR, bool WIDE, int WAVES, bool PLACES>
+__device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
+{
+    // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
+    // eight XCDs work on eight tiles side by side, so that what they read and write of a row at about the same time is one
+    // stretch of 2 KB.  The tiles beyond the last whole eight are cut into eight slices of rows.
+    const int32_t xcd = (int32_t)(block & 7u), at = (int32_t)(block >> 3), eights = tiles / 8;
+    int32_t tile, wg, slice = 0;                                     // slice: workgroups that an XCD has of the cut tiles, 0 where it has the whole tile
+    if (at < eights * row_wgs) {
+        tile = at / row_wgs * 8 + xcd;
+        wg = at - at / row_wgs * row_wgs;
+    } else {
+        const int32_t rest = (tiles - eights * 8) * row_wgs, i = xcd * ((rest + 7) / 8) + (at - eights * row_wgs);
+        slice = (rest + 7) / 8;
+        if (at - eights * row_wgs >= slice || i >= rest) return;     // the whole workgroup
+        tile = eights * 8 + i / row_wgs;
+        wg = i - i / row_wgs * row_wgs;
+    }
+    const RowsTile<LPR, WIDE> T(a, tile);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t m = (int32_t)a.m, w0 = (wg * WAVES + wv) * rpw;                    // the wave's first row
+    const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
+    const int32_t start = T.lane <= wrows && wrows > 0 ? a.row_ptr[w0 + T.lane] : 0;
+    const int32_t long_first = PLACES && wg < a.long_room ? a.long_rows[wg] : -1;    // (asked for beside the starts)
+    int32_t n_long = PLACES ? a.long_room : (a.long_count ? *a.long_count : 0);
+    n_long = n_long < a.long_room ? n_long : a.long_room;
+    int32_t turn = wg;
+    if (!PLACES && slice && n_long > 0) {
+        // The XCDs that share a tile take its long rows in turns: by the place of a workgroup among those of its XCD, then by XCD.  (In the order of `wg` the first XCD of a tile would
+        // have them all; power-law rows, 9958 x 11050, N = 64, 128, 256: 26.5 41.4 48.8 us so, 18.8 24.9 33.3 in turns.)
+        const int32_t t0 = (tile - eights * 8) * row_wgs, t1 = t0 + row_wgs, from = xcd * slice > t0 ? xcd * slice : t0, before = t0 + wg - from;
+        turn = 0;
+        for (int32_t x = 0; x < 8; ++x) {
+            const int32_t lo = x * slice > t0 ? x * slice : t0, hi = (x + 1) * slice < t1 ? (x + 1) * slice : t1, n = before + (x < xcd ? 1 : 0);
+            if (hi > lo) turn += hi - lo < n ? hi - lo : n;
+        }
+    }
+    rows_long_rows<LPR, WIDE, WAVES, PLACES>(T, n_long, turn, row_wgs, long_first, part);
+    rows_of_wave<LPR, WIDE>(T, w0, wrows, start, wave_row, a.long_row);
+}
+
+// The whole product of a matrix with uneven rows by the first kRowsAllWgs workgroups of a launch whose workgroups have a compute unit each (gridDim.x is a multiple of 8).  An XCD walks one
+// tile after the other, the tiles beyond the last whole eight are cut into a share of rows per workgroup.  A share is a stretch of rows with as many entries as the others (kRowsAllRow
+// for a row itself), another one in every tile.  The waves of a workgroup take from one queue: first its long rows in kRowsPieces pieces each, then the other rows, `rpw` at a time.  The wave that
+// ends the last piece of a row adds the sums of its pieces in their order, so that nobody waits for anybody and the bits are the same on every run.
+// Power-law rows, us: 16384 x 16384, N = 1024: 430 as items of 64 rows, the long ones by all sixteen waves between two barriers, which nothing filled; 280 with the queue and equal numbers of rows;
+// 257 with shares of equal entries; 189 with a workgroup on every compute unit whatever the bands ask for.  9958 x 11050, N = 1000: 506 -> 159; 17411 x 20000, N = 704: 415 -> 159.
+constexpr int kRowsAllWgs = 256, kRowsPieces = 8, kRowsAllLong = 64, kRowsAllRow = 8;
+struct RowsAllLds {
+    float sums[kRowsAllLong * kRowsPieces][64];           // of the pieces of the long rows
+    int32_t row[kRowsAllLong], beg[kRowsAllLong], end[kRowsAllLong], ended[kRowsAllLong], next, count;
+};
+// The first row r with row_ptr[r] + kRowsAllRow r of at least the part num / den of it all; by all lanes of a wave.
+__device__ __forceinline__ int32_t rows_all_cut(const RowsArgs& a, int64_t num, int64_t den, int lane)
+{
+    const int64_t target = (a.nnz + kRowsAllRow * a.m) * num / den;
+    int32_t lo = 0, hi = (int32_t)a.m;
+    while (lo < hi) {
+        const int32_t step = (hi - lo + 63) / 64;
+        const int64_t at = (int64_t)lo + (int64_t)(lane + 1) * step - 1;
+        const bool below = at < hi && (int64_t)a.row_ptr[at] + kRowsAllRow * at < target;
+        const int32_t n = (int32_t)__popcll(__ballot(below));
+        const int64_t top = (int64_t)lo + (int64_t)(n + 1) * step - 1;
+        lo += n * step;
+        hi = top < hi ? (int32_t)top : hi;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+template <int LPR>
+__device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32_t rpw, int32_t wave_row, RowsAllLds& lds)
+{
+    static_assert(LPR * 4 <= 64, "the sums of a piece");
+    const int32_t xcd = (int32_t)(blockIdx.x & 7u), place = (int32_t)(blockIdx.x >> 3), most = (int32_t)(gridDim.x >> 3), wgs = most < kRowsAllWgs / 8 ? most : kRowsAllWgs / 8;
+    if (place >= wgs) return;                                          // the whole workgroup
+    const int32_t eights = tiles / 8, rest = tiles - eights * 8, t = (int32_t)threadIdx.x, threads = (int32_t)blockDim.x;
+    // the share [from, to) / parts of a tile
+    auto tile_rows = [&](int32_t tile, int64_t from, int64_t to, int64_t parts) {
+        const RowsTile<LPR, false> T(a, tile);
+        const int32_t r0 = rows_all_cut(a, from, parts, T.lane), r1 = rows_all_cut(a, to, parts, T.lane);
+        // its long rows: those of more entries than `limit`, which has room for all of them
+        int32_t limit = kRowsPieces * 32, cnt;
+        while (true) {
+            __syncthreads();                                           // nobody is at the queue before, or at the count, any more
+            if (t == 0) { lds.count = 0; lds.next = 0; }
+            __syncthreads();
+            for (int32_t r = r0 + t; r < r1; r += threads) {
+                const int32_t lb = a.row_ptr[r], le = a.row_ptr[r + 1];
+                if (le - lb > limit) {
+                    const int32_t i = atomicAdd(&lds.count, 1);
+                    if (i < kRowsAllLong) { lds.row[i] = r; lds.beg[i] = lb; lds.end[i] = le; lds.ended[i] = 0; }
+                }
+            }
+            __syncthreads();
+            cnt = __builtin_amdgcn_readfirstlane(lds.count);
+            if (cnt <= kRowsAllLong) break;
+            limit = limit < INT32_MAX / 2 ? 2 * limit : INT32_MAX;
+        }
+        const int32_t pieces = cnt * kRowsPieces, items = pieces + (r1 > r0 ? (r1 - r0 + rpw - 1) / rpw : 0);
+        while (true) {
+            int32_t q = 0;
+            if (T.lane == 0) q = atomicAdd(&lds.next, 1);
+            q = __builtin_amdgcn_readfirstlane(q);
+            if (q >= items) break;
+            if (q >= pieces) {
+                const int32_t w0 = r0 + (q - pieces) * rpw, wrows = r1 - w0 < rpw ? r1 - w0 : rpw;
+                rows_of_wave<LPR, false>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row, limit);
+                continue;
+            }
+            const int32_t i = q / kRowsPieces, piece = q % kRowsPieces;
+            const int32_t r = __builtin_amdgcn_readfirstlane(lds.row[i]), lb = __builtin_amdgcn_readfirstlane(lds.beg[i]), le = __builtin_amdgcn_readfirstlane(lds.end[i]);
+            constexpr int kSlots = 64 / LPR * kRowsPieces;
+            const int32_t each = (le - lb + kSlots - 1) / kSlots, b = lb + (piece * (64 / LPR) + T.slot) * each, e = b + each < le ? b + each : le;
+            const typename RowsTile<LPR, false>::Place pl = T.place(r);
+            RowsAcc sum = T.shared_row(pl, b, e);
+            if (T.slot == 0)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) lds.sums[q][T.sl * 4 + u] = sum.x[u];
+            int32_t before = 0;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (T.lane == 0) before = atomicAdd(&lds.ended[i], 1);
+            before = __builtin_amdgcn_readfirstlane(before);
+            if (before != kRowsPieces - 1) continue;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            if (T.slot == 0) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sum.x[u] = lds.sums[i * kRowsPieces][T.sl * 4 + u];
+                for (int s = 1; s < kRowsPieces; ++s)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sum.x[u] += lds.sums[i * kRowsPieces + s][T.sl * 4 + u];
+                T.store(r, pl, sum);
+            }
+        }
+    };
+    for (int32_t j = 0; j < eights; ++j) {
+        const int32_t share = (place + j) % wgs;
+        tile_rows(j * 8 + xcd, share, share + 1, wgs);
+    }
+    const int64_t all = 8 * wgs, from = ((int64_t)xcd * wgs + place) * rest, to = from + rest;        // of the other tiles, in parts of 1 / `all` of a tile
+    for (int64_t x = from / all; x * all < to; ++x)
+        tile_rows(eights * 8 + (int32_t)x, from > x * all ? from - x * all : 0, to < (x + 1) * all ? to - x * all : all, all);
+}
+
 template <int LPR, bool WIDE, bool PLACES>
 __global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
 {
-    __shared__ __attribute__((aligned(16))) float part[kRowsThreads / LPR][LPR * 4];
+    __shared__ __attribute__((aligned(16))) float part[kRowsThreads / 64][LPR * 4];
     rows_item<LPR, WIDE, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
 }
 

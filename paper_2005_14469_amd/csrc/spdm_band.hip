@@ -19,7 +19,7 @@ static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const Ban
         if (e != hipSuccess) return e;
         done[dev].store(1u, std::memory_order_release);
     }
-    spdm_band<V, SPREAD><<<dim3((unsigned)a.grid), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
+    spdm_band<V, SPREAD><<<dim3((unsigned)(a.grid > kRowsAllWgs ? a.grid : kRowsAllWgs)), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
     return hipGetLastError();
 }
 
@@ -36,16 +36,13 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     BandArgs b = a;
     b.total = (int32_t)total;
     b.grid = (int32_t)((total + 7) / 8 * 8);                 // whole rounds over the 8 XCDs
-    // as in the launch of the row-by-row kernel: a row per slot, a tile of 64 columns
     BandRowsGrid rg;
     const int64_t mean = rows.nnz / rows.m, wave_row = 2 * mean > 64 ? 2 * mean : 64;
-    rg.tiles = (int32_t)((rows.N + 31 + 63) / 64);
-    rg.rpw = 4;
-    rg.row_wgs = (int32_t)((rows.m + kBandWaves * rg.rpw - 1) / (kBandWaves * rg.rpw));
+    if (rows.N < 4) return hipErrorInvalidConfiguration;
+    const bool c_lines = a.ldc % 32 == 0 && reinterpret_cast<uintptr_t>(a.C) % 128 == 0;
+    rg.tiles = (int32_t)((rows.N + (c_lines ? 0 : 31) + 63) / 64);
+    rg.rpw = 4;                                              // (8: as fast)
     rg.wave_row = (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row);
-    const int64_t rest = (int64_t)(rg.tiles % 8) * rg.row_wgs, items = (int64_t)(rg.tiles / 8 * 8) * rg.row_wgs + (rest + 7) / 8 * 8;
-    if (items > 0x7fffffffLL || rows.N < 4) return hipErrorInvalidConfiguration;
-    rg.items = (int32_t)items;
     // How the rows of B are requested goes by the entries of a (wave, band), of which SPREAD serves the few (us, halves and SPREAD:
     // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; tall, 19: 694 670, 27: 821 854).
     const double entries = band_entries(a.m, a.k, rows.nnz, a.h, a.v);

@@ -252,6 +252,21 @@ def test_automatic_choice_of_this_kernel_for_uneven_rows(p, N, shift):
     _run(w, p, binding.VARIANT_AUTO, shift, 3, kernel=binding.KERNEL_BAND)
 
 
+@pytest.mark.parametrize("m,N,heavy,long,short,shift", [(9000, 576, 2000, 500, 10, 0), (9000, 64, 2000, 500, 10, 4), (40, 64, 2, 3000, 30, 0), (300, 1100, 3, 3400, 60, 0),
+                                                        (5000, 516, 12, 3400, 70, 0), (5000, 96, 12, 3400, 70, 4), (2000, 2052, 40, 2000, 55, 4)])
+def test_uneven_rows_in_shares_of_equal_entries(m, N, heavy, long, short, shift):
+    """More long rows in a share than there are places for their pieces; fewer rows than shares; one tile, whole eights of tiles and tiles cut into shares; empty rows."""
+    print(f"band: uneven rows m={m} N={N} heavy={heavy} shift={shift}", flush=True)
+    rng = np.random.default_rng(m + N)
+    k = 3500
+    lens = np.where(np.arange(m) < heavy, long, short)
+    lens[heavy + 3::7] = 0
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(k, n, replace=False)) for n in lens]).astype(np.int32)
+    w = workloads.Workload("uneven", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, N)).astype(np.float32))
+    _run(w, 32, binding.VARIANT_SHARE, shift, shift, kernel=binding.KERNEL_BAND)
+
+
 def test_export_share_of_a_matrix_with_a_band_schedule():
     """There is no share schedule to copy: nothing but empty arrays, no uninitialised ones."""
     print("band: export_share", flush=True)
