@@ -441,16 +441,22 @@ int32_t share_best_p(int64_t m, int64_t N)
     return best;
 }
 
-// Times of the two kernels that the automatic choice is between, in microseconds: fitted to 219 measurements on uniform random
-// matrices (1500 to 14000 rows and columns, 0.05 to 20 % dense, N = 512 to 14000, B and C not in a cache), mean error 3 to 8 %; by them the
-// choice costs 0.5 % against always taking the faster kernel.
+// Times of the two kernels that the automatic choice is between, in microseconds: fitted to 492 products by the row-by-row kernel and 906 by the two cuts of the bands, on uniform random
+// matrices (1200 to 15000 rows and columns, 4 to 250 entries per row and up to 20 % dense, N = 300 to 15000, B not in a cache), half of them with rows of B on 128-byte lines (`lines`) and half
+// inside; mean error 5 to 8 %.  Over 360 pairs of matrix and width (N near k), choosing by them costs 0.6 % against always taking the fastest.
+// `outside`: how much of B is beyond what the memory-side cache holds of it beside C.
+double outside_cache(int64_t k, int64_t N)
+{
+    const double big = ((double)k * (double)N - 4e7) / 6e7;
+    return big < 0.0 ? 0.0 : (big > 1.0 ? 1.0 : big);
+}
 // Row by row: the bytes of B that the entries take through the vector caches, slower the less of a tile of B stays in an XCD's L2 and
 // where rows of B begin inside a 128-byte line; C and B once.
 double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 {
-    const double row = 4.0 * (double)N, kd = (double)k, taken = (double)nnz;
-    if (lines) return 6.2 + row * (taken * (1.0 + std::pow(kd / 22400.0, 1.59)) / 31.7e6 + (double)m / 12.9e6 + kd / 3.4e6);
-    return 7.3 + row * (taken * (1.0 + std::pow(kd / 10700.0, 0.95)) / 32.7e6 + (double)m / 5.2e6 + kd / 6.9e6);
+    const double row = 4.0 * (double)N, md = (double)m, kd = (double)k, taken = (double)nnz;
+    if (lines) return 2.5 + row * (taken * (1.0 + std::pow(kd / 49100.0, 0.974)) / 31.8e6 + md / 6.6e6 + kd / 5.2e6 + outside_cache(k, N) * (md + kd) / 31.8e6);
+    return 2.4 + row * (taken * (1.0 + std::pow(kd / 13200.0, 1.49)) / 29.3e6 + md / 5.9e6 + kd / 4.9e6);
 }
 // The same for matrices of so few columns that the tile kernel is the other choice (k <= 2500 or so, cache-resident, 1336 products of 100 to 20000 rows, N = 16 to 8000, mean error 8 %):
 // what its slots take of B is whole tiles, and launches of few workgroups leave compute units idle.
@@ -491,58 +497,59 @@ TilePlan tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
     last = {m, k, nnz, N, best};
     return best;
 }
-// The tile kernel is taken where it is expected to need 0.85 of the time of the row-by-row kernel from the caches: of the 1336 products that leaves one that loses more than
-// 3 % by it (60 with 1, 10 with 0.9), and they take 9.6 % less on (geometric) average (9.8 with 1).
+// The tile kernel is taken where it is expected to need 0.85 of the time of the row-by-row kernel from the caches: of 900 products that leaves 6 that lose more than
+// 3 % by it (48 with 1, 15 with 0.9), and they take 17.6 % less on (geometric) average (17.8 with 0.9).
 bool tile_preferred(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 {
     const TilePlan plan = tile_plan(m, k, nnz, N);
     return plan.row_wgs > 0 && plan.time < 0.85 * few_columns_rows_time(m, k, nnz, N, lines);
 }
-// The faster of the two without a schedule, on the scale of rows_time() and band_time(), which were fitted to products with 2 us more around them.
+// The faster of the two without a schedule.
 double no_schedule_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 {
     const double rows = rows_time(m, k, nnz, N, lines);
-    return tile_preferred(m, k, nnz, N, lines) ? std::min(rows, tile_plan(m, k, nnz, N).time + 2.0) : rows;
+    return tile_preferred(m, k, nnz, N, lines) ? std::min(rows, tile_plan(m, k, nnz, N).time + 1.0) : rows;
 }
-// Bands: a workgroup per compute unit and round; 0.7 us for a band by itself (80 KB of B, the barrier, the bubble behind it) and 2.56 ns per
-// entry of the block, 1.77 in the tall cut, whose tiles are half as wide; C and B once, and
-// more for both when they do not fit the memory-side cache.  The tall cut (fitted to 140 measurements like those of the two others, 2000 to 14000 rows
-// and columns, 0.05 to 2 % dense, N = 300 to 14000; mean error 4 to 7 %) is bound by what it fetches, which the compute units share, rather than by its last round: that
+// Bands: a workgroup per compute unit and round; 0.63 us for a band by itself (80 KB of B, the barrier, the bubble behind it) and 2.46 ns per
+// entry of the block, 0.67 and 1.64 in the tall cut, whose bands have twice the rows and whose tiles are half as wide; C and B once, and
+// more for both when they do not fit the memory-side cache.  The tall cut is bound by what it fetches, which the compute units share, rather than by its last round: that
 // counts in full for one round and less the more there are.  With more than 40 entries per (wave, band) the multiply-adds, which a compute unit has to itself, come
 // near that bound, and the last round counts for half of what was left out (10000 x 10000, 0.75 %, heights of 48, 44 and 40, that is 4.3, 4.6 and 4.9 rounds: 804 750 753 us;
-// 9600 x 9600, 0.9 %, 44 and 48, 4.1 and 3.8 rounds: 798 683).  Rows of B that begin inside a 128-byte line cost a line more per stretch of 1 KB or of 512 bytes (91 products in the
-// wide cut and 60 in the tall one, N odd and multiples of 4 beside multiples of 32: 4 and 8 %, less for dense and more for sparse matrices; mean error with that 6 and 9 %).
+// 9600 x 9600, 0.9 %, 44 and 48, 4.1 and 3.8 rounds: 798 683).
 double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bool lines)
 {
     const int64_t blocks = gcoo::band_blocks(m, plan.h), tile = 64 * plan.v, tiles = (N + tile - 1) / tile, rounds = (blocks * tiles + 255) / 256;
-    const double row = 4.0 * (double)N, big = ((double)k * (double)N - 4e7) / 6e7, outside = big < 0.0 ? 0.0 : (big > 1.0 ? 1.0 : big);
-    const double md = (double)m, kd = (double)k, block_rows = (double)(gcoo::kBandWaves * plan.h);
+    const double row = 4.0 * (double)N, md = (double)m, kd = (double)k, block_rows = (double)(gcoo::kBandWaves * plan.h), outside = outside_cache(k, N) * (md + kd);
     const double entries = plan.v == 4 || md < block_rows ? (double)nnz / (double)blocks : (double)nnz / md * block_rows;       // of a full block
     const double bands = std::ceil(kd * -std::expm1(-entries / kd) / gcoo::band_rows_of(plan.v));                  // distinct columns of a block
-    if (plan.v == 4) return (lines ? 1.0 : 1.04) * (6.6 + (double)rounds * (0.71 * bands + 0.00256 * entries) + row * (md / 5.3e6 + kd / 11.5e6 + outside * (md + kd) / 9.8e6));
+    if (plan.v == 4) {
+        if (lines) return 3.6 + (double)rounds * (0.628 * bands + 0.00246 * entries) + row * (md / 8.8e6 + kd / 5.3e6 + outside / 9.7e6);
+        return 2.9 + (double)rounds * (0.637 * bands + 0.00246 * entries) + row * (md / 3.7e6 + kd / 6.7e6 + outside / 12.8e6);
+    }
     const double full = md / block_rows * (double)tiles / 256.0, part = rounds > 1 ? 1.2 / (double)rounds : 1.0;
     const double turns = full + ((double)rounds - full) * (gcoo::band_entries(m, k, nnz, plan.h, 2) > 40.0 ? 0.5 + 0.5 * part : part);
-    return (lines ? 1.0 : 1.08) * (6.2 + turns * (0.722 * bands + 0.00177 * entries) + row * (md / 3.76e6 + outside * (md + kd) / 9.8e6));
+    if (lines) return 1.1 + turns * (0.676 * bands + 0.00166 * entries) + row * (md / 6.0e6 + kd / 6.7e6 + outside / 18.1e6);
+    return 0.3 + turns * (0.657 * bands + 0.00161 * entries) + row * (md / 2.8e6 + kd / 8.1e6 + outside / 18.6e6);
 }
 
 // The band schedule of a matrix, if it gets one.  The width of B is not known here: the blocks are cut so that a
 // product with N = k is fastest, and the schedule is built where that product gains more by it than a conversion
 // pays for it (12 us), or where GCOO_VARIANT_SHARE has to be served.
 // The tall cut fetches half as much and has half as many barriers, but reads LDS eight bytes at a time, which takes as long as sixteen.  It is
-// taken where its expected time is clearly the shorter one, by 3 %, by 1 % above 40 entries per (wave, band), where band_time() is the closer, and never above
-// 66 (product alone, us, wide and tall; 8000 x 8000, 0.35 %: 295 275, 0.5 %: 333 294, 0.9 %: 420 405, 1.2 %: 480 487; 12000 x 12000, 0.2 %: 809 669, 0.5 %: 1153 874, 0.9 %:
-// 1417 1309; 4000 x 4000, 0.5 %: 59 51, 2 %: 103 109; 14000 x 14000, 0.75 %: 2088 1845; 0.3 %, N = 500: 92 64).  Over 103 square matrices of 5000 to 14000 rows, 0.2 to
-// 1.2 % dense, that is 8 % less than with the wide cut alone.  Three of them lose by it, all of 10000 rows, whose wide launch is five rounds without a remainder:
-// 0.2 % 434 450, 0.9 % 829 838, 1 % 874 898.
+// taken where its expected time is not the longer one (by more than 2 %), and never above
+// 66 entries per (wave, band) (product alone, us, wide and tall; 8000 x 8000, 0.35 %: 295 275, 0.5 %: 333 294, 0.9 %: 420 405, 1.2 %: 480 487; 12000 x 12000, 0.2 %: 809 669, 0.5 %: 1153 874, 0.9 %:
+// 1417 1309; 4000 x 4000, 0.5 %: 59 51, 2 %: 103 109; 14000 x 14000, 0.75 %: 2088 1845; 0.3 %, N = 500: 92 64).  Over 199 matrices with N near k the cut so chosen takes 0 to 0.7 % longer than the
+// faster of the two.
 BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return {0, 0};
     const bool asked = share_kernel_preferred(m, k, nnz, p);
     const bool lines = k % 32 == 0;
-    if (!asked && no_schedule_time(m, k, nnz, k, lines) < 30.0) return {0, 0};
     // (a conversion asks for every layout it makes: the last answer of this thread is kept)
     static thread_local struct { int64_t m, k, nnz; bool asked; BandPlan plan; } last = {0, 0, 0, false, {0, 0}};
     if (last.m == m && last.k == k && last.nnz == nnz && last.asked == asked) return last.plan;
+    last = {m, k, nnz, asked, {0, 0}};
+    if (!asked && (rows_time(m, k, nnz, k, lines) < 30.0 || no_schedule_time(m, k, nnz, k, lines) < 30.0)) return last.plan;
     BandPlan best = {0, 0};
     double best_time = 0.0;
     for (int v : {4, 2}) {
@@ -553,7 +560,7 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
             const BandPlan plan = {h, v};
             const double entries = gcoo::band_entries(m, k, nnz, h, v);
             if (v == 2 && entries > 66.0) continue;
-            const double t = band_time(m, k, nnz, k, plan, lines), least = best.v == v ? best_time : (entries > 40.0 ? 0.99 : 0.97) * best_time;
+            const double t = band_time(m, k, nnz, k, plan, lines), least = best.v == v ? best_time : 1.02 * best_time;
             if (best.h == 0 || t < least) { best_time = t; best = plan; }
         }
     }
@@ -1580,7 +1587,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     }
     if (kernel == GCOO_KERNEL_ROWS || kernel == GCOO_KERNEL_BAND) {
         gcoo::RowsArgs rows{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
-                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz)};
+                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz), 0};
         if (A->from_csr && A->L.by_masks && A->L.plan.fused) {
             // no places are looked at where only a row that repeats columns could be long
             const bool some = A->k > rows.long_row;

@@ -78,12 +78,21 @@ struct RowsArgs {
     const int32_t* long_rows;  // the rows of more than `long_row` entries, in any order
     const int32_t* long_count; // or null: long_room places, -1 in those without a row
     int32_t long_row, long_room;
+    int32_t moved;             // 31: tiles are moved down to whole lines of C, 0: they are not (set by the launchers)
 };
 // A row of more entries than this is shared by a whole workgroup.
 inline int32_t rows_long(int64_t m, int64_t nnz)
 {
     const int64_t n = m > 0 ? 8 * (nnz / m) : 0;
     return (int32_t)(n < 512 ? 512 : (n > INT32_MAX ? INT32_MAX : n));
+}
+// By how many columns at the most the tiles are moved down, so that the rows of C are stored in whole 128-byte lines.  That costs a tile more and, where B has the pitch of C, takes nothing from
+// the lines of B that a stretch lies in: it pays where C is most of the traffic (us, moved and not: 12471 x 12471, rows of 1.1 entries, N = 5125: 76 81; 10845 columns, rows of 5.3, N = 9494:
+// 343 350; 6298, of 7.2, N = 2285: 42 38; 11050, of 44, N = 237: 45 37).
+inline int32_t rows_moved(int64_t m, int64_t nnz, int64_t N, const float* C, int64_t ldc)
+{
+    if (ldc % 32 == 0 && reinterpret_cast<uintptr_t>(C) % 128 == 0) return 0;
+    return nnz <= 4 * m || (nnz <= 8 * m && m * N >= 25000000) ? 31 : 0;
 }
 // Largest B (k x ldb) whose rows a buffer descriptor reaches with something left above for the entries past the end of a row.
 constexpr uint64_t kRowsMaxBytes = 0xffffefffull;

@@ -171,9 +171,9 @@ struct RowsTile {
         lane = threadIdx.x & 63;
         slot = lane / LPR;
         sl = lane % LPR;
-        const int64_t j0 = (int64_t)tile * (LPR * 4);                 // first column of the tile, less up to 31 (place())
+        const int64_t j0 = (int64_t)tile * (LPR * 4);                 // first column of the tile, less up to `moved` (place())
         // The descriptor starts at or before the first column any lane of the tile loads.
-        const int64_t first = j0 - 31 < 0 ? 0 : (j0 - 31 < a.N - 4 ? j0 - 31 : a.N - 4);
+        const int64_t first = j0 - a.moved < 0 ? 0 : (j0 - a.moved < a.N - 4 ? j0 - a.moved : a.N - 4);
         const char* bbase = reinterpret_cast<const char*>(a.B + first);
         const uint64_t bytes = ((uint64_t)(a.k - 1) * (uint64_t)a.ldb + (uint64_t)a.N - (uint64_t)first) * 4u;
         B.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(bbase), 0, (int)(uint32_t)bytes, 0x00027000);
@@ -187,13 +187,13 @@ struct RowsTile {
         c_word = (uint32_t)(reinterpret_cast<uintptr_t>(a.C) >> 2);
         ldc_word = (uint32_t)a.ldc;
     }
-    // A lane's columns in row r: the tile is moved down by what the row's start in C lies past a 128-byte line, so that the
+    // A lane's columns in row r: where `moved` is 31 the tile is moved down by what the row's start in C lies past a 128-byte line, so that the
     // stores of a slot are whole lines whatever N and ldc are.  A lane that would reach outside [0, N) loads four columns
     // inside instead and stores those that are its own.
     struct Place { int32_t jc, first, last; };              // elements [first, last) of the vector at column jc
     __device__ __forceinline__ Place place(int32_t r) const
     {
-        const int32_t want = lane_j - (int32_t)((c_word + (uint32_t)r * ldc_word) & 31u);
+        const int32_t want = lane_j - (int32_t)((c_word + (uint32_t)r * ldc_word) & (uint32_t)a.moved);
         Place pl;
         pl.jc = want < 0 ? 0 : (want > N - 4 ? N - 4 : want);
         pl.first = want - pl.jc < 0 ? 0 : want - pl.jc;

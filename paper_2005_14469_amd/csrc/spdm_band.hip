@@ -39,17 +39,18 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     BandRowsGrid rg;
     const int64_t mean = rows.nnz / rows.m, wave_row = 2 * mean > 64 ? 2 * mean : 64;
     if (rows.N < 4) return hipErrorInvalidConfiguration;
-    const bool c_lines = a.ldc % 32 == 0 && reinterpret_cast<uintptr_t>(a.C) % 128 == 0;
-    rg.tiles = (int32_t)((rows.N + (c_lines ? 0 : 31) + 63) / 64);
+    RowsArgs by_rows = rows;
+    by_rows.moved = rows_moved(rows.m, rows.nnz, rows.N, rows.C, rows.ldc);
+    rg.tiles = (int32_t)((rows.N + by_rows.moved + 63) / 64);
     rg.rpw = 4;                                              // (8: as fast)
     rg.wave_row = (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row);
     // How the rows of B are requested goes by the entries of a (wave, band), of which SPREAD serves the few (us, halves and SPREAD:
     // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; tall, 19: 694 670, 27: 821 854).
     const double entries = band_entries(a.m, a.k, rows.nnz, a.h, a.v);
     if (a.v == 2) {
-        return entries < 22.0 ? launch_band<2, true>(b, rows, rg, s) : launch_band<2, false>(b, rows, rg, s);
+        return entries < 22.0 ? launch_band<2, true>(b, by_rows, rg, s) : launch_band<2, false>(b, by_rows, rg, s);
     }
-    return entries < 28.0 ? launch_band<4, true>(b, rows, rg, s) : launch_band<4, false>(b, rows, rg, s);
+    return entries < 28.0 ? launch_band<4, true>(b, by_rows, rg, s) : launch_band<4, false>(b, by_rows, rg, s);
 }
 
 }  // namespace gcoo

@@ -4,12 +4,12 @@
 namespace gcoo {
 
 template <int LPR, bool WIDE = false>
-static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
+static hipError_t launch_rows(const RowsArgs& args, hipStream_t s)
 {
     constexpr int64_t waves = kRowsThreads / 64, tile = 4 * LPR, spw = 64 / LPR;
-    // rows of C that do not start at a 128-byte line: the tiles are moved down by up to 31 columns
-    const bool aligned = a.ldc % 32 == 0 && reinterpret_cast<uintptr_t>(a.C) % 128 == 0;
-    const int64_t tiles = (a.N + (aligned ? 0 : 31) + tile - 1) / tile, mean = a.nnz / a.m;
+    RowsArgs a = args;
+    a.moved = rows_moved(a.m, a.nnz, a.N, a.C, a.ldc);
+    const int64_t tiles = (a.N + a.moved + tile - 1) / tile, mean = a.nnz / a.m;
     auto groups = [&](int64_t r) { return (a.m + waves * r - 1) / (waves * r); };
     // Rows per wave: one per slot, so that a launch has many short workgroups.  Short rows (one batch each) go several to a
     // slot, the loads of one behind those of the one before, while enough workgroups are left (64 columns per tile, rows of 6 entries,
@@ -49,16 +49,21 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // 64, 32 or 16 columns per tile: the fewest lanes without a column of their own
     if (a.N <= 16) return launch_rows<4>(a, s);
     if (a.N <= 32) return launch_rows<8>(a, s);
-    // 128 columns per tile while the tile stays in an XCD's L2 (4 MB): rows of B that do not start at 128-byte lines cost a line
-    // more per segment (3000 x 3000, 1 %: N = 2999 59.9 us with 64 columns, 50.9 with 128; 9001 columns: 452 and 460).
-    // Rows of a few entries take theirs from a tile of B hardly more than once before it has to be read anyway, so that the wider
-    // stretches of B and C count for more than the L2 while C is wide (us with 16, 32, 64 lanes; 12000 x 12000, rows of 1, 3, 5, 9 entries:
-    // 339 277 249, 373 328 311, 398 364 374, 446 440 568; 14000 rows, N = 2000, of 3, 5, 7: 80 71 69, 86 79 85, 93 94 108; N = 501, of 3: 22 28 30;
-    // 3000 x 3000, of 3: 22 21 25).
-    // Where between two points of these sweeps a line lies is a choice, not derived from anything.
+    // 64, 128 or 256 columns per tile.  Wider tiles are fewer requests for the same bytes and, where rows of B begin inside a 128-byte line, fewer lines per byte (3 for
+    // 256 bytes, 5 for 512, 9 for 1024); narrower ones stay in an XCD's L2 (4 MB) at more rows of B, and have more slots to a wave for uneven rows, of which the host knows nothing.
+    // From the times of all three in 960 products with rows of B inside a line and 800 with rows on lines, 300 to 20000 rows and columns, rows of 1 to 250 entries and power-law rows (us,
+    // 64, 128, 256 columns): N below 1000: power-law rows, 4281 x 5127, N = 512: 26 35 57; even rows of 25 to 90 entries lose 2 to 9 % by 64 columns; 11050 x 11050, rows of 44, N = 86: 20 14.  Rows of a few entries
+    // hardly take a row of B more than once before it has to be read anyway: 10643 x 10643, of 1.2, N = 8867: 201 170 157; 18739 rows of 5.6, N = 5569: 355 340 354; 12862 of 9.3, N = 2461: 133 144
+    // 160.  Few columns: 3494 x 3494, rows of 12.6, N = 5853: 91 81 75; 4366 columns, N = 10409: 237 211 220.  Where between two points of these sweeps a line lies is a choice.
     const bool lines = a.ldb % 32 == 0 && reinterpret_cast<uintptr_t>(a.B) % 128 == 0;
-    if (a.N >= 1500 && a.nnz <= 4 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
-    if (a.N > 64 && (a.k <= (lines ? 4096 : 6500) || (a.N >= 1500 && a.nnz <= (a.N >= 6000 ? 9 : 6) * a.m))) return launch_rows<32>(a, s);
+    if (a.N >= 1500 && a.nnz <= (lines ? 4 : 3) * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
+    if (a.N < 1000) {
+        // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 90)
+        const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
+        return one || eight ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
+    }
+    if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, s);
+    if (a.k <= 9000 || a.nnz <= 8 * a.m) return launch_rows<32>(a, s);
     return launch_rows<16>(a, s);
 }
 

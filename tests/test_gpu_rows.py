@@ -156,3 +156,21 @@ def test_no_columns(p, policy):
             C = torch.full((70, N + 5), 7.0, device=DEV)
             binding.gcoo_spdm(A, torch.empty((0, N), device=DEV), C[:, :N], variant=variant)
             assert not C[:, :N].any() and torch.all(C[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("m,k,N,lens,shift,pad", [(300, 211, 203, [0, 1, 2, 3, 9], 1, 0), (300, 211, 995, [0, 1, 2, 3, 9], 2, 1), (13500, 300, 1501, [0, 1, 2, 3, 5], 3, 0),
+                                                  (90, 200, 1103, [60, 1, 17], 1, 2), (150, 6600, 77, [40, 0, 33], 2, 0), (150, 6600, 129, [40, 0, 33], 0, 0),
+                                                  (130, 9100, 1030, [7, 9, 0], 1, 0), (130, 9100, 1030, [70, 9, 0], 1, 0)])
+def test_widths_of_tiles_and_tiles_moved_to_whole_lines(m, k, N, lens, shift, pad):
+    """64, 128 and 256 columns per tile, moved down to whole lines of C (rows of a few entries) and not."""
+    print(f"rows: tiles m={m} k={k} N={N} lens={lens} shift={shift}", flush=True)
+    _check(_rows_of_lengths(np.resize(lens, m), k, N, seed=m + N), 32, shift, pad)
+
+
+@pytest.mark.parametrize("N", [64, 131, 323, 452, 515, 580])
+def test_long_rows_in_turns_over_the_xcds_of_a_tile(N):
+    """1 to 10 tiles of 64 columns, those beyond the last eight cut into slices that begin and end inside a tile; long rows at both ends of the matrix and between."""
+    print(f"rows: long rows in turns N={N}", flush=True)
+    lens = np.full(3001, 150)
+    lens[:90] = lens[2950:] = lens[500:2500:9] = 1300
+    _check(_rows_of_lengths(lens, 12000, N, seed=N), 32, 1 if N % 2 else 0)
