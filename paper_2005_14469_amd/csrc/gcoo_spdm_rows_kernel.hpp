@@ -35,7 +35,6 @@
 namespace gcoo {
 
 constexpr int kRowsThreads = 256;
-constexpr int kShortRowsPerWave = 8;     // rows per wave where they are short, at most
 typedef float rows_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t rows_u32x4 __attribute__((ext_vector_type(4)));
 
@@ -63,36 +62,37 @@ struct RowsB {
     const char* base;          // WIDE: B, at the descriptor's place
     uint64_t pitch;            // WIDE: bytes
 };
-template <int LPR, int CNT, int I, bool WIDE>
+// Pairs FROM .. FROM + CNT - 1 of the batch.
+template <int LPR, int FROM, int CNT, int I, bool WIDE>
 __device__ __forceinline__ void rows_load(const uint32_t (&off)[LPR >= 16 ? 1 : 4], uint32_t lane_off, const RowsB& B, rows_u32x4 (&b)[CNT])
 {
     if constexpr (I < CNT) {
         if constexpr (WIDE) {
-            const uint32_t col = rows_bcast<LPR, I>(off);
+            const uint32_t col = rows_bcast<LPR, FROM + I>(off);
             b[I] = 0u;
             if (col != 0xffffffffu) __builtin_memcpy(&b[I], B.base + (uint64_t)col * B.pitch + lane_off, 16);
         } else
-        b[I] = __builtin_amdgcn_raw_buffer_load_b128(B.rsrc, (int)(rows_bcast<LPR, I>(off) + lane_off), 0, 0);
-        rows_load<LPR, CNT, I + 1, WIDE>(off, lane_off, B, b);
+        b[I] = __builtin_amdgcn_raw_buffer_load_b128(B.rsrc, (int)(rows_bcast<LPR, FROM + I>(off) + lane_off), 0, 0);
+        rows_load<LPR, FROM, CNT, I + 1, WIDE>(off, lane_off, B, b);
     }
 }
-template <int LPR, int CNT, int I>
+template <int LPR, int FROM, int CNT, int I>
 __device__ __forceinline__ void rows_fma(const uint32_t (&val)[LPR >= 16 ? 1 : 4], const rows_u32x4 (&b)[CNT], RowsAcc& acc)
 {
     if constexpr (I < CNT) {
-        const float v = __uint_as_float(rows_bcast<LPR, I>(val));
+        const float v = __uint_as_float(rows_bcast<LPR, FROM + I>(val));
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc.x[u] = __builtin_fmaf(v, __uint_as_float(b[I][u]), acc.x[u]);
-        rows_fma<LPR, CNT, I + 1>(val, b, acc);
+        rows_fma<LPR, FROM, CNT, I + 1>(val, b, acc);
     }
 }
-template <int LPR, int CNT, bool WIDE>
+template <int LPR, int FROM, int CNT, bool WIDE>
 __device__ __forceinline__ void rows_batch(const uint32_t (&off)[LPR >= 16 ? 1 : 4], const uint32_t (&val)[LPR >= 16 ? 1 : 4],
                                            uint32_t lane_off, const RowsB& B, RowsAcc& acc)
 {
     rows_u32x4 b[CNT];
-    rows_load<LPR, CNT, 0, WIDE>(off, lane_off, B, b);
-    rows_fma<LPR, CNT, 0>(val, b, acc);
+    rows_load<LPR, FROM, CNT, 0, WIDE>(off, lane_off, B, b);
+    rows_fma<LPR, FROM, CNT, 0>(val, b, acc);
 }
 
 // One (column, value) pair per lane (and register) of a batch of 16 entries: columns beyond the last row of B are brought inside (a
@@ -127,22 +127,22 @@ struct RowsBatch {
     }
 };
 
-// The batch in steps of two entries: as many as the fullest slot of the wave has (a load past a row's end returns at once but
+// The entries from FROM on of the batch, CNT at the most, in steps of two: as many as the fullest slot of the wave has (a load past a row's end returns at once but
 // holds the address path as long as any other).
-template <int LPR, int CNT, bool WIDE>
+template <int LPR, int FROM, int CNT, bool WIDE>
 __device__ __forceinline__ void rows_pick(int32_t left, const RowsBatch<LPR>& now, uint32_t lane_off, const RowsB& B, RowsAcc& acc)
 {
-    if (__any(left > CNT - 2)) {
-        rows_batch<LPR, CNT, WIDE>(now.c, now.v, lane_off, B, acc);
+    if (__any(left > FROM + CNT - 2)) {
+        rows_batch<LPR, FROM, CNT, WIDE>(now.c, now.v, lane_off, B, acc);
     } else {
-        if constexpr (CNT > 2) rows_pick<LPR, CNT - 2, WIDE>(left, now, lane_off, B, acc);
+        if constexpr (CNT > 2) rows_pick<LPR, FROM, CNT - 2, WIDE>(left, now, lane_off, B, acc);
     }
 }
 
 // Adds the entries [base, end) of the slot's row (every lane of the wave calls it; the slots may have different ranges).
 // `next` holds the first batch already; on return it holds the batch [more, more_end), requested in front of the loads of
 // the last batch.
-template <int LPR, bool WIDE>
+template <int LPR, bool WIDE, int AHEAD>
 __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end,
                                              uint32_t kmax, uint32_t ldb4, uint32_t lane_off, const RowsB& B, int lane, RowsAcc& acc)
 {
@@ -153,13 +153,15 @@ __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& 
         base += 16;
         const bool last = !__any(base < end);
         next.request(a, last ? more : base, last ? more_end : end, lane);
-        rows_pick<LPR, 16, WIDE>(left, now, lane_off, B, acc);
+        rows_pick<LPR, 0, AHEAD, WIDE>(left, now, lane_off, B, acc);
+        if constexpr (AHEAD < 16)
+            if (__any(left > AHEAD)) rows_pick<LPR, AHEAD, 16 - AHEAD, WIDE>(left, now, lane_off, B, acc);
         if (last) return;
     }
 }
 
-// What a lane needs of a tile of 4 x LPR columns.
-template <int LPR, bool WIDE>
+// What a lane needs of a tile of 4 x LPR columns.  AHEAD: loads of rows of B in flight.
+template <int LPR, bool WIDE, int AHEAD>
 struct RowsTile {
     const RowsArgs& a;
     int lane, slot, sl;
@@ -214,7 +216,7 @@ struct RowsTile {
     }
     __device__ __forceinline__ void entries(RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end, const Place& pl, RowsAcc& acc) const
     {
-        rows_entries<LPR, WIDE>(a, next, base, end, more, more_end, kmax, ldb4, (uint32_t)(pl.jc - jb) * 4u, B, lane, acc);
+        rows_entries<LPR, WIDE, AHEAD>(a, next, base, end, more, more_end, kmax, ldb4, (uint32_t)(pl.jc - jb) * 4u, B, lane, acc);
     }
     // The entries [b, e) of row r, equal stretches of them for the slots of the wave; the sums of the slots added up in a fixed tree.
     __device__ __forceinline__ RowsAcc shared_row(const Place& pl, int32_t b, int32_t e) const
@@ -233,8 +235,8 @@ struct RowsTile {
 
 // The long rows `turn`, `turn` + step, ..., all slots of a workgroup of WAVES waves on each.  `part`: WAVES stretches of a tile's columns in LDS.  PLACES: the long rows are
 // in places, not counted (RowsArgs), and place `turn` holds `at_turn`.
-template <int LPR, bool WIDE, int WAVES, bool PLACES>
-__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE>& T, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
+template <int LPR, bool WIDE, int AHEAD, int WAVES, bool PLACES>
+__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
 {
     constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES;
     const RowsArgs& a = T.a;
@@ -245,7 +247,7 @@ __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE>& T, int
         const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
         if (PLACES && le - lb <= a.long_row) continue;
         const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + T.slot) * each, e = b + each < le ? b + each : le;
-        const typename RowsTile<LPR, WIDE>::Place lpl = T.place(lr);
+        const typename RowsTile<LPR, WIDE, AHEAD>::Place lpl = T.place(lr);
         RowsAcc sum = T.shared_row(lpl, b, e);
         if (T.slot == 0)
 #pragma unroll
@@ -262,8 +264,8 @@ __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE>& T, int
 }
 
 // The wave's rows [w0, w0 + wrows), a slot on each; lane i holds in `start` where row w0 + i begins, i = 0 .. wrows.  Rows of more than `long_row` entries are left out.
-template <int LPR, bool WIDE>
-__device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE>& T, int32_t w0, int32_t wrows, int32_t start, int32_t wave_row, int32_t long_row)
+template <int LPR, bool WIDE, int AHEAD>
+__device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t w0, int32_t wrows, int32_t start, int32_t wave_row, int32_t long_row)
 {
     constexpr int SPW = 64 / LPR;
     const RowsArgs& a = T.a;
@@ -290,7 +292,7 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE>& T, int32
         int32_t beg2, end2;
         bounds(i + SPW + T.slot, &beg2, &end2);
         const bool whole2 = shared(end2 - beg2);
-        const typename RowsTile<LPR, WIDE>::Place pl = T.place(r);
+        const typename RowsTile<LPR, WIDE, AHEAD>::Place pl = T.place(r);
         RowsAcc acc = {{0.0f, 0.0f, 0.0f, 0.0f}};
         T.entries(next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, pl, acc);
         if (i + T.slot < wrows && !whole) T.store(r, pl, acc);
@@ -302,7 +304,7 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE>& T, int32
             const int32_t lr = w0 + i + s, n = le - lb;
             if (n > long_row) continue;
             const int32_t each = (n + SPW - 1) / SPW, b = lb + T.slot * each, e = b + each < le ? b + each : le;
-            const typename RowsTile<LPR, WIDE>::Place lpl = T.place(lr);
+            const typename RowsTile<LPR, WIDE, AHEAD>::Place lpl = T.place(lr);
             const RowsAcc sum = T.shared_row(lpl, b, e);
             if (T.slot == 0) T.store(lr, lpl, sum);
         }
@@ -314,7 +316,7 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE>& T, int32
 
 // Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
 // places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
-template <int LPR, bool WIDE, int WAVES, bool PLACES>
+template <int LPR, bool WIDE, int AHEAD, int WAVES, bool PLACES>
 __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
 {
     // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
@@ -332,7 +334,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
         tile = eights * 8 + i / row_wgs;
         wg = i - i / row_wgs * row_wgs;
     }
-    const RowsTile<LPR, WIDE> T(a, tile);
+    const RowsTile<LPR, WIDE, AHEAD> T(a, tile);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t m = (int32_t)a.m, w0 = (wg * WAVES + wv) * rpw;                    // the wave's first row
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
@@ -351,8 +353,8 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
             if (hi > lo) turn += hi - lo < n ? hi - lo : n;
         }
     }
-    rows_long_rows<LPR, WIDE, WAVES, PLACES>(T, n_long, turn, row_wgs, long_first, part);
-    rows_of_wave<LPR, WIDE>(T, w0, wrows, start, wave_row, a.long_row);
+    rows_long_rows<LPR, WIDE, AHEAD, WAVES, PLACES>(T, n_long, turn, row_wgs, long_first, part);
+    rows_of_wave<LPR, WIDE, AHEAD>(T, w0, wrows, start, wave_row, a.long_row);
 }
 
 // The whole product of a matrix with uneven rows by the first kRowsAllWgs workgroups of a launch whose workgroups have a compute unit each (gridDim.x is a multiple of 8).  An XCD walks one
@@ -391,7 +393,7 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
     const int32_t eights = tiles / 8, rest = tiles - eights * 8, t = (int32_t)threadIdx.x, threads = (int32_t)blockDim.x;
     // the share [from, to) / parts of a tile
     auto tile_rows = [&](int32_t tile, int64_t from, int64_t to, int64_t parts) {
-        const RowsTile<LPR, false> T(a, tile);
+        const RowsTile<LPR, false, 16> T(a, tile);
         const int32_t r0 = rows_all_cut(a, from, parts, T.lane), r1 = rows_all_cut(a, to, parts, T.lane);
         // its long rows: those of more entries than `limit`, which has room for all of them
         int32_t limit = kRowsPieces * 32, cnt;
@@ -419,14 +421,14 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
             if (q >= items) break;
             if (q >= pieces) {
                 const int32_t w0 = r0 + (q - pieces) * rpw, wrows = r1 - w0 < rpw ? r1 - w0 : rpw;
-                rows_of_wave<LPR, false>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row, limit);
+                rows_of_wave<LPR, false, 16>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row, limit);
                 continue;
             }
             const int32_t i = q / kRowsPieces, piece = q % kRowsPieces;
             const int32_t r = __builtin_amdgcn_readfirstlane(lds.row[i]), lb = __builtin_amdgcn_readfirstlane(lds.beg[i]), le = __builtin_amdgcn_readfirstlane(lds.end[i]);
             constexpr int kSlots = 64 / LPR * kRowsPieces;
             const int32_t each = (le - lb + kSlots - 1) / kSlots, b = lb + (piece * (64 / LPR) + T.slot) * each, e = b + each < le ? b + each : le;
-            const typename RowsTile<LPR, false>::Place pl = T.place(r);
+            const typename RowsTile<LPR, false, 16>::Place pl = T.place(r);
             RowsAcc sum = T.shared_row(pl, b, e);
             if (T.slot == 0)
 #pragma unroll
@@ -456,11 +458,11 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
         tile_rows(eights * 8 + (int32_t)x, from > x * all ? from - x * all : 0, to < (x + 1) * all ? to - x * all : all, all);
 }
 
-template <int LPR, bool WIDE, bool PLACES>
-__global__ __launch_bounds__(kRowsThreads, 4) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
+template <int LPR, bool WIDE, int AHEAD, bool PLACES>
+__global__ __launch_bounds__(kRowsThreads, AHEAD == 16 ? 4 : 8) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
 {
     __shared__ __attribute__((aligned(16))) float part[kRowsThreads / 64][LPR * 4];
-    rows_item<LPR, WIDE, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
+    rows_item<LPR, WIDE, AHEAD, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
 }
 
 // B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a

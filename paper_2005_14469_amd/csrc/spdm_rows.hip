@@ -3,34 +3,42 @@
 
 namespace gcoo {
 
-template <int LPR, bool WIDE = false>
-static hipError_t launch_rows(const RowsArgs& args, hipStream_t s)
+template <int LPR, bool WIDE, int AHEAD>
+static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
 {
     constexpr int64_t waves = kRowsThreads / 64, tile = 4 * LPR, spw = 64 / LPR;
     RowsArgs a = args;
     a.moved = rows_moved(a.m, a.nnz, a.N, a.C, a.ldc);
     const int64_t tiles = (a.N + a.moved + tile - 1) / tile, mean = a.nnz / a.m;
     auto groups = [&](int64_t r) { return (a.m + waves * r - 1) / (waves * r); };
-    // Rows per wave: one per slot, so that a launch has many short workgroups.  Short rows (one batch each) go several to a
-    // slot, the loads of one behind those of the one before, while enough workgroups are left (64 columns per tile, rows of 6 entries,
-    // 12000 x 12000: 445 us with 4 rows per wave, 408 with 8, 399 with 16; rows of 12: 553, 499, 501; 12001 x 12001: 512, 471, 472 and
-    // 683, 653, 708; rows of 25 to 80 entries are fastest with 4).  A launch that cannot
+    // Rows per wave: one per slot, so that a launch has many short workgroups, and two or four per slot where rows are short, the loads of one behind those of the one before
+    // (us, 1, 2, 4, 8 and 16 rows per wave: 7999 x 7999, rows of 8, 64 columns per tile - 231 169 177 229, 128 columns - 164 176 211 261; 12001 x 12001, of 6, 128 columns
+    // - 426 426 448 482; 5000 x 5000, of 2, N = 5001, 256 columns - 42.6 43.2 46.1 46.3).  A launch that cannot
     // fill the chip has fewer rows per wave, each on all slots of it.
     int64_t rpw = spw;
-    if (mean <= 12) {
-        while (2 * rpw <= kShortRowsPerWave && groups(2 * rpw) * tiles >= 4096) rpw *= 2;
-    } else {
-        while (rpw > 1 && groups(rpw) * tiles < 256) rpw /= 2;
-    }
+    if (mean < 6) rpw = LPR == 32 ? 4 : (LPR == 64 ? 2 : spw);
+    else if (mean < 10) rpw = LPR == 64 ? 2 : spw;
+    else if (mean > 12) while (rpw > 1 && groups(rpw) * tiles < 256) rpw /= 2;
     const int64_t row_wgs = groups(rpw);
     const int64_t rest = tiles % 8 * row_wgs, grid = tiles / 8 * 8 * row_wgs + (rest + 7) / 8 * 8;
     if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them.
     const int64_t wave_row = rpw < spw ? 8 : (2 * mean > 64 ? 2 * mean : 64);
     const bool places = !a.long_count && a.long_room > 0;
-    (places ? spdm_rows<LPR, WIDE, true> : spdm_rows<LPR, WIDE, false>)<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(
+    (places ? spdm_rows<LPR, WIDE, AHEAD, true> : spdm_rows<LPR, WIDE, AHEAD, false>)<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(
         a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw, (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row));
     return hipGetLastError();
+}
+
+// A wave with eight rows of B in flight in place of sixteen needs half of the registers, so that twice as many waves are resident: faster where a row has not many more entries
+// than that (us, sixteen and eight: 12001 x 12001, rows of 6: 437 426; 7999 x 7999, of 8: 187 164; 10643 x 10643, of 1.2, N = 8867: 157 125; over 318 products 12 to 20 % less below 6 entries
+// per row, 2 to 9 % from 6 to 16, level from 16 to 30, 2 to 5 % more above, 13 % more for power-law rows of 49).
+template <int LPR>
+static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
+{
+    if constexpr (LPR >= 16)
+        if (a.nnz <= 16 * a.m) return launch_rows_ahead<LPR, false, 8>(a, s);
+    return launch_rows_ahead<LPR, false, 16>(a, s);
 }
 
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
@@ -45,7 +53,7 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         return hipGetLastError();
     }
     // a B of more than 4 GB is beyond the offsets of a buffer descriptor
-    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows<16, true>(a, s);
+    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows_ahead<16, true, 16>(a, s);
     // 64, 32 or 16 columns per tile: the fewest lanes without a column of their own
     if (a.N <= 16) return launch_rows<4>(a, s);
     if (a.N <= 32) return launch_rows<8>(a, s);
@@ -56,14 +64,14 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // hardly take a row of B more than once before it has to be read anyway: 10643 x 10643, of 1.2, N = 8867: 201 170 157; 18739 rows of 5.6, N = 5569: 355 340 354; 12862 of 9.3, N = 2461: 133 144
     // 160.  Few columns: 3494 x 3494, rows of 12.6, N = 5853: 91 81 75; 4366 columns, N = 10409: 237 211 220.  Where between two points of these sweeps a line lies is a choice.
     const bool lines = a.ldb % 32 == 0 && reinterpret_cast<uintptr_t>(a.B) % 128 == 0;
-    if (a.N >= 1500 && a.nnz <= (lines ? 4 : 3) * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
+    if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
     if (a.N < 1000) {
         // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 90)
         const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
-        return one || eight ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
+        return one || eight || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
     }
     if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, s);
-    if (a.k <= 9000 || a.nnz <= 8 * a.m) return launch_rows<32>(a, s);
+    if (a.k <= 9000 || a.nnz <= (lines ? 4 : 7) * a.m) return launch_rows<32>(a, s);
     return launch_rows<16>(a, s);
 }
 
