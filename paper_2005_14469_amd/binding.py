@@ -1,4 +1,5 @@
-"""ctypes binding of include/gcoo.h: argument marshalling only.
+"""Binding of include/gcoo.h: argument marshalling only, by ctypes, and for the calls of every matrix and product by the
+extension module _calls (csrc_python/calls.cpp) where the arguments are as it expects them.
 
 Every step of the path (conversion to GCOO and the product) runs in the HIP kernels of
 libgcoo.so.  torch is used for device memory and for the current stream, nothing else.  If
@@ -16,6 +17,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # GCOO_LIBRARY names another build of the same library (the host-sanitized one of build.py --host-sanitize)
 LIB_PATH = os.environ.get("GCOO_LIBRARY") or os.path.join(_HERE, "libgcoo.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 BASELINE_LIB_PATH = os.path.join(_HERE, "libgcoo_baseline.so")
 
 GCOO_OK, GCOO_EINVAL, GCOO_EBOUNDS, GCOO_ENOMEM, GCOO_EHIP, GCOO_ELIMIT = 0, -1, -2, -3, -4, -5
@@ -35,6 +37,7 @@ SYMBOLS = ["gcoo_default_p", "gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_cs
 BASELINE_SYMBOLS = ["gcoo_csr_spmm_baseline"]
 
 _lib = None
+_calls = None              # the extension module, there as soon as lib() has been called
 _baseline_lib = None
 
 
@@ -50,12 +53,14 @@ class GcooError(RuntimeError):
 
 def lib():
     """Load libgcoo.so (built in-tree by paper_2005_14469_amd/build.py)."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                f"{LIB_PATH} is missing: build it with `python -m paper_2005_14469_amd.build` "
-                "(there is no CPU fallback)")
+        for path in (LIB_PATH, CALLS_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(
+                    f"{path} is missing: build it with `python -m paper_2005_14469_amd.build` "
+                    "(there is no CPU fallback)")
+        from . import _calls as calls
         L = C.CDLL(LIB_PATH)
         i64, i32, vp, sz = C.c_int64, C.c_int32, C.c_void_p, C.c_size_t
         L.gcoo_device_bytes.restype = sz
@@ -102,6 +107,10 @@ def lib():
         L.gcoo_strerror.argtypes = [C.c_int]
         L.gcoo_last_hip_error.restype = C.c_char_p
         L.gcoo_last_hip_error.argtypes = []
+        calls.bind(*(C.cast(getattr(L, name), vp).value for name in
+                      ("gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_csr_device", "gcoo_from_csr_device_static", "gcoo_dense_count_bytes", "gcoo_dense_count",
+                       "gcoo_from_dense_counted", "gcoo_spdm_variant", "gcoo_free")))
+        _calls = calls
         _lib = L
     return _lib
 
@@ -127,7 +136,8 @@ def _check(status: int, where: str):
 
 # A product of a small matrix takes the device less time than Python needs for a torch.cuda.Stream object, a device context and
 # an info() (2.6, 1.2 and 1.2 us; the whole of gcoo_spdm() took 10.2 us for 400 x 400, of which 3.9 in the library): the calls below ask
-# for the raw stream, switch devices only where the tensors are elsewhere, and keep a matrix's shape with its handle.
+# for the raw stream, switch devices only where the tensors are elsewhere, and keep a matrix's shape with its handle.  What they do first is to leave a call of ordinary arguments on the
+# current stream to the extension module, which returns None for any other, a status, or the result.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda d: torch.cuda.current_stream(d).cuda_stream)
 _no_switch = contextlib.nullcontext()
 
@@ -155,7 +165,7 @@ class GcooMatrix:
     """Owner of one handle and of the torch buffer behind it."""
 
     def __init__(self, handle, buf: torch.Tensor):
-        self._h = handle if isinstance(handle, C.c_void_p) else C.c_void_p(handle)
+        self._h = handle.value if isinstance(handle, C.c_void_p) else handle
         self.buf = buf
         self._mk = None
 
@@ -212,7 +222,7 @@ class GcooMatrix:
 
     def free(self):
         if self._h is not None:
-            lib().gcoo_free(self._h)
+            _calls.free(self._h) if _calls else lib().gcoo_free(self._h)
             self._h = None
             self.buf = None
 
@@ -221,6 +231,20 @@ class GcooMatrix:
             self.free()
         except Exception:
             pass
+
+
+def _module():
+    lib()
+    return _calls
+
+
+def _matrix(got, shape, where: str) -> GcooMatrix:
+    """What a conversion of the extension module returned: a handle and its buffer, or a status."""
+    if type(got) is int:
+        raise GcooError(got, where)
+    A = GcooMatrix(*got)
+    A._mk = shape
+    return A
 
 
 def _alloc(nbytes: int, device) -> torch.Tensor:
@@ -236,6 +260,17 @@ def gcoo_from_csr(m: int, k: int, row_ptr, col_idx, vals, p: int, device="cuda:0
     known_nnz (device input only): the caller vouches that row_ptr[m] == len(col_idx); the
     conversion then reads nothing back and never waits for the device (gcoo_from_csr_device)."""
     on_dev = isinstance(row_ptr, torch.Tensor)
+    if stream is None:
+        calls, got = _calls or _module(), None
+        if on_dev:
+            if row_ptr.is_cuda:
+                got = calls.from_csr_device(row_ptr, col_idx, vals, m, k, p, _raw_stream(row_ptr.get_device()), known_nnz)
+        else:
+            index, current = torch.device(device).index, torch.cuda.current_device()
+            if index is None or index == current:
+                got = calls.from_csr_host(row_ptr, col_idx, vals, m, k, p, _raw_stream(current))
+        if got is not None:
+            return _matrix(got, (m, k), "gcoo_from_csr_device" if on_dev and known_nnz else "gcoo_from_csr")
     if on_dev:
         assert row_ptr.is_cuda and row_ptr.dtype == torch.int32 and row_ptr.is_contiguous()
         assert col_idx.dtype == torch.int32 and vals.dtype == torch.float32
@@ -276,6 +311,10 @@ def gcoo_from_csr_device_static(m: int, k: int, row_ptr: torch.Tensor, col_idx: 
     """gcoo_from_csr_device_static: the conversion that allocates no device memory.  out_buf (a uint8 device
     tensor the caller already owns) receives what the handle keeps; without one, a tensor of
     gcoo_static_handle_bytes is made here first (the C call itself allocates nothing either way)."""
+    if stream is None and out_buf is not None and row_ptr.is_cuda:
+        got = (_calls or _module()).from_csr_device_static(row_ptr, col_idx, vals, m, k, p, out_buf, _raw_stream(row_ptr.get_device()))
+        if got is not None:
+            return _matrix((got, out_buf) if type(got) is int else got[0], (m, k), "gcoo_from_csr_device_static")
     assert row_ptr.is_cuda and row_ptr.dtype == torch.int32 and col_idx.dtype == torch.int32 and vals.dtype == torch.float32
     nnz = int(col_idx.numel())
     need = int(lib().gcoo_static_handle_bytes(m, k, nnz, p))
@@ -306,6 +345,10 @@ def gcoo_dense_nnz(A: torch.Tensor, stream=None) -> int:
 
 def gcoo_from_dense(A: torch.Tensor, p: int, stream=None) -> GcooMatrix:
     """Algorithm 1 as the paper runs it: count, allocate by the count, fill."""
+    if stream is None and A.is_cuda:
+        got = (_calls or _module()).from_dense(A, p, _raw_stream(A.get_device()))
+        if got is not None:
+            return _matrix(got, tuple(A.shape), "gcoo_from_dense")
     assert A.is_cuda and A.dtype == torch.float32 and A.dim() == 2 and A.stride(1) == 1
     m, k = A.shape
     L, lda = lib(), A.stride(0)
@@ -330,6 +373,13 @@ def gcoo_from_dense(A: torch.Tensor, p: int, stream=None) -> GcooMatrix:
 def gcoo_spdm(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor | None = None, variant: int = VARIANT_AUTO,
               stream=None) -> torch.Tensor:
     """C = A x B on the current stream.  B: [k, N] fp32 device tensor with unit column stride."""
+    if stream is None and B.is_cuda:
+        m, k = A._mk or A.shape
+        got = (_calls or _module()).spdm(A._h or A.handle, m, k, B, C_out, _raw_stream(B.get_device()), variant)
+        if got is not None:
+            if type(got) is int:
+                raise GcooError(got, "gcoo_spdm")
+            return got
     assert B.is_cuda and B.dtype is torch.float32 and B.dim() == 2
     m, k = A._mk or A.shape
     kb, N = B.shape

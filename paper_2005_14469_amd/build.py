@@ -1,7 +1,7 @@
 """Compile the HIP library (csrc/*.hip -> libgcoo.so) for gfx950 with hipcc.  No GPU is needed.
 
 Every .hip file is one translation unit; they are compiled in parallel and linked into one
-shared library.
+shared library.  The binding's extension module is built beside it, with g++.
 """
 from __future__ import annotations
 
@@ -19,6 +19,9 @@ LIB = os.path.join(HERE, "libgcoo.so")
 # the CSR row-split routine the benchmark compares against: a library of its own, not part of the GCOO path
 BASELINE_SRC = os.path.join(HERE, "csrc_baseline", "csr_baseline.hip")
 BASELINE_LIB = os.path.join(HERE, "libgcoo_baseline.so")
+# the binding's calls as an extension module of the interpreter (host code only)
+CALLS_SRC = os.path.join(HERE, "csrc_python", "calls.cpp")
+CALLS_LIB = os.path.join(HERE, "_calls.so")
 
 # Packed fp32 VALU instructions are switched off for every kernel of this library.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -32,14 +35,15 @@ def sources():
 
 
 def _deps():
-    return sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + [os.path.join(ROOT, "include", "gcoo.h"), BASELINE_SRC,
+    return sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + [os.path.join(ROOT, "include", "gcoo.h"), BASELINE_SRC, CALLS_SRC,
                                                                   os.path.join(ROOT, "include", "gcoo_baseline.h")]
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(BASELINE_LIB):
+    built = (LIB, BASELINE_LIB, CALLS_LIB)
+    if not all(os.path.exists(x) for x in built):
         return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(BASELINE_LIB))
+    t = min(os.path.getmtime(x) for x in built)
     return any(os.path.getmtime(f) > t for f in _deps())
 
 
@@ -147,11 +151,26 @@ def verify_count_code(stem: str, text: str) -> None:
             raise RuntimeError(f"{stem} {kernel}: {arrivals} arrivals, {problems[:3]}")
 
 
+def _build_calls() -> None:
+    import sysconfig
+    import torch
+    torch_dir = os.path.dirname(torch.__file__)
+    inc, lib = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
+    tmp = CALLS_LIB + f".tmp{os.getpid()}"
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem", inc,
+                           "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), CALLS_SRC, "-o", tmp,
+                           "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{lib}"])
+    os.replace(tmp, CALLS_LIB)
+
+
 def build(force: bool = True, jobs: int = 8) -> str:
     if force or stale():
         os.makedirs(OBJ, exist_ok=True)
-        with ThreadPoolExecutor(max_workers=jobs) as ex:
+        with ThreadPoolExecutor(max_workers=jobs + 1) as ex:
+            calls = ex.submit(_build_calls)
             objs = list(ex.map(_compile, sources()))
+            calls.result()
         verify_generated_code()
         tmp = LIB + f".tmp{os.getpid()}"
         subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
