@@ -540,6 +540,8 @@ double band_time(int64_t m, int64_t k, int64_t nnz, int64_t N, BandPlan plan, bo
 // 66 entries per (wave, band) (product alone, us, wide and tall; 8000 x 8000, 0.35 %: 295 275, 0.5 %: 333 294, 0.9 %: 420 405, 1.2 %: 480 487; 12000 x 12000, 0.2 %: 809 669, 0.5 %: 1153 874, 0.9 %:
 // 1417 1309; 4000 x 4000, 0.5 %: 59 51, 2 %: 103 109; 14000 x 14000, 0.75 %: 2088 1845; 0.3 %, N = 500: 92 64).  Over 199 matrices with N near k the cut so chosen takes 0 to 0.7 % longer than the
 // faster of the two.
+// Fewer than 12 rows per wave only as long as the blocks before did not fill the compute units once: a matrix of few rows has few blocks (us, the best of 12 rows and more, and so:
+// 1836 x 2885, 20 %: 203 126; 558 x 4511, 6.6 %, N = 1504: 125 42; 2447 x 1964, 12 %: 92 71; 2467 x 3522, 3.6 %: 81 71; 765 x 6196, 9.4 %: 227 199).
 BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
 {
     if (p > gcoo::kSchedMaxP || m <= 0 || k <= 0 || nnz <= 0 || k > gcoo::kBandMaxK || share_policy_now() == GCOO_SHARE_NEVER) return {0, 0};
@@ -554,7 +556,9 @@ BandPlan band_plan(int64_t m, int64_t k, int64_t nnz, int32_t p)
     double best_time = 0.0;
     for (int v : {4, 2}) {
         if (v == 2 && (best.h == 0 || k > gcoo::kBandTallMaxK)) break;
-        for (int32_t h = 96 / v; h >= 12; --h) {
+        const int64_t tiles = (k + 64 * v - 1) / (64 * v);
+        for (int32_t h = 96 / v; h >= 1; --h) {
+            if (h < 12 && gcoo::band_blocks(m, h + 1) * tiles >= 256) break;
             // the columns of every list's rows as a bitmap, in the second sort buffer
             if (h % gcoo::band_lists_of(v) || gcoo::band_lists(m, h, v) * ((k + 31) / 32) > 3 * nnz) continue;
             const BandPlan plan = {h, v};

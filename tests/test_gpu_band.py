@@ -64,6 +64,21 @@ def test_bands_of_both_cuts(m, used, per_row, N):
     _run(_columns_used(m, 3500, used, per_row, N, seed=m + used), 32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
 
 
+@pytest.mark.parametrize("m,used,per_row,N", [(2600, 150, 150, 260), (2600, 160, 150, 256), (4601, 161, 150, 4), (4600, 240, 150, 512), (4607, 241, 150, 252), (4608, 319, 60, 260),
+                                              (4608, 320, 60, 128), (4609, 321, 60, 4), (4700, 480, 62, 252), (2700, 160, 60, 132), (1500, 320, 150, 64), (1000, 240, 205, 64)])
+def test_bands_of_both_cuts_with_many_and_few_rows_per_wave(m, used, per_row, N):
+    """Matrices of so many rows that the blocks fill the compute units with 12 to 48 rows per wave, and of fewer."""
+    print(f"band, both cuts: m={m} used={used} per_row={per_row} N={N}", flush=True)
+    _run(_columns_used(m, 3500, used, per_row, N, seed=m + used), 32, binding.VARIANT_SHARE, kernel=binding.KERNEL_BAND)
+
+
+@pytest.mark.parametrize("m,k,N,per_row", [(301, 2962, 2427, 350), (300, 4511, 4504, 300), (120, 6000, 6000, 900), (1836, 2885, 1836, 577)])
+def test_few_rows_per_wave(m, k, N, per_row):
+    """Fewer than twelve, in both cuts."""
+    print(f"band, few rows: m={m} k={k} N={N} per_row={per_row}", flush=True)
+    _run(workloads.uniform_random(m, k, N, 1 - per_row / k, seed=m + N), 32, binding.VARIANT_AUTO, 1, 1, kernel=binding.KERNEL_BAND)
+
+
 @pytest.mark.parametrize("m,k,N,s,shift,pad", [(4000, 4000, 2044, 0.98, 0, 0), (5000, 5001, 2501, 0.995, 0, 0), (5000, 5001, 2500, 0.995, 1, 0)])
 def test_automatic_choice_of_both_cuts(m, k, N, s, shift, pad):
     """The wide cut with few entries per band; the tall one with rows of B aligned to 4 bytes only, its last tile inside the one before."""
