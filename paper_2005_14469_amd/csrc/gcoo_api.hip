@@ -470,12 +470,15 @@ double few_columns_rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool 
 // where their LDS allows it, costs 1.5 us and what the tiles take to come in, and the entries of its rows: 3.8 ns per sixteen of them while enough waves read LDS, 26 ns per entry of a row for
 // a wave by itself.  Where rows are long and workgroups have fewer of them than slots, a row has a whole wave to itself (`whole`; 1000 x 2480, 20 %, N = 64: 19.7 us with a row per slot, 9.1 so).
 // Fitted to the products above in 2 to 14 cuts each: mean error 8 %; the cut so chosen takes 1.3 % longer than the best one.
-struct TilePlan { int64_t row_wgs; bool whole; double time; };
-TilePlan tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
+// `preferred`: the tile kernel is taken, [1] where rows of B are on lines: where it is expected to need 0.85 of the time of the row-by-row kernel from the caches.  Of 900 products that leaves 6
+// that lose more than 3 % by it (48 with 1, 15 with 0.9), and they take 17.6 % less on (geometric) average (17.8 with 0.9).
+struct TilePlan { int64_t row_wgs; bool whole; double time; bool preferred[2]; };
+const TilePlan& tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
 {
-    static thread_local struct { int64_t m, k, nnz, N; TilePlan plan; } last = {0, 0, 0, 0, {0, false, 0.0}};
+    // (a product asks more than once, and a small one is not long)
+    static thread_local struct { int64_t m, k, nnz, N; TilePlan plan; } last = {0, 0, 0, 0, {0, false, 0.0, {false, false}}};
     if (last.m == m && last.k == k && last.nnz == nnz && last.N == N) return last.plan;
-    TilePlan best = {0, false, 0.0};
+    TilePlan best = {0, false, 0.0, {false, false}};
     if (m >= 1 && k >= 1 && N >= gcoo::kTileCols && nnz <= gcoo::kTileMaxNnz) {
         const int64_t tiles = (N + gcoo::kTileCols - 1) / gcoo::kTileCols, room = (gcoo::kTileLdsBytes - 4 - (k + 1) * (4 * gcoo::kTileCols)) / 6;
         const int64_t most_rows = std::min<int64_t>(room, gcoo::kTileMaxRows), least = most_rows >= 1 ? (m + most_rows - 1) / most_rows : 0;
@@ -490,25 +493,21 @@ TilePlan tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
                 const double items = whole ? (double)rows : (double)((rows + gcoo::kTileCols - 1) / gcoo::kTileCols), steps = whole ? std::ceil(mean / 16.0) : mean;
                 const double full = (double)per * items * (steps + (whole ? 12.0 : 0.0)) * 0.0038, alone = std::ceil(items / 16.0) * (steps * 0.026 + (whole ? 0.52 : 0.38));
                 const double t = 2.4 + (double)rounds * (1.54 + 0.00098 * (double)(k * per) + std::max(full, alone)) + 1e-6 * (double)m * (double)N;
-                if (best.row_wgs == 0 || t < best.time) best = {wgs, whole != 0, t};
+                if (best.row_wgs == 0 || t < best.time) best = {wgs, whole != 0, t, {false, false}};
             }
         }
     }
+    if (best.row_wgs > 0)
+        for (int lines : {0, 1}) best.preferred[lines] = best.time < 0.85 * few_columns_rows_time(m, k, nnz, N, lines != 0);
     last = {m, k, nnz, N, best};
-    return best;
-}
-// The tile kernel is taken where it is expected to need 0.85 of the time of the row-by-row kernel from the caches: of 900 products that leaves 6 that lose more than
-// 3 % by it (48 with 1, 15 with 0.9), and they take 17.6 % less on (geometric) average (17.8 with 0.9).
-bool tile_preferred(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
-{
-    const TilePlan plan = tile_plan(m, k, nnz, N);
-    return plan.row_wgs > 0 && plan.time < 0.85 * few_columns_rows_time(m, k, nnz, N, lines);
+    return last.plan;
 }
 // The faster of the two without a schedule.
 double no_schedule_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 {
     const double rows = rows_time(m, k, nnz, N, lines);
-    return tile_preferred(m, k, nnz, N, lines) ? std::min(rows, tile_plan(m, k, nnz, N).time + 1.0) : rows;
+    const TilePlan& plan = tile_plan(m, k, nnz, N);
+    return plan.preferred[lines] ? std::min(rows, plan.time + 1.0) : rows;
 }
 // Bands: a workgroup per compute unit and round; 0.63 us for a band by itself (80 KB of B, the barrier, the bubble behind it) and 2.46 ns per
 // entry of the block, 0.67 and 1.64 in the tall cut, whose bands have twice the rows and whose tiles are half as wide; C and B once, and
@@ -1601,8 +1600,8 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         }
         if (kernel == GCOO_KERNEL_ROWS) {
             const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0, reach = (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
-            const TilePlan plan = tile_plan(A->m, A->k, A->nnz, N);
-            hipError_t e = reach && tile_preferred(A->m, A->k, A->nnz, N, lines) ? gcoo::launch_spdm_rows_tile(rows, plan.row_wgs, plan.whole, s) : gcoo::launch_spdm_rows(rows, s);
+            const TilePlan& plan = tile_plan(A->m, A->k, A->nnz, N);
+            hipError_t e = reach && plan.preferred[lines] ? gcoo::launch_spdm_rows_tile(rows, plan.row_wgs, plan.whole, s) : gcoo::launch_spdm_rows(rows, s);
             return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
         }
         gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band.h), A->L.band.h, A->L.band.v,

@@ -3,6 +3,9 @@
 
 namespace gcoo {
 
+// Waves of a launch that has one row and 256 columns to each: 8192 are resident at a time.
+static int64_t rows_waves(int64_t m, int64_t N) { return m * ((N + 255) / 256); }
+
 template <int LPR, bool WIDE, int AHEAD>
 static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
 {
@@ -13,11 +16,13 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
     auto groups = [&](int64_t r) { return (a.m + waves * r - 1) / (waves * r); };
     // Rows per wave: one per slot, so that a launch has many short workgroups, and two or four per slot where rows are short, the loads of one behind those of the one before
     // (us, 1, 2, 4, 8 and 16 rows per wave: 7999 x 7999, rows of 8, 64 columns per tile - 231 169 177 229, 128 columns - 164 176 211 261; 12001 x 12001, of 6, 128 columns
-    // - 426 426 448 482; 5000 x 5000, of 2, N = 5001, 256 columns - 42.6 43.2 46.1 46.3).  A launch that cannot
+    // - 426 426 448 482; 5000 x 5000, of 2, N = 5001, 256 columns - 42.6 43.2 46.1 46.3).  Not where all waves are resident at once: there a row more is a trip to memory more (322 x 295, of 2,
+    // N = 295, kernel alone, 2 and 4 rows: 3.2 3.9).  A launch that cannot
     // fill the chip has fewer rows per wave, each on all slots of it.
     int64_t rpw = spw;
-    if (mean < 6) rpw = LPR == 32 ? 4 : (LPR == 64 ? 2 : spw);
-    else if (mean < 10) rpw = LPR == 64 ? 2 : spw;
+    const bool many = rows_waves(a.m, a.N) > 8192;
+    if (many && mean < 6) rpw = LPR == 32 ? 4 : (LPR == 64 ? 2 : spw);
+    else if (many && mean < 10) rpw = LPR == 64 ? 2 : spw;
     else if (mean > 12) while (rpw > 1 && groups(rpw) * tiles < 256) rpw /= 2;
     const int64_t row_wgs = groups(rpw);
     const int64_t rest = tiles % 8 * row_wgs, grid = tiles / 8 * 8 * row_wgs + (rest + 7) / 8 * 8;
@@ -64,6 +69,11 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // hardly take a row of B more than once before it has to be read anyway: 10643 x 10643, of 1.2, N = 8867: 201 170 157; 18739 rows of 5.6, N = 5569: 355 340 354; 12862 of 9.3, N = 2461: 133 144
     // 160.  Few columns: 3494 x 3494, rows of 12.6, N = 5853: 91 81 75; 4366 columns, N = 10409: 237 211 220.  Where between two points of these sweeps a line lies is a choice.
     const bool lines = a.ldb % 32 == 0 && reinterpret_cast<uintptr_t>(a.B) % 128 == 0;
+    // While all waves are resident at once, 256 columns to each are the shortest way (kernel alone, us, 64, 128 and 256 columns: 408 x 408, rows of 0.3, N = 583: 3.4 3.4 3.3; 639 x 796, of 21,
+    // N = 639: 6.0 5.7 5.0; 2217 x 1707, of 22, N = 197: 7.3 6.4 5.4; over 96 products 5 to 10 % less), but for up to 128 columns and for rows of as many entries as uneven ones have on average.
+    const int64_t waves = rows_waves(a.m, a.N);
+    if (a.N > 64 && waves <= 8192 && (a.nnz < 25 * a.m || a.m < 1000))
+        return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, s) : launch_rows<32>(a, s);
     if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
     if (a.N < 1000) {
         // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 90)
