@@ -23,6 +23,7 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
     const bool many = rows_waves(a.m, a.N) > 8192;
     if (many && mean < 6) rpw = LPR == 32 ? 4 : (LPR == 64 ? 2 : spw);
     else if (many && mean < 10) rpw = LPR == 64 ? 2 : spw;
+    else if (mean >= 120 && groups(rpw) * tiles < 4096) rpw = spw > 4 ? spw / 4 : 1;         // (9072 x 9072, rows of 143, N = 34: 19.0 16.3; 17015, of 279, N = 20: 51.5 40.6)
     else if (mean > 12) while (rpw > 1 && groups(rpw) * tiles < 256) rpw /= 2;
     const int64_t row_wgs = groups(rpw);
     const int64_t rest = tiles % 8 * row_wgs, grid = tiles / 8 * 8 * row_wgs + (rest + 7) / 8 * 8;
@@ -59,9 +60,9 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     }
     // a B of more than 4 GB is beyond the offsets of a buffer descriptor
     if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows_ahead<16, true, 16>(a, s);
-    // 64, 32 or 16 columns per tile: the fewest lanes without a column of their own
-    if (a.N <= 16) return launch_rows<4>(a, s);
-    if (a.N <= 32) return launch_rows<8>(a, s);
+    // Up to 32 columns: four or eight lanes to a row where that leaves enough workgroups, sixteen else, those without a column of their own along (kernel alone, us, 8 lanes and 16:
+    // 6124 x 6124, rows of 19, N = 28: 7.4 4.9; 8788 x 9414, of 18, N = 27: 5.6 6.2).
+    if (a.N <= 32 && a.m >= 7000) return a.N <= 16 && a.m >= 16384 ? launch_rows<4>(a, s) : launch_rows<8>(a, s);
     // 64, 128 or 256 columns per tile.  Wider tiles are fewer requests for the same bytes and, where rows of B begin inside a 128-byte line, fewer lines per byte (3 for
     // 256 bytes, 5 for 512, 9 for 1024); narrower ones stay in an XCD's L2 (4 MB) at more rows of B, and have more slots to a wave for uneven rows, of which the host knows nothing.
     // From the times of all three in 960 products with rows of B inside a line and 800 with rows on lines, 300 to 20000 rows and columns, rows of 1 to 250 entries and power-law rows (us,

@@ -174,3 +174,10 @@ def test_long_rows_in_turns_over_the_xcds_of_a_tile(N):
     lens = np.full(3001, 150)
     lens[:90] = lens[2950:] = lens[500:2500:9] = 1300
     _check(_rows_of_lengths(lens, 12000, N, seed=N), 32, 1 if N % 2 else 0)
+
+
+@pytest.mark.parametrize("m,k,N,lens", [(17000, 900, 16, [3, 0, 9]), (7001, 900, 16, [30, 2]), (7001, 900, 29, [3, 0, 40]), (900, 7000, 31, [130, 250]), (50, 7000, 63, [900, 130, 121]), (601, 5000, 200, [300, 0, 140])])
+def test_narrow_tiles_and_rows_of_many_entries(m, k, N, lens):
+    """Four, eight and sixteen lanes to a row; rows of so many entries that all slots of a wave take one at a time."""
+    print(f"rows: narrow m={m} k={k} N={N} lens={lens}", flush=True)
+    _check(_rows_of_lengths(np.resize(lens, m), k, N, seed=m + N), 32, 1 if N % 2 else 0)
