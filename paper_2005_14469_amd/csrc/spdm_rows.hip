@@ -76,7 +76,9 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     if (a.N > 64 && waves <= 8192 && (a.nnz < 25 * a.m || a.m < 1000))
         return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, s) : launch_rows<32>(a, s);
     if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
-    if (a.N < 1000) {
+    // From 897 columns on there are eight tiles of 128 columns, one per XCD (us, 64 and 128 columns: power-law rows, 3611 x 3611, N = 926: 54 43; 4658 x 4658, N = 994: 64 56; 9046 x 9046, N = 895: 136 138;
+    // rows of 89, 3454 x 3454, N = 917: 68 59; but power-law rows, 4830 x 7014, N = 663: 59 71; 8809 x 8809, N = 761: 103 126).
+    if (a.N <= 896) {
         // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 90)
         const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
         return one || eight || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
