@@ -88,11 +88,12 @@ inline int32_t rows_long(int64_t m, int64_t nnz)
 }
 // By how many columns at the most the tiles are moved down, so that the rows of C are stored in whole 128-byte lines.  That costs a tile more and, where B has the pitch of C, takes nothing from
 // the lines of B that a stretch lies in: it pays where C is most of the traffic (us, moved and not: 12471 x 12471, rows of 1.1 entries, N = 5125: 76 81; 10845 columns, rows of 5.3, N = 9494:
-// 343 350; 6298, of 7.2, N = 2285: 42 38; 11050, of 44, N = 237: 45 37).
+// 343 350; 6298, of 7.2, N = 2285: 42 38; 11050, of 44, N = 237: 45 37).  From 129 to 160 columns there are three tiles of 64 either way, and the last is not a sliver (over 65 products 2 to 3 % less:
+// 18677 x 20000, of 13.5, N = 155: 23.5 25.7; power-law rows, 14575 x 13587, N = 158: 65 71; but from 65 to 97 level).
 inline int32_t rows_moved(int64_t m, int64_t nnz, int64_t N, const float* C, int64_t ldc)
 {
     if (ldc % 32 == 0 && reinterpret_cast<uintptr_t>(C) % 128 == 0) return 0;
-    return nnz <= 4 * m || (nnz <= 8 * m && m * N >= 25000000) ? 31 : 0;
+    return nnz <= 4 * m || (nnz <= 8 * m && m * N >= 25000000) || (N > 128 && N <= 160) ? 31 : 0;
 }
 // Largest B (k x ldb) whose rows a buffer descriptor reaches with something left above for the entries past the end of a row.
 constexpr uint64_t kRowsMaxBytes = 0xffffefffull;
