@@ -79,10 +79,14 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // From 897 columns on there are eight tiles of 128 columns, one per XCD (us, 64 and 128 columns: power-law rows, 3611 x 3611, N = 926: 54 43; 4658 x 4658, N = 994: 64 56; 9046 x 9046, N = 895: 136 138;
     // rows of 89, 3454 x 3454, N = 917: 68 59; but power-law rows, 4830 x 7014, N = 663: 59 71; 8809 x 8809, N = 761: 103 126).
     if (a.N <= 896) {
-        // One tile in place of three or four where rows begin inside lines, for rows of more entries than uneven ones have on average and while the tile stays near an XCD's L2 (us, 64 and 256 columns: 5699 x 6659,
-        // rows of 104, N = 134: 31 23; 8516 x 6585, of 65, N = 157: 28 22; 14161 x 14161, of 74, N = 154: 63 60; 5619 x 6520, of 55, N = 200: 20 17; but 9627 x 11477, of 84, N = 179: 46 50;
-        // power-law rows, of 45, 2808 x 3141, N = 131: 17 37).
-        if (!lines && a.nnz >= 53 * a.m && a.N > 128 && (a.N <= 160 || (a.N <= 208 && a.k <= 9100))) return launch_rows<64>(a, s);
+        // One tile in place of three or four where rows begin inside lines: for rows of more entries than uneven ones have on average, while the tile stays near an XCD's L2, and up to 160 columns also where none of
+        // the tiles would stay in it (us, 64 and 256 columns: 5699 x 6659, rows of 104, N = 134: 31 23; 8516 x 6585, of 65, N = 157: 28 22; 14161 x 14161, of 74, N = 154: 63 60; 5619 x 6520, of 55, N = 200: 20 17;
+        // 12411 x 12959, of 20, N = 131: 17.3 15.2; 19195 x 15201, of 4, N = 148: 9.1 8.3; power-law rows, of 50, 17075 x 17075, N = 150: 89 78, 18289 x 20000, N = 130: 101 79; but 17686 x 17757, N = 151: 90 100, 9627 x 11477, of 84, N = 179: 46 50;
+        // power-law rows, 2808 x 3141, N = 131: 17 37; 15071 x 15071, N = 131: 71 78).
+        if (!lines && a.N > 128) {
+            const int64_t from = a.nnz >= 53 * a.m ? 0 : (a.nnz < 25 * a.m ? 11000 : (a.N <= 150 ? 16000 : INT64_MAX));
+            if (a.N <= 160 ? a.k >= from : (a.N <= 208 && from == 0 && a.k <= 9100)) return launch_rows<64>(a, s);
+        }
         // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 90)
         const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
         return one || eight || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
