@@ -73,7 +73,10 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // While all waves are resident at once, 256 columns to each are the shortest way (kernel alone, us, 64, 128 and 256 columns: 408 x 408, rows of 0.3, N = 583: 3.4 3.4 3.3; 639 x 796, of 21,
     // N = 639: 6.0 5.7 5.0; 2217 x 1707, of 22, N = 197: 7.3 6.4 5.4; over 96 products 5 to 10 % less), but for up to 128 columns and for rows of as many entries as uneven ones have on average.
     const int64_t waves = rows_waves(a.m, a.N);
-    if (a.N > 64 && waves <= 8192 && (a.nnz < 25 * a.m || a.m < 1000))
+    // From half of those waves on only where the last tile is not mostly empty (three matrices in turn, 64, 128 and 256 columns: 2350 x 2350, of 5, N = 317: 4.7 5.0 5.9; 2176 x 2068, of 5, N = 456: 4.9 5.0 5.5;
+    // 4006 x 5846, of 12, N = 302, as the rules below have it and 256: 9.0 11.9; but 1541 x 1249, of 3, N = 466: 4.0 4.1 4.0; one tile, 4106 x 2467, of 25, N = 204: 10.2 8.5).
+    const bool full = waves <= 4096 || a.N <= 256 || 256 * 100 * ((a.N + 255) / 256) <= 115 * a.N;
+    if (a.N > 64 && waves <= 8192 && full && (a.nnz < 25 * a.m || a.m < 1000))
         return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, s) : launch_rows<32>(a, s);
     if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
     // From 897 columns on there are eight tiles of 128 columns, one per XCD (us, 64 and 128 columns: power-law rows, 3611 x 3611, N = 926: 54 43; 4658 x 4658, N = 994: 64 56; 9046 x 9046, N = 895: 136 138;
