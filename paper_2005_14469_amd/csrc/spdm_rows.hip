@@ -95,7 +95,13 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         return one || eight || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
     }
     if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, s);
-    if (a.k <= 9000 || a.nnz <= (lines ? 4 : 7) * a.m) return launch_rows<32>(a, s);
+    // Many rows of B: while all of B stays in the memory-side cache (256 MB), tiles of 64 columns, which stay longest in an XCD's L2; beyond, rows of a few entries take theirs from memory either way, and
+    // in longer stretches by 128 columns (64 and 128; B inside lines: 12878 x 12878, rows of 6.1, N = 1563: 57 69; 13474 x 13474, of 4.5, N = 3602: 115 127; 10081 x 10081, of 4.4, N = 5285: 109 119; 8667 x 8667, of 6.5,
+    // N = 6681: 138 144; but of 1.7 entries, 7706 x 8902, N = 1171: 19.3 16.6; of 4, 9739 x 9739, N = 1024: 19.4 17.8; 14065 x 14065, of 4, N = 6254: 236 212; 9307 x 9307, of 8.2, N = 9307: 320 283; 9531 x 9531, of 9.4: 357 322.  On lines: 13211 x 13211, of 3.8, N = 3584: 74 83; 10176 x 10176, of 4.6,
+    // N = 10176: 250 233; 10372 x 12632, of 5.8, N = 10368: 288 273; 14533 x 14533, of 8.2, N = 14528: 576 626).
+    const bool cached = a.k * a.N <= 66000000;
+    const int64_t few = cached ? (a.N <= 1024 ? (lines ? 4 : 7) : 3) : (lines ? 6 : 10);          // entries per row; up to 1024 columns are eight tiles of 128
+    if (a.k <= (cached ? 8000 : 9000) || a.nnz <= few * a.m) return launch_rows<32>(a, s);
     return launch_rows<16>(a, s);
 }
 

@@ -162,7 +162,8 @@ def test_no_columns(p, policy):
                                                   (90, 200, 1103, [60, 1, 17], 1, 2), (150, 6600, 77, [40, 0, 33], 2, 0), (150, 6600, 129, [40, 0, 33], 0, 0),
                                                   (130, 9100, 1030, [7, 9, 0], 1, 0), (130, 9100, 1030, [70, 9, 0], 1, 0), (1003, 2700, 129, [60, 53, 70], 1, 0), (1003, 2700, 208, [60, 53, 70], 0, 1),
                                                   (1003, 2700, 129, [40, 0, 33], 1, 0), (1003, 2700, 160, [40, 0, 33], 2, 1), (1003, 2700, 897, [40, 7], 1, 0),
-                                                  (9001, 11000, 135, [5, 0, 7], 1, 0), (2100, 2700, 317, [5, 0, 7], 1, 0), (1040, 2700, 1047, [5, 0, 7], 0, 0)])
+                                                  (9001, 11000, 135, [5, 0, 7], 1, 0), (2100, 2700, 317, [5, 0, 7], 1, 0), (1040, 2700, 1047, [5, 0, 7], 0, 0),
+                                                  (130, 8100, 1030, [7, 4, 0], 1, 0), (130, 9100, 7300, [9, 4, 0], 1, 0)])
 def test_widths_of_tiles_and_tiles_moved_to_whole_lines(m, k, N, lens, shift, pad):
     """64, 128 and 256 columns per tile, moved down to whole lines of C (rows of a few entries) and not."""
     print(f"rows: tiles m={m} k={k} N={N} lens={lens} shift={shift}", flush=True)
