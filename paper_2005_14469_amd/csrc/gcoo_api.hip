@@ -314,7 +314,7 @@ struct Layout {
     size_t take_flags, splits;
     size_t tmp_cols, tmp_rows, tmp_vals;                   // conversion scratch (second sort buffer)
     size_t in_row_ptr, in_cols, in_vals;                   // staging of a host CSR input
-    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4), uneven rows (4), -, ticket of a dense count (8)
+    size_t counter;                                        // device words: nnz (8 bytes), largest group (8), column-out-of-range flag (4), long rows (4), uneven rows (4), longest rows (4), ticket of a dense count (8)
     size_t persistent;                                     // bytes up to here stay in use after the conversion
     // offsets from here on are relative to the scratch area: the caller's buffer from `persistent` on, or the
     // library's static scratch

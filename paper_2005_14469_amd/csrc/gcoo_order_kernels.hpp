@@ -51,7 +51,7 @@ struct TakeArgs {
     int32_t* splits;           // [m * (parts - 1)] where the later parts of a row begin
     uint32_t* bits;            // [lists * ceil(k/32)] columns of a list, or null
     int32_t heavy;             // a list of more entries makes the matrix uneven
-    uint32_t* zero_bad;        // bad_col, the count of long rows, the word for uneven matrices
+    uint32_t* zero_bad;        // bad_col, the count of long rows, the word for uneven matrices, the count of the longest rows
     unsigned long long* stats; // or null; a workgroup more
 };
 
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(THREADS) void take_rows(TakeArgs a)
         return;
     }
     const int32_t list = (int32_t)blockIdx.x;
-    if (list == 0 && tid < 3) a.zero_bad[tid] = 0u;
+    if (list == 0 && tid < 4) a.zero_bad[tid] = 0u;
     // Offsets are clamped to [0, nnz]: with a device input whose row_ptr does not match the nnz the buffer was laid out
     // for, every later kernel still stays inside the arrays.
     const int32_t nnz = a.nnz, m = (int32_t)a.m;

@@ -75,8 +75,8 @@ struct RowsArgs {
     int64_t N;
     float* C;
     int64_t ldc;
-    const int32_t* long_rows;  // the rows of more than `long_row` entries, in any order
-    const int32_t* long_count; // or null: long_room places, -1 in those without a row
+    const int32_t* long_rows;  // long_room places for the rows of more than `long_row` entries (RowsOut)
+    const int32_t* long_count; // or null: -1 in places without a row
     int32_t long_row, long_room;
     int32_t moved;             // 31: tiles are moved down to whole lines of C, 0: they are not (set by the launchers)
 };

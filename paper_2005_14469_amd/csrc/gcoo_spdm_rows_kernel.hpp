@@ -233,16 +233,16 @@ struct RowsTile {
     }
 };
 
-// The long rows `turn`, `turn` + step, ..., all slots of a workgroup of WAVES waves on each.  `part`: WAVES stretches of a tile's columns in LDS.  PLACES: the long rows are
+// The long rows `turn`, `turn` + step, ..., the `n_front` longest first, all slots of a workgroup of WAVES waves on each.  `part`: WAVES stretches of a tile's columns in LDS.  PLACES: the long rows are
 // in places, not counted (RowsArgs), and place `turn` holds `at_turn`.
 template <int LPR, bool WIDE, int AHEAD, int WAVES, bool PLACES>
-__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
+__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t n_front, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
 {
     constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES;
     const RowsArgs& a = T.a;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int32_t x = turn; x < n_long; x += step) {
-        const int32_t lr = __builtin_amdgcn_readfirstlane(PLACES && x == turn ? at_turn : a.long_rows[x]);
+        const int32_t lr = __builtin_amdgcn_readfirstlane(PLACES ? (x == turn ? at_turn : a.long_rows[x]) : a.long_rows[x < n_front ? x : a.long_room - 1 - (x - n_front)]);
         if (PLACES && (lr < 0 || lr >= (int32_t)a.m)) continue;                      // a place without a row
         const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
         if (PLACES && le - lb <= a.long_row) continue;
@@ -340,8 +340,9 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
     const int32_t start = T.lane <= wrows && wrows > 0 ? a.row_ptr[w0 + T.lane] : 0;
     const int32_t long_first = PLACES && wg < a.long_room ? a.long_rows[wg] : -1;    // (asked for beside the starts)
-    int32_t n_long = PLACES ? a.long_room : (a.long_count ? *a.long_count : 0);
-    n_long = n_long < a.long_room ? n_long : a.long_room;
+    int32_t n_front = PLACES ? 0 : (a.long_count ? a.long_count[2] : 0), n_long = PLACES ? a.long_room : (a.long_count ? a.long_count[0] : 0);
+    n_front = n_front < a.long_room ? n_front : a.long_room;
+    n_long = n_long < a.long_room - n_front ? n_front + n_long : a.long_room;
     int32_t turn = wg;
     if (__builtin_expect(!PLACES && slice && n_long > 0, 0)) {
         // The XCDs that share a tile take its long rows in turns: by the place of a workgroup among those of its XCD, then by XCD.  (In the order of `wg` the first XCD of a tile would
@@ -354,7 +355,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
         }
     }
     // (out of the way of matrices without long rows: 12000 x 12000, 0.5 %, N = 64: 12.15 us without the hints, 12.13 so)
-    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, WAVES, PLACES>(T, n_long, turn, row_wgs, long_first, part);
+    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, WAVES, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
     rows_of_wave<LPR, WIDE, AHEAD>(T, w0, wrows, start, wave_row, a.long_row);
 }
 

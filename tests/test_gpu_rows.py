@@ -184,3 +184,11 @@ def test_narrow_tiles_and_rows_of_many_entries(m, k, N, lens):
     """Four, eight and sixteen lanes to a row; rows of so many entries that all slots of a wave take one at a time."""
     print(f"rows: narrow m={m} k={k} N={N} lens={lens}", flush=True)
     _check(_rows_of_lengths(np.resize(lens, m), k, N, seed=m + N), 32, 1 if N % 2 else 0)
+
+
+@pytest.mark.parametrize("lens", [[1536, 1537], [1537, 1537, 1537], [513, 1536], [512, 600, 2500, 0]])
+@pytest.mark.parametrize("dense", [False, True])
+def test_longest_rows_from_the_front_of_the_list(lens, dense):
+    """Rows just below and above the lengths from which a row is listed, and from the front: one class alone and both, the list filled from both sides."""
+    print(f"rows: longest first lens={lens} dense={dense}", flush=True)
+    _check(_rows_of_lengths(np.resize(lens + [3] * 20, 301), 9000, 67, seed=len(lens)), 32, dense=dense)
