@@ -480,8 +480,7 @@ const TilePlan& tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
     if (last.m == m && last.k == k && last.nnz == nnz && last.N == N) return last.plan;
     TilePlan best = {0, false, 0.0, {false, false}};
     if (m >= 1 && k >= 1 && N >= gcoo::kTileCols && nnz <= gcoo::kTileMaxNnz) {
-        const int64_t tiles = (N + gcoo::kTileCols - 1) / gcoo::kTileCols, room = (gcoo::kTileLdsBytes - 4 - (k + 1) * (4 * gcoo::kTileCols)) / 6;
-        const int64_t most_rows = std::min<int64_t>(room, gcoo::kTileMaxRows), least = most_rows >= 1 ? (m + most_rows - 1) / most_rows : 0;
+        const int64_t tiles = (N + gcoo::kTileCols - 1) / gcoo::kTileCols, most_rows = gcoo::tile_most_rows(k), least = most_rows >= 1 ? (m + most_rows - 1) / most_rows : 0;
         const double mean = (double)nnz / (double)m;
         const int64_t wanted[] = {least, 256 / tiles, 512 / tiles, 768 / tiles, 1024 / tiles, m / 512, m / 256};
         for (int64_t wgs : wanted) {

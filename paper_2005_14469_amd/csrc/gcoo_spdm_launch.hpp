@@ -105,10 +105,15 @@ constexpr int kTileCols = 16;
 constexpr int kTileMaxRows = 1023;
 constexpr int64_t kTileLdsBytes = 160 * 1024 - 16;        // the kernel has two words of its own
 constexpr int64_t kTileMaxNnz = 1 << 29;                  // byte offsets of entries
-inline int64_t tile_lds(int64_t k, int64_t rows)
+constexpr int kTileBins = 256;                            // lengths of rows in steps of four entries; the last bin is open
+// Its LDS: the tile, k rows of B and one of zeros, and before it comes in, in the same place, the bins of the row lengths; behind the larger of the two (the bins up to 14 columns), where
+// the workgroup's rows begin, `rows` + 1; its rows by falling length, 16 bits each.
+constexpr int64_t tile_lds_rows(int64_t k) { return (k + 1) * (4 * kTileCols) > 4 * kTileBins ? (k + 1) * (4 * kTileCols) : 4 * kTileBins; }
+constexpr int64_t tile_lds(int64_t k, int64_t rows) { return tile_lds_rows(k) + 4 * (rows + 1) + 2 * rows; }
+constexpr int64_t tile_most_rows(int64_t k)               // of a workgroup; less than 1: the kernel does not serve so many columns
 {
-    const int64_t bytes = (k + 1) * (4 * kTileCols) + 4 * (rows + 1) + 2 * rows;
-    return bytes < 1024 ? 1024 : bytes;                    // (the bins of the row lengths)
+    const int64_t room = (kTileLdsBytes - 4 - tile_lds_rows(k)) / 6;
+    return room < kTileMaxRows ? room : kTileMaxRows;
 }
 hipError_t launch_spdm_rows_tile(const RowsArgs& a, int64_t row_wgs, bool whole, hipStream_t s);
 

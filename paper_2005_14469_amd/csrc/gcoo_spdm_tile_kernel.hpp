@@ -34,7 +34,6 @@ constexpr int kTileThreads = 64 * kTileWaves;
 constexpr int kTileLanes = 4;                             // of a slot
 constexpr int kTileSlots = 64 / kTileLanes;
 constexpr int kTileRowBytes = 4 * kTileCols;              // of B, in LDS
-constexpr int kTileBins = 256;                            // lengths of rows in steps of four entries; the last bin is open
 constexpr int kTileLoads = 10;                            // 16-byte pieces of B per thread, at most
 static_assert(kTileCols == 4 * kTileLanes && kTileMaxRows < kTileThreads && kTileLoads * kTileThreads * 16 >= kTileLdsBytes, "a thread per row and its end; all of the LDS");
 typedef float tile_f32x4 __attribute__((ext_vector_type(4)));
@@ -113,8 +112,7 @@ __device__ __forceinline__ void tile_entries(__amdgpu_buffer_rsrc_t cols, __amdg
     }
 }
 
-// LDS: the tile, k rows of 64 bytes and one of zeros | where the workgroup's rows begin, `rows` + 1 | its rows by falling length, 16 bits each.  The bins lie where
-// the tile comes to be.  Workgroup: (tile, rows [wg * rows, ...)), an XCD takes a stretch of them with the tiles side by side, so that the workgroups that read a
+// LDS: tile_lds_rows(), the bins where the tile comes to be.  Workgroup: (tile, rows [wg * rows, ...)), an XCD takes a stretch of them with the tiles side by side, so that the workgroups that read a
 // line of B do so through one L2.  `long_steps`: a row of more steps of four entries than this has a wave to itself.
 __global__ __launch_bounds__(kTileThreads, 8) void spdm_rows_tile(RowsArgs a, int32_t row_wgs, int32_t rows, int32_t total, int32_t long_steps)
 {
@@ -128,7 +126,7 @@ __global__ __launch_bounds__(kTileThreads, 8) void spdm_rows_tile(RowsArgs a, in
     const int32_t t = (int32_t)threadIdx.x, lane = t & 63, k = (int32_t)a.k, pieces = k * kTileLanes;
     const int64_t r0 = (int64_t)wg * rows;
     const int32_t mine = (int32_t)(a.m - r0 < rows ? a.m - r0 : rows);
-    int32_t* row_at = reinterpret_cast<int32_t*>(tile_smem + (size_t)(k + 1) * kTileRowBytes);
+    int32_t* row_at = reinterpret_cast<int32_t*>(tile_smem + tile_lds_rows(k));
     uint16_t* order = reinterpret_cast<uint16_t*>(row_at + rows + 1);
     int32_t* bins = reinterpret_cast<int32_t*>(tile_smem);
 

@@ -69,11 +69,11 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shared, void** st
     *grid = t_config.grid; *block = t_config.block; *shared = t_config.shared; *stream = t_config.stream;
     return 0;
 }
-int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t, void*)
+int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t shared, void*)
 {
     std::lock_guard<std::recursive_mutex> lock(g_mutex);
     const std::string& name = g_names[f];
-    say("launch " + name + " " + std::to_string(grid.x) + " " + std::to_string(block.x));
+    say("launch " + name + " " + std::to_string(grid.x) + " " + std::to_string(block.x) + " " + std::to_string(shared));
     // the kernels that tell the host a number: the place of the pointer among their arguments
     int host = name.find("read_entry_count") != std::string::npos ? 2 : name.find("count_dense_total") != std::string::npos ? 6
              : name.find("count_dense_blocks") != std::string::npos ? 9 : -1;

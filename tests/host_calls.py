@@ -340,7 +340,8 @@ def kernel_of_product(host):
 # (m, k, N, entries, whether the row-by-row product goes by a tile of B in LDS): what tests/test_gpu_tile.py multiplies, and the shapes beside the lines of the rule
 TILES = [(2047, 63, 500, 90000, True), (1023, 400, 1031, 102300, True), (1024, 400, 1031, 102400, True), (500, 1000, 17, 200000, True), (4000, 1500, 31, 600000, True),
          (700, 1280, 48, 300000, True), (700, 1279, 1031, 300000, True), (100, 2496, 517, 90000, True), (7, 2558, 4000, 14000, True), (92, 2550, 1024, 90000, True),
-         (93, 2550, 1024, 90000, True), (1777, 2301, 1117, 122666, True), (7, 2559, 4000, 14000, False), (500, 1000, 15, 200000, False), (256, 256, 256, 6553, False), (2500, 2500, 64, 62500, False)]
+         (93, 2550, 1024, 90000, True), (1777, 2301, 1117, 122666, True), (300, 1, 1031, 18000, True), (100, 2, 500, 20000, True), (2100, 4, 500, 42000, True), (4000, 6, 500, 24000, True), (1000, 10, 1000, 10000, True), (500, 14, 2000, 5600, True),
+         (300, 14, 4000, 4200, True), (2100, 15, 500, 16800, True), (2100, 16, 500, 16800, True), (7, 2559, 4000, 14000, False), (500, 1000, 15, 200000, False), (256, 256, 256, 6553, False), (2500, 2500, 64, 62500, False)]
 
 
 def tiles(host):
@@ -351,8 +352,13 @@ def tiles(host):
                 h = host.matrix(m, k, nnz, 32)
                 host.log()
                 assert host.spdm(h, N, ldb, variant, N + 5, (1 << 30) + off, (1 << 40) + off) == OK
-                names = host.launches()
-                assert len(names) == 1 and ("spdm_rows_tile" in names[0]) == tile, (m, k, N, nnz, variant, names)
+                (line,) = [x for x in host.log() if x.startswith("launch")]
+                assert ("spdm_rows_tile" in line) == tile, (m, k, N, nnz, variant, line)
+                if tile:
+                    # behind the tile and its row of zeros, and behind the 256 bins that lie there before: where the rows begin, and the rows in their order
+                    workgroups, _, shared = (int(x) for x in line.split()[2:])
+                    rows = -(-m // (workgroups // -(-N // 16)))                  # of a workgroup, at least
+                    assert shared >= max(64 * (k + 1), 1024) + 4 * (rows + 1) + 2 * rows, (m, k, N, nnz, line)
         # a B that the buffer descriptor does not reach
         assert host.spdm(h, N, (1 << 32) // (4 * k) + N, AUTO) == OK and "spdm_rows_tile" not in host.launches()[0], (m, k, N)
 
