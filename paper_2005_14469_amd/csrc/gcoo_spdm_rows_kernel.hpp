@@ -263,7 +263,8 @@ __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>&
     }
 }
 
-// The wave's rows [w0, w0 + wrows), a slot on each; lane i holds in `start` where row w0 + i begins, i = 0 .. wrows.  Rows of more than `long_row` entries are left out.
+// The wave's rows [w0, w0 + wrows), a slot on each; lane i holds in `start` where row w0 + i begins, i = 0 .. wrows.  Rows of more than `long_row` entries, which is no less
+// than `wave_row`, are left out.
 template <int LPR, bool WIDE, int AHEAD>
 __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t w0, int32_t wrows, int32_t start, int32_t wave_row, int32_t long_row)
 {
@@ -423,7 +424,8 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
             if (q >= items) break;
             if (q >= pieces) {
                 const int32_t w0 = r0 + (q - pieces) * rpw, wrows = r1 - w0 < rpw ? r1 - w0 : rpw;
-                rows_of_wave<LPR, false, 16>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row, limit);
+                // (a row above `limit` is taken out of the slots here, whatever `wave_row` is: it has its pieces)
+                rows_of_wave<LPR, false, 16>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row < limit ? wave_row : limit, limit);
                 continue;
             }
             const int32_t i = q / kRowsPieces, piece = q % kRowsPieces;

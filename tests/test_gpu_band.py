@@ -282,6 +282,46 @@ def test_uneven_rows_in_shares_of_equal_entries(m, N, heavy, long, short, shift)
     _run(w, 32, binding.VARIANT_SHARE, shift, shift, kernel=binding.KERNEL_BAND)
 
 
+def _in_pieces(vals, rows_of_b):
+    """The sum of a long row in its pieces: eight of four stretches each, a stretch one entry after the other, the stretches of a piece by pairs, the pieces in their order.
+    Every product is exact."""
+    terms = vals[:, None] * rows_of_b
+    each = -(-len(vals) // 32)
+    stretches = np.zeros((32, terms.shape[1]), np.float32)
+    for i, term in enumerate(terms):
+        stretches[i // each] += term
+    s = stretches.reshape(8, 4, -1)
+    pieces = (s[:, 0] + s[:, 1]) + (s[:, 2] + s[:, 3])
+    total = pieces[0].copy()
+    for x in pieces[1:]:
+        total += x
+    return total
+
+
+@pytest.mark.parametrize("N,shift", [(2048, 0), (2051, 1)])
+def test_uneven_rows_of_many_entries_are_multiplied_once(N, shift):
+    """A mean of more than 128 entries, and rows that are long, but less than twice the mean: in pieces and nowhere else, so that the bits do not go by which of two waves is the last."""
+    print(f"band: uneven rows of many entries N={N}", flush=True)
+    rng = np.random.default_rng(N)
+    m, k = 4000, 3600
+    lens = rng.integers(130, 170, m)
+    lens[1000:1012] = 3000
+    long = np.arange(5, m, 50)
+    lens[long] = np.resize([255, 256, 257, 258, 288, 289, 310], len(long))
+    mean = int(lens.sum()) // m
+    assert 155 < mean and 310 < 2 * mean
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(k, n, replace=False)) for n in lens]).astype(np.int32)
+    B = (2.0 ** rng.integers(-3, 4, (k, N)) * rng.choice([-1.0, 1.0], (k, N))).astype(np.float32)
+    w = workloads.Workload("uneven", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), B)
+    _run(w, 32, binding.VARIANT_AUTO, shift, 3, kernel=binding.KERNEL_BAND)
+    Bd = torch.from_numpy(B).to(DEV)
+    A = binding.gcoo_from_csr(m, k, *[torch.from_numpy(x).to(DEV) for x in (rp, ci, w.vals)], 32, known_nnz=True)
+    C = binding.gcoo_spdm(A, Bd).cpu().numpy()
+    for r in long[lens[long] > 256]:
+        assert np.array_equal(C[r], _in_pieces(w.vals[rp[r]:rp[r + 1]], B[ci[rp[r]:rp[r + 1]]])), (r, lens[r])
+
+
 def test_export_share_of_a_matrix_with_a_band_schedule():
     """There is no share schedule to copy: nothing but empty arrays, no uninitialised ones."""
     print("band: export_share", flush=True)
