@@ -457,7 +457,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
         const int64_t rows = z->m - row0 < h ? z->m - row0 : h;
         float* __restrict__ dst = z->C + jc + row0 * ldc;
         constexpr int kStride = BandCut<V>::kMaxH + 1;
-        typedef float vec __attribute__((ext_vector_type(V)));
+        typedef float vec __attribute__((ext_vector_type(V), aligned(4)));         // rows of C are aligned to 4 bytes only
 #pragma unroll
         for (int r = 0; r < BandCut<V>::kMaxH; ++r) {
             if (r < rows) {

@@ -36,6 +36,7 @@ namespace gcoo {
 
 constexpr int kRowsThreads = 256;
 typedef float rows_f32x4 __attribute__((ext_vector_type(4)));
+typedef float rows_f32x4_any __attribute__((ext_vector_type(4), aligned(4)));    // in C, whose rows are aligned to 4 bytes only where the tiles are not moved
 typedef uint32_t rows_u32x4 __attribute__((ext_vector_type(4)));
 
 // Pair i of a batch of 16, in every lane of the slot.  LPR >= 16: lane i of every row of 16 lanes holds pair i; below,
@@ -207,7 +208,7 @@ struct RowsTile {
         float* dst = a.C + (int64_t)r * a.ldc + pl.jc;
         if (pl.first == 0 && pl.last >= 4) {
             rows_f32x4 o = {acc.x[0], acc.x[1], acc.x[2], acc.x[3]};
-            __builtin_nontemporal_store(o, reinterpret_cast<rows_f32x4*>(dst));
+            __builtin_nontemporal_store(o, reinterpret_cast<rows_f32x4_any*>(dst));
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u)

@@ -166,3 +166,13 @@ def test_arrivals_are_between_waits_and_what_they_hand_over_has_agent_scope(coun
         assert planted != body
         arrivals, problems = isa_check.check_arrivals(head + planted + tail, K)
         assert problems and any(what in x for x in problems), (what, problems)
+
+
+@pytest.mark.parametrize("stem", ["spdm_rows", "spdm_band", "spdm_tile"])
+def test_vector_stores_promise_the_alignment_that_c_has(stem):
+    """A caller's C is aligned to 4 bytes, and so are its rows: a store that promises the compiler more may become any instruction that needs more."""
+    out = os.path.join(tempfile.mkdtemp(prefix="gcoo_isa_"), "out.ll")
+    subprocess.check_call(["hipcc", *build.FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "-emit-llvm",
+                           "--cuda-device-only", "-o", out, os.path.join(CSRC, f"{stem}.hip")], stderr=subprocess.DEVNULL)
+    stores = re.findall(r"store <[24] x float> [^\n]*addrspace\(1\)[^\n]* align (\d+)", open(out).read())
+    assert stores and set(stores) == {"4"}, set(stores)
