@@ -260,14 +260,17 @@ def gcoo_from_csr(m: int, k: int, row_ptr, col_idx, vals, p: int, device="cuda:0
     known_nnz (device input only): the caller vouches that row_ptr[m] == len(col_idx); the
     conversion then reads nothing back and never waits for the device (gcoo_from_csr_device)."""
     on_dev = isinstance(row_ptr, torch.Tensor)
+    if not on_dev:
+        device = torch.device(device)
+        assert device.type == "cuda"
     if stream is None:
         calls, got = _calls or _module(), None
         if on_dev:
             if row_ptr.is_cuda:
                 got = calls.from_csr_device(row_ptr, col_idx, vals, m, k, p, _raw_stream(row_ptr.get_device()), known_nnz)
         else:
-            index, current = torch.device(device).index, torch.cuda.current_device()
-            if index is None or index == current:
+            current = torch.cuda.current_device()
+            if device.index is None or device.index == current:
                 got = calls.from_csr_host(row_ptr, col_idx, vals, m, k, p, _raw_stream(current))
         if got is not None:
             return _matrix(got, (m, k), "gcoo_from_csr_device" if on_dev and known_nnz else "gcoo_from_csr")
@@ -283,7 +286,6 @@ def gcoo_from_csr(m: int, k: int, row_ptr, col_idx, vals, p: int, device="cuda:0
         vals = np.ascontiguousarray(vals, dtype=np.float32)
         nnz = int(col_idx.shape[0])
         ptrs = (row_ptr.ctypes.data, col_idx.ctypes.data, vals.ctypes.data)
-        device = torch.device(device)
         index = torch.cuda.current_device() if device.index is None else device.index
     L = lib()
     need = L.gcoo_device_bytes(m, k, nnz, p)

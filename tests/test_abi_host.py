@@ -129,6 +129,13 @@ def test_newer_entry_points_reject_bad_arguments_on_the_host(L):
     assert Lb.gcoo_csr_spmm_baseline(0, 2, fake, fake, fake, fake, 4, 4, None, 4, None) == 0                     # nothing to do
 
 
+def test_a_host_matrix_is_converted_for_a_gpu_only():
+    rp, ci, va = np.array([0, 1, 2], np.int32), np.array([0, 1], np.int32), np.ones(2, np.float32)
+    for device in ("cpu", "meta"):
+        with pytest.raises(AssertionError):
+            binding.gcoo_from_csr(2, 2, rp, ci, va, 32, device=device)
+
+
 def _share_height(m, N):
     """The header's rule for the workgroup-shared kernel: the p in 24..48 that minimises
     ceil(workgroups / 256) x (p + 24), the taller one on a tie."""
