@@ -1,5 +1,5 @@
 """Binding of include/gcoo.h: argument marshalling only, by ctypes, and for the calls of every matrix and product by the
-extension module _calls (csrc_python/calls.cpp) where the arguments are as it expects them.
+extension module _calls (csrc_python/calls.cpp) where that is built and the arguments are as it expects them.
 
 Every step of the path (conversion to GCOO and the product) runs in the HIP kernels of
 libgcoo.so.  torch is used for device memory and for the current stream, nothing else.  If
@@ -10,6 +10,7 @@ from __future__ import annotations
 import contextlib
 import ctypes as C
 import os
+import warnings
 
 import numpy as np
 import torch
@@ -37,7 +38,7 @@ SYMBOLS = ["gcoo_default_p", "gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_cs
 BASELINE_SYMBOLS = ["gcoo_csr_spmm_baseline"]
 
 _lib = None
-_calls = None              # the extension module, there as soon as lib() has been called
+_calls = None              # the extension module, or what stands for it: there as soon as lib() has been called
 _baseline_lib = None
 
 
@@ -51,16 +52,24 @@ class GcooError(RuntimeError):
         self.status = status
 
 
+class _ByCtypes:
+    """In the place of an extension module that is not there: serves no call, so that all of them go by ctypes."""
+
+    @staticmethod
+    def free(handle):
+        lib().gcoo_free(handle)
+
+    from_csr_device = from_csr_host = from_csr_device_static = from_dense = spdm = staticmethod(lambda *args: None)
+
+
 def lib():
     """Load libgcoo.so (built in-tree by paper_2005_14469_amd/build.py)."""
     global _lib, _calls
     if _lib is None:
-        for path in (LIB_PATH, CALLS_PATH):
-            if not os.path.exists(path):
-                raise FileNotFoundError(
-                    f"{path} is missing: build it with `python -m paper_2005_14469_amd.build` "
-                    "(there is no CPU fallback)")
-        from . import _calls as calls
+        if not os.path.exists(LIB_PATH):
+            raise FileNotFoundError(
+                f"{LIB_PATH} is missing: build it with `python -m paper_2005_14469_amd.build` "
+                "(there is no CPU fallback)")
         L = C.CDLL(LIB_PATH)
         i64, i32, vp, sz = C.c_int64, C.c_int32, C.c_void_p, C.c_size_t
         L.gcoo_device_bytes.restype = sz
@@ -107,11 +116,16 @@ def lib():
         L.gcoo_strerror.argtypes = [C.c_int]
         L.gcoo_last_hip_error.restype = C.c_char_p
         L.gcoo_last_hip_error.argtypes = []
-        calls.bind(*(C.cast(getattr(L, name), vp).value for name in
-                      ("gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_csr_device", "gcoo_from_csr_device_static", "gcoo_dense_count_bytes", "gcoo_dense_count",
-                       "gcoo_from_dense_counted", "gcoo_spdm_variant", "gcoo_free")))
+        calls = _ByCtypes
+        if os.path.exists(CALLS_PATH):
+            from . import _calls as calls
+            calls.bind(*(C.cast(getattr(L, name), vp).value for name in
+                          ("gcoo_device_bytes", "gcoo_from_csr", "gcoo_from_csr_device", "gcoo_from_csr_device_static", "gcoo_dense_count_bytes", "gcoo_dense_count",
+                           "gcoo_from_dense_counted", "gcoo_spdm_variant", "gcoo_free")))
         _calls = calls
         _lib = L
+        if calls is _ByCtypes:
+            warnings.warn(f"{CALLS_PATH} is missing: all calls go by ctypes, with the same results (`python -m paper_2005_14469_amd.build` builds it)", RuntimeWarning, stacklevel=2)
     return _lib
 
 

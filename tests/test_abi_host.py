@@ -136,6 +136,23 @@ def test_a_host_matrix_is_converted_for_a_gpu_only():
             binding.gcoo_from_csr(2, 2, rp, ci, va, 32, device=device)
 
 
+def test_the_library_serves_without_the_extension_module(monkeypatch):
+    """All calls go by ctypes then; what stands for the module has all that it has."""
+    binding.lib()
+    module = binding._calls
+    assert module.__file__ == binding.CALLS_PATH
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setattr(binding, "CALLS_PATH", binding.CALLS_PATH + ".missing")
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert binding.gcoo_default_p(256, 256, 6000, 256) == 32
+    assert binding._calls is not module
+    for name in ("from_csr_device", "from_csr_host", "from_csr_device_static", "from_dense", "spdm"):
+        assert callable(getattr(module, name)) and getattr(binding._calls, name)(1, 2, 3) is None
+    assert {x for x in dir(module) if x[0] != "_"} - {x for x in dir(binding._calls) if x[0] != "_"} == {"bind"}
+    binding.GcooMatrix(0, None).free()                     # (nothing to give back)
+
+
 def _share_height(m, N):
     """The header's rule for the workgroup-shared kernel: the p in 24..48 that minimises
     ceil(workgroups / 256) x (p + 24), the taller one on a tie."""
