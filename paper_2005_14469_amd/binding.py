@@ -179,7 +179,7 @@ class GcooMatrix:
     """Owner of one handle and of the torch buffer behind it."""
 
     def __init__(self, handle, buf: torch.Tensor):
-        self._h = handle.value if isinstance(handle, C.c_void_p) else handle
+        self._h = handle.value if isinstance(handle, C.c_void_p) else handle          # the address: what the extension module takes
         self.buf = buf
         self._mk = None
 
@@ -190,11 +190,15 @@ class GcooMatrix:
             self._mk = (i["m"], i["k"])
         return self._mk
 
-    @property
-    def handle(self):
+    def _address(self) -> int:
         if self._h is None:
             raise ValueError("handle already freed")
         return self._h
+
+    @property
+    def handle(self) -> C.c_void_p:
+        """For a call of the C ABI: a pointer also for a function of which ctypes has not been told the types."""
+        return C.c_void_p(self._address())
 
     def info(self):
         m, k, nnz, g = C.c_int64(), C.c_int64(), C.c_int64(), C.c_int64()
@@ -391,7 +395,7 @@ def gcoo_spdm(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor | None = None,
     """C = A x B on the current stream.  B: [k, N] fp32 device tensor with unit column stride."""
     if stream is None and B.is_cuda:
         m, k = A._mk or A.shape
-        got = (_calls or _module()).spdm(A._h or A.handle, m, k, B, C_out, _raw_stream(B.get_device()), variant)
+        got = (_calls or _module()).spdm(A._h or A._address(), m, k, B, C_out, _raw_stream(B.get_device()), variant)
         if got is not None:
             if type(got) is int:
                 raise GcooError(got, "gcoo_spdm")
@@ -413,7 +417,7 @@ def gcoo_spdm(A: GcooMatrix, B: torch.Tensor, C_out: torch.Tensor | None = None,
     if d != torch.cuda.current_device():
         with torch.cuda.device(d):
             return gcoo_spdm(A, B, C_out, variant, stream)
-    handle = A._h or A.handle
+    handle = A._h or A._address()
     if stream is None:
         sp = _raw_stream(d)
     else:

@@ -153,6 +153,17 @@ def test_the_library_serves_without_the_extension_module(monkeypatch):
     binding.GcooMatrix(0, None).free()                     # (nothing to give back)
 
 
+def test_the_handle_is_a_pointer():
+    """Also for a function of which ctypes has not been told the types: it would pass a number as 32 bits."""
+    address = 0x7f1234567890
+    for given in (address, C.c_void_p(address)):
+        A = binding.GcooMatrix(given, None)
+        assert type(A.handle) is C.c_void_p and A.handle.value == address
+        A._h = None                                        # (there is nothing behind it)
+        with pytest.raises(ValueError):
+            A.handle
+
+
 def _share_height(m, N):
     """The header's rule for the workgroup-shared kernel: the p in 24..48 that minimises
     ceil(workgroups / 256) x (p + 24), the taller one on a tie."""
