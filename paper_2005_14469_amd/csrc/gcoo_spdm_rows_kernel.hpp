@@ -50,7 +50,17 @@ __device__ __forceinline__ uint32_t rows_bcast(const uint32_t (&x)[LPR >= 16 ? 1
         return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[I / 4], (I % 4) * 0x55, 0xf, 0xf, true);       // quad_perm:[i,i,i,i]
 }
 
-struct RowsAcc { float x[4]; };
+// The sum of a row in a lane's four columns, in SUMS parts.
+template <int SUMS>
+struct RowsAcc {
+    float x[SUMS][4] = {};
+    __device__ __forceinline__ float total(int u) const
+    {
+        static_assert(SUMS == 1 || SUMS == 2, "");
+        if constexpr (SUMS == 2) return x[0][u] + x[1][u];
+        else return x[0][u];
+    }
+};
 
 // The offset of an entry past the end of its row: no descriptor reaches that far, and a lane's place in the tile (below 2 KB) added to it
 // stays below 2^32.  Whoever launches rows_item without WIDE keeps B below kRowsMaxBytes.
@@ -77,23 +87,35 @@ __device__ __forceinline__ void rows_load(const uint32_t (&off)[LPR >= 16 ? 1 : 
         rows_load<LPR, FROM, CNT, I + 1, WIDE>(off, lane_off, B, b);
     }
 }
-template <int LPR, int FROM, int CNT, int I>
-__device__ __forceinline__ void rows_fma(const uint32_t (&val)[LPR >= 16 ? 1 : 4], const rows_u32x4 (&b)[CNT], RowsAcc& acc)
+// Adds the pairs of a batch to the sums.  A slot that takes a row by itself which SUMS narrower slots would share is as exact as they are: it keeps SUMS sums, each of every SUMS-th entry
+// (KEPT == SUMS), or, where it has not the registers, adds up eight entries by themselves first (KEPT == 1).  Error against 64 bits, 2-norm, by the narrower slots, by one chain in the wider one, and so:
+// 333 x 333, rows of 55, N = 333: 1.01e-7 1.36e-7 0.77e-7; 3706 x 5734, rows of 96, N = 27: 0.81e-7 0.99e-7 0.80e-7; power-law rows, 10992 x 10992, N = 85: 1.94e-7 2.62e-7 1.86e-7; 16283 x 16283,
+// N = 147: 1.92e-7 3.60e-7 1.46e-7.  Time: level over 110 products of uniform rows, 0.1 % more over 40 of power-law rows, N = 64 to 208 (0.8 % by eights also at 32 lanes; four sums at 64 lanes instead
+// of eights: 276 x 276, rows of 22, N = 186: 3.7 4.7 us; 14160 x 14160, rows of 122, N = 134: 74 112).
+template <int LPR, int FROM, int CNT, int I, int SUMS, int KEPT>
+__device__ __forceinline__ void rows_fma(const uint32_t (&val)[LPR >= 16 ? 1 : 4], const rows_u32x4 (&b)[CNT], float (&part)[4], RowsAcc<KEPT>& acc)
 {
     if constexpr (I < CNT) {
+        constexpr bool EIGHTS = KEPT != SUMS;
+        static_assert(!EIGHTS || KEPT == 1, "");
         const float v = __uint_as_float(rows_bcast<LPR, FROM + I>(val));
+        float(&to)[4] = EIGHTS ? part : acc.x[(FROM + I) % KEPT];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc.x[u] = __builtin_fmaf(v, __uint_as_float(b[I][u]), acc.x[u]);
-        rows_fma<LPR, FROM, CNT, I + 1>(val, b, acc);
+        for (int u = 0; u < 4; ++u) to[u] = EIGHTS && I % 8 == 0 ? v * __uint_as_float(b[I][u]) : __builtin_fmaf(v, __uint_as_float(b[I][u]), to[u]);
+        if constexpr (EIGHTS && (I % 8 == 7 || I == CNT - 1))
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc.x[0][u] += part[u];
+        rows_fma<LPR, FROM, CNT, I + 1, SUMS>(val, b, part, acc);
     }
 }
-template <int LPR, int FROM, int CNT, bool WIDE>
+template <int LPR, int FROM, int CNT, bool WIDE, int SUMS, int KEPT>
 __device__ __forceinline__ void rows_batch(const uint32_t (&off)[LPR >= 16 ? 1 : 4], const uint32_t (&val)[LPR >= 16 ? 1 : 4],
-                                           uint32_t lane_off, const RowsB& B, RowsAcc& acc)
+                                           uint32_t lane_off, const RowsB& B, RowsAcc<KEPT>& acc)
 {
     rows_u32x4 b[CNT];
     rows_load<LPR, FROM, CNT, 0, WIDE>(off, lane_off, B, b);
-    rows_fma<LPR, FROM, CNT, 0>(val, b, acc);
+    float part[4];
+    rows_fma<LPR, FROM, CNT, 0, SUMS>(val, b, part, acc);
 }
 
 // One (column, value) pair per lane (and register) of a batch of 16 entries: columns beyond the last row of B are brought inside (a
@@ -130,22 +152,22 @@ struct RowsBatch {
 
 // The entries from FROM on of the batch, CNT at the most, in steps of two: as many as the fullest slot of the wave has (a load past a row's end returns at once but
 // holds the address path as long as any other).
-template <int LPR, int FROM, int CNT, bool WIDE>
-__device__ __forceinline__ void rows_pick(int32_t left, const RowsBatch<LPR>& now, uint32_t lane_off, const RowsB& B, RowsAcc& acc)
+template <int LPR, int FROM, int CNT, bool WIDE, int SUMS, int KEPT>
+__device__ __forceinline__ void rows_pick(int32_t left, const RowsBatch<LPR>& now, uint32_t lane_off, const RowsB& B, RowsAcc<KEPT>& acc)
 {
     if (__any(left > FROM + CNT - 2)) {
-        rows_batch<LPR, FROM, CNT, WIDE>(now.c, now.v, lane_off, B, acc);
+        rows_batch<LPR, FROM, CNT, WIDE, SUMS>(now.c, now.v, lane_off, B, acc);
     } else {
-        if constexpr (CNT > 2) rows_pick<LPR, FROM, CNT - 2, WIDE>(left, now, lane_off, B, acc);
+        if constexpr (CNT > 2) rows_pick<LPR, FROM, CNT - 2, WIDE, SUMS>(left, now, lane_off, B, acc);
     }
 }
 
 // Adds the entries [base, end) of the slot's row (every lane of the wave calls it; the slots may have different ranges).
 // `next` holds the first batch already; on return it holds the batch [more, more_end), requested in front of the loads of
 // the last batch.
-template <int LPR, bool WIDE, int AHEAD>
+template <int LPR, bool WIDE, int AHEAD, int SUMS, int KEPT>
 __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end,
-                                             uint32_t kmax, uint32_t ldb4, uint32_t lane_off, const RowsB& B, int lane, RowsAcc& acc)
+                                             uint32_t kmax, uint32_t ldb4, uint32_t lane_off, const RowsB& B, int lane, RowsAcc<KEPT>& acc)
 {
     while (true) {
         RowsBatch<LPR> now = next;
@@ -154,16 +176,17 @@ __device__ __forceinline__ void rows_entries(const RowsArgs& a, RowsBatch<LPR>& 
         base += 16;
         const bool last = !__any(base < end);
         next.request(a, last ? more : base, last ? more_end : end, lane);
-        rows_pick<LPR, 0, AHEAD, WIDE>(left, now, lane_off, B, acc);
+        rows_pick<LPR, 0, AHEAD, WIDE, SUMS>(left, now, lane_off, B, acc);
         if constexpr (AHEAD < 16)
-            if (__any(left > AHEAD)) rows_pick<LPR, AHEAD, 16 - AHEAD, WIDE>(left, now, lane_off, B, acc);
+            if (__any(left > AHEAD)) rows_pick<LPR, AHEAD, 16 - AHEAD, WIDE, SUMS>(left, now, lane_off, B, acc);
         if (last) return;
     }
 }
 
 // What a lane needs of a tile of 4 x LPR columns.  AHEAD: loads of rows of B in flight.
-template <int LPR, bool WIDE, int AHEAD>
+template <int LPR, bool WIDE, int AHEAD, int SUMS>
 struct RowsTile {
+    typedef RowsAcc<AHEAD == 16 && LPR <= 32 ? SUMS : 1> Acc;
     const RowsArgs& a;
     int lane, slot, sl;
     int32_t N, jb, lane_j;
@@ -203,41 +226,45 @@ struct RowsTile {
         pl.last = want - pl.jc + 4;
         return pl;
     }
-    __device__ __forceinline__ void store(int32_t r, const Place& pl, const RowsAcc& acc) const
+    template <int KEPT>
+    __device__ __forceinline__ void store(int32_t r, const Place& pl, const RowsAcc<KEPT>& acc) const
     {
         float* dst = a.C + (int64_t)r * a.ldc + pl.jc;
         if (pl.first == 0 && pl.last >= 4) {
-            rows_f32x4 o = {acc.x[0], acc.x[1], acc.x[2], acc.x[3]};
+            rows_f32x4 o = {acc.total(0), acc.total(1), acc.total(2), acc.total(3)};
             __builtin_nontemporal_store(o, reinterpret_cast<rows_f32x4_any*>(dst));
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (u >= pl.first && u < pl.last) __builtin_nontemporal_store(acc.x[u], dst + u);
+                if (u >= pl.first && u < pl.last) __builtin_nontemporal_store(acc.total(u), dst + u);
         }
     }
-    __device__ __forceinline__ void entries(RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end, const Place& pl, RowsAcc& acc) const
+    __device__ __forceinline__ void entries(RowsBatch<LPR>& next, int32_t base, int32_t end, int32_t more, int32_t more_end, const Place& pl, Acc& acc) const
     {
-        rows_entries<LPR, WIDE, AHEAD>(a, next, base, end, more, more_end, kmax, ldb4, (uint32_t)(pl.jc - jb) * 4u, B, lane, acc);
+        rows_entries<LPR, WIDE, AHEAD, SUMS>(a, next, base, end, more, more_end, kmax, ldb4, (uint32_t)(pl.jc - jb) * 4u, B, lane, acc);
     }
     // The entries [b, e) of row r, equal stretches of them for the slots of the wave; the sums of the slots added up in a fixed tree.
-    __device__ __forceinline__ RowsAcc shared_row(const Place& pl, int32_t b, int32_t e) const
+    __device__ __forceinline__ RowsAcc<1> shared_row(const Place& pl, int32_t b, int32_t e) const
     {
         RowsBatch<LPR> mine;
         mine.request(a, b, e, lane);
-        RowsAcc sum = {{0.0f, 0.0f, 0.0f, 0.0f}};
-        entries(mine, b, e, 0, 0, pl, sum);
+        Acc all;
+        entries(mine, b, e, 0, 0, pl, all);
+        RowsAcc<1> sum;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum.x[0][u] = all.total(u);
 #pragma unroll
         for (int d = LPR; d < 64; d <<= 1)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) sum.x[u] += __shfl_xor(sum.x[u], d, 64);
+            for (int u = 0; u < 4; ++u) sum.x[0][u] += __shfl_xor(sum.x[0][u], d, 64);
         return sum;
     }
 };
 
 // The long rows `turn`, `turn` + step, ..., the `n_front` longest first, all slots of a workgroup of WAVES waves on each.  `part`: WAVES stretches of a tile's columns in LDS.  PLACES: the long rows are
 // in places, not counted (RowsArgs), and place `turn` holds `at_turn`.
-template <int LPR, bool WIDE, int AHEAD, int WAVES, bool PLACES>
-__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t n_front, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
+template <int LPR, bool WIDE, int AHEAD, int SUMS, int WAVES, bool PLACES>
+__device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD, SUMS>& T, int32_t n_front, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
 {
     constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES;
     const RowsArgs& a = T.a;
@@ -248,16 +275,16 @@ __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>&
         const int32_t lb = a.row_ptr[lr], le = a.row_ptr[lr + 1];
         if (PLACES && le - lb <= a.long_row) continue;
         const int32_t each = (le - lb + SLOTS - 1) / SLOTS, b = lb + (wv * SPW + T.slot) * each, e = b + each < le ? b + each : le;
-        const typename RowsTile<LPR, WIDE, AHEAD>::Place lpl = T.place(lr);
-        RowsAcc sum = T.shared_row(lpl, b, e);
+        const typename RowsTile<LPR, WIDE, AHEAD, SUMS>::Place lpl = T.place(lr);
+        RowsAcc<1> sum = T.shared_row(lpl, b, e);
         if (T.slot == 0)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) part[wv][T.sl * 4 + u] = sum.x[u];
+            for (int u = 0; u < 4; ++u) part[wv][T.sl * 4 + u] = sum.x[0][u];
         __syncthreads();
         if (wv == 0 && T.slot == 0) {
             for (int s = 1; s < WAVES; ++s)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) sum.x[u] += part[s][T.sl * 4 + u];
+                for (int u = 0; u < 4; ++u) sum.x[0][u] += part[s][T.sl * 4 + u];
             T.store(lr, lpl, sum);
         }
         __syncthreads();
@@ -266,8 +293,8 @@ __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD>&
 
 // The wave's rows [w0, w0 + wrows), a slot on each; lane i holds in `start` where row w0 + i begins, i = 0 .. wrows.  Rows of more than `long_row` entries, which is no less
 // than `wave_row`, are left out.
-template <int LPR, bool WIDE, int AHEAD>
-__device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD>& T, int32_t w0, int32_t wrows, int32_t start, int32_t wave_row, int32_t long_row)
+template <int LPR, bool WIDE, int AHEAD, int SUMS>
+__device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD, SUMS>& T, int32_t w0, int32_t wrows, int32_t start, int32_t wave_row, int32_t long_row)
 {
     constexpr int SPW = 64 / LPR;
     const RowsArgs& a = T.a;
@@ -294,8 +321,8 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD>& T
         int32_t beg2, end2;
         bounds(i + SPW + T.slot, &beg2, &end2);
         const bool whole2 = shared(end2 - beg2);
-        const typename RowsTile<LPR, WIDE, AHEAD>::Place pl = T.place(r);
-        RowsAcc acc = {{0.0f, 0.0f, 0.0f, 0.0f}};
+        const typename RowsTile<LPR, WIDE, AHEAD, SUMS>::Place pl = T.place(r);
+        typename RowsTile<LPR, WIDE, AHEAD, SUMS>::Acc acc;
         T.entries(next, beg, whole ? beg : end, beg2, whole2 ? beg2 : end2, pl, acc);
         if (i + T.slot < wrows && !whole) T.store(r, pl, acc);
         uint64_t todo = __ballot(whole && T.sl == 0);
@@ -306,8 +333,8 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD>& T
             const int32_t lr = w0 + i + s, n = le - lb;
             if (n > long_row) continue;
             const int32_t each = (n + SPW - 1) / SPW, b = lb + T.slot * each, e = b + each < le ? b + each : le;
-            const typename RowsTile<LPR, WIDE, AHEAD>::Place lpl = T.place(lr);
-            const RowsAcc sum = T.shared_row(lpl, b, e);
+            const typename RowsTile<LPR, WIDE, AHEAD, SUMS>::Place lpl = T.place(lr);
+            const RowsAcc<1> sum = T.shared_row(lpl, b, e);
             if (T.slot == 0) T.store(lr, lpl, sum);
         }
         beg = beg2;
@@ -318,7 +345,7 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD>& T
 
 // Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
 // places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
-template <int LPR, bool WIDE, int AHEAD, int WAVES, bool PLACES>
+template <int LPR, bool WIDE, int AHEAD, int SUMS, int WAVES, bool PLACES>
 __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
 {
     // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
@@ -336,7 +363,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
         tile = eights * 8 + i / row_wgs;
         wg = i - i / row_wgs * row_wgs;
     }
-    const RowsTile<LPR, WIDE, AHEAD> T(a, tile);
+    const RowsTile<LPR, WIDE, AHEAD, SUMS> T(a, tile);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t m = (int32_t)a.m, w0 = (wg * WAVES + wv) * rpw;                    // the wave's first row
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
@@ -357,8 +384,8 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
         }
     }
     // (out of the way of matrices without long rows: 12000 x 12000, 0.5 %, N = 64: 12.15 us without the hints, 12.13 so)
-    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, WAVES, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
-    rows_of_wave<LPR, WIDE, AHEAD>(T, w0, wrows, start, wave_row, a.long_row);
+    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, SUMS, WAVES, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
+    rows_of_wave<LPR, WIDE, AHEAD, SUMS>(T, w0, wrows, start, wave_row, a.long_row);
 }
 
 // The whole product of a matrix with uneven rows by the first kRowsAllWgs workgroups of a launch whose workgroups have a compute unit each (gridDim.x is a multiple of 8).  An XCD walks one
@@ -397,7 +424,7 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
     const int32_t eights = tiles / 8, rest = tiles - eights * 8, t = (int32_t)threadIdx.x, threads = (int32_t)blockDim.x;
     // the share [from, to) / parts of a tile
     auto tile_rows = [&](int32_t tile, int64_t from, int64_t to, int64_t parts) {
-        const RowsTile<LPR, false, 16> T(a, tile);
+        const RowsTile<LPR, false, 16, 1> T(a, tile);
         const int32_t r0 = rows_all_cut(a, from, parts, T.lane), r1 = rows_all_cut(a, to, parts, T.lane);
         // its long rows: those of more entries than `limit`, which has room for all of them
         int32_t limit = kRowsPieces * 32, cnt;
@@ -426,18 +453,18 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
             if (q >= pieces) {
                 const int32_t w0 = r0 + (q - pieces) * rpw, wrows = r1 - w0 < rpw ? r1 - w0 : rpw;
                 // (a row above `limit` is taken out of the slots here, whatever `wave_row` is: it has its pieces)
-                rows_of_wave<LPR, false, 16>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row < limit ? wave_row : limit, limit);
+                rows_of_wave<LPR, false, 16, 1>(T, w0, wrows, T.lane <= wrows ? a.row_ptr[w0 + T.lane] : 0, wave_row < limit ? wave_row : limit, limit);
                 continue;
             }
             const int32_t i = q / kRowsPieces, piece = q % kRowsPieces;
             const int32_t r = __builtin_amdgcn_readfirstlane(lds.row[i]), lb = __builtin_amdgcn_readfirstlane(lds.beg[i]), le = __builtin_amdgcn_readfirstlane(lds.end[i]);
             constexpr int kSlots = 64 / LPR * kRowsPieces;
             const int32_t each = (le - lb + kSlots - 1) / kSlots, b = lb + (piece * (64 / LPR) + T.slot) * each, e = b + each < le ? b + each : le;
-            const typename RowsTile<LPR, false, 16>::Place pl = T.place(r);
-            RowsAcc sum = T.shared_row(pl, b, e);
+            const typename RowsTile<LPR, false, 16, 1>::Place pl = T.place(r);
+            RowsAcc<1> sum = T.shared_row(pl, b, e);
             if (T.slot == 0)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) lds.sums[q][T.sl * 4 + u] = sum.x[u];
+                for (int u = 0; u < 4; ++u) lds.sums[q][T.sl * 4 + u] = sum.x[0][u];
             int32_t before = 0;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             if (T.lane == 0) before = atomicAdd(&lds.ended[i], 1);
@@ -446,10 +473,10 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             if (T.slot == 0) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) sum.x[u] = lds.sums[i * kRowsPieces][T.sl * 4 + u];
+                for (int u = 0; u < 4; ++u) sum.x[0][u] = lds.sums[i * kRowsPieces][T.sl * 4 + u];
                 for (int s = 1; s < kRowsPieces; ++s)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) sum.x[u] += lds.sums[i * kRowsPieces + s][T.sl * 4 + u];
+                    for (int u = 0; u < 4; ++u) sum.x[0][u] += lds.sums[i * kRowsPieces + s][T.sl * 4 + u];
                 T.store(r, pl, sum);
             }
         }
@@ -463,11 +490,11 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
         tile_rows(eights * 8 + (int32_t)x, from > x * all ? from - x * all : 0, to < (x + 1) * all ? to - x * all : all, all);
 }
 
-template <int LPR, bool WIDE, int AHEAD, bool PLACES>
+template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
 __global__ __launch_bounds__(kRowsThreads, AHEAD == 16 ? 4 : 8) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
 {
     __shared__ __attribute__((aligned(16))) float part[kRowsThreads / 64][LPR * 4];
-    rows_item<LPR, WIDE, AHEAD, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
+    rows_item<LPR, WIDE, AHEAD, SUMS, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
 }
 
 // B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a

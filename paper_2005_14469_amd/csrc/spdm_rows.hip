@@ -6,7 +6,7 @@ namespace gcoo {
 // Waves of a launch that has one row and 256 columns to each: 8192 are resident at a time.
 static int64_t rows_waves(int64_t m, int64_t N) { return m * ((N + 255) / 256); }
 
-template <int LPR, bool WIDE, int AHEAD>
+template <int LPR, bool WIDE, int AHEAD, int SUMS>
 static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
 {
     constexpr int64_t waves = kRowsThreads / 64, tile = 4 * LPR, spw = 64 / LPR;
@@ -31,7 +31,7 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
     // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them.
     const int64_t wave_row = rpw < spw ? 8 : (2 * mean > 64 ? 2 * mean : 64);
     const bool places = !a.long_count && a.long_room > 0;
-    (places ? spdm_rows<LPR, WIDE, AHEAD, true> : spdm_rows<LPR, WIDE, AHEAD, false>)<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(
+    (places ? spdm_rows<LPR, WIDE, AHEAD, SUMS, true> : spdm_rows<LPR, WIDE, AHEAD, SUMS, false>)<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(
         a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw, (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row));
     return hipGetLastError();
 }
@@ -39,12 +39,13 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
 // A wave with eight rows of B in flight in place of sixteen needs half of the registers, so that twice as many waves are resident: faster where a row has not many more entries
 // than that (us, sixteen and eight: 12001 x 12001, rows of 6: 437 426; 7999 x 7999, of 8: 187 164; 10643 x 10643, of 1.2, N = 8867: 157 125; over 318 products 12 to 20 % less below 6 entries
 // per row, 2 to 9 % from 6 to 16, level from 16 to 30, 2 to 5 % more above, 13 % more for power-law rows of 49).
-template <int LPR>
+// SUMS: of a row in a slot (rows_fma()): as many as there are slots of 16 lanes in one, and two where 16 lanes serve up to 32 columns, for which eight are enough.
+template <int LPR, int SUMS = LPR <= 16 ? 1 : LPR / 16>
 static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
 {
     if constexpr (LPR >= 16)
-        if (a.nnz <= 16 * a.m) return launch_rows_ahead<LPR, false, 8>(a, s);
-    return launch_rows_ahead<LPR, false, 16>(a, s);
+        if (a.nnz <= 16 * a.m) return launch_rows_ahead<LPR, false, 8, SUMS>(a, s);
+    return launch_rows_ahead<LPR, false, 16, SUMS>(a, s);
 }
 
 hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
@@ -59,10 +60,11 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         return hipGetLastError();
     }
     // a B of more than 4 GB is beyond the offsets of a buffer descriptor
-    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows_ahead<16, true, 16>(a, s);
+    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows_ahead<16, true, 16, 1>(a, s);
     // Up to 32 columns: four or eight lanes to a row where that leaves enough workgroups, sixteen else, those without a column of their own along (kernel alone, us, 8 lanes and 16:
     // 6124 x 6124, rows of 19, N = 28: 7.4 4.9; 8788 x 9414, of 18, N = 27: 5.6 6.2).
     if (a.N <= 32 && a.m >= 7000) return a.N <= 16 && a.m >= 16384 ? launch_rows<4>(a, s) : launch_rows<8>(a, s);
+    if (a.N <= 32) return launch_rows<16, 2>(a, s);
     // 64, 128 or 256 columns per tile.  Wider tiles are fewer requests for the same bytes and, where rows of B begin inside a 128-byte line, fewer lines per byte (3 for
     // 256 bytes, 5 for 512, 9 for 1024); narrower ones stay in an XCD's L2 (4 MB) at more rows of B, and have more slots to a wave for uneven rows, of which the host knows nothing.
     // From the times of all three in 960 products with rows of B inside a line and 800 with rows on lines, 300 to 20000 rows and columns, rows of 1 to 250 entries and power-law rows (us,

@@ -363,6 +363,22 @@ def tiles(host):
         assert host.spdm(h, N, (1 << 32) // (4 * k) + N, AUTO) == OK and "spdm_rows_tile" not in host.launches()[0], (m, k, N)
 
 
+# ---- the widths of a slot ------------------------------------------------------------------------------
+
+# (lanes of a slot, rows of B in flight, sums of a row: the instance of the row-by-row kernel; m, k, N, entries of every row): what tests/test_gpu_rows.py compares bit by bit
+SUMS = [(64, 16, 4, 333, 333, 333, 21), (64, 8, 4, 422, 422, 285, 15), (32, 16, 2, 9000, 9000, 85, 49), (32, 8, 2, 9000, 9000, 85, 13), (16, 16, 2, 5000, 5700, 27, 45), (8, 16, 1, 9000, 5700, 13, 45),
+        (16, 16, 1, 9000, 9000, 64, 49)]
+
+
+def sums(host):
+    for lanes, ahead, parts, m, k, N, per_row in SUMS:
+        h = host.matrix(m, k, m * per_row, 32)
+        host.log()
+        assert host.spdm(h, N, N) == OK
+        (name,) = host.launches()
+        assert f"spdm_rowsILi{lanes}ELb0ELi{ahead}ELi{parts}E" in name, (m, k, N, per_row, name)
+
+
 # ---- the cuts of the band schedule -------------------------------------------------------------------
 
 # (m, k, N, entries, variant): what tests/test_gpu_band.py multiplies by the wide cut and by the tall one, and by which instance

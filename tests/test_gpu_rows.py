@@ -8,6 +8,7 @@ torch = pytest.importorskip("torch")
 
 from oracle import gcoo_oracle as orc
 from paper_2005_14469_amd import binding, workloads
+from tests.host_calls import SUMS
 
 pytestmark = pytest.mark.gpu
 
@@ -192,3 +193,37 @@ def test_longest_rows_from_the_front_of_the_list(lens, dense):
     """Rows just below and above the lengths from which a row is listed, and from the front: one class alone and both, the list filled from both sides."""
     print(f"rows: longest first lens={lens} dense={dense}", flush=True)
     _check(_rows_of_lengths(np.resize(lens + [3] * 20, 301), 9000, 67, seed=len(lens)), 32, dense=dense)
+
+
+def _added_up(terms, sums, eights):
+    """The sum over the entries (axis 1) in the order that a slot with a row to itself has: in one chain; in `sums` chains of every sums-th entry; eight by themselves first."""
+    if eights:
+        total = np.zeros_like(terms[:, 0])
+        for at in range(0, terms.shape[1], 8):
+            part = terms[:, at].copy()
+            for i in range(at + 1, min(at + 8, terms.shape[1])):
+                part += terms[:, i]
+            total += part
+        return total
+    chains = []
+    for s in range(sums):
+        chains.append(np.zeros_like(terms[:, 0]))
+        for i in range(s, terms.shape[1], sums):
+            chains[s] += terms[:, i]
+    return chains[0] if sums == 1 else chains[0] + chains[1]
+
+
+@pytest.mark.parametrize("lanes,ahead,sums,m,k,N,per_row", SUMS)
+def test_a_row_that_narrower_slots_would_share_is_no_less_exact(lanes, ahead, sums, m, k, N, per_row):
+    """Every product is exact, so the bits of a sum show the order of it.  (Which instance serves a shape: tests/test_host_calls.py.)"""
+    print(f"rows: {sums} sums, {lanes} lanes, N={N}", flush=True)
+    rng = np.random.default_rng(N)
+    w = _rows_of_lengths([per_row] * m, k, N, seed=N)
+    w.B[:] = 2.0 ** rng.integers(-3, 4, (k, N)) * rng.choice([-1.0, 1.0], (k, N))
+    A = binding.gcoo_from_csr(m, k, *[torch.from_numpy(x).to(DEV) for x in (w.row_ptr, w.col_idx, w.vals)], 32, known_nnz=True)
+    C = binding.gcoo_spdm(A, torch.from_numpy(w.B).to(DEV)).cpu().numpy()
+    terms = w.vals.reshape(m, per_row, 1) * w.B[w.col_idx.reshape(m, per_row)]
+    assert np.array_equal(C, _added_up(terms, sums, eights=sums > 1 and (lanes == 64 or ahead == 8)))
+    if sums > 1 and per_row > 16:
+        exact = terms.sum(1, dtype=np.float64)
+        assert np.linalg.norm(C - exact) < 0.85 * np.linalg.norm(_added_up(terms, 1, False) - exact)
