@@ -17,14 +17,15 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
     // Rows per wave: one per slot, so that a launch has many short workgroups, and two or four per slot where rows are short, the loads of one behind those of the one before
     // (us, 1, 2, 4, 8 and 16 rows per wave: 7999 x 7999, rows of 8, 64 columns per tile - 231 169 177 229, 128 columns - 164 176 211 261; 12001 x 12001, of 6, 128 columns
     // - 426 426 448 482; 5000 x 5000, of 2, N = 5001, 256 columns - 42.6 43.2 46.1 46.3).  Not where all waves are resident at once: there a row more is a trip to memory more (322 x 295, of 2,
-    // N = 295, kernel alone, 2 and 4 rows: 3.2 3.9).  A launch that cannot
-    // fill the chip has fewer rows per wave, each on all slots of it.
+    // N = 295, kernel alone, 2 and 4 rows: 3.2 3.9).  A launch of fewer than 192
+    // workgroups has a row per wave, on all slots of it.  (Rows of more than 12 entries, a row and four rows per wave: 0.83 to 0.98 of the time below 125 workgroups, 0.94 to 1.02 up to 200, 1 to 1.05 up to
+    // 256; two rows per wave, each on half of the slots, never less than the better of the two.  By eight lanes, 8123 x 11104, rows of 13, N = 22: eight rows per wave 5.3 us, four 7.3.)
     int64_t rpw = spw;
     const bool many = rows_waves(a.m, a.N) > 8192;
     if (many && mean < 6) rpw = LPR == 32 ? 4 : (LPR == 64 ? 2 : spw);
     else if (many && mean < 10) rpw = LPR == 64 ? 2 : spw;
     else if (mean >= 120 && groups(rpw) * tiles < 4096) rpw = spw > 4 ? spw / 4 : 1;         // (9072 x 9072, rows of 143, N = 34: 19.0 16.3; 17015, of 279, N = 20: 51.5 40.6)
-    else if (mean > 12) while (rpw > 1 && groups(rpw) * tiles < 256) rpw /= 2;
+    else if (mean > 12 && groups(rpw) * tiles < 192) rpw = 1;
     const int64_t row_wgs = groups(rpw);
     const int64_t rest = tiles % 8 * row_wgs, grid = tiles / 8 * 8 * row_wgs + (rest + 7) / 8 * 8;
     if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;

@@ -379,6 +379,21 @@ def sums(host):
         assert f"spdm_rowsILi{lanes}ELb0ELi{ahead}ELi{parts}E" in name, (m, k, N, per_row, name)
 
 
+# (m, k, N, entries of every row; lanes of a slot, workgroups)
+WIDTHS = [(8123, 11104, 22, 13, 8, 254), (7000, 7000, 22, 30, 8, 219), (3200, 3000, 40, 20, 16, 200), (3100, 3000, 40, 20, 16, 194), (3000, 3000, 40, 20, 16, 750), (700, 600, 300, 11, 64, 350)]
+
+
+def widths(host):
+    """Which instance of the row-by-row kernel a launch takes, and how many rows a wave has."""
+    for m, k, N, per_row, lanes, workgroups in WIDTHS:
+        h = host.matrix(m, k, m * per_row, 32)
+        host.log()
+        assert host.spdm(h, N, N) == OK
+        (line,) = [x for x in host.log() if x.startswith("launch")]
+        got = int(line.split()[2])
+        assert f"spdm_rowsILi{lanes}ELb0E" in line and workgroups <= got < workgroups + 8, (m, k, N, per_row, line)
+
+
 # ---- the cuts of the band schedule -------------------------------------------------------------------
 
 # (m, k, N, entries, variant): what tests/test_gpu_band.py multiplies by the wide cut and by the tall one, and by which instance
