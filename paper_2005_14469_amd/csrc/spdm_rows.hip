@@ -93,8 +93,9 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
             const int64_t from = a.nnz >= 53 * a.m ? 0 : (a.nnz < 25 * a.m ? 11000 : (a.N <= 150 ? 16000 : INT64_MAX));
             if (a.N <= 160 ? a.k >= from : (a.N <= 208 && from == 0 && a.k <= 9100)) return launch_rows<64>(a, s);
         }
-        // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 90)
-        const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
+        // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 64 and 25 to 90; us, 64 and 128 columns:
+        // 6133 x 5725, rows of 108, N = 93: 19.7 14.4; 6470 x 6470, of 98, N = 67: 20.8 15.5; over 40 products of rows of 64 and more, N = 65 to 128, up to 6500 rows of B, 13 % less)
+        const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m || a.nnz >= 64 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
         return one || eight || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
     }
     if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, s);
