@@ -79,7 +79,10 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // From half of those waves on only where the last tile is not mostly empty (three matrices in turn, 64, 128 and 256 columns: 2350 x 2350, of 5, N = 317: 4.7 5.0 5.9; 2176 x 2068, of 5, N = 456: 4.9 5.0 5.5;
     // 4006 x 5846, of 12, N = 302, as the rules below have it and 256: 9.0 11.9; but 1541 x 1249, of 3, N = 466: 4.0 4.1 4.0; one tile, 4106 x 2467, of 25, N = 204: 10.2 8.5).
     const bool full = waves <= 4096 || a.N <= 256 || 256 * 100 * ((a.N + 255) / 256) <= 115 * a.N;
-    if (a.N > 64 && waves <= 8192 && full && (a.nnz < 25 * a.m || a.m < 1000))
+    // Nor for rows of 28 entries and more on less than 600 waves, 700 from 36 on: 64 columns and all slots of a wave on a row take 0.89 to 0.97 of the time for rows of 36 and more, 0.97 for 28 to 36, but 1.00 to 1.07 at 700 to
+    // 1000 waves, and 1.02 and 1.06 for rows of 20 to 28 and of 14 to 20 (300 products, three matrices in turn; us: 221 x 221, rows of 41, N = 235: 4.7 and 4.15; 250 x 377, of 58, N = 250: 5.3 and 4.7).
+    const bool sparse_launch = a.nnz >= 28 * a.m && waves < (a.nnz >= 36 * a.m ? 700 : 600);
+    if (a.N > 64 && waves <= 8192 && full && !sparse_launch && (a.nnz < 25 * a.m || a.m < 1000))
         return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, s) : launch_rows<32>(a, s);
     if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
     // From 897 columns on there are eight tiles of 128 columns, one per XCD (us, 64 and 128 columns: power-law rows, 3611 x 3611, N = 926: 54 43; 4658 x 4658, N = 994: 64 56; 9046 x 9046, N = 895: 136 138;
@@ -89,7 +92,7 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         // the tiles would stay in it (us, 64 and 256 columns: 5699 x 6659, rows of 104, N = 134: 31 23; 8516 x 6585, of 65, N = 157: 28 22; 14161 x 14161, of 74, N = 154: 63 60; 5619 x 6520, of 55, N = 200: 20 17;
         // 12411 x 12959, of 20, N = 131: 17.3 15.2; 19195 x 15201, of 4, N = 148: 9.1 8.3; power-law rows, of 50, 17075 x 17075, N = 150: 89 78, 18289 x 20000, N = 130: 101 79; but 17686 x 17757, N = 151: 90 100, 9627 x 11477, of 84, N = 179: 46 50;
         // power-law rows, 2808 x 3141, N = 131: 17 37; 15071 x 15071, N = 131: 71 78).
-        if (!lines && a.N > 128) {
+        if (!lines && a.N > 128 && !sparse_launch) {
             const int64_t from = a.nnz >= 53 * a.m ? 0 : (a.nnz < 25 * a.m ? 11000 : (a.N <= 150 ? 16000 : INT64_MAX));
             if (a.N <= 160 ? a.k >= from : (a.N <= 208 && from == 0 && a.k <= 9100)) return launch_rows<64>(a, s);
         }

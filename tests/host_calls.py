@@ -381,7 +381,9 @@ def sums(host):
 
 # (m, k, N, entries of every row; lanes of a slot, workgroups)
 WIDTHS = [(8123, 11104, 22, 13, 8, 254), (7000, 7000, 22, 30, 8, 219), (3200, 3000, 40, 20, 16, 200), (3100, 3000, 40, 20, 16, 194), (3000, 3000, 40, 20, 16, 750), (700, 600, 300, 11, 64, 350),
-          (6133, 5725, 93, 108, 32, 767), (6133, 5725, 93, 64, 32, 767), (6133, 5725, 93, 63, 16, 768), (6133, 5725, 96, 108, 16, 768)]
+          (6133, 5725, 93, 108, 32, 767), (6133, 5725, 93, 64, 32, 767), (6133, 5725, 93, 63, 16, 768), (6133, 5725, 96, 108, 16, 768),
+          (299, 300, 300, 28, 16, 375), (299, 300, 300, 27, 64, 150), (300, 300, 300, 28, 64, 150),
+          (205, 300, 205, 74, 16, 208), (349, 300, 300, 36, 16, 440), (350, 300, 300, 36, 64, 175)]
 
 
 def widths(host):
