@@ -383,7 +383,8 @@ def sums(host):
 WIDTHS = [(8123, 11104, 22, 13, 8, 254), (7000, 7000, 22, 30, 8, 219), (3200, 3000, 40, 20, 16, 200), (3100, 3000, 40, 20, 16, 194), (3000, 3000, 40, 20, 16, 750), (700, 600, 300, 11, 64, 350),
           (6133, 5725, 93, 108, 32, 767), (6133, 5725, 93, 64, 32, 767), (6133, 5725, 93, 63, 16, 768), (6133, 5725, 96, 108, 16, 768),
           (299, 300, 300, 28, 16, 375), (299, 300, 300, 27, 64, 150), (300, 300, 300, 28, 64, 150),
-          (205, 300, 205, 74, 16, 208), (349, 300, 300, 36, 16, 440), (350, 300, 300, 36, 64, 175)]
+          (205, 300, 205, 74, 16, 208), (349, 300, 300, 36, 16, 440), (350, 300, 300, 36, 64, 175),
+          (2600, 2500, 256, 5, 64, 650), (2600, 2501, 256, 5, 16, 652), (2600, 2501, 255, 5, 64, 650), (1600, 1500, 320, 5, 64, 800), (1600, 1501, 320, 5, 16, 500), (6000, 6000, 128, 12, 16, 750)]
 
 
 def widths(host):
