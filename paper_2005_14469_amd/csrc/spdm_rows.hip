@@ -102,7 +102,10 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 64 and 25 to 90; us, 64 and 128 columns:
         // 6133 x 5725, rows of 108, N = 93: 19.7 14.4; 6470 x 6470, of 98, N = 67: 20.8 15.5; over 40 products of rows of 64 and more, N = 65 to 128, up to 6500 rows of B, 13 % less)
         const bool one = !lines && a.N > 64 && a.N <= 128 && (a.k >= 6500 || a.nnz < 25 * a.m || a.nnz >= 64 * a.m), eight = a.N >= 700 && a.k <= 6500 && (a.nnz < 25 * a.m || a.nnz >= 90 * a.m);
-        return one || eight || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
+        // and, for rows of 64 entries and more, wherever tiles of 128 columns are no wider together than those of 64 (up to 6500 rows of B: 0.83 to 0.95 of the time in 28 products of N = 209 to 512; where the last tile
+        // would be half empty 0.98 to 1.3 in 40 others; us, 64 and 128 columns: 3218 x 3218, rows of 93, N = 326: 28.4 24.0)
+        const bool even = !lines && a.nnz >= 64 * a.m && a.m >= 1000 && a.k < 6500 && (a.N - 1) % 128 >= 64;
+        return one || eight || even || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
     }
     if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, s);
     // Many rows of B: while all of B stays in the memory-side cache (256 MB), tiles of 64 columns, which stay longest in an XCD's L2; beyond, rows of a few entries take theirs from memory either way, and
