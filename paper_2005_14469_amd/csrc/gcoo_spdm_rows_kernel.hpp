@@ -34,7 +34,7 @@
 
 namespace gcoo {
 
-constexpr int kRowsThreads = 256;
+constexpr int kRowsThreads = 256, kRowsWaves = kRowsThreads / 64;
 typedef float rows_f32x4 __attribute__((ext_vector_type(4)));
 typedef float rows_f32x4_any __attribute__((ext_vector_type(4), aligned(4)));    // in C, whose rows are aligned to 4 bytes only where the tiles are not moved
 typedef uint32_t rows_u32x4 __attribute__((ext_vector_type(4)));
@@ -261,12 +261,12 @@ struct RowsTile {
     }
 };
 
-// The long rows `turn`, `turn` + step, ..., the `n_front` longest first, all slots of a workgroup of WAVES waves on each.  `part`: WAVES stretches of a tile's columns in LDS.  PLACES: the long rows are
+// The long rows `turn`, `turn` + step, ..., the `n_front` longest first, all slots of a workgroup on each.  `part`: a stretch of a tile's columns per wave in LDS.  PLACES: the long rows are
 // in places, not counted (RowsArgs), and place `turn` holds `at_turn`.
-template <int LPR, bool WIDE, int AHEAD, int SUMS, int WAVES, bool PLACES>
+template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
 __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD, SUMS>& T, int32_t n_front, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
 {
-    constexpr int SPW = 64 / LPR, SLOTS = SPW * WAVES;
+    constexpr int SPW = 64 / LPR, SLOTS = SPW * kRowsWaves;
     const RowsArgs& a = T.a;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int32_t x = turn; x < n_long; x += step) {
@@ -282,7 +282,7 @@ __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD, 
             for (int u = 0; u < 4; ++u) part[wv][T.sl * 4 + u] = sum.x[0][u];
         __syncthreads();
         if (wv == 0 && T.slot == 0) {
-            for (int s = 1; s < WAVES; ++s)
+            for (int s = 1; s < kRowsWaves; ++s)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) sum.x[0][u] += part[s][T.sl * 4 + u];
             T.store(lr, lpl, sum);
@@ -343,9 +343,9 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD, SU
     }
 }
 
-// Item `block` of a workgroup of WAVES waves, (tile, wg): rows [wg * WAVES * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
+// Item `block`, (tile, wg): rows [wg * kRowsWaves * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
 // places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
-template <int LPR, bool WIDE, int AHEAD, int SUMS, int WAVES, bool PLACES>
+template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
 __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
 {
     // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
@@ -365,7 +365,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     }
     const RowsTile<LPR, WIDE, AHEAD, SUMS> T(a, tile);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t m = (int32_t)a.m, w0 = (wg * WAVES + wv) * rpw;                    // the wave's first row
+    const int32_t m = (int32_t)a.m, w0 = (wg * kRowsWaves + wv) * rpw;                    // the wave's first row
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
     const int32_t start = T.lane <= wrows && wrows > 0 ? a.row_ptr[w0 + T.lane] : 0;
     const int32_t long_first = PLACES && wg < a.long_room ? a.long_rows[wg] : -1;    // (asked for beside the starts)
@@ -384,7 +384,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
         }
     }
     // (out of the way of matrices without long rows: 12000 x 12000, 0.5 %, N = 64: 12.15 us without the hints, 12.13 so)
-    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, SUMS, WAVES, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
+    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, SUMS, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
     rows_of_wave<LPR, WIDE, AHEAD, SUMS>(T, w0, wrows, start, wave_row, a.long_row);
 }
 
@@ -493,8 +493,8 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
 template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
 __global__ __launch_bounds__(kRowsThreads, AHEAD == 16 ? 4 : 8) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
 {
-    __shared__ __attribute__((aligned(16))) float part[kRowsThreads / 64][LPR * 4];
-    rows_item<LPR, WIDE, AHEAD, SUMS, kRowsThreads / 64, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
+    __shared__ __attribute__((aligned(16))) float part[kRowsWaves][LPR * 4];
+    rows_item<LPR, WIDE, AHEAD, SUMS, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
 }
 
 // B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a
