@@ -82,10 +82,14 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // Nor for rows of 28 entries and more on less than 600 waves, 700 from 36 on: 64 columns and all slots of a wave on a row take 0.89 to 0.97 of the time for rows of 36 and more, 0.97 for 28 to 36, but 1.00 to 1.07 at 700 to
     // 1000 waves, and 1.02 and 1.06 for rows of 20 to 28 and of 14 to 20 (300 products, three matrices in turn; us: 221 x 221, rows of 41, N = 235: 4.7 and 4.15; 250 x 377, of 58, N = 250: 5.3 and 4.7).
     const bool sparse_launch = a.nnz >= 28 * a.m && waves < (a.nnz >= 36 * a.m ? 700 : 600);
+    // Nor for rows of 36 entries and more on 1025 to 1399 waves, that is 257 to 350 workgroups, whose last tile is more than a quarter empty: a compute unit with a second workgroup has eight long chains, and a part of them works for
+    // nothing, where tiles of 64 columns are workgroups enough to come out even (39 products, three matrices in turn, 13 % less by 64 columns, up to 1199 waves 16 %, above 8 %; us, 256 and 64: 530 x 530, rows of 95, N = 267: 8.9 6.6;
+    // 363 x 363, of 68, N = 547: 7.55 6.1; 590 x 590, of 39, N = 335: 5.8 5.4; with less of the tile empty 0.87 to 1.11 in 11 others, from 1400 waves on 0.92 to 1.02).
+    const bool uneven_rounds = a.nnz >= 36 * a.m && waves > 1024 && waves < 1400 && a.N < 192 * ((a.N + 255) / 256);
     // Nor for many rows of B on lines, where wider tiles take no fewer lines per byte and B leaves an XCD's L2 the sooner (time against 64 columns, rows of 3 to 25 entries, 700 products: up to 1000 rows of B 0.90 to 0.97, to 1500
     // 0.93 to 1.05, to 2500 0.97 to 1.02 for N up to 256 and 1.01 to 1.20 beyond, from there on 1.01 to 1.25: 5000 to 8192 rows of B, rows of 10 to 25, N = 224 and 256: 1.22).
     const bool stays = !lines || a.k <= (a.N <= 256 ? 2500 : 1500);
-    if (a.N > 64 && waves <= 8192 && full && !sparse_launch && stays && (a.nnz < 25 * a.m || a.m < 1000))
+    if (a.N > 64 && waves <= 8192 && full && !sparse_launch && !uneven_rounds && stays && (a.nnz < 25 * a.m || a.m < 1000))
         return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, s) : launch_rows<32>(a, s);
     if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
     // From 897 columns on there are eight tiles of 128 columns, one per XCD (us, 64 and 128 columns: power-law rows, 3611 x 3611, N = 926: 54 43; 4658 x 4658, N = 994: 64 56; 9046 x 9046, N = 895: 136 138;

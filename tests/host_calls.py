@@ -384,6 +384,8 @@ WIDTHS = [(8123, 11104, 22, 13, 8, 254), (7000, 7000, 22, 30, 8, 219), (3200, 30
           (6133, 5725, 93, 108, 32, 767), (6133, 5725, 93, 64, 32, 767), (6133, 5725, 93, 63, 16, 768), (6133, 5725, 96, 108, 16, 768),
           (299, 300, 300, 28, 16, 375), (299, 300, 300, 27, 64, 150), (300, 300, 300, 28, 64, 150),
           (205, 300, 205, 74, 16, 208), (349, 300, 300, 36, 16, 440), (350, 300, 300, 36, 64, 175),
+          (513, 600, 300, 36, 16, 645), (512, 600, 300, 36, 64, 256), (513, 600, 300, 35, 64, 258), (699, 700, 383, 36, 16, 264), (699, 700, 384, 36, 64, 350), (700, 700, 383, 36, 64, 350),
+          (1200, 3000, 140, 60, 64, 300),
           (2600, 2500, 256, 5, 64, 650), (2600, 2501, 256, 5, 16, 652), (2600, 2501, 255, 5, 64, 650), (1600, 1500, 320, 5, 64, 800), (1600, 1501, 320, 5, 16, 500), (6000, 6000, 128, 12, 16, 750),
           (3218, 3218, 326, 93, 32, 1209), (3218, 3218, 321, 93, 32, 1209), (3218, 3218, 257, 93, 16, 1010), (3218, 3218, 319, 93, 16, 1010), (3218, 3218, 326, 63, 16, 1212), (3218, 3218, 320, 93, 16, 1010)]
 
