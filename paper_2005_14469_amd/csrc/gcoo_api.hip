@@ -443,7 +443,8 @@ int32_t share_best_p(int64_t m, int64_t N)
 
 // Times of the two kernels that the automatic choice is between, in microseconds: fitted to 492 products by the row-by-row kernel and 906 by the two cuts of the bands, on uniform random
 // matrices (1200 to 15000 rows and columns, 4 to 250 entries per row and up to 20 % dense, N = 300 to 15000, B not in a cache), half of them with rows of B on 128-byte lines (`lines`) and half
-// inside; mean error 5 to 8 %.  Over 360 pairs of matrix and width (N near k), choosing by them costs 0.6 % against always taking the fastest.
+// inside; mean error 5 to 8 %.  The row-by-row kernel has had other tiles since (spdm_rows.hip): over 1237 drawn products of more than 1200 rows its time is 3 % short on average, mean error 13 %.  Choosing among the three
+// kernels by these times took 0.6 % longer than always the fastest over 1600 drawn products, 1.0 % over the 579 of them with a band schedule.
 // `outside`: how much of B is beyond what the memory-side cache holds of it beside C.
 double outside_cache(int64_t k, int64_t N)
 {
@@ -458,8 +459,9 @@ double rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
     if (lines) return 2.5 + row * (taken * (1.0 + std::pow(kd / 49100.0, 0.974)) / 31.8e6 + md / 6.6e6 + kd / 5.2e6 + outside_cache(k, N) * (md + kd) / 31.8e6);
     return 2.4 + row * (taken * (1.0 + std::pow(kd / 13200.0, 1.49)) / 29.3e6 + md / 5.9e6 + kd / 4.9e6);
 }
-// The same for matrices of so few columns that the tile kernel is the other choice (k <= 2500 or so, cache-resident, 1336 products of 100 to 20000 rows, N = 16 to 8000, mean error 8 %):
-// what its slots take of B is whole tiles, and launches of few workgroups leave compute units idle.
+// The same for matrices of so few columns that the tile kernel is the other choice (k <= 2500 or so, cache-resident, fitted to 1336 products of 100 to 20000 rows, N = 16 to 8000, mean error 8 %):
+// what its slots take of B is whole tiles, and launches of few workgroups leave compute units idle.  The widths here are those of the kernel that was fitted, not those that launch_spdm_rows() takes now, with which
+// it needs 14 to 18 % less than this on average (mean error 15 to 18 %, 1700 drawn products).
 double few_columns_rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool lines)
 {
     const int64_t tile = N <= 16 ? 16 : (N <= 32 ? 32 : (N > 64 && k <= (lines ? 4096 : 6500) ? 128 : 64)), tiles = (N + (lines ? 0 : 31) + tile - 1) / tile;
@@ -470,8 +472,8 @@ double few_columns_rows_time(int64_t m, int64_t k, int64_t nnz, int64_t N, bool 
 // where their LDS allows it, costs 1.5 us and what the tiles take to come in, and the entries of its rows: 3.8 ns per sixteen of them while enough waves read LDS, 26 ns per entry of a row for
 // a wave by itself.  Where rows are long and workgroups have fewer of them than slots, a row has a whole wave to itself (`whole`; 1000 x 2480, 20 %, N = 64: 19.7 us with a row per slot, 9.1 so).
 // Fitted to the products above in 2 to 14 cuts each: mean error 8 %; the cut so chosen takes 1.3 % longer than the best one.
-// `preferred`: the tile kernel is taken, [1] where rows of B are on lines: where it is expected to need 0.85 of the time of the row-by-row kernel from the caches.  Of 900 products that leaves 6
-// that lose more than 3 % by it (48 with 1, 15 with 0.9), and they take 17.6 % less on (geometric) average (17.8 with 0.9).
+// `preferred`: the tile kernel is taken, [1] where rows of B are on lines: where it is expected to need 0.85 of few_columns_rows_time(), which is about what the row-by-row kernel
+// really takes: of 900 drawn products of up to 2558 columns 29 lose more than 3 % by the choice, 7 more than 10 %, and all take 0.5 % longer than by the faster of the two.
 struct TilePlan { int64_t row_wgs; bool whole; double time; bool preferred[2]; };
 const TilePlan& tile_plan(int64_t m, int64_t k, int64_t nnz, int64_t N)
 {

@@ -21,10 +21,10 @@
 // Bound, by the counters: 4 x nnz x N bytes have to come from L2 through the vector caches, which take 64 bytes per clock and compute unit (39 TB/s) at
 // the most.  Where the tile of B that an XCD works on stays in its L2 the kernel gets 17 to 23 TB/s of that: 22.7 at 1777 x 2301, 3 %, N = 1117
 // (94 % of the requests hit; the tile kernel is faster there), 17.4 at 12000 x 12000, 0.5 %, N = 64.  Where it does not, what the L2 has to fetch counts as well: power-law rows,
-// 16384 x 16384, N = 512, whose tile of 64 columns is all of an XCD's 4 MB, take 0.32 GB from behind the L2 for a B of 34 MB (17.6 TB/s from L2);
+// 16384 x 16384, N = 512, whose tile of 64 columns is all of an XCD's 4 MB, take 0.31 GB from behind the L2 for a B of 34 MB (19.6 TB/s from L2);
 // 12001 x 12001 with 6 entries per row 2.4 GB for a B of 0.58 GB, which with C is 7.0 TB/s between the L2s and memory where a large copy reaches 5.2:
 // there the bound lies behind the L2.  Tiles of 64 columns that fetch 0.76 GB for the aligned rows of 12000 x 12000 take as long as those of 128 that fetch 1.5 (369 and 365 us): memory gives stretches of 256 bytes more slowly.
-// Measured (product alone, before = the register kernel): 12000 x 12000, 0.5 %, N = 64: 83 -> 11.0 us; 2500 x 2500, 1 %, N = 1024: 38 -> 14.2; 256 x 256, 10 %, N = 256: 35 -> 4.1;
+// Measured (product alone, before = the register kernel): 12000 x 12000, 0.5 %, N = 64: 83 -> 11.0 us; 2500 x 2500, 1 %, N = 1024: 38 -> 15.2; 256 x 256, 10 %, N = 256: 35 -> 4.1;
 // 400 x 400, 2 %: 3.4; 4000 x 4000, 2 %, N = 4000: 25 TB/s through the vector cache.  12001 x 12001 as above: 437 us with sixteen rows of B in flight, 427 with eight.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -383,7 +383,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
             if (hi > lo) turn += hi - lo < n ? hi - lo : n;
         }
     }
-    // (out of the way of matrices without long rows: 12000 x 12000, 0.5 %, N = 64: 12.15 us without the hints, 12.13 so)
+    // (out of the way of matrices without long rows; 12000 x 12000, 0.5 %, N = 64: level, 12.15 us without the hints, 12.13 so)
     if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, SUMS, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
     rows_of_wave<LPR, WIDE, AHEAD, SUMS>(T, w0, wrows, start, wave_row, a.long_row);
 }

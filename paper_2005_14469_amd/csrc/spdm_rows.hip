@@ -66,6 +66,8 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // 6124 x 6124, rows of 19, N = 28: 7.4 4.9; 8788 x 9414, of 18, N = 27: 5.6 6.2).
     if (a.N <= 32 && a.m >= 7000) return a.N <= 16 && a.m >= 16384 ? launch_rows<4>(a, s) : launch_rows<8>(a, s);
     if (a.N <= 32) return launch_rows<16, 2>(a, s);
+    // ("As many entries as uneven rows have on average" below: the host knows the mean only, and 25 to 90 entries is that of the power law that was measured, exponent 1.5 with up to 4096 entries, over 2000 to 20000 columns.
+    // Uniform rows of such a mean lose by it, up to 30 % between 129 and 400 columns; power-law rows of another exponent or limit have another mean.)
     // 64, 128 or 256 columns per tile.  Wider tiles are fewer requests for the same bytes and, where rows of B begin inside a 128-byte line, fewer lines per byte (3 for
     // 256 bytes, 5 for 512, 9 for 1024); narrower ones stay in an XCD's L2 (4 MB) at more rows of B, and have more slots to a wave for uneven rows, of which the host knows nothing.
     // From the times of all three in 960 products with rows of B inside a line and 800 with rows on lines, 300 to 20000 rows and columns, rows of 1 to 250 entries and power-law rows (us,
