@@ -99,6 +99,11 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     "s_set_gpr_idx_idx " #meta1 "\n\t"                             \
     BD_FMAC_##B(val1)                                              \
     "s_set_gpr_idx_off\n\t"
+// Step i of a unit at priority i, so that the waves of a SIMD go through their entries at one pace.  Among waves of one priority a SIMD serves the oldest first: the
+// others had what was left, and the youngest went through the last of its entries alone, one instruction in six clocks (clocks from a barrier to the end of a wave's entries,
+// waves 0 - 3, 4 - 7, 8 - 11 and 12 - 15, 8000 x 8000, 10 %: 9800 11400 14100 16500).  Product alone (us): 8000 x 8000, 10 % 2300 -> 2030,
+// 4000 x 4000, 5 % 198 -> 183, 2 % 111 -> 108; 14000 x 14000, 2 % 3180 -> 2990; 8000 x 8000, 0.5 % 296 -> 286.  Falling with the steps as fast; two priorities in turn 2170 to 2220 for the first.
+#define BD_TURN(i) "s_setprio " #i "\n\t"
 #define BD_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
 
 // Request t of the five of a wave for the next band: one row of B (wide) or two, one per half of the wave (tall); the column, or both, in s<16 + t>.
@@ -186,20 +191,20 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     BD_READ_T0(m0) BD_READ_T1(m2) BD_READ_T2(m4) BD_READ_T3(m6)                                 \
     BD_ASK_START(p, X)                                                                          \
     ".Lbd_p0_" #X "_%=:\n\t"                                                                    \
-    "s_sub_u32 s21, s21, 1\n\t"                                                                 \
+    BD_TURN(0) "s_sub_u32 s21, s21, 1\n\t"                                                      \
     BD_READ_T4(m8) BD_WAIT(4) BD_TWO(a0, m0, T0, a1, m1, T0)                                    \
     BD_READ_T5(m10) BD_WAIT(4) BD_TWO(a2, m2, T1, a3, m3, T1)                                   \
     BD_ASK_STEP(p, 0, X)                                                                        \
     "s_sub_u32 s21, s21, 1\n\ts_cbranch_scc1 .Lbd_ps1_" #X "_%=\n\t"                            \
-    BD_READ_T0(m12) BD_WAIT(4) BD_TWO(a4, m4, T2, a5, m5, T2)                                   \
+    BD_TURN(1) BD_READ_T0(m12) BD_WAIT(4) BD_TWO(a4, m4, T2, a5, m5, T2)                        \
     BD_READ_T1(m14) BD_WAIT(4) BD_TWO(a6, m6, T3, a7, m7, T3)                                   \
     BD_ASK_STEP(p, 1, X)                                                                        \
     "s_sub_u32 s21, s21, 1\n\ts_cbranch_scc1 .Lbd_ps2_" #X "_%=\n\t"                            \
-    BD_WAIT(3) BD_TWO(a8, m8, T4, a9, m9, T4)                                                   \
+    BD_TURN(2) BD_WAIT(3) BD_TWO(a8, m8, T4, a9, m9, T4)                                        \
     BD_WAIT(2) BD_TWO(a10, m10, T5, a11, m11, T5)                                               \
     BD_ASK_STEP(p, 2, X)                                                                        \
     "s_sub_u32 s21, s21, 1\n\ts_cbranch_scc1 .Lbd_ps3_" #X "_%=\n\t"                            \
-    BD_WAIT(1) BD_TWO(a12, m12, T0, a13, m13, T0)                                               \
+    BD_TURN(3) BD_WAIT(1) BD_TWO(a12, m12, T0, a13, m13, T0)                                    \
     BD_WAIT(0) BD_TWO(a14, m14, T1, a15, m15, T1)                                               \
     "s_cmp_lg_u32 s21, 0\n\ts_cbranch_scc1 .Lbd_unitp_" #Y "_%=\n\t"                            \
     "s_cmp_lg_u32 s22, 0\n\ts_cbranch_scc1 .Lbd_units_" #Y "_%=\n\t"                            \
@@ -213,22 +218,22 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     BD_READ_T0(m0) BD_READ_T1(m1) BD_READ_T2(m2) BD_READ_T3(m3)                                 \
     BD_ASK_START(s, X)                                                                          \
     ".Lbd_s0_" #X "_%=:\n\t"                                                                    \
-    "s_sub_u32 s22, s22, 1\n\t"                                                                 \
+    BD_TURN(0) "s_sub_u32 s22, s22, 1\n\t"                                                                 \
     BD_READ_T4(m4) BD_READ_T5(m5) BD_WAIT(4) BD_TWO(a0, m0, T0, a1, m1, T1)                     \
     BD_READ_T0(m6) BD_READ_T1(m7) BD_WAIT(4) BD_TWO(a2, m2, T2, a3, m3, T3)                     \
     BD_ASK_STEP(s, 0, X)                                                                        \
     ".Lbd_s1_" #X "_%=:\n\t"                                                                    \
-    "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
+    BD_TURN(1) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
     BD_READ_T2(m8) BD_READ_T3(m9) BD_WAIT(4) BD_TWO(a4, m4, T4, a5, m5, T5)                     \
     BD_READ_T4(m10) BD_READ_T5(m11) BD_WAIT(4) BD_TWO(a6, m6, T0, a7, m7, T1)                   \
     BD_ASK_STEP(s, 1, X)                                                                        \
     ".Lbd_s2_" #X "_%=:\n\t"                                                                    \
-    "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
+    BD_TURN(2) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
     BD_READ_T0(m12) BD_READ_T1(m13) BD_WAIT(4) BD_TWO(a8, m8, T2, a9, m9, T3)                   \
     BD_READ_T2(m14) BD_READ_T3(m15) BD_WAIT(4) BD_TWO(a10, m10, T4, a11, m11, T5)               \
     BD_ASK_STEP(s, 2, X)                                                                        \
     ".Lbd_s3_" #X "_%=:\n\t"                                                                    \
-    "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
+    BD_TURN(3) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
     BD_WAIT(2) BD_TWO(a12, m12, T0, a13, m13, T1)                                               \
     BD_WAIT(0) BD_TWO(a14, m14, T2, a15, m15, T3)                                               \
     "s_cmp_lg_u32 s22, 0\n\ts_cbranch_scc1 .Lbd_units_" #Y "_%=\n\t"                            \
