@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gcoo_band_build.hpp"
 #include "gcoo_build_kernels.hpp"
 
@@ -227,7 +229,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     extern __shared__ uint32_t order_lds[];
     __shared__ int32_t seg[ROWS], off[ROWS];     // a row's place among the part's entries (or in the input), and what takes it to the input
     __shared__ int32_t wsum[WAVES], wsum2[WAVES];
-    __shared__ int32_t below_s, count_s, long_s;
+    __shared__ int32_t below_s, count_s, long_s, group_s[2];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int32_t parts = a.plan.parts, shift = a.plan.shift, ncols = 1 << shift, later = parts - 1;
     const int64_t q = item / parts;
@@ -251,17 +253,20 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     uint8_t* o_row = (uint8_t*)(o_col + a.plan.cap);
 
     // everything that does not wait for anything else
-    int32_t g0, g1;
+    int32_t g0 = 0, g1 = 0;
     int32_t rs0 = 0, re = 0, s = 0, e = 0;
     if constexpr (FUSED) {
+        // (one thread asks for an offset, not every wave: of host memory each would be a read over the link)
         auto at = [&](int64_t r) { const int32_t x = a.row_ptr[r]; return x < 0 ? 0 : (x > a.nnz ? a.nnz : x); };    // as in take_rows
-        g0 = at(r0);
-        g1 = at(r0 + rows);
+        if (tid == 0) g1 = at(r0 + rows);
         if (tid < rows) {
             rs0 = at(r0 + tid);
             a.row_start_out[r0 + tid] = rs0;
         }
         if (tid == 0) {
+            g0 = rs0;
+            group_s[0] = g0;
+            group_s[1] = g1;
             a.gIdxes_out[q] = g0;
             a.nnzPerGroup_out[q] = g1 < g0 ? 0 : g1 - g0;
             if (q == a.g - 1) {
@@ -295,7 +300,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     const bool in_order = !FUSED && parts > 1 && __syncthreads_or((int)(f & kUnsorted)) == 0;
     const bool some = !FUSED && parts > 1 && !in_order;                // entries of other parts are among those looked at
 
-    int32_t n, out0;                                         // entries to look at, place of the part's first one in the arrays
+    int32_t n = 0, out0 = 0;                                 // entries to look at, place of the part's first one in the arrays
     if (in_order) {
         const int32_t len = e - s;
         int32_t incl = len, skip = s - rs0;
@@ -310,13 +315,14 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
         __syncthreads();
         int32_t at = incl - len;
         for (int j = 0; j < wv; ++j) at += wsum[j];
-        n = 0;
         out0 = g0;
         for (int j = 0; j < WAVES; ++j) { n += wsum[j]; out0 += wsum2[j]; }
         if (tid < ROWS) {
             seg[tid] = tid < rows ? at : INT32_MAX;
             off[tid] = s - at;
         }
+    } else if (FUSED) {
+        if (tid < ROWS) seg[tid] = tid < rows ? rs0 : INT32_MAX;       // (in the input)
     } else {
         n = g1 - g0;
         out0 = g0;
@@ -326,6 +332,11 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
         }
     }
     __syncthreads();
+    if constexpr (FUSED) {
+        out0 = g0 = __builtin_amdgcn_readfirstlane(group_s[0]);
+        g1 = __builtin_amdgcn_readfirstlane(group_s[1]);
+        n = g1 - g0;
+    }
     if (!FUSED && part == 0 && tid < rows && a.out.cols) list_long_row(a.out, (int32_t)r0 + tid, re - rs0);
     if (n <= 0) {                                            // the whole workgroup
         if (FUSED && tid == 0) a.flags_out[q] = 0u;
@@ -337,7 +348,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     if (FUSED && a.out.cols) {
         long0 = g0 / a.out.long_row;
         long1 = g1 / a.out.long_row;
-        if (tid < rows && (tid + 1 < rows ? seg[tid + 1] : n) - seg[tid] > a.out.long_row) {
+        if (tid < rows && (tid + 1 < rows ? seg[tid + 1] : g1) - seg[tid] > a.out.long_row) {
             const int32_t at = long0 + atomicAdd(&long_s, 1);
             if (at < long1) a.out.long_rows[at] = (int32_t)r0 + tid;
         }
@@ -346,8 +357,8 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     bool bad = false;                                        // FUSED: a column was out of range
     // entry i of those to look at: its row, its column in the part, its value
     auto take = [&](int32_t i, int32_t* r, int32_t* c, float* v) {
-        *r = row_of_entry<ROWS>(seg, i);
-        const int32_t at = off[*r] + i, col = a.cols[at];
+        *r = row_of_entry<ROWS>(seg, FUSED ? g0 + i : i);
+        const int32_t at = FUSED ? g0 + i : off[*r] + i, col = a.cols[at];
         const int32_t inside = col < 0 ? 0 : (col > kmax ? kmax : col);
         *c = inside - c0;
         *v = a.vals[at];
@@ -355,12 +366,21 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     };
     int32_t r[EACH], c[EACH];
     float v[EACH];
-    auto take_some = [&](int32_t i0) {                       // eight entries per thread; past the end the last one again
+    // Up to eight entries per thread, side by side; past the end the last one again, but a wave asks for one, two or four where it has no more: what is past the end costs a search and two
+    // requests as well (conversion and product, us, eight always and so: 1777 x 2301, 3 %, N = 1117: 35.4 34.6; power-law rows, 16384 x 16384, N = 512: 131.8 129.1).
+    auto take_n = [&](auto most, int32_t i0) {
 #pragma unroll
-        for (int x = 0; x < EACH; ++x) {
+        for (int x = 0; x < decltype(most)::value; ++x) {
             const int32_t i = i0 + x * THREADS + tid;
             take(i < n ? i : n - 1, &r[x], &c[x], &v[x]);
         }
+    };
+    auto take_some = [&](int32_t i0) {
+        const int32_t left = n - i0 - __builtin_amdgcn_readfirstlane(tid & ~63);          // from the wave's first entry on
+        if (left > 4 * THREADS) take_n(std::integral_constant<int, EACH>{}, i0);
+        else if (left > 2 * THREADS) take_n(std::integral_constant<int, 4>{}, i0);
+        else if (left > THREADS) take_n(std::integral_constant<int, 2>{}, i0);
+        else if (left > 0) take_n(std::integral_constant<int, 1>{}, i0);
     };
 
     // the masks (RANKED: the bitmap); what lies before the part and what is in it, where that is not known yet
