@@ -1045,13 +1045,21 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     const int32_t* d_cols = col_idx;
     const float* d_vals = vals;
     HostStage stage;
+    bool starts_given = false;
     const size_t in_bytes = L.in_vals + (size_t)nnz * 4 - L.in_row_ptr;          // row_ptr, columns and values as they lie in the scratch area
     if (!src_on_device && in_bytes <= kStageBytes && stage.claim()) {
         // the caller may release its host arrays as soon as this call returns
         char* to = stage.ptr();
         std::memcpy(to, row_ptr, (size_t)(m + 1) * 4);
+        starts_given = L.by_masks && L.plan.fused && h->has_rows() && g <= gcoo::kOrderHostGroups;
         if (nnz > 0) {
-            std::memcpy(to + (L.in_cols - L.in_row_ptr), col_idx, (size_t)nnz * 4);
+            if (starts_given) {
+                // one launch is the whole conversion: of its columns, 4096 at the most, half of the words go over the link
+                uint16_t* narrow = reinterpret_cast<uint16_t*>(to + (L.in_cols - L.in_row_ptr));
+                for (int64_t e = 0; e < nnz; ++e) narrow[e] = (uint16_t)col_idx[e];
+            } else {
+                std::memcpy(to + (L.in_cols - L.in_row_ptr), col_idx, (size_t)nnz * 4);
+            }
             std::memcpy(to + (L.in_vals - L.in_row_ptr), vals, (size_t)nnz * 4);
         }
         if (L.by_masks && h->has_rows()) {
@@ -1089,9 +1097,17 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
         o.row_ptr = d_row_ptr; o.nnz = (int32_t)nnz; o.g = g; o.gIdxes_out = h->gIdxes(); o.nnzPerGroup_out = h->nnzPerGroup();
         o.row_start_out = h->row_start(); o.flags_out = h->take_flags();
+        if (starts_given) {
+            gcoo::GroupStarts starts;
+            for (int64_t q = 0; q <= g; ++q) starts.at[q] = row_ptr[q < g ? q * p : m];
+            auto order = L.plan.threads == 1024 ? (words == 1 ? gcoo::order_groups_host<1, 1024> : gcoo::order_groups_host<2, 1024>)
+                                                : (words == 1 ? gcoo::order_groups_host<1, gcoo::kOrderThreads> : gcoo::order_groups_host<2, gcoo::kOrderThreads>);
+            order<<<dim3((unsigned)g), dim3((unsigned)L.plan.threads), gcoo::order_lds_bytes(L.plan, words), s>>>(o, starts);
+        } else {
         auto order = L.plan.threads == 1024 ? (words == 1 ? gcoo::order_groups<1, gcoo::kOrderFused, 1024> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderFused, 1024> : gcoo::order_groups<8, gcoo::kOrderFused, 1024>))
                                             : (words == 1 ? gcoo::order_groups<1, gcoo::kOrderFused> : (words == 2 ? gcoo::order_groups<2, gcoo::kOrderFused> : gcoo::order_groups<8, gcoo::kOrderFused>));
         order<<<dim3((unsigned)g), dim3((unsigned)L.plan.threads), gcoo::order_lds_bytes(L.plan, words), s>>>(o);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "order_groups"); }
     } else if (L.by_masks) {

@@ -220,12 +220,17 @@ inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 //
 // RANKED (many columns per entry): a part has many more columns, of which a bitmap says which hold an entry; the places of those among themselves take the
 // place of the columns, so that nothing is done per column but for a bit.  More distinct columns than plan.keys go window by window.
-enum OrderKind { kOrderMasks, kOrderFused, kOrderRanked };
+//
+// HOST: as FUSED, for an input in host memory.  The launch says in the kernel's arguments where the groups begin, so that a group's entries are asked for beside its rows' starts and not one
+// trip over the link behind them, and the columns have 16 bits there, six bytes per entry in place of eight: 2500 x 2500, 1 %: 17.7 -> 14.1 us, of which the link takes about 7 (9 with eight).
+enum OrderKind { kOrderMasks, kOrderFused, kOrderRanked, kOrderHost };
+constexpr int kOrderHostGroups = 512;        // at most, 2 KB of arguments
+struct GroupStarts { int32_t at[kOrderHostGroups + 1]; };
 template <int WORDS, OrderKind KIND, int THREADS>
-__device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
+__device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int32_t known0 = 0, int32_t known1 = 0)
 {
     constexpr int ROWS = WORDS == 8 ? 256 : 32 * WORDS, WAVES = THREADS / 64, EACH = 8;
-    constexpr bool FUSED = KIND == kOrderFused, RANKED = KIND == kOrderRanked;
+    constexpr bool HOST = KIND == kOrderHost, FUSED = KIND == kOrderFused || HOST, RANKED = KIND == kOrderRanked;
     extern __shared__ uint32_t order_lds[];
     __shared__ int32_t seg[ROWS], off[ROWS];     // a row's place among the part's entries (or in the input), and what takes it to the input
     __shared__ int32_t wsum[WAVES], wsum2[WAVES];
@@ -253,20 +258,22 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     uint8_t* o_row = (uint8_t*)(o_col + a.plan.cap);
 
     // everything that does not wait for anything else
-    int32_t g0 = 0, g1 = 0;
+    int32_t g0 = known0, g1 = known1;
     int32_t rs0 = 0, re = 0, s = 0, e = 0;
     if constexpr (FUSED) {
         // (one thread asks for an offset, not every wave: of host memory each would be a read over the link)
         auto at = [&](int64_t r) { const int32_t x = a.row_ptr[r]; return x < 0 ? 0 : (x > a.nnz ? a.nnz : x); };    // as in take_rows
-        if (tid == 0) g1 = at(r0 + rows);
+        if (!HOST && tid == 0) g1 = at(r0 + rows);
         if (tid < rows) {
             rs0 = at(r0 + tid);
             a.row_start_out[r0 + tid] = rs0;
         }
         if (tid == 0) {
-            g0 = rs0;
-            group_s[0] = g0;
-            group_s[1] = g1;
+            if (!HOST) {
+                g0 = rs0;
+                group_s[0] = g0;
+                group_s[1] = g1;
+            }
             a.gIdxes_out[q] = g0;
             a.nnzPerGroup_out[q] = g1 < g0 ? 0 : g1 - g0;
             if (q == a.g - 1) {
@@ -300,7 +307,51 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
     const bool in_order = !FUSED && parts > 1 && __syncthreads_or((int)(f & kUnsorted)) == 0;
     const bool some = !FUSED && parts > 1 && !in_order;                // entries of other parts are among those looked at
 
-    int32_t n = 0, out0 = 0;                                 // entries to look at, place of the part's first one in the arrays
+    int32_t n = HOST ? g1 - g0 : 0, out0 = HOST ? g0 : 0;    // entries to look at, place of the part's first one in the arrays
+    const int32_t c0 = part << shift, kmax = a.k - 1, wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
+    bool bad = false;                                        // FUSED: a column was out of range
+    // Entry i of those to look at is of row r, in column c of the part.  A thread has up to eight of them, side by side; past the end the last one again, but a wave asks for one, two or four
+    // where it has no more: what is past the end costs a search and two requests as well (conversion
+    // and product, us, eight always and so: 1777 x 2301, 3 %, N = 1117: 35.4 34.6; power-law rows, 16384 x 16384, N = 512: 131.8 129.1).
+    int32_t r[EACH], c[EACH];
+    float v[EACH];
+    auto column = [&](int32_t at) -> int32_t { return HOST ? (int32_t)reinterpret_cast<const uint16_t*>(a.cols)[at] : a.cols[at]; };
+    auto inside = [&](int32_t col) { return col < 0 ? 0 : (col > kmax ? kmax : col); };
+    auto ask = [&](auto most, int32_t i0) {
+#pragma unroll
+        for (int x = 0; x < decltype(most)::value; ++x) {
+            const int32_t i = i0 + x * THREADS + tid, e = i < n ? i : n - 1;
+            if constexpr (!FUSED) r[x] = row_of_entry<ROWS>(seg, e);
+            const int32_t at = FUSED ? g0 + e : off[r[x]] + e;
+            c[x] = column(at);
+            v[x] = a.vals[at];
+        }
+    };
+    auto find = [&](auto most, int32_t i0) {
+#pragma unroll
+        for (int x = 0; x < decltype(most)::value; ++x) {
+            const int32_t i = i0 + x * THREADS + tid, col = c[x];
+            if constexpr (FUSED) {
+                r[x] = row_of_entry<ROWS>(seg, g0 + (i < n ? i : n - 1));
+                bad |= inside(col) != col;
+            }
+            c[x] = inside(col) - c0;
+        }
+    };
+    auto take = [&](int32_t i, int32_t* ri, int32_t* ci, float* vi) {
+        *ri = row_of_entry<ROWS>(seg, FUSED ? g0 + i : i);
+        const int32_t at = FUSED ? g0 + i : off[*ri] + i;
+        *ci = inside(column(at)) - c0;
+        *vi = a.vals[at];
+    };
+    if constexpr (HOST) {
+        if (wave0 < n) {
+            if (n - wave0 > 4 * THREADS) ask(std::integral_constant<int, EACH>{}, 0);
+            else if (n - wave0 > 2 * THREADS) ask(std::integral_constant<int, 4>{}, 0);
+            else if (n - wave0 > THREADS) ask(std::integral_constant<int, 2>{}, 0);
+            else ask(std::integral_constant<int, 1>{}, 0);
+        }
+    }
     if (in_order) {
         const int32_t len = e - s;
         int32_t incl = len, skip = s - rs0;
@@ -332,7 +383,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
         }
     }
     __syncthreads();
-    if constexpr (FUSED) {
+    if constexpr (FUSED && !HOST) {
         out0 = g0 = __builtin_amdgcn_readfirstlane(group_s[0]);
         g1 = __builtin_amdgcn_readfirstlane(group_s[1]);
         n = g1 - g0;
@@ -353,41 +404,23 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item)
             if (at < long1) a.out.long_rows[at] = (int32_t)r0 + tid;
         }
     }
-    const int32_t c0 = part << shift, kmax = a.k - 1;
-    bool bad = false;                                        // FUSED: a column was out of range
-    // entry i of those to look at: its row, its column in the part, its value
-    auto take = [&](int32_t i, int32_t* r, int32_t* c, float* v) {
-        *r = row_of_entry<ROWS>(seg, FUSED ? g0 + i : i);
-        const int32_t at = FUSED ? g0 + i : off[*r] + i, col = a.cols[at];
-        const int32_t inside = col < 0 ? 0 : (col > kmax ? kmax : col);
-        *c = inside - c0;
-        *v = a.vals[at];
-        if (FUSED) bad |= inside != col;
-    };
-    int32_t r[EACH], c[EACH];
-    float v[EACH];
-    // Up to eight entries per thread, side by side; past the end the last one again, but a wave asks for one, two or four where it has no more: what is past the end costs a search and two
-    // requests as well (conversion and product, us, eight always and so: 1777 x 2301, 3 %, N = 1117: 35.4 34.6; power-law rows, 16384 x 16384, N = 512: 131.8 129.1).
-    auto take_n = [&](auto most, int32_t i0) {
-#pragma unroll
-        for (int x = 0; x < decltype(most)::value; ++x) {
-            const int32_t i = i0 + x * THREADS + tid;
-            take(i < n ? i : n - 1, &r[x], &c[x], &v[x]);
-        }
-    };
-    auto take_some = [&](int32_t i0) {
-        const int32_t left = n - i0 - __builtin_amdgcn_readfirstlane(tid & ~63);          // from the wave's first entry on
-        if (left > 4 * THREADS) take_n(std::integral_constant<int, EACH>{}, i0);
-        else if (left > 2 * THREADS) take_n(std::integral_constant<int, 4>{}, i0);
-        else if (left > THREADS) take_n(std::integral_constant<int, 2>{}, i0);
-        else if (left > 0) take_n(std::integral_constant<int, 1>{}, i0);
+    auto take_some = [&](int32_t i0, bool asked = false) {
+        const int32_t left = n - i0 - wave0;                 // from the wave's first entry on
+        auto go = [&](auto most) {
+            if (!asked) ask(most, i0);
+            find(most, i0);
+        };
+        if (left > 4 * THREADS) go(std::integral_constant<int, EACH>{});
+        else if (left > 2 * THREADS) go(std::integral_constant<int, 4>{});
+        else if (left > THREADS) go(std::integral_constant<int, 2>{});
+        else if (left > 0) go(std::integral_constant<int, 1>{});
     };
 
     // the masks (RANKED: the bitmap); what lies before the part and what is in it, where that is not known yet
     bool twice = false;
     int32_t below = 0, mine = 0;
     for (int32_t i0 = 0; i0 < n; i0 += EACH * THREADS) {
-        take_some(i0);
+        take_some(i0, HOST && i0 == 0);
 #pragma unroll
         for (int x = 0; x < EACH; ++x) {
             if (i0 + x * THREADS + tid >= n) break;
@@ -591,6 +624,13 @@ template <int WORDS, OrderKind KIND, int THREADS = kOrderThreads>
 __global__ __launch_bounds__(THREADS) void order_groups(OrderArgs a)
 {
     order_part<WORDS, KIND, THREADS>(a, (int32_t)blockIdx.x);
+}
+
+// A part per group; the input's columns have 16 bits (OrderArgs::cols points to them).
+template <int WORDS, int THREADS>
+__global__ __launch_bounds__(THREADS) void order_groups_host(OrderArgs a, GroupStarts starts)
+{
+    order_part<WORDS, kOrderHost, THREADS>(a, (int32_t)blockIdx.x, starts.at[blockIdx.x], starts.at[blockIdx.x + 1]);
 }
 
 // order_groups and band_fill in one launch, the lists first: neither needs anything of the other, both wait for LDS and memory most of their time, and neither fills the

@@ -59,3 +59,29 @@ def test_from_several_threads():
     for ws, out in zip(sets, outs):
         assert len(out) == len(ws)
         _check(out, 32)
+
+
+@pytest.mark.parametrize("m,k,p,lens", [
+    (512, 300, 1, 3), (513, 300, 1, 3),                       # as many groups as the launch says the starts of, and one more
+    (70, 4096, 32, 40), (70, 4097, 32, 40),                   # the last column that one launch takes (1024 threads), and one more
+    (130, 900, 50, 9), (64, 1, 64, 1),                        # masks of two words; one column
+    (40, 500, 32, [0] * 20 + [500] * 6 + [0] * 14),           # more entries in a group than its threads take at once; empty rows and a nearly empty group
+    (96, 2500, 32, [0] * 32 + [33] * 32 + [0] * 32),          # groups without an entry
+])
+def test_one_launch_from_host_memory(m, k, p, lens):
+    print(f"host stage, one launch: {m}x{k} p={p}", flush=True)
+    rng = np.random.default_rng(m + k)
+    lens = np.full(m, lens) if np.isscalar(lens) else np.array(lens)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([rng.permutation(np.r_[k - 1, rng.choice(k - 1, n - 1, replace=False)] if n > 1 else [k - 1] * n) for n in lens]).astype(np.int32)
+    w = workloads.Workload("host", m, k, 70, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, 70)).astype(np.float32))
+    for twice in (False, True):
+        if twice and lens[33 % m] > 1:                         # a coordinate repeated
+            w.col_idx[rp[33 % m]] = w.col_idx[rp[33 % m] + 1]
+        handles = []
+        _convert_many([w], p, handles)
+        _check(handles, p)
+        C = binding.gcoo_spdm(handles[0][1], torch.from_numpy(w.B).to(DEV))
+        C64, D64 = orc.spdm_csr(w.k, w.N, w.row_ptr, w.col_idx, w.vals, w.B)
+        err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
+        assert bad == 0 and err < 2e-6, (err, bad)
