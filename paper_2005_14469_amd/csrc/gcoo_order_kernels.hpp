@@ -310,16 +310,17 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     int32_t n = HOST ? g1 - g0 : 0, out0 = HOST ? g0 : 0;    // entries to look at, place of the part's first one in the arrays
     const int32_t c0 = part << shift, kmax = a.k - 1, wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
     bool bad = false;                                        // FUSED: a column was out of range
-    // Entry i of those to look at is of row r, in column c of the part.  A thread has up to eight of them, side by side; past the end the last one again, but a wave asks for one, two or four
-    // where it has no more: what is past the end costs a search and two requests as well (conversion
-    // and product, us, eight always and so: 1777 x 2301, 3 %, N = 1117: 35.4 34.6; power-law rows, 16384 x 16384, N = 512: 131.8 129.1).
+    // Entry i of those to look at is of row r, in column c of the part.  A thread goes through eight at a time, side by side, past the end the last one again; a wave that has no more than four
+    // per thread goes through four: what is past the end costs a search and two requests as well (conversion and product, us, eight always and so: 1777 x 2301, 3 %, N = 1117: 35.4 34.6; power-law
+    // rows, 16384 x 16384, N = 512: 140.6 134.8; one, two, four or eight: 34.5 and 139, and twice the code).
+    static_assert(EACH == 8, "four and four");
     int32_t r[EACH], c[EACH];
     float v[EACH];
     auto column = [&](int32_t at) -> int32_t { return HOST ? (int32_t)reinterpret_cast<const uint16_t*>(a.cols)[at] : a.cols[at]; };
     auto inside = [&](int32_t col) { return col < 0 ? 0 : (col > kmax ? kmax : col); };
-    auto ask = [&](auto most, int32_t i0) {
+    auto ask = [&](auto from, int32_t i0) {
 #pragma unroll
-        for (int x = 0; x < decltype(most)::value; ++x) {
+        for (int x = decltype(from)::value; x < decltype(from)::value + 4; ++x) {
             const int32_t i = i0 + x * THREADS + tid, e = i < n ? i : n - 1;
             if constexpr (!FUSED) r[x] = row_of_entry<ROWS>(seg, e);
             const int32_t at = FUSED ? g0 + e : off[r[x]] + e;
@@ -327,9 +328,9 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
             v[x] = a.vals[at];
         }
     };
-    auto find = [&](auto most, int32_t i0) {
+    auto find = [&](auto from, int32_t i0) {
 #pragma unroll
-        for (int x = 0; x < decltype(most)::value; ++x) {
+        for (int x = decltype(from)::value; x < decltype(from)::value + 4; ++x) {
             const int32_t i = i0 + x * THREADS + tid, col = c[x];
             if constexpr (FUSED) {
                 r[x] = row_of_entry<ROWS>(seg, g0 + (i < n ? i : n - 1));
@@ -346,10 +347,8 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     };
     if constexpr (HOST) {
         if (wave0 < n) {
-            if (n - wave0 > 4 * THREADS) ask(std::integral_constant<int, EACH>{}, 0);
-            else if (n - wave0 > 2 * THREADS) ask(std::integral_constant<int, 4>{}, 0);
-            else if (n - wave0 > THREADS) ask(std::integral_constant<int, 2>{}, 0);
-            else ask(std::integral_constant<int, 1>{}, 0);
+            ask(std::integral_constant<int, 0>{}, 0);
+            if (n - wave0 > 4 * THREADS) ask(std::integral_constant<int, 4>{}, 0);
         }
     }
     if (in_order) {
@@ -406,14 +405,13 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     }
     auto take_some = [&](int32_t i0, bool asked = false) {
         const int32_t left = n - i0 - wave0;                 // from the wave's first entry on
-        auto go = [&](auto most) {
-            if (!asked) ask(most, i0);
-            find(most, i0);
-        };
-        if (left > 4 * THREADS) go(std::integral_constant<int, EACH>{});
-        else if (left > 2 * THREADS) go(std::integral_constant<int, 4>{});
-        else if (left > THREADS) go(std::integral_constant<int, 2>{});
-        else if (left > 0) go(std::integral_constant<int, 1>{});
+        if (left <= 0) return;
+        if (!asked) ask(std::integral_constant<int, 0>{}, i0);
+        if (left > 4 * THREADS) {
+            if (!asked) ask(std::integral_constant<int, 4>{}, i0);
+            find(std::integral_constant<int, 4>{}, i0);
+        }
+        find(std::integral_constant<int, 0>{}, i0);
     };
 
     // the masks (RANKED: the bitmap); what lies before the part and what is in it, where that is not known yet
