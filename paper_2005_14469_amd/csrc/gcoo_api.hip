@@ -1045,16 +1045,17 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     const int32_t* d_cols = col_idx;
     const float* d_vals = vals;
     HostStage stage;
-    bool starts_given = false;
+    bool starts_given = false, narrow_cols = false;      // where the groups begin goes with the launch; the columns have 16 bits in the pinned buffer
     const size_t in_bytes = L.in_vals + (size_t)nnz * 4 - L.in_row_ptr;          // row_ptr, columns and values as they lie in the scratch area
     if (!src_on_device && in_bytes <= kStageBytes && stage.claim()) {
         // the caller may release its host arrays as soon as this call returns
         char* to = stage.ptr();
         std::memcpy(to, row_ptr, (size_t)(m + 1) * 4);
-        starts_given = L.by_masks && L.plan.fused && h->has_rows() && g <= gcoo::kOrderHostGroups;
+        const bool in_place = L.by_masks && h->has_rows();
+        starts_given = in_place && L.plan.fused && g <= gcoo::kOrderHostGroups;
+        narrow_cols = in_place && (starts_given || (!L.plan.fused && k <= 65536));
         if (nnz > 0) {
-            if (starts_given) {
-                // one launch is the whole conversion: of its columns, 4096 at the most, half of the words go over the link
+            if (narrow_cols) {
                 uint16_t* narrow = reinterpret_cast<uint16_t*>(to + (L.in_cols - L.in_row_ptr));
                 for (int64_t e = 0; e < nnz; ++e) narrow[e] = (uint16_t)col_idx[e];
             } else {
@@ -1062,7 +1063,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
             }
             std::memcpy(to + (L.in_vals - L.in_row_ptr), vals, (size_t)nnz * 4);
         }
-        if (L.by_masks && h->has_rows()) {
+        if (in_place) {
             // every word of the input is read once: the kernel takes it from where it is
             void* seen = nullptr;
             hipError_t e = hipHostGetDevicePointer(&seen, to, 0);
@@ -1123,7 +1124,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         t.zero_bad = h->bad_col();
         t.stats = h->has_sched ? stats : nullptr;
         const bool few = !stage && nnz / L.lists > 2048;
-        (stage ? gcoo::take_rows<true, 512> : (few ? gcoo::take_rows<false, 1024> : gcoo::take_rows<false, 512>))<<<
+        (narrow_cols ? gcoo::take_rows<gcoo::kTakeHost16, 512> : (stage ? gcoo::take_rows<gcoo::kTakeHost, 512> : (few ? gcoo::take_rows<gcoo::kTakeDevice, 1024> : gcoo::take_rows<gcoo::kTakeDevice, 512>)))<<<
             dim3((unsigned)(L.lists + (h->has_sched ? 1 : 0))), dim3(few ? 1024 : 512), marked ? (size_t)((k + 31) / 32) * 4 : 0, s>>>(t);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "take_rows"); }

@@ -69,14 +69,17 @@ __device__ __forceinline__ int32_t row_of_entry(const int32_t* start, int32_t e)
 }
 
 // One workgroup per list of rows.  Bound: memory, an entry is read once and its copy in row order written once.  Dynamic LDS: the
-// list's columns as a bitmap, where the band schedule wants it.  FROM_HOST: the input is host memory, and a column is not read twice
-// (from device memory the second read, which the vector cache serves, is the cheaper way: 36.6 and 42.7 us for 6.4 million entries).
+// list's columns as a bitmap, where the band schedule wants it.  FROM kTakeHost: the input is host memory, and a column is not read twice
+// (from device memory the second read, which the vector cache serves, is the cheaper way: 36.6 and 42.7 us for 6.4 million entries).  kTakeHost16: its columns have 16 bits (TakeArgs::cols points to
+// them), six bytes per entry over the link in place of eight (conversion and product, us, eight and six: 3881 x 4000, 1.28 %, N = 516: 77.8 70.6; 2877 x 3824, 1.29 %, N = 1183: 77.0 71.8).
 // THREADS = 1024 for lists of more than 2048 entries, of which there are few (4000 x 4000, 5 %: 10.0 us with 512, 8.4 so; 8000 x 8000, 10 %: 24.2 and 23.0; but
 // 0.5 %: 6.6 and 7.3; before the rows were found by lanes 10.0 and 27.6 for the first two).
-template <bool FROM_HOST, int THREADS>
+enum TakeFrom { kTakeDevice, kTakeHost, kTakeHost16 };
+template <TakeFrom FROM, int THREADS>
 __global__ __launch_bounds__(THREADS) void take_rows(TakeArgs a)
 {
     constexpr int EACH = 4;
+    auto column = [&](int32_t e) -> int32_t { return FROM == kTakeHost16 ? (int32_t)reinterpret_cast<const uint16_t*>(a.cols)[e] : a.cols[e]; };
     extern __shared__ uint32_t take_bits[];
     __shared__ int32_t rs[66];
     __shared__ uint32_t flag_s;
@@ -126,11 +129,11 @@ __global__ __launch_bounds__(THREADS) void take_rows(TakeArgs a)
 #pragma unroll
         for (int x = 0; x < EACH; ++x) {
             const int32_t i = e + x * THREADS < end ? e + x * THREADS : end - 1;
-            c[x] = a.cols[i];
+            c[x] = column(i);
             if (a.row_cols) v[x] = a.vals[i];
             // the column before it
-            if constexpr (FROM_HOST) {
-                const int32_t first = (tid & 63) == 0 && i > beg ? a.cols[i - 1] : 0;
+            if constexpr (FROM != kTakeDevice) {
+                const int32_t first = (tid & 63) == 0 && i > beg ? column(i - 1) : 0;
                 before[x] = __builtin_amdgcn_update_dpp(first, c[x], 0x138, 0xf, 0xf, false);       // wave_shr:1
             } else {
                 before[x] = a.cols[i > beg ? i - 1 : i];

@@ -85,3 +85,14 @@ def test_one_launch_from_host_memory(m, k, p, lens):
         C64, D64 = orc.spdm_csr(w.k, w.N, w.row_ptr, w.col_idx, w.vals, w.B)
         err, bad = orc.max_scaled_error(C.cpu().numpy(), C64, D64)
         assert bad == 0 and err < 2e-6, (err, bad)
+
+
+@pytest.mark.parametrize("m,k", [(3000, 4000), (33, 65536), (33, 65537)])
+def test_two_launches_from_host_memory(m, k):
+    """Columns of 16 bits as far as they go, and of 32 bits beyond."""
+    print(f"host stage, two launches: {m}x{k}", flush=True)
+    w = workloads.uniform_random(m, k, 1, 1 - 100000 / (m * k), seed=m)
+    w.col_idx[w.row_ptr[1] - 1] = k - 1                        # (the last column, in order)
+    handles = []
+    _convert_many([w], 32, handles)
+    _check(handles, 32)
