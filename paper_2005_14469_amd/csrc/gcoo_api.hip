@@ -760,6 +760,7 @@ struct gcoo_matrix {
     bool has_sched;            // the run schedule of the register kernel was built
     bool has_share;            // the share schedule was built
     bool from_csr = false;     // the input was CSR (as opposed to dense)
+    bool long_places = false;  // the long rows are in places of their groups, not counted (RowsArgs)
     bool share_preferred;      // GCOO_VARIANT_SHARE can be asked for and is what gcoo_spdm_pick() answers where B is wide enough
     int device;
     char* base;
@@ -848,8 +849,9 @@ hipError_t band_fill_lds_limit()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (done[dev].load(std::memory_order_acquire)) return hipSuccess;
-    for (const void* f : {reinterpret_cast<const void*>(&gcoo::band_fill<4, 512, 8>), reinterpret_cast<const void*>(&gcoo::band_fill<4, 1024, 4>),
-                          reinterpret_cast<const void*>(&gcoo::band_fill<2, 1024, 4>)}) {
+    for (const void* f : {reinterpret_cast<const void*>(&gcoo::band_fill<4, 512, 8, false>), reinterpret_cast<const void*>(&gcoo::band_fill<4, 1024, 4, false>),
+                          reinterpret_cast<const void*>(&gcoo::band_fill<2, 1024, 4, false>), reinterpret_cast<const void*>(&gcoo::band_fill<4, 512, 8, true>),
+                          reinterpret_cast<const void*>(&gcoo::band_fill<4, 1024, 4, true>), reinterpret_cast<const void*>(&gcoo::band_fill<2, 1024, 4, true>)}) {
         e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBandFillMaxLds);
         if (e != hipSuccess) return e;
     }
@@ -871,8 +873,8 @@ gcoo::FillArgs fill_args(const gcoo_matrix* h, const char* scratch, bool both)
 
 // The kernel-private schedules that a conversion ends with (see share_schedule_wanted(), run_schedule_wanted() and band_plan()), on the
 // conversion's stream, so that the handle is never written again.
-// `scratch`: the conversion's scratch area (the counter of share_fill sits in it).  `marked`: the bitmaps of the band schedule are there.
-int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false, bool filled = false)
+// `scratch`: the conversion's scratch area (the counter of share_fill sits in it).  `marked`: the bitmaps of the band schedule are there; `grouped`: those of fill_dense_groups().
+int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bool marked = false, bool filled = false, bool grouped = false)
 {
     uint32_t* share_alloc = reinterpret_cast<uint32_t*>(scratch + h->L.share_alloc);
     if (h->g > 0 && h->has_sched) {
@@ -928,9 +930,14 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
                                                                                                                 gcoo::band_heavy(h->nnz, marks), h->uneven());
         HIP_TRY(hipGetLastError());
         const bool large = v == 2 || h->nnz / lists > 4096;
-        const gcoo::FillArgs f = fill_args(h, scratch, false);
+        gcoo::FillArgs f = fill_args(h, scratch, false);
+        if (grouped) { f.out = rows_out(h); f.g = h->g; f.p = h->p; f.says_uneven = h->uneven(); f.flag_count = (int32_t)marks; f.heavy = (uint32_t)gcoo::band_heavy(h->nnz, marks); }
         HIP_TRY(band_fill_lds_limit());
-        (v == 2 ? gcoo::band_fill<2, 1024, 4> : (large ? gcoo::band_fill<4, 1024, 4> : gcoo::band_fill<4, 512, 8>))
+        auto pick = [&](auto by_groups) {
+            constexpr bool GROUPED = decltype(by_groups)::value;
+            return v == 2 ? gcoo::band_fill<2, 1024, 4, GROUPED> : (large ? gcoo::band_fill<4, 1024, 4, GROUPED> : gcoo::band_fill<4, 512, 8, GROUPED>);
+        };
+        (grouped ? pick(std::true_type{}) : pick(std::false_type{}))
             <<<dim3(lists), dim3(large ? 1024 : 512), gcoo::band_fill_lds(h->k, f.chunk, v), s>>>(f);
         HIP_TRY(hipGetLastError());
     }
@@ -1093,6 +1100,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
     bool marked = false;
     const int words = p <= 32 ? 1 : (p <= 64 ? 2 : 8);
     if (L.by_masks && L.plan.fused) {
+        h->long_places = true;
         gcoo::OrderArgs o{};
         o.cols = d_cols; o.vals = d_vals; o.m = m; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.out = rows_out(h);
         o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
@@ -1283,6 +1291,26 @@ namespace {
 // 8000 x 8000 takes 171 us instead of 161 at 0.5 % and 267 instead of 252 at 5 %.
 bool dense_masks_wanted(int32_t p) { return p >= 8 && p <= 64; }
 
+// Workgroups of fill_dense_groups() to a group: as many, up to four, as leave each no more entries than its LDS holds in row order, and 256 columns at least.  Each goes through all masks of its
+// group, so that more are slower where one holds all (conversion with its count, us, 1, 2 and 4; entries per group in brackets: 4000 x 4000, 2 % (2560): 47.2 48.5 49.3; 5 % (6400): 58.5 54.6 55.1;
+// 10 % (12800): 79.4 72.4 65.1; 6000 x 1000, 10 % (3200): 27.7 31.5 36.6; 500 x 4000, 20 % (25600): 84 62.7 48; 64 rows per group, 2000 x 2000, 2 % (2560): 30.2 27.2 28.4).
+int32_t dense_groups_split(int64_t k, int64_t mean, int32_t p)
+{
+    const int64_t most = gcoo::dense_group_list(p), entries = mean + mean / 16;
+    const int32_t split = entries <= most ? 1 : (entries <= 2 * most ? 2 : 4);
+    return k <= 256 ? 1 : (k <= 512 && split > 2 ? 2 : split);
+}
+// Whether the fill, the order by rows and the bitmaps of the bands are one launch: where a workgroup has all columns of a group in its LDS, but not for many groups of a few rows each, which cost
+// a workgroup of 1024 threads however little is in them (conversion with its count, us, three launches and one: 12000 x 3000, 1 %, 8 rows per group: 91 100; 20000 x 2000, 0.2 %, 16 rows: 57.1 57.6; 2000 x 2000, 1 %,
+// 8 rows: 22.9 21.8).
+bool dense_groups_wanted(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band)
+{
+    const int64_t g = (m + p - 1) / p;
+    if (k > gcoo::kDenseWindow || (p < 24 && g > 512)) return false;
+    // a group lies in two blocks at the most, and the bitmaps go where the lists' would, into three words per entry
+    return band.h == 0 || (gcoo::kBandWaves * band.h >= p && (g + gcoo::band_blocks(m, band.h)) * ((k + 31) / 32) <= 3 * nnz);
+}
+
 // The counts of a dense matrix, at the places where a matrix buffer has them (offsets that do not depend on nnz).
 // `masks`: a buffer that holds them as well, behind the others.
 gcoo::DenseCounts dense_counts(void* buf, const Layout& L, bool masks)
@@ -1346,6 +1374,7 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
     const int64_t nblk = dense_blocks(k, vw);
     const bool masks = counts != dev_buf && dense_masks_wanted(p);        // (in a buffer of its own the matrix lies where they would)
     const gcoo::DenseCounts from = dense_counts(const_cast<void*>(counts), h->L, masks), to = dense_counts(dev_buf, h->L, false);
+    const bool grouped = masks && g > 0 && k > 0 && dense_groups_wanted(m, k, nnz, p, h->L.band) && !h->has_share;
     // Groups of more than 64 rows: the regrouped copy is counted on the device alone, behind the fill, which clears its ticket.
     const size_t own = al(h->L.total);
     char* inner_buf = nullptr;
@@ -1357,7 +1386,14 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
     {
         const dim3 grid((unsigned)(g * nblk > 0 ? g * nblk : 1)), block(gcoo::kDenseThreads);
         const bool small = p <= 64;
-        if (masks)
+        if (grouped) {
+            const bool band = h->L.band.h > 0;
+            h->long_places = !band;
+            const int32_t split = dense_groups_split(k, nnz / g, p);
+            (split > 1 ? (p <= 32 ? gcoo::fill_dense_groups<32, true> : gcoo::fill_dense_groups<64, true>) : (p <= 32 ? gcoo::fill_dense_groups<32, false> : gcoo::fill_dense_groups<64, false>))<<<dim3((unsigned)(g * split)), dim3(gcoo::kDenseGroupThreads), 0, s>>>(
+                A_dev, lda, m, k, p, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols(), rows_out(h), !band,
+                band ? reinterpret_cast<uint32_t*>(h->base + h->L.persistent + h->L.tmp_cols) : nullptr, gcoo::kBandWaves * h->L.band.h, split);
+        } else if (masks)
             (vw == 4 ? gcoo::fill_dense_masked<4> : gcoo::fill_dense_masked<1>)<<<grid, block, 0, s>>>(
                 A_dev, lda, k, p, nblk, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols());
         else (vw == 4 ? (small ? gcoo::fill_dense_blocks<4, true> : gcoo::fill_dense_blocks<4, false>)
@@ -1366,14 +1402,14 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "fill_dense_blocks"); }
     }
-    if (g > 0 && h->has_rows()) {
+    if (g > 0 && h->has_rows() && !grouped) {
         gcoo::sort_groups_by_col_digit<gcoo::kSortByRow, gcoo::kSortWaves><<<dim3((unsigned)g), dim3(gcoo::kSortWaves * gcoo::kWave), 0, s>>>(
             h->gIdxes(), nullptr, m, p, h->cols(), h->rows(), h->values(), h->row_cols(), nullptr, h->row_vals(), 0, 0, (int32_t)k,
             nullptr, rows_out(h));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { delete h; return hip_fail(e, "sort_groups_by_col_digit"); }
     }
-    rc = launch_build_schedule(h, h->base + h->L.persistent, s);
+    rc = launch_build_schedule(h, h->base + h->L.persistent, s, grouped && h->L.band.h > 0, false, grouped);
     if (rc != GCOO_OK) { delete h; return rc; }
     if (inner_buf) {
         rc = launch_dense_count(m, k, A_dev, lda, kInnerP, inner_buf, false, {inner_ticket, 1}, nullptr, s);
@@ -1609,7 +1645,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     if (kernel == GCOO_KERNEL_ROWS || kernel == GCOO_KERNEL_BAND) {
         gcoo::RowsArgs rows{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
                             A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz), 0};
-        if (A->from_csr && A->L.by_masks && A->L.plan.fused) {
+        if (A->long_places) {
             // no places are looked at where only a row that repeats columns could be long
             const bool some = A->k > rows.long_row;
             rows.long_count = nullptr;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "gcoo_band.hpp"
+#include "gcoo_build_kernels.hpp"
 
 namespace gcoo {
 
@@ -80,17 +81,9 @@ __device__ __forceinline__ int32_t band_block_scan(int32_t mine, int32_t* wsum, 
 template <int LANES>
 __device__ __forceinline__ int32_t band_row_scan(int32_t x, int32_t* total)
 {
-    int32_t incl = x;
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
-    if constexpr (LANES == 32) {
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15, into rows 1 and 3
-        *total = __shfl(incl, (int)(threadIdx.x & 63u) | 31, 64);
-    } else {
-        *total = __builtin_amdgcn_update_dpp(0, incl, 0x15f, 0xf, 0xf, true);  // row_newbcast:15
-    }
+    const int32_t incl = lanes_scan<LANES>(x);
+    if constexpr (LANES == 32) *total = __shfl(incl, (int)(threadIdx.x & 63u) | 31, 64);
+    else *total = __builtin_amdgcn_update_dpp(0, incl, 0x15f, 0xf, 0xf, true);  // row_newbcast:15
     return incl - x;
 }
 
@@ -153,8 +146,14 @@ struct FillArgs {
     const uint32_t* flags;     // the word of every list, in some of which a bit of `heavy` says so
     int32_t flag_count;
     uint32_t heavy;
+    RowsOut out;               // GROUPED only
+    uint32_t* says_uneven;
+    int64_t g;
+    int32_t p;
 };
-template <int V, int kBandBuildThreads, int EACH>
+// GROUPED: behind fill_dense_groups().  The bitmaps are those of the groups, and no launch before this one could list the long rows or say that the lists are uneven, `flag_count` lists (as in
+// band_mark) of at most `heavy` entries where they are not: this one does, the list of a wave for its own rows and the first one for the matrix.
+template <int V, int kBandBuildThreads, int EACH, bool GROUPED = false>
 __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
 {
     typedef BandCut<V> Cut;
@@ -182,16 +181,33 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     uint32_t* place_of = (uint32_t*)(rows_of + chunk);      // pairs | singles << 16 of the band in front of five columns
     // What waits for nothing but the rows' bounds is asked for first: the bitmaps, then the entries.
     uint32_t by_rows = 0u;
-    if (a.uneven) by_rows = *a.uneven;
+    if constexpr (GROUPED) {
+        const int64_t each = a.h / band_lists_of(V);
+        for (int64_t i = tid; i < a.flag_count; i += kBandBuildThreads) {
+            const int64_t b = i * each < m ? i * each : m, e = b + each < m ? b + each : m;
+            by_rows |= (uint32_t)(row_start[e] - row_start[b]) > a.heavy;
+        }
+    } else if (a.uneven) by_rows = *a.uneven;
     else
         for (int32_t i = tid; i < a.flag_count; i += kBandBuildThreads) by_rows |= a.flags[i] & a.heavy;
     const BandList l = band_list(row_start, m, h, list);
-    uint32_t mine_bits = 0u;
-    if (tid < nbw) {
+    // word i of the block's columns
+    auto columns = [&](int32_t i) {
+        uint32_t b = 0u;
+        if constexpr (GROUPED) {
+            const int64_t r0 = Q * kBandWaves * h, r1 = r0 + kBandWaves * h < m ? r0 + kBandWaves * h : m, q0 = r0 / a.p, q1 = (r1 - 1) / a.p;
+            b = parts[(q0 * a.p == r0 ? q0 : a.g + Q) * nbw + i];
+            for (int64_t q = q0 + 1; q <= q1; q += 8)
 #pragma unroll
-        for (int x = 0; x < kParts; ++x) mine_bits |= parts[(Q * kParts + x) * nbw + tid];
-    }
-    if (a.uneven && by_rows != 0u) return;
+                for (int x = 0; x < 8; ++x) b |= parts[(q + x < q1 ? q + x : q1) * nbw + i];      // (the last one again)
+        } else {
+#pragma unroll
+            for (int x = 0; x < kParts; ++x) b |= parts[(Q * kParts + x) * nbw + i];
+        }
+        return b;
+    };
+    const uint32_t mine_bits = tid < nbw ? columns(tid) : 0u;
+    if (!GROUPED && a.uneven && by_rows != 0u) return;
     const int32_t n = l.end - l.beg, begins = lane < l.rows ? row_start[l.r0 + lane] : INT32_MAX;
     const int32_t* list_cols = row_cols + l.beg;
     const float* list_vals = row_vals + l.beg;
@@ -208,14 +224,15 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     if (n > 0) take(0);
     for (int32_t i = tid; i < chunk; i += kBandBuildThreads) rows_of[i] = 0;
     if (tid < nbw) words[tid].x = mine_bits;
-    for (int32_t i = tid + kBandBuildThreads; i < nbw; i += kBandBuildThreads) {
-        uint32_t b = 0u;
-#pragma unroll
-        for (int x = 0; x < kParts; ++x) b |= parts[(Q * kParts + x) * nbw + i];
-        words[i].x = b;
-    }
+    for (int32_t i = tid + kBandBuildThreads; i < nbw; i += kBandBuildThreads) words[i].x = columns(i);
     if (tid == 0) repeated_s = 0;
-    if (__syncthreads_or((int)by_rows)) return;             // the whole workgroup
+    if constexpr (GROUPED) {
+        if (wv == 0 && lane < l.rows) list_long_row(a.out, (int32_t)l.r0 + lane, row_start[l.r0 + lane + 1] - begins);
+    }
+    if (__syncthreads_or((int)by_rows)) {                   // the whole workgroup
+        if (GROUPED && list == 0 && tid == 0) *a.says_uneven = 1u;      // (zero so far)
+        return;
+    }
     {
         const int32_t per = (nbw + kBandBuildThreads - 1) / kBandBuildThreads;
         const int32_t i0 = tid * per, i1 = i0 + per < nbw ? i0 + per : nbw;
@@ -406,10 +423,10 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     }
 }
 
-template <int V, int kBandBuildThreads, int EACH>
+template <int V, int kBandBuildThreads, int EACH, bool GROUPED>
 __global__ __launch_bounds__(kBandBuildThreads) void band_fill(FillArgs a)
 {
-    band_fill_list<V, kBandBuildThreads, EACH>(a, blockIdx.x);
+    band_fill_list<V, kBandBuildThreads, EACH, GROUPED>(a, blockIdx.x);
 }
 
 }  // namespace gcoo

@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace gcoo {
 
 constexpr int kWave = 64;
@@ -589,10 +591,11 @@ __global__ __launch_bounds__(kDenseThreads) void count_dense_blocks(const float*
 // function of the matrix alone.
 // SMALL (at most 64 rows per group): a first walk leaves a bit per element behind, and only the elements that are entries
 // are read a second time, the next one of each column together; taller groups walk the columns again.
-// (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)  Where the count has left the bits in memory fill_dense_masked() does this step.
+// (4000 x 4000, 2 %: 32 us walking twice, 19 with the bits.)  Where the count has left the bits in memory fill_dense_masked() or fill_dense_groups() does this step.
 // The launch also puts the index arrays in place where they were counted elsewhere (`from`), and clears zeroed[0..3] and, where given, the
 // ticket of the count that follows.
 // ---------------------------------------------------------------------------------------------
+template <int THREADS = kDenseThreads>
 __device__ __forceinline__ void place_dense_counts(const DenseCounts& from, const DenseCounts& to, int64_t g, uint32_t* zeroed, unsigned long long* ticket)
 {
     const int tid = threadIdx.x;
@@ -600,7 +603,7 @@ __device__ __forceinline__ void place_dense_counts(const DenseCounts& from, cons
     if (blockIdx.x == 0 && tid == 4 && ticket) *ticket = 0ull;
     if (from.gIdxes != to.gIdxes) {
         if (blockIdx.x == 0 && tid < 2) to.stats[tid] = from.stats[tid];
-        for (int64_t q = (int64_t)blockIdx.x * kDenseThreads + tid; q <= g; q += (int64_t)gridDim.x * kDenseThreads) {
+        for (int64_t q = (int64_t)blockIdx.x * THREADS + tid; q <= g; q += (int64_t)gridDim.x * THREADS) {
             to.gIdxes[q] = from.gIdxes[q];
             if (q < g) to.nnzPerGroup[q] = from.nnzPerGroup[q];
         }
@@ -772,6 +775,171 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_masked(const float* 
             cols[to_slot] = (int32_t)c0 + cc;
         }
         __syncthreads();
+    }
+}
+
+// Inclusive prefix sum over every stretch of LANES (16, 32 or 64) lanes of a whole wave.
+template <int LANES>
+__device__ __forceinline__ int32_t lanes_scan(int32_t x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    if constexpr (LANES >= 32) x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15, into rows 1 and 3
+    if constexpr (LANES == 64) x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31, into rows 2 and 3
+    return x;
+}
+
+// The same and the entries in row order for a matrix of up to kDenseWindow columns, `split` workgroups per group, each with a part of the columns: what a sort of the group by row would find follows from
+// the masks as well.  The entries of the group, as a bit per row and column in LDS, say how many of its row lie in front of each; where the part's entries fit, they are put into row order
+// there and written whole lines at a time.
+// `parts`, for the band schedule: the columns of each group as a bitmap; those of a group that lies across the border of two blocks of `block_rows` rows, of no more than one, as two, the rows of the later block b
+// in parts[g + b].  `places`: the long rows are listed in places of their group (RowsArgs), else by a later launch, since this one clears their count.
+// Bound: a chain of latencies (masks, list, entries behind the L2), a third of it the loops over a thread's bits and the sums, 16 waves side by side.  Two workgroups to a compute unit, hence 64 registers.
+// Conversion with its count (us; fill, sort by row and, for bands, the bitmaps as launches of their own, and so): 4000 x 4000, 2 %: 48.7 46.9; 10 %: 83.2 65.1; 1000 x 1000, 2 %: 24.0 22.2; 300 x 300, 5 %: 23.1 21.0;
+// 500 x 4000, 20 %: 78.9 47.3; 6000 x 3000, 20 %: 168 123; 14000 x 4000, 0.5 %: 83.8 83.1; 20 %: 517 352.
+constexpr int kDenseGroupThreads = 1024, kDenseWindow = 4 * kDenseGroupThreads;
+constexpr int dense_group_list(int rows) { return rows <= 32 ? 4096 : 2048; }      // entries that a workgroup has in LDS at a time
+template <int ROWS, bool SPLIT>
+__global__ __launch_bounds__(kDenseGroupThreads, 8) void fill_dense_groups(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k, int32_t p, int64_t g,
+                                                                         DenseCounts from, DenseCounts to, uint32_t* __restrict__ zeroed,
+                                                                         float* __restrict__ values, int32_t* __restrict__ rows, int32_t* __restrict__ cols,
+                                                                         RowsOut out, bool places, uint32_t* __restrict__ parts, int32_t block_rows, int32_t split)
+{
+    constexpr int THREADS = kDenseGroupThreads, WAVES = THREADS / kWave, WORDS = kDenseWindow / 32, PITCH = WORDS + 1;      // (a word more keeps the rows on different banks)
+    constexpr int LIST = dense_group_list(ROWS), EACH = LIST / THREADS;
+    constexpr int PER_ROW = THREADS / ROWS, PER_THREAD = WORDS / PER_ROW;      // threads that count a row, words of it for each
+    static_assert(WAVES == 16, "");
+    typedef typename std::conditional<ROWS == 32, uint32_t, uint64_t>::type Mask;
+    __shared__ uint32_t bits_s[ROWS * PITCH], list[LIST];
+    typedef typename std::conditional<SPLIT, uint32_t, uint16_t>::type Place;
+    __shared__ Place staged_s[LIST];                          // SPLIT: as in `list`, else the column
+    __shared__ uint16_t before_s[ROWS * WORDS];               // entries of the row in front of a word
+    __shared__ int32_t wsum[WAVES], row_n[ROWS], row_to[ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    place_dense_counts<THREADS>(from, to, g, zeroed, nullptr);
+    const int64_t q = SPLIT ? blockIdx.x / split : blockIdx.x, r0 = q * p;
+    const int32_t part = SPLIT ? (int32_t)(blockIdx.x - q * split) : 0;
+    const int32_t nr = (int32_t)(m - r0 < p ? m - r0 : p), g0 = from.gIdxes[q], g1 = from.gIdxes[q + 1];
+    Mask bits[4];                                             // of the thread's columns, four side by side
+    int32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bits[u] = 4 * tid + u < k ? (Mask)from.masks[q * k + 4 * tid + u] : 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) mine += ROWS == 32 ? __popc((uint32_t)bits[u]) : __popcll(bits[u]);
+    const int32_t incl = lanes_scan<64>(mine);
+    if (lane == 63) wsum[w] = incl;
+    for (int i = tid; i < ROWS * PITCH; i += THREADS) bits_s[i] = 0u;
+    __syncthreads();
+    // The workgroup's part of the columns: those of the waves [w0, w1), 256 each.
+    const int32_t each = ((int32_t)((k + 255) / 256) + split - 1) / split, w0 = !SPLIT ? 0 : part * each < WAVES ? part * each : WAVES, w1 = !SPLIT ? WAVES : w0 + each < WAVES ? w0 + each : WAVES;
+    const int32_t waves = lanes_scan<16>(wsum[lane & 15]);
+    auto upto = [&](int32_t wave) { return wave > 0 ? __builtin_amdgcn_readlane(waves, wave - 1) : 0; };
+    const int32_t before = SPLIT ? upto(w0) : 0, total = upto(w1) - before, begin = incl - mine + upto(w) - before;      // of the part, of the thread's entries in it
+    // The entries `done` to done + LIST, column by column: row, and column.  The first time each leaves its bit for the row.
+    auto place = [&](int32_t done, bool first) {
+        int32_t at = begin - done;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (Mask b = bits[u]; b; b &= b - 1, ++at) {
+                const uint32_t r = (uint32_t)(ROWS == 32 ? __ffs((uint32_t)b) : __ffsll((unsigned long long)b)) - 1u;
+                if (first) atomicOr(&bits_s[r * PITCH + tid / 8], 1u << ((4 * tid + u) & 31));
+                if ((!SPLIT || (w >= w0 && w < w1)) && (uint32_t)at < (uint32_t)LIST) list[at] = r * kDenseWindow + (uint32_t)(4 * tid + u);
+            }
+    };
+    place(0, true);
+    __syncthreads();
+    const bool staged = total <= LIST;                        // the row order goes through LDS and out in whole lines
+    const float* band = A + r0 * lda;
+    int32_t row_at = 0, row_from = 0;                         // of row `lane`: its place in the row order, what takes a place in it to one in the staged part
+    for (int32_t done = 0; done < total || done == 0; done += LIST) {
+        const int32_t n = total - done < LIST ? total - done : LIST;
+        float v[EACH];
+        uint32_t e[EACH];
+        if (done > 0) {
+            __syncthreads();
+            place(done, false);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int x = 0; x < EACH; ++x) {
+            e[x] = x * THREADS + tid < n ? list[x * THREADS + tid] : 0u;
+            v[x] = n > 0 ? band[(int64_t)(e[x] / kDenseWindow) * lda + e[x] % kDenseWindow] : 0.0f;
+        }
+        if (done == 0) {                                      // (while the values are on their way)
+            const int r = tid / PER_ROW, j = tid % PER_ROW;
+            int32_t in_front[PER_THREAD], sum = 0;
+#pragma unroll
+            for (int x = 0; x < PER_THREAD; ++x) {
+                in_front[x] = sum;
+                sum += __popc(bits_s[r * PITCH + j * PER_THREAD + x]);
+            }
+            const int32_t so_far = lanes_scan<PER_ROW>(sum);
+            const int32_t word = tid - (THREADS - WORDS), nbw = (int32_t)((k + 31) / 32);
+            if (parts && part == 0 && word >= 0 && word < nbw) {
+                const int64_t later = r0 / block_rows + 1;
+                const int32_t mid = later * block_rows - r0 < nr ? (int32_t)(later * block_rows - r0) : nr;
+                uint32_t here = 0u, beyond = 0u;
+#pragma unroll 4
+                for (int i = 0; i < ROWS; ++i) (i < mid ? here : beyond) |= bits_s[i * PITCH + word];
+                parts[q * nbw + word] = here;
+                if (mid < nr) parts[(g + later) * nbw + word] = beyond;
+            }
+#pragma unroll
+            for (int x = 0; x < PER_THREAD; ++x) before_s[r * WORDS + j * PER_THREAD + x] = (uint16_t)(so_far - sum + in_front[x]);
+            if (j == PER_ROW - 1) row_n[r] = so_far;
+            __syncthreads();
+            const int32_t of_row = lane < ROWS ? row_n[lane] : 0;
+            row_at = g0 + lanes_scan<64>(of_row) - of_row;
+            if constexpr (SPLIT) {
+                const int32_t skip = lane < ROWS && w0 > 0 ? (w0 < WAVES ? (int32_t)before_s[lane * WORDS + 8 * w0] : of_row) : 0;
+                const int32_t here = (lane < ROWS && w1 < WAVES ? (int32_t)before_s[lane * WORDS + 8 * w1] : of_row) - skip;
+                row_from = lanes_scan<64>(here) - here - skip;
+                if (w == 0 && lane < ROWS) row_to[lane] = row_at - row_from;
+            } else {
+                row_from = row_at - g0;
+            }
+            if (w == 0 && part == 0) {
+                if (lane < nr) out.start[r0 + lane] = row_at;
+                if (lane == 0 && q == g - 1) out.start[m] = g1;
+                if (places) {
+                    // as in order_groups: a group has the places that the multiples of long_row in its stretch give it, never fewer than rows of more entries than that
+                    const int32_t l0 = g0 / out.long_row, l1 = g1 / out.long_row;
+                    const uint64_t is = __ballot(lane < nr && of_row > out.long_row);
+                    const int32_t at = l0 + __popcll(is & lanemask_lt());
+                    if ((is >> lane & 1) && at < l1) out.long_rows[at] = (int32_t)r0 + lane;
+                    for (int32_t i = l0 + __popcll(is) + lane; i < l1; i += kWave) out.long_rows[i] = -1;
+                }
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < EACH; ++x) {
+            const uint32_t r = e[x] / kDenseWindow, c = e[x] % kDenseWindow;
+            const int32_t by_row = __shfl(staged ? row_from : row_at, (int)r, kWave) + (int32_t)before_s[r * WORDS + c / 32] + __popc(bits_s[r * PITCH + c / 32] & ((1u << (c & 31u)) - 1u));
+            if (x * THREADS + tid < n) {
+                const int32_t slot = g0 + before + done + x * THREADS + tid;
+                values[slot] = v[x];
+                rows[slot] = (int32_t)(r0 + r);
+                cols[slot] = (int32_t)c;
+                if (staged) {
+                    list[by_row] = __float_as_uint(v[x]);
+                    staged_s[by_row] = (Place)(SPLIT ? e[x] : c);
+                } else {
+                    out.cols[by_row] = (int32_t)c;
+                    out.vals[by_row] = v[x];
+                }
+            }
+        }
+    }
+    if (staged) {
+        __syncthreads();
+        for (int32_t i = tid; i < total; i += THREADS) {
+            const uint32_t e = staged_s[i];
+            const int32_t to_slot = (SPLIT ? row_to[e / kDenseWindow] : g0) + i;
+            out.cols[to_slot] = (int32_t)(e % kDenseWindow);
+            out.vals[to_slot] = __uint_as_float(list[i]);
+        }
     }
 }
 

@@ -161,3 +161,32 @@ def test_fill_of_tall_groups_in_a_graph(m, k, p):
         assert torch.equal(Cg, Ce), replay
         ref = A.double() @ B.double()
         assert ((Cg.double() - ref).abs().max() / ref.abs().max()).item() < 2e-6
+
+
+@pytest.mark.parametrize("m,k,p,density,long_rows", [
+    (70, 255, 32, 0.3, 0), (69, 256, 32, 0.9, 1), (40, 300, 8, 0.2, 1), (130, 513, 31, 1.0, 0),
+    (130, 4095, 31, 0.02, 1), (130, 4096, 32, 0.029, 0), (130, 4096, 32, 0.031, 2), (130, 4097, 32, 0.02, 1), (100, 2000, 33, 0.03, 1), (100, 2000, 64, 0.02, 0), (67, 4096, 64, 0.5, 0),
+    (2100, 2600, 32, 0.05, 0), (2113, 2600, 31, 0.05, 3), (2100, 2500, 40, 0.08, 70), (1500, 4096, 64, 0.03, 5), (1501, 2900, 9, 0.06, 0)])
+def test_row_order_and_bands_of_a_dense_matrix(m, k, p, density, long_rows):
+    """The order by rows, the rows that are long and the columns of the bands come with the fill where the count left its masks, up to 4096 columns: one, two and four workgroups to a group, entries that fit
+    the LDS and that do not, groups across two blocks of the band schedule, rows many times as long as the others, few and so many together that no bands are built.  Whole numbers, so that the
+    product is exact: by rows and, the widest of a matrix of some size, by the band schedule."""
+    print(f"dense rows and bands: {m}x{k} p={p} density={density} long={long_rows}", flush=True)
+    rng = np.random.default_rng(m + k + p)
+    Ah = (rng.integers(1, 8, (m, k)) * (rng.random((m, k)) < density)).astype(np.float32)
+    Ah[rng.integers(0, m, 3)] = 0.0
+    at = m // 2
+    Ah[at:at + long_rows] = rng.integers(1, 8, (min(long_rows, m - at), k))
+    A = torch.from_numpy(Ah).to(DEV)
+    B = torch.from_numpy(rng.integers(-8, 8, (k, 2504)).astype(np.float32)).to(DEV)
+    want = torch.from_numpy(Ah.astype(np.float64) @ B.cpu().numpy().astype(np.float64)).to(DEV)
+    e, ref = binding.gcoo_from_dense(A, p).export(), orc.gcoo_from_dense(Ah, p)
+    assert np.array_equal(e["values"], ref.values) and np.array_equal(e["rows"], ref.rows) and np.array_equal(e["cols"], ref.cols)
+    for _ in range(2):
+        H = binding.gcoo_from_dense(A, p)
+        for N in (8, 64, 2504):
+            C = torch.full((m, N), 7.0, device=DEV)
+            kernel = binding.gcoo_spdm_kernel(H, B[:, :N], C)
+            binding.gcoo_spdm(H, B[:, :N], C)
+            assert torch.equal(C.double(), want[:, :N]), (N, kernel)
+        assert kernel == binding.KERNEL_BAND or m < 1500
