@@ -57,26 +57,6 @@ __global__ __launch_bounds__(kBandMarkThreads) void band_mark(const int32_t* __r
     for (int32_t i = threadIdx.x; i < nbw; i += kBandMarkThreads) out[i] = band_lds[i];
 }
 
-// Exclusive prefix sum over the workgroup; the total in *total (shared).
-template <int kBandBuildThreads>
-__device__ __forceinline__ int32_t band_block_scan(int32_t mine, int32_t* wsum, int32_t* total)
-{
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int32_t incl = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t t = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += t;
-    }
-    if (lane == 63) wsum[wv] = incl;
-    __syncthreads();
-    int32_t off = incl - mine;
-    for (int j = 0; j < wv; ++j) off += wsum[j];
-    if (threadIdx.x == kBandBuildThreads - 1) *total = off + mine;
-    __syncthreads();
-    return off;
-}
-
 // Exclusive prefix sum of x over every stretch of LANES (16 or 32) lanes; the stretch's total in *total.
 template <int LANES>
 __device__ __forceinline__ int32_t band_row_scan(int32_t x, int32_t* total)
@@ -165,7 +145,7 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     constexpr Mask kRowsOnly = ((Mask)1 << Cut::kMaxH) - 1;
     static_assert(kBandChunk % kBandRows == 0 && kBandChunkBands <= kBandBuildThreads && (kLanes == 16 || kLanes == 32), "");
     extern __shared__ __attribute__((aligned(16))) uint32_t band_lds[];
-    __shared__ int32_t wsum[kBandBuildWaves], total_s, repeated_s;
+    __shared__ int32_t wsum[kBandBuildWaves], any_s[kBandBuildWaves], repeated_s;
     __shared__ int2 band_s[kBandChunkBands];                // first unit and pairs of a band
     __shared__ int32_t singles_s[kBandChunkBands];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -229,22 +209,23 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     if constexpr (GROUPED) {
         if (wv == 0 && lane < l.rows) list_long_row(a.out, (int32_t)l.r0 + lane, row_start[l.r0 + lane + 1] - begins);
     }
-    if (__syncthreads_or((int)by_rows)) {                   // the whole workgroup
+    if (block_any<kBandBuildWaves>(by_rows != 0u, any_s)) {                   // the whole workgroup
         if (GROUPED && list == 0 && tid == 0) *a.says_uneven = 1u;      // (zero so far)
         return;
     }
+    int32_t nU;
     {
         const int32_t per = (nbw + kBandBuildThreads - 1) / kBandBuildThreads;
         const int32_t i0 = tid * per, i1 = i0 + per < nbw ? i0 + per : nbw;
         int32_t mine = 0;
         for (int32_t i = i0; i < i1; ++i) mine += __popc(words[i].x);
-        int32_t at = band_block_scan<kBandBuildThreads>(mine, wsum, &total_s);
+        int32_t at = block_scan<kBandBuildWaves>(mine, wsum, &nU);
         for (int32_t i = i0; i < i1; ++i) {
             words[i].y = (uint32_t)at;
             at += __popc(words[i].x);
         }
     }
-    const int32_t nU = total_s, NB = (nU + kBandRows - 1) / kBandRows;
+    const int32_t NB = (nU + kBandRows - 1) / kBandRows;
     __syncthreads();
     // A list has as many units as its entries and bands can make (band_units()) for itself, so that no list waits for another to be counted.
     const int64_t most = band_max_bands(k, V) * list, base = l.beg / 16 + most + (most < l.beg ? most : l.beg);
@@ -359,17 +340,17 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
         }
         __syncthreads();
         // units in front of every band of the chunk
+        int32_t units_here;
         {
             const int32_t ps = tid < bands ? (band_s[tid].y + 1) / 2 : 0, ss = tid < bands ? (singles_s[tid] + 3) / 4 : 0;
             const int32_t mine = tid < bands ? (ps + ss > 0 ? (ps + ss + 3) / 4 : 1) : 0;
-            const int32_t off = band_block_scan<kBandBuildThreads>(mine, wsum, &total_s);
+            const int32_t off = block_scan<kBandBuildWaves>(mine, wsum, &units_here);
             if (tid < bands) {
                 band_s[tid].x = off;
                 hd[(b0 + tid + 1) * kBandHeadWords + 5] = (uint32_t)ps;
                 hd[(b0 + tid + 1) * kBandHeadWords + 6] = (uint32_t)ss;
             }
         }
-        const int32_t units_here = total_s;
         __syncthreads();
         uint2* chunk_rec = rec + (int64_t)listed * 16;
         listed += units_here;

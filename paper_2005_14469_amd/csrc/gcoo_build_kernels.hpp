@@ -97,6 +97,44 @@ __device__ __forceinline__ uint64_t lanemask_lt()
     return (1ull << (threadIdx.x & 63)) - 1ull;   // one wave per workgroup in the kernels below
 }
 
+// Inclusive prefix sum over every stretch of LANES (16, 32 or 64) lanes of a whole wave.
+template <int LANES>
+__device__ __forceinline__ int32_t lanes_scan(int32_t x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    if constexpr (LANES >= 32) x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15, into rows 1 and 3
+    if constexpr (LANES == 64) x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31, into rows 2 and 3
+    return x;
+}
+
+// Exclusive prefix sum over a workgroup of WAVES whole waves, 16 at the most; the total in *all.  One barrier; `sums` is free again behind the next one.
+template <int WAVES>
+__device__ __forceinline__ int32_t block_scan(int32_t x, int32_t* sums, int32_t* all)
+{
+    static_assert(WAVES <= 16, "");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t incl = lanes_scan<64>(x);
+    if (lane == 63) sums[wave] = incl;
+    __syncthreads();
+    const int32_t waves = lanes_scan<16>(lane < WAVES ? sums[lane] : 0);
+    *all = __builtin_amdgcn_readlane(waves, WAVES - 1);
+    return incl - x + (wave > 0 ? __builtin_amdgcn_readlane(waves, wave - 1) : 0);
+}
+
+// Whether x holds in any thread of it.  One barrier, where __syncthreads_or() has more; `any` as `sums` above.
+template <int WAVES>
+__device__ __forceinline__ bool block_any(bool x, int32_t* any)
+{
+    const int lane = threadIdx.x & 63;
+    const bool mine = __any(x);
+    if (lane == 0) any[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    return __any(lane < WAVES && any[lane] != 0);
+}
+
 // Lanes of the wave whose 8-bit digit equals this lane's, among the lanes in `active`.
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool is_active)
 {
@@ -776,19 +814,6 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_masked(const float* 
         }
         __syncthreads();
     }
-}
-
-// Inclusive prefix sum over every stretch of LANES (16, 32 or 64) lanes of a whole wave.
-template <int LANES>
-__device__ __forceinline__ int32_t lanes_scan(int32_t x)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    if constexpr (LANES >= 32) x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15, into rows 1 and 3
-    if constexpr (LANES == 64) x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31, into rows 2 and 3
-    return x;
 }
 
 // The same and the entries in row order for a matrix of up to kDenseWindow columns, `split` workgroups per group, each with a part of the columns: what a sort of the group by row would find follows from

@@ -216,7 +216,8 @@ inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 // two passes where they are all, the parts are small enough for several workgroups per compute unit, and a part's entries leave LDS in
 // their order, so that the stores are whole lines.
 // (Index, two radix passes and bitmaps before, take_rows and this now: 8000 x 8000, 10 %: 190 -> 78 us; 0.5 %: 28 -> 17; 4000 x 4000,
-// 5 %: 41 -> 19; power-law rows, 16384 x 16384: 65 -> 40.)
+// 5 %: 41 -> 19; power-law rows, 16384 x 16384: 65 -> 40.  The sums over a workgroup by DPP and one barrier each, here and in band_fill_list(), instead of shuffles and up to 16 reads of LDS, conversion and
+// product: 1777 x 2301, 3 %, N = 1117: 33.3 32.9; 4000 x 4000, 5 %: 180.8 179.3; 8000 x 8000, 0.5 %: 298.5 296.2; power-law rows, 16384 x 16384, N = 512: 128.6 127.1.)
 //
 // FUSED (one part per group, no band schedule): there is nothing to know about a group but its rows, so this is the whole conversion, one
 // launch instead of two (256 x 256: 4.2 + 6.4 us before, 6.3 so; order_plan() has more).
@@ -236,7 +237,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     constexpr bool HOST = KIND == kOrderHost, FUSED = KIND == kOrderFused || HOST, RANKED = KIND == kOrderRanked;
     extern __shared__ uint32_t order_lds[];
     __shared__ int32_t seg[ROWS], off[ROWS];     // a row's place among the part's entries (or in the input), and what takes it to the input
-    __shared__ int32_t wsum[WAVES], wsum2[WAVES];
+    __shared__ int32_t wsum[WAVES], wsum2[WAVES], any_s[WAVES];
     __shared__ int32_t below_s, count_s, long_s, group_s[2];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int32_t parts = a.plan.parts, shift = a.plan.shift, ncols = 1 << shift, later = parts - 1;
@@ -307,7 +308,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
         for (int32_t i = tid; i < ncols * WORDS + spare; i += THREADS) mask[i] = 0u;
     }
     // With one part the group is taken in the order of the input and nothing depends on the order in its rows.
-    const bool in_order = !FUSED && parts > 1 && __syncthreads_or((int)(f & kUnsorted)) == 0;
+    const bool in_order = !FUSED && parts > 1 && !block_any<WAVES>((f & kUnsorted) != 0, any_s);
     const bool some = !FUSED && parts > 1 && !in_order;                // entries of other parts are among those looked at
 
     int32_t n = HOST ? g1 - g0 : 0, out0 = HOST ? g0 : 0;    // entries to look at, place of the part's first one in the arrays
@@ -356,20 +357,10 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     }
     if (in_order) {
         const int32_t len = e - s;
-        int32_t incl = len, skip = s - rs0;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int32_t t = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += t;
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) skip += __shfl_xor(skip, d, 64);
-        if (lane == 63) { wsum[wv] = incl; wsum2[wv] = skip; }
-        __syncthreads();
-        int32_t at = incl - len;
-        for (int j = 0; j < wv; ++j) at += wsum[j];
-        out0 = g0;
-        for (int j = 0; j < WAVES; ++j) { n += wsum[j]; out0 += wsum2[j]; }
+        const int32_t at = block_scan<WAVES>(len, wsum, &n);
+        int32_t skip;
+        block_scan<WAVES>(s - rs0, wsum2, &skip);
+        out0 = g0 + skip;
         if (tid < ROWS) {
             seg[tid] = tid < rows ? at : INT32_MAX;
             off[tid] = s - at;
@@ -449,7 +440,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
         if (mine) atomicAdd(&count_s, mine);
     }
     if (FUSED && bad) atomicOr(&below_s, 1);
-    if (!RANKED) twice = __syncthreads_or(twice) != 0;
+    if (!RANKED) twice = block_any<WAVES>(twice, any_s);
     else __syncthreads();
     if (FUSED && tid == 0) a.flags_out[q] = below_s ? kBadColumn : 0u;
     if (FUSED)
@@ -459,23 +450,8 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
         count = count_s;
         if (count == 0) return;                              // the whole workgroup
     }
-    // Exclusive prefix sum over the workgroup; *all: the total.  (wsum was read before the barrier above, or the one at the end here.)
-    auto prefix = [&](int32_t x, int32_t* all) {
-        int32_t incl = x;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int32_t t = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += t;
-        }
-        if (lane == 63) wsum[wv] = incl;
-        __syncthreads();
-        int32_t at = incl - x;
-        for (int j = 0; j < wv; ++j) at += wsum[j];
-        int32_t sum = 0;
-        for (int j = 0; j < WAVES; ++j) sum += wsum[j];
-        *all = sum;
-        return at;
-    };
+    // (wsum was read before the barrier above, or the one at the end here)
+    auto prefix = [&](int32_t x, int32_t* all) { return block_scan<WAVES>(x, wsum, all); };
     int32_t distinct = ncols;
     if constexpr (RANKED) {
         const int32_t per = (nbw + THREADS - 1) / THREADS, i0 = tid * per < nbw ? tid * per : nbw, i1 = i0 + per < nbw ? i0 + per : nbw;
@@ -513,7 +489,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
                     twice |= (old & bit) != 0;
                 }
             }
-            twice = __syncthreads_or(twice) != 0;
+            twice = block_any<WAVES>(twice, any_s);
         }
         if (twice) {
             // counts instead of masks

@@ -68,6 +68,18 @@ def test_in_one_launch(m, k, entries, p, long, kind):
     _check(m, k, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), p)
 
 
+# groups of just so many entries that each of 256 (or 1024) threads has four of them, or eight, one fewer and one more; columns that come to four a thread and to one more
+@pytest.mark.parametrize("k", [300, 1024, 1025])
+@pytest.mark.parametrize("sizes", [[1023, 1024, 1025, 0, 1, 960, 961], [2047, 2048, 2049, 64, 1984, 1985], [4095, 4096, 4097, 3, 4032, 4033]])
+def test_as_many_entries_as_the_threads_take_at_a_time(sizes, k):
+    print(f"order: groups of {sizes}, {k} columns", flush=True)
+    rng = np.random.default_rng(k + sizes[0])
+    lens = np.concatenate([np.diff(np.arange(33) * n // 32) for n in sizes])
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.permutation(k)[:n]) for n in lens]).astype(np.int32)
+    _check(len(lens), k, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), 32)
+
+
 def _check(m, k, rp, ci, va, p):
     want = orc.gcoo_from_csr(m, k, rp, ci, va, p)
     dev = [torch.from_numpy(x).to(DEV) for x in (rp, ci, va)]
