@@ -1105,7 +1105,7 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.cols = d_cols; o.vals = d_vals; o.m = m; o.p = p; o.k = (int32_t)k; o.plan = L.plan; o.out = rows_out(h);
         o.dst_cols = h->cols(); o.dst_rows = h->rows(); o.dst_vals = h->values();
         o.row_ptr = d_row_ptr; o.nnz = (int32_t)nnz; o.g = g; o.gIdxes_out = h->gIdxes(); o.nnzPerGroup_out = h->nnzPerGroup();
-        o.row_start_out = h->row_start(); o.flags_out = h->take_flags();
+        o.row_start_out = h->row_start(); o.flags_out = h->take_flags(); o.far = (bool)stage;
         if (starts_given) {
             gcoo::GroupStarts starts;
             for (int64_t q = 0; q <= g; ++q) starts.at[q] = row_ptr[q < g ? q * p : m];

@@ -202,6 +202,7 @@ struct OrderArgs {
     int32_t* nnzPerGroup_out;
     int32_t* row_start_out;
     uint32_t* flags_out;       // [g]
+    bool far;                  // the input is in host memory
 };
 
 inline size_t order_lds_bytes(const OrderPlan& plan, int words)
@@ -258,26 +259,30 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     float* o_val = (float*)(base + keys + spare);
     auto mask_at = [&](int32_t key) { return mask + key * WORDS + (RANKED ? 0 : key >> ps); };
     auto base_at = [&](int32_t key) { return base + key + (RANKED ? 0 : key >> ps); };
-    int32_t* o_col = (int32_t*)(o_val + a.plan.cap);
-    uint8_t* o_row = (uint8_t*)(o_col + a.plan.cap);
+    uint32_t* o_place = (uint32_t*)(o_val + a.plan.cap);      // row | column << 8
 
     // everything that does not wait for anything else
     int32_t g0 = known0, g1 = known1;
     int32_t rs0 = 0, re = 0, s = 0, e = 0;
     if constexpr (FUSED) {
-        // (one thread asks for an offset, not every wave: of host memory each would be a read over the link)
+        // Every wave asks for the group's own offsets, so that the entries wait for nothing else; in host memory, where each would be a read over the link, one thread for all.
         auto at = [&](int64_t r) { const int32_t x = a.row_ptr[r]; return x < 0 ? 0 : (x > a.nnz ? a.nnz : x); };    // as in take_rows
-        if (!HOST && tid == 0) g1 = at(r0 + rows);
+        if (!HOST && !a.far) {
+            g0 = at(r0);
+            g1 = at(r0 + rows);
+        }
+        if (!HOST && a.far && tid == 0) group_s[1] = at(r0 + rows);
         if (tid < rows) {
             rs0 = at(r0 + tid);
             a.row_start_out[r0 + tid] = rs0;
         }
+        if (!HOST && a.far) {
+            if (tid == 0) group_s[0] = rs0;
+            __syncthreads();
+            g0 = __builtin_amdgcn_readfirstlane(group_s[0]);
+            g1 = __builtin_amdgcn_readfirstlane(group_s[1]);
+        }
         if (tid == 0) {
-            if (!HOST) {
-                g0 = rs0;
-                group_s[0] = g0;
-                group_s[1] = g1;
-            }
             a.gIdxes_out[q] = g0;
             a.nnzPerGroup_out[q] = g1 < g0 ? 0 : g1 - g0;
             if (q == a.g - 1) {
@@ -311,7 +316,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     const bool in_order = !FUSED && parts > 1 && !block_any<WAVES>((f & kUnsorted) != 0, any_s);
     const bool some = !FUSED && parts > 1 && !in_order;                // entries of other parts are among those looked at
 
-    int32_t n = HOST ? g1 - g0 : 0, out0 = HOST ? g0 : 0;    // entries to look at, place of the part's first one in the arrays
+    int32_t n = FUSED ? g1 - g0 : 0, out0 = FUSED ? g0 : 0;  // entries to look at, place of the part's first one in the arrays
     const int32_t c0 = part << shift, kmax = a.k - 1, wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
     bool bad = false;                                        // FUSED: a column was out of range
     // Entry i of those to look at is of row r, in column c of the part.  A thread goes through eight at a time, side by side, past the end the last one again; a wave that has no more than four
@@ -349,7 +354,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
         *ci = inside(column(at)) - c0;
         *vi = a.vals[at];
     };
-    if constexpr (HOST) {
+    if constexpr (FUSED) {
         if (wave0 < n) {
             ask(std::integral_constant<int, 0>{}, 0);
             if (n - wave0 > 4 * THREADS) ask(std::integral_constant<int, 4>{}, 0);
@@ -376,11 +381,6 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
         }
     }
     __syncthreads();
-    if constexpr (FUSED && !HOST) {
-        out0 = g0 = __builtin_amdgcn_readfirstlane(group_s[0]);
-        g1 = __builtin_amdgcn_readfirstlane(group_s[1]);
-        n = g1 - g0;
-    }
     if (!FUSED && part == 0 && tid < rows && a.out.cols) list_long_row(a.out, (int32_t)r0 + tid, re - rs0);
     if (n <= 0) {                                            // the whole workgroup
         if (FUSED && tid == 0) a.flags_out[q] = 0u;
@@ -412,7 +412,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
     bool twice = false;
     int32_t below = 0, mine = 0;
     for (int32_t i0 = 0; i0 < n; i0 += EACH * THREADS) {
-        take_some(i0, HOST && i0 == 0);
+        take_some(i0, FUSED && i0 == 0);
 #pragma unroll
         for (int x = 0; x < EACH; ++x) {
             if (i0 + x * THREADS + tid >= n) break;
@@ -516,15 +516,27 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
                 for (int w = 0; w < WORDS; ++w) x += __popc(mask_at(k)[w]);
                 return x;
             };
-            int32_t sum = 0;
+            int32_t sum = 0, kept[4];
+            if (per <= 4) {                                  // (the same for all)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    kept[x] = sum;
+                    if (i0 + x < i1) sum += entries(i0 + x);
+                }
+                const int32_t at = prefix(sum, &entries_of_window);
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (i0 + x < i1) *base_at(i0 + x) = at + kept[x];
+            } else {
 #pragma unroll 4
-            for (int32_t i = i0; i < i1; ++i) sum += entries(i);
-            int32_t at = prefix(sum, &entries_of_window);
+                for (int32_t i = i0; i < i1; ++i) sum += entries(i);
+                int32_t at = prefix(sum, &entries_of_window);
 #pragma unroll 4
-            for (int32_t i = i0; i < i1; ++i) {
-                const int32_t x = entries(i);
-                *base_at(i) = at;
-                at += x;
+                for (int32_t i = i0; i < i1; ++i) {
+                    const int32_t x = entries(i);
+                    *base_at(i) = at;
+                    at += x;
+                }
             }
         }
         __syncthreads();
@@ -574,8 +586,7 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
                     }
                     if (staged) {
                         o_val[at] = v[x];
-                        o_col[at] = c0 + c[x];
-                        o_row[at] = (uint8_t)r[x];
+                        o_place[at] = (uint32_t)r[x] | (uint32_t)c[x] << 8;
                     } else {
                         a.dst_cols[out0 + at] = c0 + c[x];
                         a.dst_rows[out0 + at] = (int32_t)r0 + r[x];
@@ -586,8 +597,8 @@ __device__ __forceinline__ void order_part(const OrderArgs& a, int32_t item, int
             if (staged) {
                 __syncthreads();
                 for (int32_t i = tid; i < count; i += THREADS) {
-                    a.dst_cols[out0 + i] = o_col[i];
-                    a.dst_rows[out0 + i] = (int32_t)r0 + (int32_t)o_row[i];
+                    a.dst_cols[out0 + i] = c0 + (int32_t)(o_place[i] >> 8);
+                    a.dst_rows[out0 + i] = (int32_t)r0 + (int32_t)(o_place[i] & 255u);
                     a.dst_vals[out0 + i] = o_val[i];
                 }
             }
