@@ -123,9 +123,9 @@ def verify_band_code(stem: str, text: str) -> None:
     """The sixteen-wave kernel, its instances (four and two columns per lane): no register spills, 128 VGPRs at most (four waves per SIMD), every load
     that writes LDS sets M0 itself, nothing is in flight at a barrier, and its asm text writes the scalar registers that its clobber list names."""
     from . import isa_check
-    instances = [(4, 0), (4, 1), (2, 0), (2, 1)]
-    for v, spread in instances:
-        kernel = f"_ZN4gcoo9spdm_bandILi{v}ELb{spread}E"
+    instances = [(4, 0, 0), (4, 0, 1), (4, 1, 0), (4, 1, 1), (2, 0, 0), (2, 0, 1), (2, 1, 0)]
+    for v, spread, late in instances:
+        kernel = f"_ZN4gcoo9spdm_bandILi{v}ELb{spread}ELb{late}E"
         loads, problems = isa_check.check_lds_loads(text, kernel, asm_only=True)
         if loads < 15 or problems or isa_check.check_lds_loads(text, kernel)[0] != loads:
             raise RuntimeError(f"{stem} {kernel}: {loads} loads to LDS, {problems[:3]}")

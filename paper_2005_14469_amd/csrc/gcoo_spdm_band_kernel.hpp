@@ -31,14 +31,17 @@
 // 4 bytes per lane instead, so, and N = 8000): 0.5 % 358 317 288; 2 % 677 646 630; 10 % 2335 2295 2287.
 //
 // When the rows are requested.  A request holds the one address path of the compute unit for 16 clocks, and a wave that finds it taken
-// stands still: with all five requests of all waves at the band's start nobody multiplied for the first 0.5 us.  Two ways:
-//   SPREAD false   waves 0 - 7 at the start, waves 8 - 15 behind their first unit (or at the end of a band that has only one): one half
-//                  multiplies while the other asks
-//   SPREAD true    every wave asks for two rows at the start and one behind each of its first three steps; a band of few entries per
-//                  wave would end before the late half's rows have landed
-// Product alone, all at the start -> now (us): 14000 x 14000, 2 % 3460 -> 3165; 8000 x 8000, 2 % 672 -> 633; 10 % 2323 -> 2284; 6001 x 6001,
-// 1 % 290 -> 254; SPREAD: 8000 x 8000, 0.5 % 366 -> 345; 10000 x 10000, 0.4 % 667 -> 590 (the other way 371 and 670).  A quarter of the
-// waves at a time, a unit apart, was slower (3517 for the first); so was asking a row at a time and step everywhere (3365).
+// stands still: with all five requests of all waves at the band's start nobody multiplied for the first 0.5 us.  Four ways (SPREAD, LATE):
+//   true, false     every wave asks for two rows at the start and one behind each of its first three steps; a band of few entries per
+//                   wave would end before the late half's rows have landed
+//   true, true      waves 0 - 7 at the start, waves 8 - 15 behind the second step of their first unit (or at the end of the band): one half
+//                   multiplies while the other asks
+//   false, false    as that, waves 8 - 15 behind their first unit
+//   false, true     as that, waves 8 - 15 behind their second unit: where a band has units enough, the later the better
+// Product alone, all at the start -> behind the first unit (us): 14000 x 14000, 2 % 3460 -> 3165; 8000 x 8000, 2 % 672 -> 633; 10 % 2323 -> 2284; 6001 x 6001,
+// 1 % 290 -> 254; spread: 8000 x 8000, 0.5 % 366 -> 345; 10000 x 10000, 0.4 % 667 -> 590 (by halves 371 and 670).  A quarter of the
+// waves at a time, a unit apart, is slower (1 % and more below 60 entries of a (wave, band), up to 10 % at 20); so is asking a row at a time and step everywhere (3365 for the first),
+// the late half behind the first step (1 to 4 % slower than behind the first unit), and the early half behind its first step (2 %).  Where each is taken: launch_spdm_band().
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -79,7 +82,8 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 //   s12 s13   byte offsets of the head after next and of the next unit    s14  where the wave's rows of the next band go in LDS
 //   s15 bands left   s[16:22]  head of this band: five columns, pair steps, single steps    s[24:30] of the next one    s23 scratch
 //   s[32:35]  buffer descriptor of B, from the tile's first column on
-//   vcc       not 0: rows of the next band are still to be requested (SPREAD: 1 + how often it was done behind a step)
+//   vcc       not 0: rows of the next band are still to be requested (spread: 1 + how often it was done behind a step; halves: 1 or 2, the units behind which they will be);
+//             all 64 bits are written each time, as a write to a half need not reach what s_cbranch_vccnz looks at
 //   tall only: v126 scratch, v127 all ones in the upper half of the wave, s100 scratch
 // What differs between the cuts: BD_FMAC_T<i> (the entry's partial sums += value x set i), BD_READ_T<i>, BD_MASK, BD_BEGIN, BD_FILL.
 #define BD_FMAC_WIDE(val, b0, b1, b2, b3)              \
@@ -119,15 +123,25 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 // The places where rows are requested; T = p (pair steps) or s (single steps).  BD_ASK_START behind the first reads of a band, BD_ASK_STEP behind
 // step I of its first unit, BD_ASK_UNIT in front of a further unit, BD_ASK_END at its end; what is done there stands out of line (BD_ASK_REST).
 #define BD_ASK_HERE(L, X) "s_cbranch_vccnz .Lbd_" #L "_" #X "_%=\n.Lbd_" #L "back_" #X "_%=:\n\t"
-#define BD_ASK_THERE(L, X, STATE, FILLS) ".Lbd_" #L "_" #X "_%=:\n\ts_mov_b32 vcc_lo, " #STATE "\n\t" FILLS "s_branch .Lbd_" #L "back_" #X "_%=\n"
+#define BD_ASK_THERE(L, X, STATE, FILLS) ".Lbd_" #L "_" #X "_%=:\n\ts_mov_b64 vcc, " #STATE "\n\t" FILLS "s_branch .Lbd_" #L "back_" #X "_%=\n"
 #define BD_ASK_END(X) BD_ASK_HERE(fe, X)
-// SPREAD false
-#define BD_HALVES_START(T, X) "s_cmp_ge_u32 %[fillw], 0xa000\n\ts_cselect_b32 vcc_lo, 1, 0\n\ts_cbranch_scc1 .Lbd_late" #T "_" #X "_%=\n\t" BD_FILL_BAND ".Lbd_late" #T "_" #X "_%=:\n\t"
+// by halves, waves 8 - 15 behind unit LATE (STEP1: behind the second step of the first one)
+#define BD_HALVES_START(T, X, LATE) "s_cmp_ge_u32 %[fillw], 0xa000\n\ts_cselect_b64 vcc, " #LATE ", 0\n\ts_cbranch_scc1 .Lbd_late" #T "_" #X "_%=\n\t" BD_FILL_BAND ".Lbd_late" #T "_" #X "_%=:\n\t"
 #define BD_HALVES_STEP(T, I, X)
 #define BD_HALVES_UNIT(T, X) BD_ASK_HERE(f##T, X)
-#define BD_HALVES_REST(X) BD_ASK_THERE(fp, X, 0, BD_FILL_BAND) BD_ASK_THERE(fs, X, 0, BD_FILL_BAND) BD_ASK_THERE(fe, X, 0, BD_FILL_BAND)
-// SPREAD true
-#define BD_SPREAD_START(T, X) "s_mov_b32 vcc_lo, 1\n\t" BD_FILL(s16, 0) BD_FILL(s17, 0x400)
+#define BD_FIRST_START(T, X) BD_HALVES_START(T, X, 1)
+#define BD_FIRST_REST(X) BD_ASK_THERE(fp, X, 0, BD_FILL_BAND) BD_ASK_THERE(fs, X, 0, BD_FILL_BAND) BD_ASK_THERE(fe, X, 0, BD_FILL_BAND)
+#define BD_STEP1_STEP(T, I, X) BD_STEP1_STEP_##I(T, X)
+#define BD_STEP1_STEP_0(T, X)
+#define BD_STEP1_STEP_1(T, X) BD_ASK_HERE(f##T##1, X)
+#define BD_STEP1_STEP_2(T, X)
+#define BD_STEP1_UNIT(T, X)
+#define BD_STEP1_REST(X) BD_ASK_THERE(fp1, X, 0, BD_FILL_BAND) BD_ASK_THERE(fs1, X, 0, BD_FILL_BAND) BD_ASK_THERE(fe, X, 0, BD_FILL_BAND)
+#define BD_SECOND_START(T, X) BD_HALVES_START(T, X, 2)
+#define BD_SECOND_UNIT(L, X) ".Lbd_" #L "_" #X "_%=:\n\ts_lshr_b64 vcc, vcc, 1\n\ts_cbranch_scc1 .Lbd_" #L "back_" #X "_%=\n\t" BD_FILL_BAND "s_branch .Lbd_" #L "back_" #X "_%=\n"
+#define BD_SECOND_REST(X) BD_SECOND_UNIT(fp, X) BD_SECOND_UNIT(fs, X) BD_ASK_THERE(fe, X, 0, BD_FILL_BAND)
+// spread
+#define BD_SPREAD_START(T, X) "s_mov_b64 vcc, 1\n\t" BD_FILL(s16, 0) BD_FILL(s17, 0x400)
 #define BD_SPREAD_STEP(T, I, X) BD_ASK_HERE(f##T##I, X)
 #define BD_SPREAD_UNIT(T, X)
 #define BD_SPREAD_REST(X)                                                                              \
@@ -136,7 +150,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     ".Lbd_fe_" #X "_%=:\n\t"                                                                           \
     "s_cmp_gt_u32 vcc_lo, 1\n\ts_cbranch_scc1 .Lbd_fe1_" #X "_%=\n\t" BD_FILL(s18, 0x800) ".Lbd_fe1_" #X "_%=:\n\t"     \
     "s_cmp_gt_u32 vcc_lo, 2\n\ts_cbranch_scc1 .Lbd_fe2_" #X "_%=\n\t" BD_FILL(s19, 0xc00) ".Lbd_fe2_" #X "_%=:\n\t"     \
-    BD_FILL(s20, 0x1000) "s_mov_b32 vcc_lo, 0\n\ts_branch .Lbd_feback_" #X "_%=\n"
+    BD_FILL(s20, 0x1000) "s_mov_b64 vcc, 0\n\ts_branch .Lbd_feback_" #X "_%=\n"
 
 #define BD_LOAD_UNIT(lo, hi)                                      \
     "s_load_dwordx16 s[" lo "], %[units], s13\n\t"                 \
@@ -300,7 +314,7 @@ struct BandRowsGrid { int32_t tiles, rpw, wave_row; };
 // A matrix with a list of far more entries than the others (take_rows and band_mark say so on the device, where the
 // row lengths are) has no schedule: the waves would wait for that list in every band.  Its rows are multiplied one by one, by the
 // workgroups of this launch.
-template <int V, bool SPREAD>            // V = 4: the wide cut, 2: the tall one
+template <int V, bool SPREAD, bool LATE>            // V = 4: the wide cut, 2: the tall one; when the rows of the next band are requested
 __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
@@ -352,7 +366,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #define BD_FILL BD_FILL_WIDE
             const uint32_t lane_b = jb + (int32_t)(lane * 4u) < n ? lane * 16u : 0u;
 #define BD_LOAD_ROW "buffer_load_dwordx4 v2, s[32:35], s23 offen lds\n\t"
-            if constexpr (SPREAD) {
+            if constexpr (SPREAD && !LATE) {
 #define BD_ASK_START BD_SPREAD_START
 #define BD_ASK_STEP BD_SPREAD_STEP
 #define BD_ASK_UNIT BD_SPREAD_UNIT
@@ -362,11 +376,31 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #undef BD_ASK_STEP
 #undef BD_ASK_UNIT
 #undef BD_ASK_REST
-            } else {
-#define BD_ASK_START BD_HALVES_START
+            } else if constexpr (SPREAD) {
+#define BD_ASK_START BD_FIRST_START
+#define BD_ASK_STEP BD_STEP1_STEP
+#define BD_ASK_UNIT BD_STEP1_UNIT
+#define BD_ASK_REST BD_STEP1_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else if constexpr (LATE) {
+#define BD_ASK_START BD_SECOND_START
 #define BD_ASK_STEP BD_HALVES_STEP
 #define BD_ASK_UNIT BD_HALVES_UNIT
-#define BD_ASK_REST BD_HALVES_REST
+#define BD_ASK_REST BD_SECOND_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else {
+#define BD_ASK_START BD_FIRST_START
+#define BD_ASK_STEP BD_HALVES_STEP
+#define BD_ASK_UNIT BD_HALVES_UNIT
+#define BD_ASK_REST BD_FIRST_REST
                 BD_MAIN;
 #undef BD_ASK_START
 #undef BD_ASK_STEP
@@ -406,7 +440,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #define BD_MORE_SCALARS , "s100"
             const uint32_t lane_b = jb + (int32_t)((lane & 31u) * 4u) < n ? (lane & 31u) * 16u : 0u;
 #define BD_FILL BD_FILL_TALL
-            if constexpr (SPREAD) {
+            if constexpr (SPREAD && !LATE) {
 #define BD_ASK_START BD_SPREAD_START
 #define BD_ASK_STEP BD_SPREAD_STEP
 #define BD_ASK_UNIT BD_SPREAD_UNIT
@@ -416,11 +450,31 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #undef BD_ASK_STEP
 #undef BD_ASK_UNIT
 #undef BD_ASK_REST
-            } else {
-#define BD_ASK_START BD_HALVES_START
+            } else if constexpr (SPREAD) {
+#define BD_ASK_START BD_FIRST_START
+#define BD_ASK_STEP BD_STEP1_STEP
+#define BD_ASK_UNIT BD_STEP1_UNIT
+#define BD_ASK_REST BD_STEP1_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else if constexpr (LATE) {
+#define BD_ASK_START BD_SECOND_START
 #define BD_ASK_STEP BD_HALVES_STEP
 #define BD_ASK_UNIT BD_HALVES_UNIT
-#define BD_ASK_REST BD_HALVES_REST
+#define BD_ASK_REST BD_SECOND_REST
+                BD_MAIN;
+#undef BD_ASK_START
+#undef BD_ASK_STEP
+#undef BD_ASK_UNIT
+#undef BD_ASK_REST
+            } else {
+#define BD_ASK_START BD_FIRST_START
+#define BD_ASK_STEP BD_HALVES_STEP
+#define BD_ASK_UNIT BD_HALVES_UNIT
+#define BD_ASK_REST BD_FIRST_REST
                 BD_MAIN;
 #undef BD_ASK_START
 #undef BD_ASK_STEP

@@ -5,7 +5,7 @@
 
 namespace gcoo {
 
-template <int V, bool SPREAD>
+template <int V, bool SPREAD, bool LATE>
 static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const BandRowsGrid& rg, hipStream_t s)
 {
     // more LDS than the default limit of a workgroup: asked for once per device
@@ -15,11 +15,11 @@ static hipError_t launch_band(const BandArgs& a, const RowsArgs& rows, const Ban
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!done[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<V, SPREAD>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdm_band<V, SPREAD, LATE>), hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes);
         if (e != hipSuccess) return e;
         done[dev].store(1u, std::memory_order_release);
     }
-    spdm_band<V, SPREAD><<<dim3((unsigned)(a.grid > kRowsAllWgs ? a.grid : kRowsAllWgs)), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
+    spdm_band<V, SPREAD, LATE><<<dim3((unsigned)(a.grid > kRowsAllWgs ? a.grid : kRowsAllWgs)), dim3(64 * kBandWaves), kBandLdsBytes, s>>>(a, rows, rg);
     return hipGetLastError();
 }
 
@@ -44,13 +44,23 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     rg.tiles = (int32_t)((rows.N + by_rows.moved + 63) / 64);
     rg.rpw = 4;                                              // (8: as fast)
     rg.wave_row = (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row);
-    // How the rows of B are requested goes by the entries of a (wave, band), of which SPREAD serves the few (us, halves and SPREAD:
-    // 10 entries 370 and 345, 19: 466 444, 27: 248 245, 38: 633 659; tall, 19: 694 670, 27: 821 854).
+    // How the rows of B are requested goes by the entries of a (wave, band).  Product alone, against behind the first unit, mean of 20 to 200 matrices each; wide:
+    //   entries                    8 - 10  12 - 14  14 - 16  16 - 18  20 - 22  24 - 26  28 - 32  36 - 40  40 - 50  80 - 150
+    //   a row at a time             0.975    0.978    0.993    1.004    1.031    1.051    1.058    1.043    1.044     1.021
+    //   behind the second step      0.999    0.985    0.986    0.989    0.999    1.011    1.017    1.012    1.013     1.006
+    //   behind the second unit      1.000    1.018    1.031    1.051    1.087    1.077    1.049    1.007    0.998     0.997
+    // tall:
+    //   entries                   14 - 16  16 - 18  18 - 20  20 - 22  24 - 26  28 - 32  32 - 36  36 - 40  40 - 50   60 - 80
+    //   a row at a time             0.989    0.990    0.997    1.003    1.029    1.049    1.052    1.056    1.056     1.055
+    //   behind the second step      1.004    1.006    1.009    1.010    1.014    1.027    1.033    1.033    1.031     1.024
+    //   behind the second unit      0.996    0.994    1.006    1.018    1.022    1.019    1.009    0.996    0.986     0.973
     const double entries = band_entries(a.m, a.k, rows.nnz, a.h, a.v);
     if (a.v == 2) {
-        return entries < 22.0 ? launch_band<2, true>(b, by_rows, rg, s) : launch_band<2, false>(b, by_rows, rg, s);
+        if (entries < 20.0) return launch_band<2, true, false>(b, by_rows, rg, s);
+        return entries < 37.0 ? launch_band<2, false, false>(b, by_rows, rg, s) : launch_band<2, false, true>(b, by_rows, rg, s);
     }
-    return entries < 28.0 ? launch_band<4, true>(b, by_rows, rg, s) : launch_band<4, false>(b, by_rows, rg, s);
+    if (entries < 28.0) return entries < 14.0 ? launch_band<4, true, false>(b, by_rows, rg, s) : launch_band<4, true, true>(b, by_rows, rg, s);
+    return entries < 42.0 ? launch_band<4, false, false>(b, by_rows, rg, s) : launch_band<4, false, true>(b, by_rows, rg, s);
 }
 
 }  // namespace gcoo

@@ -94,6 +94,19 @@ def test_requests_spread_over_a_band_from_rows_aligned_to_4_bytes(m, k, N, nnz, 
     _run(workloads.uniform_random(m, k, N, 1 - nnz / (m * k), seed=m + N), 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
 
 
+@pytest.mark.parametrize("m,k,per_row,N", [(4000, 4000, 40, 2605), (5000, 5001, 47, 2605), (5000, 5001, 42, 2605), (4000, 4000, 160, 2053), (4000, 4000, 120, 2053), (4000, 4000, 76, 2053)])
+@pytest.mark.parametrize("even", [True, False])
+def test_requests_of_the_late_half_behind_the_first_and_the_second_unit(m, k, per_row, N, even):
+    """Both cuts, on both sides of the number of entries from which the late half asks behind its second unit; waves of one unit to a band beside waves of many."""
+    print(f"band, late half: m={m} k={k} per_row={per_row} even={even}", flush=True)
+    rng = np.random.default_rng(m + per_row)
+    n = np.full(m, per_row) if even else np.resize(np.repeat([per_row // 8, 2 * per_row, per_row // 2, 3 * per_row // 2], 40), m)
+    rp = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(k, x, replace=False)) for x in n]).astype(np.int32)
+    _run(workloads.Workload("late", m, k, N, rp, ci, rng.standard_normal(len(ci)).astype(np.float32), rng.standard_normal((k, N)).astype(np.float32)),
+         32, binding.VARIANT_AUTO, kernel=binding.KERNEL_BAND)
+
+
 def test_tall_cut_with_repeated_coordinates_and_infinities():
     """Lists that are written the slow way, of more than 32 rows; rows of B that no entry touches hold infinities."""
     rng = np.random.default_rng(21)
