@@ -14,14 +14,14 @@
 // scalar cache, a unit of 16 at a time into one of two register banks while the other is multiplied, so no vector instruction
 // moves them.  A multiply-add with a scalar (or DPP) operand or in index mode takes 1.8 ns per SIMD, the other vector
 // instructions too: five of them per single entry, 9 ns, are what bounds dense bands; 10.1 measured in a loop of nothing else.
-// By the counters a SIMD issues a vector instruction every 2.5 ns at 8000 x 8000, 10 %, and every 2.9 at 14000 x 14000, 2 % (15 of 16 waves resident,
-// waiting half their time).  Sparser matrices have few entries per (wave, band), 3.7 ns at 4000 x 4000, 2 %: there the bands by themselves weigh.  No bank conflicts anywhere.
+// By the counters a SIMD issues a vector instruction every 2.2 ns at 8000 x 8000, 10 %, and every 2.8 at 14000 x 14000, 2 % (15 and 14 of 16 waves resident).
+// Sparser matrices have few entries per (wave, band), 3.4 ns at 4000 x 4000, 2 %: there the bands by themselves weigh.  No bank conflicts anywhere.
 //
 // The tall cut (V = 2): the same registers and the same LDS hold twice the rows of A and of B, half as wide.  A row of B is fetched for twice as
 // many rows of A, and a launch has half as many bands, each with four times the entries of a wave; an entry costs a multiply-add
 // less than half but the same address, read and index (7.5 ns in a loop of nothing else, where the wide cut takes 10.2 for twice the columns): the unit that reads LDS takes
 // as long for 8 bytes per lane as for 16, and is the bound of dense matrices.  For sparse ones what is fetched and the bands are: 8000 x 8000, 0.5 %: 333 -> 294 us (a vector
-// instruction every 4.3 ns, rows of B and entries from L2 at 9.2 TB/s),
+// instruction every 4.2 ns, rows of B and entries from L2 at 9.5 TB/s),
 // where the same launch without its multiply-adds takes 290, without its requests 240, and with neither requests nor
 // entries 68: a band is a chain of waits (rows of B from L2, LDS, barrier) that fifteen other waves in the same phase do not fill.
 //
