@@ -322,7 +322,7 @@ struct Layout {
     size_t total;
 };
 
-constexpr size_t kTicketAt = 32;                           // among the words of `counter`
+constexpr size_t kTicketAt = 32, kSoonAt = 128;            // among the words of `counter` (FillArgs::soon)
 
 // Column windows of the run schedule: bands of kWindowCols columns (a band of B of that many
 // rows by one column tile stays in the L2 of the XCD working on the tile), at most kMaxWindows,
@@ -671,7 +671,7 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     // counted into them before nnz is known
     L.gIdxes = take((size_t)(g + 1) * 4);
     L.nnzPerGroup = take((size_t)g * 4);
-    L.counter = take(kTicketAt + 8);
+    L.counter = take(kSoonAt + 4);
     L.blk = take((size_t)g * (size_t)dense_blocks(k) * 4);
     L.values = take(n4);
     L.rows = take(n4);
@@ -781,6 +781,7 @@ struct gcoo_matrix {
     float* row_vals() const { return reinterpret_cast<float*>(base + L.row_vals); }
     int32_t* long_rows() const { return reinterpret_cast<int32_t*>(base + L.row_long); }
     uint32_t* uneven() const { return reinterpret_cast<uint32_t*>(base + L.counter + 24); }
+    uint32_t* soon() const { return reinterpret_cast<uint32_t*>(base + L.counter + kSoonAt); }
     int32_t* long_count() const { return reinterpret_cast<int32_t*>(base + L.counter + 20); }
     uint32_t* band_head() const { return reinterpret_cast<uint32_t*>(base + L.band_head); }
     uint32_t* band_units() const { return reinterpret_cast<uint32_t*>(base + L.band_units); }
@@ -931,7 +932,7 @@ int launch_build_schedule(const gcoo_matrix* h, char* scratch, hipStream_t s, bo
         HIP_TRY(hipGetLastError());
         const bool large = v == 2 || h->nnz / lists > 4096;
         gcoo::FillArgs f = fill_args(h, scratch, false);
-        if (grouped) { f.out = rows_out(h); f.g = h->g; f.p = h->p; f.says_uneven = h->uneven(); f.flag_count = (int32_t)marks; f.heavy = (uint32_t)gcoo::band_heavy(h->nnz, marks); }
+        if (grouped) { f.out = rows_out(h); f.g = h->g; f.p = h->p; f.says_uneven = h->uneven(); f.soon = h->soon(); f.flag_count = (int32_t)marks; f.heavy = (uint32_t)gcoo::band_heavy(h->nnz, marks); }
         HIP_TRY(band_fill_lds_limit());
         auto pick = [&](auto by_groups) {
             constexpr bool GROUPED = decltype(by_groups)::value;
@@ -1391,7 +1392,7 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
             h->long_places = !band;
             const int32_t split = dense_groups_split(k, nnz / g, p);
             (split > 1 ? (p <= 32 ? gcoo::fill_dense_groups<32, true> : gcoo::fill_dense_groups<64, true>) : (p <= 32 ? gcoo::fill_dense_groups<32, false> : gcoo::fill_dense_groups<64, false>))<<<dim3((unsigned)(g * split)), dim3(gcoo::kDenseGroupThreads), 0, s>>>(
-                A_dev, lda, m, k, p, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols(), rows_out(h), !band,
+                A_dev, lda, m, k, p, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols(), rows_out(h), !band, band ? h->soon() : nullptr,
                 band ? reinterpret_cast<uint32_t*>(h->base + h->L.persistent + h->L.tmp_cols) : nullptr, gcoo::kBandWaves * h->L.band.h, split);
         } else if (masks)
             (vw == 4 ? gcoo::fill_dense_masked<4> : gcoo::fill_dense_masked<1>)<<<grid, block, 0, s>>>(

@@ -63,6 +63,15 @@ __host__ __device__ inline int64_t band_blocks(int64_t m, int32_t h) { return (m
 inline int64_t band_lists(int64_t m, int32_t h, int v) { return band_blocks(m, h) * kBandWaves * band_lists_of(v); }
 __host__ __device__ inline int64_t band_max_bands(int64_t k, int v) { return (k + band_rows_of(v) - 1) / band_rows_of(v); }
 __host__ __device__ inline int64_t band_head_stride(int64_t k, int v) { return band_max_bands(k, v) + 5; }
+// The lists that workgroup w of a launch looks at for one that is heavy, where no launch before it could: all of them, or, of more than kBandTestAll, band_tests() from band_test_from() on, as far as
+// there are any.  Then those that band_test_says() names have all of them together and say so, for the workgroups that begin later; a matrix with many heavy lists has one in any 256.
+// (All of them by every workgroup are lists x lists: conversion with its count, us, the order by rows and the lists by launches of their own, all by every workgroup, and so; 32 rows per group, 2 %:
+// 64000 x 1000, 2667 lists: 153 143 132; 128000 x 1000: 319 331 283; 400000 x 500, 5 %: 776 1375 648; 300000 x 128, 10 %: 418 784 368.  Power-law rows, 128000 x 1000: 238 301 237.  A single heavy
+// list, the last one: 64000 x 1000 123 131 121.  From 1024 on for that: 32000 x 3000, 1334 lists, even 181 169 165, one heavy list 186 173 180; 24000 x 3000, 1000 lists, 256 of them by each were no faster, 121 to 119.)
+constexpr int32_t kBandTestAll = 1024, kBandTestSome = 256;
+__host__ __device__ inline int32_t band_tests(int32_t lists) { return lists <= kBandTestAll ? lists : kBandTestSome; }
+__host__ __device__ inline int64_t band_test_from(int64_t w, int32_t lists) { return lists <= kBandTestAll ? 0 : w * kBandTestSome % lists; }
+__host__ __device__ inline bool band_test_says(int64_t w, int32_t lists) { return lists <= kBandTestAll ? w == 0 : w * kBandTestSome < lists; }
 // Entries of a (wave, band), on average, where the columns are uniform.
 inline double band_entries(int64_t m, int64_t k, int64_t nnz, int32_t h, int v)
 {

@@ -128,11 +128,12 @@ struct FillArgs {
     uint32_t heavy;
     RowsOut out;               // GROUPED only
     uint32_t* says_uneven;
+    uint32_t* soon;            // the same for this launch, cleared by the one before it, on a line of its own: the count of the long rows lies beside the other
     int64_t g;
     int32_t p;
 };
 // GROUPED: behind fill_dense_groups().  The bitmaps are those of the groups, and no launch before this one could list the long rows or say that the lists are uneven, `flag_count` lists (as in
-// band_mark) of at most `heavy` entries where they are not: this one does, the list of a wave for its own rows and the first one for the matrix.
+// band_mark) of at most `heavy` entries where they are not: this one does, the list of a wave for its own rows, and the lists in front for the matrix (band_tests()).
 template <int V, int kBandBuildThreads, int EACH, bool GROUPED = false>
 __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
 {
@@ -160,11 +161,13 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     Mask* rows_of = (Mask*)(words + nbw);                   // rows of the list with an entry in a column of the chunk
     uint32_t* place_of = (uint32_t*)(rows_of + chunk);      // pairs | singles << 16 of the band in front of five columns
     // What waits for nothing but the rows' bounds is asked for first: the bitmaps, then the entries.
-    uint32_t by_rows = 0u;
+    uint32_t by_rows = 0u, seen = 0u;
     if constexpr (GROUPED) {
-        const int64_t each = a.h / band_lists_of(V);
-        for (int64_t i = tid; i < a.flag_count; i += kBandBuildThreads) {
-            const int64_t b = i * each < m ? i * each : m, e = b + each < m ? b + each : m;
+        const int64_t each = a.h / band_lists_of(V), from = band_test_from(list, a.flag_count);
+        const int32_t tests = band_tests(a.flag_count);
+        if (tests < a.flag_count) seen = __hip_atomic_load(a.soon, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int32_t i = tid; i < tests; i += kBandBuildThreads) {
+            const int64_t r = (from + i) * each, b = r < m ? r : m, e = b + each < m ? b + each : m;
             by_rows |= (uint32_t)(row_start[e] - row_start[b]) > a.heavy;
         }
     } else if (a.uneven) by_rows = *a.uneven;
@@ -209,8 +212,11 @@ __device__ __forceinline__ void band_fill_list(const FillArgs& a, int64_t list)
     if constexpr (GROUPED) {
         if (wv == 0 && lane < l.rows) list_long_row(a.out, (int32_t)l.r0 + lane, row_start[l.r0 + lane + 1] - begins);
     }
-    if (block_any<kBandBuildWaves>(by_rows != 0u, any_s)) {                   // the whole workgroup
-        if (GROUPED && list == 0 && tid == 0) *a.says_uneven = 1u;      // (zero so far)
+    if (block_any<kBandBuildWaves>((by_rows | seen) != 0u, any_s)) {          // the whole workgroup
+        if (GROUPED && __any(by_rows != 0u) && seen == 0u && lane == 0 && band_test_says(list, a.flag_count)) {      // (zero so far)
+            *a.says_uneven = 1u;
+            __hip_atomic_store(a.soon, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         return;
     }
     int32_t nU;

@@ -190,3 +190,26 @@ def test_row_order_and_bands_of_a_dense_matrix(m, k, p, density, long_rows):
             binding.gcoo_spdm(H, B[:, :N], C)
             assert torch.equal(C.double(), want[:, :N]), (N, kernel)
         assert kernel == binding.KERNEL_BAND or m < 1500
+
+
+@pytest.mark.parametrize("long_rows", ["none", "last", "many"])
+def test_more_lists_than_a_workgroup_looks_at(long_rows):
+    """2672 lists of a dense matrix: none of them heavy, so that all have to be written; one in the last rows, which one workgroup finds; and one in about a hundred.  Whole numbers, so that the product is exact."""
+    m, k, N = 64001, 1000, 2504
+    print(f"dense, many lists: long={long_rows}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    share = torch.full((m, 1), 0.02, device=DEV)
+    if long_rows == "last":
+        share[-8:] = 0.9
+    elif long_rows == "many":
+        share.view(-1)[:m - 1].view(-1, 10)[::250] = 0.9
+    A = torch.randint(1, 8, (m, k), generator=g, device=DEV, dtype=torch.float32) * (torch.rand((m, k), generator=g, device=DEV) < share)
+    B = torch.randint(-8, 9, (k, N), generator=g, device=DEV, dtype=torch.float32)
+    H = binding.gcoo_from_dense(A, 32)
+    for cols in (64, N):
+        C_ = torch.full((m, cols), 7.0, device=DEV)
+        kernel = binding.gcoo_spdm_kernel(H, B[:, :cols], C_)
+        binding.gcoo_spdm(H, B[:, :cols], C_)
+        assert torch.equal(C_.double(), A.double() @ B[:, :cols].double()), (cols, kernel)
+    assert kernel == binding.KERNEL_BAND
