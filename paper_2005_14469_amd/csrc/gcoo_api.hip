@@ -322,7 +322,7 @@ struct Layout {
     size_t total;
 };
 
-constexpr size_t kTicketAt = 32, kSoonAt = 128;            // among the words of `counter` (FillArgs::soon)
+constexpr size_t kTicketAt = 32, kZeroedAt = 16;           // among the words of `counter`
 
 // Column windows of the run schedule: bands of kWindowCols columns (a band of B of that many
 // rows by one column tile stays in the L2 of the XCD working on the tile), at most kMaxWindows,
@@ -671,7 +671,7 @@ Layout make_layout(int64_t m, int64_t k, int64_t nnz, int64_t g, int32_t p, bool
     // counted into them before nnz is known
     L.gIdxes = take((size_t)(g + 1) * 4);
     L.nnzPerGroup = take((size_t)g * 4);
-    L.counter = take(kSoonAt + 4);
+    L.counter = take(kZeroedAt + 4 * gcoo::kSoonWord + 4);
     L.blk = take((size_t)g * (size_t)dense_blocks(k) * 4);
     L.values = take(n4);
     L.rows = take(n4);
@@ -781,7 +781,7 @@ struct gcoo_matrix {
     float* row_vals() const { return reinterpret_cast<float*>(base + L.row_vals); }
     int32_t* long_rows() const { return reinterpret_cast<int32_t*>(base + L.row_long); }
     uint32_t* uneven() const { return reinterpret_cast<uint32_t*>(base + L.counter + 24); }
-    uint32_t* soon() const { return reinterpret_cast<uint32_t*>(base + L.counter + kSoonAt); }
+    uint32_t* soon() const { return bad_col() + gcoo::kSoonWord; }
     int32_t* long_count() const { return reinterpret_cast<int32_t*>(base + L.counter + 20); }
     uint32_t* band_head() const { return reinterpret_cast<uint32_t*>(base + L.band_head); }
     uint32_t* band_units() const { return reinterpret_cast<uint32_t*>(base + L.band_units); }
@@ -792,7 +792,7 @@ struct gcoo_matrix {
     int32_t* order() const { return reinterpret_cast<int32_t*>(base + L.order); }
     unsigned long long* stats() const { return reinterpret_cast<unsigned long long*>(base + L.counter); }
     uint32_t* take_flags() const { return reinterpret_cast<uint32_t*>(base + L.take_flags); }
-    uint32_t* bad_col() const { return reinterpret_cast<uint32_t*>(base + L.counter + 16); }
+    uint32_t* bad_col() const { return reinterpret_cast<uint32_t*>(base + L.counter + kZeroedAt); }
     int32_t* share_ucols() const { return reinterpret_cast<int32_t*>(base + L.share_ucols); }
     int32_t* share_ucount() const { return reinterpret_cast<int32_t*>(base + L.share_ucount); }
     uint32_t* share_hdr() const { return reinterpret_cast<uint32_t*>(base + L.share_hdr); }
@@ -1392,7 +1392,7 @@ int from_dense_counted(int64_t m, int64_t k, int64_t nnz, const float* A_dev, in
             h->long_places = !band;
             const int32_t split = dense_groups_split(k, nnz / g, p);
             (split > 1 ? (p <= 32 ? gcoo::fill_dense_groups<32, true> : gcoo::fill_dense_groups<64, true>) : (p <= 32 ? gcoo::fill_dense_groups<32, false> : gcoo::fill_dense_groups<64, false>))<<<dim3((unsigned)(g * split)), dim3(gcoo::kDenseGroupThreads), 0, s>>>(
-                A_dev, lda, m, k, p, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols(), rows_out(h), !band, band ? h->soon() : nullptr,
+                A_dev, lda, m, k, p, g, from, to, h->bad_col(), h->values(), h->rows(), h->cols(), rows_out(h), !band,
                 band ? reinterpret_cast<uint32_t*>(h->base + h->L.persistent + h->L.tmp_cols) : nullptr, gcoo::kBandWaves * h->L.band.h, split);
         } else if (masks)
             (vw == 4 ? gcoo::fill_dense_masked<4> : gcoo::fill_dense_masked<1>)<<<grid, block, 0, s>>>(

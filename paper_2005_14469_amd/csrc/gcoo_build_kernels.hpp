@@ -820,17 +820,18 @@ __global__ __launch_bounds__(kDenseThreads) void fill_dense_masked(const float* 
 // the masks as well.  The entries of the group, as a bit per row and column in LDS, say how many of its row lie in front of each; where the part's entries fit, they are put into row order
 // there and written whole lines at a time.
 // `parts`, for the band schedule: the columns of each group as a bitmap; those of a group that lies across the border of two blocks of `block_rows` rows, of no more than one, as two, the rows of the later block b
-// in parts[g + b].  `places`: the long rows are listed in places of their group (RowsArgs), else by a later launch, since this one clears their count, and the word `soon` of FillArgs.
+// in parts[g + b].  `places`: the long rows are listed in places of their group (RowsArgs), else by a later launch, since this one clears their count, and zeroed[kSoonWord] (FillArgs::soon).
 // Bound: a chain of latencies (masks, list, entries behind the L2), a third of it the loops over a thread's bits and the sums, 16 waves side by side.  Two workgroups to a compute unit, hence 64 registers.
 // Conversion with its count (us; fill, sort by row and, for bands, the bitmaps as launches of their own, and so): 4000 x 4000, 2 %: 48.7 46.9; 10 %: 83.2 65.1; 1000 x 1000, 2 %: 24.0 22.2; 300 x 300, 5 %: 23.1 21.0;
 // 500 x 4000, 20 %: 78.9 47.3; 6000 x 3000, 20 %: 168 123; 14000 x 4000, 0.5 %: 83.8 83.1; 20 %: 517 352.
+constexpr int kSoonWord = 28;                        // (zeroed[0] is 16 bytes behind the beginning of a line)
 constexpr int kDenseGroupThreads = 1024, kDenseWindow = 4 * kDenseGroupThreads;
 constexpr int dense_group_list(int rows) { return rows <= 32 ? 4096 : 2048; }      // entries that a workgroup has in LDS at a time
 template <int ROWS, bool SPLIT>
 __global__ __launch_bounds__(kDenseGroupThreads, 8) void fill_dense_groups(const float* __restrict__ A, int64_t lda, int64_t m, int64_t k, int32_t p, int64_t g,
                                                                          DenseCounts from, DenseCounts to, uint32_t* __restrict__ zeroed,
                                                                          float* __restrict__ values, int32_t* __restrict__ rows, int32_t* __restrict__ cols,
-                                                                         RowsOut out, bool places, uint32_t* __restrict__ soon, uint32_t* __restrict__ parts, int32_t block_rows, int32_t split)
+                                                                         RowsOut out, bool places, uint32_t* __restrict__ parts, int32_t block_rows, int32_t split)
 {
     constexpr int THREADS = kDenseGroupThreads, WAVES = THREADS / kWave, WORDS = kDenseWindow / 32, PITCH = WORDS + 1;      // (a word more keeps the rows on different banks)
     constexpr int LIST = dense_group_list(ROWS), EACH = LIST / THREADS;
@@ -844,7 +845,7 @@ __global__ __launch_bounds__(kDenseGroupThreads, 8) void fill_dense_groups(const
     __shared__ int32_t wsum[WAVES], row_n[ROWS], row_to[ROWS];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     place_dense_counts<THREADS>(from, to, g, zeroed, nullptr);
-    if (soon && blockIdx.x == 0 && threadIdx.x == 4) *soon = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 4) zeroed[kSoonWord] = 0u;
     const int64_t q = SPLIT ? blockIdx.x / split : blockIdx.x, r0 = q * p;
     const int32_t part = SPLIT ? (int32_t)(blockIdx.x - q * split) : 0;
     const int32_t nr = (int32_t)(m - r0 < p ? m - r0 : p), g0 = from.gIdxes[q], g1 = from.gIdxes[q + 1];
