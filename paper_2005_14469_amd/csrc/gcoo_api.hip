@@ -1303,13 +1303,20 @@ int32_t dense_groups_split(int64_t k, int64_t mean, int32_t p)
 }
 // Whether the fill, the order by rows and the bitmaps of the bands are one launch: where a workgroup has all columns of a group in its LDS, but not for many groups of a few rows each, which cost
 // a workgroup of 1024 threads however little is in them (conversion with its count, us, three launches and one: 12000 x 3000, 1 %, 8 rows per group: 91 100; 20000 x 2000, 0.2 %, 16 rows: 57.1 57.6; 2000 x 2000, 1 %,
-// 8 rows: 22.9 21.8).
+// 8 rows: 22.9 21.8).  Where there are bands it takes two launches off (308 shapes of 8 to 64 rows per group: 0.81 of the time; two of more than half of their cells filled 1.06 and 1.08).  Where there are none it takes one off and
+// two workgroups to a compute unit are one round: beyond that only groups of a thousand entries in 200 columns (us, two launches and one, 32 rows per group: 60000 x 64, 16 and 31 % (160 and 640 per group): 43.2 48.5, 52.7 62.6;
+// 200000 x 256, 0.5 %: 110 124; 60000 x 1024, 0.1 %: 73 77; 40000 x 300, 15 % (1440): 55 53, 30 %: 71 61; the group in two parts, 60 % (5760, 24 rows): 135 192).  And a thread goes through all bits of its four columns,
+// so not narrow matrices of which most is filled, nor groups of more than 32 rows whose entries do not fit the list, while their columns are one part or hardly two (200 x 64, all filled: 1.04 and 1.06 of the time at 24 and 32 rows per group,
+// 1.35 to 1.56 at 64; 64 rows, 4000 x 128, 31 %: 34.5 42.2; 256 columns, 35 to 100 %: 1.1 to 1.7; 512: 0.84 to 1).
 bool dense_groups_wanted(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band)
 {
-    const int64_t g = (m + p - 1) / p;
+    const int64_t g = (m + p - 1) / p, mean = nnz / g;
     if (k > gcoo::kDenseWindow || (p < 24 && g > 512)) return false;
     // a group lies in two blocks at the most, and the bitmaps go where the lists' would, into three words per entry
-    return band.h == 0 || (gcoo::kBandWaves * band.h >= p && (g + gcoo::band_blocks(m, band.h)) * ((k + 31) / 32) <= 3 * nnz);
+    if (band.h > 0) return gcoo::kBandWaves * band.h >= p && (g + gcoo::band_blocks(m, band.h)) * ((k + 31) / 32) <= 3 * nnz;
+    const int32_t split = dense_groups_split(k, mean, p);
+    if (g * split > 512 && (split > 1 || k < 200 || mean < 1000)) return false;
+    return !(k <= 64 && mean > 24 * k) && !(p > 32 && k <= 300 && mean + mean / 16 > gcoo::dense_group_list(p));
 }
 
 // The counts of a dense matrix, at the places where a matrix buffer has them (offsets that do not depend on nnz).

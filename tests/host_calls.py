@@ -283,6 +283,31 @@ def dense_waits(host):
     assert host.L.gcoo_from_dense_counted(m, k, nnz, 1 << 20, k, 128, 1 << 20, 1 << 30, 1 << 50, None, C.byref(h)) == OK
 
 
+# ---- how many launches a dense matrix takes --------------------------------------------------------------
+
+def dense_launches(host):
+    """The one launch for a dense matrix's orders is for groups that have work for its threads: not where more workgroups than two to a compute unit have few columns or entries each, nor for narrow groups that are mostly
+    filled; with a band schedule it stands for two launches and is taken there."""
+    def names(m, k, nnz, p):
+        h = C.c_void_p()
+        host.log()
+        assert host.L.gcoo_from_dense_counted(m, k, nnz, 1 << 20, k, p, 1 << 20, 1 << 30, 1 << 50, None, C.byref(h)) == OK
+        log = host.launches()
+        host.L.gcoo_free(h)
+        kinds = [x for x in ("fill_dense_groups", "fill_dense_masked", "band_fill") if any(x in name for name in log)]
+        assert len(kinds) == len(log) or kinds[0] == "fill_dense_masked", log
+        return kinds
+    one, two = ["fill_dense_groups"], ["fill_dense_masked"]
+    for m, p in [(512 * 32, 32), (512 * 64, 64), (512 * 8, 8)]:
+        assert names(m, 64, 20 * m, p) == one and names(m + 1, 64, 20 * m, p) == two, p
+    for k, per_group, p, kinds in [(199, 1500, 32, two), (200, 1500, 32, one), (200, 999, 32, two), (200, 1000, 32, one), (300, 4000, 32, two)]:
+        assert names(20000, k, 625 * per_group, p) == kinds, (k, per_group)
+    for k, per_group, p, kinds in [(64, 64 * 24, 32, one), (64, 64 * 25, 32, two), (65, 65 * 25, 32, one), (65, 1900, 64, one), (65, 2100, 64, two), (300, 2100, 64, two), (301, 2100, 64, one), (256, 4100, 32, one)]:
+        assert names(10 * p, k, 10 * per_group, p) == kinds, (k, per_group, p)
+    for m, k, nnz, p in [(64000, 1000, 1280000, 32), (300000, 128, 3840000, 32), (4000, 4000, 320000, 32)]:
+        assert names(m, k, nnz, p) == ["fill_dense_groups", "band_fill"], (m, k)
+
+
 # ---- a matrix without columns --------------------------------------------------------------------------
 
 def no_columns(host):
