@@ -1652,7 +1652,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     }
     if (kernel == GCOO_KERNEL_ROWS || kernel == GCOO_KERNEL_BAND) {
         gcoo::RowsArgs rows{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
-                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz), 0};
+                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz), !A->from_csr, 0};
         if (A->long_places) {
             // no places are looked at where only a row that repeats columns could be long
             const bool some = A->k > rows.long_row;

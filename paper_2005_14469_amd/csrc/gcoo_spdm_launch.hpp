@@ -62,6 +62,25 @@ struct ShareArgs {
 };
 hipError_t launch_spdm_share(const ShareArgs& a, hipStream_t s);
 
+// Which place workgroup `wg` of a tile begins with, where XCDs share the tile and the long rows are in places of a dense matrix: a stretch of a tile's workgroups is on one XCD, and the places in
+// their order would be too.  The workgroups are cut into as many pieces as XCDs share a tile, and the places are dealt to the pieces one by one.  Product against a counted list, places in their order and so:
+// twenty rows 90 % full in matrices of rows of a few entries, 31 of 1000 to 20000 rows, N = 16 to 1000: 1.05 0.98 of the time (us: 2564 x 1762, N = 120: 11.8 15.8 11.5); power-law rows, 59 of them: 1.00 1.01; even rows: 0.98 0.98.
+// (Exact turns by XCD, a sum over the XCDs in front of the entries: even rows 1.02.  From CSR arrays, where long rows are in places too, 166 uneven matrices were level with and without.)
+struct RowsTurns {
+    int32_t piece, whole, rest;      // workgroups of a piece, pieces of as many, workgroups of the one behind them
+    uint32_t inverse;                // of `piece`, in units of 2^-32
+};
+inline RowsTurns rows_turns(int64_t row_wgs, int64_t tiles)
+{
+    const int64_t rest = tiles % 8 ? tiles % 8 : 8, xcds = (8 + rest - 1) / rest, even = (row_wgs + xcds - 1) / xcds, piece = even > 2 ? even : 2;
+    return {(int32_t)piece, (int32_t)(row_wgs / piece), (int32_t)(row_wgs % piece), (uint32_t)(0xffffffffull / (uint64_t)piece) + 1u};
+}
+__host__ __device__ inline int32_t rows_turn(const RowsTurns& t, int32_t wg)
+{
+    const int32_t q = (int32_t)(((uint64_t)(uint32_t)wg * t.inverse) >> 32), i = wg - q * t.piece;
+    return i < t.rest ? i * (t.whole + 1) + q : t.rest * (t.whole + 1) + (i - t.rest) * t.whole + q;
+}
+
 // The kernel that works row by row on the entries in row order: any N, ldb < 2^30, any alignment of 4 bytes, k >= 1.
 struct RowsArgs {
     const int32_t* row_ptr;    // [m + 1]
@@ -78,6 +97,7 @@ struct RowsArgs {
     const int32_t* long_rows;  // long_room places for the rows of more than `long_row` entries (RowsOut)
     const int32_t* long_count; // or null: -1 in places without a row
     int32_t long_row, long_room;
+    bool spread;               // the places are taken by rows_turn()
     int32_t moved;             // 31: tiles are moved down to whole lines of C, 0: they are not (set by the launchers)
 };
 // A row of more entries than this is shared by a whole workgroup.

@@ -261,11 +261,15 @@ struct RowsTile {
     }
 };
 
+// Where the long rows are: in a list, or in places, which workgroups begin with in their order or by rows_turn().
+enum RowsLong { kLongCounted, kLongPlaces, kLongSpread };
+
 // The long rows `turn`, `turn` + step, ..., the `n_front` longest first, all slots of a workgroup on each.  `part`: a stretch of a tile's columns per wave in LDS.  PLACES: the long rows are
 // in places, not counted (RowsArgs), and place `turn` holds `at_turn`.
-template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
+template <int LPR, bool WIDE, int AHEAD, int SUMS, RowsLong LONG>
 __device__ __forceinline__ void rows_long_rows(const RowsTile<LPR, WIDE, AHEAD, SUMS>& T, int32_t n_front, int32_t n_long, int32_t turn, int32_t step, int32_t at_turn, float (*part)[LPR * 4])
 {
+    constexpr bool PLACES = LONG != kLongCounted;
     constexpr int SPW = 64 / LPR, SLOTS = SPW * kRowsWaves;
     const RowsArgs& a = T.a;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -345,12 +349,13 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD, SU
 
 // Item `block`, (tile, wg): rows [wg * kRowsWaves * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
 // places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
-template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
-__device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, float (*part)[LPR * 4])
+template <int LPR, bool WIDE, int AHEAD, int SUMS, RowsLong LONG>
+__device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, const RowsTurns& turns, float (*part)[LPR * 4])
 {
     // XCD-aware order: an XCD walks all rows of one column tile before the next, so that the tile of B stays in its L2, and the
     // eight XCDs work on eight tiles side by side, so that what they read and write of a row at about the same time is one
     // stretch of 2 KB.  The tiles beyond the last whole eight are cut into eight slices of rows.
+    constexpr bool PLACES = LONG != kLongCounted;
     const int32_t xcd = (int32_t)(block & 7u), at = (int32_t)(block >> 3), eights = tiles / 8;
     int32_t tile, wg, slice = 0;                                     // slice: workgroups that an XCD has of the cut tiles, 0 where it has the whole tile
     if (at < eights * row_wgs) {
@@ -368,11 +373,12 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
     const int32_t m = (int32_t)a.m, w0 = (wg * kRowsWaves + wv) * rpw;                    // the wave's first row
     const int32_t wrows = m - w0 < 0 ? 0 : (m - w0 < rpw ? m - w0 : rpw);
     const int32_t start = T.lane <= wrows && wrows > 0 ? a.row_ptr[w0 + T.lane] : 0;
-    const int32_t long_first = PLACES && wg < a.long_room ? a.long_rows[wg] : -1;    // (asked for beside the starts)
+    int32_t turn = wg;
+    if constexpr (LONG == kLongSpread) turn = slice ? rows_turn(turns, wg) : wg;
+    const int32_t long_first = PLACES && turn < a.long_room ? a.long_rows[turn] : -1;    // (asked for beside the starts)
     int32_t n_front = PLACES ? 0 : (a.long_count ? a.long_count[2] : 0), n_long = PLACES ? a.long_room : (a.long_count ? a.long_count[0] : 0);
     n_front = n_front < a.long_room ? n_front : a.long_room;
     n_long = n_long < a.long_room - n_front ? n_front + n_long : a.long_room;
-    int32_t turn = wg;
     if (__builtin_expect(!PLACES && slice && n_long > 0, 0)) {
         // The XCDs that share a tile take its long rows in turns: by the place of a workgroup among those of its XCD, then by XCD.  (In the order of `wg` the first XCD of a tile would
         // have them all; power-law rows, 9958 x 11050, N = 64, 128, 256: 26.5 41.4 48.8 us so, 18.8 24.9 33.3 in turns.)
@@ -384,7 +390,7 @@ __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int
         }
     }
     // (out of the way of matrices without long rows; 12000 x 12000, 0.5 %, N = 64: level, 12.15 us without the hints, 12.13 so)
-    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, SUMS, PLACES>(T, n_front, n_long, turn, row_wgs, long_first, part);
+    if (PLACES || __builtin_expect(n_long > 0, 0)) rows_long_rows<LPR, WIDE, AHEAD, SUMS, LONG>(T, n_front, n_long, turn, row_wgs, long_first, part);
     rows_of_wave<LPR, WIDE, AHEAD, SUMS>(T, w0, wrows, start, wave_row, a.long_row);
 }
 
@@ -490,11 +496,11 @@ __device__ __forceinline__ void rows_all(const RowsArgs& a, int32_t tiles, int32
         tile_rows(eights * 8 + (int32_t)x, from > x * all ? from - x * all : 0, to < (x + 1) * all ? to - x * all : all, all);
 }
 
-template <int LPR, bool WIDE, int AHEAD, int SUMS, bool PLACES>
-__global__ __launch_bounds__(kRowsThreads, AHEAD == 16 ? 4 : 8) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row)
+template <int LPR, bool WIDE, int AHEAD, int SUMS, RowsLong LONG>
+__global__ __launch_bounds__(kRowsThreads, AHEAD == 16 ? 4 : 8) void spdm_rows(RowsArgs a, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, RowsTurns turns)
 {
     __shared__ __attribute__((aligned(16))) float part[kRowsWaves][LPR * 4];
-    rows_item<LPR, WIDE, AHEAD, SUMS, PLACES>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, part);
+    rows_item<LPR, WIDE, AHEAD, SUMS, LONG>(a, blockIdx.x, tiles, row_wgs, rpw, wave_row, turns, part);
 }
 
 // B of one, two or three columns: sixteen lanes share a row, each takes every sixteenth entry, and their sums are added up in a
