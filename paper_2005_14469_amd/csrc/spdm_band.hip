@@ -45,10 +45,10 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
     rg.rpw = 4;                                              // (8: as fast)
     rg.wave_row = (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row);
     // How the rows of B are requested goes by the entries of a (wave, band).  Product alone, against behind the first unit, mean of 20 to 200 matrices each; wide:
-    //   entries                    8 - 10  12 - 14  14 - 16  16 - 18  20 - 22  24 - 26  28 - 32  36 - 40  40 - 50  80 - 150
-    //   a row at a time             0.975    0.978    0.993    1.004    1.031    1.051    1.058    1.043    1.044     1.021
-    //   behind the second step      0.999    0.985    0.986    0.989    0.999    1.011    1.017    1.012    1.013     1.006
-    //   behind the second unit      1.000    1.018    1.031    1.051    1.087    1.077    1.049    1.007    0.998     0.997
+    //   entries                    8 - 10  12 - 14  14 - 16  17 - 18  19 - 20  20 - 21  22 - 23  25 - 26  28 - 29  36 - 40  40 - 50  80 - 150
+    //   a row at a time             0.975    0.978    0.993    1.025    1.028    1.038    1.043    1.043    1.051    1.043    1.044     1.021
+    //   behind the second step      0.999    0.985    0.986    0.993    0.998    1.002    1.007    1.010    1.016    1.012    1.013     1.006
+    //   behind the second unit      1.000    1.018    1.031    1.088    1.095    1.105    1.089    1.062    1.047    1.007    0.998     0.997
     // tall:
     //   entries                   14 - 16  16 - 18  18 - 20  20 - 22  24 - 26  28 - 32  32 - 36  36 - 40  40 - 50   60 - 80
     //   a row at a time             0.989    0.990    0.997    1.003    1.029    1.049    1.052    1.056    1.056     1.055
@@ -59,7 +59,7 @@ hipError_t launch_spdm_band(const BandArgs& a, const RowsArgs& rows, hipStream_t
         if (entries < 20.0) return launch_band<2, true, false>(b, by_rows, rg, s);
         return entries < 37.0 ? launch_band<2, false, false>(b, by_rows, rg, s) : launch_band<2, false, true>(b, by_rows, rg, s);
     }
-    if (entries < 28.0) return entries < 14.0 ? launch_band<4, true, false>(b, by_rows, rg, s) : launch_band<4, true, true>(b, by_rows, rg, s);
+    if (entries < 20.0) return entries < 14.0 ? launch_band<4, true, false>(b, by_rows, rg, s) : launch_band<4, true, true>(b, by_rows, rg, s);
     return entries < 42.0 ? launch_band<4, false, false>(b, by_rows, rg, s) : launch_band<4, false, true>(b, by_rows, rg, s);
 }
 

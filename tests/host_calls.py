@@ -453,6 +453,19 @@ def cuts(host):
         assert "spdm_bandILi%dE" % (2 if k == 65536 else 4) in host.launches()[0], k
 
 
+def requests(host):
+    """When the rows of the next band are asked for, by the entries of a (wave, band); in the wide cut the late half behind the second step of its first unit up to 20, behind that unit from there on
+    (measured, us: 4000 x 4000, 2 %, 25 entries: 88.6 88.2; 8632 x 8488, 1.7 %, 24 entries: 730 715; the other way round at 17: 7417 x 7331, 1.2 %: 366 369)."""
+    for m, k, N, nnz, kernel in [(1000, 3000, 2045, 150000, "ILi4ELb1ELb0E"), (7417, 7331, 7272, 631827, "ILi4ELb1ELb1E"), (4000, 4000, 2045, 224000, "ILi4ELb1ELb1E"), (4000, 4000, 4000, 320000, "ILi4ELb0ELb0E"),
+                                 (4000, 4000, 2053, 480000, "ILi4ELb0ELb0E"), (4000, 4000, 2053, 640000, "ILi4ELb0ELb1E"), (5600, 5601, 2601, 90000, "ILi2ELb1ELb0E"), (5000, 5001, 2605, 210000, "ILi2ELb0ELb0E"),
+                                 (5000, 5001, 2605, 235000, "ILi2ELb0ELb1E")]:
+        h = host.matrix(m, k, nnz, 32)
+        host.log()
+        assert host.spdm(h, N, N) == OK
+        (name,) = host.launches()
+        assert "spdm_band" + kernel in name, (m, k, N, nnz, name)
+
+
 def tall_rounds(host):
     """Where a (wave, band) has many entries a launch in the tall cut costs whole rounds of its workgroups over the 256 compute units: one that leaves much of its
     last round idle is not taken (measured, us, with the idle round and with the height taken: 9000 x 9000, 1 %: 776 657; 9600 x 9600, 0.9 %: 798 720; 10000 x 10000, 0.75 %:

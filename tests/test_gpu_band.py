@@ -86,10 +86,11 @@ def test_automatic_choice_of_both_cuts(m, k, N, s, shift, pad):
     _run(workloads.uniform_random(m, k, N, s, seed=m + N), 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
 
 
-@pytest.mark.parametrize("m,k,N,nnz", [(4000, 4000, 2045, 320000), (5600, 5601, 2601, 90000)])
+@pytest.mark.parametrize("m,k,N,nnz", [(4000, 4000, 2045, 320000), (5600, 5601, 2601, 90000), (1000, 3000, 2045, 150000), (4000, 4000, 2045, 224000)])
 @pytest.mark.parametrize("shift,pad", [(1, 0), (2, 1), (3, 2)])
 def test_requests_spread_over_a_band_from_rows_aligned_to_4_bytes(m, k, N, nnz, shift, pad):
-    """Sixteen bytes per lane from any multiple of four bytes straight to LDS, in the wide cut and in the tall one with few entries per band."""
+    """Sixteen bytes per lane from any multiple of four bytes straight to LDS: by the late half behind its first unit, a row at a time and step in the tall cut and in the wide one, and by the late half behind its second
+    step."""
     print(f"band, spread requests: m={m} k={k} N={N} shift={shift} pad={pad}", flush=True)
     _run(workloads.uniform_random(m, k, N, 1 - nnz / (m * k), seed=m + N), 32, binding.VARIANT_AUTO, shift, pad, kernel=binding.KERNEL_BAND)
 
@@ -97,7 +98,7 @@ def test_requests_spread_over_a_band_from_rows_aligned_to_4_bytes(m, k, N, nnz, 
 @pytest.mark.parametrize("m,k,per_row,N", [(4000, 4000, 40, 2605), (5000, 5001, 47, 2605), (5000, 5001, 42, 2605), (4000, 4000, 160, 2053), (4000, 4000, 120, 2053), (4000, 4000, 76, 2053)])
 @pytest.mark.parametrize("even", [True, False])
 def test_requests_of_the_late_half_behind_the_first_and_the_second_unit(m, k, per_row, N, even):
-    """Both cuts, on both sides of the number of entries from which the late half asks behind its second unit; waves of one unit to a band beside waves of many."""
+    """Both cuts, on both sides of the number of entries from which the late half asks behind its second unit, by its first one below; waves of one unit to a band beside waves of many."""
     print(f"band, late half: m={m} k={k} per_row={per_row} even={even}", flush=True)
     rng = np.random.default_rng(m + per_row)
     n = np.full(m, per_row) if even else np.resize(np.repeat([per_row // 8, 2 * per_row, per_row // 2, 3 * per_row // 2], 40), m)
