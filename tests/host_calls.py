@@ -428,13 +428,14 @@ def widths(host):
 
 # ---- the cuts of the band schedule -------------------------------------------------------------------
 
-# (m, k, N, entries, variant): what tests/test_gpu_band.py multiplies by the wide cut and by the tall one, and by which instance
-CUTS = [("ILi2ELb0E", 384, 3500, 260, 384 * 150, SHARE), ("ILi2ELb0E", 777, 3500, 252, 777 * 150, SHARE), ("ILi4ELb1E", 4000, 4000, 2044, 320000, AUTO),
+# (m, k, N, entries, variant): what tests/test_gpu_band.py multiplies by the wide cut and by the tall one, and by which instance (Lb1: requests within a band's first unit, below 20 entries of a (wave, band); in the wide
+# cut it was below 28, four of these are between, and 522 matrices are faster so: requests())
+CUTS = [("ILi2ELb0E", 384, 3500, 260, 384 * 150, SHARE), ("ILi2ELb0E", 777, 3500, 252, 777 * 150, SHARE), ("ILi4ELb0E", 4000, 4000, 2044, 320000, AUTO),
         ("ILi4ELb0E", 4000, 3000, 1001, 1200000, AUTO), ("ILi2ELb1E", 384, 3500, 260, 384 * 60, SHARE), ("ILi2ELb1E", 777, 3500, 252, 777 * 62, SHARE),
         ("ILi2ELb1E", 97, 3500, 64, 97 * 130, SHARE), ("ILi2ELb1E", 300, 7000, 1000, 9450, SHARE), ("ILi2ELb1E", 40, 3500, 256, 2800, SHARE),
-        ("ILi2ELb0E", 5000, 5001, 2501, 125025, AUTO), ("ILi4ELb1E", 4000, 4000, 2045, 320000, AUTO), ("ILi2ELb1E", 5600, 5601, 2601, 90000, AUTO),
-        ("ILi4ELb0E", 2600, 3500, 260, 2600 * 150, SHARE), ("ILi4ELb0E", 4607, 3500, 252, 4607 * 150, SHARE), ("ILi4ELb1E", 4700, 3500, 252, 4700 * 62, SHARE),
-        ("ILi2ELb0E", 2700, 3500, 260, 2700 * 60, SHARE), ("ILi4ELb1E", 1500, 3500, 64, 1500 * 150, SHARE), ("ILi4ELb1E", 1000, 3500, 64, 1000 * 205, SHARE),
+        ("ILi2ELb0E", 5000, 5001, 2501, 125025, AUTO), ("ILi4ELb0E", 4000, 4000, 2045, 320000, AUTO), ("ILi2ELb1E", 5600, 5601, 2601, 90000, AUTO),
+        ("ILi4ELb0E", 2600, 3500, 260, 2600 * 150, SHARE), ("ILi4ELb0E", 4607, 3500, 252, 4607 * 150, SHARE), ("ILi4ELb0E", 4700, 3500, 252, 4700 * 62, SHARE),
+        ("ILi2ELb0E", 2700, 3500, 260, 2700 * 60, SHARE), ("ILi4ELb0E", 1500, 3500, 64, 1500 * 150, SHARE), ("ILi4ELb1E", 1000, 3500, 64, 1000 * 205, SHARE),
         ("ILi2ELb0E", 301, 2962, 2427, 301 * 350, AUTO), ("ILi2ELb0E", 120, 6000, 6000, 120 * 900, AUTO), ("ILi4ELb0E", 1836, 2885, 1836, 1836 * 577, AUTO)]
 
 
