@@ -633,8 +633,9 @@ bool order_plan(int64_t m, int64_t k, int64_t nnz, int32_t p, BandPlan band, boo
     const bool ranked = 2 * k > 11 * mean && (k > ((int64_t)1 << most) || band.h > 0 || run_schedule_wanted(p));
     int32_t shift = ranked ? 5 : 0;
     while (((int64_t)1 << shift) < k && shift < (ranked ? 14 : most)) ++shift;
-    // entries that the LDS holds beside the masks of a part's columns
-    const auto room_at = [&](int32_t shift) { return (kOrderLds - 4 * (((int64_t)1 << shift) * (words + 1) + 2 * 1024)) / 9; };
+    // entries, of eight bytes, that the LDS holds beside the masks of a part's columns (the largest groups that go in one launch, us, in two and so: 3000 x 1000, 16 % (5180 per group): 14.8 9.9;
+    // 3000 x 2500, 3 % (2440): 13.0 7.0; 1000 x 2000, 6 % (4020): 11.1 7.5)
+    const auto room_at = [&](int32_t shift) { return (kOrderLds - 4 * (((int64_t)1 << shift) * (words + 1) + 2 * 1024)) / 8; };
     const int64_t room = room_at(shift);
     const bool fused = !ranked && k <= ((int64_t)1 << most) && mean + mean / 16 <= room && band.h == 0 && !run_schedule_wanted(p);
     const int32_t threads = fused && (mean > 2048 || (g <= 256 && ((int64_t)words << shift) >= 4096)) ? 1024 : gcoo::kOrderThreads;

@@ -207,9 +207,9 @@ struct OrderArgs {
 
 inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 {
-    if (plan.keys) return ((size_t)2 << plan.shift) / 8 + (size_t)plan.keys * (4 * words + 4) + (size_t)plan.cap * 9;
+    if (plan.keys) return ((size_t)2 << plan.shift) / 8 + (size_t)plan.keys * (4 * words + 4) + (size_t)plan.cap * 8;
     const size_t ncols = (size_t)1 << plan.shift, spare = ncols < (size_t)plan.threads ? ncols : (size_t)plan.threads;
-    return (ncols * (words + 1) + 2 * spare) * 4 + (size_t)plan.cap * 9;
+    return (ncols * (words + 1) + 2 * spare) * 4 + (size_t)plan.cap * 8;
 }
 
 // Workgroup (q, part).  WORDS = 32-bit words of a column's mask.  Dynamic LDS: order_lds_bytes().

@@ -308,6 +308,21 @@ def dense_launches(host):
         assert names(m, k, nnz, p) == ["fill_dense_groups", "band_fill"], (m, k)
 
 
+# ---- LDS of the conversion by masks ----------------------------------------------------------------------
+
+def order_lds(host):
+    """A place of a group's entries in LDS is eight bytes, value and row and column in a word: one launch converts groups of as many entries as 61 KB hold of them beside the masks, and asks for no more than it uses."""
+    for m, k, per_group, p, launches in [(3200, 1000, 5350, 32, 1), (3200, 1000, 5450, 32, 2), (3200, 2300, 2500, 32, 1), (3200, 2300, 2580, 32, 2), (6400, 1000, 4000, 64, 1)]:
+        host.log()
+        host.L.gcoo_free(host.matrix(m, k, per_group * (m // p), p))
+        log = [line.split() for line in host.log() if line.startswith("launch")]
+        assert len(log) == launches, (k, per_group, log)
+        if launches == 1:
+            keys, words, threads = 1 << (k - 1).bit_length(), p // 32, int(log[0][3])
+            held = (int(log[0][4]) - 4 * (keys * (words + 1) + 2 * min(keys, threads))) / 8
+            assert held == int(held) and per_group < held <= 3 * (per_group + 1) // 2 + 67 and int(log[0][4]) <= 61 * 1024, (k, per_group, log)
+
+
 # ---- a matrix without columns --------------------------------------------------------------------------
 
 def no_columns(host):
