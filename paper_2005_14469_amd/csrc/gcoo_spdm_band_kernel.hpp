@@ -34,7 +34,7 @@
 // stands still: with all five requests of all waves at the band's start nobody multiplied for the first 0.5 us.  Four ways (SPREAD, LATE):
 //   true, false     every wave asks for two rows at the start and one behind each of its first three steps; a band of few entries per
 //                   wave would end before the late half's rows have landed
-//   true, true      waves 0 - 7 at the start, waves 8 - 15 behind the second step of their first unit (or at the end of the band): one half
+//   true, true      (the wide cut only) waves 0 - 7 at the start, waves 8 - 15 behind the second step of their first unit (or at the end of the band): one half
 //                   multiplies while the other asks
 //   false, false    as that, waves 8 - 15 behind their first unit
 //   false, true     as that, waves 8 - 15 behind their second unit: where a band has units enough, the later the better
@@ -233,22 +233,22 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     BD_READ_T0(m0) BD_READ_T1(m1) BD_READ_T2(m2) BD_READ_T3(m3)                                 \
     BD_ASK_START(s, X)                                                                          \
     ".Lbd_s0_" #X "_%=:\n\t"                                                                    \
-    BD_TURN(0) "s_sub_u32 s22, s22, 1\n\t"                                                                 \
+    BD_TURN(0) "s_sub_u32 s22, s22, 1\n\t"                                                      \
     BD_READ_T4(m4) BD_READ_T5(m5) BD_WAIT(4) BD_TWO(a0, m0, T0, a1, m1, T1)                     \
     BD_READ_T0(m6) BD_READ_T1(m7) BD_WAIT(4) BD_TWO(a2, m2, T2, a3, m3, T3)                     \
     BD_ASK_STEP(s, 0, X)                                                                        \
     ".Lbd_s1_" #X "_%=:\n\t"                                                                    \
-    BD_TURN(1) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
+    BD_TURN(1) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                 \
     BD_READ_T2(m8) BD_READ_T3(m9) BD_WAIT(4) BD_TWO(a4, m4, T4, a5, m5, T5)                     \
     BD_READ_T4(m10) BD_READ_T5(m11) BD_WAIT(4) BD_TWO(a6, m6, T0, a7, m7, T1)                   \
     BD_ASK_STEP(s, 1, X)                                                                        \
     ".Lbd_s2_" #X "_%=:\n\t"                                                                    \
-    BD_TURN(2) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
+    BD_TURN(2) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                 \
     BD_READ_T0(m12) BD_READ_T1(m13) BD_WAIT(4) BD_TWO(a8, m8, T2, a9, m9, T3)                   \
     BD_READ_T2(m14) BD_READ_T3(m15) BD_WAIT(4) BD_TWO(a10, m10, T4, a11, m11, T5)               \
     BD_ASK_STEP(s, 2, X)                                                                        \
     ".Lbd_s3_" #X "_%=:\n\t"                                                                    \
-    BD_TURN(3) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                            \
+    BD_TURN(3) "s_sub_u32 s22, s22, 1\n\ts_cbranch_scc1 .Lbd_end_" #Y "_%=\n\t"                 \
     BD_WAIT(2) BD_TWO(a12, m12, T0, a13, m13, T1)                                               \
     BD_WAIT(0) BD_TWO(a14, m14, T2, a15, m15, T3)                                               \
     "s_cmp_lg_u32 s22, 0\n\ts_cbranch_scc1 .Lbd_units_" #Y "_%=\n\t"                            \
@@ -317,6 +317,7 @@ struct BandRowsGrid { int32_t tiles, rpw, wave_row; };
 template <int V, bool SPREAD, bool LATE>            // V = 4: the wide cut, 2: the tall one; when the rows of the next band are requested
 __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArgs by_rows, BandRowsGrid rg)
 {
+    static_assert(V == 4 || !(SPREAD && LATE), "");
     extern __shared__ __attribute__((aligned(16))) uint32_t band_smem[];
     if (*a.uneven != 0u) {
         rows_all<16>(by_rows, rg.tiles, rg.rpw, rg.wave_row, *reinterpret_cast<RowsAllLds*>(band_smem));
@@ -440,21 +441,11 @@ __global__ __launch_bounds__(64 * kBandWaves) void spdm_band(BandArgs a, RowsArg
 #define BD_MORE_SCALARS , "s100"
             const uint32_t lane_b = jb + (int32_t)((lane & 31u) * 4u) < n ? (lane & 31u) * 16u : 0u;
 #define BD_FILL BD_FILL_TALL
-            if constexpr (SPREAD && !LATE) {
+            if constexpr (SPREAD) {
 #define BD_ASK_START BD_SPREAD_START
 #define BD_ASK_STEP BD_SPREAD_STEP
 #define BD_ASK_UNIT BD_SPREAD_UNIT
 #define BD_ASK_REST BD_SPREAD_REST
-                BD_MAIN;
-#undef BD_ASK_START
-#undef BD_ASK_STEP
-#undef BD_ASK_UNIT
-#undef BD_ASK_REST
-            } else if constexpr (SPREAD) {
-#define BD_ASK_START BD_FIRST_START
-#define BD_ASK_STEP BD_STEP1_STEP
-#define BD_ASK_UNIT BD_STEP1_UNIT
-#define BD_ASK_REST BD_STEP1_REST
                 BD_MAIN;
 #undef BD_ASK_START
 #undef BD_ASK_STEP
