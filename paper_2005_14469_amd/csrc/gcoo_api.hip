@@ -1109,8 +1109,10 @@ int from_csr(int64_t m, int64_t k, const int32_t* row_ptr, const int32_t* col_id
         o.row_ptr = d_row_ptr; o.nnz = (int32_t)nnz; o.g = g; o.gIdxes_out = h->gIdxes(); o.nnzPerGroup_out = h->nnzPerGroup();
         o.row_start_out = h->row_start(); o.flags_out = h->take_flags(); o.far = (bool)stage;
         if (starts_given) {
+            // from the copy, which nobody else writes, and held inside the entries as the kernel holds what it reads itself
+            const int32_t* copied = reinterpret_cast<const int32_t*>(stage.ptr());
             gcoo::GroupStarts starts;
-            for (int64_t q = 0; q <= g; ++q) starts.at[q] = row_ptr[q < g ? q * p : m];
+            for (int64_t q = 0; q <= g; ++q) starts.at[q] = std::min(std::max(copied[q < g ? q * p : m], 0), (int32_t)nnz);
             auto order = L.plan.threads == 1024 ? (words == 1 ? gcoo::order_groups_host<1, 1024> : gcoo::order_groups_host<2, 1024>)
                                                 : (words == 1 ? gcoo::order_groups_host<1, gcoo::kOrderThreads> : gcoo::order_groups_host<2, gcoo::kOrderThreads>);
             order<<<dim3((unsigned)g), dim3((unsigned)L.plan.threads), gcoo::order_lds_bytes(L.plan, words), s>>>(o, starts);

@@ -19,6 +19,10 @@ std::map<const void*, void*> g_vars;
 std::map<std::string, long long> g_settings;
 std::string g_log;
 void* g_told = nullptr;
+std::string g_poke_in;                                       // see host_poke()
+int32_t* g_poke_at = nullptr;
+int32_t g_poke_value = 0;
+int32_t g_starts[513];                                       // see host_starts()
 
 long long setting(const char* key)
 {
@@ -31,6 +35,10 @@ void say(const std::string& line)
     std::lock_guard<std::recursive_mutex> lock(g_mutex);
     g_log += line + "\n";
 }
+void poke(const char* call)
+{
+    if (g_poke_at && g_poke_in == call) { *g_poke_at = g_poke_value; g_poke_at = nullptr; }
+}
 }  // namespace
 
 extern "C" {
@@ -41,6 +49,9 @@ void host_set(const char* key, long long value)
     std::lock_guard<std::recursive_mutex> lock(g_mutex);
     g_settings[key] = value;
 }
+// The next `call` (hipStreamIsCapturing or hipHostGetDevicePointer) stores `value` at `at`, as another thread of the program might.
+void host_poke(const char* call, int32_t* at, int32_t value) { g_poke_in = call; g_poke_at = at; g_poke_value = value; }
+const int32_t* host_starts() { return g_starts; }            // what the last order_groups_host was told about the groups
 void* host_told() { return g_told; }                         // where the last counting kernel wrote its number
 const char* host_log()
 {
@@ -74,6 +85,7 @@ int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t sh
     std::lock_guard<std::recursive_mutex> lock(g_mutex);
     const std::string& name = g_names[f];
     say("launch " + name + " " + std::to_string(grid.x) + " " + std::to_string(block.x) + " " + std::to_string(shared));
+    if (name.find("order_groups_host") != std::string::npos) memcpy(g_starts, args[1], sizeof g_starts);
     // the kernels that tell the host a number: the place of the pointer among their arguments
     int host = name.find("read_entry_count") != std::string::npos ? 2 : name.find("count_dense_total") != std::string::npos ? 6
              : name.find("count_dense_blocks") != std::string::npos ? 9 : -1;
@@ -96,11 +108,11 @@ int hipGetSymbolAddress(void** p, const void* var)
     return *p ? 0 : 1;
 }
 int hipHostMalloc(void** p, size_t bytes, unsigned flags) { *p = aligned_alloc(4096, (bytes + 4095) / 4096 * 4096); say("pinned " + std::to_string(flags)); return 0; }
-int hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return 0; }
+int hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; poke("hipHostGetDevicePointer"); return 0; }
 int hipMemcpyAsync(void* to, const void* from, size_t bytes, int, void*) { memcpy(to, from, bytes); say("copy"); return 0; }
 int hipStreamSynchronize(void*) { say("wait stream"); return (int)setting("hipStreamSynchronize"); }
 int hipDeviceSynchronize() { say("wait device"); return (int)setting("hipDeviceSynchronize"); }
-int hipStreamIsCapturing(void*, int* status) { *status = (int)setting("capturing"); return (int)setting("hipStreamIsCapturing"); }
+int hipStreamIsCapturing(void*, int* status) { poke("hipStreamIsCapturing"); *status = (int)setting("capturing"); return (int)setting("hipStreamIsCapturing"); }
 int hipEventCreateWithFlags(void** e, unsigned) { *e = malloc(1); return 0; }
 int hipEventDestroy(void* e) { free(e); return 0; }
 int hipEventRecord(void*, void*) { say("record"); return (int)setting("hipEventRecord"); }

@@ -31,6 +31,8 @@ class Host:
         self.hip.host_set.argtypes = [C.c_char_p, C.c_longlong]
         self.hip.host_log.restype = C.c_char_p
         self.hip.host_told.restype = C.c_void_p
+        self.hip.host_poke.argtypes = [C.c_char_p, C.c_void_p, C.c_int32]
+        self.hip.host_starts.restype = C.POINTER(C.c_int32)
         self.L = C.CDLL(LIB)
         i64, i32, vp, sz = C.c_int64, C.c_int32, C.c_void_p, C.c_size_t
         for name, res, args in [
@@ -184,6 +186,27 @@ def stage_release_fails(host):
     assert _host_csr(host, *shape) == OK
     log = host.log()
     assert "record" not in log and log.count("copy") == 3 and "wait stream" in log, log
+
+
+def starts_of_a_changing_input(host):
+    """Where the groups begin goes to the device in a launch's arguments, and the kernel reads and writes from there to there: whatever another thread does to the caller's arrays behind their check, no group begins or ends
+    outside the entries, and once the arrays are copied nothing of them is read again."""
+    m, k, per_row, p = 100, 200, 5, 32
+    rp = (np.arange(m + 1) * per_row).astype(np.int32)
+    ci, va = np.tile(np.arange(per_row, dtype=np.int32), m), np.ones(m * per_row, np.float32)
+    need = host.L.gcoo_device_bytes(m, k, m * per_row, p)
+    want = [0, 160, 320, 480, 500]
+    for call, at, value, starts in [(b"", 0, 0, want), (b"hipHostGetDevicePointer", 64, 1 << 30, want), (b"hipHostGetDevicePointer", 100, 1 << 30, want),
+                                    (b"hipStreamIsCapturing", 64, 1 << 30, [0, 160, 500, 480, 500]), (b"hipStreamIsCapturing", 32, -7, [0, 0, 320, 480, 500])]:
+        mine, h = rp.copy(), C.c_void_p()
+        if call:
+            host.hip.host_poke(call, mine.ctypes.data + 4 * at, value)
+        host.log()
+        assert host.L.gcoo_from_csr(m, k, mine.ctypes.data, ci.ctypes.data, va.ctypes.data, 0, p, host.buffer(need), need, None, C.byref(h)) == OK
+        assert any("order_groups_host" in name for name in host.launches())
+        assert not call or mine[at] == value
+        assert list(host.hip.host_starts()[:5]) == starts, (call, at, list(host.hip.host_starts()[:5]))
+        host.L.gcoo_free(h)
 
 
 def pinned_memory_is_coherent(host):
