@@ -1655,7 +1655,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
     }
     if (kernel == GCOO_KERNEL_ROWS || kernel == GCOO_KERNEL_BAND) {
         gcoo::RowsArgs rows{A->row_start(), A->row_cols(), A->row_vals(), A->m, A->k, A->nnz, B_dev, ldb, N, C_dev, ldc,
-                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz), !A->from_csr, 0};
+                            A->long_rows(), A->long_count(), gcoo::rows_long(A->m, A->nnz), long_room(A->m, A->nnz), 0};
         if (A->long_places) {
             // no places are looked at where only a row that repeats columns could be long
             const bool some = A->k > rows.long_row;
@@ -1666,7 +1666,7 @@ int gcoo_spdm_variant(const gcoo_matrix* A, const float* B_dev, int64_t ldb, int
         if (kernel == GCOO_KERNEL_ROWS) {
             const bool lines = ldb % 32 == 0 && reinterpret_cast<uintptr_t>(B_dev) % 128 == 0, reach = (uint64_t)A->k * (uint64_t)ldb * 4u <= gcoo::kRowsMaxBytes;
             const TilePlan& plan = tile_plan(A->m, A->k, A->nnz, N);
-            hipError_t e = reach && plan.preferred[lines] ? gcoo::launch_spdm_rows_tile(rows, plan.row_wgs, plan.whole, s) : gcoo::launch_spdm_rows(rows, s);
+            hipError_t e = reach && plan.preferred[lines] ? gcoo::launch_spdm_rows_tile(rows, plan.row_wgs, plan.whole, s) : gcoo::launch_spdm_rows(rows, !A->from_csr, s);
             return e == hipSuccess ? GCOO_OK : hip_fail(e, "spdm_rows launch");
         }
         gcoo::BandArgs a{A->band_head(), A->band_units(), A->band_first(), A->band_count(), (int32_t)gcoo::band_blocks(A->m, A->L.band.h), A->L.band.h, A->L.band.v,

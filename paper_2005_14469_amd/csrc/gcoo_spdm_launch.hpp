@@ -97,7 +97,6 @@ struct RowsArgs {
     const int32_t* long_rows;  // long_room places for the rows of more than `long_row` entries (RowsOut)
     const int32_t* long_count; // or null: -1 in places without a row
     int32_t long_row, long_room;
-    bool spread;               // the places are taken by rows_turn()
     int32_t moved;             // 31: tiles are moved down to whole lines of C, 0: they are not (set by the launchers)
 };
 // A row of more entries than this is shared by a whole workgroup.
@@ -117,7 +116,8 @@ inline int32_t rows_moved(int64_t m, int64_t nnz, int64_t N, const float* C, int
 }
 // Largest B (k x ldb) whose rows a buffer descriptor reaches with something left above for the entries past the end of a row.
 constexpr uint64_t kRowsMaxBytes = 0xffffefffull;
-hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s);
+// `spread`: long rows in places are taken by rows_turn().
+hipError_t launch_spdm_rows(const RowsArgs& a, bool spread, hipStream_t s);
 
 // The kernel that works row by row on a tile of B in LDS (gcoo_spdm_tile_kernel.hpp), `row_wgs` workgroups per tile of kTileCols columns: N of at least a tile, any alignment of
 // 4 bytes, at most kTileMaxRows rows for a workgroup, tile_lds() at most kTileLdsBytes, k x ldb at most kRowsMaxBytes, at most kTileMaxNnz entries.

@@ -7,7 +7,7 @@ namespace gcoo {
 static int64_t rows_waves(int64_t m, int64_t N) { return m * ((N + 255) / 256); }
 
 template <int LPR, bool WIDE, int AHEAD, int SUMS>
-static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
+static hipError_t launch_rows_ahead(const RowsArgs& args, bool spread_places, hipStream_t s)
 {
     constexpr int64_t waves = kRowsThreads / 64, tile = 4 * LPR, spw = 64 / LPR;
     RowsArgs a = args;
@@ -32,7 +32,7 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
     // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them.
     const int64_t wave_row = rpw < spw ? 8 : (2 * mean > 64 ? 2 * mean : 64);
     const bool places = !a.long_count && a.long_room > 0;
-    const bool spread = places && a.spread && tiles % 8;
+    const bool spread = places && spread_places && tiles % 8;
     const auto kernel = !places ? spdm_rows<LPR, WIDE, AHEAD, SUMS, kLongCounted> : (spread ? spdm_rows<LPR, WIDE, AHEAD, SUMS, kLongSpread> : spdm_rows<LPR, WIDE, AHEAD, SUMS, kLongPlaces>);
     kernel<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw, (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row),
                                                                spread ? rows_turns(row_wgs, tiles) : RowsTurns{});
@@ -44,14 +44,14 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, hipStream_t s)
 // per row, 2 to 9 % from 6 to 16, level from 16 to 30, 2 to 5 % more above, 13 % more for power-law rows of 49).
 // SUMS: of a row in a slot (rows_fma()): as many as there are slots of 16 lanes in one, and two where 16 lanes serve up to 32 columns, for which eight are enough.
 template <int LPR, int SUMS = LPR <= 16 ? 1 : LPR / 16>
-static hipError_t launch_rows(const RowsArgs& a, hipStream_t s)
+static hipError_t launch_rows(const RowsArgs& a, bool spread, hipStream_t s)
 {
     if constexpr (LPR >= 16)
-        if (a.nnz <= 16 * a.m) return launch_rows_ahead<LPR, false, 8, SUMS>(a, s);
-    return launch_rows_ahead<LPR, false, 16, SUMS>(a, s);
+        if (a.nnz <= 16 * a.m) return launch_rows_ahead<LPR, false, 8, SUMS>(a, spread, s);
+    return launch_rows_ahead<LPR, false, 16, SUMS>(a, spread, s);
 }
 
-hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
+hipError_t launch_spdm_rows(const RowsArgs& a, bool spread, hipStream_t s)
 {
     if (a.m < 1 || a.k < 1 || a.N < 1 || a.ldb > 0x3fffffffLL) return hipErrorInvalidValue;
     if (a.N < 4) {
@@ -63,11 +63,11 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         return hipGetLastError();
     }
     // a B of more than 4 GB is beyond the offsets of a buffer descriptor
-    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows_ahead<16, true, 16, 1>(a, s);
+    if ((uint64_t)a.k * (uint64_t)a.ldb * 4u > kRowsMaxBytes) return launch_rows_ahead<16, true, 16, 1>(a, spread, s);
     // Up to 32 columns: four or eight lanes to a row where that leaves enough workgroups, sixteen else, those without a column of their own along (kernel alone, us, 8 lanes and 16:
     // 6124 x 6124, rows of 19, N = 28: 7.4 4.9; 8788 x 9414, of 18, N = 27: 5.6 6.2).
-    if (a.N <= 32 && a.m >= 7000) return a.N <= 16 && a.m >= 16384 ? launch_rows<4>(a, s) : launch_rows<8>(a, s);
-    if (a.N <= 32) return launch_rows<16, 2>(a, s);
+    if (a.N <= 32 && a.m >= 7000) return a.N <= 16 && a.m >= 16384 ? launch_rows<4>(a, spread, s) : launch_rows<8>(a, spread, s);
+    if (a.N <= 32) return launch_rows<16, 2>(a, spread, s);
     // ("As many entries as uneven rows have on average" below: the host knows the mean only, and 25 to 90 entries is that of the power law that was measured, exponent 1.5 with up to 4096 entries, over 2000 to 20000 columns.
     // Uniform rows of such a mean lose by it, up to 30 % between 129 and 400 columns; power-law rows of another exponent or limit have another mean.)
     // 64, 128 or 256 columns per tile.  Wider tiles are fewer requests for the same bytes and, where rows of B begin inside a 128-byte line, fewer lines per byte (3 for
@@ -94,8 +94,8 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
     // 0.93 to 1.05, to 2500 0.97 to 1.02 for N up to 256 and 1.01 to 1.20 beyond, from there on 1.01 to 1.25: 5000 to 8192 rows of B, rows of 10 to 25, N = 224 and 256: 1.22).
     const bool stays = !lines || a.k <= (a.N <= 256 ? 2500 : 1500);
     if (a.N > 64 && waves <= 8192 && full && !sparse_launch && !uneven_rounds && stays && (a.nnz < 25 * a.m || a.m < 1000))
-        return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, s) : launch_rows<32>(a, s);
-    if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, s);
+        return a.N > 128 || (waves < 1000 && a.nnz < 25 * a.m) ? launch_rows<64>(a, spread, s) : launch_rows<32>(a, spread, s);
+    if (a.N >= 1500 && a.nnz <= 3 * a.m && a.m * a.N >= 20000000) return launch_rows<64>(a, spread, s);
     // From 897 columns on there are eight tiles of 128 columns, one per XCD (us, 64 and 128 columns: power-law rows, 3611 x 3611, N = 926: 54 43; 4658 x 4658, N = 994: 64 56; 9046 x 9046, N = 895: 136 138;
     // rows of 89, 3454 x 3454, N = 917: 68 59; but power-law rows, 4830 x 7014, N = 663: 59 71; 8809 x 8809, N = 761: 103 126).
     if (a.N <= 896) {
@@ -105,7 +105,7 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         // power-law rows, 2808 x 3141, N = 131: 17 37; 15071 x 15071, N = 131: 71 78).
         if (!lines && a.N > 128 && !sparse_launch) {
             const int64_t from = a.nnz >= 53 * a.m ? 0 : (a.nnz < 25 * a.m ? 11000 : (a.N <= 150 ? 16000 : INT64_MAX));
-            if (a.N <= 160 ? a.k >= from : (a.N <= 208 && from == 0 && a.k <= 9100)) return launch_rows<64>(a, s);
+            if (a.N <= 160 ? a.k >= from : (a.N <= 208 && from == 0 && a.k <= 9100)) return launch_rows<64>(a, spread, s);
         }
         // one tile in place of two, and up to eight in place of sixteen, but not for rows of as many entries as uneven ones have on average (25 to 64 and 25 to 90; us, 64 and 128 columns:
         // 6133 x 5725, rows of 108, N = 93: 19.7 14.4; 6470 x 6470, of 98, N = 67: 20.8 15.5; over 40 products of rows of 64 and more, N = 65 to 128, up to 6500 rows of B, 13 % less)
@@ -113,17 +113,17 @@ hipError_t launch_spdm_rows(const RowsArgs& a, hipStream_t s)
         // and, for rows of 64 entries and more, wherever tiles of 128 columns are no wider together than those of 64 (up to 6500 rows of B: 0.83 to 0.95 of the time in 28 products of N = 209 to 512; where the last tile
         // would be half empty 0.98 to 1.3 in 40 others; us, 64 and 128 columns: 3218 x 3218, rows of 93, N = 326: 28.4 24.0)
         const bool even = !lines && a.nnz >= 64 * a.m && a.m >= 1000 && a.k < 6500 && (a.N - 1) % 128 >= 64;
-        return one || eight || even || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, s) : launch_rows<16>(a, s);
+        return one || eight || even || (a.N >= 200 && a.nnz <= 3 * a.m) ? launch_rows<32>(a, spread, s) : launch_rows<16>(a, spread, s);
     }
-    if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, s);
+    if (a.N >= 1100 && a.k <= (lines ? 2600 : 3200)) return launch_rows<64>(a, spread, s);
     // Many rows of B: while all of B stays in the memory-side cache (256 MB), tiles of 64 columns, which stay longest in an XCD's L2; beyond, rows of a few entries take theirs from memory either way, and
     // in longer stretches by 128 columns (64 and 128; B inside lines: 12878 x 12878, rows of 6.1, N = 1563: 57 69; 13474 x 13474, of 4.5, N = 3602: 115 127; 10081 x 10081, of 4.4, N = 5285: 109 119; 8667 x 8667, of 6.5,
     // N = 6681: 138 144; but of 1.7 entries, 7706 x 8902, N = 1171: 19.3 16.6; of 4, 9739 x 9739, N = 1024: 19.4 17.8; 14065 x 14065, of 4, N = 6254: 236 212; 9307 x 9307, of 8.2, N = 9307: 320 283; 9531 x 9531, of 9.4: 357 322.  On lines: 13211 x 13211, of 3.8, N = 3584: 74 83; 10176 x 10176, of 4.6,
     // N = 10176: 250 233; 10372 x 12632, of 5.8, N = 10368: 288 273; 14533 x 14533, of 8.2, N = 14528: 576 626).
     const bool cached = a.k * a.N <= 66000000;
     const int64_t few = cached ? (a.N <= 1024 ? (lines ? 4 : 7) : 3) : (lines ? 6 : 10);          // entries per row; up to 1024 columns are eight tiles of 128
-    if (a.k <= (cached ? 8000 : 9000) || a.nnz <= few * a.m) return launch_rows<32>(a, s);
-    return launch_rows<16>(a, s);
+    if (a.k <= (cached ? 8000 : 9000) || a.nnz <= few * a.m) return launch_rows<32>(a, spread, s);
+    return launch_rows<16>(a, spread, s);
 }
 
 }  // namespace gcoo
