@@ -218,7 +218,7 @@ inline size_t order_lds_bytes(const OrderPlan& plan, int words)
 // their order, so that the stores are whole lines.
 // (Index, two radix passes and bitmaps before, take_rows and this now: 8000 x 8000, 10 %: 190 -> 78 us; 0.5 %: 28 -> 17; 4000 x 4000,
 // 5 %: 41 -> 19; power-law rows, 16384 x 16384: 65 -> 40.  The sums over a workgroup by DPP and one barrier each, here and in band_fill_list(), instead of shuffles and up to 16 reads of LDS, conversion and
-// product: 1777 x 2301, 3 %, N = 1117: 33.3 32.9; 4000 x 4000, 5 %: 180.8 179.3; 8000 x 8000, 0.5 %: 298.5 296.2; power-law rows, 16384 x 16384, N = 512: 128.6 127.1.)
+// product: 1777 x 2301, 3 %, N = 1117: 33.3 32.9; 4000 x 4000, 5 %: 180.8 179.3; power-law rows, 16384 x 16384, N = 512: 128.6 127.1.)
 //
 // FUSED (one part per group, no band schedule): there is nothing to know about a group but its rows, so this is the whole conversion, one
 // launch instead of two (256 x 256: 4.2 + 6.4 us before, 6.3 so; order_plan() has more).

@@ -14,20 +14,20 @@
 // scalar cache, a unit of 16 at a time into one of two register banks while the other is multiplied, so no vector instruction
 // moves them.  A multiply-add with a scalar (or DPP) operand or in index mode takes 1.8 ns per SIMD, the other vector
 // instructions too: five of them per single entry, 9 ns, are what bounds dense bands; 10.1 measured in a loop of nothing else.
-// By the counters a SIMD issues a vector instruction every 2.2 ns at 8000 x 8000, 10 %, and every 2.8 at 14000 x 14000, 2 % (15 and 14 of 16 waves resident).
-// Sparser matrices have few entries per (wave, band), 3.4 ns at 4000 x 4000, 2 %: there the bands by themselves weigh.  No bank conflicts anywhere.
+// By the counters a SIMD issues a vector instruction every 2.2 ns at 8000 x 8000, 10 %, and every 2.7 at 14000 x 14000, 2 % (15 and 14 of 16 waves resident).
+// Sparser matrices have few entries per (wave, band), 3.5 ns at 4000 x 4000, 2 %: there the bands by themselves weigh.  No bank conflicts anywhere.
 //
 // The tall cut (V = 2): the same registers and the same LDS hold twice the rows of A and of B, half as wide.  A row of B is fetched for twice as
 // many rows of A, and a launch has half as many bands, each with four times the entries of a wave; an entry costs a multiply-add
 // less than half but the same address, read and index (7.5 ns in a loop of nothing else, where the wide cut takes 10.2 for twice the columns): the unit that reads LDS takes
 // as long for 8 bytes per lane as for 16, and is the bound of dense matrices.  For sparse ones what is fetched and the bands are: 8000 x 8000, 0.5 %: 333 -> 294 us (a vector
-// instruction every 4.2 ns, rows of B and entries from L2 at 9.5 TB/s),
+// instruction every 4.1 ns, rows of B and entries from L2 at 9.7 TB/s),
 // where the same launch without its multiply-adds takes 290, without its requests 240, and with neither requests nor
 // entries 68: a band is a chain of waits (rows of B from L2, LDS, barrier) that fifteen other waves in the same phase do not fill.
 //
 // B: two bands of 80 rows x 1 KB in LDS.  While band b is multiplied, the rows of band b + 1 are requested, five per wave, straight
-// to LDS; their columns come with the band's head, and the address is formed by the scalar unit.  One barrier per band, nothing in
-// flight across it.  Rows of B that are aligned to 4 bytes only are fetched by the same requests of 16 bytes per lane, a line more for each: 8000 x 8000, N = 7999 (us, four requests of
+// to LDS; their columns come with the band's head, and the address is formed by the scalar unit.  One barrier per band, no rows of B
+// in flight across it.  Rows of B that are aligned to 4 bytes only are fetched by the same requests of 16 bytes per lane, a line more for each: 8000 x 8000, N = 7999 (us, four requests of
 // 4 bytes per lane instead, so, and N = 8000): 0.5 % 358 317 288; 2 % 677 646 630; 10 % 2335 2295 2287.
 //
 // When the rows are requested.  A request holds the one address path of the compute unit for 16 clocks, and a wave that finds it taken
@@ -106,7 +106,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
 // Step i of a unit at priority i, so that the waves of a SIMD go through their entries at one pace.  Among waves of one priority a SIMD serves the oldest first: the
 // others had what was left, and the youngest went through the last of its entries alone, one instruction in six clocks (clocks from a barrier to the end of a wave's entries,
 // waves 0 - 3, 4 - 7, 8 - 11 and 12 - 15, 8000 x 8000, 10 %: 9800 11400 14100 16500).  Product alone (us): 8000 x 8000, 10 % 2300 -> 2030,
-// 4000 x 4000, 5 % 198 -> 183, 2 % 111 -> 108; 14000 x 14000, 2 % 3180 -> 2990; 8000 x 8000, 0.5 % 296 -> 286.  Falling with the steps as fast; two priorities in turn 2170 to 2220 for the first.
+// 4000 x 4000, 5 % 198 -> 183, 2 % 111 -> 108; 14000 x 14000, 2 % 3180 -> 2990; 8000 x 8000, 0.5 % 296 -> 286 (a whole step of it, conversion and product in turn, is level: 323).  Falling with the steps as fast; two priorities in turn 2170 to 2220 for the first.
 #define BD_TURN(i) "s_setprio " #i "\n\t"
 #define BD_WAIT(n) "s_waitcnt lgkmcnt(" #n ")\n\t"
 
@@ -186,7 +186,7 @@ __device__ __forceinline__ float band_acc_get(const BandAcc& a, int s)
     BD_READ_T0(m12) BD_READ_T1(m13) BD_READ_T2(m14) BD_READ_T3(m15)                             \
     "s_branch .Lbd_s3_" #X "_%=\n"                                                              \
     /* the end of a band: its last row requests, then the rows of the next band have landed and all waves are done with this one; its second unit is asked for in front of the barrier, whose wait \
-       hides what it can of that (product alone, us, behind it and so: 4000 x 4000, 2 % 92.0 91.0, 5 % 158.7 157.3; 8000 x 8000, 0.5 % 274.4 273.7, 10 % 2023 2012; 14000 x 14000, 2 % 2985 2969) */ \
+       hides what it can of that (product alone, us, behind it and so: 4000 x 4000, 2 % 92.0 91.0, 5 % 158.7 157.3; 8000 x 8000, 0.5 % 274.4 273.7 (about 300 behind a conversion), 10 % 2023 2012; 14000 x 14000, 2 % 2985 2969) */ \
     ".Lbd_end_" #X "_%=:\n\t"                                                                   \
     BD_ASK_END(X)                                                                               \
     "s_sub_u32 s14, %[flip], s14\n\t"                                                           \

@@ -20,8 +20,8 @@
 //
 // Bound, by the counters: 4 x nnz x N bytes have to come from L2 through the vector caches, which take 64 bytes per clock and compute unit (39 TB/s) at
 // the most.  Where the tile of B that an XCD works on stays in its L2 the kernel gets 17 to 23 TB/s of that: 22.7 at 1777 x 2301, 3 %, N = 1117
-// (94 % of the requests hit; the tile kernel is faster there), 17.4 at 12000 x 12000, 0.5 %, N = 64.  Where it does not, what the L2 has to fetch counts as well: power-law rows,
-// 16384 x 16384, N = 512, whose tile of 64 columns is all of an XCD's 4 MB, take 0.31 GB from behind the L2 for a B of 34 MB (19.6 TB/s from L2);
+// (94 % of the requests hit; the tile kernel is faster there), 16.6 to 17.4 at 12000 x 12000, 0.5 %, N = 64.  Where it does not, what the L2 has to fetch counts as well: power-law rows,
+// 16384 x 16384, N = 512, whose tile of 64 columns is all of an XCD's 4 MB, take 0.31 GB from behind the L2 for a B of 34 MB (17.8 TB/s from L2);
 // 12001 x 12001 with 6 entries per row 2.4 GB for a B of 0.58 GB, which with C is 7.0 TB/s between the L2s and memory where a large copy reaches 5.2:
 // there the bound lies behind the L2.  Tiles of 64 columns that fetch 0.76 GB for the aligned rows of 12000 x 12000 take as long as those of 128 that fetch 1.5 (369 and 365 us): memory gives stretches of 256 bytes more slowly.
 // Measured (product alone, before = the register kernel): 12000 x 12000, 0.5 %, N = 64: 83 -> 11.0 us; 2500 x 2500, 1 %, N = 1024: 38 -> 15.2; 256 x 256, 10 %, N = 256: 35 -> 4.1;
@@ -347,7 +347,7 @@ __device__ __forceinline__ void rows_of_wave(const RowsTile<LPR, WIDE, AHEAD, SU
     }
 }
 
-// Item `block`, (tile, wg): rows [wg * kRowsWaves * rpw, ...), `rpw` of them per wave, columns of the tile.  PLACES is a template, since the
+// Item `block`, (tile, wg): rows [wg * kRowsWaves * rpw, ...), `rpw` of them per wave, columns of the tile.  Where the long rows are is a template, since the
 // places in the one kernel cost the other matrices up to 3 % (12000 x 12000, 0.5 %, N = 64: 12.08 and 12.20 us).
 template <int LPR, bool WIDE, int AHEAD, int SUMS, RowsLong LONG>
 __device__ __forceinline__ void rows_item(const RowsArgs& a, uint32_t block, int32_t tiles, int32_t row_wgs, int32_t rpw, int32_t wave_row, const RowsTurns& turns, float (*part)[LPR * 4])

@@ -49,11 +49,11 @@ def test_counts_and_fill(m, k, p, density):
 
 
 @pytest.mark.parametrize("p", [7, 8, 9, 31, 32, 63, 64, 65])
-@pytest.mark.parametrize("k,density", [(511, 1.0), (512, 1.0), (513, 0.6), (1024, 0.5), (1025, 0.02)])
+@pytest.mark.parametrize("k,density", [(511, 1.0), (512, 1.0), (513, 0.6), (1024, 0.5), (1025, 0.02), (4100, 0.02), (4608, 1.0), (5121, 0.6)])
 def test_fill_from_the_masks_of_the_count(p, k, density):
     """8 to 64 rows per group are filled from a bit per element that the count left in its buffer, other heights and a count in the matrix's
     own buffer by reading the matrix again: both against the oracle, rows that are longer than k, columns in fours and one by one, blocks of less than a list, of a
-    whole one (8 x 512 entries) and of many, with and without an entry in the last row of a group."""
+    whole one (8 x 512 entries) and of many, with and without an entry in the last row of a group; up to 4096 columns the bits are those of a group, beyond of a block of columns."""
     print(f"dense fill: k={k} p={p} density={density}", flush=True)
     rng = np.random.default_rng(k + p)
     m = 2 * p + 3
@@ -213,3 +213,36 @@ def test_more_lists_than_a_workgroup_looks_at(long_rows):
         binding.gcoo_spdm(H, B[:, :cols], C_)
         assert torch.equal(C_.double(), A.double() @ B[:, :cols].double()), (cols, kernel)
     assert kernel == binding.KERNEL_BAND
+
+
+@pytest.mark.parametrize("m,k,p,density,long_rows", [(16417, 64, 32, 0.1, 3), (1025, 60, 64, 0.5, 0), (131, 64, 64, 1.0, 0), (130, 300, 64, 0.5, 1), (4200, 700, 8, 0.01, 2), (17000, 199, 32, 0.2, 0), (17000, 200, 32, 0.2, 0)])
+def test_fill_and_order_by_rows_in_launches_of_their_own(m, k, p, density, long_rows):
+    """Without bands: more groups than two to a compute unit with few columns or entries each, and narrow ones that are mostly filled; the last but one beside the last, where one launch does it."""
+    print(f"dense, two launches: {m}x{k} p={p} density={density}", flush=True)
+    rng = np.random.default_rng(m + k + p)
+    Ah = (rng.integers(1, 8, (m, k)) * (rng.random((m, k)) < density)).astype(np.float32)
+    Ah[m // 2:m // 2 + long_rows] = rng.integers(1, 8, (long_rows, k))
+    A = torch.from_numpy(Ah).to(DEV)
+    B = torch.from_numpy(rng.integers(-8, 8, (k, 130)).astype(np.float32)).to(DEV)
+    H = binding.gcoo_from_dense(A, p)
+    e, ref = H.export(), orc.gcoo_from_dense(Ah, p)
+    assert np.array_equal(e["values"], ref.values) and np.array_equal(e["rows"], ref.rows) and np.array_equal(e["cols"], ref.cols)
+    for N in (1, 4, 64, 130):
+        C_ = binding.gcoo_spdm(H, B[:, :N], torch.full((m, N), 7.0, device=DEV))
+        assert torch.equal(C_.double(), A.double() @ B[:, :N].double()), N
+
+
+@pytest.mark.parametrize("m,k,rows", [(600, 700, [0, 1, 2, 3, 4, 5, 6, 7]), (2000, 1800, list(range(0, 2000, 97))), (16384, 600, [5, 6000, 16383]), (1000, 4096, [999])])
+def test_long_rows_of_a_dense_matrix_in_turns(m, k, rows):
+    """Long rows beside each other and far apart, in places that the XCDs of a shared tile take in turns: one to seven tiles of 64 columns, whole eights and more."""
+    print(f"dense, long rows in turns: {m}x{k}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m)
+    share = torch.full((m, 1), 0.001, device=DEV)
+    share[torch.tensor(rows)] = 0.95
+    A = torch.randint(1, 8, (m, k), generator=g, device=DEV, dtype=torch.float32) * (torch.rand((m, k), generator=g, device=DEV) < share)
+    B = torch.randint(-8, 9, (k, 700), generator=g, device=DEV, dtype=torch.float32)
+    H = binding.gcoo_from_dense(A, 32)
+    for N in (4, 16, 33, 64, 100, 150, 200, 300, 420, 512, 700):
+        C_ = binding.gcoo_spdm(H, B[:, :N], torch.full((m, N), 7.0, device=DEV))
+        assert torch.equal(C_.double(), A.double() @ B[:, :N].double()), N
