@@ -70,6 +70,7 @@ struct RowsTurns {
     int32_t piece, whole, rest;      // workgroups of a piece, pieces of as many, workgroups of the one behind them
     uint32_t inverse;                // of `piece`, in units of 2^-32
 };
+constexpr int64_t kRowsTurnsMost = 65535;      // workgroups of a tile up to which the quotient below is exact: its error is less than wg x piece in 2^-32 of one
 inline RowsTurns rows_turns(int64_t row_wgs, int64_t tiles)
 {
     const int64_t rest = tiles % 8 ? tiles % 8 : 8, xcds = (8 + rest - 1) / rest, even = (row_wgs + xcds - 1) / xcds, piece = even > 2 ? even : 2;

@@ -32,7 +32,7 @@ static hipError_t launch_rows_ahead(const RowsArgs& args, bool spread_places, hi
     // Rows well above the mean hold their slot up while the others of the wave have ended: all slots of the wave take them.
     const int64_t wave_row = rpw < spw ? 8 : (2 * mean > 64 ? 2 * mean : 64);
     const bool places = !a.long_count && a.long_room > 0;
-    const bool spread = places && spread_places && tiles % 8;
+    const bool spread = places && spread_places && tiles % 8 && row_wgs <= kRowsTurnsMost;
     const auto kernel = !places ? spdm_rows<LPR, WIDE, AHEAD, SUMS, kLongCounted> : (spread ? spdm_rows<LPR, WIDE, AHEAD, SUMS, kLongSpread> : spdm_rows<LPR, WIDE, AHEAD, SUMS, kLongPlaces>);
     kernel<<<dim3((unsigned)grid), dim3(kRowsThreads), 0, s>>>(a, (int32_t)tiles, (int32_t)row_wgs, (int32_t)rpw, (int32_t)(wave_row > INT32_MAX ? INT32_MAX : wave_row),
                                                                spread ? rows_turns(row_wgs, tiles) : RowsTurns{});

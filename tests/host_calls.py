@@ -346,6 +346,21 @@ def order_lds(host):
             assert held == int(held) and per_group < held <= 3 * (per_group + 1) // 2 + 67 and int(log[0][4]) <= 61 * 1024, (k, per_group, log)
 
 
+# ---- long rows of a dense matrix --------------------------------------------------------------------------
+
+def places_in_turns(host):
+    """The long rows of a dense matrix that one launch converted are dealt to the XCDs that share a tile; not where every XCD has whole tiles; those of a matrix from CSR arrays are in places too, in their order, and those of two launches are counted."""
+    def dense(m, k, nnz, p):
+        h = C.c_void_p()
+        assert host.L.gcoo_from_dense_counted(m, k, nnz, 1 << 20, k, p, 1 << 20, 1 << 30, 1 << 50, None, C.byref(h)) == OK
+        return h
+    for h, N, kind in [(dense(2000, 1800, 20000, 32), 64, 2), (dense(2000, 1800, 20000, 32), 420, 2), (dense(2000, 1800, 20000, 32), 512, 1), (host.matrix(2000, 1800, 20000, 32), 64, 1), (dense(60000, 1024, 61000, 32), 64, 0)]:
+        host.log()
+        assert host.spdm(h, N, N) == OK
+        (name,) = host.launches()
+        assert f"RowsLongE{kind}E" in name, (N, kind, name)
+
+
 # ---- a matrix without columns --------------------------------------------------------------------------
 
 def no_columns(host):

@@ -37,7 +37,7 @@ def test_lists_looked_at_grow_with_the_lists(rules, lists):
 
 
 @pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 7, 9, 12])
-@pytest.mark.parametrize("row_wgs", [1, 2, 3, 7, 8, 9, 40, 63, 64, 65, 1000, 1249])
+@pytest.mark.parametrize("row_wgs", [1, 2, 3, 7, 8, 9, 40, 63, 64, 65, 1000, 1249, 65521, 65535])
 def test_long_rows_are_dealt_to_the_xcds(rules, row_wgs, tiles):
     """Every place has one workgroup of a tile that begins with it, and where two or more XCDs come to a tile one of them begins with no more than three quarters of the first sixteen."""
     rest = tiles % 8
