@@ -51,7 +51,7 @@ def test_ordered_by_masks(m, k, density, p, kind):
 # entries than a thread keeps; rows of more than 512 entries, which have places by group: the first and the last row of a group, all of them, none
 @pytest.mark.parametrize("kind", ["sorted", "twice"])
 @pytest.mark.parametrize("m,k,entries,p,long", [(8192, 300, 30, 32, []), (8193, 300, 30, 32, []), (8193, 300, 75, 32, []), (64, 4096, 70, 32, []), (64, 4096, 72, 32, []),
-                                                (96, 2048, 123, 32, []), (96, 2048, 125, 32, []), (320, 700, 5, 32, [*range(32), 96, 159, 319]),
+                                                (96, 2048, 123, 32, []), (96, 2048, 125, 32, []), (96, 2300, 79, 32, []), (96, 2300, 80, 32, []), (96, 2048, 139, 32, []), (96, 2048, 140, 32, []), (320, 700, 5, 32, [*range(32), 96, 159, 319]),
                                                 (9000, 700, 3, 32, [*range(32), 96, 159, 8999]), (9000, 600, 8, 33, [0, 32, 33, 65, 66]),
                                                 (300, 2000, 20, 64, [63, 64, 127, 299]), (300, 512, 7, 65, [3, 299]), (200, 513, 2, 1, [0, 77, 199])])
 def test_in_one_launch(m, k, entries, p, long, kind):
